@@ -2,7 +2,7 @@
 
 A case names a configuration of workloads.py and the largest sizes m, k, n of the
 goal it is solved under: the lattice then holds every allowed size up to those.  The seed draws the
-target's cost coefficients (and the Specs that are asked for).  Four operations:
+target's cost coefficients (and the Specs that are asked for).  Five operations:
 
   solve     fill and compress every lattice of the configuration into buffers the program keeps
             (binding.solve_lattices); the outputs are the dense tables and the number of boxes
