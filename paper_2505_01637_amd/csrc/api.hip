@@ -51,6 +51,10 @@ constexpr uint32_t kQueryChunk = 4096;
 #define MRL_SECOND_ON_CELLS 1
 #endif
 constexpr bool kSecondOnCells = MRL_SECOND_ON_CELLS;
+constexpr uint64_t kStretch = 8;            // a wave of fill_units_kernel takes at most this many times 64 entries, and
+constexpr uint64_t kFullWaves = 4096;       // more than one only where this many waves are left: its candidates' constants
+                                            // cost a wave as much as two steps do (config 7's fill: stretch 4 and 16384
+                                            // waves 1.17 ms, 4 and 8192 1.04, 8 and 4096 1.00, 16 and 2048 1.04)
 constexpr uint32_t kLookupChunk = 65536;   // points per launch of a lookup in the box lists
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -66,6 +70,7 @@ struct Compiled {
   uint32_t n_shapes;
   uint64_t n_specs;
   std::vector<uint8_t> mk_entry;          // [256][V]
+  std::vector<uint32_t> qdec;             // [Q] the axes of every bound vector, a byte each
   uint32_t max_task;                      // entries of one unit = ncombo * V
   int lay_axis[5], dt_axis[5];            // coordinate axis of the operand's bit, -1 if none
   mrl_target_desc target;
@@ -79,7 +84,7 @@ struct Compiled {
 
 // Offsets of the fixed part of the scratch buffer.
 struct FixedLayout {
-  size_t counters, params, tiles, level_shapes, shape_class, level_off, mk_entry, list_whole, list_slice, list_wide, list_cnt, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
+  size_t counters, params, tiles, level_shapes, shape_class, level_off, mk_entry, qdec, list_whole, list_slice, list_wide, list_cnt, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
       q_idx, q_cost, q_arg, upload_end, end;
   uint32_t n_words;
 };
@@ -111,6 +116,7 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.level_shapes = take(c.level_shapes.size() * 4);
   f.level_off = take(c.level_off.size() * 4);
   f.mk_entry = take(c.mk_entry.size());
+  f.qdec = take(c.qdec.size() * 4);
   f.upload_end = o;
   f.shape_class = take(c.level_shapes.size() * 4);
   f.list_whole = take((size_t)c.n_shapes * 4);
@@ -292,6 +298,13 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
   if ((uint64_t)P.ncombo * P.npass * P.V * P.Q >= (1ull << 32)) return fail(MRL_E_INVAL, "too many entries per shape");
   P.G = P.ncombo * P.npass * P.V * P.Q;
   c.n_specs = (uint64_t)c.n_shapes * P.G;
+  if (c.n_specs < (1ull << 32) && P.nlim) {
+    c.qdec.resize(P.Q);
+    for (uint32_t q = 0; q < P.Q; q++) {
+      c.qdec[q] = 0;
+      for (uint32_t a = 0; a < P.nlim; a++) c.qdec[q] |= (q / P.lim_stride[a] % P.lim_nq[a]) << (8 * a);
+    }
+  }
   if (c.n_specs >= (1ull << 32)) return fail(MRL_E_INVAL, "lattice has %llu specs; the limit is 2^32-1", (unsigned long long)c.n_specs);
 
   // target
@@ -848,6 +861,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   uint32_t* d_list_cnt = (uint32_t*)(base + f.list_cnt);
   uint32_t* d_fitmap = (uint32_t*)(base + f.fitmap);
   P.mk_entry = (const uint8_t*)(base + f.mk_entry);
+  P.qdec = (const uint32_t*)(base + f.qdec);
   if (!c.staging) {
     HIP_TRY(hipHostMalloc((void**)&c.staging, f.upload_end, hipHostMallocDefault));
     memset(c.staging, 0, f.upload_end);
@@ -855,6 +869,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     memcpy(c.staging + f.level_shapes, c.level_shapes.data(), c.level_shapes.size() * 4);
     memcpy(c.staging + f.level_off, c.level_off.data(), c.level_off.size() * 4);
     memcpy(c.staging + f.mk_entry, c.mk_entry.data(), c.mk_entry.size());
+    memcpy(c.staging + f.qdec, c.qdec.data(), c.qdec.size() * 4);
   }
   memcpy(c.staging + f.params, &P, sizeof P);
   AuxLease lease;
@@ -884,22 +899,51 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     // of level assignments, each over Specs that depend only on earlier launches.
     launch_fill_ones(d_fitmap, ((size_t)f.n_words + 2) * 8, st);
     const int gather_mode = P.kind == kKindV ? 1 : P.moves ? 2 : 0;
-    for (uint32_t d = 0; d + 1 < n_lev + P.nranks; d++) {
-      BoundSegs segs;
+    const uint64_t qv = (uint64_t)P.Q * P.V;
+    const bool units = fill_by_units(gather_mode, qv);
+    BoundSegs segs;
+    segs.n = 0; segs.block0[0] = 0; segs.waves_per_unit = segs.lanes_per_wave = 1;
+    auto flush = [&]() {
+      launch_fill_bounded(d_P, gather_mode, units, d_level_shapes, segs, tab->d_cost, tab->d_arg, d_ctr, st);
       segs.n = 0; segs.block0[0] = 0;
-      auto flush = [&]() { launch_fill_bounded(d_P, gather_mode, d_level_shapes, segs, tab->d_cost, tab->d_arg, d_ctr, st); segs.n = 0; segs.block0[0] = 0; };
-      for (uint32_t l = d < P.nranks ? 0 : d - (P.nranks - 1); l < n_lev && l <= d; l++) {
-        const uint32_t r = d - l, ns = c.level_off[l + 1] - c.level_off[l];
-        const uint64_t lanes = (uint64_t)ns * (P.rank_off[r + 1] - P.rank_off[r]) * P.npass * P.Q * P.V;
-        const uint64_t blocks = (lanes + 255) / 256;
-        if (!blocks) continue;
-        if (segs.n == kBoundSegs || segs.block0[segs.n] + blocks >= (1ull << 31)) flush();
-        if (blocks >= (1ull << 31)) return fail(MRL_E_INVAL, "a dependency level of the bounded lattice is too large for one launch");
-        segs.first_shape[segs.n] = c.level_off[l]; segs.n_shapes[segs.n] = ns; segs.rank[segs.n] = r;
-        segs.block0[segs.n + 1] = segs.block0[segs.n] + (uint32_t)blocks;
-        segs.n++;
+    };
+    // one segment: `level_units` = (shape, level assignment, intermediate's level) combinations of it
+    auto add = [&](uint32_t l, uint32_t r, uint64_t level_units) -> int32_t {
+      const uint64_t blocks = units ? (level_units * segs.waves_per_unit + 3) / 4 : (level_units * qv + 255) / 256;
+      if (!blocks) return MRL_OK;
+      if (segs.n == kBoundSegs || segs.block0[segs.n] + blocks >= (1ull << 31)) flush();
+      if (blocks >= (1ull << 31)) return fail(MRL_E_INVAL, "a dependency level of the bounded lattice is too large for one launch");
+      segs.first_shape[segs.n] = c.level_off[l]; segs.n_shapes[segs.n] = c.level_off[l + 1] - c.level_off[l]; segs.rank[segs.n] = r;
+      segs.block0[segs.n + 1] = segs.block0[segs.n] + (uint32_t)blocks;
+      segs.n++;
+      return MRL_OK;
+    };
+    // a wave's stretch: up to kStretch times 64 entries of a unit, fewer while that leaves the chip short of waves
+    auto set_stretch = [&](uint64_t launch_units) {
+      uint64_t stretch = 1;
+      while (stretch < kStretch && launch_units * ((qv + 128 * stretch - 1) / (128 * stretch)) >= kFullWaves) stretch *= 2;
+      segs.lanes_per_wave = (uint32_t)(64 * stretch);
+      segs.waves_per_unit = (uint32_t)((qv + 64 * stretch - 1) / (64 * stretch));
+    };
+    if (gather_mode == 1) {
+      // Move Specs have no Moves: the level assignments of a shape do not depend on each other
+      for (uint32_t l = 0; l < n_lev; l++) {
+        const uint64_t n = (uint64_t)(c.level_off[l + 1] - c.level_off[l]) * P.ncombo;
+        set_stretch(n);
+        rc = add(l, 0, n);
+        if (rc) return rc;
+        flush();
       }
-      flush();
+    } else {
+      for (uint32_t d = 0; d + 1 < n_lev + P.nranks; d++) {
+        const uint32_t l0 = d < P.nranks ? 0 : d - (P.nranks - 1);
+        auto seg_units = [&](uint32_t l) { return (uint64_t)(c.level_off[l + 1] - c.level_off[l]) * (P.rank_off[d - l + 1] - P.rank_off[d - l]) * P.npass; };
+        uint64_t n = 0;
+        for (uint32_t l = l0; l < n_lev && l <= d; l++) n += seg_units(l);
+        set_stretch(n);
+        for (uint32_t l = l0; l < n_lev && l <= d; l++) { rc = add(l, d - l, seg_units(l)); if (rc) return rc; }
+        flush();
+      }
     }
   } else {
   // plan (with the pre-fill; a separate streaming kernel for tables it cannot serve), then the

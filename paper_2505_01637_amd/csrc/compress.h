@@ -24,14 +24,17 @@ void launch_fill_level(const DevParams* P, uint32_t npass, uint32_t G, uint32_t 
 
 // Segments of one launch of the bounded fill: segment i is (dependency level of shapes, rank)
 // = shapes [first_shape, first_shape + n_shapes) of the level-ordered shape list at rank[i], and
-// owns workgroups [block0[i], block0[i + 1]).
+// owns workgroups [block0[i], block0[i + 1]).  Where a wave takes a stretch of one (shape, level
+// assignment) (fill_by_units): lanes_per_wave entries of it, waves_per_unit waves for all of them.
 constexpr uint32_t kBoundSegs = 32;
 struct BoundSegs {
-  uint32_t n;
+  uint32_t n, waves_per_unit, lanes_per_wave;
   uint32_t first_shape[kBoundSegs], n_shapes[kBoundSegs], rank[kBoundSegs], block0[kBoundSegs + 1];
 };
 // mode 0: a lattice with memory bounds; 1: Move Specs; 2: a Matmul whose Moves are Move Specs.
-void launch_fill_bounded(const DevParams* P, int mode, const uint32_t* all_level_shapes, const BoundSegs& segs, uint64_t* cost,
+// qv: entries per level assignment.
+bool fill_by_units(int mode, uint64_t qv);
+void launch_fill_bounded(const DevParams* P, int mode, bool units, const uint32_t* all_level_shapes, const BoundSegs& segs, uint64_t* cost,
                          uint16_t* arg, Counters* ctr, hipStream_t stream);
 void launch_fill_ones(void* p, size_t bytes, hipStream_t stream, bool short_lived = false);
 void launch_zero_words(unsigned long long* p, uint32_t n, hipStream_t st);

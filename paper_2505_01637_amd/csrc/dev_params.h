@@ -80,6 +80,7 @@ struct DevParams {
   uint32_t lim_nq[4];        // extent of bound axis a
   uint32_t lim_stride[4];    // its stride inside the bound vector's index (first axis slowest)
   uint32_t lim_of_level[4];  // bound axis of memory level l, kNoBit if the level is unbounded
+  const uint32_t* qdec;      // device, [Q]: the axes of a bound vector (or abstract vector), a byte each
   // ---- Move Specs (kind kKindV) and the Matmul whose Moves are Move Specs (moves = 1, kind kKindM) ----
   // A Move lattice keeps its four abstract-value axes (contiguousness and aligned flag of source and
   // destination) where a bounded lattice keeps its bounds: nlim = 4, lim_nq = {3, 2, 3, 2}.

@@ -1067,7 +1067,385 @@ __device__ __forceinline__ uint64_t add_or_limit(uint64_t a, uint64_t b) {
   return (a >= kLimit || b >= kLimit || a + b >= kLimit) ? kLimit : a + b;
 }
 
-// MODE 0: memory bounds as coordinates; 1: Move Specs; 2: the Matmul whose Moves are Move Specs.
+// ---- a wave per stretch of one (shape, level assignment)
+// What the candidates of a Spec are (which Moves and tiles exist, their constants, the groups their
+// sub-Specs lie in, the bytes a Move allocates) depends on the shape and the level assignment only;
+// the bound vector (or abstract vector) and the variant pick the entry inside those groups.  So a
+// wave stays on one such unit of Q * V consecutive entries: its lanes first work out one candidate
+// each (UnitMove, UnitTile), then every lane walks the candidates, whose constants it gets as
+// scalars (readlane), and its own share of one is an offset, a read and a comparison.  The
+// candidates come in the order of their ids, so a strictly lower cost is all that has to be tested.
+// With a lane per Spec that decoded its own shape and levels the kernel was bound by those
+// instructions (config 7, 41 M Specs, 413 M candidates: fill 1.84 ms, now 1.00 ms, about half of
+// it instruction issue; config 12's Move table, 16.8 M Specs: 0.84 ms, now 0.36 ms).
+// Needs enough entries per unit to fill a wave (kUnitLanes); narrower units stay with the kernel below.
+constexpr uint32_t kUnitLanes = 32;
+constexpr int kUnitBatch = 8;         // candidates whose reads are in flight together
+
+// A buffer of `bytes` out of a bound q (q = 0: nothing, else 2^(q-1) bytes): the least q that holds
+// it, and how far that q falls when the rest is rounded down to a power of two.  Any larger q falls
+// by one: 2^(q-1) - bytes is then at least half of 2^(q-1), but less than it.
+struct BoundStep { uint32_t qmin, dmin; };
+__device__ __forceinline__ BoundStep bound_step(uint64_t bytes) {
+  const uint32_t lg = bytes <= 1 ? 0u : 64u - (uint32_t)__clzll((long long)(bytes - 1));
+  const uint64_t left = (1ull << lg) - bytes;
+  BoundStep b;
+  b.qmin = lg + 1;
+  b.dmin = b.qmin - (left ? 64u - (uint32_t)__clzll((long long)left) : 0u);
+  return b;
+}
+
+// Section 2.4.3 for one tile of a shape, for every layout at once: 4 bits per layout y at 4 * y,
+// bits 0..1 = the most contiguousness that is left, bits 2 and 3 = the tile's suffix products are
+// whole cache lines for 4- and for 2-byte elements (tile_abstract's `keep` and `lines_ok`).
+__device__ __forceinline__ uint32_t tile_word(const DevParams* __restrict__ P, uint32_t rows, uint32_t cols, uint32_t r2, uint32_t c2) {
+  const uint32_t strip = P->strip ? P->strip : 1u;
+  uint32_t word = 0;
+  for (uint32_t y = 0; y < P->xw; y++)
+#pragma unroll
+    for (uint32_t bf = 0; bf < 2; bf++) {
+      uint32_t keep, line_ok;
+      // (a tensor that is aligned and contiguous in all its dimensions keeps what the tile allows)
+      tile_abstract(y, rows, cols, r2, c2, bf ? 2u : 4u, strip, P->line_bytes, P->line_mask, y >= 2 ? 3u : 2u, 1u, keep, line_ok);
+      word |= keep << (4 * y) | line_ok << (4 * y + 2 + bf);
+    }
+  return word;
+}
+
+// One lane's candidate of the unit.
+struct UnitTile {
+  uint32_t cell, trips, id, word;      // first entry of the child's unit; trip count; rewrite id; Move Specs: tile_word
+};
+struct UnitMove {
+  bool exists;
+  uint32_t delta;                      // the body's unit lies this many entries before this one
+  uint32_t id, b_lo, b_hi;             // coefficient * elements, at most kLimit
+  uint32_t steps;                      // bound_step's qmin of the buffer at 4 (byte 0) and at 2 bytes per element (byte 1); byte 2: bit of the bound in qdec
+  uint32_t stride, fall4, fall2;       // stride of the destination's bound; dmin * stride at 4 and at 2 bytes (all 0, and qmin 0, if unbounded)
+  uint32_t vxor, vclear, need;         // variant of the body = (variant ^ vxor) & ~vclear; lanes with the bit `need` only (0: all)
+  uint32_t half;                       // variant bit that says the moved operand has 2 bytes per element (0: never, ~0: always)
+};
+
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+
+// MODE 0: memory bounds as coordinates; 1: Move Specs (no Moves: all level assignments of a
+// dependency level of shapes in one launch, and the segments' rank is not used).  R: entries per
+// lane and step; two share a candidate's constants where a wave has that many (config 7's fill 1.24 ms
+// with one, 1.19 ms with two).
+template <int MODE, int R>
+__global__ __launch_bounds__(256) void fill_units_kernel(const DevParams* __restrict__ P,
+                                                         const uint32_t* __restrict__ all_level_shapes, const BoundSegs segs,
+                                                         uint64_t* cost, uint16_t* __restrict__ arg,
+                                                         Counters* __restrict__ ctr) {
+  __shared__ uint32_t wave_n[4], wave_adm[4];
+  uint32_t seg = 0;
+  while (seg + 1 < segs.n && blockIdx.x >= segs.block0[seg + 1]) seg++;
+  const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t log2V = P->log2V, V = 1u << log2V, Q = P->Q, npass = P->npass, nops = P->nops, QV = Q << log2V;
+  const uint32_t c0 = MODE == 1 ? 0u : P->rank_off[segs.rank[seg]], ncr = MODE == 1 ? P->ncombo : P->rank_off[segs.rank[seg] + 1] - c0;
+  const uint32_t wv = (blockIdx.x - segs.block0[seg]) * 4u + wave;
+  const uint32_t unit = wv / segs.waves_per_unit, chunk = wv - unit * segs.waves_per_unit;
+  uint32_t n_rw = 0, n_adm = 0, ovf = 0;
+  if (unit < segs.n_shapes[seg] * ncr * npass) {
+    const uint32_t sl = unit / (ncr * npass), rem = unit - sl * ncr * npass;
+    const uint32_t ci = rem / npass, pass = rem - ci * npass;
+    const uint32_t shape = all_level_shapes[segs.first_shape[seg] + sl];
+    Shape S;
+    load_shape(P, shape, S);
+    const uint32_t pack = P->pos_info[c0 + ci] & 0xFFu;
+    uint32_t combo = 0, lv[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      if ((uint32_t)i < nops) { lv[i] = (pack >> P->pack_shift[i]) & 3u; combo += lv[i] * P->lvpow[i]; }
+    const uint32_t row = (combo * npass + pass) * QV;          // the unit's first entry inside the group
+    const uint32_t first_cell = shape * P->G + row;            // (cells of a table fit 32 bits)
+    uint64_t* mine = cost + first_cell;
+
+    // microkernels whose shape predicate holds
+    uint32_t mk_shape = 0;
+    for (uint32_t j = 0; j < P->nmk; j++) mk_shape |= (mk_shape_reps(P, S, j) ? 1u : 0u) << j;
+
+    // the unit's Moves, lane t = ((operand * 3 + destination) * 2 + transposed) * 2 + converted (at most 48)
+    UnitMove mv;
+    mv.exists = false; mv.delta = mv.id = mv.b_lo = mv.b_hi = mv.steps = mv.stride = mv.fall4 = mv.fall2 = mv.vxor = mv.vclear = mv.need = mv.half = 0;
+    bool halves = false;       // some Move's operand may have 2 bytes per element
+    if (MODE == 0) {
+      const uint32_t i = lane / 12u, dst = lane / 4u - 3u * i, xx = (lane >> 1) & 1u, cv = lane & 1u;
+      if (i < nops) {
+        const uint32_t src = i == 0 ? lv[0] : i == 1 ? lv[1] : i == 2 ? lv[2] : lv[3];
+        const bool has_dt = P->dt_bit[i] != kNoBit, has_lay = P->lay_bit[i] != kNoBit;
+        const uint32_t coef = dst < src && (!xx || has_lay) && (!cv || (P->can_convert[i] && has_dt)) ? P->mcoef[i][src][dst][xx] : 0u;
+        if (coef) {
+          const uint64_t numel = i == 0 ? S.numel[0] : i == 1 ? S.numel[1] : i == 2 ? S.numel[2] : S.numel[3];
+          const uint64_t bc = mul_or_limit((uint64_t)coef + (cv ? P->convert : 0u), numel);
+          const uint32_t dtbit = has_dt ? 1u << P->dt_bit[i] : 0u, la = P->lim_of_level[dst];
+          mv.exists = true;
+          mv.delta = (src - dst) * P->lvpow[i] * npass * QV;
+          mv.id = P->move_base + ((i * (P->NL - 1u) + dst) * 2u + xx) * 2u + cv;
+          mv.b_lo = (uint32_t)bc; mv.b_hi = (uint32_t)(bc >> 32);
+          if (la != kNoBit) {
+            const BoundStep s4 = bound_step(numel * 4u), s2 = bound_step(numel * 2u);
+            mv.steps = s4.qmin | s2.qmin << 8 | (8u * la) << 16;
+            mv.stride = P->lim_stride[la]; mv.fall4 = s4.dmin * mv.stride; mv.fall2 = s2.dmin * mv.stride;
+          }
+          mv.vxor = xx ? 1u << P->lay_bit[i] : 0u;
+          mv.vclear = cv ? dtbit : 0u;
+          mv.need = cv ? dtbit : 0u;
+          mv.half = cv ? 0u : has_dt ? dtbit : P->base_bf16[i] ? ~0u : 0u;     // element size after the Move
+        }
+      }
+      halves = __any(mv.half != 0);
+    }
+    const unsigned long long moves = __ballot(mv.exists);
+    const bool variants = log2V != 0;
+
+    // its tiles, one per lane; where there are more than 64, the further ones in rounds
+    uint32_t n_tile = 0;
+#pragma unroll
+    for (int d = 0; d < 4; d++) n_tile += P->tile_dim_ok[d] ? P->tile_off[d][S.si[d] + 1] - P->tile_off[d][S.si[d]] : 0u;
+    UnitTile tl;
+    tl.cell = tl.trips = tl.id = tl.word = 0;
+    auto fetch_tiles = [&](uint32_t t0) {
+      if (t0 + lane < n_tile) {
+        uint32_t first = 0, td = 0, at = 0;
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+          const uint32_t lo = P->tile_off[d][S.si[d]];
+          const uint32_t cnt = P->tile_dim_ok[d] ? P->tile_off[d][S.si[d] + 1] - lo : 0u;
+          if (t0 + lane >= first && t0 + lane < first + cnt) { td = d; at = lo + (t0 + lane - first); }
+          first += cnt;
+        }
+        const TileEntry te = P->tiles[at];
+        const uint32_t sj = td == 0 ? S.si[0] : td == 1 ? S.si[1] : td == 2 ? S.si[2] : S.si[3];
+        tl.cell = (shape - (sj - te.jt) * P->shape_stride[td]) * P->G + row;
+        tl.trips = te.trips;
+        tl.id = P->tile_base + td * P->maxs + te.jt;
+        if (MODE == 1)
+          tl.word = tile_word(P, (uint32_t)S.d[1], (uint32_t)S.d[3], td == 1 ? P->sizes[1][te.jt] : (uint32_t)S.d[1],
+                              td == 3 ? P->sizes[3][te.jt] : (uint32_t)S.d[3]);
+      }
+    };
+    fetch_tiles(0);
+
+    const uint32_t x_end = QV < (chunk + 1) * segs.lanes_per_wave ? QV : (chunk + 1) * segs.lanes_per_wave;
+    for (uint32_t x0 = chunk * segs.lanes_per_wave; x0 < x_end; x0 += 64 * R) {
+      uint32_t x[R], q[R], v[R], qd[R], best_id[R], over = 0;    // over: OR of the high words of all finite candidates
+      uint64_t best[R];
+      bool on[R], live[R];
+      uint32_t y[R][2], bfl[R][2];
+#pragma unroll
+      for (int r = 0; r < R; r++) {
+        on[r] = x0 + 64 * r + lane < x_end;
+        x[r] = on[r] ? x0 + 64 * r + lane : x_end - 1;
+        q[r] = x[r] >> log2V; v[r] = x[r] & (V - 1u);
+        qd[r] = P->qdec[q[r]];                                   // the bound vector's (abstract vector's) axes, a byte each
+        best[r] = kInf; best_id[r] = kNone;
+        live[r] = on[r];
+        if (MODE == 1) {
+#pragma unroll
+          for (int ts = 0; ts < 2; ts++) {
+            y[r][ts] = P->lay_bit[ts] != kNoBit ? (v[r] >> P->lay_bit[ts]) & ((1u << P->lay_w[ts]) - 1u) : 0u;
+            bfl[r][ts] = P->dt_bit[ts] != kNoBit ? (v[r] >> P->dt_bit[ts]) & 1u : P->base_bf16[ts];
+            // no such tensor: a packed layout with a broken strip, more adjacent dimensions than the tensor can have
+            if (P->xw == 4)
+              live[r] = live[r] && layout_fits(y[r][ts], (uint32_t)S.d[3], P->strip) &&
+                        ((qd[r] >> (16 * ts)) & 0xFFu) <= max_contig(y[r][ts], (uint32_t)S.d[3], P->strip);
+          }
+          n_adm += (uint32_t)__popcll(__ballot(live[r]));
+        }
+      }
+
+      for (uint32_t left = mk_shape; left; left &= left - 1) {
+        const uint32_t j = (uint32_t)__ffs((int)left) - 1u;
+        const uint64_t k = mul_or_limit(P->mk_cost[j], mk_shape_reps(P, S, j));
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+          bool ok = live[r] && ((P->mk_entry[(pack << log2V) + v[r]] >> j) & 1u);
+          if (MODE == 1 && P->mk_kind[j] >= 6u) {
+            // vector moves: the inner dimension of both tensors adjacent in memory; the aligned form: both aligned;
+            // a row of whole strips: the strips must be whole vectors
+            ok = ok && (qd[r] & 0xFFu) >= 1u && ((qd[r] >> 16) & 0xFFu) >= 1u;
+            if (P->mk_kind[j] == 7u) ok = ok && ((qd[r] >> 8) & 1u) && ((qd[r] >> 24) & 1u);
+            if (P->xw == 4 && S.d[3] >= P->strip && P->strip % P->mk_lanes[j] != 0) ok = ok && y[r][0] < 2 && y[r][1] < 2;
+          }
+          over |= ok ? (uint32_t)(k >> 32) : 0u;
+          const bool better = ok && k < best[r];
+          best[r] = better ? k : best[r];
+          best_id[r] = better ? j : best_id[r];
+          n_rw += (uint32_t)__popcll(__ballot(ok));
+        }
+      }
+
+      if (MODE == 0) {
+        for (unsigned long long todo = moves; todo;) {
+          uint64_t sub[kUnitBatch][R];
+          bool ok[kUnitBatch][R];
+          unsigned long long left = todo;
+#pragma unroll
+          for (int u = 0; u < kUnitBatch; u++) {
+#pragma unroll
+            for (int r = 0; r < R; r++) { ok[u][r] = false; sub[u][r] = kInf; }
+            if (left) {
+              const uint32_t t = (uint32_t)__builtin_ctzll(left);
+              left &= left - 1;
+              const uint32_t steps = lane_of(mv.steps, t), stride = lane_of(mv.stride, t), fall4 = lane_of(mv.fall4, t);
+              const char* to = (const char*)(mine - lane_of(mv.delta, t));
+#pragma unroll
+              for (int r = 0; r < R; r++) {
+                uint32_t qmin = steps & 0xFFu, fall = fall4;
+                if (halves) {
+                  const uint32_t half = lane_of(mv.half, t), fall2 = lane_of(mv.fall2, t);
+                  const bool h = (v[r] & half) != 0 || half == ~0u;
+                  qmin = h ? (steps >> 8) & 0xFFu : qmin;
+                  fall = h ? fall2 : fall;
+                }
+                const uint32_t qa = (qd[r] >> (steps >> 16)) & 0xFFu;
+                ok[u][r] = live[r] && qa >= qmin;
+                uint32_t at = q[r] - (qa > qmin ? stride : fall);
+                if (variants) {
+                  const uint32_t need = lane_of(mv.need, t);
+                  ok[u][r] = ok[u][r] && (v[r] & need) == need;
+                  at = (at << log2V) + ((v[r] ^ lane_of(mv.vxor, t)) & ~lane_of(mv.vclear, t));
+                }
+                at = ok[u][r] ? at << 3 : 0u;        // the others read any finished entry and drop it
+                sub[u][r] = *(const uint64_t*)(to + at);
+              }
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kUnitBatch; u++) {
+            if (todo) {
+              const uint32_t t = (uint32_t)__builtin_ctzll(todo);
+              todo &= todo - 1;
+              const uint64_t b = (uint64_t)lane_of(mv.b_hi, t) << 32 | lane_of(mv.b_lo, t);
+              const uint32_t id = lane_of(mv.id, t);
+#pragma unroll
+              for (int r = 0; r < R; r++) {
+                const bool fin = ok[u][r] && (uint32_t)(sub[u][r] >> 32) != ~0u;
+                const uint64_t cand = sub[u][r] + b;                // each at most 2^62: no wrap
+                over |= fin ? (uint32_t)(cand >> 32) : 0u;
+                const bool better = fin && cand < best[r];
+                best[r] = better ? cand : best[r];
+                best_id[r] = better ? id : best_id[r];
+                n_rw += (uint32_t)__popcll(__ballot(ok[u][r]));
+              }
+            }
+          }
+        }
+      }
+
+      // tiles: the same entry of a smaller shape's group (a Move Spec's: the entry with what the tile leaves)
+      const uint64_t s_loop = P->s;
+      for (uint32_t t0 = 0; t0 < n_tile; t0 += 64) {
+        if (n_tile > 64) fetch_tiles(t0);
+        const uint32_t n_here = n_tile - t0 < 64u ? n_tile - t0 : 64u;
+        for (uint32_t u0 = 0; u0 < n_here; u0 += kUnitBatch) {
+          uint64_t sub[kUnitBatch][R];
+#pragma unroll
+          for (int u = 0; u < kUnitBatch; u++) {
+#pragma unroll
+            for (int r = 0; r < R; r++) sub[u][r] = kInf;
+            if (u0 + u < n_here) {
+              const char* to = (const char*)(cost + lane_of(tl.cell, u0 + u));
+              const uint32_t word = MODE == 1 ? lane_of(tl.word, u0 + u) : 0u;
+#pragma unroll
+              for (int r = 0; r < R; r++) {
+                uint32_t at = x[r];
+                if (MODE == 1) {
+                  uint32_t qc = 0;
+#pragma unroll
+                  for (int ts = 0; ts < 2; ts++) {
+                    const uint32_t f = word >> (4 * y[r][ts]), keep = f & 3u, lines = (f >> (2 + bfl[r][ts])) & 1u;
+                    const uint32_t contig = (qd[r] >> (16 * ts)) & 0xFFu, aligned = (qd[r] >> (16 * ts + 8)) & 1u;
+                    const uint32_t nd = y[r][ts] >= 2 ? 3u : 2u;
+                    qc += (contig < keep ? contig : keep) * P->lim_stride[2 * ts] + (contig == nd ? aligned & lines : 0u) * P->lim_stride[2 * ts + 1];
+                  }
+                  at = (qc << log2V) + v[r];
+                }
+                sub[u][r] = *(const uint64_t*)(to + (at << 3));
+              }
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kUnitBatch; u++) {
+            if (u0 + u < n_here) {
+              const uint32_t a = lane_of(tl.trips, u0 + u), id = lane_of(tl.id, u0 + u);
+#pragma unroll
+              for (int r = 0; r < R; r++) {
+                const bool fin = live[r] && (uint32_t)(sub[u][r] >> 32) != ~0u;
+                const uint64_t lo = (uint64_t)a * (uint32_t)sub[u][r];
+                const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u][r] >> 32) + (lo >> 32);     // bits 32.. of the product
+                const uint64_t cand = ((hi << 32) | (uint32_t)lo) + s_loop;
+                // (bits from 2^64 up of the product count as well)
+                over |= fin ? (uint32_t)(cand >> 32) | ((uint32_t)(hi >> 32) ? 1u << 30 : 0u) : 0u;
+                const bool better = fin && cand < best[r];
+                best[r] = better ? cand : best[r];
+                best_id[r] = better ? id : best_id[r];
+              }
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; r++) n_rw += n_tile * (uint32_t)__popcll(__ballot(live[r]));
+
+      // bufferize (fused Spec): the Matmul into the intermediate at level `pass`, then the bias-add + ReLU out of it
+      if (MODE == 0 && P->kind == kKindF) {
+        const uint32_t la = P->lim_of_level[pass], NL = P->NL;
+        const BoundStep step = bound_step(S.numel[4] * 4u);
+        const uint32_t zc = pass == 0 ? P->zero[0] : pass == 1 ? P->zero[1] : pass == 2 ? P->zero[2] : P->zero[3];
+        const uint64_t z = mul_or_limit(zc, S.numel[4]);
+        const uint64_t* __restrict__ at_m = P->costM + (uint64_t)((S.si[1] * P->nkM + S.si[2] + P->kM_first) * P->nsz[3] + S.si[3]) * P->GM +
+                                            (uint64_t)((lv[0] * NL + lv[1]) * NL + pass) * Q * P->VM;
+        const uint64_t* __restrict__ at_e = P->costE + (uint64_t)(S.si[1] * P->nszE_n + S.si[3]) * P->GE +
+                                            (uint64_t)((pass * NL + lv[2]) * NL + lv[3]) * Q * P->VE;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+          uint32_t qc = q[r];
+          bool fits = live[r];
+          if (la != kNoBit) {
+            const uint32_t qa = (qd[r] >> (8u * la)) & 0xFFu;
+            fits = fits && qa >= step.qmin;
+            qc = q[r] - (qa > step.qmin ? 1u : step.dmin) * P->lim_stride[la];
+          }
+          const uint32_t y0 = P->lay_bit[0] != kNoBit ? (v[r] >> P->lay_bit[0]) & 1u : 0u;
+          const uint32_t y1 = P->lay_bit[1] != kNoBit ? (v[r] >> P->lay_bit[1]) & 1u : 0u;
+          const uint32_t y3 = P->lay_bit[3] != kNoBit ? (v[r] >> P->lay_bit[3]) & 1u : 0u;
+          const uint32_t vm = (P->layM[0] != kNoBit ? y0 << P->layM[0] : 0u) + (P->layM[1] != kNoBit ? y1 << P->layM[1] : 0u);
+          const uint32_t ve = P->layE[2] != kNoBit ? y3 << P->layE[2] : 0u;
+          const uint64_t cm = fits ? at_m[qc * P->VM + vm] : kInf, ce = fits ? at_e[qc * P->VE + ve] : kInf;
+          if (cm != kInf && ce != kInf) {
+            const uint64_t zm = z + cm, cand = zm + ce;       // each term at most 2^62: no wrap
+            over |= (uint32_t)((z | zm | cand) >> 32);
+            if (cand < best[r]) { best[r] = cand; best_id[r] = P->buf_id; }
+          }
+          n_rw += (uint32_t)__popcll(__ballot(fits));
+        }
+      }
+
+#pragma unroll
+      for (int r = 0; r < R; r++)
+        if (on[r]) {
+          mine[x[r]] = best[r];
+          arg[first_cell + x[r]] = (uint16_t)best_id[r];
+        }
+      ovf |= over >> 30;
+    }
+  }
+  // rewrites evaluated (and Specs that exist): one atomic each per workgroup
+  if (lane == 0) { wave_n[wave] = n_rw; wave_adm[wave] = n_adm; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t n = wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
+    if (n) atomicAdd(&ctr->n_rewrites[blockIdx.x % kCtrSlots], (unsigned long long)n);
+    const uint32_t na = wave_adm[0] + wave_adm[1] + wave_adm[2] + wave_adm[3];
+    if (MODE != 0 && na) atomicAdd(&ctr->n_admissible[blockIdx.x % kCtrSlots], (unsigned long long)na);
+  }
+  if (ovf) atomicOr(&ctr->overflow, 1u);
+}
+
+// A lane per Spec.  MODE 0: memory bounds as coordinates, with fewer than kUnitLanes entries per level
+// assignment; 2: the Matmul whose Moves are Move Specs.
 template <int MODE>
 __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __restrict__ P,
                                                            const uint32_t* __restrict__ all_level_shapes, const BoundSegs segs,
@@ -1112,23 +1490,12 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
     }
     const uint64_t group = (uint64_t)shape * P->G;
     const uint32_t off = ((combo * npass + pass) * Q + q) * V + v;
-    constexpr bool move_specs = MODE == 1, moves = MODE == 2;
+    constexpr bool moves = MODE == 2;
 
     // Where Moves are Specs the lattice is the plain Matmul's: a Spec whose operands do not fit
     // their levels has no implementation and evaluates nothing.
     bool admissible = true;
     const auto layout_of = [&](int i) { return P->lay_bit[i] != kNoBit ? (v >> P->lay_bit[i]) & ((1u << P->lay_w[i]) - 1u) : 0u; };
-    if (move_specs) {
-      // no such tensor: a packed layout with a broken strip, more adjacent dimensions than the tensor can have
-      if (P->xw == 4) {
-#pragma unroll
-        for (int ts = 0; ts < 2; ts++) {
-          const uint32_t y = layout_of(ts);
-          admissible = admissible && layout_fits(y, (uint32_t)S.d[3], P->strip) && qi[2 * ts] <= max_contig(y, (uint32_t)S.d[3], P->strip);
-        }
-      }
-      n_adm = admissible ? 1u : 0u;
-    }
     if (moves) {
       if (P->xw == 4) {
 #pragma unroll
@@ -1157,22 +1524,15 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
       if (!((mm >> j) & 1u)) continue;
       const uint64_t reps = mk_shape_reps(P, S, j);
       if (!reps) continue;
-      if (move_specs && P->mk_kind[j] >= 6u) {
-        // vector moves: the inner dimension of both tensors adjacent in memory; the aligned form: both aligned
-        if (qi[0] < 1u || qi[2] < 1u) continue;
-        if (P->mk_kind[j] == 7u && !(qi[1] && qi[3])) continue;
-        // a row of whole strips: the strips must be whole vectors
-        if (P->xw == 4 && S.d[3] >= P->strip && P->strip % P->mk_lanes[j] != 0 && (layout_of(0) >= 2 || layout_of(1) >= 2)) continue;
-      }
       const uint64_t k = mul_or_limit(P->mk_cost[j], reps);
       if (k >= kLimit) e.ovf = 1; else consider(e, k, j);
       e.n++;
     }
 
-    // Moves (a Move Spec has none)
+    // Moves
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-      if ((uint32_t)i >= nops || move_specs) continue;
+      if ((uint32_t)i >= nops) continue;
       const uint32_t src = lv[i];
       const bool has_dt = P->dt_bit[i] != kNoBit, has_lay = P->lay_bit[i] != kNoBit;
       const uint32_t bf = has_dt ? (v >> P->dt_bit[i]) & 1u : P->base_bf16[i];
@@ -1264,27 +1624,7 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
       for (uint32_t te_i = P->tile_off[d][S.si[d]]; te_i < P->tile_off[d][S.si[d] + 1]; te_i++) {
         const TileEntry te = P->tiles[te_i];
         const uint32_t child = shape - (S.si[d] - te.jt) * P->shape_stride[d];
-        uint32_t off_c = off;
-        if (move_specs) {
-          // Section 2.4.3: what is known of a tile of either tensor.  Cutting the inner dimension
-          // leaves only that dimension adjacent; the tile is aligned only if the tensor was aligned
-          // and contiguous and the tile's rows (and so the tile) are whole cache lines.
-          const uint32_t r2 = d == 1 ? P->sizes[1][te.jt] : (uint32_t)S.d[1], c2 = d == 3 ? P->sizes[3][te.jt] : (uint32_t)S.d[3];
-          const uint32_t strip = P->strip ? P->strip : 1u;
-          uint32_t qc = 0;
-#pragma unroll
-          for (int ts = 0; ts < 2; ts++) {
-            const uint32_t y = layout_of(ts);
-            const uint32_t bf = P->dt_bit[ts] != kNoBit ? (v >> P->dt_bit[ts]) & 1u : P->base_bf16[ts];
-            const uint32_t eb = bf ? 2u : 4u;
-            uint32_t contig2, aligned2;
-            tile_abstract(y, (uint32_t)S.d[1], (uint32_t)S.d[3], r2, c2, eb, strip, P->line_bytes, P->line_mask, qi[2 * ts], qi[2 * ts + 1],
-                          contig2, aligned2);
-            qc += contig2 * P->lim_stride[2 * ts] + aligned2 * P->lim_stride[2 * ts + 1];
-          }
-          off_c = ((combo * npass + pass) * Q + qc) * V + v;
-        }
-        const uint64_t sub = cost[(uint64_t)child * P->G + off_c];
+        const uint64_t sub = cost[(uint64_t)child * P->G + off];
         const bool fin = sub != kInf;
         const uint32_t a = te.trips;
         const uint64_t lo = (uint64_t)a * (uint32_t)sub;
@@ -1353,15 +1693,22 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
   if (e.ovf) atomicOr(&ctr->overflow, e.ovf);
 }
 
-// One diagonal (or a part of it): n_blocks = segs.block0[segs.n].
-void launch_fill_bounded(const DevParams* P, int mode, const uint32_t* all_level_shapes, const BoundSegs& segs, uint64_t* cost,
+// One launch over segs: one diagonal (or a part of it), or for Move Specs one dependency level.
+void launch_fill_bounded(const DevParams* P, int mode, bool units, const uint32_t* all_level_shapes, const BoundSegs& segs, uint64_t* cost,
                          uint16_t* arg, Counters* ctr, hipStream_t stream) {
   if (!segs.n || !segs.block0[segs.n]) return;
   const dim3 grid(segs.block0[segs.n]);
-  if (mode == 1) hipLaunchKernelGGL(fill_bounded_kernel<1>, grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
+  const bool two = segs.lanes_per_wave >= 128;
+  if (mode == 1 && two) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<1, 2>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
+  else if (mode == 1) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<1, 1>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
+  else if (units && two) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<0, 2>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
+  else if (units) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<0, 1>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
   else if (mode == 2) hipLaunchKernelGGL(fill_bounded_kernel<2>, grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
   else hipLaunchKernelGGL(fill_bounded_kernel<0>, grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
 }
+
+// (a lane's offset inside a unit is 32 bits of bytes)
+bool fill_by_units(int mode, uint64_t qv) { return mode == 1 || (mode == 0 && qv >= kUnitLanes && qv < (1ull << 29)); }
 
 void launch_plan(const DevParams* P, uint32_t n_shapes, uint32_t npass, uint32_t G, const uint32_t* level_shapes,
                  const uint32_t* level_off, uint32_t n_levels, uint32_t* shape_class, uint32_t* list_whole,

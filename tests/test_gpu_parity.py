@@ -294,6 +294,23 @@ def test_parity_memory_bounds(case):
     check_compressed_queries(got[label], want[label], 100_000, seed=3)
 
 
+@pytest.mark.parametrize("caps,sizes", [
+    ((1 << 29, W.UNBOUNDED), (1, 2, 3)),         # 31 bounds per level assignment: a lane per Spec
+    ((1 << 30, W.UNBOUNDED), (1, 2, 3)),         # 32: a wave per level assignment, half of its lanes idle
+    ((1 << 61, W.UNBOUNDED), (1, 2, 3, 6)),      # 63: one lane short of a wave
+    ((1 << 62, W.UNBOUNDED), (1, 2, 3, 6)),      # 64: exactly one
+    ((1 << 3, 1 << 11), (1, 2, 4)),              # 65: a second wave with one lane
+    ((1 << 14, 1 << 15), (1, 2, 4, 8)),          # 272
+    ((16, 64), tuple(d for d in range(1, 2521) if 2520 % d == 0)),      # up to 94 tiles per Spec: two rounds of candidates
+])
+def test_parity_units_of_bounds(caps, sizes):
+    """Bounded lattices whose number of bounds per level assignment lies at the edges of a wave."""
+    cfg = two_level_bounded(caps, sizes)
+    if len(sizes) > 8:
+        cfg["lattices"][0][1]["sizes"][3] = [1]
+    compare_config(cfg)
+
+
 @pytest.mark.parametrize("case", ["two-level", "config8-small", "config8"])
 def test_parity_memory_bounds_through_a_pipeline(case):
     """Memory bounds on all three tables of the fused workload (Section 2.4.4: Moves and
