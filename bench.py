@@ -217,12 +217,14 @@ def main():
     n_launch = stats[big]["n_levels_run"]
     has_deps = any(deps for label, _, deps in cfg["lattices"] if label == big)
     kernel_text = ("fill of table %s: plan_kernel, sort_work_kernel, the (INF, NONE) pre-fill (%s), "
-                   "fill_kernel / fill_big_kernel per dependency level"
+                   "fill_kernel per dependency level (bundles of small items, and the wide ones beside them)"
                    % (big, "fill_ones_short_kernel, beside the fills of the tables it reads" if has_deps else "inside plan_kernel"))
-    if big_kind in W.BOUNDED_KINDS + (W.KIND_MOVE, W.KIND_MATMUL_MOVES):
+    if big_kind == W.KIND_MOVE:
+        kernel_text = "fill of table %s: fill_units_kernel, one launch per dependency level" % big
+    elif big_kind in W.BOUNDED_KINDS:
         # one launch per diagonal: dependency level of shapes + rank (sum of the operand levels)
         n_launch += W.n_operands(big_kind) * (cfg["target"]["n_levels"] - 1)
-        kernel_text = "fill of table %s: fill_bounded_kernel, one launch per diagonal of (dependency level, rank)" % big
+        kernel_text = "fill of table %s: fill_units_kernel, one launch per diagonal of (dependency level, rank)" % big
     n_big, adm_big = sizes[big], stats[big]["n_admissible"]
     algo_bytes = method_bytes(n_big, adm_big, fused)
     algo_bytes_per_launch = algo_bytes / n_launch

@@ -84,7 +84,7 @@ struct Compiled {
 
 // Offsets of the fixed part of the scratch buffer.
 struct FixedLayout {
-  size_t counters, params, tiles, level_shapes, shape_class, level_off, mk_entry, qdec, list_whole, list_slice, list_wide, list_cnt, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
+  size_t counters, params, tiles, level_shapes, level_off, mk_entry, qdec, recs, masks, item_tasks, sort_tmp, list_small, bundle_first, list_wide, list_cnt, bind, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
       q_idx, q_cost, q_arg, upload_end, end;
   uint32_t n_words;
 };
@@ -104,6 +104,12 @@ bool second_on_cells(const Compiled& c, uint32_t* a0_out, uint32_t* a1_out) {
   return kSecondOnCells && found == 2 && g.stride[a0] % 64 == 0 && g.stride[a1] % (g.stride[a0] * g.ext[a0]) == 0 && g.ext[a1] <= 64;
 }
 
+// Entries of the table of alloc-binding costs (bind_kernel): read-only and accumulated operands of
+// every size pair of the Move table.
+size_t bind_entries(const Compiled& c) {
+  return 2 * c.sizes[1].size() * c.sizes[3].size() * c.P.bind_d * ((size_t)6 << (2 * c.P.yb));
+}
+
 FixedLayout fixed_layout(const Compiled& c) {
   FixedLayout f;
   size_t o = 0;
@@ -118,11 +124,19 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.mk_entry = take(c.mk_entry.size());
   f.qdec = take(c.qdec.size() * 4);
   f.upload_end = o;
-  f.shape_class = take(c.level_shapes.size() * 4);
-  f.list_whole = take((size_t)c.n_shapes * 4);
-  f.list_slice = take((size_t)c.n_shapes * c.P.npass * 4);
-  f.list_wide = take((size_t)c.n_shapes * c.P.npass * 4);
-  f.list_cnt = take(4 * c.level_off.size() * 4);
+  const size_t n_items = (size_t)c.n_shapes * c.P.npass;
+  f.recs = f.sort_tmp = f.masks = f.item_tasks = f.list_small = f.bundle_first = f.list_wide = f.list_cnt = f.bind = 0;
+  if (!c.P.gather) {
+    f.masks = take(n_items * ((size_t)c.P.nwp << c.P.ndt) * 8);
+    f.item_tasks = take(n_items * 2);
+    f.recs = take(plan_bytes_recs(c.n_shapes));
+    f.sort_tmp = take(plan_bytes_sort(c.level_off.data(), (uint32_t)c.level_off.size() - 1, c.P.npass));
+    f.list_small = take(n_items * 4);
+    f.bundle_first = take((n_items + c.level_off.size()) * 4);
+    f.list_wide = take(n_items * 4);
+    f.list_cnt = take(3 * c.level_off.size() * 4);
+    if (c.P.moves) f.bind = take(bind_entries(c) * 8);
+  }
   f.fitmap = take((size_t)f.n_words * 8 + 16);
   f.maskD = take((size_t)f.n_words * 8);
   f.maskC = take((size_t)f.n_words * 8);
@@ -232,7 +246,10 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
     P.lim_nq[0] = packed ? 4 : 3; P.lim_nq[1] = 2; P.lim_nq[2] = packed ? 4 : 3; P.lim_nq[3] = 2;
   }
   for (uint32_t a = P.nlim; a-- > 0;) { P.lim_stride[a] = P.Q; P.Q *= P.lim_nq[a]; }
-  P.gather = bounded || move_specs || moves ? 1u : 0u;
+  P.gather = bounded || move_specs ? 1u : 0u;
+  P.bind_d = 1;
+  for (uint32_t i = 0; i < 3; i++) if (L->dtype_coord[i] || L->base_dtype_bytes[i] == 2) P.bind_d = 3;
+  P.yb = packed ? 2 : 1;
   P.moves = moves ? 1u : 0u;
   P.chain = chain ? 1u : 0u;
   P.split = split ? 1u : 0u;
@@ -287,7 +304,7 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
   P.V = 1u << (P.nlay + P.ndt);
   P.log2V = P.nlay + P.ndt;
 
-  if (P.V > (P.gather ? 64u : 16u)) return fail(MRL_E_INVAL, "too many layout/dtype bits");
+  if (P.V > (P.gather || P.moves ? 64u : 16u)) return fail(MRL_E_INVAL, "too many layout/dtype bits");
   {
     uint32_t axis = 4 + P.nlv + P.nlim, seen_l = 0, seen_d = 0;
     for (uint32_t i = 0; i < P.nops; i++)
@@ -401,6 +418,7 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
   }
 
   // operand-level combos by rank
+  P.nwp = (P.ncombo + 63) / 64;
   P.nranks = P.nops * (P.NL - 1) + 1;
   {
     std::vector<std::pair<uint32_t, uint32_t>> order;
@@ -422,6 +440,7 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
       uint32_t info = pack;
       for (uint32_t op = 0; op < P.nops; op++) info |= 1u << (8 + 4 * ((combo / P.lvpow[op]) % P.NL) + op);
       P.pos_info[i] = info;
+      P.pos_entry[i] = pack | order[i].first << 8 | combo << 16;
     }
     for (uint32_t r = 0; r < P.nranks; r++) P.pos_info[P.rank_off[r]] |= (r + 1) << 24;     // first position of rank r
   }
@@ -853,15 +872,14 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   P.tiles = (const TileEntry*)(base + f.tiles);
   const uint32_t n_lev = (uint32_t)c.level_off.size() - 1;
   uint32_t* d_level_shapes = (uint32_t*)(base + f.level_shapes);
-  uint32_t* d_shape_class = (uint32_t*)(base + f.shape_class);
   uint32_t* d_level_off = (uint32_t*)(base + f.level_off);
-  uint32_t* d_list_whole = (uint32_t*)(base + f.list_whole);
-  uint32_t* d_list_slice = (uint32_t*)(base + f.list_slice);
-  uint32_t* d_list_wide = (uint32_t*)(base + f.list_wide);
-  uint32_t* d_list_cnt = (uint32_t*)(base + f.list_cnt);
+  const PlanBuffers plan{base + f.recs, (unsigned long long*)(base + f.masks), (uint16_t*)(base + f.item_tasks), base + f.sort_tmp,
+                         (uint32_t*)(base + f.list_small), (uint32_t*)(base + f.bundle_first), (uint32_t*)(base + f.list_wide),
+                         (uint32_t*)(base + f.list_cnt)};
   uint32_t* d_fitmap = (uint32_t*)(base + f.fitmap);
   P.mk_entry = (const uint8_t*)(base + f.mk_entry);
   P.qdec = (const uint32_t*)(base + f.qdec);
+  P.bind = (const uint64_t*)(base + f.bind);
   if (!c.staging) {
     HIP_TRY(hipHostMalloc((void**)&c.staging, f.upload_end, hipHostMallocDefault));
     memset(c.staging, 0, f.upload_end);
@@ -894,11 +912,11 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   const hipEvent_t uploaded = aux->events[ev_used++];
   HIP_TRY(hipEventRecord(uploaded, st));
   if (P.gather) {
-    // Memory bounds as coordinates (and Move Specs, and Matmuls whose Moves are Specs): every Spec is evaluated (no admissibility test, so every cell
+    // Memory bounds as coordinates (and Move Specs): every Spec is evaluated (no admissibility test, so every cell
     // counts as fitting for the compression); one launch per dependency level of shapes and rank
     // of level assignments, each over Specs that depend only on earlier launches.
     launch_fill_ones(d_fitmap, ((size_t)f.n_words + 2) * 8, st);
-    const int gather_mode = P.kind == kKindV ? 1 : P.moves ? 2 : 0;
+    const int gather_mode = P.kind == kKindV ? 1 : 0;
     const uint64_t qv = (uint64_t)P.Q * P.V;
     const bool units = fill_by_units(gather_mode, qv);
     BoundSegs segs;
@@ -956,12 +974,11 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   // the plan kernel also streams (INF, NONE) over the tables when a shape's entries are whole 16-byte pieces
   // (not when the pre-fill runs beside the fill of the tables this lattice reads: see launch_fill_ones)
   const bool fused_prefill = P.G % 8 == 0 && !deps_late;
-  launch_plan(d_P, c.n_shapes, P.npass, P.G, d_level_shapes, d_level_off, n_lev, d_shape_class, d_list_whole, d_list_slice,
-              d_list_wide, d_list_cnt, d_fitmap, d_ctr, fused_prefill ? tab->d_cost : nullptr,
-              fused_prefill ? tab->d_arg : nullptr, st);
-  if (16 + 4 * (size_t)n_lev > kPinnedCounts) return fail(MRL_E_INVAL, "too many dependency levels (%u)", n_lev);
+  launch_plan(d_P, P, c.n_shapes, c.max_task, d_level_shapes, d_level_off, c.level_off.data(), n_lev, plan, d_fitmap, d_ctr,
+              fused_prefill ? tab->d_cost : nullptr, fused_prefill ? tab->d_arg : nullptr, st);
+  if (16 + 3 * (size_t)n_lev > kPinnedCounts) return fail(MRL_E_INVAL, "too many dependency levels (%u)", n_lev);
   const uint32_t* cnt = aux->h_counts + 16;            // pinned: the copy does not go through a staging buffer
-  HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, d_list_cnt, 4 * (size_t)n_lev * 4, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, plan.list_cnt, 3 * (size_t)n_lev * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   hipEvent_t counts_ready = aux->events[ev_used++];
   if (!fused_prefill) {
@@ -986,38 +1003,36 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   }
   HIP_TRY(hipEventRecord(ev[5], st));
   levels_timed = true;
+  if (P.moves) launch_bind(d_P, (uint64_t*)(base + f.bind), (uint32_t)bind_entries(c), st);
   bool wide_started = false;
   hipEvent_t wide_done = nullptr;          // recorded behind the last wide launch that the caller's stream has not waited for yet
   for (uint32_t l = 0; l < n_lev; l++) {
-    const uint32_t first = c.level_off[l];
-    const uint32_t n_small = cnt[l], n_slice = cnt[n_lev + l], n_wide = cnt[2 * n_lev + l], n_bigwhole = cnt[3 * n_lev + l];
-    const uint32_t n_stretch = c.level_off[l + 1] - first;
-    if (n_small + n_bigwhole > n_stretch || n_slice + n_wide > n_stretch * P.npass)
-      return fail(MRL_E_HIP, "internal error: work lists of level %u overflow", l);
-    // The wide items (slices with more tasks than an LDS slice of a wave holds) run on the helper
-    // stream, level after level, without waiting for the other items: a tile of a wide slice
-    // leads to the same slice of a smaller shape, in which at least as much fits, so that one is
-    // wide as well, and wide items read nothing that the others write.  The others read entries
-    // of any kind, so a level's launch on the caller's stream waits for the wide items of all
-    // lower levels.  (With both kinds joined at every level the levels of the fused table took
-    // 1.49 ms, the wide items setting the pace of most of them.)
+    const size_t first = (size_t)c.level_off[l] * P.npass, n_items = (size_t)(c.level_off[l + 1] - c.level_off[l]) * P.npass;
+    const uint32_t n_bundles = cnt[l], n_wide = cnt[n_lev + l];
+    if ((size_t)n_bundles + n_wide > n_items) return fail(MRL_E_HIP, "internal error: work lists of level %u overflow", l);
+    // The wide items (with more tasks than a bundle takes) run on the helper stream, level after
+    // level, without waiting for the other items: a tile of a wide item leads to the same item of a
+    // smaller shape, in which at least as much fits, so that one is wide as well, and wide items
+    // read nothing that the others write.  The others read entries of any kind, so a level's
+    // launch on the caller's stream waits for the wide items of all lower levels.  (With both
+    // kinds joined at every level the levels of the fused table took 1.49 ms, the wide items
+    // setting the pace of most of them.)  Packed layouts exist for some sizes only, so there a
+    // smaller shape may have fewer tasks: both kinds then share the caller's stream.
+    const hipStream_t sw = P.moves ? st : s2;
     if (n_wide) {
-      if (!wide_started) {
+      if (!wide_started && sw != st) {
         HIP_TRY(hipEventRecord(aux->events[ev_used], st));
         HIP_TRY(hipStreamWaitEvent(s2, aux->events[ev_used++], 0));
         wide_started = true;
       }
-      launch_fill_level(d_P, P.npass, P.G, c.max_task, d_list_whole + first, n_stretch, 0, 0,
-                        d_list_slice + (size_t)first * P.npass, 0, d_list_wide + (size_t)first * P.npass, n_wide,
-                        tab->d_cost, tab->d_arg, d_ctr, st, s2);
+      launch_fill_wide(d_P, P, c.max_task, n_wide, plan.list_wide + first, plan, tab->d_cost, tab->d_arg, d_ctr, sw);
     }
-    if (n_small + n_bigwhole + n_slice) {
+    if (n_bundles) {
       if (wide_done) { HIP_TRY(hipStreamWaitEvent(st, wide_done, 0)); wide_done = nullptr; }
-      launch_fill_level(d_P, P.npass, P.G, c.max_task, d_list_whole + first, n_stretch, n_small, n_bigwhole,
-                        d_list_slice + (size_t)first * P.npass, n_slice, d_list_wide + (size_t)first * P.npass, 0,
-                        tab->d_cost, tab->d_arg, d_ctr, st, st);
+      launch_fill_level(d_P, P, c.max_task, n_bundles, plan.list_small + first,
+                        n_bundles == cnt[2 * n_lev + l] ? nullptr : plan.bundle_first + first + l, plan, tab->d_cost, tab->d_arg, d_ctr, st);
     }
-    if (n_wide) {
+    if (n_wide && sw != st) {
       // the next level's other items wait here
       HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
       wide_done = aux->events[ev_used++];

@@ -13,14 +13,28 @@ struct Geo {
   uint32_t ext[16], stride[16];
 };
 
-void launch_plan(const DevParams* P, uint32_t n_shapes, uint32_t npass, uint32_t G, const uint32_t* level_shapes,
-                 const uint32_t* level_off, uint32_t n_levels, uint32_t* shape_class, uint32_t* list_whole,
-                 uint32_t* list_slice, uint32_t* list_wide, uint32_t* list_cnt, uint32_t* fitmap, Counters* ctr,
+// Device buffers of the work lists.
+struct PlanBuffers {
+  void* recs;                              // plan_bytes_recs
+  unsigned long long* masks;
+  uint16_t* item_tasks;
+  void* sort_tmp;                          // plan_bytes_sort
+  uint32_t *list_small, *bundle_first, *list_wide, *list_cnt;      // counts: bundles, wide items, small items per level
+};
+size_t plan_bytes_recs(uint32_t n_shapes);
+size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass);
+// h: the host's copy of *P.  max_task: entries of the largest possible item.
+void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint32_t max_task, const uint32_t* level_shapes,
+                 const uint32_t* level_off, const uint32_t* h_level_off, uint32_t n_levels, const PlanBuffers& B, uint32_t* fitmap, Counters* ctr,
                  void* prefill_cost, void* prefill_arg, hipStream_t stream);
-void launch_fill_level(const DevParams* P, uint32_t npass, uint32_t G, uint32_t max_task, const uint32_t* list_whole,
-                       uint32_t n_stretch, uint32_t n_small, uint32_t n_bigwhole, const uint32_t* list_slice,
-                       uint32_t n_slice, const uint32_t* list_wide, uint32_t n_wide, uint64_t* cost, uint16_t* arg,
-                       Counters* ctr, hipStream_t stream, hipStream_t wide_stream);
+// The costs of the alloc-bindings of a Matmul whose Moves are Move Specs, from its Move table.
+void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream);
+// One dependency level: n bundles of its small items (starts: where each begins in `items`; nullptr:
+// every item by itself), and n wide items.
+void launch_fill_level(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const uint32_t* starts,
+                       const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
+void launch_fill_wide(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const PlanBuffers& B,
+                      uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
 
 // Segments of one launch of the bounded fill: segment i is (dependency level of shapes, rank)
 // = shapes [first_shape, first_shape + n_shapes) of the level-ordered shape list at rank[i], and
@@ -31,7 +45,7 @@ struct BoundSegs {
   uint32_t n, waves_per_unit, lanes_per_wave;
   uint32_t first_shape[kBoundSegs], n_shapes[kBoundSegs], rank[kBoundSegs], block0[kBoundSegs + 1];
 };
-// mode 0: a lattice with memory bounds; 1: Move Specs; 2: a Matmul whose Moves are Move Specs.
+// mode 0: a lattice with memory bounds; 1: Move Specs.
 // qv: entries per level assignment.
 bool fill_by_units(int mode, uint64_t qv);
 void launch_fill_bounded(const DevParams* P, int mode, bool units, const uint32_t* all_level_shapes, const BoundSegs& segs, uint64_t* cost,

@@ -73,6 +73,8 @@ struct DevParams {
   // per rank-major position: pack | (operands resident in level l, one nibble per level) << 8
   // | (r + 1) << 24 at the first position of rank r
   uint32_t pos_info[kMaxCombo];
+  uint32_t pos_entry[kMaxCombo];   // pack | rank << 8 | mixed-radix index << 16
+  uint32_t nwp;              // 64-bit words of an item's mask per value of the dtype bits: ceil(ncombo / 64)
   // ---- memory bounds as coordinates (a Matmul lattice whose Specs carry a bound per level of
   // finite capacity; kind stays kKindM).  Bound index q stands for 0 bytes (q = 0) or 2^(q-1).
   uint32_t bounded;          // 1: G = ncombo * Q * V, entry = (combo * Q + bound vector) * V + variant
@@ -84,8 +86,10 @@ struct DevParams {
   // ---- Move Specs (kind kKindV) and the Matmul whose Moves are Move Specs (moves = 1, kind kKindM) ----
   // A Move lattice keeps its four abstract-value axes (contiguousness and aligned flag of source and
   // destination) where a bounded lattice keeps its bounds: nlim = 4, lim_nq = {3, 2, 3, 2}.
-  uint32_t gather;           // 1: filled by the lane-per-Spec kernel (bounded, Move and moves lattices)
+  uint32_t gather;           // 1: filled by gathers from the table (bounded and Move lattices)
   uint32_t moves;            // 1: a Move costs m(src) + m(dest) + the load / store Move Specs read from costM
+  const uint64_t* bind;      // device: those costs (bind_kernel)
+  uint32_t bind_d, yb;       // data types it distinguishes (1: f32; 3: also bf16, kept and converted), layout bits per tensor
   uint32_t weight[4];        // per-level weight of m(t)
   uint32_t line_bytes;
   uint32_t GV, VV, nszV;     // the Move table: entries per shape, variants, number of column sizes

@@ -5,48 +5,41 @@
 // costs.  Here the table is filled bottom-up: all shapes of one dependency
 // level in one launch, every sub-Spec of another shape already final.
 //
-// Mapping (gfx950, wave64).  One wavefront owns one shape (b,m,k,n): all its
-// level / layout / dtype entries, which is a set closed under Moves, so waves
-// never wait for each other and the wave's writes are one contiguous stretch
-// of the table.  Per shape:
-//   1. lanes decide, per level assignment, which entries fit their levels;
-//      the admissible ones are compacted, ordered by rank (sum of the operand
-//      levels), into a task list in LDS (most entries do not fit);
-//   2. (before the first level, once per table) the whole table is set to
-//      (INF, NONE) by the plan kernel's waves (or a plain streaming kernel), so
-//      this kernel writes the admissible entries only;
-//   3. one lane per task evaluates the tile and bufferize rewrites, whose
+// An item is one shape (b,m,k,n) at one value of the passive level axis (the
+// intermediate's level of a fused Spec; other kinds have one value): a set of
+// entries closed under Moves.  Before the first level a plan kernel decides,
+// for every item and every value of the dtype bits, which level assignments
+// fit their levels (most do not), as one bit mask per item in rank order
+// (rank = sum of the operand levels), and sets the whole table to (INF, NONE),
+// so that the level kernels write admissible entries only; a second kernel
+// puts the items with anything to do into work lists per dependency level:
+// bundles of items (about kBundle tasks together; a task is an admissible
+// entry) and wide items of their own.
+//
+// A workgroup takes a bundle.  Its first lanes take an item each (shape,
+// masks, tile counts, everything that does not depend on the entry), then the
+// admissible entries of all its items are listed in LDS, once by item and once
+// by rank, and
+//   1. one lane per task evaluates the tile and bufferize rewrites, whose
 //      sub-Specs belong to other shapes or tables and are final: a tile
-//      sub-Spec sits at the same offset of a smaller shape's group, so
-//      consecutive lanes read consecutive addresses, several loads in flight
-//      per lane.  The best of them is parked in LDS;
-//   4. rank by rank, one lane per task evaluates the microkernels and the
-//      Moves (sub-Specs of the same shape at a lower rank: read from LDS), in
-//      id order, keeping the first strict minimum (= lowest id among ties),
-//      then takes the parked candidate if strictly lower (its ids are higher).
-//      Results go to LDS (for later ranks) and to the table.
-// Before the first level a plan kernel counts, per shape and per value of the
-// passive level axis (the intermediate's level of a fused Spec: such slices are
-// independent), the entries that fit, and sorts the work into three lists per
-// dependency level: shapes one wave can hold whole, slices one wave can hold,
-// and slices that get a whole workgroup and an LDS slice sized for the largest
-// possible slice.  Shapes in which nothing fits get no work at all.  Nothing is
-// reduced across lanes and no result depends on which wave handles an item:
-// the table is deterministic.
+//      sub-Spec sits at the same offset of a smaller shape's group, several
+//      loads in flight per lane.  The best of them is parked in LDS;
+//   2. rank by rank, a quad of lanes per task evaluates the Moves (sub-Specs
+//      of the same item at a lower rank: read from LDS), an operand per lane;
+//      the quad's first lane adds the microkernels and the parked candidate;
+//   3. the results go to the table, a task per lane.
+// The ranks of a shape are a chain (10 of three operands, 13 of four), and a
+// rank of one item holds only a few tasks; the bundle's items go through it
+// together, which fills the lanes, and share the cost of setting up.
+// Candidates are compared by (cost, id), so ties go to the lowest id whatever
+// the order; nothing is reduced across workgroups: the table is deterministic.
 #include <hip/hip_runtime.h>
-#include <cstdlib>
 #include "compress.h"
 #include "dev_params.h"
 
 namespace mrl {
 
 constexpr int kBatch = 8;              // sub-Spec costs fetched together before they are compared
-constexpr uint32_t kSmallCap = 512;    // entries per shape up to which a shape's whole group is one LDS slice
-constexpr uint32_t kSlicedCap = 256;   // tasks per LDS slice for lattices with more entries per shape
-constexpr uint32_t kWaveCap = 64;      // whole shapes of at most this many tasks count as small
-constexpr uint32_t kBigBlock = 512;    // threads per item that does not fit a wave's slice
-constexpr uint32_t kTileLds = 64;      // tile rewrites of the shape staged in LDS at a time
-constexpr uint32_t kWideBelow = 2048;  // levels with fewer shapes than this get 256 threads per shape
 
 struct Eval {
   uint64_t best;
@@ -93,47 +86,6 @@ __device__ __forceinline__ void load_shape(const DevParams* __restrict__ P, uint
   else { S.numel[0] = m * k; S.numel[1] = k * n; S.numel[2] = n; S.numel[3] = m * n; S.numel[4] = m * n; }
 }
 
-// The uniform fields the per-task code needs, read once per unit so that they stay in scalar
-// registers (a scalar load in the middle of the LDS traffic stalls on the counter they share).
-struct Hot {
-  uint32_t nops, NL, npass, log2V, ndt, move_base;
-  uint32_t pack_shift[4], lay_bit[4], dt_bit[4], can_convert[4], lvpow[4];
-  // the same per-operand fields, one byte per operand (0xFF = no bit), for lanes that pick their
-  // operand by lane index: a shift instead of an indexed read (which would put the struct in scratch)
-  uint32_t lay_bytes, dt_bytes, shift_bytes, cv_bits;
-};
-
-__device__ __forceinline__ Hot load_hot(const DevParams* __restrict__ P) {
-  Hot H;
-  H.nops = P->nops; H.NL = P->NL; H.npass = P->npass; H.log2V = P->log2V; H.ndt = P->ndt; H.move_base = P->move_base;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    H.pack_shift[i] = P->pack_shift[i]; H.lay_bit[i] = P->lay_bit[i]; H.dt_bit[i] = P->dt_bit[i];
-    H.can_convert[i] = P->can_convert[i]; H.lvpow[i] = P->lvpow[i];
-  }
-  H.lay_bytes = H.dt_bytes = H.shift_bytes = H.cv_bits = 0;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    H.lay_bytes |= (H.lay_bit[i] == kNoBit ? 0xFFu : H.lay_bit[i] & 0xFFu) << (8 * i);
-    H.dt_bytes |= (H.dt_bit[i] == kNoBit ? 0xFFu : H.dt_bit[i] & 0xFFu) << (8 * i);
-    H.shift_bytes |= (H.pack_shift[i] & 0xFFu) << (8 * i);
-    H.cv_bits |= (H.can_convert[i] ? 1u : 0u) << i;
-  }
-  return H;
-}
-
-// Table offset (inside the shape's group) of entry (pack, pass, variant).
-__device__ __forceinline__ uint32_t entry_offset(const Hot& H, uint32_t xpack, uint32_t v) {
-  const uint32_t pack = xpack & 0xFFu, pass = xpack >> 8;
-  uint32_t combo = pack;
-  if (H.NL != 4) {
-    combo = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) if ((uint32_t)i < H.nops) combo += ((pack >> H.pack_shift[i]) & 3u) * H.lvpow[i];
-  }
-  return ((combo * H.npass + pass) << H.log2V) + v;
-}
-
 // Shape part of microkernel j's predicate: number of repetitions, 0 if it fails
 // (Section 2, Microkernel Selection; Figure 1 for BroadcastVecMultAdd).  The
 // level/layout/dtype part is tabulated per entry (DevParams::mk_entry).
@@ -157,258 +109,380 @@ __device__ __forceinline__ uint64_t mk_shape_reps(const DevParams* __restrict__ 
   }
 }
 
-// LDS of one unit (a shape, or one passive-level slice of it).  "xpack" = pass<<8 | pack.
-struct UnitLds {
-  uint64_t* bterm;    // [256] Move cost of this shape: [convert][operand][src][dst][transposed]; 0 = no such Move
-  uint64_t* tl_base;  // [kTileLds] tile rewrites of this shape: table offset of the sub-shape's group,
-  uint32_t* tl_trips; // [kTileLds]   trip count,
-  uint32_t* tl_id;    // [kTileLds]   rewrite id
-  uint64_t* t_cost;   // [cap] per task: best tile/bufferize candidate, then the final cost
-  uint32_t* t_spec;   // [cap] xpack | variant<<10 | id<<16
-  uint32_t* c_info;   // [npass*256] by xpack: admissible variants (low 16 bits) | first task << 16
-  uint32_t* r_off;    // [nranks+1] first task of the rank
-  uint32_t* wave_tot; // [16] scan scratch
-  uint32_t* fit;      // [16] see build_fit
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
+
+// ---------------------------------------------------------------- work lists
+// The layouts a shape's tensors can have: operand i's layout field takes values below 1 << width(i)
+// (the packed layouts need whole strips; an operand without a layout coordinate has width 0).
+__device__ __forceinline__ uint32_t layout_width(const DevParams* __restrict__ P, const Shape& S, uint32_t i) {
+  const uint32_t w = P->lay_w[i];
+  if (!P->moves || w < 2) return w;
+  const uint32_t cols = (uint32_t)(i == 0 ? S.d[2] : S.d[3]);
+  return cols % P->strip == 0 ? 2u : 1u;
+}
+
+// What the level kernels need of a shape, worked out once by the plan kernel.
+struct alignas(16) ShapeRec {
+  uint64_t numel[5];             // elements of the operands ([4]: the intermediate)
+  uint32_t shape, si;            // index; the four size indices, a byte each
+  uint32_t n_serial, n_tile;     // tile rewrites: serial loops, with parallel loops
+  uint32_t tile_lo[4], tile_cnt; // first entry of each dimension's list of tiles, their numbers (a byte each)
+  uint32_t mk_var;               // microkernels whose shape predicate holds (bits 0..7); packed layouts: layouts that exist << 8 (see variant_of)
 };
+static_assert(sizeof(ShapeRec) == 80, "read as five 16-byte pieces");
 
-__host__ __device__ inline uint32_t unit_lds_bytes(uint32_t cap, uint32_t npass) {
-  return (2048u + kTileLds * 16u + cap * 12u + npass * 1024u + (kMaxRanks + 2) * 4u + 32u * 4u + 16u + 15u) & ~15u;   // slices stay 16-byte aligned
-}
+// Plan: one wave per kPlanShapes shapes, in the order of the dependency levels.  Its first lanes take
+// a shape each and write its record; then, shape by shape, the lanes are level assignments: which
+// of them fit is written as one mask per item (bit = position in rank order, one plane of nwp words
+// per value of the dtype bits) with the item's number of tasks, and the entries that fit are marked
+// in a bit map in table order (bit = cell; read by the compression pass).
+constexpr uint32_t kPlanShapes = 16;
 
-__device__ __forceinline__ UnitLds carve(unsigned char* w, uint32_t cap, uint32_t npass) {
-  UnitLds L;
-  L.bterm = reinterpret_cast<uint64_t*>(w);
-  L.tl_base = L.bterm + 256;
-  L.t_cost = L.tl_base + kTileLds;
-  L.tl_trips = reinterpret_cast<uint32_t*>(L.t_cost + cap);
-  L.tl_id = L.tl_trips + kTileLds;
-  L.t_spec = L.tl_id + kTileLds;
-  L.c_info = L.t_spec + cap;
-  L.r_off = L.c_info + npass * 256u;
-  L.wave_tot = L.r_off + kMaxRanks + 2;
-  L.fit = L.wave_tot + 16;
-  return L;
-}
-
-// Synchronise the T threads that share a unit: one wave needs no s_barrier.
-template <int T>
-__device__ __forceinline__ void unit_sync() {
-  if (T == 64) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  } else {
-    __syncthreads();
-  }
-}
-
-// fit[dt * 4 + l], bit s: the tensors of subset s (operands 0..3, bit 4 = the fused Spec's
-// intermediate) together fit level l when the dtype bits are dt.  Computed by one wave.
-__device__ __forceinline__ void build_fit(const DevParams* __restrict__ P, const Shape& S, uint32_t* fit) {
-  const uint32_t s = threadIdx.x & 63u;
-  for (uint32_t dt = 0; dt < (1u << P->ndt); dt++) {
-    uint64_t sum = 0;
+__global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, uint32_t n_shapes, const uint32_t* __restrict__ level_shapes,
+                                                   ShapeRec* __restrict__ recs, unsigned long long* __restrict__ masks,
+                                                   uint16_t* __restrict__ item_tasks, uint32_t* __restrict__ fitmap, Counters* __restrict__ ctr,
+                                                   uint4* __restrict__ cost16, uint4* __restrict__ arg16) {
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
+  const uint32_t npass = P->npass, ncombo = P->ncombo, V = P->V, nb = npass * V, ndp = 1u << P->ndt, nwp = P->nwp, nw = ndp * nwp, NL = P->NL, nops = P->nops;
+  const uint32_t first = (blockIdx.x * 4 + wave) * kPlanShapes;
+  if (first >= n_shapes) return;
+  const uint32_t n_here = n_shapes - first < kPlanShapes ? n_shapes - first : kPlanShapes;
+  // ---- a shape per lane ----
+  Shape S;
+  uint32_t shape = 0, var = 0, nvb = 0;
+  unsigned long long lays = 1;                  // bit v: variant v (dtype bits 0) has layouts that exist
+  if (lane < n_here) {
+    shape = level_shapes[first + lane];
+    load_shape(P, shape, S);
+    uint32_t n_serial = 0, n_par = 0, cnts = 0, mk = 0;
+    uint32_t lo[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      if ((uint32_t)i >= P->nops) break;
-      const uint32_t bf = P->dt_bit[i] != kNoBit ? (dt >> P->dt_bit[i]) & 1u : P->base_bf16[i];
-      sum += (s >> i) & 1u ? S.numel[i] * (bf ? 2u : 4u) : 0;
+    for (int d = 0; d < 4; d++) {
+      lo[d] = P->tile_off[d][S.si[d]];
+      const uint32_t c = P->tile_off[d][S.si[d] + 1] - lo[d];
+      cnts |= c << (8 * d);
+      if (P->tile_dim_ok[d]) n_serial += c;
+      if (P->par && d != 2) n_par += c;
     }
-    sum += (s >> 4) & 1u ? S.numel[4] * 4u : 0;
+    for (uint32_t j = 0; j < P->nmk; j++) mk |= (mk_shape_reps(P, S, j) ? 1u : 0u) << j;
+    for (uint32_t i = nops; i-- > 0;) {         // from the lowest layout field up
+      const uint32_t w = layout_width(P, S, i);
+      if (i < 3) var |= w << (2 * i) | nvb << (8 + 4 * i);
+      nvb += w;
+      if (!w) continue;
+      const uint32_t step = 1u << P->lay_bit[i];
+      lays |= lays << step;
+      if (w == 2) lays |= lays << (2 * step);
+    }
+    ShapeRec r;
 #pragma unroll
-    for (int l = 0; l < 4; l++) {
-      const unsigned long long ok = __ballot(s < 32 && sum <= P->cap[l]);
-      if (s == 0) fit[dt * 4 + l] = (uint32_t)ok;
-    }
+    for (int i = 0; i < 5; i++) r.numel[i] = S.numel[i];
+    r.shape = shape; r.si = S.si[0] | S.si[1] << 8 | S.si[2] << 16 | S.si[3] << 24;
+    r.n_serial = n_serial; r.n_tile = n_serial + n_par;
+#pragma unroll
+    for (int d = 0; d < 4; d++) r.tile_lo[d] = lo[d];
+    r.tile_cnt = cnts;
+    r.mk_var = mk | (P->moves ? (var & 0x3Fu) << 8 | (var >> 8 & 7u) << 14 | (var >> 12 & 7u) << 17 | (var >> 16 & 7u) << 20 | nvb << 23 : 0u);
+    const uint4* from = reinterpret_cast<const uint4*>(&r);
+    uint4* to = reinterpret_cast<uint4*>(recs + first + lane);
+#pragma unroll
+    for (int i = 0; i < 5; i++) to[i] = from[i];
   }
-}
-
-// Bit v of the result: variant v of the level assignment `info` (DevParams::pos_info) fits.
-// f = fit[0..3] in registers serves the common case of no dtype bits.
-__device__ __forceinline__ uint32_t admissible_mask(const DevParams* __restrict__ P, const uint32_t* fit,
-                                                    const uint32_t f[4], uint32_t info, uint32_t pass) {
+  // ---- a level assignment per lane ----
+  uint32_t info[4], off0[4];
+#pragma unroll
+  for (int it = 0; it < 4; it++) {
+    info[it] = it * 64 + lane < ncombo ? P->pos_info[it * 64 + lane] : 0u;
+    off0[it] = it * 64 + lane < ncombo ? ((P->pos_entry[it * 64 + lane] >> 16) * npass) << P->log2V : 0u;      // pass 0, variant 0 of this level assignment
+  }
   const bool fused = P->kind == kKindF;
-  if (P->ndt == 0) {
-    uint32_t ok = 1;
+  unsigned long long n_adm = 0;
+  for (uint32_t s = 0; s < n_here; s++) {
+    const uint32_t sh = lane_of(shape, s), vb = lane_of(nvb, s);
+    const unsigned long long lay_s = (unsigned long long)lane_of((uint32_t)(lays >> 32), s) << 32 | lane_of((uint32_t)lays, s);
+    uint64_t numel[5];
 #pragma unroll
-    for (int l = 0; l < 4; l++) {
-      const uint32_t subset = ((info >> (8 + 4 * l)) & 15u) | (fused && pass == (uint32_t)l ? 16u : 0u);
-      ok &= (uint32_t)l < P->NL ? f[l] >> subset : 1u;
+    for (int i = 0; i < 5; i++) numel[i] = (uint64_t)lane_of((uint32_t)(S.numel[i] >> 32), s) << 32 | lane_of((uint32_t)S.numel[i], s);
+    if (cost16) {
+      // (INF, NONE) = all-ones over the shape's whole group: the level kernels overwrite what fits
+      const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
+      const uint32_t nc = P->G >> 1, na = P->G >> 3;       // 16-byte pieces (G is a multiple of 8)
+      uint4* c16 = cost16 + (size_t)sh * nc;
+      uint4* a16 = arg16 + (size_t)sh * na;
+      for (uint32_t i = lane; i < nc; i += 64) c16[i] = ones;
+      for (uint32_t i = lane; i < na; i += 64) a16[i] = ones;
     }
-    return (ok & 1u) ? (1u << P->V) - 1u : 0u;
-  }
-  const uint32_t ndtpat = 1u << P->ndt;
-  uint32_t bits = 0;
-  for (uint32_t dt = 0; dt < ndtpat; dt++) {
-    uint32_t ok = 1;
+    const uint64_t group = (uint64_t)sh * P->G;
+    uint32_t ents[4] = {0, 0, 0, 0};
+    unsigned long long my_word = 0;             // lane pass * nw + word keeps that word
+    unsigned long long bits[4] = {0, 0, 0, 0};
+    for (uint32_t dt = 0; dt < ndp; dt++) {
+      // bit b of fit[l]: the tensors of subset b (operands 0..3, bit 4 = the intermediate) together fit level l
+      uint64_t sum = 0;
 #pragma unroll
-    for (int l = 0; l < 4; l++) {
-      if ((uint32_t)l >= P->NL) break;
-      const uint32_t subset = ((info >> (8 + 4 * l)) & 15u) | (fused && pass == (uint32_t)l ? 16u : 0u);
-      ok &= fit[dt * 4 + l] >> subset;
+      for (int i = 0; i < 4; i++) {
+        if ((uint32_t)i >= nops) break;
+        const uint32_t bf = P->dt_bit[i] != kNoBit ? (dt >> P->dt_bit[i]) & 1u : P->base_bf16[i];
+        sum += (lane >> i) & 1u ? numel[i] << (bf ? 1u : 2u) : 0;
+      }
+      sum += (lane >> 4) & 1u ? numel[4] << 2 : 0;
+      uint32_t fit[4];
+#pragma unroll
+      for (int l = 0; l < 4; l++) fit[l] = (uint32_t)__ballot(sum <= P->cap[l]);
+#pragma unroll
+      for (int it = 0; it < 4; it++) {
+        if ((uint32_t)(it * 64) >= ncombo) break;
+#pragma unroll
+        for (int ps = 0; ps < 4; ps++) {
+          if ((uint32_t)ps >= npass) break;
+          uint32_t ok = it * 64 + lane < ncombo ? 1u : 0u;
+#pragma unroll
+          for (int l = 0; l < 4; l++)
+            if ((uint32_t)l < NL) ok &= fit[l] >> (((info[it] >> (8 + 4 * l)) & 15u) | (fused && ps == l ? 16u : 0u));
+          const unsigned long long bal = __ballot(ok & 1u);
+          if (lane == ps * nw + dt * nwp + it) my_word = bal;
+          ents[ps] += (uint32_t)__popcll(bal);
+          if (ok & 1u) bits[it] |= lay_s << (dt + ps * V);
+        }
+      }
     }
-    bits |= (ok & 1u) << dt;
+#pragma unroll
+    for (int it = 0; it < 4; it++) {
+      if ((uint32_t)(it * 64) >= ncombo) break;
+      if (it * 64 + lane >= ncombo) continue;
+      if (nb == 32 || nb == 64) {
+        // whole words of the map (the group size is a multiple of nb): stored, the map is not zeroed
+        uint32_t* w = fitmap + ((group + off0[it]) >> 5);
+        w[0] = (uint32_t)bits[it];
+        if (nb == 64) w[1] = (uint32_t)(bits[it] >> 32);
+      } else if (bits[it]) {
+        const uint64_t cell0 = group + off0[it];
+        const uint32_t shift = (uint32_t)(cell0 & 31u);
+        uint32_t* w = fitmap + (cell0 >> 5);
+        atomicOr(w, (uint32_t)(bits[it] << shift));
+        if (shift + nb > 32) {
+          atomicOr(w + 1, (uint32_t)(bits[it] >> (32 - shift)));
+          if (shift + nb > 64) atomicOr(w + 2, (uint32_t)(bits[it] >> (64 - shift)));
+        }
+      }
+    }
+    if (lane < npass * nw) masks[(size_t)(first + s) * npass * nw + lane] = my_word;
+    const uint32_t mine = lane == 0 ? ents[0] : lane == 1 ? ents[1] : lane == 2 ? ents[2] : ents[3];
+    if (lane < npass) item_tasks[(size_t)(first + s) * npass + lane] = (uint16_t)(mine << vb);
+    n_adm += (unsigned long long)(ents[0] + ents[1] + ents[2] + ents[3]) << vb;
   }
-  uint32_t mask = 0;
-  for (uint32_t lay = 0; lay < (1u << P->nlay); lay++) mask |= bits << (lay * ndtpat);
-  return mask;
+  if (lane == 0 && n_adm) atomicAdd(&ctr->n_admissible[blockIdx.x % kCtrSlots], n_adm);
 }
 
-// Move cost per (convert, operand, src, dst, transposed) for this shape: coefficient * elements.
-// The coefficients (thread t: entries t, t + T, ... of the 128-entry table, for both conversion
-// planes) and the first tile rewrites are fetched at the start of a unit, long before they are needed.
-template <int T>
-struct Prefetch {
-  static constexpr int kCoef = 256 / T < 1 ? 1 : 256 / T;
-  uint32_t coef[kCoef];
-  TileEntry te;
-  uint32_t td;
-  bool tvalid;
+// Work lists, kSortTile items of one dependency level per workgroup: the level's items in order,
+// those of at most small_max tasks cut into bundles (bundle b = items [bundle_first[b],
+// bundle_first[b + 1]) of the level's stretch of list_small), the others in list_wide.  An item
+// weighs its tasks (at least min_weight, which bounds the items of a bundle); a bundle ends with the
+// item that fills its quota, kBundle tasks on levels with work enough to fill the chip, less on
+// others.  Levels of several tiles: sort_sums_kernel first adds up every tile.
+constexpr uint32_t kSortThreads = 1024, kSortItems = 8, kSortTile = kSortThreads * kSortItems;
+// (sweeps with the final kernels: quotas of 64, 96, 192 and 256 tasks are 0 to 3 % slower on the
+// large lattices, 2048 and 4096 bundles before they grow 3 and 8 % on config 4, 512 the same)
+constexpr uint32_t kBundle = 128;            // tasks per bundle
+constexpr uint32_t kMinBundles = 1024;       // a level is cut into this many bundles before they grow
+
+__device__ __forceinline__ unsigned long long block_scan_1024(unsigned long long v, unsigned long long* sh, unsigned long long& total) {
+  unsigned long long incl = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned long long o = __shfl_up(incl, d, 64);
+    if ((int)(threadIdx.x & 63u) >= d) incl += o;
+  }
+  __syncthreads();
+  if ((threadIdx.x & 63u) == 63) sh[threadIdx.x >> 6] = incl;
+  __syncthreads();
+  unsigned long long excl = incl - v;
+  total = 0;
+  for (uint32_t w = 0; w < kSortThreads / 64; w++) {
+    const unsigned long long x = sh[w];
+    if (w < (threadIdx.x >> 6)) excl += x;
+    total += x;
+  }
+  return excl;
+}
+
+// The level and the tile of it that workgroup `b` has: levels in order, each with its tiles.
+__device__ __forceinline__ void sort_place(const uint32_t* __restrict__ level_off, uint32_t npass, uint32_t b, uint32_t& lv, uint32_t& tile) {
+  lv = 0;
+  tile = b;
+  for (;;) {
+    const uint32_t t = ((level_off[lv + 1] - level_off[lv]) * npass + kSortTile - 1) / kSortTile;
+    if (tile < t) return;
+    tile -= t;
+    lv++;
+  }
+}
+
+// sums[workgroup]: tasks of the tile's small items.
+__global__ __launch_bounds__(kSortThreads) void sort_sums_kernel(const uint32_t* __restrict__ level_off, uint32_t npass, const uint16_t* __restrict__ item_tasks,
+                                                                 uint32_t small_max, uint32_t* __restrict__ sums) {
+  __shared__ unsigned long long sh[kSortThreads / 64];
+  uint32_t lv, tile;
+  sort_place(level_off, npass, blockIdx.x, lv, tile);
+  const uint32_t first = level_off[lv] * npass, n = (level_off[lv + 1] - level_off[lv]) * npass, base = tile * kSortTile;
+  unsigned long long work = 0, total = 0;
+  for (uint32_t i = base + threadIdx.x; i < n && i < base + kSortTile; i += kSortThreads) { const uint32_t t = item_tasks[first + i]; if (t <= small_max) work += t; }
+  block_scan_1024(work, sh, total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = (uint32_t)total;
+}
+
+// part 0: with the quota known, the weights and numbers of the tile (parts[workgroup]); part 1: the
+// lists.  A grid of one tile per level needs part 1 only.
+__global__ __launch_bounds__(kSortThreads) void sort_work_kernel(const uint32_t* __restrict__ level_off, uint32_t n_levels, uint32_t npass,
+                                                                 const uint16_t* __restrict__ item_tasks, uint32_t small_max, uint32_t min_weight,
+                                                                 uint32_t part, const uint32_t* __restrict__ sums, uint4* __restrict__ parts,
+                                                                 uint32_t* __restrict__ list_small, uint32_t* __restrict__ bundle_first,
+                                                                 uint32_t* __restrict__ list_wide, uint32_t* __restrict__ list_cnt) {
+  __shared__ unsigned long long sh[kSortThreads / 64];
+  uint32_t lv, tile;
+  sort_place(level_off, npass, blockIdx.x, lv, tile);
+  const uint32_t first = level_off[lv] * npass, n = (level_off[lv + 1] - level_off[lv]) * npass, base = tile * kSortTile;
+  const uint32_t tiles = (n + kSortTile - 1) / kSortTile, wg0 = blockIdx.x - tile;
+  uint32_t tasks[kSortItems];
+  unsigned long long work = 0, total = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kSortItems; k++) {
+    const uint32_t i = base + threadIdx.x * kSortItems + k;
+    tasks[k] = i < n ? item_tasks[first + i] : 0u;
+    if (tasks[k] <= small_max) work += tasks[k];
+  }
+  if (sums) for (uint32_t t = 0; t < tiles; t++) total += sums[wg0 + t];
+  else block_scan_1024(work, sh, total);
+  uint32_t quota = (uint32_t)(total / kMinBundles);
+  quota = quota < min_weight ? min_weight : quota > kBundle ? kBundle : quota;
+  auto weight = [&](uint32_t t) { return t < min_weight ? min_weight : t > quota ? quota : t; };
+  unsigned long long mine = 0;                      // weight (32 bits) | small items (16) | wide items (16)
+#pragma unroll
+  for (uint32_t k = 0; k < kSortItems; k++) {
+    if (tasks[k] > small_max) mine += 1ull << 48;
+    else if (tasks[k]) mine += 1ull << 32 | weight(tasks[k]);
+  }
+  const unsigned long long excl = block_scan_1024(mine, sh, total);
+  const uint32_t all_w = (uint32_t)total, all_s = (uint32_t)((total >> 32) & 0xFFFFu), all_x = (uint32_t)(total >> 48);
+  if (part == 0) {
+    if (threadIdx.x == 0) parts[blockIdx.x] = make_uint4(all_w, all_s, all_x, 0);
+    return;
+  }
+  uint32_t run_w = 0, run_s = 0, run_x = 0;          // weight and number of the small items, number of the wide ones, of the tiles before
+  if (sums)
+    for (uint32_t t = 0; t < tile; t++) { const uint4 p = parts[wg0 + t]; run_w += p.x; run_s += p.y; run_x += p.z; }
+  uint32_t w = run_w + (uint32_t)excl, s = run_s + (uint32_t)((excl >> 32) & 0xFFFFu), x = run_x + (uint32_t)(excl >> 48);
+  uint32_t* starts = bundle_first + first + lv;
+#pragma unroll
+  for (uint32_t k = 0; k < kSortItems; k++) {
+    const uint32_t item = first + base + threadIdx.x * kSortItems + k;
+    if (tasks[k] > small_max) list_wide[first + x++] = item;
+    else if (tasks[k]) {
+      const uint32_t add = weight(tasks[k]);
+      list_small[first + s++] = item;
+      if ((w + add) / quota != w / quota) starts[(w + add) / quota] = s;       // (weights are at most the quota: no bundle is skipped)
+      w += add;
+    }
+  }
+  if (threadIdx.x == 0) {
+    if (tile == 0) starts[0] = 0;
+    if (tile + 1 == tiles) {
+      const uint32_t bundles = (run_w + all_w + quota - 1) / quota;
+      starts[bundles] = run_s + all_s;
+      list_cnt[lv] = bundles; list_cnt[n_levels + lv] = run_x + all_x; list_cnt[2 * n_levels + lv] = run_s + all_s;
+    }
+  }
+}
+
+// ---------------------------------------------------------------- one dependency level
+// LDS of a workgroup: up to cap tasks of up to ni items, kt tile rewrites per item at a time.
+struct FillGeom {
+  uint32_t cap, ni, kt;
+  uint32_t bt;          // Move-cost entries per item
+  uint32_t isz;         // entries of an item's table of level assignments (dtype bits x pack)
+  uint32_t nlay;        // layout bits; without MOVES a task index is an entry index and these bits
+  uint32_t ns;          // entries at most; entry ns stands for "does not fit" (its tasks cost INF)
 };
 
-// Tile rewrite e0 + thread of this shape (dims in order, sizes ascending).  With parallel loops
-// the same lists of b, m and n follow once more: td = 4 + dim, trips = rounds of `threads` trips.
-template <int T>
-__device__ __forceinline__ void fetch_tile(const DevParams* __restrict__ P, const Shape& S, uint32_t e0, uint32_t n_tile,
-                                           TileEntry& te, uint32_t& td, bool& valid) {
-  const uint32_t tid = T == 64 ? (threadIdx.x & 63u) : threadIdx.x;
-  const uint32_t e = e0 + tid;
-  valid = tid < kTileLds && e < n_tile;
-  td = 0;
-  te.jt = 0; te.trips = 0;
-  if (valid) {
-    uint32_t first = 0, q = 0;
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      const uint32_t lo = P->tile_off[a][S.si[a]];
-      const uint32_t cnt = P->tile_dim_ok[a] ? P->tile_off[a][S.si[a] + 1] - lo : 0u;
-      if (e >= first && e < first + cnt) { td = a; q = lo + (e - first); }
-      first += cnt;
-    }
-    if (P->par) {
-#pragma unroll
-      for (int a = 0; a < 4; a++) {
-        if (a == 2) continue;
-        const uint32_t lo = P->tile_off[a][S.si[a]];
-        const uint32_t cnt = P->tile_off[a][S.si[a] + 1] - lo;
-        if (e >= first && e < first + cnt) { td = 4 + a; q = lo + (e - first); }
-        first += cnt;
-      }
-    }
-    te = P->tiles[q];
-    if (td >= 4) te.trips = (te.trips + P->threads - 1) / P->threads;
-  }
+struct FillLds {
+  uint64_t *t_cost, *bterm, *it_numel, *it_z;
+  unsigned long long* it_mask;
+  uint32_t *tl_cell, *tl_trips, *tl_id, *ent, *rl_ent, *it_base, *it_si, *it_pass, *it_ntile, *it_nserial, *it_first, *it_mk, *it_rowM, *it_rowE, *it_var, *it_lo, *it_cnt, *rcnt;
+  uint16_t *t_arg, *rl_slot, *place, *idx, *tk0, *tslot;
+};
+
+// Carves the workgroup's LDS (w = nullptr: only counts the bytes).
+__host__ __device__ inline uint32_t carve_fill(unsigned char* w, const FillGeom& g, bool moves, FillLds& L) {
+  uint32_t o = 0;
+  auto take = [&](uint32_t bytes) { unsigned char* p = w + o; o += (bytes + 15u) & ~15u; return p; };
+  L.t_cost = (uint64_t*)take((g.cap + (1u << g.nlay)) * 8);
+  L.bterm = (uint64_t*)take(g.ni * g.bt * 8);
+  L.it_numel = (uint64_t*)take(g.ni * 5 * 8);
+  L.it_z = (uint64_t*)take(g.ni * 8);
+  L.it_mask = (unsigned long long*)take(g.ni * 4 * 8);
+  L.tl_cell = (uint32_t*)take(g.ni * g.kt * 4);
+  L.tl_trips = (uint32_t*)take(g.ni * g.kt * 4);
+  L.tl_id = (uint32_t*)take(g.ni * g.kt * 4);
+  L.ent = (uint32_t*)take(g.ns * 4);
+  L.rl_ent = (uint32_t*)take(g.ns * 4);
+  uint32_t* it = (uint32_t*)take((g.ni * 15 + 1) * 4);
+  L.it_base = it; L.it_si = it + g.ni; L.it_pass = it + 2 * g.ni; L.it_ntile = it + 3 * g.ni; L.it_nserial = it + 4 * g.ni;
+  L.it_mk = it + 5 * g.ni; L.it_rowM = it + 6 * g.ni; L.it_rowE = it + 7 * g.ni; L.it_var = it + 8 * g.ni; L.it_cnt = it + 9 * g.ni;
+  L.it_lo = it + 10 * g.ni; L.it_first = it + 14 * g.ni;
+  L.rcnt = (uint32_t*)take((kMaxRanks + 2) * 4);
+  L.t_arg = (uint16_t*)take(g.cap * 2);
+  L.rl_slot = (uint16_t*)take(g.ns * 2);
+  L.place = (uint16_t*)take(g.ns * 2);
+  L.idx = (uint16_t*)take(g.ni * g.isz * 2);
+  L.tk0 = (uint16_t*)take(moves ? (g.ns + 1) * 2 : 0);
+  L.tslot = (uint16_t*)take(moves ? g.cap * 2 : 0);
+  return o;
 }
 
-// Tile rewrites of a shape: the serial loops, and with parallel loops those over b, m, n again.
-__device__ __forceinline__ void count_tiles(const DevParams* __restrict__ P, const Shape& S, uint32_t& n_serial,
-                                            uint32_t& n_tile) {
-  n_serial = 0;
-  uint32_t n_par = 0;
-#pragma unroll
-  for (int d = 0; d < 4; d++) {
-    const uint32_t cnt = P->tile_off[d][S.si[d] + 1] - P->tile_off[d][S.si[d]];
-    if (P->tile_dim_ok[d]) n_serial += cnt;
-    if (P->par && d != 2) n_par += cnt;
-  }
-  n_tile = n_serial + n_par;
-}
+// An entry of the workgroup's list: level assignment, dtype bits, item, rank, mixed-radix index.
+__device__ __forceinline__ uint32_t ent_pack(uint32_t e) { return e & 0xFFu; }
+__device__ __forceinline__ uint32_t ent_dt(uint32_t e) { return (e >> 8) & 3u; }
+__device__ __forceinline__ uint32_t ent_item(uint32_t e) { return (e >> 10) & 63u; }
+__device__ __forceinline__ uint32_t ent_rank(uint32_t e) { return (e >> 16) & 15u; }
+__device__ __forceinline__ uint32_t ent_combo(uint32_t e) { return e >> 20; }
 
-// ... into LDS: table offset of the sub-shape's group, trip count, rewrite id.
-template <int T>
-__device__ __forceinline__ void store_tile(const DevParams* __restrict__ P, const UnitLds& L, const Shape& S, uint32_t shape,
-                                           const TileEntry& te, uint32_t d, bool valid) {
-  const uint32_t tid = T == 64 ? (threadIdx.x & 63u) : threadIdx.x;
-  if (valid) {
-    const uint32_t dd = d & 3u;
-    const uint32_t j = dd == 0 ? S.si[0] : dd == 1 ? S.si[1] : dd == 2 ? S.si[2] : S.si[3];
-    const uint32_t stride = dd == 0 ? P->shape_stride[0] : dd == 1 ? P->shape_stride[1] : dd == 2 ? P->shape_stride[2] : P->shape_stride[3];
-    L.tl_base[tid] = (uint64_t)(shape - (j - te.jt) * stride) * P->G;      // the serial table has the same geometry
-    L.tl_trips[tid] = te.trips;
-    L.tl_id[tid] = (d >= 4 ? P->par_base : P->tile_base) + dd * P->maxs + te.jt;
-  }
-}
-
-template <int T>
-__device__ __forceinline__ void prefetch_unit(const DevParams* __restrict__ P, const Shape& S, uint32_t n_tile, Prefetch<T>& F) {
-  const uint32_t tid = T == 64 ? (threadIdx.x & 63u) : threadIdx.x;
+// Variant of an entry's c-th task.  Without packed layouts c is the layout bits; with them an item
+// lists only the layouts that exist: var holds, per operand, the width of its field (2 bits at 2 * i)
+// and the field's position inside c (3 bits at 8 + 4 * i).
+template <bool MOVES>
+__device__ __forceinline__ uint32_t variant_of(const DevParams* __restrict__ P, uint32_t var, uint32_t c, uint32_t dt) {
+  if (!MOVES) return c << P->ndt | dt;
+  uint32_t v = dt;
 #pragma unroll
-  for (int i = 0; i < Prefetch<T>::kCoef; i++) {
-    const uint32_t e = tid + i * T;
-    F.coef[i] = e < 256 ? (&P->mcoef[0][0][0][0])[e & 127u] : 0u;
+  for (int i = 0; i < 3; i++) {
+    const uint32_t w = (var >> (2 * i)) & 3u;
+    if (w) v |= ((c >> ((var >> (8 + 4 * i)) & 7u)) & ((1u << w) - 1u)) << P->lay_bit[i];
   }
-  fetch_tile<T>(P, S, 0, n_tile, F.te, F.td, F.tvalid);
-}
-
-template <int T>
-__device__ __forceinline__ void build_move_costs(const DevParams* __restrict__ P, const Shape& S, const Prefetch<T>& F,
-                                                 uint64_t* bterm) {
-  const uint32_t tid = T == 64 ? (threadIdx.x & 63u) : threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < Prefetch<T>::kCoef; k++) {
-    const uint32_t e = tid + k * T;
-    if (e < 256) {
-      const uint32_t cv = e >> 7, i = (e >> 5) & 3u, c = F.coef[k];
-      const uint64_t n = i == 0 ? S.numel[0] : i == 1 ? S.numel[1] : i == 2 ? S.numel[2] : S.numel[3];
-      bterm[e] = c ? mul_or_limit((uint64_t)c + (cv ? P->convert : 0u), n) : 0;   // 0 = the Move does not exist
-    }
-  }
-}
-
-// Tile candidates first, first + step, ... < n_here of the ones staged in LDS, for one task: the
-// sub-Spec sits at the same offset `off` inside a smaller shape's group.  trips * sub + s in 96
-// bits; reaching 2^62 = overflow.  Candidates from par_from on are parallel loops: their body is
-// the serial-only Spec (read from the serial table) and their constant is the synchronisation cost.
-__device__ __forceinline__ void task_tiles(const DevParams* __restrict__ P, const UnitLds& L, uint32_t n_here,
-                                           uint32_t par_from, uint32_t first, uint32_t step, uint32_t off,
-                                           const uint64_t* __restrict__ cost, Eval& e) {
-  const uint64_t s_serial = P->s, s_par = P->sync;
-  const uint64_t* __restrict__ serial = P->costM;
-  for (uint32_t t0 = first; t0 < n_here; t0 += kBatch * step) {
-    uint64_t sub[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; u++) {
-      const uint32_t t = t0 + u * step;
-      sub[u] = kInf;
-      if (t < n_here) sub[u] = (t >= par_from ? serial : cost)[L.tl_base[t] + off];     // no request for a candidate that is not there
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; u++) {
-      const uint32_t t = t0 + u * step;
-      if (t < n_here) {
-        const bool fin = sub[u] != kInf;
-        const uint32_t a = L.tl_trips[t];
-        const uint64_t lo = (uint64_t)a * (uint32_t)sub[u];
-        const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);   // bits 32.. of the product
-        const uint64_t c = ((hi << 32) | (uint32_t)lo) + (t >= par_from ? s_par : s_serial);
-        const bool over = fin & (((hi >> 30) != 0) | (c >= kLimit));
-        e.ovf |= over ? 1u : 0u;
-        consider(e, c, L.tl_id[t], fin & !over);
-      }
-    }
-  }
+  return v;
 }
 
 // bufferize (FUSED): Matmul into the intermediate, then bias-add+ReLU out of it.  The composition
 // of two Matmuls (Section 2.1): the first, (m, k, p), into the intermediate, then the second,
 // (m, p, n), out of it; both are entries of the same Matmul table.  The bias-add + ReLU with its
-// own bufferize: per level l in which the intermediate fits next to the operands that live there
-// (fit: build_fit's words), the bias add into it plus the ReLU out of it.
+// own bufferize: per level l in which the intermediate fits next to the operands that live there,
+// the bias add into it plus the ReLU out of it.  rowM, rowE: the shape's first entries in the two
+// tables; z: cost of initialising the intermediate; numel: the item's element counts.
 // Returns the number of candidates evaluated.
-__device__ __forceinline__ uint32_t task_bufferize(const DevParams* __restrict__ P, const Shape& S, uint32_t shape,
-                                                   uint32_t xpack, uint32_t v, const uint32_t* fit, Eval& e) {
-  const uint32_t NL = P->NL, pack = xpack & 0xFFu, pass = xpack >> 8;
+__device__ __forceinline__ uint32_t task_bufferize(const DevParams* __restrict__ P, uint32_t rowM, uint32_t rowE, uint64_t z,
+                                                   const uint64_t* numel, uint32_t pack, uint32_t pass, uint32_t v, Eval& e) {
+  const uint32_t NL = P->NL;
+  const auto level = [&](int i) { return (pack >> P->pack_shift[i]) & 3u; };
+  const auto lay = [&](int i) { return P->lay_bit[i] != kNoBit ? (v >> P->lay_bit[i]) & 1u : 0u; };
+  const auto at = [](uint32_t y, uint32_t bit) { return bit != kNoBit ? y << bit : 0u; };
   if (P->split) {
-    const uint32_t l0 = (pack >> P->pack_shift[0]) & 3u, l1 = (pack >> P->pack_shift[1]) & 3u, l2 = (pack >> P->pack_shift[2]) & 3u;
-    const uint32_t y0 = P->lay_bit[0] != kNoBit ? (v >> P->lay_bit[0]) & 1u : 0u;
-    const uint32_t y2 = P->lay_bit[2] != kNoBit ? (v >> P->lay_bit[2]) & 1u : 0u;
-    const uint64_t sh = (uint64_t)(S.si[1] * P->nsz[3] + S.si[3]);
-    const uint32_t va = P->layM[0] != kNoBit ? y0 << P->layM[0] : 0u, vr = P->layE[1] != kNoBit ? y2 << P->layE[1] : 0u;
+    const uint32_t l0 = level(0), l1 = level(1), l2 = level(2);
+    const uint32_t va = at(lay(0), P->layM[0]), vr = at(lay(2), P->layE[1]);
     uint32_t cnt = 0;
     for (uint32_t l = 0; l < NL; l++) {
-      const uint32_t subset = (l0 == l ? 1u : 0u) | (l1 == l ? 2u : 0u) | (l2 == l ? 4u : 0u) | 16u;
-      if (!((fit[l] >> subset) & 1u)) continue;
-      const uint64_t ca = P->costM[sh * P->GM + ((l0 * NL + l1) * NL + l) * P->VM + va];
-      const uint64_t cr = P->costE[sh * P->GE + (l * NL + l2) * P->VE + vr];
+      const uint64_t bytes = 4u * (numel[2] + (l0 == l ? numel[0] : 0u) + (l1 == l ? numel[1] : 0u) + (l2 == l ? numel[2] : 0u));
+      if (bytes > P->cap[l]) continue;
+      const uint64_t ca = P->costM[rowM + ((l0 * NL + l1) * NL + l) * P->VM + va];
+      const uint64_t cr = P->costE[rowE + (l * NL + l2) * P->VE + vr];
       if (ca != kInf && cr != kInf) {
         if (ca + cr >= kLimit) e.ovf = 1; else consider(e, ca + cr, P->buf_id + l);     // each below 2^62: no wrap
       }
@@ -416,101 +490,16 @@ __device__ __forceinline__ uint32_t task_bufferize(const DevParams* __restrict__
     }
     return cnt;
   }
-  const uint32_t l0 = (pack >> P->pack_shift[0]) & 3u, l1 = (pack >> P->pack_shift[1]) & 3u;
-  const uint32_t l2 = (pack >> P->pack_shift[2]) & 3u, l3 = (pack >> P->pack_shift[3]) & 3u;
-  const uint32_t y0 = P->lay_bit[0] != kNoBit ? (v >> P->lay_bit[0]) & 1u : 0u;
-  const uint32_t y1 = P->lay_bit[1] != kNoBit ? (v >> P->lay_bit[1]) & 1u : 0u;
-  const uint32_t y3 = P->lay_bit[3] != kNoBit ? (v >> P->lay_bit[3]) & 1u : 0u;
-  const uint32_t zc = pass == 0 ? P->zero[0] : pass == 1 ? P->zero[1] : pass == 2 ? P->zero[2] : P->zero[3];
-  if (P->chain) {
-    const uint32_t y2 = P->lay_bit[2] != kNoBit ? (v >> P->lay_bit[2]) & 1u : 0u;
-    const uint32_t x1 = ((l0 * NL + l1) * NL + pass) * P->VM +
-                        (P->layM[0] != kNoBit ? y0 << P->layM[0] : 0u) + (P->layM[1] != kNoBit ? y1 << P->layM[1] : 0u);
-    const uint32_t x2 = ((pass * NL + l2) * NL + l3) * P->VM +
-                        (P->layM[1] != kNoBit ? y2 << P->layM[1] : 0u) + (P->layM[2] != kNoBit ? y3 << P->layM[2] : 0u);
-    // the table's k and n lists are this lattice's p list (and k and n lists)
-    const uint64_t c1 = P->costM[(uint64_t)((S.si[1] * P->nkM + S.si[2]) * P->nsz[3] + S.si[0]) * P->GM + x1];
-    const uint64_t c2 = P->costM[(uint64_t)((S.si[1] * P->nkM + S.si[0]) * P->nsz[3] + S.si[3]) * P->GM + x2];
-    if (c1 != kInf && c2 != kInf) {
-      const uint64_t z = mul_or_limit(zc, S.numel[4]);
-      const uint64_t sum = z + c1;          // each term <= 2^62: no wrap
-      if (z >= kLimit || sum >= kLimit || sum + c2 >= kLimit) e.ovf = 1; else consider(e, sum + c2, P->buf_id);
-    }
-    return 1;
-  }
-  const uint32_t xm = ((l0 * NL + l1) * NL + pass) * P->VM +
-                      (P->layM[0] != kNoBit ? y0 << P->layM[0] : 0u) + (P->layM[1] != kNoBit ? y1 << P->layM[1] : 0u);
-  const uint32_t xe = ((pass * NL + l2) * NL + l3) * P->VE + (P->layE[2] != kNoBit ? y3 << P->layE[2] : 0u);
-  const uint64_t cm = P->costM[(uint64_t)((S.si[1] * P->nkM + S.si[2] + P->kM_first) * P->nsz[3] + S.si[3]) * P->GM + xm];
-  const uint64_t ce = P->costE[(uint64_t)(S.si[1] * P->nszE_n + S.si[3]) * P->GE + xe];
+  const uint32_t l0 = level(0), l1 = level(1), l2 = level(2), l3 = level(3);
+  const uint32_t xm = ((l0 * NL + l1) * NL + pass) * P->VM + at(lay(0), P->layM[0]) + at(lay(1), P->layM[1]);
+  const uint32_t xe = P->chain ? ((pass * NL + l2) * NL + l3) * P->VM + at(lay(2), P->layM[1]) + at(lay(3), P->layM[2])
+                               : ((pass * NL + l2) * NL + l3) * P->VE + at(lay(3), P->layE[2]);
+  const uint64_t cm = P->costM[rowM + xm], ce = (P->chain ? P->costM : P->costE)[rowE + xe];
   if (cm != kInf && ce != kInf) {
-    const uint64_t z = mul_or_limit(zc, S.numel[4]);
     const uint64_t sum = z + cm;          // each term <= 2^62: no wrap
     if (z >= kLimit || sum >= kLimit || sum + ce >= kLimit) e.ovf = 1; else consider(e, sum + ce, P->buf_id);
   }
   return 1;
-}
-
-// The rank loop gives every task a quad of lanes, one per operand: lane `op` of the quad
-// evaluates the Moves of operand `op` (to every lower level, same or transposed layout, with or
-// without conversion), then the quad's candidates are reduced to the lexicographic minimum of
-// (cost, id).  Most ranks of most shapes hold fewer than 16 tasks, so this divides the
-// instructions a rank costs (what a small shape's fill is bound by) by about three.
-struct MyOperand {
-  bool exists;                 // op < number of operands
-  bool has_x, can_cv;
-  uint32_t sh, xbit, dtbit;    // level field inside the pack; layout / dtype bit of the variant index
-  uint32_t id0, brow;          // first Move id of this operand; its row of the Move-cost table
-};
-
-__device__ __forceinline__ MyOperand my_operand(const Hot& H, uint32_t op) {
-  MyOperand M;
-  M.exists = op < H.nops;
-  const uint32_t lay = (H.lay_bytes >> (8u * op)) & 0xFFu;
-  const uint32_t dt = (H.dt_bytes >> (8u * op)) & 0xFFu;
-  M.sh = (H.shift_bytes >> (8u * op)) & 0xFFu;
-  M.can_cv = ((H.cv_bits >> op) & 1u) != 0;
-  M.has_x = lay != 0xFFu;
-  M.xbit = M.has_x ? 1u << (lay & 31u) : 0u;
-  M.dtbit = M.can_cv ? 1u << (dt & 31u) : 0u;
-  M.id0 = H.move_base + op * (H.NL - 1) * 4u;
-  M.brow = op * 32u;
-  return M;
-}
-
-// One conversion plane (cv) of my operand's Moves: 3 destinations x {same, transposed}.  ci[dst] is
-// the (admissible variants | first task) word of the destination's level assignment.  All
-// sub-Specs have a lower rank and are final in LDS.
-__device__ __forceinline__ void move_plane(const Hot& H, const MyOperand& M, const UnitLds& L, uint32_t q, uint32_t src,
-                                           uint32_t v, uint32_t cv, bool on, const uint32_t ci[3], Eval& e,
-                                           uint32_t& hi_or) {
-  const bool has_dt = H.ndt != 0;
-  const uint32_t cvbit = cv ? M.dtbit : 0u;
-  const uint32_t brow = cv * 128u + M.brow + src * 8u;
-  uint64_t b[6], t[6];
-  bool has[6];
-#pragma unroll
-  for (uint32_t dst = 0; dst < 3; dst++)
-#pragma unroll
-    for (uint32_t x = 0; x < 2; x++) {
-      const uint32_t c = dst * 2 + x, v2 = (v ^ (x ? M.xbit : 0u)) & ~cvbit;
-      b[c] = L.bterm[brow + dst * 2u + x];
-      has[c] = on && dst < src && (x == 0 || M.has_x) && ((ci[dst] >> v2) & 1u);
-      const uint32_t idx = (ci[dst] >> 16) + (has_dt ? __popc(ci[dst] & 0xFFFFu & ((1u << v2) - 1u)) : v2);
-      t[c] = L.t_cost[has[c] ? idx : q];
-    }
-#pragma unroll
-  for (uint32_t dst = 0; dst < 3; dst++)
-#pragma unroll
-    for (uint32_t x = 0; x < 2; x++) {
-      const uint32_t c = dst * 2 + x;
-      const bool exists = on && dst < src && (x == 0 || M.has_x) && b[c] != 0;     // b == 0: the target has no such Move
-      e.n += exists ? 1u : 0u;
-      const bool fin = exists & has[c] & (t[c] != kInf);
-      const uint64_t cand = t[c] + b[c];                        // t < 2^62 when finite, b <= 2^62: no wrap
-      hi_or |= fin ? (uint32_t)(cand >> 32) : 0u;
-      consider(e, cand, M.id0 + (dst * 2u + x) * 2u + cv, fin);
-    }
 }
 
 // Exchange inside a quad of lanes (lane ^ 1, lane ^ 2) without going through LDS.
@@ -525,478 +514,484 @@ __device__ __forceinline__ void quad_min(Eval& e) {
   consider(e, (uint64_t)hi << 32 | lo, id);
 }
 
-// One unit = passes [pass0, pass0 + np) of one shape, handled by T threads.
-template <int T>
-__device__ __forceinline__ void solve_unit(const DevParams* __restrict__ P, const UnitLds& L, uint32_t cap,
-                                           const Shape& S, uint32_t shape, uint32_t pass0, uint32_t np,
-                                           uint64_t* __restrict__ cost, uint16_t* __restrict__ arg, Eval& tot) {
-  const uint32_t tid = T == 64 ? (threadIdx.x & 63u) : threadIdx.x;
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t ncombo = P->ncombo;
-  const uint64_t group = (uint64_t)shape * P->G;
-  const Hot H = load_hot(P);
-  uint32_t n_serial, n_tile;
-  count_tiles(P, S, n_serial, n_tile);
-  Prefetch<T> pre;
-  prefetch_unit<T>(P, S, n_tile, pre);
-
-  // ---- 1. admissibility, compaction in rank order (rank-major level assignments, then pass) ----
-  constexpr int kIter = 256 / T < 1 ? 1 : 256 / T;   // ncombo <= 256
-  uint32_t info[kIter];
-#pragma unroll
-  for (int it = 0; it < kIter; it++) info[it] = it * T + tid < ncombo ? P->pos_info[it * T + tid] : 0u;
-  if (T == 64 || threadIdx.x < 64) build_fit(P, S, L.fit);
-  unit_sync<T>();
-  uint32_t f[4];
-#pragma unroll
-  for (int l = 0; l < 4; l++) f[l] = L.fit[l];
-  uint32_t n_task = 0;
-  if (H.ndt == 0) {
-    // No dtype coordinate: the variants of a (level assignment, pass) fit all or none, so a ballot
-    // per pass holds everything and the prefix sums are popcounts.  A: level l holds its operands;
-    // B: and the intermediate as well.
-    const uint32_t V = 1u << H.log2V;
-    const bool fused = P->kind == kKindF;
-#pragma unroll
-    for (int it = 0; it < kIter; it++) {
-      if ((uint32_t)(it * T) >= ncombo) break;
-      const uint32_t pc = it * T + tid;
-      uint32_t A = 0, B = 0;
-#pragma unroll
-      for (int l = 0; l < 4; l++) {
-        const uint32_t sub = (info[it] >> (8 + 4 * l)) & 15u;
-        A |= ((uint32_t)l < H.NL ? (f[l] >> sub) & 1u : 1u) << l;
-        B |= ((uint32_t)l < H.NL ? (f[l] >> (sub | 16u)) & 1u : 1u) << l;
-      }
-      bool ok[4];
-      unsigned long long bal[4];
-      uint32_t before = 0, wave_cnt = 0;
-#pragma unroll
-      for (int ps = 0; ps < 4; ps++) {
-        const uint32_t pass = pass0 + ps;
-        ok[ps] = (uint32_t)ps < np && pc < ncombo && (fused ? ((A | 1u << pass) == 15u) && ((B >> pass) & 1u) : A == 15u);
-        bal[ps] = __ballot(ok[ps]);
-        before += __builtin_amdgcn_mbcnt_hi((uint32_t)(bal[ps] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal[ps], 0u));
-        wave_cnt += (uint32_t)__popcll(bal[ps]);
-      }
-      uint32_t base = n_task + before * V;
-      if (T == 64) {
-        n_task += wave_cnt * V;
-      } else {
-        const uint32_t w = threadIdx.x >> 6;
-        if (lane == 0) L.wave_tot[w] = wave_cnt * V;
-        __syncthreads();
-        for (uint32_t i = 0; i < T / 64; i++) {
-          const uint32_t t = L.wave_tot[i];
-          if (i < w) base += t;
-          n_task += t;
-        }
-        __syncthreads();
-      }
-      if (pc < ncombo) {
-#pragma unroll
-        for (int ps = 0; ps < 4; ps++)
-          if ((uint32_t)ps < np) {
-            const uint32_t xpack = (pass0 + ps) << 8 | (info[it] & 0xFFu);
-            if (ps == 0 && (info[it] >> 24)) L.r_off[(info[it] >> 24) - 1u] = base;      // this position opens a rank
-            L.c_info[xpack] = (ok[ps] ? (1u << V) - 1u : 0u) | base << 16;
-            if (ok[ps]) {
-              if (base + V <= cap) {
-                if (V >= 4) {
-                  for (uint32_t v0 = 0; v0 < V; v0 += 4)
-                    *reinterpret_cast<uint4*>(&L.t_spec[base + v0]) =
-                        make_uint4(xpack | v0 << 10, xpack | (v0 + 1) << 10, xpack | (v0 + 2) << 10, xpack | (v0 + 3) << 10);
-                } else {
-                  for (uint32_t v0 = 0; v0 < V; v0++) L.t_spec[base + v0] = xpack | v0 << 10;
-                }
-              }
-              base += V;
-            }
-          }
-      }
-    }
-  } else {
-#pragma unroll
-    for (int it = 0; it < kIter; it++) {
-      if ((uint32_t)(it * T) >= ncombo) break;
-      const uint32_t pc = it * T + tid;
-      uint32_t mask[4] = {0, 0, 0, 0}, cnt = 0;
-      if (pc < ncombo) {
-#pragma unroll
-        for (int ps = 0; ps < 4; ps++)
-          if ((uint32_t)ps < np) { mask[ps] = admissible_mask(P, L.fit, f, info[it], pass0 + ps); cnt += __popc(mask[ps]); }
-      }
-      uint32_t incl = cnt;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, 64);
-        if ((int)lane >= d) incl += o;
-      }
-      uint32_t base = n_task + incl - cnt;
-      if (T == 64) {
-        n_task += __shfl(incl, 63, 64);
-      } else {
-        const uint32_t w = threadIdx.x >> 6;
-        if (lane == 63) L.wave_tot[w] = incl;
-        __syncthreads();
-        for (uint32_t i = 0; i < T / 64; i++) {
-          const uint32_t t = L.wave_tot[i];
-          if (i < w) base += t;
-          n_task += t;
-        }
-        __syncthreads();
-      }
-      if (pc < ncombo) {
-#pragma unroll
-        for (int ps = 0; ps < 4; ps++)
-          if ((uint32_t)ps < np) {
-            const uint32_t xpack = (pass0 + ps) << 8 | (info[it] & 0xFFu);
-            if (ps == 0 && (info[it] >> 24)) L.r_off[(info[it] >> 24) - 1u] = base;      // this position opens a rank
-            L.c_info[xpack] = mask[ps] | base << 16;
-            const uint32_t c = __popc(mask[ps]);
-            if (base + c <= cap) {
-              uint32_t q = base;
-              for (uint32_t m = mask[ps]; m; m &= m - 1) L.t_spec[q++] = xpack | ((uint32_t)__ffs(m) - 1u) << 10;
-            }
-            base += c;
-          }
-      }
-    }
-  }
-  if (n_task == 0) return;          // nothing here fits anywhere: the table already says so
-  if (n_task > cap) { tot.ovf |= 2u; return; }   // the plan guarantees this cannot happen; reported as an internal error
-  if (tid == 0) L.r_off[P->nranks] = n_task;
-  build_move_costs<T>(P, S, pre, L.bterm);
-
-  // ---- 3. tile and bufferize candidates of every task (sub-Specs of other shapes / tables: final) ----
-  const bool has_buf = P->kind == kKindF || P->split;
-  const uint32_t n_per_task = n_tile;          // (the bufferize candidates are counted where they are evaluated)
-  for (uint32_t e0 = 0; e0 == 0 || e0 < n_tile; e0 += kTileLds) {
-    if (e0) {
-      unit_sync<T>();
-      fetch_tile<T>(P, S, e0, n_tile, pre.te, pre.td, pre.tvalid);
-    }
-    store_tile<T>(P, L, S, shape, pre.te, pre.td, pre.tvalid);
-    unit_sync<T>();
-    const uint32_t n_here = n_tile - e0 < kTileLds ? n_tile - e0 : kTileLds;
-    const uint32_t par_from = n_serial > e0 ? (n_serial - e0 < n_here ? n_serial - e0 : n_here) : 0u;
-    if (n_task * 2 <= T) {
-      // few tasks: a quad of lanes per task, every fourth candidate each (fewer reads one after the other)
-      for (uint32_t qb = 0; qb < n_task; qb += T / 4) {
-        const bool active = qb + (tid >> 2) < n_task;
-        const uint32_t q = active ? qb + (tid >> 2) : 0u, sub4 = tid & 3u;
-        const uint32_t sp = L.t_spec[q];
-        const uint32_t xpack = sp & 0x3FFu, v = (sp >> 10) & 31u;
-        Eval e;
-        e.ovf = 0; e.best = kInf; e.arg = kNone;
-        if (sub4 == 0) {
-          if (e0 == 0) { if (has_buf) { const uint32_t nb = task_bufferize(P, S, shape, xpack, v, L.fit, e); tot.n += active ? nb : 0u; } }
-          else { e.best = L.t_cost[q]; e.arg = sp >> 16; }
-        }
-        task_tiles(P, L, n_here, par_from, sub4, 4, entry_offset(H, xpack, v), cost, e);
-        if (active) tot.ovf |= e.ovf;
-        quad_min<0xB1>(e);
-        quad_min<0x4E>(e);
-        if (active && sub4 == 0) {
-          L.t_cost[q] = e.best;
-          L.t_spec[q] = (sp & 0xFFFFu) | e.arg << 16;
-        }
-      }
-    } else {
-      for (uint32_t q = tid; q < n_task; q += T) {
-        const uint32_t sp = L.t_spec[q];
-        const uint32_t xpack = sp & 0x3FFu, v = (sp >> 10) & 31u;
-        Eval e;
-        e.ovf = 0;
-        if (e0 == 0) {
-          e.best = kInf; e.arg = kNone;
-          if (has_buf) tot.n += task_bufferize(P, S, shape, xpack, v, L.fit, e);
-        } else {
-          e.best = L.t_cost[q]; e.arg = sp >> 16;
-        }
-        task_tiles(P, L, n_here, par_from, 0, 1, entry_offset(H, xpack, v), cost, e);
-        L.t_cost[q] = e.best;
-        L.t_spec[q] = (sp & 0xFFFFu) | e.arg << 16;
-        tot.ovf |= e.ovf;
-      }
-    }
-  }
-  tot.n += n_per_task * ((n_task > tid ? n_task - tid + T - 1 : 0u) / T);
-  unit_sync<T>();
-
-  // microkernels whose shape predicate holds for this shape (uniform)
-  uint32_t mk_shape = 0;
-  for (uint32_t j = 0; j < P->nmk; j++) mk_shape |= (mk_shape_reps(P, S, j) ? 1u : 0u) << j;
-
-  // ---- 4. rank by rank: microkernels and Moves, then the parked tile/bufferize candidate ----
-  const uint32_t op = tid & 3u;
-  const MyOperand M = my_operand(H, op);
-  for (uint32_t r = 0; r < P->nranks; r++) {
-    const uint32_t t0 = L.r_off[r], t1 = L.r_off[r + 1];
-    if (t0 == t1) continue;
-    for (uint32_t qb = t0; qb < t1; qb += T / 4) {
-      const bool active = qb + (tid >> 2) < t1;
-      const uint32_t q = active ? qb + (tid >> 2) : t0;        // idle lanes read task t0 and drop the result
-      const uint32_t sp = L.t_spec[q];
-      const uint32_t xpack = sp & 0x3FFu, v = (sp >> 10) & 31u;
-      // my operand's Moves
-      Eval e;
-      e.best = kInf; e.arg = kNone; e.n = 0; e.ovf = 0;
-      uint32_t hi_or = 0;           // OR of the high words of all finite Move candidates
-      const uint32_t src = (xpack >> M.sh) & 3u;
-      const bool on = active && M.exists && src != 0;
-      if (__any(on)) {
-        uint32_t ci[3];
-#pragma unroll
-        for (uint32_t dst = 0; dst < 3; dst++) ci[dst] = L.c_info[on && dst < src ? xpack - ((src - dst) << M.sh) : xpack];
-        move_plane(H, M, L, q, src, v, 0, on, ci, e, hi_or);
-        const bool cv_on = on && M.can_cv && (v & M.dtbit);
-        if (__any(cv_on)) move_plane(H, M, L, q, src, v, 1, cv_on, ci, e, hi_or);
-      }
-      if (hi_or >> 30) e.ovf = 1;   // bit 62 of some finite candidate: the solve reports overflow
-      tot.n += e.n;
-      tot.ovf |= e.ovf;
-      quad_min<0xB1>(e);            // lanes ^ 1
-      quad_min<0x4E>(e);            // lanes ^ 2
-      if (active && op == 0) {
-        // the quad's first lane adds the microkernels (lowest ids) and the parked candidate, and stores
-        Eval f;
-        f.best = L.t_cost[q]; f.arg = sp >> 16; f.n = 0; f.ovf = 0;
-        consider(f, e.best, e.arg);
-        if (mk_shape) {
-          for (uint32_t mm = P->mk_entry[(xpack & 0xFFu) * P->V + v] & mk_shape; mm; mm &= mm - 1) {
-            const uint32_t j = (uint32_t)__ffs(mm) - 1u;
-            const uint64_t k = mul_or_limit(P->mk_cost[j], mk_shape_reps(P, S, j));
-            if (k >= kLimit) f.ovf = 1; else consider(f, k, j);
-            f.n++;
-          }
-        }
-        L.t_cost[q] = f.best;
-        L.t_spec[q] = (sp & 0xFFFFu) | f.arg << 16;
-        tot.n += f.n;
-        tot.ovf |= f.ovf;
-      }
-    }
-    unit_sync<T>();
-  }
-  // Results to the table after the last rank, a task per lane: inside the rank loop every chunk
-  // would wait for the previous chunk's stores (stores count on the same counter as loads here).
-  for (uint32_t q = tid; q < n_task; q += T) {
-    const uint32_t sp = L.t_spec[q];
-    const uint32_t off = entry_offset(H, sp & 0x3FFu, (sp >> 10) & 31u);
-    cost[group + off] = L.t_cost[q];
-    arg[group + off] = (uint16_t)(sp >> 16);
-  }
-}
-
-__device__ __forceinline__ void flush_counters(Counters* __restrict__ ctr, const Eval& tot) {
-  uint32_t n_rw = tot.n;
+__device__ __forceinline__ void flush_counters(Counters* __restrict__ ctr, uint32_t n_rw, uint32_t ovf) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) n_rw += __shfl_down(n_rw, d, 64);
   if ((threadIdx.x & 63u) == 0 && n_rw) atomicAdd(&ctr->n_rewrites[blockIdx.x % kCtrSlots], (unsigned long long)n_rw);
-  if (tot.ovf) atomicOr(&ctr->overflow, tot.ovf);
+  if (ovf) atomicOr(&ctr->overflow, ovf);
 }
 
-// Plan: one wave per kPlanShapes consecutive shapes (the per-assignment table and the parameters
-// stay in registers across them).  Counts the entries that fit per passive-level slice, marks them
-// in a bit map in table order (bit = cell; read by the compression pass) and classifies the shape:
-// bit 8 = one LDS slice holds it whole (bit 9: even a wave's small slice); else bits 0..3 = passive-level
-// slices that fit an LDS slice, bits 4..7 = slices that need the large one.  sort_work_kernel turns the classes into per-level work lists.
-constexpr uint32_t kPlanShapes = 8;
+// One bundle (starts: the level's bundle starts; nullptr: an item each) per workgroup of T threads.
+// LAY: the lattice has layout bits.  MOVES: the Matmul whose Moves are Move Specs.
+// Bound by instruction issue on levels with many items (2,200 lane-instructions per task with eight
+// lanes per task everywhere, about 1,200 with four) and by the chain of memory and LDS round trips
+// on the others (9 us for one item of 4 tasks: records 2.4, lists 2, tiles 2.3, ranks 1.8).  Fill
+// times against one item per wave without bundles or records: config 2 1.49 -> 0.77 ms, config 3
+// 0.69 -> 0.60, config 4 0.80 -> 0.73, config 5's F 2.22 -> 2.12, config 12's Matmul, which then was
+// a lane per Spec with three gathers per Move, 5.04 -> 2.16.
+// T: 512 for a wide item (100 registers would leave 2 instead of 3 workgroups on a unit, hence the
+// bound), 256 on levels short of bundles, else 128 (64: config 4 +9 %, F +5 %).
+template <int T, bool LAY, bool MOVES>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 5 : 4))) void fill_kernel(
+    const DevParams* __restrict__ P, const FillGeom g, const uint32_t* __restrict__ items, const uint32_t* __restrict__ starts,
+    const ShapeRec* __restrict__ recs, const unsigned long long* __restrict__ masks, uint64_t* __restrict__ cost, uint16_t* __restrict__ arg,
+    Counters* __restrict__ ctr) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  FillLds L;
+  carve_fill(smem, g, MOVES, L);
+  const uint32_t tid = threadIdx.x, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t i0 = starts ? starts[blockIdx.x] : blockIdx.x, n_it = starts ? starts[blockIdx.x + 1] - i0 : 1u;
+  const uint32_t npass = P->npass, nops = P->nops, ndt = P->ndt, ndp = 1u << ndt, nwp = P->nwp, nw = ndp * nwp, log2V = P->log2V;
+  const uint32_t nlay = g.nlay, psz = 1u << (2 * nops);
+  constexpr uint32_t kXw = LAY && !MOVES ? 2u : 1u;      // Move-cost entries per (operand, source, destination)
+  uint32_t n_rw = 0, ovf = 0;
+  if (n_it > g.ni) { if (tid == 0) atomicOr(&ctr->overflow, 2u); return; }       // the work lists guarantee this cannot happen
 
-__global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, uint32_t n_shapes,
-                                                   uint32_t cap_whole, uint32_t cap_slice, uint32_t cap_wave,
-                                                   uint32_t* __restrict__ shape_class, uint32_t* __restrict__ fitmap,
-                                                   Counters* __restrict__ ctr, uint4* __restrict__ cost16,
-                                                   uint4* __restrict__ arg16) {
-  __shared__ uint32_t fit_all[4][16];
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  uint32_t* fit = fit_all[wave];
-  const uint32_t npass = P->npass, ncombo = P->ncombo, V = P->V, nb = npass * V;
-  const Hot H = load_hot(P);
-  uint32_t info[4], off0[4];
+  // ---- the items, one per lane of the first wave ----
+  if (wave == 0) {
+    uint32_t cnt = 0;
+    if (lane < n_it) {
+      const uint32_t item = items[i0 + lane];
+      unsigned long long m[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int it = 0; it < 4; it++) {
-    info[it] = it * 64 + lane < ncombo ? P->pos_info[it * 64 + lane] : 0u;
-    off0[it] = entry_offset(H, info[it] & 0xFFu, 0);      // pass 0, variant 0 of this level assignment
-  }
-  unsigned long long n_adm = 0;
-  const uint32_t first_shape = (blockIdx.x * 4 + wave) * kPlanShapes;
-  for (uint32_t shape = first_shape; shape < first_shape + kPlanShapes && shape < n_shapes; shape++) {
-    if (cost16) {
-      // (INF, NONE) = all-ones over the shape's whole group: the level kernels overwrite what fits
-      const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
-      const uint32_t nc = P->G >> 1, na = P->G >> 3;       // 16-byte pieces (G is a multiple of 8)
-      uint4* c16 = cost16 + (size_t)shape * nc;
-      uint4* a16 = arg16 + (size_t)shape * na;
-      for (uint32_t i = lane; i < nc; i += 64) c16[i] = ones;
-      for (uint32_t i = lane; i < na; i += 64) a16[i] = ones;
-    }
-    Shape S;
-    load_shape(P, shape, S);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    build_fit(P, S, fit);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    uint32_t f[4];
+      for (int w = 0; w < 4; w++) if ((uint32_t)w < nw) m[w] = masks[(size_t)item * nw + w];
+      const uint32_t si_i = item / npass, pass = item - si_i * npass;
+      const ShapeRec R = recs[si_i];
+      uint32_t si[4];
 #pragma unroll
-    for (int l = 0; l < 4; l++) f[l] = fit[l];
-    const uint64_t group = (uint64_t)shape * P->G;
-    uint32_t cnt[4] = {0, 0, 0, 0};
+      for (int d = 0; d < 4; d++) si[d] = (R.si >> (8 * d)) & 0xFFu;
 #pragma unroll
-    for (int it = 0; it < 4; it++) {
-      if ((uint32_t)(it * 64) >= ncombo) break;
-      if (it * 64 + lane >= ncombo) continue;
-      unsigned long long bits = 0;
+      for (int w = 0; w < 4; w++) { L.it_mask[lane * 4 + w] = m[w]; cnt += (uint32_t)__popcll(m[w]); }
+      L.it_pass[lane] = pass; L.it_base[lane] = R.shape * P->G + (pass << log2V);
+      L.it_si[lane] = R.si; L.it_nserial[lane] = R.n_serial; L.it_ntile[lane] = R.n_tile; L.it_mk[lane] = R.mk_var & 0xFFu;
+      L.it_cnt[lane] = R.tile_cnt;
 #pragma unroll
-      for (int ps = 0; ps < 4; ps++)
-        if ((uint32_t)ps < npass) {
-          const uint32_t m = admissible_mask(P, fit, f, info[it], ps);
-          cnt[ps] += __popc(m);
-          bits |= (unsigned long long)m << (ps * V);
+      for (int d = 0; d < 4; d++) L.it_lo[lane * 4 + d] = R.tile_lo[d];
+#pragma unroll
+      for (int i = 0; i < 5; i++) L.it_numel[lane * 5 + i] = R.numel[i];
+      uint32_t rowM = 0, rowE = 0;
+      uint64_t z = 0;
+      if (P->kind == kKindF) {
+        const uint32_t zc = pass == 0 ? P->zero[0] : pass == 1 ? P->zero[1] : pass == 2 ? P->zero[2] : P->zero[3];
+        z = mul_or_limit(zc, R.numel[4]);
+        if (P->chain) {
+          // the table's k and n lists are this lattice's p list (and k and n lists)
+          rowM = ((si[1] * P->nkM + si[2]) * P->nsz[3] + si[0]) * P->GM;
+          rowE = ((si[1] * P->nkM + si[0]) * P->nsz[3] + si[3]) * P->GM;
+        } else {
+          rowM = ((si[1] * P->nkM + si[2] + P->kM_first) * P->nsz[3] + si[3]) * P->GM;
+          rowE = (si[1] * P->nszE_n + si[3]) * P->GE;
         }
-      if (nb == 32 || nb == 64) {
-        // whole words of the map (the group size is a multiple of nb): stored, the map is not zeroed
-        uint32_t* w = fitmap + ((group + off0[it]) >> 5);
-        w[0] = (uint32_t)bits;
-        if (nb == 64) w[1] = (uint32_t)(bits >> 32);
-      } else if (bits) {
-        const uint64_t cell0 = group + off0[it];
-        const uint32_t sh = (uint32_t)(cell0 & 31u);
-        uint32_t* w = fitmap + (cell0 >> 5);
-        atomicOr(w, (uint32_t)(bits << sh));
-        if (sh + nb > 32) {
-          atomicOr(w + 1, (uint32_t)(bits >> (32 - sh)));
-          if (sh + nb > 64) atomicOr(w + 2, (uint32_t)(bits >> (64 - sh)));
+      } else if (P->split) {
+        const uint32_t sh = si[1] * P->nsz[3] + si[3];
+        rowM = sh * P->GM; rowE = sh * P->GE;
+      }
+      L.it_rowM[lane] = rowM; L.it_rowE[lane] = rowE; L.it_z[lane] = z;
+      // (unpacked: widths at 2 * i, positions at 8 + 4 * i, their sum at 24)
+      const uint32_t pv = R.mk_var >> 8;
+      L.it_var[lane] = (pv & 0x3Fu) | (pv >> 6 & 7u) << 8 | (pv >> 9 & 7u) << 12 | (pv >> 12 & 7u) << 16 | (pv >> 15) << 24;
+    }
+    uint32_t incl = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t o = __shfl_up(incl, d, 64);
+      if ((int)lane >= d) incl += o;
+    }
+    if (lane < n_it) L.it_first[lane] = incl - cnt;
+    if (lane == 63) L.it_first[n_it] = incl;
+    if (lane < kMaxRanks + 2) L.rcnt[lane] = 0;
+  }
+  for (uint32_t i = tid; i < n_it * g.isz / 2; i += T) reinterpret_cast<uint32_t*>(L.idx)[i] = g.ns | g.ns << 16;
+  if (tid < (1u << nlay)) L.t_cost[(MOVES ? g.cap : g.ns << nlay) + tid] = kInf;
+  if (MOVES && tid == 0) L.tk0[g.ns] = (uint16_t)g.cap;
+  __syncthreads();
+  const uint32_t n_ent = L.it_first[n_it];
+  if (n_ent > g.ns) { if (tid == 0) atomicOr(&ctr->overflow, 2u); return; }      // (nor this)
+
+  // (what the next three steps read of the parameters does not depend on the items: it is requested
+  // together with the first tile rewrites, so that one trip to memory serves all of them)
+  auto tile_at = [&](uint32_t i, uint32_t e0, uint32_t& td) -> uint32_t {       // entry of the tile list behind LDS place i
+    const uint32_t j = i / g.kt, e = e0 + (i - j * g.kt), cnts = L.it_cnt[j];
+    uint32_t first = 0, q = ~0u;
+    td = 0;
+    if (e >= L.it_ntile[j]) return q;
+#pragma unroll
+    for (int d = 0; d < 4; d++) {
+      const uint32_t cnt = P->tile_dim_ok[d] ? (cnts >> (8 * d)) & 0xFFu : 0u;
+      if (e >= first && e < first + cnt) { td = d; q = L.it_lo[j * 4 + d] + (e - first); }
+      first += cnt;
+    }
+    if (P->par) {        // the parallel loops over b, m, n follow
+#pragma unroll
+      for (int d = 0; d < 4; d++) {
+        if (d == 2) continue;
+        const uint32_t cnt = (cnts >> (8 * d)) & 0xFFu;
+        if (e >= first && e < first + cnt) { td = 4 + d; q = L.it_lo[j * 4 + d] + (e - first); }
+        first += cnt;
+      }
+    }
+    return q;
+  };
+  auto put_tile = [&](uint32_t i, uint32_t td, const TileEntry& te) {           // first cell of the child's item, trips, id
+    const uint32_t j = i / g.kt, si = L.it_si[j], d = td & 3u, sj = (si >> (8 * d)) & 0xFFu;
+    const uint32_t stride = d == 0 ? P->shape_stride[0] : d == 1 ? P->shape_stride[1] : d == 2 ? P->shape_stride[2] : P->shape_stride[3];
+    L.tl_cell[i] = L.it_base[j] - (sj - te.jt) * stride * P->G;                 // the serial table has the same geometry
+    L.tl_trips[i] = td >= 4 ? (te.trips + P->threads - 1) / P->threads : te.trips;
+    L.tl_id[i] = (td >= 4 ? P->par_base : P->tile_base) + d * P->maxs + te.jt;
+  };
+  uint32_t td0 = 0;
+  const uint32_t q_tile0 = tid < n_it * g.kt ? tile_at(tid, 0, td0) : ~0u;
+  const TileEntry te0 = P->tiles[q_tile0 == ~0u ? 0u : q_tile0];
+  const uint32_t pos0 = (wave % nw % nwp) * 64u + lane, pe0 = P->pos_entry[pos0 < kMaxCombo ? pos0 : 0u];
+
+  // ---- the admissible entries: by item, and counted by rank ----
+  for (uint32_t jw = wave; jw < n_it * nw; jw += T / 64) {
+    const uint32_t j = jw / nw, w = jw - j * nw, dt = w / nwp, pos = (w - dt * nwp) * 64u + lane;
+    const unsigned long long m = L.it_mask[j * 4 + w];
+    uint32_t slot = L.it_first[j];
+#pragma unroll
+    for (uint32_t u = 0; u < 3; u++) if (u < w) slot += (uint32_t)__popcll(L.it_mask[j * 4 + u]);
+    if ((m >> lane) & 1ull) {
+      slot += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+      const uint32_t pe = jw == wave ? pe0 : P->pos_entry[pos], pack = pe & 0xFFu, rank = (pe >> 8) & 0xFFu;       // pack | rank << 8 | mixed-radix index << 16
+      L.ent[slot] = pack | dt << 8 | j << 10 | rank << 16 | (pe >> 16) << 20;
+      L.idx[j * g.isz + dt * psz + pack] = (uint16_t)slot;
+      L.place[slot] = (uint16_t)atomicAdd(&L.rcnt[rank], 1u);                       // its place among the rank's entries
+    }
+  }
+  // Move costs: coefficient * elements per (converted, operand, source level - 1, destination level, transposed),
+  // 0 = no such Move; of a Matmul whose Moves are Specs: what bind_kernel tabulated for the operand's size
+  if (MOVES) {
+    const uint32_t per_op = 6u << (2 * P->yb), per_size = P->bind_d * per_op;
+    for (uint32_t i = tid; i < n_it * g.bt; i += T) {
+      const uint32_t j = i / g.bt, r = i - j * g.bt, dc = r / (3u * per_op), q = r - dc * 3u * per_op, op = q / per_op;
+      const uint32_t si = L.it_si[j], sm = (si >> 8) & 0xFFu, sk = (si >> 16) & 0xFFu, sn = si >> 24;
+      const uint32_t rows = op == 1 ? sk : sm, cols = op == 0 ? sk : sn;
+      L.bterm[i] = P->bind[((size_t)(op == 2 ? P->nszV * P->nszV : 0u) + rows * P->nszV + cols) * per_size + dc * per_op + (q - op * per_op)];
+    }
+  } else {
+    for (uint32_t i = tid; i < n_it * g.bt; i += T) {
+      const uint32_t j = i / g.bt, r = i - j * g.bt, x = kXw == 2 ? r & 1u : 0u, sd = (r / kXw) % 9u, co = (r / kXw) / 9u, cv = co / nops, op = co - cv * nops;
+      const uint32_t src = sd / 3u + 1u, dst = sd - (src - 1u) * 3u;
+      const uint32_t c = dst < src ? P->mcoef[op][src][dst][x] : 0u;
+      L.bterm[i] = c ? mul_or_limit((uint64_t)c + (cv ? P->convert : 0u), L.it_numel[j * 5 + op]) : 0;
+    }
+  }
+  if (q_tile0 != ~0u) put_tile(tid, td0, te0);
+  auto stage_tiles = [&](uint32_t e0, uint32_t i0) {
+    for (uint32_t i = i0; i < n_it * g.kt; i += T) {
+      uint32_t td;
+      const uint32_t q = tile_at(i, e0, td);
+      if (q != ~0u) put_tile(i, td, P->tiles[q]);
+    }
+  };
+  stage_tiles(0, tid + T);
+  __syncthreads();
+
+  // every wave keeps the ranks' first places in its lanes (lane r: rank r)
+  uint32_t rank_first;
+  {
+    const uint32_t c = lane < P->nranks ? L.rcnt[lane] : 0u;
+    uint32_t incl = c;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      const uint32_t o = __shfl_up(incl, d, 64);
+      if ((int)lane >= d) incl += o;
+    }
+    rank_first = lane < P->nranks ? incl - c : n_ent;
+  }
+  // the entries in rank order (used after the tile phase)
+  for (uint32_t s0 = 0; s0 < n_ent; s0 += T) {
+    const uint32_t s = s0 + tid, en = L.ent[s < n_ent ? s : 0u];
+    const uint32_t at = __shfl(rank_first, ent_rank(en), 64);
+    if (s < n_ent) { const uint32_t k = at + L.place[s]; L.rl_ent[k] = en; L.rl_slot[k] = (uint16_t)s; }
+  }
+  // tasks: the entries' layouts
+  uint32_t n_task;
+  if (MOVES) {
+    if (wave == 0) {
+      uint32_t run = 0;
+      for (uint32_t s0 = 0; s0 < n_ent; s0 += 64) {
+        const uint32_t s = s0 + lane, c = s < n_ent ? 1u << (L.it_var[ent_item(L.ent[s])] >> 24) : 0u;
+        uint32_t incl = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const uint32_t o = __shfl_up(incl, d, 64);
+          if ((int)lane >= d) incl += o;
+        }
+        if (s < n_ent) L.tk0[s] = (uint16_t)(run + incl - c);
+        run += __shfl(incl, 63, 64);
+      }
+      if (lane == 0) L.rcnt[kMaxRanks + 1] = run;
+    }
+    __syncthreads();
+    n_task = L.rcnt[kMaxRanks + 1];
+    if (n_task > g.cap) { if (tid == 0) atomicOr(&ctr->overflow, 2u); return; }
+    for (uint32_t s = tid; s < n_ent; s += T) {
+      const uint32_t c = 1u << (L.it_var[ent_item(L.ent[s])] >> 24), t0 = L.tk0[s];
+      for (uint32_t k = 0; k < c; k++) L.tslot[t0 + k] = (uint16_t)s;
+    }
+    __syncthreads();
+  } else {
+    n_task = n_ent << nlay;
+  }
+
+  // ---- 1. tile and bufferize candidates of every task (sub-Specs of other shapes / tables: final) ----
+  uint32_t max_tile = 0;
+  for (uint32_t j = 0; j < n_it; j++) { const uint32_t t = L.it_ntile[j]; max_tile = t > max_tile ? t : max_tile; }
+  const bool has_buf = !MOVES && (P->kind == kKindF || P->split);
+  const uint64_t s_serial = P->s, s_par = P->sync;
+  const uint64_t* __restrict__ serial = P->costM;
+  // few tasks: a quad of lanes per task, every fourth candidate each (fewer reads one after the other)
+  const uint32_t lg = n_task * 4 <= T ? 2u : 0u, sub4 = lg ? tid & 3u : 0u;
+  for (uint32_t e0 = 0; e0 == 0 || e0 < max_tile; e0 += g.kt) {
+    if (e0) { __syncthreads(); stage_tiles(e0, tid); __syncthreads(); }
+    for (uint32_t qb = 0; qb < n_task; qb += T >> lg) {
+      const uint32_t q0 = qb + (tid >> lg);
+      if (!lg && q0 >= n_task) break;
+      const uint32_t q = q0 < n_task ? q0 : 0u;
+      const uint32_t slot = MOVES ? (uint32_t)L.tslot[q] : q >> nlay, c = MOVES ? q - L.tk0[slot] : q & ((1u << nlay) - 1u);
+      const uint32_t en = L.ent[slot], j = ent_item(en);
+      const uint32_t v = variant_of<MOVES>(P, MOVES ? L.it_var[j] : 0u, c, ent_dt(en));
+      const uint32_t off = ((ent_combo(en) * npass) << log2V) + v;
+      const uint32_t all = L.it_ntile[j], n_here = all <= e0 ? 0u : all - e0 < g.kt ? all - e0 : g.kt;
+      const uint32_t n_ser = L.it_nserial[j] > e0 ? L.it_nserial[j] - e0 : 0u;     // from here on parallel loops
+      Eval e;
+      e.best = kInf; e.arg = kNone; e.ovf = 0;
+      if (e0 && sub4 == 0) { e.best = L.t_cost[q]; e.arg = L.t_arg[q]; }
+      // trips * sub + s in 96 bits; reaching 2^62 = overflow.  A parallel loop's body is the
+      // serial-only Spec (read from the serial table), its constant the synchronisation cost.
+      for (uint32_t t0 = sub4; t0 < n_here; t0 += kBatch << lg) {
+        uint64_t sub[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; u++) {
+          const uint32_t t = t0 + (u << lg);
+          sub[u] = kInf;
+          if (t < n_here) sub[u] = (t >= n_ser ? serial : cost)[L.tl_cell[j * g.kt + t] + off];     // no request for a candidate that is not there
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; u++) {
+          const uint32_t t = t0 + (u << lg);
+          if (t < n_here) {
+            const bool fin = (uint32_t)(sub[u] >> 32) != ~0u;
+            const uint32_t a = L.tl_trips[j * g.kt + t];
+            const uint64_t lo = (uint64_t)a * (uint32_t)sub[u];
+            const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);   // bits 32.. of the product
+            const uint64_t cand = ((hi << 32) | (uint32_t)lo) + (t >= n_ser ? s_par : s_serial);
+            const bool over = fin & (((hi >> 30) != 0) | (cand >= kLimit));
+            e.ovf |= over ? 1u : 0u;
+            const bool better = fin & !over & (cand < e.best);       // ids ascend
+            e.best = better ? cand : e.best;
+            e.arg = better ? L.tl_id[j * g.kt + t] : e.arg;
+          }
+        }
+      }
+      if (has_buf && e0 == 0 && sub4 == 0) {
+        const uint32_t nb = task_bufferize(P, L.it_rowM[j], L.it_rowE[j], L.it_z[j], L.it_numel + j * 5, ent_pack(en), L.it_pass[j], v, e);
+        if (q0 < n_task) n_rw += nb;
+      }
+      if (lg) { quad_min<0xB1>(e); quad_min<0x4E>(e); }
+      if (q0 < n_task) {
+        ovf |= e.ovf;
+        if (sub4 == 0) {
+          L.t_cost[q] = e.best; L.t_arg[q] = (uint16_t)e.arg;
+          if (e0 == 0) n_rw += all;
         }
       }
     }
-    uint32_t total = 0;
-#pragma unroll
-    for (int ps = 0; ps < 4; ps++) {
-#pragma unroll
-      for (int d = 32; d > 0; d >>= 1) cnt[ps] += __shfl_down(cnt[ps], d, 64);
-      cnt[ps] = __shfl(cnt[ps], 0, 64);
-      total += cnt[ps];
-    }
-    if (lane == 0) {
-      n_adm += total;
-      uint32_t cls = 0;
-      if (total && total <= cap_whole) cls = total <= cap_wave ? 0x300u : 0x100u;
-      else
-        for (uint32_t ps = 0; ps < npass; ps++)
-          if (cnt[ps]) cls |= 1u << (cnt[ps] <= cap_slice ? ps : 4 + ps);
-      shape_class[shape] = cls;
-    }
   }
-  if (lane == 0 && n_adm) atomicAdd(&ctr->n_admissible[blockIdx.x % kCtrSlots], n_adm);
-}
-
-// One workgroup per dependency level: walks the level's shapes in index order and writes its work
-// lists and their lengths: whole shapes (the small ones from the front of the level's stretch of
-// list_whole, the others from its back), slices, and wide slices.
-constexpr uint32_t kSortThreads = 1024;
-__global__ __launch_bounds__(kSortThreads) void sort_work_kernel(const uint32_t* __restrict__ level_shapes,
-                                                                 const uint32_t* __restrict__ level_off, uint32_t n_levels,
-                                                                 uint32_t npass, const uint32_t* __restrict__ shape_class,
-                                                                 uint32_t* __restrict__ list_whole, uint32_t* __restrict__ list_slice,
-                                                                 uint32_t* __restrict__ list_wide, uint32_t* __restrict__ list_cnt) {
-  constexpr uint32_t kWaves = kSortThreads / 64;
-  __shared__ unsigned long long wave_sum[kWaves];
-  __shared__ uint32_t run[4];
-  const uint32_t lv = blockIdx.x, first = level_off[lv], n = level_off[lv + 1] - first;
-  if (threadIdx.x < 4) run[threadIdx.x] = 0;
   __syncthreads();
-  for (uint32_t base = 0; base < n; base += kSortThreads) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t shape = i < n ? level_shapes[first + i] : 0u;
-    const uint32_t cls = i < n ? shape_class[shape] : 0u;
-    const uint32_t cw = (cls >> 9) & 1u, cb = ((cls >> 8) & 1u) & ~cw, cs = __popc(cls & 15u), cx = __popc((cls >> 4) & 15u);
-    // four counts in 16-bit fields (per kSortThreads threads: <= 1024, 4096, 4096, 1024)
-    const unsigned long long packed = (unsigned long long)cw | (unsigned long long)cs << 16 | (unsigned long long)cx << 32 |
-                                      (unsigned long long)cb << 48;
-    unsigned long long incl = packed;
+
+  // ---- 2. rank by rank: Moves, microkernels, the parked tile/bufferize candidate ----
+  // Four lanes per task, one operand each (its Moves to every lower level and layout); the lanes'
+  // candidates are then reduced to the lexicographic minimum of (cost, id).  All tables are indexed
+  // directly; a level assignment that does not fit reads the tasks of entry ns (INF).  On levels
+  // short of work (T = 256) the chain of ranks is what counts, and eight lanes per task halve a
+  // lane's work in each: lane 4 * x + op takes the changes of layout x and x + 2.  Elsewhere it is
+  // the instructions, most of which a lane spends whatever its number of candidates.
+  constexpr uint32_t kTaskLanes = LAY && T == 256 ? 8u : 4u, kXLanes = kTaskLanes / 4u;
+  const uint32_t op = tid & 3u, x = kXLanes == 2 ? (tid >> 2) & 1u : 0u;
+  const uint32_t my_shift = op == 0 ? P->pack_shift[0] : op == 1 ? P->pack_shift[1] : op == 2 ? P->pack_shift[2] : P->pack_shift[3];
+  const uint32_t my_lay = op == 0 ? P->lay_bit[0] : op == 1 ? P->lay_bit[1] : op == 2 ? P->lay_bit[2] : P->lay_bit[3];
+  const uint32_t my_dt = op == 0 ? P->dt_bit[0] : op == 1 ? P->dt_bit[1] : op == 2 ? P->dt_bit[2] : P->dt_bit[3];
+  const bool my_cv = (op == 0 ? P->can_convert[0] : op == 1 ? P->can_convert[1] : op == 2 ? P->can_convert[2] : P->can_convert[3]) != 0 && my_dt != kNoBit;
+  const uint32_t base_bf = op == 0 ? P->base_bf16[0] : op == 1 ? P->base_bf16[1] : op == 2 ? P->base_bf16[2] : P->base_bf16[3];
+  const uint32_t my_lw = op == 0 ? P->lay_w[0] : op == 1 ? P->lay_w[1] : op == 2 ? P->lay_w[2] : P->lay_w[3];
+  const bool my_part = op < nops && (x == 0 || my_lay != kNoBit);
+  const uint32_t xw = MOVES ? P->xw : 2u, id0 = P->move_base + op * (P->NL - 1u) * xw * 2u + x * 2u;
+  const uint32_t yb = MOVES ? P->yb : 0u, nranks = P->nranks, bind_d = MOVES ? P->bind_d : 1u;
+  const uint32_t my_fb = my_lay != kNoBit ? my_lay - ndt : 0u, op_row = op * 9u * kXw + x;
+  // (with packed layouts the entries of a rank may have different numbers of tasks: lanes for the most of any item)
+  uint32_t lays = nlay;
+  if (MOVES) {
+    lays = 0;
+    for (uint32_t j = 0; j < n_it; j++) { const uint32_t w = L.it_var[j] >> 24; lays = w > lays ? w : lays; }
+  }
+  for (uint32_t r = 0; r < nranks; r++) {
+    const uint32_t r0 = lane_of(rank_first, r), r1 = lane_of(rank_first, r + 1);
+    if (r0 == r1) continue;
+    const uint32_t n_here = (r1 - r0) << lays;
+    for (uint32_t qb = 0; qb < n_here; qb += T / kTaskLanes) {
+      const uint32_t qq = qb + tid / kTaskLanes;
+      bool active = qq < n_here;
+      const uint32_t k = r0 + (active ? qq >> lays : 0u);
+      const uint32_t slot = L.rl_slot[k], en = L.rl_ent[k], j = ent_item(en), pack = ent_pack(en), dt = ent_dt(en);
+      uint32_t c = active ? qq & ((1u << lays) - 1u) : 0u, var = 0;
+      if (MOVES) {
+        var = L.it_var[j];
+        active = active && c < (1u << (var >> 24));
+        c = active ? c : 0u;
+      }
+      const uint32_t q = MOVES ? L.tk0[slot] + c : (slot << nlay) + c;
+      Eval parked;
+      parked.best = L.t_cost[q]; parked.arg = L.t_arg[q];
+      const uint32_t mk_shape = L.it_mk[j];
+      Eval e;
+      e.best = kInf; e.arg = kNone;
+      uint32_t hi_or = 0;           // OR of the high words of all finite Move candidates
+      const uint32_t src = (pack >> my_shift) & 3u;
+      const bool on = active && my_part && src != 0;
+      if (__any(on)) {
+        const uint32_t src1 = on ? src - 1u : 0u, at = j * g.isz + pack;
+        const uint32_t bf = my_dt != kNoBit ? (dt >> my_dt) & 1u : base_bf;
+        for (uint32_t cv = 0; cv < ndp && cv < 2u; cv++) {             // as it is, then converted
+          const bool plane = on && (cv == 0 || (my_cv && bf));
+          if (cv && !__any(plane)) break;
+          const uint32_t dt2 = cv ? dt & ~(1u << (my_dt & 31u)) : dt;
+          uint32_t to[3];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const unsigned long long o = __shfl_up(incl, d, 64);
-      if ((int)(threadIdx.x & 63u) >= d) incl += o;
-    }
-    if ((threadIdx.x & 63u) == 63) wave_sum[threadIdx.x >> 6] = incl;
-    __syncthreads();
-    unsigned long long excl = incl - packed, tot = 0;
-    for (uint32_t w = 0; w < kWaves; w++) {
-      if (w < (threadIdx.x >> 6)) excl += wave_sum[w];
-      tot += wave_sum[w];
-    }
-    uint32_t ow = run[0] + (uint32_t)(excl & 0xFFFFu), os = run[1] + (uint32_t)((excl >> 16) & 0xFFFFu);
-    uint32_t ox = run[2] + (uint32_t)((excl >> 32) & 0xFFFFu);
-    if (cw) list_whole[first + ow] = shape;
-    if (cb) list_whole[first + n - 1u - (run[3] + (uint32_t)(excl >> 48))] = shape;
-    for (uint32_t ps = 0; ps < npass; ps++) {
-      if ((cls >> ps) & 1u) list_slice[(size_t)first * npass + os++] = shape * npass + ps;
-      if ((cls >> (4 + ps)) & 1u) list_wide[(size_t)first * npass + ox++] = shape * npass + ps;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      run[0] += (uint32_t)(tot & 0xFFFFu); run[1] += (uint32_t)((tot >> 16) & 0xFFFFu);
-      run[2] += (uint32_t)((tot >> 32) & 0xFFFFu); run[3] += (uint32_t)(tot >> 48);
+          for (uint32_t dst = 0; dst < 3; dst++) to[dst] = L.idx[at + dt2 * psz - (plane && dst < src ? (src - dst) << my_shift : 0u)];
+          if (MOVES) {
+            // my operand's field inside c, its width
+            const uint32_t fw = (var >> (2 * op)) & 3u, fb = (var >> (8 + 4 * op)) & 7u, y0 = (c >> fb) & ((1u << fw) - 1u);
+            const uint32_t row = j * g.bt + ((((bind_d == 3 && bf ? 1u + cv : 0u) * 3u + op) * 6u + (src1 + 1u) * src1 / 2u) << (2 * yb)) + (y0 << yb);
+            for (uint32_t xx = x; xx < xw; xx += kXLanes) {
+              const bool counts = plane && xx < (1u << my_lw);
+              const bool exists = counts && xx < (1u << fw);          // (a packed layout that this size cannot have: no such Spec)
+              n_rw += counts ? src : 0u;
+              if (!__any(exists)) continue;
+#pragma unroll
+              for (uint32_t dst = 0; dst < 3; dst++) {
+                const bool ok = exists && dst < src;
+                const uint64_t b = L.bterm[ok ? row + (dst << (2 * yb)) + (y0 ^ xx) : 0u], t = L.t_cost[ok ? L.tk0[to[dst]] + (c ^ (xx << fb)) : q];
+                const bool fin = ok && (uint32_t)(b >> 32) != ~0u && (uint32_t)(t >> 32) != ~0u;
+                const uint64_t cand = t + b;                          // each at most 2^62 when finite: no wrap
+                hi_or |= fin ? (uint32_t)(cand >> 32) : 0u;
+                consider(e, cand, id0 + (dst * xw + (xx - x)) * 2u + cv, fin);
+              }
+            }
+          } else {
+            const uint32_t row = j * g.bt + cv * nops * 9u * kXw + op_row + src1 * 3u * kXw;
+            constexpr uint32_t kMine = kXw / kXLanes ? kXw / kXLanes : 1u;      // changes of layout per lane
+            uint64_t b[3][kMine], t[3][kMine];
+#pragma unroll
+            for (uint32_t dst = 0; dst < 3; dst++)
+#pragma unroll
+              for (uint32_t u = 0; u < kMine; u++) {
+                b[dst][u] = L.bterm[row + dst * kXw + u];
+                t[dst][u] = L.t_cost[(to[dst] << nlay) + (c ^ ((x + u) << my_fb))];
+              }
+#pragma unroll
+            for (uint32_t dst = 0; dst < 3; dst++)
+#pragma unroll
+              for (uint32_t u = 0; u < kMine; u++) {
+                const bool counts = plane && b[dst][u] != 0;          // 0 = no such Move (and no destination at or above src)
+                n_rw += counts ? 1u : 0u;
+                const bool fin = counts && (uint32_t)(t[dst][u] >> 32) != ~0u;
+                const uint64_t cand = t[dst][u] + b[dst][u];          // t < 2^62 when finite, b <= 2^62: no wrap
+                hi_or |= fin ? (uint32_t)(cand >> 32) : 0u;
+                const uint32_t id = id0 + dst * 4u + u * 2u + cv;
+                if (cv) consider(e, cand, id, fin);
+                else {
+                  const bool better = fin && cand < e.best;           // ids ascend
+                  e.best = better ? cand : e.best;
+                  e.arg = better ? id : e.arg;
+                }
+              }
+          }
+        }
+      }
+      if (hi_or >> 30) ovf |= 1u;   // bit 62 of some finite candidate: the solve reports overflow
+      quad_min<0xB1>(e);            // lanes ^ 1
+      quad_min<0x4E>(e);            // lanes ^ 2
+      if (kXLanes == 2) quad_min<0x141>(e);  // the other quad of eight (mirrored: the lanes of a quad agree by now)
+      if (active && (tid & (kTaskLanes - 1u)) == 0) {
+        // the task's first lane adds the microkernels (lowest ids) and the parked candidate (highest), and stores
+        consider(e, parked.best, parked.arg);
+        if (mk_shape) {
+          const uint32_t v = variant_of<MOVES>(P, var, c, dt), si = L.it_si[j];
+          for (uint32_t mm = P->mk_entry[(pack << log2V) + v] & mk_shape; mm; mm &= mm - 1) {
+            const uint32_t m = (uint32_t)__ffs((int)mm) - 1u;
+            Shape S;
+#pragma unroll
+            for (int d = 0; d < 4; d++) S.d[d] = P->sizes[d][(si >> (8 * d)) & 0xFFu];
+            const uint64_t ck = mul_or_limit(P->mk_cost[m], mk_shape_reps(P, S, m));
+            if (ck >= kLimit) ovf |= 1u; else consider(e, ck, m);
+            n_rw++;
+          }
+        }
+        L.t_cost[q] = e.best;
+        L.t_arg[q] = (uint16_t)e.arg;
+      }
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    list_cnt[lv] = run[0]; list_cnt[n_levels + lv] = run[1]; list_cnt[2 * n_levels + lv] = run[2];
-    list_cnt[3 * n_levels + lv] = run[3];
+  // ---- 3. results to the table, a task per lane: inside the rank loop every chunk would wait for
+  // the previous chunk's stores (stores count on the same counter as loads here) ----
+  for (uint32_t q = tid; q < n_task; q += T) {
+    const uint32_t slot = MOVES ? (uint32_t)L.tslot[q] : q >> nlay, c = MOVES ? q - L.tk0[slot] : q & ((1u << nlay) - 1u);
+    const uint32_t en = L.ent[slot], j = ent_item(en);
+    const uint32_t cell = L.it_base[j] + ((ent_combo(en) * npass) << log2V) + variant_of<MOVES>(P, MOVES ? L.it_var[j] : 0u, c, ent_dt(en));
+    cost[cell] = L.t_cost[q];
+    arg[cell] = L.t_arg[q];
   }
+  flush_counters(ctr, n_rw, ovf);
 }
 
-// One dependency level, the items an LDS slice holds: first the larger ones
-// (whole shapes from the back of the level's stretch of list_whole, then slices), which take
-// longest, then the small whole shapes, which fill the gaps at the end.  T threads per item: one
-// wave when the level has enough items to fill the chip, four when it has few (then an item's
-// tasks are spread over more lanes).
-template <int T>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(1, 4))) void fill_kernel(
-    const DevParams* __restrict__ P, const uint32_t* __restrict__ list_whole, uint32_t n_stretch, uint32_t n_bigwhole,
-    const uint32_t* __restrict__ list_slice, uint32_t n_slice, uint32_t cap, uint64_t* __restrict__ cost,
-    uint16_t* __restrict__ arg, Counters* __restrict__ ctr) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const uint32_t n_big = n_bigwhole + n_slice;
-  uint32_t shape, pass0 = 0, np = P->npass;
-  if (blockIdx.x < n_bigwhole) {
-    shape = list_whole[n_stretch - 1u - blockIdx.x];
-  } else if (blockIdx.x < n_big) {
-    const uint32_t unit = list_slice[blockIdx.x - n_bigwhole];
-    shape = unit / P->npass; pass0 = unit - shape * P->npass; np = 1;
-  } else {
-    shape = list_whole[blockIdx.x - n_big];
-  }
-  Shape S;
-  load_shape(P, shape, S);
-  const UnitLds L = carve(smem, cap, P->npass);
-  Eval tot;
-  tot.n = 0; tot.ovf = 0;
-  solve_unit<T>(P, L, cap, S, shape, pass0, np, cost, arg, tot);
-  flush_counters(ctr, tot);
+// What an alloc-binding costs beside its body (Section 2, Memory Movement; Section 3): m(src) +
+// m(dest) in cache lines, the load Move Spec and, for the accumulated output, the store Move Spec,
+// both of fresh tensors.  It depends on the operand's size, the two levels, the two layouts and the
+// data types only, so it is tabulated once per table instead of being gathered for every Spec.
+// [read only, accumulated][rows][columns][data types][level pair][layout before][layout after];
+// kInf: no such Move; kLimit: the sum reaches 2^62.
+__device__ __forceinline__ uint64_t add_or_limit(uint64_t a, uint64_t b) {
+  return (a >= kLimit || b >= kLimit || a + b >= kLimit) ? kLimit : a + b;
 }
 
-// The slices too large for a wave's LDS slice: one workgroup of TB threads each (kBigBlock, or
-// twice as many on levels with so few of them that most compute units would hold one or none).
-template <int TB>
-__global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(1, 4))) void fill_big_kernel(const DevParams* __restrict__ P,
-                                                             const uint32_t* __restrict__ list_wide, uint32_t cap,
-                                                             uint64_t* __restrict__ cost, uint16_t* __restrict__ arg,
-                                                             Counters* __restrict__ ctr) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const UnitLds L = carve(smem, cap, P->npass);
-  Eval tot;
-  tot.n = 0; tot.ovf = 0;
-  const uint32_t unit = list_wide[blockIdx.x];
-  const uint32_t shape = unit / P->npass, pass = unit % P->npass;
-  Shape S;
-  load_shape(P, shape, S);
-  solve_unit<TB>(P, L, cap, S, shape, pass, 1, cost, arg, tot);
-  flush_counters(ctr, tot);
+__global__ __launch_bounds__(256) void bind_kernel(const DevParams* __restrict__ P, uint64_t* __restrict__ bind, uint32_t n) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t yb = P->yb, NL = P->NL;
+  uint32_t r = i;
+  const uint32_t y1 = r & ((1u << yb) - 1u); r >>= yb;
+  const uint32_t y0 = r & ((1u << yb) - 1u); r >>= yb;
+  const uint32_t pr = r % 6u; r /= 6u;
+  const uint32_t dc = r % P->bind_d; r /= P->bind_d;
+  const uint32_t ci = r % P->nszV; r /= P->nszV;
+  const uint32_t ri = r % P->nszV, rmw = r / P->nszV;
+  const uint32_t src = pr < 1 ? 1u : pr < 3 ? 2u : 3u, dst = pr - src * (src - 1u) / 2u;
+  uint64_t out = kInf;
+  if (src < NL && (y0 < 2 || P->xw == 4) && (y1 < 2 || P->xw == 4)) {
+    const uint32_t bf = dc ? 1u : 0u, child_bf = dc == 1 ? 1u : 0u;
+    const uint64_t numel = (uint64_t)P->sizes[1][ri] * P->sizes[3][ci], line = P->line_bytes;
+    const uint64_t lines_s = (numel * (bf ? 2u : 4u) + line - 1) / line, lines_d = (numel * (child_bf ? 2u : 4u) + line - 1) / line;
+    const uint64_t groupV = (uint64_t)(ri * P->nszV + ci) * P->GV;
+    // both tensors fresh: every physical dimension adjacent, aligned
+    const uint32_t top0 = y0 >= 2 ? 3u : 2u, top1 = y1 >= 2 ? 3u : 2u;
+    const uint32_t q_load = top0 * P->limV_stride[0] + P->limV_stride[1] + top1 * P->limV_stride[2] + P->limV_stride[3];
+    const uint32_t q_store = top1 * P->limV_stride[0] + P->limV_stride[1] + top0 * P->limV_stride[2] + P->limV_stride[3];
+    auto variant = [&](uint32_t ys, uint32_t yd, uint32_t fs, uint32_t fd) {
+      return (P->layV[0] != kNoBit ? ys << P->layV[0] : 0u) + (P->layV[1] != kNoBit ? yd << P->layV[1] : 0u) +
+             (P->dtV[0] != kNoBit ? fs << P->dtV[0] : 0u) + (P->dtV[1] != kNoBit ? fd << P->dtV[1] : 0u);
+    };
+    const uint64_t c_load = P->costM[groupV + ((src * NL + dst) * P->QV + q_load) * P->VV + variant(y0, y1, bf, child_bf)];
+    const uint64_t c_store = rmw ? P->costM[groupV + ((dst * NL + src) * P->QV + q_store) * P->VV + variant(y1, y0, child_bf, bf)] : 0;
+    if (c_load != kInf && c_store != kInf) {
+      out = add_or_limit(mul_or_limit(lines_s, P->weight[src]), mul_or_limit(lines_d, P->weight[dst]));
+      out = add_or_limit(add_or_limit(out, c_load), c_store);
+    }
+  }
+  bind[i] = out;
 }
 
 // (INF, NONE) are all-ones bytes: stream 16 bytes per lane and store over both tables.
@@ -1036,11 +1031,6 @@ void launch_fill_ones(void* p, size_t bytes, hipStream_t stream, bool short_live
   if (bytes % 16) (void)hipMemsetAsync((char*)p + n16 * 16, 0xFF, bytes % 16, stream);
 }
 
-// Tasks per LDS slice: a whole shape's group when it has at most kSmallCap entries, else
-// kSlicedCap (a smaller slice, i.e. more items in flight per CU, pays once shapes are split into
-// passive-level slices anyway: measured 256 < 320 < 192 < 512 < 128 on the fused lattice).
-uint32_t fill_wave_cap(uint32_t G) { return G <= kSmallCap ? G : kSlicedCap; }
-
 // ---------------------------------------------------------------- memory bounds as coordinates
 // Sections 2.2 and 2.4.4: a Spec carries, per level of finite capacity, the bytes an implementation
 // may still allocate there; a Move allocates the moved operand's buffer in its destination, so it
@@ -1056,17 +1046,10 @@ uint32_t fill_wave_cap(uint32_t G) { return G <= kSmallCap ? G : kSlicedCap; }
 // variant), variant fastest.  A bufferize (fused Spec) allocates the intermediate in its level:
 // it needs 4 * m * n bytes of that level's bound, and both stages get the rest, rounded down.
 //
-// The same kernel fills two further kinds of lattice, which also are gathers from finished
-// entries.  Move Specs (Section 2.2; kind kKindV): two tensors, no Move rewrites; where a bounded
-// lattice has its bounds they have the abstract values of Section 2.4.3 (contiguousness and
-// aligned flag of source and destination), which a tile changes and the vector-move microkernels
-// test.  And the Matmul whose Moves are Move Specs (Section 2, Memory Movement; Section 3): the
-// plain Matmul Specs with their admissibility test, where a Move costs m(src) + m(dest) in cache
-// lines plus the load and store Move Specs, read from the Move table.
-__device__ __forceinline__ uint64_t add_or_limit(uint64_t a, uint64_t b) {
-  return (a >= kLimit || b >= kLimit || a + b >= kLimit) ? kLimit : a + b;
-}
-
+// Move Specs (Section 2.2; kind kKindV) are also gathers from finished entries: two tensors, no
+// Move rewrites; where a bounded lattice has its bounds they have the abstract values of Section
+// 2.4.3 (contiguousness and aligned flag of source and destination), which a tile changes and the
+// vector-move microkernels test.
 // ---- a wave per stretch of one (shape, level assignment)
 // What the candidates of a Spec are (which Moves and tiles exist, their constants, the groups their
 // sub-Specs lie in, the bytes a Move allocates) depends on the shape and the level assignment only;
@@ -1125,8 +1108,6 @@ struct UnitMove {
   uint32_t vxor, vclear, need;         // variant of the body = (variant ^ vxor) & ~vclear; lanes with the bit `need` only (0: all)
   uint32_t half;                       // variant bit that says the moved operand has 2 bytes per element (0: never, ~0: always)
 };
-
-__device__ __forceinline__ uint32_t lane_of(uint32_t v, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane); }
 
 // MODE 0: memory bounds as coordinates; 1: Move Specs (no Moves: all level assignments of a
 // dependency level of shapes in one launch, and the segments' rank is not used).  R: entries per
@@ -1444,14 +1425,12 @@ __global__ __launch_bounds__(256) void fill_units_kernel(const DevParams* __rest
   if (ovf) atomicOr(&ctr->overflow, 1u);
 }
 
-// A lane per Spec.  MODE 0: memory bounds as coordinates, with fewer than kUnitLanes entries per level
-// assignment; 2: the Matmul whose Moves are Move Specs.
-template <int MODE>
+// A lane per Spec: bounded lattices with fewer than kUnitLanes entries per level assignment.
 __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __restrict__ P,
                                                            const uint32_t* __restrict__ all_level_shapes, const BoundSegs segs,
                                                            uint64_t* cost, uint16_t* __restrict__ arg,
                                                            Counters* __restrict__ ctr) {
-  __shared__ uint32_t wave_n[4], wave_adm[4];
+  __shared__ uint32_t wave_n[4];
   uint32_t seg = 0;
   while (seg + 1 < segs.n && blockIdx.x >= segs.block0[seg + 1]) seg++;
   const uint32_t rank = segs.rank[seg], n_level_shapes = segs.n_shapes[seg];
@@ -1463,7 +1442,6 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
   const bool active = t < per_shape * n_level_shapes;
   Eval e;
   e.best = kInf; e.arg = kNone; e.n = 0; e.ovf = 0;
-  uint32_t n_adm = 0;
   if (active) {
     // (an active lane's index is below the number of Specs of the lattice, which fits 32 bits)
     const uint32_t sl = (uint32_t)t / (uint32_t)per_shape;
@@ -1490,34 +1468,6 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
     }
     const uint64_t group = (uint64_t)shape * P->G;
     const uint32_t off = ((combo * npass + pass) * Q + q) * V + v;
-    constexpr bool moves = MODE == 2;
-
-    // Where Moves are Specs the lattice is the plain Matmul's: a Spec whose operands do not fit
-    // their levels has no implementation and evaluates nothing.
-    bool admissible = true;
-    const auto layout_of = [&](int i) { return P->lay_bit[i] != kNoBit ? (v >> P->lay_bit[i]) & ((1u << P->lay_w[i]) - 1u) : 0u; };
-    if (moves) {
-      if (P->xw == 4) {
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-          const uint32_t cols = (uint32_t)(i == 0 ? S.d[2] : S.d[3]);
-          admissible = admissible && (layout_of(i) < 2 || cols % P->strip == 0);      // whole tensors: whole strips
-        }
-      }
-#pragma unroll
-      for (int l = 0; l < 4; l++) {
-        uint64_t bytes = 0;
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-          const uint32_t bf = P->dt_bit[i] != kNoBit ? (v >> P->dt_bit[i]) & 1u : P->base_bf16[i];
-          bytes += lv[i] == (uint32_t)l ? S.numel[i] * (bf ? 2u : 4u) : 0u;
-        }
-        admissible = admissible && ((uint32_t)l >= P->NL || bytes <= P->cap[l]);
-      }
-      n_adm = admissible ? 1u : 0u;
-    }
-    if (admissible) {
-
     // microkernels
     const uint32_t mm = P->mk_entry[pack * V + v];
     for (uint32_t j = 0; j < P->nmk; j++) {
@@ -1537,59 +1487,12 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
       const bool has_dt = P->dt_bit[i] != kNoBit, has_lay = P->lay_bit[i] != kNoBit;
       const uint32_t bf = has_dt ? (v >> P->dt_bit[i]) & 1u : P->base_bf16[i];
       const uint64_t numel = S.numel[i];
-      // cache lines of the operand as f32 and as bf16 (Section 3, m(t)), once per operand
-      uint64_t lines_f32 = 0, lines_bf16 = 0;
-      if (moves) {
-        const uint64_t line = P->line_bytes;
-        if (P->line_mask || line == 1) {
-          const uint32_t sh = 31u - (uint32_t)__clz((int)P->line_bytes);
-          lines_f32 = (numel * 4u + line - 1) >> sh; lines_bf16 = (numel * 2u + line - 1) >> sh;
-        } else {
-          lines_f32 = (numel * 4u + line - 1) / line; lines_bf16 = (numel * 2u + line - 1) / line;
-        }
-      }
       for (uint32_t dst = 0; dst < src; dst++)
-        for (uint32_t x = 0; x < (moves ? P->xw : 2u); x++)          // the Move leaves the operand in layout (its own) xor x
+        for (uint32_t x = 0; x < 2; x++)
           for (uint32_t cv = 0; cv < 2; cv++) {
             if (x && !has_lay) continue;
-            if (x >= 2 && P->lay_w[i] != 2) continue;
             if (cv && !(P->can_convert[i] && has_dt && bf)) continue;
             const uint32_t child_bf = cv ? 0u : bf;
-            if (moves) {
-              // the alloc-binding: m(src) + m(dest), the load Move Spec (operands that are read), the
-              // body, the store Move Spec (operands that are written); the operand is rows x cols
-              const uint32_t ri = i == 1 ? S.si[2] : S.si[1], ci = i == 0 ? S.si[2] : S.si[3];
-              const uint64_t groupV = (uint64_t)(ri * P->nszV + ci) * P->GV;
-              const uint32_t y0 = layout_of(i), y1 = y0 ^ x;
-              // both tensors fresh: every physical dimension adjacent, aligned
-              const uint32_t top0 = y0 >= 2 ? 3u : 2u, top1 = y1 >= 2 ? 3u : 2u;
-              const uint32_t q_load = top0 * P->limV_stride[0] + P->limV_stride[1] + top1 * P->limV_stride[2] + P->limV_stride[3];
-              const uint32_t q_store = top1 * P->limV_stride[0] + P->limV_stride[1] + top0 * P->limV_stride[2] + P->limV_stride[3];
-              auto variantV = [&](uint32_t ys, uint32_t yd, uint32_t fs, uint32_t fd) {
-                return (P->layV[0] != kNoBit ? ys << P->layV[0] : 0u) + (P->layV[1] != kNoBit ? yd << P->layV[1] : 0u) +
-                       (P->dtV[0] != kNoBit ? fs << P->dtV[0] : 0u) + (P->dtV[1] != kNoBit ? fd << P->dtV[1] : 0u);
-              };
-              uint64_t c_load = 0, c_store = 0;
-              if (P->access[i] != kWrite)
-                c_load = P->costM[groupV + ((src * P->NL + dst) * P->QV + q_load) * P->VV + variantV(y0, y1, bf, child_bf)];
-              if (P->access[i] != kRead)
-                c_store = P->costM[groupV + ((dst * P->NL + src) * P->QV + q_store) * P->VV + variantV(y1, y0, child_bf, bf)];
-              const uint32_t combo_c = combo - (src - dst) * P->lvpow[i];
-              uint32_t v_c = v ^ (x ? x << P->lay_bit[i] : 0u);
-              if (cv) v_c &= ~(1u << P->dt_bit[i]);
-              const uint64_t sub = cost[group + (uint64_t)((combo_c * npass + pass) * Q + q) * V + v_c];
-              const uint64_t lines_s = bf ? lines_bf16 : lines_f32, lines_d = child_bf ? lines_bf16 : lines_f32;
-              const uint32_t ws = src == 1 ? P->weight[1] : src == 2 ? P->weight[2] : P->weight[3];
-              const uint32_t wd = dst == 0 ? P->weight[0] : dst == 1 ? P->weight[1] : P->weight[2];
-              const uint32_t id = P->move_base + (((uint32_t)i * (P->NL - 1u) + dst) * P->xw + x) * 2u + cv;
-              if (sub != kInf && c_load != kInf && c_store != kInf) {
-                uint64_t tot = add_or_limit(mul_or_limit(lines_s, ws), mul_or_limit(lines_d, wd));
-                tot = add_or_limit(add_or_limit(tot, c_load), add_or_limit(c_store, sub));
-                if (tot >= kLimit) e.ovf = 1; else consider(e, tot, id);
-              }
-              e.n++;
-              continue;
-            }
             const uint32_t coef = P->mcoef[i][src][dst][x];
             if (!coef) continue;
             uint32_t qc = q;
@@ -1671,24 +1574,20 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
         e.n++;
       }
     }
-    }   // admissible
     cost[group + off] = e.best;
     arg[group + off] = (uint16_t)e.arg;
   }
-  // rewrites evaluated (and Specs that fit): one atomic each per workgroup
+  // rewrites evaluated: one atomic per workgroup
   uint32_t n_rw = e.n;
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {
     n_rw += __shfl_down(n_rw, d, 64);
-    if (MODE != 0) n_adm += __shfl_down(n_adm, d, 64);
   }
-  if ((threadIdx.x & 63u) == 0) { wave_n[threadIdx.x >> 6] = n_rw; wave_adm[threadIdx.x >> 6] = n_adm; }
+  if ((threadIdx.x & 63u) == 0) wave_n[threadIdx.x >> 6] = n_rw;
   __syncthreads();
   if (threadIdx.x == 0) {
     const uint32_t n = wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
     if (n) atomicAdd(&ctr->n_rewrites[blockIdx.x % kCtrSlots], (unsigned long long)n);
-    const uint32_t na = wave_adm[0] + wave_adm[1] + wave_adm[2] + wave_adm[3];
-    if (MODE != 0 && na) atomicAdd(&ctr->n_admissible[blockIdx.x % kCtrSlots], (unsigned long long)na);
   }
   if (e.ovf) atomicOr(&ctr->overflow, e.ovf);
 }
@@ -1703,47 +1602,85 @@ void launch_fill_bounded(const DevParams* P, int mode, bool units, const uint32_
   else if (mode == 1) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<1, 1>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
   else if (units && two) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<0, 2>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
   else if (units) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_units_kernel<0, 1>), grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
-  else if (mode == 2) hipLaunchKernelGGL(fill_bounded_kernel<2>, grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
-  else hipLaunchKernelGGL(fill_bounded_kernel<0>, grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
+  else hipLaunchKernelGGL(fill_bounded_kernel, grid, dim3(256), 0, stream, P, all_level_shapes, segs, cost, arg, ctr);
 }
 
 // (a lane's offset inside a unit is 32 bits of bytes)
 bool fill_by_units(int mode, uint64_t qv) { return mode == 1 || (mode == 0 && qv >= kUnitLanes && qv < (1ull << 29)); }
 
-void launch_plan(const DevParams* P, uint32_t n_shapes, uint32_t npass, uint32_t G, const uint32_t* level_shapes,
-                 const uint32_t* level_off, uint32_t n_levels, uint32_t* shape_class, uint32_t* list_whole,
-                 uint32_t* list_slice, uint32_t* list_wide, uint32_t* list_cnt, uint32_t* fitmap, Counters* ctr,
-                 void* prefill_cost, void* prefill_arg, hipStream_t stream) {
-  const uint32_t cap = fill_wave_cap(G);
-  hipLaunchKernelGGL(plan_kernel, dim3((n_shapes + 4 * kPlanShapes - 1) / (4 * kPlanShapes)), dim3(256), 0, stream, P,
-                     n_shapes, cap, cap, kWaveCap < cap ? kWaveCap : cap, shape_class, fitmap, ctr, (uint4*)prefill_cost,
-                     (uint4*)prefill_arg);
-  hipLaunchKernelGGL(sort_work_kernel, dim3(n_levels), dim3(kSortThreads), 0, stream, level_shapes, level_off, n_levels, npass,
-                     shape_class, list_whole, list_slice, list_wide, list_cnt);
+// ---------------------------------------------------------------- launches
+// Items of at most this many tasks go into bundles: everything where a whole shape is that small.
+uint32_t fill_small_max(uint32_t max_task) { return max_task <= 512 ? max_task : 256; }
+
+// Items per bundle at most (the tables of Move costs of packed layouts are large).
+static uint32_t fill_items(const DevParams& P) { return P.moves ? 4u : 8u; }
+
+static FillGeom fill_geom(const DevParams& P, uint32_t max_task, bool wide) {
+  FillGeom g;
+  g.ni = wide ? 1u : fill_items(P);
+  g.cap = wide ? max_task : kBundle + fill_small_max(max_task);
+  g.kt = wide ? 64u : 24u;
+  g.bt = P.moves ? P.bind_d * 3u * (6u << (2 * P.yb)) : (P.ndt ? 2u : 1u) * P.nops * (P.nlay ? 18u : 9u);
+  g.isz = (1u << P.ndt) << (2 * P.nops);
+  g.nlay = P.nlay;
+  const uint32_t entries = (P.ncombo << P.ndt) * g.ni;
+  g.ns = P.moves ? (g.cap < entries ? g.cap : entries) : g.cap >> P.nlay;
+  return g;
 }
 
-// One dependency level: the items an LDS slice holds, and the wide ones (independent of each other:
-// the caller may give them a stream of their own).  list_whole: the level's stretch of n_stretch
-// entries, n_small small shapes at its front and n_bigwhole others at its back.
-void launch_fill_level(const DevParams* P, uint32_t npass, uint32_t G, uint32_t max_task, const uint32_t* list_whole,
-                       uint32_t n_stretch, uint32_t n_small, uint32_t n_bigwhole, const uint32_t* list_slice,
-                       uint32_t n_slice, const uint32_t* list_wide, uint32_t n_wide, uint64_t* cost, uint16_t* arg,
-                       Counters* ctr, hipStream_t stream, hipStream_t wide_stream) {
-  const uint32_t cap = fill_wave_cap(G), n = n_bigwhole + n_slice + n_small;
-  static const uint32_t wide_below = getenv("MRL_WIDE_BELOW") ? (uint32_t)atoi(getenv("MRL_WIDE_BELOW")) : kWideBelow;
-  static const uint32_t big2_below = getenv("MRL_BIG2_BELOW") ? (uint32_t)atoi(getenv("MRL_BIG2_BELOW")) : 0u;
-  if (n >= wide_below)
-    hipLaunchKernelGGL(fill_kernel<64>, dim3(n), dim3(64), unit_lds_bytes(cap, npass), stream, P, list_whole, n_stretch,
-                       n_bigwhole, list_slice, n_slice, cap, cost, arg, ctr);
-  else if (n)
-    hipLaunchKernelGGL(fill_kernel<256>, dim3(n), dim3(256), unit_lds_bytes(cap, npass), stream, P, list_whole, n_stretch,
-                       n_bigwhole, list_slice, n_slice, cap, cost, arg, ctr);
-  if (n_wide && n_wide < big2_below)
-    hipLaunchKernelGGL(fill_big_kernel<2 * kBigBlock>, dim3(n_wide), dim3(2 * kBigBlock), unit_lds_bytes(max_task, npass), wide_stream, P,
-                       list_wide, max_task, cost, arg, ctr);
-  else if (n_wide)
-    hipLaunchKernelGGL(fill_big_kernel<kBigBlock>, dim3(n_wide), dim3(kBigBlock), unit_lds_bytes(max_task, npass), wide_stream, P,
-                       list_wide, max_task, cost, arg, ctr);
+// Workgroups of the sort kernels: the levels' tiles.
+static uint32_t sort_tiles(const uint32_t* level_off, uint32_t n_levels, uint32_t npass) {
+  uint32_t n = 0;
+  for (uint32_t l = 0; l < n_levels; l++) n += ((level_off[l + 1] - level_off[l]) * npass + kSortTile - 1) / kSortTile;
+  return n;
+}
+size_t plan_bytes_recs(uint32_t n_shapes) { return (size_t)n_shapes * sizeof(ShapeRec); }
+size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass) { return (size_t)sort_tiles(level_off, n_levels, npass) * 32 + 16; }
+
+void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint32_t max_task, const uint32_t* level_shapes,
+                 const uint32_t* level_off, const uint32_t* h_level_off, uint32_t n_levels, const PlanBuffers& B, uint32_t* fitmap, Counters* ctr,
+                 void* prefill_cost, void* prefill_arg, hipStream_t stream) {
+  hipLaunchKernelGGL(plan_kernel, dim3((n_shapes + 4 * kPlanShapes - 1) / (4 * kPlanShapes)), dim3(256), 0, stream, P,
+                     n_shapes, level_shapes, (ShapeRec*)B.recs, B.masks, B.item_tasks, fitmap, ctr, (uint4*)prefill_cost, (uint4*)prefill_arg);
+  const uint32_t tiles = sort_tiles(h_level_off, n_levels, h.npass), small_max = fill_small_max(max_task), min_weight = kBundle / fill_items(h);
+  uint4* parts = (uint4*)B.sort_tmp;
+  uint32_t* sums = tiles > n_levels ? (uint32_t*)(parts + tiles) : nullptr;
+  if (sums) {
+    hipLaunchKernelGGL(sort_sums_kernel, dim3(tiles), dim3(kSortThreads), 0, stream, level_off, h.npass, B.item_tasks, small_max, sums);
+    hipLaunchKernelGGL(sort_work_kernel, dim3(tiles), dim3(kSortThreads), 0, stream, level_off, n_levels, h.npass, B.item_tasks, small_max,
+                       min_weight, 0u, sums, parts, B.list_small, B.bundle_first, B.list_wide, B.list_cnt);
+  }
+  hipLaunchKernelGGL(sort_work_kernel, dim3(tiles), dim3(kSortThreads), 0, stream, level_off, n_levels, h.npass, B.item_tasks, small_max,
+                     min_weight, 1u, sums, parts, B.list_small, B.bundle_first, B.list_wide, B.list_cnt);
+}
+
+void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream) {
+  hipLaunchKernelGGL(bind_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, P, bind, n);
+}
+
+template <int T>
+static void launch_items(const DevParams* P, const DevParams& h, const FillGeom& g, uint32_t n, const uint32_t* items, const uint32_t* starts,
+                         const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
+  FillLds L;
+  const uint32_t lds = carve_fill(nullptr, g, h.moves != 0, L);
+  const ShapeRec* recs = (const ShapeRec*)B.recs;
+  if (h.moves) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, true>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+  else if (h.nlay) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+  else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, false, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+}
+
+// The bundles of one dependency level (starts = nullptr: every item is a bundle of its own).
+void launch_fill_level(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const uint32_t* starts,
+                       const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
+  if (!n) return;
+  const FillGeom g = fill_geom(h, max_task, false);
+  if (n >= kMinBundles) launch_items<128>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
+  else launch_items<256>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
+}
+// Its wide items.
+void launch_fill_wide(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const PlanBuffers& B,
+                      uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
+  if (n) launch_items<512>(P, h, fill_geom(h, max_task, true), n, items, nullptr, B, cost, arg, ctr, stream);
 }
 
 }  // namespace mrl

@@ -246,6 +246,39 @@ def test_parity_parallel_loops_with_layout_and_dtype_bits():
     assert e.value.code == B.E_INVAL
 
 
+@pytest.mark.parametrize("case", ["two-levels-40-sizes", "three-levels-dtypes", "fused-three-levels", "one-item-per-level"])
+def test_parity_bundles_of_items(case):
+    """Level assignments of 8, 27 x 4 dtypes and 81, several items per workgroup, dependency levels
+    with more items than one workgroup of the list building takes, and lattices with one item per level."""
+    if case == "two-levels-40-sizes":
+        cfg = W.config(1)
+        r = list(range(1, 41))
+        cfg["lattices"][0][1]["sizes"][1:] = [r, r, r]
+    elif case == "one-item-per-level":
+        cfg = W.config(4)
+        p2 = [1, 2, 4, 8, 16, 32, 64, 128]
+        cfg["lattices"][0][1]["sizes"] = [[1], p2, [1], [1]]
+    else:
+        caps = (40, 300, W.UNBOUNDED)
+        t = W._empty_target(3, caps)
+        for src in range(1, 3):
+            for dst in range(src):
+                t["load_coef"][src][dst] = [src + dst, 2 * src + 1]
+                t["store_coef"][dst][src] = [src, src + 3]
+        t["convert_coef"], t["loop_overhead"], t["zero_coef"] = 2, 1, [1, 2, 3, 0]
+        t["microkernels"] = [(W.MK_SCALAR_FMA, 1, 2), (W.MK_BCAST_VEC_MULADD, 2, 3), (W.MK_SCALAR_ADDRELU, 1, 1)]
+        r = [1, 2, 3, 4, 6, 8, 12, 24]
+        if case == "three-levels-dtypes":
+            lats = [("M", W._lattice(W.KIND_MATMUL_ACCUM, [[1, 2], r, r, r], layout=(1, 0, 1, 0, 0), dtype=(1, 1, 0, 0, 0),
+                                     base_bytes=(2, 2, 4, 4, 4)), [])]
+        else:
+            lats = [("M", W._lattice(W.KIND_MATMUL_ACCUM, [[1], r, r, r], layout=(1, 1, 1, 0, 0)), []),
+                    ("E", W._lattice(W.KIND_BIAS_ADD_RELU, [[1], r, [1], r], layout=(1, 0, 1, 0, 0)), []),
+                    ("F", W._lattice(W.KIND_FUSED_MM_ADD_RELU, [[1], r, r, r], layout=(1, 1, 0, 1, 0)), ["M", "E"])]
+        cfg = {"name": case, "target": t, "lattices": lats}
+    compare_config(cfg)
+
+
 def two_level_bounded(caps, sizes):
     cfg = W.config(1, seed=11, max_size=4)
     t = cfg["target"]
