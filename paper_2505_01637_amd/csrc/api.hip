@@ -508,7 +508,11 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
 
 
 // compile() costs a few hundred microseconds for the larger lattices; repeated solves of the
-// same (target, lattice) reuse the result.  Entries are immutable once published.
+// same (target, lattice) reuse the result.  Entries are immutable once published.  kCompiledMost of
+// them, the least recently used goes first: a program that takes turns between a few targets keeps
+// all of its lattices (config 5 has three; with 8 entries, first in first out, three targets in turn
+// compiled all of them in every step: 6.8 instead of 5.4 ms).
+constexpr size_t kCompiledMost = 32;
 using CompiledPtr = std::shared_ptr<const Compiled>;
 
 bool same_problem(const Compiled& c, const mrl_target_desc& T, const mrl_lattice_desc& L) {
@@ -526,17 +530,21 @@ bool same_problem(const Compiled& c, const mrl_target_desc& T, const mrl_lattice
 
 int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, CompiledPtr& out) {
   static std::mutex mu;
-  static std::vector<CompiledPtr> cache;          // most recent last, at most 8
+  static std::vector<CompiledPtr> cache;          // most recently used last
   if (L && L->kind <= MRL_KIND_BIAS_ADD_RELU_SPLIT) {
     std::lock_guard<std::mutex> lock(mu);
     for (size_t i = cache.size(); i-- > 0;)
-      if (same_problem(*cache[i], T, *L)) { out = cache[i]; return MRL_OK; }
+      if (same_problem(*cache[i], T, *L)) {
+        std::rotate(cache.begin() + i, cache.begin() + i + 1, cache.end());
+        out = cache.back();
+        return MRL_OK;
+      }
   }
   auto c = std::make_shared<Compiled>();
   const int32_t rc = compile(T, L, *c);
   if (rc) return rc;
   std::lock_guard<std::mutex> lock(mu);
-  if (cache.size() >= 8) cache.erase(cache.begin());
+  if (cache.size() >= kCompiledMost) cache.erase(cache.begin());
   cache.push_back(c);
   out = c;
   return MRL_OK;
