@@ -55,7 +55,7 @@ constexpr uint64_t kStretch = 8;            // a wave of fill_units_kernel takes
 constexpr uint64_t kFullWaves = 4096;       // more than one only where this many waves are left: its candidates' constants
                                             // cost a wave as much as two steps do (config 7's fill: stretch 4 and 16384
                                             // waves 1.17 ms, 4 and 8192 1.04, 8 and 4096 1.00, 16 and 2048 1.04)
-constexpr uint32_t kLookupChunk = 65536;   // points per launch of a lookup in the box lists
+constexpr uint32_t kLookupChunk = 32768;   // points per launch of a lookup in the box lists
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Host-side compiled lattice: everything derived from (target, lattice).
@@ -600,6 +600,68 @@ int32_t get_aux(size_t n_events, AuxLease& lease) {
   return MRL_OK;
 }
 
+// Pinned host memory through which a call exchanges data with the GPU, in two halves: the kernels
+// read and write it in place (no copy commands), one half while the host works on the other.
+// Blocks are kept for the next call, at most kStageKeep of them idle.
+constexpr size_t kStageHalf = 1310720;
+constexpr size_t kStageKeep = 4;
+std::mutex g_stage_mu;
+std::vector<char*> g_stage_idle;
+
+struct StageLease {
+  char* mem = nullptr;
+  ~StageLease() {
+    if (!mem) return;
+    {
+      std::lock_guard<std::mutex> lock(g_stage_mu);
+      if (g_stage_idle.size() < kStageKeep) {          // (room for kStageKeep is reserved below)
+        g_stage_idle.push_back(mem);
+        return;
+      }
+    }
+    (void)hipHostFree(mem);
+  }
+  char* half(size_t i) const { return mem + (i & 1) * kStageHalf; }
+};
+
+int32_t get_stage(StageLease& lease) {
+  {
+    std::lock_guard<std::mutex> lock(g_stage_mu);
+    g_stage_idle.reserve(kStageKeep);
+    if (!g_stage_idle.empty()) {
+      lease.mem = g_stage_idle.back();
+      g_stage_idle.pop_back();
+      return MRL_OK;
+    }
+  }
+  HIP_TRY(hipHostMalloc((void**)&lease.mem, 2 * kStageHalf, hipHostMallocPortable | hipHostMallocMapped));
+  return MRL_OK;
+}
+
+// Take n items through the GPU, `chunk` at a time, on `stream`: fill(first, m, half) writes a chunk's
+// inputs, launch(first, m, half) queues its kernels and drain(first, m, half) takes its results.  While
+// the GPU has one chunk the host drains the one before it and fills the next.  When this returns,
+// with or without an error, nothing queued here is still running.
+template <class Fill, class Launch, class Drain>
+int32_t take_through(size_t n, size_t chunk, const StageLease& stage, hipStream_t stream, Fill&& fill, Launch&& launch, Drain&& drain) {
+  const size_t n_chunks = (n + chunk - 1) / chunk;
+  auto items = [&](size_t i) { return (uint32_t)std::min(chunk, n - i * chunk); };
+  for (size_t i = 0; i <= n_chunks; i++) {
+    int32_t rc = i < n_chunks ? fill(i * chunk, items(i), stage.half(i)) : MRL_OK;
+    if (i > 0) HIP_TRY(hipStreamSynchronize(stream));
+    if (rc) return rc;
+    if (i < n_chunks) {
+      launch(i * chunk, items(i), stage.half(i));
+      HIP_TRY(hipGetLastError());
+    }
+    if (i > 0 && (rc = drain((i - 1) * chunk, items(i - 1), stage.half(i - 1)))) {
+      (void)hipStreamSynchronize(stream);
+      return rc;
+    }
+  }
+  return MRL_OK;
+}
+
 }  // namespace
 
 struct mrl_table {
@@ -614,16 +676,14 @@ struct mrl_table {
   // final lists inside scratch: [0] decisions, [1] costs
   size_t list_off[2];
   uint64_t list_n[2];
-  // Lookups in the box lists (mrl_query_compressed): bounding-box hierarchy per list and staging
-  // for one chunk of points, allocated at the first such query and freed with the table.
+  // Lookups in the box lists (mrl_query_compressed): bounding-box hierarchy per list, allocated at
+  // the first such query and freed with the table.
   struct BoxIndex { IndexLevels L; BoxBounds* nodes = nullptr; };
   mutable BoxIndex index[2];
-  mutable char* lookup_buf = nullptr;
   mutable std::mutex lookup_mu;
   mutable std::mutex query_mu;      // mrl_query stages through one area of the scratch buffer and the table's stream
   ~mrl_table() {
     for (auto& ix : index) if (ix.nodes) (void)hipFree(ix.nodes);
-    if (lookup_buf) (void)hipFree(lookup_buf);
   }
 };
 
@@ -1777,15 +1837,12 @@ int32_t mrl_query_compressed(const mrl_table* tab, const mrl_coord* specs, size_
   for (uint32_t a = 0; a < g.ndim; a++)
     if (g.ext[a] > 256) return fail(MRL_E_INVAL, "axis %u has %u coordinates: the box index holds one byte per axis", a, g.ext[a]);
   std::lock_guard<std::mutex> lock(tab->lookup_mu);
-  const uint64_t* fv[2][2];
-  const uint32_t* cells[2];
+  LookupList lists[2];
   for (uint32_t which = 0; which < 2; which++) {
     const uint64_t nb = tab->list_n[which];
     const char* r = tab->scratch + tab->list_off[which];
-    const uint32_t* fcell = cells[which] = (const uint32_t*)r; r += align_up(nb * 4);
+    const uint32_t* fcell = (const uint32_t*)r; r += align_up(nb * 4);
     const void* flen = r; r += align_up(nb * 16);
-    fv[which][0] = (const uint64_t*)r; r += align_up(nb * 8);
-    fv[which][1] = (const uint64_t*)r;
     mrl_table::BoxIndex& ix = tab->index[which];
     if (!ix.nodes) {
       ix.L = index_levels((uint32_t)nb);
@@ -1793,52 +1850,44 @@ int32_t mrl_query_compressed(const mrl_table* tab, const mrl_coord* specs, size_
       launch_build_index(g, ix.L, fcell, flen, ix.nodes, tab->stream);
       HIP_TRY(hipGetLastError());
     }
+    lists[which] = LookupList{ix.L, ix.nodes, fcell, (const uint64_t*)r, (const uint64_t*)(r + align_up(nb * 8))};
   }
-  // staging of one chunk: points, then per list v0, v1 (u64) and the box index (u32)
-  const size_t o_pts = 0, o_val = o_pts + (size_t)kLookupChunk * 16, o_which = o_val + 4 * (size_t)kLookupChunk * 8,
-               total = o_which + 2 * (size_t)kLookupChunk * 4;
-  if (!tab->lookup_buf) HIP_TRY(hipMalloc((void**)&tab->lookup_buf, total));
-  uint8_t* d_pts = (uint8_t*)(tab->lookup_buf + o_pts);
-  uint64_t* d_val = (uint64_t*)(tab->lookup_buf + o_val);
-  uint32_t* d_which = (uint32_t*)(tab->lookup_buf + o_which);
-  std::vector<uint8_t> pts((size_t)kLookupChunk * 16);
-  std::vector<uint64_t> val(4 * (size_t)kLookupChunk), vol(kLookupChunk);
-  std::vector<uint32_t> hit(2 * (size_t)kLookupChunk);
-  for (size_t done = 0; done < n; done += kLookupChunk) {
-    const uint32_t m = (uint32_t)std::min<size_t>(kLookupChunk, n - done);
-    memset(pts.data(), 0, (size_t)m * 16);
-    for (uint32_t i = 0; i < m; i++) {
-      for (uint32_t a = 0; a < g.ndim; a++) {
-        const uint32_t v = specs[done + i].x[a];
-        if (v >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", done + i, a, v, g.ext[a]);
-        pts[(size_t)i * 16 + a] = (uint8_t)v;
+  if (!n) return MRL_OK;
+  // a chunk: points (16 bytes), volumes, costs, rewrite ids, a byte per list that marks a miss
+  constexpr size_t o_vol = (size_t)kLookupChunk * 16, o_cost = o_vol + (size_t)kLookupChunk * 8, o_arg = o_cost + (size_t)kLookupChunk * 8,
+                   o_miss = o_arg + (size_t)kLookupChunk * 2;
+  static_assert(o_miss + 2 * (size_t)kLookupChunk <= kStageHalf, "a chunk fits half a staging block");
+  StageLease stage;
+  int32_t rc = get_stage(stage);
+  if (rc) return rc;
+  return take_through(n, kLookupChunk, stage, tab->stream,
+    [&](size_t first, uint32_t m, char* h) -> int32_t {
+      uint64_t* vol = (uint64_t*)(h + o_vol);
+      for (uint32_t i = 0; i < m; i++) {
+        const uint32_t* x = specs[first + i].x;
+        uint8_t p[16] = {};
+        for (uint32_t a = 0; a < g.ndim; a++) {
+          if (x[a] >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", first + i, a, x[a], g.ext[a]);
+          p[a] = (uint8_t)x[a];
+        }
+        memcpy(h + (size_t)i * 16, p, 16);
+        uint64_t w = 1;
+        for (uint32_t d = 0; d < 4; d++) w *= c.sizes[d][x[d]];
+        vol[i] = w;
       }
-      uint64_t w = 1;
-      for (uint32_t d = 0; d < 4; d++) w *= c.sizes[d][specs[done + i].x[d]];
-      vol[i] = w;
-    }
-    HIP_TRY(hipMemcpyAsync(d_pts, pts.data(), (size_t)m * 16, hipMemcpyHostToDevice, tab->stream));
-    for (uint32_t which = 0; which < 2; which++)
-      launch_lookup(g, tab->index[which].L, tab->index[which].nodes, cells[which], d_pts, m, fv[which][0], fv[which][1],
-                    d_val + (2 * which) * (size_t)kLookupChunk, d_val + (2 * which + 1) * (size_t)kLookupChunk,
-                    d_which + which * (size_t)kLookupChunk, tab->stream);
-    HIP_TRY(hipGetLastError());
-    for (uint32_t k = 0; k < 4; k++)
-      HIP_TRY(hipMemcpyAsync(val.data() + k * (size_t)kLookupChunk, d_val + k * (size_t)kLookupChunk, (size_t)m * 8,
-                             hipMemcpyDeviceToHost, tab->stream));
-    for (uint32_t k = 0; k < 2; k++)
-      HIP_TRY(hipMemcpyAsync(hit.data() + k * (size_t)kLookupChunk, d_which + k * (size_t)kLookupChunk, (size_t)m * 4,
-                             hipMemcpyDeviceToHost, tab->stream));
-    HIP_TRY(hipStreamSynchronize(tab->stream));
-    for (uint32_t i = 0; i < m; i++) {
-      if (hit[i] == 0xFFFFFFFFu || hit[kLookupChunk + i] == 0xFFFFFFFFu)
-        return fail(MRL_E_HIP, "internal error: spec %zu lies in no box", done + i);
-      rewrite_out[done + i] = (uint16_t)val[i];
-      const uint64_t v0 = val[2 * (size_t)kLookupChunk + i], v1 = val[3 * (size_t)kLookupChunk + i];
-      cost_out[done + i] = v1 == 0 ? kInf : (uint64_t)((unsigned __int128)v0 * vol[i] / v1);
-    }
-  }
-  return MRL_OK;
+      return MRL_OK;
+    },
+    [&](size_t, uint32_t m, char* h) {
+      launch_lookup(g, lists, h, (const uint64_t*)(h + o_vol), m, (uint64_t*)(h + o_cost), (uint16_t*)(h + o_arg), (uint8_t*)(h + o_miss), tab->stream);
+    },
+    [&](size_t first, uint32_t m, char* h) -> int32_t {
+      const char* miss = h + o_miss;
+      const void* bad = memchr(miss, 1, 2 * (size_t)m);
+      if (bad) return fail(MRL_E_HIP, "internal error: spec %zu lies in no box", first + (size_t)((const char*)bad - miss) % m);
+      memcpy(cost_out + first, h + o_cost, (size_t)m * 8);
+      memcpy(rewrite_out + first, h + o_arg, (size_t)m * 2);
+      return MRL_OK;
+    });
   });
 }
 

@@ -106,11 +106,17 @@ struct IndexLevels {
 IndexLevels index_levels(uint32_t n_boxes);
 void launch_build_index(const Geo& g, const IndexLevels& L, const uint32_t* fcell, const void* flen, BoxBounds* nodes,
                         hipStream_t st);
-// points: 16 bytes per point (coordinates, zero padded).  out0/out1: the value of the box that
-// holds the point; which_out: its index, 0xFFFFFFFF if none.
-void launch_lookup(const Geo& g, const IndexLevels& L, const BoxBounds* nodes, const uint32_t* fcell,
-                   const uint8_t* points, uint32_t n_points, const uint64_t* fv0, const uint64_t* fv1, uint64_t* out0,
-                   uint64_t* out1, uint32_t* which_out, hipStream_t st);
+// One of the two final lists with its index.
+struct LookupList {
+  IndexLevels L;
+  const BoxBounds* nodes;
+  const uint32_t* fcell;
+  const uint64_t *fv0, *fv1;
+};
+// lists: decisions, costs.  points: 16 bytes per point (coordinates, zero padded); vols: the volume
+// b*m*k*n of each.  miss: a byte per list and point (n_points apart), 1 where no box holds the point.
+void launch_lookup(const Geo& g, const LookupList lists[2], const void* points, const uint64_t* vols, uint32_t n_points,
+                   uint64_t* cost_out, uint16_t* arg_out, uint8_t* miss, hipStream_t st);
 
 constexpr uint32_t kScanTileItems = 2048;   // items per scan tile (tile_tmp needs n/2048 + 1 words)
 
