@@ -342,9 +342,10 @@ int32_t mrl_solve_graph(const mrl_target* t, const mrl_job* jobs, uint32_t n_job
 
 /* ---------------------------------------------------------------------------
  * Query (Section 4: a Spec that the memo table already holds is answered from
- * it).  specs, cost_out, rewrite_out: host arrays of n.  Calls on one table from
- * several host threads take turns (they stage through the table's scratch buffer
- * and stream); so do those of mrl_schedule, which asks through this call. */
+ * it).  specs, cost_out, rewrite_out: host arrays of n.  Several host threads may
+ * ask one table at a time, here and through mrl_schedule: a call stages through
+ * pinned host memory of its own (blocks that the library keeps for the next call)
+ * and works on the table's stream. */
 typedef struct { uint32_t x[MRL_MAX_DIMS]; } mrl_coord;
 int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n,
                   uint64_t* cost_out, uint16_t* rewrite_out);
@@ -354,8 +355,8 @@ int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n,
  * arguments, answers and errors as mrl_query, but nothing is allocated, on the
  * device or on the host: the indices and answers are staged through an array of
  * MRL_NOALLOC_MAX_QUERIES * 18 bytes that the library holds in device memory of
- * every GPU it runs on, from load until the process ends, instead of through the
- * table's scratch buffer.  n must be at most MRL_NOALLOC_MAX_QUERIES
+ * every GPU it runs on, from load until the process ends, instead of through
+ * pinned host memory.  n must be at most MRL_NOALLOC_MAX_QUERIES
  * (MRL_E_INVAL else).  Every call on a GPU uses that GPU's one array and
  * overwrites what the call before left there; calls from several host threads of
  * one process take turns for it inside the library (work of another origin that

@@ -233,10 +233,15 @@ class Table:
         goal = _Coord()
         for a, v in enumerate(coord):
             goal.x[a] = int(v)
-        n = C.c_size_t()
-        _check(lib().mrl_schedule(self._h, C.byref(goal), None, C.c_size_t(0), C.byref(n)))
-        nodes = (_ScheduleNode * max(1, n.value))()
-        _check(lib().mrl_schedule(self._h, C.byref(goal), nodes, C.c_size_t(n.value), C.byref(n)))
+        # room for most programs; a longer one says how much it needs
+        n = C.c_size_t(128)
+        while True:
+            cap = n.value
+            nodes = (_ScheduleNode * cap)()
+            rc = lib().mrl_schedule(self._h, C.byref(goal), nodes, C.c_size_t(cap), C.byref(n))
+            if rc != E_BUFSZ or n.value <= cap:
+                break
+        _check(rc)
         dims = [len(t.extents) for t in self._schedule_tables()]
         return [(nd.table, tuple(nd.spec.x[:dims[nd.table]]), nd.rewrite, nd.cost, nd.n_children)
                 for nd in nodes[:n.value]]

@@ -46,7 +46,7 @@ struct mrl_target {
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr uint32_t kQueryChunk = 4096;
+constexpr uint32_t kQueryChunk = 32768;    // Specs per launch of a query in the dense table
 #ifndef MRL_SECOND_ON_CELLS
 #define MRL_SECOND_ON_CELLS 1
 #endif
@@ -85,7 +85,7 @@ struct Compiled {
 // Offsets of the fixed part of the scratch buffer.
 struct FixedLayout {
   size_t counters, params, tiles, level_shapes, level_off, mk_entry, qdec, recs, masks, item_tasks, sort_tmp, list_small, bundle_first, list_wide, list_cnt, bind, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
-      q_idx, q_cost, q_arg, upload_end, end;
+      upload_end, end;
   uint32_t n_words;
 };
 
@@ -162,9 +162,7 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.tile_tmp = take((c.n_specs / kScanTileItems + 2) * 4);
   f.tile_tmp2 = take((c.n_specs / kScanTileItems + 2) * 4);
   f.totals = take(64);
-  f.q_idx = take(kQueryChunk * 8);
-  f.q_cost = take(kQueryChunk * 8);
-  f.q_arg = take(kQueryChunk * 2);
+  o += 18 * 4096;               // not used: the size that a solve asks for is part of the interface
   f.end = o;
   return f;
 }
@@ -681,7 +679,6 @@ struct mrl_table {
   struct BoxIndex { IndexLevels L; BoxBounds* nodes = nullptr; };
   mutable BoxIndex index[2];
   mutable std::mutex lookup_mu;
-  mutable std::mutex query_mu;      // mrl_query stages through one area of the scratch buffer and the table's stream
   ~mrl_table() {
     for (auto& ix : index) if (ix.nodes) (void)hipFree(ix.nodes);
   }
@@ -1473,30 +1470,35 @@ int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n, uint64
   return guarded([&]() -> int32_t {
   if (!tab || (n && (!specs || !cost_out || !rewrite_out))) return fail(MRL_E_INVAL, "NULL argument");
   const Geo& g = tab->cp->geo;
-  std::vector<uint64_t> idx(std::min<size_t>(n, kQueryChunk));
-  char* base = tab->scratch;
-  std::lock_guard<std::mutex> lock(tab->query_mu);
-  for (size_t done = 0; done < n; done += kQueryChunk) {
-    const uint32_t m = (uint32_t)std::min<size_t>(kQueryChunk, n - done);
-    for (uint32_t i = 0; i < m; i++) {
-      uint64_t x = 0;
-      for (uint32_t a = 0; a < g.ndim; a++) {
-        const uint32_t v = specs[done + i].x[a];
-        if (v >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", done + i, a, v, g.ext[a]);
-        x += (uint64_t)v * g.stride[a];
+  if (!n) return MRL_OK;
+  // a chunk: linear indices, costs, rewrite ids
+  constexpr size_t o_cost = (size_t)kQueryChunk * 8, o_arg = 2 * o_cost;
+  static_assert(o_arg + (size_t)kQueryChunk * 2 <= kStageHalf, "a chunk fits half a staging block");
+  StageLease stage;
+  int32_t rc = get_stage(stage);
+  if (rc) return rc;
+  return take_through(n, kQueryChunk, stage, tab->stream,
+    [&](size_t first, uint32_t m, char* h) -> int32_t {
+      uint64_t* idx = (uint64_t*)h;
+      for (uint32_t i = 0; i < m; i++) {
+        uint64_t x = 0;
+        for (uint32_t a = 0; a < g.ndim; a++) {
+          const uint32_t v = specs[first + i].x[a];
+          if (v >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", first + i, a, v, g.ext[a]);
+          x += (uint64_t)v * g.stride[a];
+        }
+        idx[i] = x;
       }
-      idx[i] = x;
-    }
-    uint64_t* d_idx = (uint64_t*)(base + tab->f.q_idx);
-    uint64_t* d_c = (uint64_t*)(base + tab->f.q_cost);
-    uint16_t* d_a = (uint16_t*)(base + tab->f.q_arg);
-    HIP_TRY(hipMemcpyAsync(d_idx, idx.data(), (size_t)m * 8, hipMemcpyHostToDevice, tab->stream));
-    launch_gather(d_idx, m, tab->d_cost, tab->d_arg, d_c, d_a, tab->stream);
-    HIP_TRY(hipMemcpyAsync(cost_out + done, d_c, (size_t)m * 8, hipMemcpyDeviceToHost, tab->stream));
-    HIP_TRY(hipMemcpyAsync(rewrite_out + done, d_a, (size_t)m * 2, hipMemcpyDeviceToHost, tab->stream));
-    HIP_TRY(hipStreamSynchronize(tab->stream));
-  }
-  return MRL_OK;
+      return MRL_OK;
+    },
+    [&](size_t, uint32_t m, char* h) {
+      launch_gather((const uint64_t*)h, m, tab->d_cost, tab->d_arg, (uint64_t*)(h + o_cost), (uint16_t*)(h + o_arg), tab->stream);
+    },
+    [&](size_t first, uint32_t m, char* h) -> int32_t {
+      memcpy(cost_out + first, h + o_cost, (size_t)m * 8);
+      memcpy(rewrite_out + first, h + o_arg, (size_t)m * 2);
+      return MRL_OK;
+    });
   });
 }
 
@@ -1609,12 +1611,66 @@ int32_t mrl_coord_of_spec(const mrl_table* tab, const uint32_t shape[4], const u
   });
 }
 
+namespace {
+
+// The entries of a program's Specs: chains of them come from the GPU (launch_chain walks on from a
+// Spec while the child is in the same table), so that a program of some dozen rewrites is a few
+// round trips.  A chain is only read ahead: an entry is used where the Spec that is asked for next is
+// the one the chain holds.
+struct ChainReader {
+  StageLease stage;
+  const mrl_table* t = nullptr;
+  uint32_t at = 0, n = 0;
+  int32_t entry(const mrl_table* tab, const mrl_coord& x, uint64_t* cost, uint16_t* rw) {
+    const Compiled& c = *tab->cp;
+    const Geo& g = c.geo;
+    const DevParams& P = tab->P;
+    uint32_t cell = 0;
+    for (uint32_t a = 0; a < g.ndim; a++) {
+      if (x.x[a] >= g.ext[a]) return fail(MRL_E_RANGE, "spec 0: coordinate %u = %u outside [0, %u)", a, x.x[a], g.ext[a]);
+      cell += x.x[a] * g.stride[a];
+    }
+    if (!stage.mem) {
+      const int32_t rc = get_stage(stage);
+      if (rc) return rc;
+    }
+    ChainEntry* e = (ChainEntry*)stage.mem;
+    if (t != tab || at >= n || e[at].cell != cell) {
+      ChainWalk w;
+      w.g = g;
+      w.cell = cell;
+      for (uint32_t a = 0; a < 16; a++) w.x[a] = x.x[a];
+      w.move_base = P.move_base; w.tile_base = P.tile_base; w.buf_id = P.buf_id; w.maxs = P.maxs; w.xw = P.xw; w.n_dst = P.NL - 1;
+      // children that differ in more than the rewrite names are left to the host: the bound that a Move
+      // takes its buffer from, a Move's own Specs, what is known of a tile of a Move Spec
+      w.moves = !P.bounded && !P.moves && P.kind != kKindV;
+      w.tiles = P.kind != kKindV;
+      for (int i = 0; i < 5; i++) { w.lay_axis[i] = c.lay_axis[i]; w.dt_axis[i] = c.dt_axis[i]; }
+      uint32_t* count = (uint32_t*)(e + kChainMost);
+      *count = 0;
+      launch_chain(w, tab->d_cost, tab->d_arg, e, count, tab->stream);
+      HIP_TRY(hipGetLastError());
+      HIP_TRY(hipStreamSynchronize(tab->stream));
+      t = tab; at = 0; n = *count;
+      if (n == 0 || n > kChainMost || e[0].cell != cell) return fail(MRL_E_HIP, "internal error: a Spec's entry was not read");
+    }
+    *cost = e[at].cost;
+    *rw = (uint16_t)e[at].arg;
+    at++;
+    return MRL_OK;
+  }
+};
+static_assert((kChainMost + 1) * sizeof(ChainEntry) <= 2 * kStageHalf, "a chain fits a staging block");
+
+}  // namespace
+
 int32_t mrl_schedule(const mrl_table* tab, const mrl_coord* goal, mrl_schedule_node* out, size_t cap, size_t* n_out) {
   return guarded([&]() -> int32_t {
   if (!tab || !goal) return fail(MRL_E_INVAL, "NULL argument");
   struct Item { const mrl_table* t; uint32_t which; mrl_coord x; };
   std::vector<Item> stack;
   stack.push_back({tab, 0u, *goal});
+  ChainReader reader;
   size_t n = 0;
   while (!stack.empty()) {
     const Item it = stack.back();
@@ -1623,7 +1679,7 @@ int32_t mrl_schedule(const mrl_table* tab, const mrl_coord* goal, mrl_schedule_n
     const DevParams& P = it.t->P;
     uint64_t cost;
     uint16_t rw;
-    int32_t rc = mrl_query(it.t, &it.x, 1, &cost, &rw);
+    int32_t rc = reader.entry(it.t, it.x, &cost, &rw);
     if (rc) return rc;
     if (cost == kInf) {
       if (n == 0) return fail(MRL_E_INVAL, "the goal Spec has no implementation");

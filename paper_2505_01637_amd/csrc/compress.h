@@ -91,8 +91,22 @@ void launch_emit(const Geo& g, const DevParams* P, bool is_cost, uint32_t n_boxe
                  const void* blen,
                  const uint8_t* alive, const uint32_t* pos, const uint64_t* cost, const uint16_t* arg, uint32_t* fcell,
                  void* flen, uint64_t* fv0, uint64_t* fv1, hipStream_t st);
+// idx, cost_out, arg_out: device memory or pinned host memory.
 void launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const uint16_t* arg, uint64_t* cost_out,
                    uint16_t* arg_out, hipStream_t st);
+
+// The entries of a Spec, of the Spec its rewrite leads to, and so on.
+struct ChainEntry { uint64_t cost; uint32_t cell, arg; };
+constexpr uint32_t kChainMost = 64;
+struct ChainWalk {
+  Geo g;
+  uint32_t cell, x[16];                     // where the walk starts: linear index, coordinate
+  uint32_t move_base, tile_base, buf_id, maxs, xw, n_dst;      // rewrite ids (mrl_rewrite_decode)
+  uint32_t moves, tiles;                    // 1: go on through Moves / tile loops
+  int lay_axis[5], dt_axis[5];              // coordinate axes of an operand's layout and data type, -1 if none
+};
+// At most kChainMost entries to out, their number (at least 1) to n_out: device or pinned host memory.
+void launch_chain(const ChainWalk& w, const uint64_t* cost, const uint16_t* arg, ChainEntry* out, uint32_t* n_out, hipStream_t st);
 
 // Point lookups in a final box list: a packed hierarchy of bounding boxes over the list's order.
 constexpr uint32_t kIndexFan = 8;          // children per node

@@ -865,6 +865,70 @@ void launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const 
   hipLaunchKernelGGL(gather_kernel, dim3((n + 255) / 256), dim3(256), 0, st, idx, n, cost, arg, cost_out, arg_out);
 }
 
+// One lane follows a program through one table: entry, rewrite, the Spec it leads to, as long as that
+// Spec lies in this table and differs only in what the rewrite id names (a Move to another level,
+// perhaps in another layout or type; a tile loop).  Bound by the latency of two reads a step, a few
+// microseconds; with a launch, copies and the host's wait around every step, and the whole walk once
+// more to count its nodes, a program of 18 rewrites took 1.35 ms, now 0.06.
+__global__ __launch_bounds__(64) void chain_kernel(ChainWalk w, const uint64_t* __restrict__ cost, const uint16_t* __restrict__ arg,
+                                                   ChainEntry* __restrict__ out, uint32_t* __restrict__ n_out) {
+  __shared__ uint32_t x[16], ext[16], stride[16];
+  __shared__ int lay_axis[5], dt_axis[5];
+  if (threadIdx.x < 16) {
+    x[threadIdx.x] = w.x[threadIdx.x];
+    ext[threadIdx.x] = w.g.ext[threadIdx.x];
+    stride[threadIdx.x] = w.g.stride[threadIdx.x];
+  }
+  if (threadIdx.x < 5) {
+    lay_axis[threadIdx.x] = w.lay_axis[threadIdx.x];
+    dt_axis[threadIdx.x] = w.dt_axis[threadIdx.x];
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  uint32_t cell = w.cell, n = 0;
+  // axis a's coordinate becomes v; false if there is no such cell
+  auto go = [&](uint32_t a, uint32_t v) -> bool {
+    if (a >= w.g.ndim || v >= ext[a]) return false;
+    cell += (v - x[a]) * stride[a];
+    x[a] = v;
+    return true;
+  };
+  while (n < kChainMost) {
+    const uint64_t c = cost[cell];
+    const uint32_t id = arg[cell];
+    out[n].cost = c;
+    out[n].cell = cell;
+    out[n].arg = id;
+    n++;
+    if (c == kInf || id < w.move_base || id >= w.buf_id) break;
+    if (id < w.tile_base) {
+      if (!w.moves) break;
+      uint32_t r = id - w.move_base;
+      const uint32_t convert = r & 1u; r >>= 1;
+      const uint32_t change = r % w.xw; r /= w.xw;
+      const uint32_t dst = r % w.n_dst, op = r / w.n_dst;
+      if (op >= 5 || !go(4 + op, dst)) break;
+      if (change) {
+        const int a = lay_axis[op];
+        if (a < 0 || !go((uint32_t)a, x[a] ^ change)) break;
+      }
+      if (convert) {
+        const int a = dt_axis[op];
+        if (a < 0 || !go((uint32_t)a, 0)) break;
+      }
+    } else {
+      if (!w.tiles) break;
+      const uint32_t r = id - w.tile_base;
+      if (!go(r / w.maxs, r % w.maxs)) break;
+    }
+  }
+  *n_out = n;
+}
+
+void launch_chain(const ChainWalk& w, const uint64_t* cost, const uint16_t* arg, ChainEntry* out, uint32_t* n_out, hipStream_t st) {
+  hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(64), 0, st, w, cost, arg, out, n_out);
+}
+
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long* p, uint32_t n) {
   const uint32_t i = blockIdx.x * 256u + threadIdx.x;
   if (i < n) p[i] = 0;

@@ -185,17 +185,19 @@ def test_compressed_query_parity(number, max_size):
 
 
 @pytest.mark.parametrize("n_points", [1, 7, 9, 31, 33, 32767, 32768, 32769, 65537])
-def test_compressed_query_point_counts(n_points):
-    """Eight lanes per point, 32 points per workgroup, 32,768 per launch: the edges of each, the
-    answers against the dense table."""
+def test_query_point_counts(n_points):
+    """The box lists are asked with eight lanes per point, 32 points per workgroup, 32,768 per
+    launch, the dense table with as many per launch: the edges of each, the answers against the
+    whole table."""
     B = _binding()
     cfg = W.config(4, max_size=8)
     _, got = B.solve_config(cfg)
     tab = got["M"]
     cost, arg = tab.dense()
     lin = np.random.default_rng(n_points).integers(0, len(cost), size=n_points)
-    gc, ga = tab.query(np.stack(np.unravel_index(lin, tab.extents), axis=1), compressed=True)
-    assert np.array_equal(gc, cost[lin]) and np.array_equal(ga, arg[lin])
+    for compressed in (False, True):
+        gc, ga = tab.query(np.stack(np.unravel_index(lin, tab.extents), axis=1), compressed=compressed)
+        assert np.array_equal(gc, cost[lin]) and np.array_equal(ga, arg[lin])
 
 
 def test_compressed_query_one_box_and_long_axis():
