@@ -46,6 +46,7 @@ struct mrl_target {
 namespace {
 
 constexpr size_t kAlign = 256;
+constexpr uint32_t kEmitChunk = 16384;     // boxes per launch of mrl_emit_compressed (half a staging block)
 constexpr uint32_t kQueryChunk = 32768;    // Specs per launch of a query in the dense table
 #ifndef MRL_SECOND_ON_CELLS
 #define MRL_SECOND_ON_CELLS 1
@@ -636,6 +637,20 @@ int32_t get_stage(StageLease& lease) {
   return MRL_OK;
 }
 
+// Makes a device current for a scope.
+struct OnDevice {
+  int before = -1;
+  int32_t set(int device) {
+    int now = 0;
+    HIP_TRY(hipGetDevice(&now));
+    if (now == device) return MRL_OK;
+    HIP_TRY(hipSetDevice(device));
+    before = now;
+    return MRL_OK;
+  }
+  ~OnDevice() { if (before >= 0) (void)hipSetDevice(before); }
+};
+
 // Take n items through the GPU, `chunk` at a time, on `stream`: fill(first, m, half) writes a chunk's
 // inputs, launch(first, m, half) queues its kernels and drain(first, m, half) takes its results.  While
 // the GPU has one chunk the host drains the one before it and fills the next.  When this returns,
@@ -670,6 +685,7 @@ struct mrl_table {
   uint64_t* d_cost;
   uint16_t* d_arg;
   hipStream_t stream;
+  int device = 0;             // where it was solved
   const mrl_table* deps[2] = {nullptr, nullptr};      // a FUSED table: the tables it was solved against
   // final lists inside scratch: [0] decisions, [1] costs
   size_t list_off[2];
@@ -930,6 +946,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   if (scratch_bytes < f.end) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.end);
   char* base = (char*)d_scratch;
   hipStream_t st = (hipStream_t)hip_stream;
+  HIP_TRY(hipGetDevice(&tab->device));
   tab->scratch = base; tab->d_cost = (uint64_t*)d_cost; tab->d_arg = (uint16_t*)d_argmin; tab->stream = st;
 
   Counters* d_ctr = (Counters*)(base + f.counters);
@@ -1858,29 +1875,31 @@ int32_t mrl_emit_compressed(const mrl_table* tab, uint32_t which, mrl_box* out, 
   if (!out) return MRL_OK;
   if (cap < n) return fail(MRL_E_BUFSZ, "box buffer holds %zu, %llu needed", cap, (unsigned long long)n);
   const Geo& g = tab->cp->geo;
+  if (!n) return MRL_OK;
   const char* r = tab->scratch + tab->list_off[which];
-  std::vector<uint32_t> fcell(n);
-  std::vector<uint8_t> flen(n * 16);
-  std::vector<uint64_t> fv0(n), fv1(n);
-  if (n) {
-    HIP_TRY(hipMemcpy(fcell.data(), r, n * 4, hipMemcpyDeviceToHost)); r += align_up(n * 4);
-    HIP_TRY(hipMemcpy(flen.data(), r, n * 16, hipMemcpyDeviceToHost)); r += align_up(n * 16);
-    HIP_TRY(hipMemcpy(fv0.data(), r, n * 8, hipMemcpyDeviceToHost)); r += align_up(n * 8);
-    HIP_TRY(hipMemcpy(fv1.data(), r, n * 8, hipMemcpyDeviceToHost));
-  }
-  for (uint64_t i = 0; i < n; i++) {
-    mrl_box& b = out[i];
-    memset(&b, 0, sizeof b);
-    uint32_t x = fcell[i];
-    for (uint32_t a = 0; a < g.ndim; a++) {
-      const uint32_t lo = x / g.stride[a];
-      x -= lo * g.stride[a];
-      b.lo[a] = (uint16_t)lo;
-      b.hi[a] = (uint16_t)(lo + flen[i * 16 + a] - 1);
-    }
-    b.v0 = fv0[i]; b.v1 = fv1[i];
-  }
-  return MRL_OK;
+  const uint32_t* fcell = (const uint32_t*)r; r += align_up(n * 4);
+  const char* flen = r; r += align_up(n * 16);
+  const uint64_t* fv0 = (const uint64_t*)r; r += align_up(n * 8);
+  const uint64_t* fv1 = (const uint64_t*)r;
+  // The GPU writes the records into pinned memory, kEmitChunk at a time, while the host copies the
+  // chunk before out of it.  On the null stream of the table's device: nothing that the caller has
+  // given up since the solve (its stream) is used, and work on the caller's streams is ordered as by a copy.
+  static_assert(sizeof(mrl_box) == 80 && (size_t)kEmitChunk * sizeof(mrl_box) <= kStageHalf, "a chunk fits half a staging block");
+  OnDevice on;
+  int32_t rc = on.set(tab->device);
+  if (rc) return rc;
+  StageLease stage;
+  rc = get_stage(stage);
+  if (rc) return rc;
+  return take_through(n, kEmitChunk, stage, nullptr,
+    [&](size_t, uint32_t, char*) -> int32_t { return MRL_OK; },
+    [&](size_t first, uint32_t m, char* h) {
+      launch_expand_boxes(g, m, fcell + first, flen + first * 16, fv0 + first, fv1 + first, h, nullptr);
+    },
+    [&](size_t first, uint32_t m, char* h) -> int32_t {
+      memcpy((void*)(out + first), h, (size_t)m * sizeof(mrl_box));
+      return MRL_OK;
+    });
   });
 }
 

@@ -91,6 +91,9 @@ void launch_emit(const Geo& g, const DevParams* P, bool is_cost, uint32_t n_boxe
                  const void* blen,
                  const uint8_t* alive, const uint32_t* pos, const uint64_t* cost, const uint16_t* arg, uint32_t* fcell,
                  void* flen, uint64_t* fv0, uint64_t* fv1, hipStream_t st);
+// n boxes of a final list as the 80-byte records of the interface; out: pinned host memory, 16-byte aligned.
+void launch_expand_boxes(const Geo& g, uint32_t n, const uint32_t* fcell, const void* flen, const uint64_t* fv0, const uint64_t* fv1, void* out,
+                         hipStream_t st);
 // idx, cost_out, arg_out: device memory or pinned host memory.
 void launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const uint16_t* arg, uint64_t* cost_out,
                    uint16_t* arg_out, hipStream_t st);

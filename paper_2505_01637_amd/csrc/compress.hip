@@ -850,6 +850,44 @@ void launch_emit(const Geo& g, const DevParams* P, bool is_cost, uint32_t n_boxe
                        alive, pos, cost, arg, fcell, (uint4*)flen, fv0, fv1);
 }
 
+// The records of a final list, as the caller gets them: 80 bytes each (lo[16], hi[16] of 16 bits, then
+// v0, v1), 16 bytes per lane, so that a wave writes one contiguous stretch.  out: pinned host memory.
+// Bound by the link and by the host's copy out of the pinned block.  The lists of a pipeline's three
+// tables (15.7 M Specs, solved and taken to the host): 7.2 ms in all; 16.6 ms when the host expanded
+// them out of four copies into pageable memory.
+__global__ __launch_bounds__(256) void expand_boxes_kernel(Geo g, uint32_t n, const uint32_t* __restrict__ fcell, const uint4* __restrict__ flen,
+                                                           const uint64_t* __restrict__ fv0, const uint64_t* __restrict__ fv1,
+                                                           uint4* __restrict__ out) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  const uint32_t b = i / 5u, piece = i - b * 5u;
+  if (b >= n) return;
+  if (piece == 4) {
+    const uint64_t v0 = fv0[b], v1 = fv1[b];
+    out[i] = make_uint4((uint32_t)v0, (uint32_t)(v0 >> 32), (uint32_t)v1, (uint32_t)(v1 >> 32));
+    return;
+  }
+  const uint32_t cell = fcell[b], half = piece & 1u;         // axes 0..7 or 8..15
+  const bool hi = piece >= 2;
+  const uint4 L = flen[b];
+  const uint32_t l0 = half ? L.z : L.x, l1 = half ? L.w : L.y;
+  uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (uint32_t k = 0; k < 8; k++) {
+    const uint32_t a = half * 8u + k;
+    if (a >= g.ndim) break;
+    const uint32_t stride = half ? g.stride[8 + k] : g.stride[k], ext = half ? g.ext[8 + k] : g.ext[k];
+    uint32_t x = (cell / stride) % ext;
+    if (hi) x += (((k < 4 ? l0 : l1) >> (8u * (k & 3u))) & 0xFFu) - 1u;
+    w[k >> 1] |= (x & 0xFFFFu) << (16u * (k & 1u));
+  }
+  out[i] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+void launch_expand_boxes(const Geo& g, uint32_t n, const uint32_t* fcell, const void* flen, const uint64_t* fv0, const uint64_t* fv1, void* out,
+                         hipStream_t st) {
+  if (n) hipLaunchKernelGGL(expand_boxes_kernel, dim3((n * 5u + 255u) / 256u), dim3(256), 0, st, g, n, fcell, (const uint4*)flen, fv0, fv1, (uint4*)out);
+}
+
 // ---------------------------------------------------------------- query
 __global__ __launch_bounds__(256) void gather_kernel(const uint64_t* __restrict__ idx, uint32_t n,
                                                      const uint64_t* __restrict__ cost, const uint16_t* __restrict__ arg,

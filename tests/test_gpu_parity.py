@@ -222,6 +222,31 @@ def test_compressed_query_one_box_and_long_axis():
     compare_config({"name": "100-on-k", "target": base["target"], "lattices": [("M", lat, [])]})
 
 
+@pytest.mark.parametrize("number,max_size", [(1, 2), (5, 8), (10, 6), (12, 8)])
+def test_box_records_into_a_larger_buffer(number, max_size):
+    """mrl_emit_compressed: lists from a few boxes to several chunks of 16,384 with a ragged last
+    one, seven to thirteen axes; nothing is written behind the list, and a short buffer is refused
+    untouched.  The solve runs on a stream of its own."""
+    import ctypes as C
+    import torch
+    B = _binding()
+    cfg = W.config(number, max_size=max_size)
+    want = O.solve_config(cfg)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        _, got = B.solve_config(cfg)
+    for label, lat, _ in cfg["lattices"]:
+        lists = O.compress_table(cfg["target"], lat, want[label]["cost"], want[label]["argmin"])
+        for which in (0, 1):
+            n = C.c_size_t()
+            room = len(lists[which]) + 3
+            out = np.full((room, B.BOX_DTYPE.itemsize), 0xA5, dtype=np.uint8)
+            rc = B.lib().mrl_emit_compressed(got[label]._h, C.c_uint32(which), C.c_void_p(out.ctypes.data), C.c_size_t(len(lists[which]) - 1), C.byref(n))
+            assert rc == B.E_BUFSZ and n.value == len(lists[which]) and (out == 0xA5).all()
+            assert B.lib().mrl_emit_compressed(got[label]._h, C.c_uint32(which), C.c_void_p(out.ctypes.data), C.c_size_t(room), C.byref(n)) == 0
+            assert out[:-3].tobytes() == lists[which].tobytes() and (out[-3:] == 0xA5).all()
+
+
 @pytest.mark.parametrize("max_size,threads,sync", [(16, 8, None), (12, 3, 7), (20, 1, 2), (64, 8, None)])
 def test_parity_parallel_loops(max_size, threads, sync):
     """Parallel loops (Section 3's loop rule with threads; Section 2.2's serial-only flag): the
