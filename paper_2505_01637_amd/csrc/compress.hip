@@ -187,16 +187,60 @@ __global__ __launch_bounds__(256) void head_flags_wave_kernel(Geo g, uint32_t a0
 constexpr uint8_t kLive = 0x80;
 
 // ---------------------------------------------------------------- prefix sums
+// Items come in pairs: one wide load each, coalesced over a wave (both arrays start on 256 bytes
+// and pairs on even items).
 struct LoadPopc {
   const unsigned long long* p;
-  __device__ __forceinline__ uint32_t operator()(uint32_t i) const { return (uint32_t)__popcll(p[i]); }
+  __device__ __forceinline__ uint32_t one(uint32_t i) const { return (uint32_t)__popcll(p[i]); }
+  __device__ __forceinline__ void two(uint32_t i, uint32_t& x, uint32_t& y) const {
+    const ulonglong2 v = *(const ulonglong2*)(p + i);
+    x = (uint32_t)__popcll(v.x);
+    y = (uint32_t)__popcll(v.y);
+  }
 };
 struct LoadFlag {
   const uint8_t* p;
-  __device__ __forceinline__ uint32_t operator()(uint32_t i) const { return p[i] ? 1u : 0u; }
+  __device__ __forceinline__ uint32_t one(uint32_t i) const { return p[i] ? 1u : 0u; }
+  __device__ __forceinline__ void two(uint32_t i, uint32_t& x, uint32_t& y) const {
+    const uint32_t v = *(const uint16_t*)(p + i);
+    x = v & 0xFFu ? 1u : 0u;
+    y = v >> 8 ? 1u : 0u;
+  }
 };
 
-constexpr uint32_t kScanItems = 8, kScanBlock = 256, kScanTile = kScanItems * kScanBlock;
+// A tile is 2048 items of a workgroup of four waves; a wave has 512 consecutive ones in four rows of
+// 128, two per lane and row.  A row adds up to at most 128 * 64, so two rows share a word.
+// Bound by the number of memory requests: with eight items in a row per lane, read one by one, and the
+// top in steps of 256 sums, the scans of a solved pipeline (7 M words, 12 M flags and the two smaller
+// tables) took 484 us of kernel time, now 289 (apply over 7 M words 68 -> 25 us, the top 23 -> 9); the
+// solve 5422 -> 5332 us, the smallest one 519 -> 488 us (four to eight launches fewer).
+constexpr uint32_t kScanRows = 4, kScanRow = 128, kScanTile = 4 * kScanRows * kScanRow;
+static_assert(kScanTile == kScanTileItems, "the caller's scratch is sized by the tile");
+constexpr uint32_t kScanTop = 2048;         // more tiles than this are added up by scan_top_kernel
+
+template <class L>
+__device__ __forceinline__ void scan_load(const L& load, uint32_t first, uint32_t n, uint32_t (&x)[kScanRows], uint32_t (&y)[kScanRows]) {
+#pragma unroll
+  for (uint32_t r = 0; r < kScanRows; r++) {
+    const uint32_t i = first + r * kScanRow;
+    x[r] = y[r] = 0;
+    if (i + 1 < n) load.two(i, x[r], y[r]);
+    else if (i < n) x[r] = load.one(i);
+  }
+}
+
+__device__ __forceinline__ uint32_t scan_first() {
+  return blockIdx.x * kScanTile + (threadIdx.x >> 6) * (kScanRows * kScanRow) + (threadIdx.x & 63u) * 2;
+}
+
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(v, d, 64);
+    if ((int)(threadIdx.x & 63u) >= d) v += o;
+  }
+  return v;
+}
 
 __device__ __forceinline__ uint32_t block_reduce_256(uint32_t v, uint32_t* sh) {
 #pragma unroll
@@ -211,71 +255,91 @@ __device__ __forceinline__ uint32_t block_reduce_256(uint32_t v, uint32_t* sh) {
 template <class L>
 __global__ __launch_bounds__(256) void scan_tile_sums_kernel(L load, uint32_t n, uint32_t* __restrict__ tile_sum) {
   __shared__ uint32_t sh[4];
-  const uint32_t first = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-  uint32_t s = 0;
+  uint32_t x[kScanRows], y[kScanRows], s = 0;
+  scan_load(load, scan_first(), n, x, y);
 #pragma unroll
-  for (uint32_t i = 0; i < kScanItems; i++) if (first + i < n) s += load(first + i);
+  for (uint32_t r = 0; r < kScanRows; r++) s += x[r] + y[r];
   const uint32_t t = block_reduce_256(s, sh);
   if (threadIdx.x == 0) tile_sum[blockIdx.x] = t;
 }
 
-// One workgroup: exclusive scan of tile_sum in place; the grand total goes to *total.
-__global__ __launch_bounds__(256) void scan_top_kernel(uint32_t* __restrict__ tile_sum, uint32_t n_tiles,
-                                                       uint32_t* __restrict__ total) {
-  __shared__ uint32_t sh[4];
-  __shared__ uint32_t carry_sh;
-  if (threadIdx.x == 0) carry_sh = 0;
-  __syncthreads();
-  for (uint32_t base = 0; base < n_tiles; base += 256) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t v = i < n_tiles ? tile_sum[i] : 0;
-    uint32_t incl = v;
+// One workgroup: exclusive scan of tile_sum in place, 4096 sums at a time.
+__global__ __launch_bounds__(1024) void scan_top_kernel(uint32_t* __restrict__ tile_sum, uint32_t n_tiles) {
+  __shared__ uint32_t sh[16];
+  uint32_t carry = 0;
+  for (uint32_t base = 0; base < n_tiles; base += 4096) {
+    const uint32_t i = base + threadIdx.x * 4;
+    uint32_t v[4], s = 0;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      uint32_t o = __shfl_up(incl, d, 64);
-      if ((int)(threadIdx.x & 63u) >= d) incl += o;
-    }
+    for (uint32_t k = 0; k < 4; k++) { v[k] = i + k < n_tiles ? tile_sum[i + k] : 0; s += v[k]; }
+    const uint32_t incl = wave_incl_scan(s);
     if ((threadIdx.x & 63u) == 63) sh[threadIdx.x >> 6] = incl;
     __syncthreads();
-    uint32_t wbase = 0;
-    for (uint32_t w = 0; w < (threadIdx.x >> 6); w++) wbase += sh[w];
-    const uint32_t carry = carry_sh;
-    if (i < n_tiles) tile_sum[i] = carry + wbase + incl - v;
+    uint32_t run = carry + incl - s;
+    for (uint32_t w = 0; w < 16; w++) {
+      if (w < (threadIdx.x >> 6)) run += sh[w];
+      carry += sh[w];
+    }
     __syncthreads();
-    if (threadIdx.x == 255) carry_sh = carry + wbase + incl;
-    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) { if (i + k < n_tiles) tile_sum[i + k] = run; run += v[k]; }
   }
-  if (threadIdx.x == 0) *total = carry_sh;
 }
 
-template <class L>
-__global__ __launch_bounds__(256) void scan_apply_kernel(L load, uint32_t n, const uint32_t* __restrict__ tile_excl,
-                                                         uint32_t* __restrict__ out) {
+// out[i] = sum of the items before i, *total = sum of all.  TOP: tile_sum holds the sums before each
+// tile; otherwise the tiles' own sums, and a workgroup adds up those before its own.
+template <class L, bool TOP>
+__global__ __launch_bounds__(256) void scan_apply_kernel(L load, uint32_t n, const uint32_t* __restrict__ tile_sum,
+                                                         uint32_t* __restrict__ out, uint32_t* __restrict__ total) {
   __shared__ uint32_t sh[4];
-  const uint32_t first = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-  uint32_t v[kScanItems], s = 0;
-#pragma unroll
-  for (uint32_t i = 0; i < kScanItems; i++) { v[i] = first + i < n ? load(first + i) : 0; s += v[i]; }
-  uint32_t incl = s;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t o = __shfl_up(incl, d, 64);
-    if ((int)(threadIdx.x & 63u) >= d) incl += o;
+  const uint32_t first = scan_first();
+  uint32_t x[kScanRows], y[kScanRows];
+  scan_load(load, first, n, x, y);
+  uint32_t base;
+  if (TOP) {
+    base = tile_sum[blockIdx.x];
+  } else {
+    uint32_t s = 0;
+    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += 256) s += tile_sum[t];
+    base = block_reduce_256(s, sh);
   }
-  if ((threadIdx.x & 63u) == 63) sh[threadIdx.x >> 6] = incl;
+  uint32_t row[kScanRows], before[kScanRows];      // the lane's sum of a row; of the rows before it and of the lanes before it
+#pragma unroll
+  for (uint32_t r = 0; r < kScanRows; r++) row[r] = x[r] + y[r];
+  uint32_t wave = 0;
+#pragma unroll
+  for (uint32_t r = 0; r < kScanRows; r += 2) {
+    const uint32_t incl = wave_incl_scan(row[r] | row[r + 1] << 16), tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    before[r] = wave + (incl & 0xFFFFu) - row[r];
+    wave += tot & 0xFFFFu;
+    before[r + 1] = wave + (incl >> 16) - row[r + 1];
+    wave += tot >> 16;
+  }
+  if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = wave;
   __syncthreads();
-  uint32_t run = tile_excl[blockIdx.x] + incl - s;
+  uint32_t run = base;
   for (uint32_t w = 0; w < (threadIdx.x >> 6); w++) run += sh[w];
 #pragma unroll
-  for (uint32_t i = 0; i < kScanItems; i++) { if (first + i < n) out[first + i] = run; run += v[i]; }
+  for (uint32_t r = 0; r < kScanRows; r++) {
+    const uint32_t i = first + r * kScanRow, at = run + before[r];
+    if (i + 1 < n) *(uint2*)(out + i) = make_uint2(at, at + x[r]);
+    else if (i < n) out[i] = at;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base + sh[0] + sh[1] + sh[2] + sh[3];
 }
 
+// One launch up to one tile, two up to kScanTop, then three: adding up the tiles before its own costs a
+// workgroup up to eight reads per thread there, less than a launch between the two others.
 template <class L>
 static void exclusive_scan(L load, uint32_t n, uint32_t* tile_tmp, uint32_t* out, uint32_t* total, hipStream_t st) {
-  const uint32_t n_tiles = (n + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(scan_tile_sums_kernel<L>, dim3(n_tiles), dim3(256), 0, st, load, n, tile_tmp);
-  hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(256), 0, st, tile_tmp, n_tiles, total);
-  hipLaunchKernelGGL(scan_apply_kernel<L>, dim3(n_tiles), dim3(256), 0, st, load, n, tile_tmp, out);
+  const uint32_t n_tiles = n ? (n - 1) / kScanTile + 1 : 1;
+  if (n_tiles > 1) hipLaunchKernelGGL(scan_tile_sums_kernel<L>, dim3(n_tiles), dim3(256), 0, st, load, n, tile_tmp);
+  if (n_tiles > kScanTop) {
+    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(1024), 0, st, tile_tmp, n_tiles);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(scan_apply_kernel<L, true>), dim3(n_tiles), dim3(256), 0, st, load, n, tile_tmp, out, total);
+  } else {
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(scan_apply_kernel<L, false>), dim3(n_tiles), dim3(256), 0, st, load, n, tile_tmp, out, total);
+  }
 }
 
 void scan_mask_words(const unsigned long long* mask, uint32_t n_words, uint32_t* tile_tmp, uint32_t* prefix,

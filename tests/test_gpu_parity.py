@@ -368,6 +368,15 @@ def test_parity_memory_bounds(case):
     check_compressed_queries(got[label], want[label], 100_000, seed=3)
 
 
+@pytest.mark.parametrize("m,k,n", [(1, 1, 1), (23, 89, 8), (16, 32, 32), (5, 29, 113), (31, 32, 33)])
+def test_parity_prefix_sum_tiles(m, k, n):
+    """Bit maps of 1, 2047, 2048, 2049 and 4092 words: the prefix sums take 2048 items per tile, one
+    tile alone in one launch (the full-size pipeline has more tiles than a workgroup adds up)."""
+    cfg = W.config(1)
+    cfg["lattices"][0][1]["sizes"][1:] = [list(range(1, x + 1)) for x in (m, k, n)]
+    compare_config(cfg)
+
+
 @pytest.mark.parametrize("caps,sizes", [
     ((1 << 29, W.UNBOUNDED), (1, 2, 3)),         # 31 bounds per level assignment: a lane per Spec
     ((1 << 30, W.UNBOUNDED), (1, 2, 3)),         # 32: a wave per level assignment, half of its lanes idle
