@@ -31,8 +31,9 @@
 // The ranks of a shape are a chain (10 of three operands, 13 of four), and a
 // rank of one item holds only a few tasks; the bundle's items go through it
 // together, which fills the lanes, and share the cost of setting up.
-// Candidates are compared by (cost, id), so ties go to the lowest id whatever
-// the order; nothing is reduced across workgroups: the table is deterministic.
+// Ties go to the lowest id: a lane meets its candidates in the order of their
+// ids where it compares the cost alone, all else is compared by (cost, id).
+// Nothing is reduced across workgroups: the table is deterministic.
 #include <hip/hip_runtime.h>
 #include "compress.h"
 #include "dev_params.h"
@@ -780,13 +781,13 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 5 
             const uint64_t cand = ((hi << 32) | (uint32_t)lo) + (t >= n_ser ? s_par : s_serial);
             const bool over = fin & (((hi >> 30) != 0) | (cand >= kLimit));
             e.ovf |= over ? 1u : 0u;
-            const bool better = fin & !over & (cand < e.best);       // ids ascend
+            const bool better = fin & !over & (cand < e.best);       // ids ascend, also over the stretches of kt tiles
             e.best = better ? cand : e.best;
             e.arg = better ? L.tl_id[j * g.kt + t] : e.arg;
           }
         }
       }
-      if (has_buf && e0 == 0 && sub4 == 0) {
+      if (has_buf && e0 + g.kt >= max_tile && sub4 == 0) {       // after the last tiles: its id is above theirs
         const uint32_t nb = task_bufferize(P, L.it_rowM[j], L.it_rowE[j], L.it_z[j], L.it_numel + j * 5, ent_pack(en), L.it_pass[j], v, e);
         if (q0 < n_task) n_rw += nb;
       }

@@ -320,6 +320,33 @@ def test_parity_bundles_of_items(case):
     compare_config(cfg)
 
 
+@pytest.mark.parametrize("case", ["fused-29-tiles", "fused-layouts-42-tiles", "fused-wide-items-76-tiles", "split-42-tiles", "composition-31-tiles"])
+def test_parity_bufferize_beside_many_tiles(case):
+    """More tile rewrites than a workgroup holds at a time (24 per item of a bundle, 64 of a wide
+    item) beside a bufferize, whose id is higher than theirs: with a free loop, tiles of the second
+    stretch cost what the bufferize does, and the lowest id is the answer."""
+    div = lambda n: [d for d in range(1, n + 1) if n % d == 0]
+    if case.startswith("fused"):
+        m, n, y = {"fused-29-tiles": (120, 120, 0), "fused-layouts-42-tiles": (360, 240, 1), "fused-wide-items-76-tiles": (5040, 180, 1)}[case]
+        cfg = W.config(5, seed=1, max_size=1)
+        if "wide" in case:
+            cfg["target"]["capacity_bytes"] = [1 << 16, 1 << 18, 1 << 20, W.UNBOUNDED]
+        m, n = div(m), div(n)
+        cfg["lattices"] = [("M", W._lattice(W.KIND_MATMUL_ACCUM, [[1], m, [1], n], layout=(y, y, y, 0, 0)), []),
+                           ("E", W._lattice(W.KIND_BIAS_ADD_RELU, [[1], m, [1], n], layout=(y, 0, y, 0, 0)), []),
+                           ("F", W._lattice(W.KIND_FUSED_MM_ADD_RELU, [[1], m, [1], n], layout=(y, y, 0, y, 0)), ["M", "E"])]
+    elif case.startswith("split"):
+        cfg = split_config([1], fused=False)
+        for _, lat, _ in cfg["lattices"]:
+            lat["sizes"][1], lat["sizes"][3] = div(360), div(240)
+    else:
+        cfg = chain_config([1, 2, 4])
+        for _, lat, _ in cfg["lattices"]:
+            lat["sizes"][1] = div(720)
+    cfg["target"]["loop_overhead"] = 0
+    compare_config(cfg)
+
+
 def two_level_bounded(caps, sizes):
     cfg = W.config(1, seed=11, max_size=4)
     t = cfg["target"]
