@@ -1358,8 +1358,8 @@ __global__ __launch_bounds__(256) void fill_units_kernel(const DevParams* __rest
                 const uint64_t lo = (uint64_t)a * (uint32_t)sub[u][r];
                 const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u][r] >> 32) + (lo >> 32);     // bits 32.. of the product
                 const uint64_t cand = ((hi << 32) | (uint32_t)lo) + s_loop;
-                // (bits from 2^64 up of the product count as well)
-                over |= fin ? (uint32_t)(cand >> 32) | ((uint32_t)(hi >> 32) ? 1u << 30 : 0u) : 0u;
+                // (the product's own bits count as well: the sum may pass 2^64)
+                over |= fin ? (uint32_t)(cand >> 32) | (uint32_t)hi | ((uint32_t)(hi >> 32) ? 1u << 30 : 0u) : 0u;
                 const bool better = fin && cand < best[r];
                 best[r] = better ? cand : best[r];
                 best_id[r] = better ? id : best_id[r];

@@ -421,6 +421,32 @@ def test_parity_units_of_bounds(caps, sizes):
     compare_config(cfg)
 
 
+@pytest.mark.parametrize("kind,caps", [("matmul", (1 << 40, W.UNBOUNDED)), ("matmul", (64, W.UNBOUNDED)), ("moves", None)])
+@pytest.mark.parametrize("cost,loop,rc", [((1 << 62) - 1, 4, -6), ((1 << 62) - 2, 4, -6), ((1 << 60) - 1, 4, -6), ((1 << 60) - 1, 3, 0)])
+def test_loop_cost_at_the_limit(kind, caps, cost, loop, rc):
+    """Four trips of a body at the limit, plus the loop constant: a sum that reaches 2^64, one that
+    does not, one that reaches 2^62 exactly and one just below it (42 and 8 bounds per level
+    assignment, Move Specs)."""
+    B = _binding()
+    if kind == "matmul":
+        cfg = two_level_bounded(caps, (1,))
+        cfg["lattices"][0][1]["sizes"][1] = [1, 4]
+        cfg["target"]["load_coef"][1][0][0] = cfg["target"]["store_coef"][0][1][0] = 0
+        cfg["target"]["microkernels"] = [(W.MK_SCALAR_FMA, 1, cost)]
+    else:
+        cfg = W.config(9, max_size=1)
+        cfg["lattices"] = [("V", dict(cfg["lattices"][0][1], sizes=[[1], [1, 4], [1], [1]]), [])]
+        cfg["target"]["microkernels"] = [(W.MK_SCALAR_MOVE, 1, cost)]
+    cfg["target"]["loop_overhead"] = loop
+    assert O.solve(cfg["target"], cfg["lattices"][0][1])["rc"] == rc
+    if rc == 0:
+        compare_config(cfg)
+        return
+    with pytest.raises(B.MorelloError) as e:
+        B.solve_config(cfg)
+    assert e.value.code == B.E_OVERFLOW
+
+
 @pytest.mark.parametrize("case", ["two-level", "config8-small", "config8"])
 def test_parity_memory_bounds_through_a_pipeline(case):
     """Memory bounds on all three tables of the fused workload (Section 2.4.4: Moves and
