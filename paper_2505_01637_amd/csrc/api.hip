@@ -939,6 +939,9 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   }
   if (!deps_late) { rc = bind_deps(); if (rc) return rc; }
 
+  if (!P.gather && !plan_fits(P, c.n_shapes, c.level_off.data(), (uint32_t)c.level_off.size() - 1))
+    return fail(MRL_E_INVAL, "a dependency level has too many shapes for its work lists");
+
   std::unique_lock<std::mutex> solve_lock(c.solve_mu);      // for the upload image, until the upload has run
 
   const FixedLayout f = fixed_layout(c);

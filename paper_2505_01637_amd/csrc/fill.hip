@@ -1635,6 +1635,15 @@ static uint32_t sort_tiles(const uint32_t* level_off, uint32_t n_levels, uint32_
   for (uint32_t l = 0; l < n_levels; l++) n += ((level_off[l + 1] - level_off[l]) * npass + kSortTile - 1) / kSortTile;
   return n;
 }
+// A level's weights are added up in 32 bits (an item weighs at least kBundle / fill_items; the
+// tasks themselves are fewer than 2^32), and a launch has fewer than 2^32 threads: the plan's has
+// four per shape, a level's 128 per bundle.
+bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels) {
+  if (n_shapes >= (1u << 30) - 4 * kPlanShapes) return false;
+  for (uint32_t l = 0; l < n_levels; l++)
+    if ((uint64_t)(level_off[l + 1] - level_off[l]) * h.npass >= (1ull << 32) / (kBundle / fill_items(h))) return false;
+  return true;
+}
 size_t plan_bytes_recs(uint32_t n_shapes) { return (size_t)n_shapes * sizeof(ShapeRec); }
 size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass) { return (size_t)sort_tiles(level_off, n_levels, npass) * 32 + 16; }
 

@@ -158,3 +158,19 @@ def test_moves_as_specs_host_checks():
         with pytest.raises(B.MorelloError) as e:
             B.geometry(B.Target(bad_target), bad_lat)
         assert e.value.code == B.E_INVAL
+
+
+def test_level_beyond_the_work_lists_is_refused_before_device_work():
+    """129^4 shapes of two levels, 128^4 = 2^28 of them on one dependency level (primes: no size but 1
+    divides another): their weights in the work lists would add up to 2^32.  The call is refused before
+    the device is touched (the buffers are addresses of nothing)."""
+    import ctypes as C
+    primes = [p for p in range(2, 720) if all(p % q for q in range(2, int(p ** 0.5) + 1))]
+    cfg = W.config(1)
+    lat = dict(cfg["lattices"][0][1], sizes=[[1] + primes[:128]] * 4)
+    t = B.Target(cfg["target"])
+    h, stats = C.c_void_p(), B.Stats()
+    rc = B.lib().mrl_solve(t._h, C.byref(B._lattice_desc(lat)), None, C.c_uint32(0), C.c_void_p(1 << 40), C.c_void_p(1 << 41),
+                           C.c_void_p(1 << 42), C.c_size_t(1 << 50), C.c_void_p(None), C.byref(h), C.byref(stats))
+    assert rc == B.E_INVAL and not h.value
+    assert "dependency level" in B.lib().mrl_last_error().decode()
