@@ -562,7 +562,8 @@ struct Aux {
   bool busy = false;
 };
 
-// One set per solve in flight (solves on different host threads may overlap), kept for reuse.
+// One set per solve in flight (solves on different host threads may overlap; a box list that is taken
+// to the host uses the stream of one), kept for reuse.
 struct AuxLease {
   Aux* a = nullptr;
   ~AuxLease();
@@ -1885,19 +1886,25 @@ int32_t mrl_emit_compressed(const mrl_table* tab, uint32_t which, mrl_box* out, 
   const uint64_t* fv0 = (const uint64_t*)r; r += align_up(n * 8);
   const uint64_t* fv1 = (const uint64_t*)r;
   // The GPU writes the records into pinned memory, kEmitChunk at a time, while the host copies the
-  // chunk before out of it.  On the null stream of the table's device: nothing that the caller has
-  // given up since the solve (its stream) is used, and work on the caller's streams is ordered as by a copy.
+  // chunk before out of it.  On a stream of the library's own (a helper stream of the table's device):
+  // the caller may have given up the solve's stream, and a launch on the null stream would wait for
+  // every blocking stream of the process, and they for it, once per chunk.  The lists are complete:
+  // the solve has waited for them.
   static_assert(sizeof(mrl_box) == 80 && (size_t)kEmitChunk * sizeof(mrl_box) <= kStageHalf, "a chunk fits half a staging block");
   OnDevice on;
   int32_t rc = on.set(tab->device);
   if (rc) return rc;
+  AuxLease aux;
+  rc = get_aux(0, aux);
+  if (rc) return rc;
+  const hipStream_t st = aux.a->stream;
   StageLease stage;
   rc = get_stage(stage);
   if (rc) return rc;
-  return take_through(n, kEmitChunk, stage, nullptr,
+  return take_through(n, kEmitChunk, stage, st,
     [&](size_t, uint32_t, char*) -> int32_t { return MRL_OK; },
     [&](size_t first, uint32_t m, char* h) {
-      launch_expand_boxes(g, m, fcell + first, flen + first * 16, fv0 + first, fv1 + first, h, nullptr);
+      launch_expand_boxes(g, m, fcell + first, flen + first * 16, fv0 + first, fv1 + first, h, st);
     },
     [&](size_t first, uint32_t m, char* h) -> int32_t {
       memcpy((void*)(out + first), h, (size_t)m * sizeof(mrl_box));

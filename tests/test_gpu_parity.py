@@ -1165,3 +1165,33 @@ def test_graph_calls_from_two_threads_on_the_same_lattices():
         th.join(timeout=120)       # a circular wait between the two calls must fail the test, not hang it
     assert not any(th.is_alive() for th in threads), "the two graph calls wait for each other"
     assert not errors, errors
+
+
+def test_box_lists_taken_while_another_thread_solves():
+    """Lists of several chunks are taken to the host from a thread of their own while another thread
+    solves on the null stream: they wait for nothing of it and stay what they are."""
+    import threading
+    import torch
+    B = _binding()
+    cfg, other = W.config(5, max_size=24), W.config(4, max_size=24)
+    target, got = B.solve_config(cfg)
+    _, solved = B.solve_config(other)
+    lists = [got["F"].boxes(which).tobytes() for which in (0, 1)]
+    want = [solved["M"].boxes(which).tobytes() for which in (0, 1)]
+    dev, errors = torch.cuda.current_device(), []
+
+    def solver():
+        try:
+            torch.cuda.set_device(dev)
+            for _ in range(6):
+                again = B.solve(B.Target(other["target"]), other["lattices"][0][1], stream=torch.cuda.default_stream())
+                assert [again.boxes(which).tobytes() for which in (0, 1)] == want
+        except BaseException as e:
+            errors.append(e)
+
+    th = threading.Thread(target=solver, daemon=True)
+    th.start()
+    for _ in range(12):
+        assert [got["F"].boxes(which).tobytes() for which in (0, 1)] == lists
+    th.join(timeout=60)
+    assert not th.is_alive() and not errors, errors
