@@ -653,7 +653,7 @@ struct OnDevice {
 };
 
 // Take n items through the GPU, `chunk` at a time, on `stream`: fill(first, m, half) writes a chunk's
-// inputs, launch(first, m, half) queues its kernels and drain(first, m, half) takes its results.  While
+// inputs, launch(first, m, half) queues its kernel and drain(first, m, half) takes its results.  While
 // the GPU has one chunk the host drains the one before it and fills the next.  When this returns,
 // with or without an error, nothing queued here is still running.
 template <class Fill, class Launch, class Drain>
@@ -664,10 +664,7 @@ int32_t take_through(size_t n, size_t chunk, const StageLease& stage, hipStream_
     int32_t rc = i < n_chunks ? fill(i * chunk, items(i), stage.half(i)) : MRL_OK;
     if (i > 0) HIP_TRY(hipStreamSynchronize(stream));
     if (rc) return rc;
-    if (i < n_chunks) {
-      launch(i * chunk, items(i), stage.half(i));
-      HIP_TRY(hipGetLastError());
-    }
+    if (i < n_chunks) HIP_TRY(launch(i * chunk, items(i), stage.half(i)));      // (a launch that fails queues nothing)
     if (i > 0 && (rc = drain((i - 1) * chunk, items(i - 1), stage.half(i - 1)))) {
       (void)hipStreamSynchronize(stream);
       return rc;
@@ -1513,7 +1510,7 @@ int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n, uint64
       return MRL_OK;
     },
     [&](size_t, uint32_t m, char* h) {
-      launch_gather((const uint64_t*)h, m, tab->d_cost, tab->d_arg, (uint64_t*)(h + o_cost), (uint16_t*)(h + o_arg), tab->stream);
+      return launch_gather((const uint64_t*)h, m, tab->d_cost, tab->d_arg, (uint64_t*)(h + o_cost), (uint16_t*)(h + o_arg), tab->stream);
     },
     [&](size_t first, uint32_t m, char* h) -> int32_t {
       memcpy(cost_out + first, h + o_cost, (size_t)m * 8);
@@ -1570,8 +1567,7 @@ int32_t mrl_query_noalloc(const mrl_table* tab, const mrl_coord* specs, size_t n
   // cost[0, n), arg[0, n), and only those come back
   const uint32_t m = (uint32_t)n;
   HIP_TRY(hipMemcpyAsync(d->idx, idx, n * 8, hipMemcpyHostToDevice, tab->stream));
-  launch_gather(d->idx, m, tab->d_cost, tab->d_arg, d->cost, d->arg, tab->stream);
-  HIP_TRY(hipGetLastError());
+  HIP_TRY(launch_gather(d->idx, m, tab->d_cost, tab->d_arg, d->cost, d->arg, tab->stream));
   HIP_TRY(hipMemcpyAsync(cost_out, d->cost, n * 8, hipMemcpyDeviceToHost, tab->stream));
   HIP_TRY(hipMemcpyAsync(rewrite_out, d->arg, n * 2, hipMemcpyDeviceToHost, tab->stream));
   HIP_TRY(hipStreamSynchronize(tab->stream));
@@ -1669,8 +1665,7 @@ struct ChainReader {
       for (int i = 0; i < 5; i++) { w.lay_axis[i] = c.lay_axis[i]; w.dt_axis[i] = c.dt_axis[i]; }
       uint32_t* count = (uint32_t*)(e + kChainMost);
       *count = 0;
-      launch_chain(w, tab->d_cost, tab->d_arg, e, count, tab->stream);
-      HIP_TRY(hipGetLastError());
+      HIP_TRY(launch_chain(w, tab->d_cost, tab->d_arg, e, count, tab->stream));
       HIP_TRY(hipStreamSynchronize(tab->stream));
       t = tab; at = 0; n = *count;
       if (n == 0 || n > kChainMost || e[0].cell != cell) return fail(MRL_E_HIP, "internal error: a Spec's entry was not read");
@@ -1904,7 +1899,7 @@ int32_t mrl_emit_compressed(const mrl_table* tab, uint32_t which, mrl_box* out, 
   return take_through(n, kEmitChunk, stage, st,
     [&](size_t, uint32_t, char*) -> int32_t { return MRL_OK; },
     [&](size_t first, uint32_t m, char* h) {
-      launch_expand_boxes(g, m, fcell + first, flen + first * 16, fv0 + first, fv1 + first, h, st);
+      return launch_expand_boxes(g, m, fcell + first, flen + first * 16, fv0 + first, fv1 + first, h, st);
     },
     [&](size_t first, uint32_t m, char* h) -> int32_t {
       memcpy((void*)(out + first), h, (size_t)m * sizeof(mrl_box));
@@ -1963,7 +1958,7 @@ int32_t mrl_query_compressed(const mrl_table* tab, const mrl_coord* specs, size_
       return MRL_OK;
     },
     [&](size_t, uint32_t m, char* h) {
-      launch_lookup(g, lists, h, (const uint64_t*)(h + o_vol), m, (uint64_t*)(h + o_cost), (uint16_t*)(h + o_arg), (uint8_t*)(h + o_miss), tab->stream);
+      return launch_lookup(g, lists, h, (const uint64_t*)(h + o_vol), m, (uint64_t*)(h + o_cost), (uint16_t*)(h + o_arg), (uint8_t*)(h + o_miss), tab->stream);
     },
     [&](size_t first, uint32_t m, char* h) -> int32_t {
       const char* miss = h + o_miss;

@@ -195,12 +195,12 @@ void launch_build_index(const Geo& g, const IndexLevels& L, const uint32_t* fcel
                        L.count[l - 1], nodes + L.off[l], L.count[l]);
 }
 
-void launch_lookup(const Geo& g, const LookupList lists[2], const void* points, const uint64_t* vols, uint32_t n_points,
+hipError_t launch_lookup(const Geo& g, const LookupList lists[2], const void* points, const uint64_t* vols, uint32_t n_points,
                    uint64_t* cost_out, uint16_t* arg_out, uint8_t* miss, hipStream_t st) {
-  if (!n_points) return;
+  if (!n_points) return hipSuccess;
   static_assert(kIndexFan == 8, "a group of siblings is eight lanes and a byte of a ballot; node indices shift by 3 bits per level");
-  hipLaunchKernelGGL(lookup_kernel, dim3((n_points + kLookupPoints - 1) / kLookupPoints, 2), dim3(256), 0, st, g,
-                     LookupLists{{lists[0], lists[1]}}, (const uint4*)points, vols, n_points, cost_out, arg_out, miss);
+  return launch_checked(lookup_kernel, dim3((n_points + kLookupPoints - 1) / kLookupPoints, 2), dim3(256), st, g,
+                        LookupLists{{lists[0], lists[1]}}, (const uint4*)points, vols, n_points, cost_out, arg_out, miss);
 }
 
 }  // namespace mrl

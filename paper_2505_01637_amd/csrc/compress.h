@@ -3,9 +3,21 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <tuple>
 #include "dev_params.h"
 
 namespace mrl {
+
+// A launch that gives its own status.  (The runtime's last error may be one that another call of the
+// calling thread left there: it says nothing about this launch.)
+template <class... P, class... A>
+hipError_t launch_checked(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t st, const A&... args) {
+  std::tuple<P...> v(args...);
+  return std::apply([&](P&... a) {
+    void* at[] = {(void*)&a...};
+    return hipLaunchKernel((const void*)kernel, grid, block, at, 0, st);
+  }, v);
+}
 
 // Table geometry passed by value to the compression kernels (cells < 2^32).
 struct Geo {
@@ -94,10 +106,10 @@ void launch_emit(const Geo& g, const DevParams* P, bool is_cost, uint32_t n_boxe
                  const uint8_t* alive, const uint32_t* pos, const uint64_t* cost, const uint16_t* arg, uint32_t* fcell,
                  void* flen, uint64_t* fv0, uint64_t* fv1, hipStream_t st);
 // n boxes of a final list as the 80-byte records of the interface; out: pinned host memory, 16-byte aligned.
-void launch_expand_boxes(const Geo& g, uint32_t n, const uint32_t* fcell, const void* flen, const uint64_t* fv0, const uint64_t* fv1, void* out,
+hipError_t launch_expand_boxes(const Geo& g, uint32_t n, const uint32_t* fcell, const void* flen, const uint64_t* fv0, const uint64_t* fv1, void* out,
                          hipStream_t st);
 // idx, cost_out, arg_out: device memory or pinned host memory.
-void launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const uint16_t* arg, uint64_t* cost_out,
+hipError_t launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const uint16_t* arg, uint64_t* cost_out,
                    uint16_t* arg_out, hipStream_t st);
 
 // The entries of a Spec, of the Spec its rewrite leads to, and so on.
@@ -111,7 +123,7 @@ struct ChainWalk {
   int lay_axis[5], dt_axis[5];              // coordinate axes of an operand's layout and data type, -1 if none
 };
 // At most kChainMost entries to out, their number (at least 1) to n_out: device or pinned host memory.
-void launch_chain(const ChainWalk& w, const uint64_t* cost, const uint16_t* arg, ChainEntry* out, uint32_t* n_out, hipStream_t st);
+hipError_t launch_chain(const ChainWalk& w, const uint64_t* cost, const uint16_t* arg, ChainEntry* out, uint32_t* n_out, hipStream_t st);
 
 // Point lookups in a final box list: a packed hierarchy of bounding boxes over the list's order.
 constexpr uint32_t kIndexFan = 8;          // children per node
@@ -134,7 +146,7 @@ struct LookupList {
 };
 // lists: decisions, costs.  points: 16 bytes per point (coordinates, zero padded); vols: the volume
 // b*m*k*n of each.  miss: a byte per list and point (n_points apart), 1 where no box holds the point.
-void launch_lookup(const Geo& g, const LookupList lists[2], const void* points, const uint64_t* vols, uint32_t n_points,
+hipError_t launch_lookup(const Geo& g, const LookupList lists[2], const void* points, const uint64_t* vols, uint32_t n_points,
                    uint64_t* cost_out, uint16_t* arg_out, uint8_t* miss, hipStream_t st);
 
 constexpr uint32_t kScanTileItems = 2048;   // items per scan tile (tile_tmp needs n/2048 + 1 words)

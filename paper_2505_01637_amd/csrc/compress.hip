@@ -947,9 +947,10 @@ __global__ __launch_bounds__(256) void expand_boxes_kernel(Geo g, uint32_t n, co
   out[i] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-void launch_expand_boxes(const Geo& g, uint32_t n, const uint32_t* fcell, const void* flen, const uint64_t* fv0, const uint64_t* fv1, void* out,
+hipError_t launch_expand_boxes(const Geo& g, uint32_t n, const uint32_t* fcell, const void* flen, const uint64_t* fv0, const uint64_t* fv1, void* out,
                          hipStream_t st) {
-  if (n) hipLaunchKernelGGL(expand_boxes_kernel, dim3((n * 5u + 255u) / 256u), dim3(256), 0, st, g, n, fcell, (const uint4*)flen, fv0, fv1, (uint4*)out);
+  if (!n) return hipSuccess;
+  return launch_checked(expand_boxes_kernel, dim3((n * 5u + 255u) / 256u), dim3(256), st, g, n, fcell, (const uint4*)flen, fv0, fv1, (uint4*)out);
 }
 
 // ---------------------------------------------------------------- query
@@ -962,9 +963,9 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint64_t* __restrict_
   arg_out[i] = arg[idx[i]];
 }
 
-void launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const uint16_t* arg, uint64_t* cost_out,
+hipError_t launch_gather(const uint64_t* idx, uint32_t n, const uint64_t* cost, const uint16_t* arg, uint64_t* cost_out,
                    uint16_t* arg_out, hipStream_t st) {
-  hipLaunchKernelGGL(gather_kernel, dim3((n + 255) / 256), dim3(256), 0, st, idx, n, cost, arg, cost_out, arg_out);
+  return launch_checked(gather_kernel, dim3((n + 255) / 256), dim3(256), st, idx, n, cost, arg, cost_out, arg_out);
 }
 
 // One lane follows a program through one table: entry, rewrite, the Spec it leads to, as long as that
@@ -1027,8 +1028,8 @@ __global__ __launch_bounds__(64) void chain_kernel(ChainWalk w, const uint64_t* 
   *n_out = n;
 }
 
-void launch_chain(const ChainWalk& w, const uint64_t* cost, const uint16_t* arg, ChainEntry* out, uint32_t* n_out, hipStream_t st) {
-  hipLaunchKernelGGL(chain_kernel, dim3(1), dim3(64), 0, st, w, cost, arg, out, n_out);
+hipError_t launch_chain(const ChainWalk& w, const uint64_t* cost, const uint16_t* arg, ChainEntry* out, uint32_t* n_out, hipStream_t st) {
+  return launch_checked(chain_kernel, dim3(1), dim3(64), st, w, cost, arg, out, n_out);
 }
 
 __global__ __launch_bounds__(256) void zero_words_kernel(unsigned long long* p, uint32_t n) {

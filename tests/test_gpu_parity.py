@@ -1195,3 +1195,26 @@ def test_box_lists_taken_while_another_thread_solves():
         assert [got["F"].boxes(which).tobytes() for which in (0, 1)] == lists
     th.join(timeout=60)
     assert not th.is_alive() and not errors, errors
+
+
+def test_answers_do_not_depend_on_an_earlier_call_s_error():
+    """The runtime keeps the last error of a thread until somebody asks for it.  One that the caller
+    left there (a device that does not exist) is not taken for an error of a question's launch."""
+    import ctypes as C
+    B = _binding()
+    cfg = W.config(5, max_size=8)
+    want = O.solve_config(cfg)["F"]
+    _, got = B.solve_config(cfg)
+    tab, hip = got["F"], B.lib()                # (the library's handle finds its runtime's functions too)
+    x = np.array(np.unravel_index(np.flatnonzero(want["cost"] != O.INF)[-1], tab.extents))
+    lists = [O.compress_table(cfg["target"], next(lat for label, lat, _ in cfg["lattices"] if label == "F"), want["cost"], want["argmin"])]
+    asks = [lambda: tab.query(x)[0][0], lambda: tab.query(x, noalloc=True)[0][0], lambda: tab.query(x, compressed=True)[0][0],
+            lambda: tab.schedule(x)[0][3], lambda: tab.boxes(1).tobytes() == lists[0][1].tobytes()]
+    first = [ask() for ask in asks]             # (the box index is built here)
+    try:
+        for ask, answer in zip(asks, first):
+            assert hip.hipSetDevice(C.c_int(9999)) != 0
+            assert ask() == answer
+    finally:
+        hip.hipGetLastError()
+    assert first[:4] == [want["cost"][np.ravel_multi_index(tuple(x), tab.extents)]] * 4 and first[4]
