@@ -86,8 +86,10 @@ struct Compiled {
 // Offsets of the fixed part of the scratch buffer.
 struct FixedLayout {
   size_t counters, params, tiles, level_shapes, level_off, mk_entry, qdec, recs, masks, item_tasks, sort_tmp, list_small, bundle_first, list_wide, list_cnt, bind, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
-      upload_end, end;
+      upload_end, fill_end, end;
   uint32_t n_words;
+  // a solve's least: the fill's buffers share their place with the compression's and its lists
+  size_t least() const { return fill_end > end ? fill_end : end; }
 };
 
 // Whether the pass on the second merge axis a1 runs on the cells, before the boxes are made: the
@@ -125,7 +127,11 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.mk_entry = take(c.mk_entry.size());
   f.qdec = take(c.qdec.size() * 4);
   f.upload_end = o;
-  const size_t n_items = (size_t)c.n_shapes * c.P.npass;
+  f.fitmap = take((size_t)f.n_words * 8 + 16);
+  // What the fill alone needs lies where the compression, which starts when the fill has ended, has
+  // its masks and lists: an 80-byte record per shape would otherwise be 6 % of what a solve of a
+  // lattice with two memory levels asks for.
+  const size_t shared = o, n_items = (size_t)c.n_shapes * c.P.npass;
   f.recs = f.sort_tmp = f.masks = f.item_tasks = f.list_small = f.bundle_first = f.list_wide = f.list_cnt = f.bind = 0;
   if (!c.P.gather) {
     f.masks = take(n_items * ((size_t)c.P.nwp << c.P.ndt) * 8);
@@ -138,7 +144,8 @@ FixedLayout fixed_layout(const Compiled& c) {
     f.list_cnt = take(3 * c.level_off.size() * 4);
     if (c.P.moves) f.bind = take(bind_entries(c) * 8);
   }
-  f.fitmap = take((size_t)f.n_words * 8 + 16);
+  f.fill_end = o;
+  o = shared;
   f.maskD = take((size_t)f.n_words * 8);
   f.maskC = take((size_t)f.n_words * 8);
   f.mask2D = f.mask2C = f.colD = f.colC = 0;
@@ -163,7 +170,6 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.tile_tmp = take((c.n_specs / kScanTileItems + 2) * 4);
   f.tile_tmp2 = take((c.n_specs / kScanTileItems + 2) * 4);
   f.totals = take(64);
-  o += 18 * 4096;               // not used: the size that a solve asks for is part of the interface
   f.end = o;
   return f;
 }
@@ -752,7 +758,10 @@ int32_t mrl_table_bytes(const mrl_target* t, const mrl_lattice_desc* lat, size_t
   const Compiled& c = *cp;
   if (cost_bytes) *cost_bytes = c.n_specs * 8;
   if (argmin_bytes) *argmin_bytes = c.n_specs * 2;
-  if (scratch_bytes) *scratch_bytes = fixed_layout(c).end + 2 * final_bytes(c.n_specs) + 2 * work_bytes(c.n_specs);
+  if (scratch_bytes) {
+    const FixedLayout f = fixed_layout(c);
+    *scratch_bytes = std::max(f.fill_end, f.end + 2 * final_bytes(c.n_specs) + 2 * work_bytes(c.n_specs));
+  }
   return MRL_OK;
   });
 }
@@ -944,7 +953,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
 
   const FixedLayout f = fixed_layout(c);
   tab->f = f;
-  if (scratch_bytes < f.end) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.end);
+  if (scratch_bytes < f.least()) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
   char* base = (char*)d_scratch;
   hipStream_t st = (hipStream_t)hip_stream;
   HIP_TRY(hipGetDevice(&tab->device));
@@ -1290,7 +1299,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     tab->list_n[which] = nf;
     front += fb;
   }
-  needed = front + wbL[0] + wbL[1];
+  needed = std::max(f.fill_end, front + wbL[0] + wbL[1]);
   HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
   HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
   HIP_TRY(hipGetLastError());

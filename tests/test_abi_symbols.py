@@ -174,3 +174,17 @@ def test_level_beyond_the_work_lists_is_refused_before_device_work():
                            C.c_void_p(1 << 42), C.c_size_t(1 << 50), C.c_void_p(None), C.byref(h), C.byref(stats))
     assert rc == B.E_INVAL and not h.value
     assert "dependency level" in B.lib().mrl_last_error().decode()
+
+
+def test_scratch_asked_for_does_not_grow():
+    """What sufficed for any contents keeps sufficing: the scratch sizes that callers have been given for
+    lattices with 8 to 8192 entries per shape, Move tables and what reads them, a bounded lattice."""
+    known = {(1, "M"): 6122496, (2, "M"): 3046799872, (3, "M"): 16980480, (4, "M"): 4323233536, (5, "E"): 67266304, (5, "F"): 81646040576,
+             (7, "B"): 7449747712, (9, "V"): 444924160, (9, "M"): 3050599680, (10, "G"): 12400997632, (11, "R"): 14367232, (12, "M"): 12200152320}
+    for (number, label), most in known.items():
+        cfg = W.config(number)
+        lat = next(lat for lb, lat, _ in cfg["lattices"] if lb == label)
+        assert B.table_bytes(B.Target(cfg["target"]), lat)[2] <= most, (number, label)
+    cfg = W.config(1)
+    r = list(range(1, 256))
+    assert B.table_bytes(B.Target(cfg["target"]), dict(cfg["lattices"][0][1], sizes=[[1], r, r, r]))[2] <= 24313211136

@@ -1218,3 +1218,27 @@ def test_answers_do_not_depend_on_an_earlier_call_s_error():
     finally:
         hip.hipGetLastError()
     assert first[:4] == [want["cost"][np.ravel_multi_index(tuple(x), tab.extents)]] * 4 and first[4]
+
+
+@pytest.mark.parametrize("number,max_size,label", [(1, None, "M"), (2, 5, "M"), (4, 16, "M"), (5, 2, "F"), (7, 2, "B"), (12, 4, "M")])
+def test_scratch_at_its_limits(number, max_size, label):
+    """The buffers that only the fill needs share their place with the compression's: a table solved with
+    exactly the scratch that mrl_table_bytes asks for, and with exactly what that solve then says it
+    used, is the same, and 256 bytes less are refused."""
+    B = _binding()
+    cfg = W.config(number, max_size=max_size)
+    want = O.solve_config(cfg)
+    target, tabs = B.solve_config(cfg)
+    lat, deps = next((lat, [tabs[d] for d in deps]) for lb, lat, deps in cfg["lattices"] if lb == label)
+    dec, cst = O.compress_table(cfg["target"], lat, want[label]["cost"], want[label]["argmin"])
+    used = tabs[label].stats.scratch_used
+    assert used <= B.table_bytes(target, lat)[2]
+    for scratch in (B.table_bytes(target, lat)[2], used):
+        tab = B.solve(target, lat, deps=deps, scratch_bytes=scratch)
+        cost, arg = tab.dense()
+        assert np.array_equal(cost, want[label]["cost"]) and np.array_equal(arg, want[label]["argmin"])
+        assert tab.boxes(0).tobytes() == dec.tobytes() and tab.boxes(1).tobytes() == cst.tobytes()
+        assert tab.stats.scratch_used == used
+    with pytest.raises(B.MorelloError) as e:
+        B.solve(target, lat, deps=deps, scratch_bytes=used - 256)
+    assert e.value.code == B.E_NOMEM
