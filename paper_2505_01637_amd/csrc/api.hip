@@ -512,12 +512,15 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
 }
 
 
-// compile() costs a few hundred microseconds for the larger lattices; repeated solves of the
-// same (target, lattice) reuse the result.  Entries are immutable once published.  kCompiledMost of
-// them, the least recently used goes first: a program that takes turns between a few targets keeps
-// all of its lattices (config 5 has three; with 8 entries, first in first out, three targets in turn
-// compiled all of them in every step: 6.8 instead of 5.4 ms).
-constexpr size_t kCompiledMost = 32;
+// compile() costs up to a few milliseconds for the larger lattices; repeated solves of the same
+// (target, lattice) reuse the result.  Entries are immutable once published; the least recently used
+// goes first.  A program that takes turns between a few targets keeps all of its lattices: up to
+// kCompiledMost of them within kCompiledBytes, and kCompiledLeast however large they are (config 5 has
+// three lattices; with 8 entries, first in first out, three targets in turn compiled all of them in every
+// step: 6.8 instead of 5.4 ms.  That helps a program which comes back to a target; a target's first
+// solve compiles its lattices as ever).
+constexpr size_t kCompiledMost = 32, kCompiledLeast = 8;
+constexpr size_t kCompiledBytes = 64u << 20;
 using CompiledPtr = std::shared_ptr<const Compiled>;
 
 bool same_problem(const Compiled& c, const mrl_target_desc& T, const mrl_lattice_desc& L) {
@@ -549,9 +552,15 @@ int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, Compil
   const int32_t rc = compile(T, L, *c);
   if (rc) return rc;
   std::lock_guard<std::mutex> lock(mu);
-  if (cache.size() >= kCompiledMost) cache.erase(cache.begin());
   cache.push_back(c);
   out = c;
+  // what an entry holds: its lists, and from its first solve on their image in pinned memory
+  size_t bytes = 0;
+  for (const CompiledPtr& e : cache) bytes += 2 * fixed_layout(*e).upload_end;
+  while (cache.size() > kCompiledMost || (cache.size() > kCompiledLeast && bytes > kCompiledBytes)) {
+    bytes -= 2 * fixed_layout(*cache.front()).upload_end;
+    cache.erase(cache.begin());
+  }
   return MRL_OK;
 }
 

@@ -188,3 +188,22 @@ def test_scratch_asked_for_does_not_grow():
     cfg = W.config(1)
     r = list(range(1, 256))
     assert B.table_bytes(B.Target(cfg["target"]), dict(cfg["lattices"][0][1], sizes=[[1], r, r, r]))[2] <= 24313211136
+
+
+def test_compiled_lattices_are_kept_within_a_bound_of_bytes():
+    """Lattices of 4.2 M shapes (33 MB each with their upload image) for 28 targets: at most eight of
+    them are kept, so the process does not grow by all of them."""
+    def resident():
+        with open("/proc/self/statm") as f:
+            return int(f.read().split()[1]) * os.sysconf("SC_PAGE_SIZE")
+    cfg = W.config(1)
+    r = list(range(1, 256))
+    lat = dict(cfg["lattices"][0][1], sizes=[[1], r, r[:64], r])
+    targets = []
+    for i in range(28):
+        cfg["target"]["loop_overhead"] = i
+        targets.append(B.Target(cfg["target"]))
+        B.geometry(targets[-1], lat)
+        if i == 7:
+            before = resident()
+    assert resident() - before < 5 * 4 * 255 * 255 * 64
