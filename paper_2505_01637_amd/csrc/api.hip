@@ -447,7 +447,6 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
       P.pos_info[i] = info;
       P.pos_entry[i] = pack | order[i].first << 8 | combo << 16;
     }
-    for (uint32_t r = 0; r < P.nranks; r++) P.pos_info[P.rank_off[r]] |= (r + 1) << 24;     // first position of rank r
   }
 
   // dependency level of a shape = sum over tiled dims of the longest divisor chain below its size
@@ -567,7 +566,7 @@ int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, Compil
 // A second stream (default priority, non-blocking) for work that is independent of what runs on
 // the caller's stream: the wide items of a dependency level beside its other items, and one of the
 // two box lists beside the other; with it the events and the pinned counters a solve needs.
-constexpr size_t kPinnedCounts = 16 + 4 * 1024;   // u32: 16 for the box lists, then the level lists' lengths (4 per level)
+constexpr size_t kPinnedCounts = 16 + 3 * 1024;   // u32: 16 for the box lists, then the level lists' lengths (3 per level, at most 1017 levels)
 struct Aux {
   hipStream_t stream = nullptr;
   std::vector<hipEvent_t> events;
@@ -937,7 +936,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
       if (V.P.dt_bit[0] == kNoBit && (V.P.base_bf16[0] || V.P.base_bf16[1])) return fail(MRL_E_INVAL, "a MOVE table without dtype bits must be f32");
       P.costM = deps[0]->d_cost;
       tab->deps[0] = deps[0];
-      P.GV = V.P.G; P.VV = V.P.V; P.nszV = V.P.nsz[3]; P.QV = V.P.Q; P.qV_top = V.P.Q - 1;
+      P.GV = V.P.G; P.VV = V.P.V; P.nszV = V.P.nsz[3]; P.QV = V.P.Q;
       for (int a = 0; a < 4; a++) P.limV_stride[a] = V.P.lim_stride[a];
       for (int i = 0; i < 2; i++) { P.layV[i] = V.P.lay_bit[i]; P.dtV[i] = V.P.dt_bit[i]; }
     } else if (n_deps != 0) {
@@ -945,7 +944,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     }
     return MRL_OK;
   };
-  // (the lane-per-Spec kinds have no pre-fill to run ahead: they take their deps at once)
+  // (the kinds filled by gathers have no pre-fill to run ahead: they take their deps at once)
   const bool deps_late = (bool)late_deps && !P.gather && n_deps > 0;
   if (late_deps && !deps_late && n_deps > 0) {
     rc = late_deps(late_tables, late_ready);
@@ -1166,7 +1165,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   const bool on_cells = second_on_cells(c, nullptr, &a1);
   const unsigned long long* colL[2] = {nullptr, nullptr};
   if (on_cells) launch_zero_words((unsigned long long*)(base + f.colD), (uint32_t)((f.colC - f.colD) / 8 + c.n_specs / g.ext[a1]), st);
-  // the two prefix sums side by side (each is three short kernels): the decisions' on the helper stream
+  // the two prefix sums side by side (each is one to three short kernels): the decisions' on the helper stream
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   HIP_TRY(hipStreamWaitEvent(s2, aux->events[ev_used++], 0));
   if (on_cells) {

@@ -71,7 +71,6 @@ struct DevParams {
   uint32_t nranks;
   uint32_t rank_off[kMaxRanks + 2];
   // per rank-major position: pack | (operands resident in level l, one nibble per level) << 8
-  // | (r + 1) << 24 at the first position of rank r
   uint32_t pos_info[kMaxCombo];
   uint32_t pos_entry[kMaxCombo];   // pack | rank << 8 | mixed-radix index << 16
   uint32_t nwp;              // 64-bit words of an item's mask per value of the dtype bits: ceil(ncombo / 64)
@@ -93,7 +92,7 @@ struct DevParams {
   uint32_t weight[4];        // per-level weight of m(t)
   uint32_t line_bytes;
   uint32_t GV, VV, nszV;     // the Move table: entries per shape, variants, number of column sizes
-  uint32_t QV, qV_top;       // its abstract vectors per level pair, and the index of (contiguous, aligned) twice
+  uint32_t QV;               // its abstract vectors per level pair
   uint32_t layV[2], dtV[2];  // bit positions of its layout and dtype bits, kNoBit if absent
   uint32_t limV_stride[4];   // strides of its four abstract-value axes inside the abstract vector's index
   // ---- packed layouts (Move lattices and the Matmul whose Moves are Move Specs) ----

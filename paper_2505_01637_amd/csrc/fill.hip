@@ -1042,8 +1042,8 @@ void launch_fill_ones(void* p, size_t bytes, hipStream_t stream, bool short_live
 // same level assignment of a smaller shape (a lower dependency level of shapes), so the Specs of
 // (level l, rank r) depend only on (l, r' < r) and (l' < l, r): all pairs on one diagonal
 // l + r = d are independent, and one launch takes a whole diagonal, one segment of workgroups per
-// pair.  One lane per Spec, every candidate a gather from finished entries.  Lane -> (shape of
-// the level, level assignment of the rank, level of the fused Spec's intermediate, bound vector,
+// pair.  Every candidate is a gather from finished entries.  Specs are numbered (shape of the
+// level, level assignment of the rank, level of the fused Spec's intermediate, bound vector,
 // variant), variant fastest.  A bufferize (fused Spec) allocates the intermediate in its level:
 // it needs 4 * m * n bytes of that level's bound, and both stages get the rest, rounded down.
 //
