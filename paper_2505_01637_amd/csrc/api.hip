@@ -90,6 +90,7 @@ struct FixedLayout {
   uint32_t n_words;
   // a solve's least: the fill's buffers share their place with the compression's and its lists
   size_t least() const { return fill_end > end ? fill_end : end; }
+  size_t image_bytes() const { return upload_end - counters; }          // of what is uploaded, in pinned memory
 };
 
 // Whether the pass on the second merge axis a1 runs on the cells, before the boxes are made: the
@@ -118,20 +119,21 @@ FixedLayout fixed_layout(const Compiled& c) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
   f.n_words = (uint32_t)((c.n_specs + 63) / 64);
-  // uploaded in one copy: counters (zero), parameters, tile lists, level lists, microkernel table
+  f.fitmap = take((size_t)f.n_words * 8 + 16);
+  // uploaded in one copy: counters (zero), parameters, tile lists, level lists, microkernel table, bound vectors
   f.counters = take(sizeof(Counters));
   f.params = take(sizeof(DevParams));
+  // From here on up to fill_end lies what the fill alone needs, and over it the compression's masks
+  // and lists, which are written when the fill has ended: an 80-byte record per shape would otherwise
+  // be 6 % of what a solve of a lattice with two memory levels asks for.
+  const size_t shared = o;
   f.tiles = take(c.tiles.size() * sizeof(TileEntry) + 8);
   f.level_shapes = take(c.level_shapes.size() * 4);
   f.level_off = take(c.level_off.size() * 4);
   f.mk_entry = take(c.mk_entry.size());
   f.qdec = take(c.qdec.size() * 4);
   f.upload_end = o;
-  f.fitmap = take((size_t)f.n_words * 8 + 16);
-  // What the fill alone needs lies where the compression, which starts when the fill has ended, has
-  // its masks and lists: an 80-byte record per shape would otherwise be 6 % of what a solve of a
-  // lattice with two memory levels asks for.
-  const size_t shared = o, n_items = (size_t)c.n_shapes * c.P.npass;
+  const size_t n_items = (size_t)c.n_shapes * c.P.npass;
   f.recs = f.sort_tmp = f.masks = f.item_tasks = f.list_small = f.bundle_first = f.list_wide = f.list_cnt = f.bind = 0;
   if (!c.P.gather) {
     f.masks = take(n_items * ((size_t)c.P.nwp << c.P.ndt) * 8);
@@ -555,9 +557,9 @@ int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, Compil
   out = c;
   // what an entry holds: its lists, and from its first solve on their image in pinned memory
   size_t bytes = 0;
-  for (const CompiledPtr& e : cache) bytes += 2 * fixed_layout(*e).upload_end;
+  for (const CompiledPtr& e : cache) bytes += 2 * fixed_layout(*e).image_bytes();
   while (cache.size() > kCompiledMost || (cache.size() > kCompiledLeast && bytes > kCompiledBytes)) {
-    bytes -= 2 * fixed_layout(*cache.front()).upload_end;
+    bytes -= 2 * fixed_layout(*cache.front()).image_bytes();
     cache.erase(cache.begin());
   }
   return MRL_OK;
@@ -980,16 +982,17 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   P.mk_entry = (const uint8_t*)(base + f.mk_entry);
   P.qdec = (const uint32_t*)(base + f.qdec);
   P.bind = (const uint64_t*)(base + f.bind);
+  const auto image = [&](size_t at) { return c.staging + (at - f.counters); };
   if (!c.staging) {
-    HIP_TRY(hipHostMalloc((void**)&c.staging, f.upload_end, hipHostMallocDefault));
-    memset(c.staging, 0, f.upload_end);
-    if (!c.tiles.empty()) memcpy(c.staging + f.tiles, c.tiles.data(), c.tiles.size() * sizeof(TileEntry));
-    memcpy(c.staging + f.level_shapes, c.level_shapes.data(), c.level_shapes.size() * 4);
-    memcpy(c.staging + f.level_off, c.level_off.data(), c.level_off.size() * 4);
-    memcpy(c.staging + f.mk_entry, c.mk_entry.data(), c.mk_entry.size());
-    memcpy(c.staging + f.qdec, c.qdec.data(), c.qdec.size() * 4);
+    HIP_TRY(hipHostMalloc((void**)&c.staging, f.image_bytes(), hipHostMallocDefault));
+    memset(c.staging, 0, f.image_bytes());
+    if (!c.tiles.empty()) memcpy(image(f.tiles), c.tiles.data(), c.tiles.size() * sizeof(TileEntry));
+    memcpy(image(f.level_shapes), c.level_shapes.data(), c.level_shapes.size() * 4);
+    memcpy(image(f.level_off), c.level_off.data(), c.level_off.size() * 4);
+    memcpy(image(f.mk_entry), c.mk_entry.data(), c.mk_entry.size());
+    if (!c.qdec.empty()) memcpy(image(f.qdec), c.qdec.data(), c.qdec.size() * 4);
   }
-  memcpy(c.staging + f.params, &P, sizeof P);
+  memcpy(image(f.params), &P, sizeof P);
   AuxLease lease;
   rc = get_aux(2 * (size_t)n_lev + 8, lease);
   if (rc) return rc;
@@ -1001,7 +1004,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     hipStream_t a, b;
     ~Drain() { (void)hipStreamSynchronize(a); (void)hipStreamSynchronize(b); }
   } drain{st, aux->stream};
-  HIP_TRY(hipMemcpyAsync(base, c.staging, f.upload_end, hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(base + f.counters, c.staging, f.image_bytes(), hipMemcpyHostToDevice, st));
 
   // ---- fill: plan, then one launch (or two) per dependency level ----
   hipEvent_t* ev = aux->timing;
@@ -1096,8 +1099,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     deps = late_tables;
     rc = bind_deps();
     if (rc) return rc;
-    memcpy(c.staging + f.params, &P, sizeof P);
-    HIP_TRY(hipMemcpyAsync(d_P, c.staging + f.params, sizeof P, hipMemcpyHostToDevice, st));
+    memcpy(image(f.params), &P, sizeof P);
+    HIP_TRY(hipMemcpyAsync(d_P, image(f.params), sizeof P, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(uploaded, st));
     for (uint32_t i = 0; i < n_deps; i++) HIP_TRY(hipStreamWaitEvent(st, late_ready[i], 0));
   }

@@ -188,6 +188,10 @@ def test_scratch_asked_for_does_not_grow():
     cfg = W.config(1)
     r = list(range(1, 256))
     assert B.table_bytes(B.Target(cfg["target"]), dict(cfg["lattices"][0][1], sizes=[[1], r, r, r]))[2] <= 24313211136
+    # long bound vectors: four levels of finite capacity, 67,320 bounds per level assignment
+    cfg = W.config(7)
+    cfg["target"]["capacity_bytes"] = [256, 512, 32768, 1 << 34]
+    assert B.table_bytes(B.Target(cfg["target"]), dict(cfg["lattices"][0][1], sizes=[[1], [1, 2], [1], [1]]))[2] <= 1559586048
 
 
 def test_compiled_lattices_are_kept_within_a_bound_of_bytes():

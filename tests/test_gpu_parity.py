@@ -1220,7 +1220,7 @@ def test_answers_do_not_depend_on_an_earlier_call_s_error():
     assert first[:4] == [want["cost"][np.ravel_multi_index(tuple(x), tab.extents)]] * 4 and first[4]
 
 
-@pytest.mark.parametrize("number,max_size,label", [(1, None, "M"), (2, 5, "M"), (4, 16, "M"), (5, 2, "F"), (7, 2, "B"), (12, 4, "M")])
+@pytest.mark.parametrize("number,max_size,label", [(1, None, "M"), (2, 5, "M"), (4, 16, "M"), (5, 2, "F"), (7, 2, "B"), (9, 3, "V"), (12, 4, "M")])
 def test_scratch_at_its_limits(number, max_size, label):
     """The buffers that only the fill needs share their place with the compression's: a table solved with
     exactly the scratch that mrl_table_bytes asks for, and with exactly what that solve then says it
