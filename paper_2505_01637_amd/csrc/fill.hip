@@ -524,9 +524,10 @@ __device__ __forceinline__ void flush_counters(Counters* __restrict__ ctr, uint3
 
 // One bundle (starts: the level's bundle starts; nullptr: an item each) per workgroup of T threads.
 // LAY: the lattice has layout bits.  MOVES: the Matmul whose Moves are Move Specs.
-// Bound by instruction issue on levels with many items (2,200 lane-instructions per task with eight
-// lanes per task everywhere, about 1,200 with four) and by the chain of memory and LDS round trips
-// on the others (9 us for one item of 4 tasks: records 2.4, lists 2, tiles 2.3, ranks 1.8).  Fill
+// Bound by instruction issue on levels with many items (counters: 1,890 vector lane-instructions per
+// task in config 5's F, 3,250 in config 2; the vector units issue half of the time that the launches
+// of 128 threads take) and by the chain of memory and LDS round trips on the others (a fifth of the
+// time there; 9 us for one item of 4 tasks: records 2.4, lists 2, tiles 2.3, ranks 1.8).  Fill
 // times against one item per wave without bundles or records: config 2 1.49 -> 0.77 ms, config 3
 // 0.69 -> 0.60, config 4 0.80 -> 0.73, config 5's F 2.22 -> 2.12, config 12's Matmul, which then was
 // a lane per Spec with three gathers per Move, 5.04 -> 2.16.
@@ -1061,7 +1062,7 @@ void launch_fill_ones(void* p, size_t bytes, hipStream_t stream, bool short_live
 // candidates come in the order of their ids, so a strictly lower cost is all that has to be tested.
 // With a lane per Spec that decoded its own shape and levels the kernel was bound by those
 // instructions (config 7, 41 M Specs, 413 M candidates: fill 1.84 ms, now 1.00 ms, about half of
-// it instruction issue; config 12's Move table, 16.8 M Specs: 0.84 ms, now 0.36 ms).
+// it instruction issue; config 12's Move table, 16.8 M Specs: 0.84 ms, now 0.42 ms).
 // Needs enough entries per unit to fill a wave (kUnitLanes); narrower units stay with the kernel below.
 constexpr uint32_t kUnitLanes = 32;
 constexpr int kUnitBatch = 8;         // candidates whose reads are in flight together
