@@ -741,6 +741,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 5 
   // ---- 1. tile and bufferize candidates of every task (sub-Specs of other shapes / tables: final) ----
   uint32_t max_tile = 0;
   for (uint32_t j = 0; j < n_it; j++) { const uint32_t t = L.it_ntile[j]; max_tile = t > max_tile ? t : max_tile; }
+  max_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)max_tile);          // the same in every lane: kept as a scalar
   const bool has_buf = !MOVES && (P->kind == kKindF || P->split);
   const uint64_t s_serial = P->s, s_par = P->sync;
   const uint64_t* __restrict__ serial = P->costM;
