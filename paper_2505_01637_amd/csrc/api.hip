@@ -59,6 +59,53 @@ constexpr uint64_t kFullWaves = 4096;       // more than one only where this man
 constexpr uint32_t kLookupChunk = 32768;   // points per launch of a lookup in the box lists
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+// Pinned host memory for upload images.  Pinning new memory costs about 0.45 ms per MB, so blocks that
+// are given back stay for the next image: at most kImageKeep of them and kImageKeepBytes, the
+// smallest go first (the largest, where the bytes are too many).
+constexpr size_t kImageKeep = 8, kImageKeepBytes = 16u << 20;
+struct PinnedImage { char* mem = nullptr; size_t bytes = 0; };
+std::mutex g_image_mu;
+std::vector<PinnedImage> g_image_idle;      // by size
+
+// most: the largest idle block to take for it.
+int32_t take_image(size_t bytes, size_t most, PinnedImage& out) {
+  {
+    std::lock_guard<std::mutex> lock(g_image_mu);
+    g_image_idle.reserve(kImageKeep + 1);   // (so that giving back allocates nothing)
+    for (size_t i = 0; i < g_image_idle.size(); i++)
+      if (g_image_idle[i].bytes >= bytes && g_image_idle[i].bytes <= most) {
+        out = g_image_idle[i];
+        g_image_idle.erase(g_image_idle.begin() + i);
+        return MRL_OK;
+      }
+  }
+  const size_t size = (bytes + 0xFFFF) & ~(size_t)0xFFFF;
+  HIP_TRY(hipHostMalloc((void**)&out.mem, size, hipHostMallocPortable));
+  out.bytes = size;
+  return MRL_OK;
+}
+
+void give_image(PinnedImage& image) {
+  if (!image.mem) return;
+  PinnedImage drop[kImageKeep + 1];
+  size_t n_drop = 0, total = image.bytes;
+  {
+    std::lock_guard<std::mutex> lock(g_image_mu);
+    auto at = g_image_idle.begin();
+    for (const PinnedImage& x : g_image_idle) { total += x.bytes; at += x.bytes < image.bytes; }
+    g_image_idle.insert(at, image);
+    while (total > kImageKeepBytes) { total -= g_image_idle.back().bytes; drop[n_drop++] = g_image_idle.back(); g_image_idle.pop_back(); }
+    if (g_image_idle.size() > kImageKeep) { drop[n_drop++] = g_image_idle.front(); g_image_idle.erase(g_image_idle.begin()); }
+  }
+  for (size_t i = 0; i < n_drop; i++) (void)hipHostFree(drop[i].mem);
+  image = PinnedImage();
+}
+
+struct ImageLease {
+  PinnedImage image;
+  ~ImageLease() { give_image(image); }
+};
+
 // Host-side compiled lattice: everything derived from (target, lattice).
 struct Compiled {
   DevParams P;
@@ -76,11 +123,12 @@ struct Compiled {
   int lay_axis[5], dt_axis[5];            // coordinate axis of the operand's bit, -1 if none
   mrl_target_desc target;
   mrl_lattice_desc lat;                   // sizes pointers re-pointed to this->sizes
-  // Pinned image of the uploaded head of the scratch buffer (counters .. mk_entry), built at the
-  // first solve and patched per call (device pointers).
-  mutable char* staging = nullptr;
+  // Pinned image of what a solve uploads (counters .. qdec), patched per call (device pointers).  The
+  // first solve borrows a block for it, the second one keeps its own: many targets are solved once.
+  mutable PinnedImage staging;
+  mutable bool solved = false;
   mutable std::mutex solve_mu;            // solves of one compiled lattice take turns (they share the image)
-  ~Compiled() { if (staging) (void)hipHostFree(staging); }
+  ~Compiled() { give_image(staging); }
 };
 
 // Offsets of the fixed part of the scratch buffer.
@@ -982,10 +1030,16 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   P.mk_entry = (const uint8_t*)(base + f.mk_entry);
   P.qdec = (const uint32_t*)(base + f.qdec);
   P.bind = (const uint64_t*)(base + f.bind);
-  const auto image = [&](size_t at) { return c.staging + (at - f.counters); };
-  if (!c.staging) {
-    HIP_TRY(hipHostMalloc((void**)&c.staging, f.image_bytes(), hipHostMallocDefault));
-    memset(c.staging, 0, f.image_bytes());
+  ImageLease borrowed;
+  char* upload = c.staging.mem;
+  const auto image = [&](size_t at) { return upload + (at - f.counters); };
+  if (!upload) {
+    PinnedImage& to = c.solved ? c.staging : borrowed.image;
+    rc = take_image(f.image_bytes(), c.solved ? 2 * f.image_bytes() + (64u << 10) : SIZE_MAX, to);
+    if (rc) return rc;
+    c.solved = true;
+    upload = to.mem;
+    memset(upload, 0, f.params - f.counters);
     if (!c.tiles.empty()) memcpy(image(f.tiles), c.tiles.data(), c.tiles.size() * sizeof(TileEntry));
     memcpy(image(f.level_shapes), c.level_shapes.data(), c.level_shapes.size() * 4);
     memcpy(image(f.level_off), c.level_off.data(), c.level_off.size() * 4);
@@ -1004,7 +1058,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     hipStream_t a, b;
     ~Drain() { (void)hipStreamSynchronize(a); (void)hipStreamSynchronize(b); }
   } drain{st, aux->stream};
-  HIP_TRY(hipMemcpyAsync(base + f.counters, c.staging, f.image_bytes(), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipMemcpyAsync(base + f.counters, upload, f.image_bytes(), hipMemcpyHostToDevice, st));
 
   // ---- fill: plan, then one launch (or two) per dependency level ----
   hipEvent_t* ev = aux->timing;

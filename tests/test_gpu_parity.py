@@ -1242,3 +1242,54 @@ def test_scratch_at_its_limits(number, max_size, label):
     with pytest.raises(B.MorelloError) as e:
         B.solve(target, lat, deps=deps, scratch_bytes=used - 256)
     assert e.value.code == B.E_NOMEM
+
+
+def test_upload_images_borrowed_and_kept():
+    """A lattice's first solve borrows pinned memory for what it uploads, its second keeps a block of
+    its own: more targets than blocks stay idle, in turn, of lattices of different sizes (10 KB to 0.5 MB
+    of lists), one of them from three threads at once, and a solve that fails in between."""
+    import threading
+    import torch
+    B = _binding()
+    jobs = []
+    for i in range(12):
+        cfg = W.config((1, 2, 4)[i % 3], max_size=(8, 12, 16)[i % 3])
+        cfg["target"]["loop_overhead"] = 3 + i
+        if i == 9:
+            cfg["lattices"][0][1]["sizes"][1:] = [list(range(1, 51))] * 3          # 125,000 shapes
+        lat = cfg["lattices"][0][1]
+        want = O.solve(cfg["target"], lat)
+        jobs.append((B.Target(cfg["target"]), lat, want["cost"], want["argmin"]))
+
+    def check(target, lat, cost, arg):
+        got = B.solve(target, lat).dense()
+        assert np.array_equal(got[0], cost) and np.array_equal(got[1], arg)
+
+    for turn in range(3):
+        for k, job in enumerate(jobs):
+            if turn == 1 and k == 4:
+                with pytest.raises(B.MorelloError) as e:
+                    B.solve(job[0], job[1], scratch_bytes=4096)
+                assert e.value.code == B.E_NOMEM
+            check(*job)
+    cfg = W.config(4, max_size=24)
+    cfg["target"]["loop_overhead"] = 77
+    lat = cfg["lattices"][0][1]
+    want = O.solve(cfg["target"], lat)
+    target, dev, errors = B.Target(cfg["target"]), torch.cuda.current_device(), []
+
+    def worker():
+        try:
+            torch.cuda.set_device(dev)
+            with torch.cuda.stream(torch.cuda.Stream(device=dev)):
+                for _ in range(3):
+                    check(target, lat, want["cost"], want["argmin"])
+        except BaseException as e:
+            errors.append(e)
+
+    threads = [threading.Thread(target=worker, daemon=True) for _ in range(3)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join(timeout=60)
+    assert not any(th.is_alive() for th in threads) and not errors, errors
