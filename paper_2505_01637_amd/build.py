@@ -5,7 +5,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmorello_mi355x.so")
-SOURCES = ["api.hip", "fill.hip", "compress.hip", "boxindex.hip"]
+SOURCES = ["api.hip", "fill.hip", "compress.hip", "rowmerge.hip", "boxindex.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-result",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

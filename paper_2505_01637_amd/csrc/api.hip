@@ -136,6 +136,8 @@ struct FixedLayout {
   size_t counters, params, tiles, level_shapes, level_off, mk_entry, qdec, recs, masks, item_tasks, sort_tmp, list_small, bundle_first, list_wide, list_cnt, bind, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
       upload_end, fill_end, end;
   uint32_t n_words;
+  // the merge word by word (row_geo): its fixed lists from `shared` on, then dyn
+  size_t shared, rows_rows, rows_first, rows_cnt, rows_start, rows_piled, rows_sum, rows_tot, rows_dyn;
   // a solve's least: the fill's buffers share their place with the compression's and its lists
   size_t least() const { return fill_end > end ? fill_end : end; }
   size_t image_bytes() const { return upload_end - counters; }          // of what is uploaded, in pinned memory
@@ -162,6 +164,30 @@ size_t bind_entries(const Compiled& c) {
   return 2 * c.sizes[1].size() * c.sizes[3].size() * c.P.bind_d * ((size_t)6 << (2 * c.P.yb));
 }
 
+// Whether the table's boxes are merged word by word (rowmerge.hip) and its geometry there: the fit map comes from the
+// plan, the size axes are merged first, there are four memory levels, a shape is one to kRowShapeWords mask words, and a
+// row along n has at most 64 steps.
+bool row_geo(const Compiled& c, RowGeo& g) {
+  const DevParams& P = c.P;
+  memset(&g, 0, sizeof g);
+  if (P.gather || P.NL != 4 || P.log2V > 6 || c.n_specs >= (1ull << 31) || P.G % 64 || P.G / 64 > kRowShapeWords || P.nsz[3] > 64) return false;
+  g.en = P.nsz[3]; g.ek = P.nsz[2]; g.em = P.nsz[1]; g.eb = P.nsz[0];
+  g.G = P.G; g.nw = P.G / 64;
+  while ((1u << g.lg_nw) < g.nw) g.lg_nw++;
+  g.n_shapes = c.n_shapes;
+  g.n_planes = g.eb * g.em * g.nw;
+  g.lv = P.log2V; g.ndt = P.ndt;
+  g.n_levels = P.nlv; g.level_axis = 3 + P.nlv;
+  for (uint32_t a = 4 + P.nlv; a < c.geo.ndim; a++) {
+    uint32_t bit = 0;
+    while ((1u << bit) < c.geo.stride[a]) bit++;
+    g.var_first |= 1u << bit;
+    if (c.geo.ext[a] == 4) g.var_two |= 1u << bit;
+    g.var_axis[bit] = a;
+  }
+  return true;
+}
+
 FixedLayout fixed_layout(const Compiled& c) {
   FixedLayout f;
   size_t o = 0;
@@ -174,7 +200,7 @@ FixedLayout fixed_layout(const Compiled& c) {
   // From here on up to fill_end lies what the fill alone needs, and over it the compression's masks
   // and lists, which are written when the fill has ended: an 80-byte record per shape would otherwise
   // be 6 % of what a solve of a lattice with two memory levels asks for.
-  const size_t shared = o;
+  const size_t shared = f.shared = o;
   f.tiles = take(c.tiles.size() * sizeof(TileEntry) + 8);
   f.level_shapes = take(c.level_shapes.size() * 4);
   f.level_off = take(c.level_off.size() * 4);
@@ -221,6 +247,19 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.tile_tmp2 = take((c.n_specs / kScanTileItems + 2) * 4);
   f.totals = take(64);
   f.end = o;
+  RowGeo g;
+  f.rows_rows = f.rows_first = f.rows_cnt = f.rows_start = f.rows_piled = f.rows_sum = f.rows_tot = f.rows_dyn = 0;
+  if (row_geo(c, g)) {
+    o = shared;
+    f.rows_rows = take((size_t)g.n_planes * 4);
+    f.rows_first = take((size_t)g.n_planes * 4);
+    f.rows_cnt = take((size_t)g.n_shapes * 8);
+    f.rows_start = take((size_t)g.n_shapes * 8);
+    f.rows_piled = take((size_t)g.n_shapes * 8);
+    f.rows_sum = take(rows_sum_bytes());
+    f.rows_tot = take(kRowTotals * 4);
+    f.rows_dyn = o;
+  }
   return f;
 }
 
@@ -1011,7 +1050,11 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
 
   const FixedLayout f = fixed_layout(c);
   tab->f = f;
-  if (scratch_bytes < f.least()) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
+  RowGeo row_g;
+  const bool by_rows = row_geo(c, row_g) && scratch_bytes >= f.rows_dyn;
+  // (what the merge word by word needs beyond the fill's part depends on the contents; where it does not suffice, boxes
+  // are merged one by one)
+  if (scratch_bytes < (by_rows ? f.fill_end : f.least())) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
   char* base = (char*)d_scratch;
   hipStream_t st = (hipStream_t)hip_stream;
   HIP_TRY(hipGetDevice(&tab->device));
@@ -1209,6 +1252,29 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
 
   // ---- compression ----
   const Geo& g = c.geo;
+  Counters h_ctr;
+  size_t needed = 0;
+  bool merged = false;
+  if (by_rows) {
+    const RowBufs rb{(uint32_t*)(base + f.rows_rows), (uint32_t*)(base + f.rows_first), (uint32_t*)(base + f.rows_cnt), (uint32_t*)(base + f.rows_start),
+                     (uint32_t*)(base + f.rows_piled), (uint32_t*)(base + f.rows_sum), (uint32_t*)(base + f.rows_tot), base + f.rows_dyn, scratch_bytes - f.rows_dyn};
+    launch_rows(row_g, rb, tab->d_cost, tab->d_arg, d_fitmap, (const uint32_t*)((char*)d_P + offsetof(DevParams, sizes)), st);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipEventRecord(ev[2], st));
+    HIP_TRY(hipMemcpyAsync(aux->h_counts, rb.tot, kRowTotals * 4, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(&h_ctr, d_ctr, sizeof h_ctr, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    uint64_t list_at[2], end = 0;
+    merged = rows_fit(row_g, aux->h_counts, rb.room, list_at, &end);
+    if (merged) {
+      tab->list_n[0] = aux->h_counts[kBoxesFirst];
+      tab->list_n[1] = aux->h_counts[kBoxesTotal] - tab->list_n[0];
+      for (int which = 0; which < 2; which++) tab->list_off[which] = f.rows_dyn + list_at[which];
+      needed = std::max(f.fill_end, f.rows_dyn + (size_t)end);
+    }
+  }
+  if (!merged) {
+  if (scratch_bytes < f.least()) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
   uint32_t a0 = c.merge_order[0];
   for (uint32_t q = 0; q < g.ndim; q++) if (g.ext[c.merge_order[q]] > 1) { a0 = c.merge_order[q]; break; }
   unsigned long long* maskL[2] = {(unsigned long long*)(base + f.maskD), (unsigned long long*)(base + f.maskC)};
@@ -1249,7 +1315,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   const uint64_t nbL[2] = {h_tot[0], h_tot[1]};
   const size_t wbL[2] = {work_bytes(nbL[0]), work_bytes(nbL[1])};
   size_t front = f.end;
-  size_t needed = f.end + wbL[0] + wbL[1] + final_bytes(nbL[0]) + final_bytes(nbL[1]);   // upper bound until the final counts are known
+  needed = f.end + wbL[0] + wbL[1] + final_bytes(nbL[0]) + final_bytes(nbL[1]);   // upper bound until the final counts are known
   if (scratch_bytes < f.end + wbL[0] + wbL[1])
     return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, up to %zu needed", scratch_bytes, needed);
   char* work_lo = base + (scratch_bytes - wbL[0] - wbL[1]) / kAlign * kAlign;
@@ -1369,9 +1435,9 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(ev[2], st));
-  Counters h_ctr;
   HIP_TRY(hipMemcpyAsync(&h_ctr, d_ctr, sizeof h_ctr, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
+  }
   if (h_ctr.overflow & 2u) return fail(MRL_E_HIP, "internal error: a work item exceeded its LDS slice");
   if (h_ctr.overflow) return fail(MRL_E_OVERFLOW, "a finite cost reached 2^62");
   if (stats) {

@@ -149,6 +149,35 @@ struct LookupList {
 hipError_t launch_lookup(const Geo& g, const LookupList lists[2], const void* points, const uint64_t* vols, uint32_t n_points,
                    uint64_t* cost_out, uint16_t* arg_out, uint8_t* miss, hipStream_t st);
 
+// ---- the merge word by word (rowmerge.hip), for tables whose shapes are whole mask words
+constexpr uint32_t kRowLevels = 5;         // level axes at most
+constexpr uint32_t kRowShapeWords = 256;   // words of a shape at most
+// The axes n, k, m, b; inside a shape the level axes, four values each (level axis i, in merge order, is the bits
+// [lv + 2 i, lv + 2 i + 2) of a cell's place), then those of layouts and dtypes (fields of the lv bits below).
+struct RowGeo {
+  uint32_t en, ek, em, eb;                 // en: at most 64
+  uint32_t G, nw, lg_nw;                   // cells and 64-cell words of a shape
+  uint32_t n_shapes, n_planes;             // planes: (b, m, word of the shape)
+  uint32_t lv, n_levels, level_axis;       // level_axis: coordinate axis of level axis 0 (the others lie before it)
+  uint32_t var_first, var_two, ndt;        // bits at which a layout or dtype field starts; which are two bits wide; dtype bits (the lowest, merged last)
+  uint32_t var_axis[6];                    // coordinate axis of the field that starts at a bit
+};
+enum : uint32_t { kRowsTotal = 0, kLongTotal = 1, kPiled = 2, kBoxesTotal = 3, kBoxesFirst = 4, kRowTotals = 5 };
+struct RowBufs {
+  uint32_t *rows, *first;                  // per plane: rows kept, index of its first
+  uint32_t *cnt, *start, *piled;           // per list and shape: boxes, boxes before, where its boxes lie on the pile
+  uint32_t *sum;                           // rows_sum_bytes()
+  uint32_t *tot;                           // kRowTotals
+  char* dyn;                               // what depends on the contents: word arrays, extents, the pile, final lists
+  uint64_t room;                           // bytes there
+};
+size_t rows_sum_bytes();
+// The whole merge and the final lists; nothing is read back.  sizes: DevParams::sizes on the device.
+void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const uint16_t* arg, const uint32_t* fitmap,
+                 const uint32_t* sizes, hipStream_t st);
+// Given the totals: whether all of it fitted (nothing valid was written if not), where in dyn the lists lie, and the end.
+bool rows_fit(const RowGeo& g, const uint32_t* tot, uint64_t room, uint64_t list_at[2], uint64_t* end);
+
 constexpr uint32_t kScanTileItems = 2048;   // items per scan tile (tile_tmp needs n/2048 + 1 words)
 
 }  // namespace mrl

@@ -347,6 +347,66 @@ def test_parity_bufferize_beside_many_tiles(case):
     compare_config(cfg)
 
 
+def row_merge_case(case):
+    """Lattices of four memory levels, whose box lists are merged a word of 64 cells at a time."""
+    cfg = W.config(4)
+    lat = cfg["lattices"][0][1]
+    kind, _, tail = case.partition("-")
+    if kind == "steps":                                 # along n: one, two, and around the 64 a row may have
+        n = int(tail)
+        lat.update(sizes=[[1], [1, 2, 3], [1, 2, 4, 8, 16], list(range(1, n + 1))], layout_coord=[0, 0, 0, 0, 0])
+    elif kind == "bits":                                # bits of layouts and dtypes below the level axes
+        lay, dt = {"0": ((0, 0, 0), (0, 0)), "1": ((0, 1, 0), (0, 0)), "2": ((1, 1, 0), (0, 0)), "2d": ((0, 0, 0), (1, 1)), "3d": ((0, 1, 1), (0, 1)),
+                   "4d": ((1, 0, 1), (1, 1))}[tail]
+        lat.update(sizes=[[1, 2], [1, 2, 6], [1, 3, 6, 12, 48], [1, 2, 4, 8, 16, 24]], layout_coord=list(lay) + [0, 0], dtype_coord=list(dt) + [0, 0, 0])
+    elif kind == "packed":                              # 6: four layouts on every operand, 5 and 4 on some
+        lays = {"6": [2, 2, 2, 0, 0], "5": [2, 1, 2, 0, 0], "4": [2, 2, 0, 0, 0]}[tail]
+        cfg = W.config(12, max_size=8)
+        for _, x, _ in cfg["lattices"]:
+            x["sizes"] = [[1], [1, 2, 8], [1], [1, 2, 8]] if x["kind"] == W.KIND_MOVE else [[1], [1, 2, 8], [1, 2, 8], [1, 2, 8]]
+        cfg["lattices"][1][1]["layout_coord"] = lays
+    elif kind == "long":                                # chains of 70 boxes along k and m, all alike: one box at the end
+        r = list(range(1, 71))
+        lat.update(sizes={"km": [[1], r, r, [1, 2, 3]], "bk": [[1, 2], [1], r, [1, 2, 3]], "kn": [[1], [1, 2], r[:64], r[:64]]}[tail])
+        cfg["target"]["microkernels"] = []
+        cfg["target"]["capacity_bytes"] = [W.UNBOUNDED] * 4
+    elif kind == "full":                                # every cell fits: no empty words, batches of 256 everywhere
+        cfg = {"fused": W.config(5, max_size=8), "chain": W.config(10, max_size=4)}[tail]
+        cfg["target"]["capacity_bytes"] = [W.UNBOUNDED] * 4
+    elif kind == "b":                                   # long along b, chains along k and m before it
+        lat.update(sizes=[list(range(1, 41)), [1, 2, 4], [1, 2, 3, 6], [1, 2, 8]])
+    return dict(cfg, name="rows-" + case)
+
+
+@pytest.mark.parametrize("case", ["steps-1", "steps-2", "steps-63", "steps-64", "steps-65", "bits-0", "bits-1", "bits-2", "bits-2d", "bits-3d", "bits-4d",
+                                  "packed-4", "packed-5", "packed-6", "long-km", "long-bk", "long-kn", "full-fused", "full-chain", "b"])
+def test_parity_boxes_merged_by_rows(case):
+    """The merge word by word: rows of 1 to 64 steps (65: the general one), 0 to 6 bits below the level axes (a level axis
+    then lies inside a word, over two words or above), chains longer than a wave, batches without an empty word."""
+    compare_config(row_merge_case(case))
+
+
+@pytest.mark.parametrize("case", ["steps-64", "full-fused", "long-kn"])
+def test_boxes_merged_one_by_one_where_the_rows_do_not_fit(case):
+    """With less scratch than the merge word by word uses, the boxes are merged one by one if that is enough, and the
+    call is refused if not; both give the same lists."""
+    B = _binding()
+    cfg = row_merge_case(case)
+    target, tabs = B.solve_config(cfg)
+    label, lat, deps = cfg["lattices"][-1]
+    lists = [tabs[label].boxes(which).tobytes() for which in (0, 1)]
+    used, took = int(tabs[label].stats.scratch_used), []
+    for part in (1.0, 0.95, 0.9, 0.8, 0.7, 0.6, 0.4):
+        try:
+            tab = B.solve(target, lat, deps=[tabs[d] for d in deps], scratch_bytes=int(used * part) // 256 * 256)
+        except B.MorelloError as e:
+            assert e.code == B.E_NOMEM and part < 1
+            continue
+        took.append(part)
+        assert [tab.boxes(which).tobytes() for which in (0, 1)] == lists
+    assert took[:1] == [1.0] and (case != "long-kn" or len(took) > 1)
+
+
 def two_level_bounded(caps, sizes):
     cfg = W.config(1, seed=11, max_size=4)
     t = cfg["target"]
