@@ -151,6 +151,7 @@ hipError_t launch_lookup(const Geo& g, const LookupList lists[2], const void* po
 
 // ---- the merge word by word (rowmerge.hip), for tables whose shapes are whole mask words
 constexpr uint32_t kRowLevels = 5;         // level axes at most
+constexpr uint32_t kRowInfoBytes = 64;
 constexpr uint32_t kRowShapeWords = 256;   // words of a shape at most
 // The axes n, k, m, b; inside a shape the level axes, four values each (level axis i, in merge order, is the bits
 // [lv + 2 i, lv + 2 i + 2) of a cell's place), then those of layouts and dtypes (fields of the lv bits below).
@@ -158,17 +159,18 @@ struct RowGeo {
   uint32_t en, ek, em, eb;                 // en: at most 64
   uint32_t G, nw, lg_nw;                   // cells and 64-cell words of a shape
   uint32_t n_shapes, n_planes;             // planes: (b, m, word of the shape)
-  uint32_t lv, n_levels, level_axis;       // level_axis: coordinate axis of level axis 0 (the others lie before it)
+  uint32_t lv, n_levels, n_inner, level_axis;      // n_inner = n_levels + lv; level_axis: coordinate axis of level axis 0 (the others lie before it)
   uint32_t var_first, var_two, ndt;        // bits at which a layout or dtype field starts; which are two bits wide; dtype bits (the lowest, merged last)
   uint32_t var_axis[6];                    // coordinate axis of the field that starts at a bit
 };
-enum : uint32_t { kRowsTotal = 0, kLongTotal = 1, kPiled = 2, kBoxesTotal = 3, kBoxesFirst = 4, kRowTotals = 5 };
+enum : uint32_t { kLongTotal = 0, kHeadsTotal = 1, kRowsTotal = 2, kBoxesTotal = 3, kBoxesFirst = 4, kRowTotals = 5 };     // (the first two are written as one)
 struct RowBufs {
-  uint32_t *rows, *first;                  // per plane: rows kept, index of its first
-  uint32_t *cnt, *start, *piled;           // per list and shape: boxes, boxes before, where its boxes lie on the pile
-  uint32_t *sum;                           // rows_sum_bytes()
+  uint32_t *rows, *first, *plane_of;       // per plane: rows kept, index of its first; per kept row: its plane
+  void* info;                              // per kept row: kRowInfoBytes
+  uint32_t *cnt, *start;                   // per list and shape: boxes, boxes before
+  void* sum;                               // rows_sum_bytes()
   uint32_t *tot;                           // kRowTotals
-  char* dyn;                               // what depends on the contents: word arrays, extents, the pile, final lists
+  char* dyn;                               // what depends on the contents: word arrays, extents, final lists
   uint64_t room;                           // bytes there
 };
 size_t rows_sum_bytes();
