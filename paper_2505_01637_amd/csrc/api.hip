@@ -1209,7 +1209,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   hipEvent_t wide_done = nullptr;          // recorded behind the last wide launch that the caller's stream has not waited for yet
   for (uint32_t l = 0; l < n_lev; l++) {
     const size_t first = (size_t)c.level_off[l] * P.npass, n_items = (size_t)(c.level_off[l + 1] - c.level_off[l]) * P.npass;
-    const uint32_t n_bundles = cnt[l], n_wide = cnt[n_lev + l];
+    const uint32_t n_bundles = cnt[l], n_wide = cnt[n_lev + l], n_small = cnt[2 * n_lev + l] & ((1u << kItemsBits) - 1u), lg_tasks = cnt[2 * n_lev + l] >> kItemsBits;
     if ((size_t)n_bundles + n_wide > n_items) return fail(MRL_E_HIP, "internal error: work lists of level %u overflow", l);
     // The wide items (with more tasks than a bundle takes) run on the helper stream, level after
     // level, without waiting for the other items: a tile of a wide item leads to the same item of a
@@ -1231,7 +1231,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     if (n_bundles) {
       if (wide_done) { HIP_TRY(hipStreamWaitEvent(st, wide_done, 0)); wide_done = nullptr; }
       launch_fill_level(d_P, P, c.max_task, n_bundles, plan.list_small + first,
-                        n_bundles == cnt[2 * n_lev + l] ? nullptr : plan.bundle_first + first + l, plan, tab->d_cost, tab->d_arg, d_ctr, st);
+                        n_bundles == n_small ? nullptr : plan.bundle_first + first + l, lg_tasks, plan, tab->d_cost, tab->d_arg, d_ctr, st);
     }
     if (n_wide && sw != st) {
       // the next level's other items wait here

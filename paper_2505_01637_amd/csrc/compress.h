@@ -31,8 +31,9 @@ struct PlanBuffers {
   unsigned long long* masks;
   uint16_t* item_tasks;
   void* sort_tmp;                          // plan_bytes_sort
-  uint32_t *list_small, *bundle_first, *list_wide, *list_cnt;      // counts: bundles, wide items, small items per level
+  uint32_t *list_small, *bundle_first, *list_wide, *list_cnt;      // counts per level: bundles, wide items, small items | log2 of the tasks per bundle << kItemsBits
 };
+constexpr uint32_t kItemsBits = 28;
 size_t plan_bytes_recs(uint32_t n_shapes);
 size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass);
 // Whether the work lists can hold the lattice's dependency levels.  h: the host's copy of *P.
@@ -44,9 +45,9 @@ void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint
 // The costs of the alloc-bindings of a Matmul whose Moves are Move Specs, from its Move table.
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream);
 // One dependency level: n bundles of its small items (starts: where each begins in `items`; nullptr:
-// every item by itself), and n wide items.
+// every item by itself) of about 2^lg_tasks tasks, and n wide items.
 void launch_fill_level(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const uint32_t* starts,
-                       const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
+                       uint32_t lg_tasks, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
 void launch_fill_wide(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const PlanBuffers& B,
                       uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
 

@@ -285,6 +285,7 @@ constexpr uint32_t kSortThreads = 1024, kSortItems = 8, kSortTile = kSortThreads
 // (sweeps with the final kernels: quotas of 64, 96, 192 and 256 tasks are 0 to 3 % slower on the
 // large lattices, 2048 and 4096 bundles before they grow 3 and 8 % on config 4, 512 the same)
 constexpr uint32_t kBundle = 128;            // tasks per bundle
+constexpr uint32_t kFewBundles = 256, kManyTasks = 7;      // a bundle has a compute unit for itself, and 2^7 tasks and more
 constexpr uint32_t kMinBundles = 1024;       // a level is cut into this many bundles before they grow
 
 __device__ __forceinline__ unsigned long long block_scan_1024(unsigned long long v, unsigned long long* sh, unsigned long long& total) {
@@ -354,6 +355,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_work_kernel(const uint32_t*
   }
   if (sums) for (uint32_t t = 0; t < tiles; t++) total += sums[wg0 + t];
   else block_scan_1024(work, sh, total);
+  const uint32_t level_tasks = (uint32_t)total;
   uint32_t quota = (uint32_t)(total / kMinBundles);
   quota = quota < min_weight ? min_weight : quota > kBundle ? kBundle : quota;
   auto weight = [&](uint32_t t) { return t < min_weight ? min_weight : t > quota ? quota : t; };
@@ -390,7 +392,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_work_kernel(const uint32_t*
     if (tile + 1 == tiles) {
       const uint32_t bundles = (run_w + all_w + quota - 1) / quota;
       starts[bundles] = run_s + all_s;
-      list_cnt[lv] = bundles; list_cnt[n_levels + lv] = run_x + all_x; list_cnt[2 * n_levels + lv] = run_s + all_s;
+      const uint32_t each = bundles ? level_tasks / bundles : 0u, lg = each ? 31u - (uint32_t)__builtin_clz(each) : 0u;
+      list_cnt[lv] = bundles; list_cnt[n_levels + lv] = run_x + all_x;
+      list_cnt[2 * n_levels + lv] = (run_s + all_s) | (lg < 15u ? lg : 15u) << kItemsBits;       // (plan_fits: fewer than 2^28 items)
     }
   }
 }
@@ -532,7 +536,10 @@ __device__ __forceinline__ void flush_counters(Counters* __restrict__ ctr, uint3
 // 0.69 -> 0.60, config 4 0.80 -> 0.73, config 5's F 2.22 -> 2.12, config 12's Matmul, which then was
 // a lane per Spec with three gathers per Move, 5.04 -> 2.16.
 // T: 512 for a wide item (100 registers would leave 2 instead of 3 workgroups on a unit, hence the
-// bound), 256 on levels short of bundles, else 128 (64: config 4 +9 %, F +5 %).
+// bound), 256 on levels short of bundles, else 128 (64: config 4 +9 %, F +5 %).  1024 where the bundles of a level are no
+// more than the compute units and have 128 tasks and more: then the time is one bundle's, most of it the chain of ranks
+// (config 3's levels of up to 12 bundles 26 -> 19 us, the solve 773 -> 703 us, config 4's 1102 -> 1065; with fewer tasks
+// 256 threads are faster, 11 against 13 us, and so they are with Move Specs, config 12's solve 3166 against 3220).
 template <int T, bool LAY, bool MOVES>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 5 : 4))) void fill_kernel(
     const DevParams* __restrict__ P, const FillGeom g, const uint32_t* __restrict__ items, const uint32_t* __restrict__ starts,
@@ -812,7 +819,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 5 
   // short of work (T = 256) the chain of ranks is what counts, and eight lanes per task halve a
   // lane's work in each: lane 4 * x + op takes the changes of layout x and x + 2.  Elsewhere it is
   // the instructions, most of which a lane spends whatever its number of candidates.
-  constexpr uint32_t kTaskLanes = LAY && T == 256 ? 8u : 4u, kXLanes = kTaskLanes / 4u;
+  constexpr uint32_t kTaskLanes = LAY && (T == 256 || T == 1024) ? 8u : 4u, kXLanes = kTaskLanes / 4u;
   const uint32_t op = tid & 3u, x = kXLanes == 2 ? (tid >> 2) & 1u : 0u;
   const uint32_t my_shift = op == 0 ? P->pack_shift[0] : op == 1 ? P->pack_shift[1] : op == 2 ? P->pack_shift[2] : P->pack_shift[3];
   const uint32_t my_lay = op == 0 ? P->lay_bit[0] : op == 1 ? P->lay_bit[1] : op == 2 ? P->lay_bit[2] : P->lay_bit[3];
@@ -1683,10 +1690,11 @@ static void launch_items(const DevParams* P, const DevParams& h, const FillGeom&
 
 // The bundles of one dependency level (starts = nullptr: every item is a bundle of its own).
 void launch_fill_level(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const uint32_t* starts,
-                       const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
+                       uint32_t lg_tasks, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
   if (!n) return;
   const FillGeom g = fill_geom(h, max_task, false);
   if (n >= kMinBundles) launch_items<128>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
+  else if (n <= kFewBundles && lg_tasks >= kManyTasks && !h.moves) launch_items<1024>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
   else launch_items<256>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
 }
 // Its wide items.
