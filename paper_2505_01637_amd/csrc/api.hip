@@ -1167,10 +1167,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   } else {
   // plan (with the pre-fill; a separate streaming kernel for tables it cannot serve), then the
   // host reads the list sizes back
-  // A level assignment's fit bits (passive levels x variants) are whole 32-bit words of the map when
-  // there are 32 or 64 of them: the plan kernel then stores them, and only the two pad words are zeroed.
-  const bool fit_words = P.npass * P.V == 32 || P.npass * P.V == 64;
-  if (fit_words) launch_zero_words((unsigned long long*)d_fitmap + f.n_words, 2, st);
+  // the map's last word (which may not be whole) and its two pad words are zeroed, all of it only where the plan adds bits to it
+  if (fit_map_stored(P)) launch_zero_words((unsigned long long*)d_fitmap + f.n_words - 1, 3, st);
   else launch_zero_words((unsigned long long*)d_fitmap, f.n_words + 2, st);
   // the plan kernel also streams (INF, NONE) over the tables when a shape's entries are whole 16-byte pieces
   // (not when the pre-fill runs beside the fill of the tables this lattice reads: see launch_fill_ones)

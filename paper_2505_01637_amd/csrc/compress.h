@@ -38,7 +38,8 @@ size_t plan_bytes_recs(uint32_t n_shapes);
 size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass);
 // Whether the work lists can hold the lattice's dependency levels.  h: the host's copy of *P.
 bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels);
-// h: the host's copy of *P.  max_task: entries of the largest possible item.
+bool fit_map_stored(const DevParams& h);
+// h: the host's copy of *P.  max_task: entries of the largest possible item.  fitmap: zero before, unless fit_map_stored.
 void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint32_t max_task, const uint32_t* level_shapes,
                  const uint32_t* level_off, const uint32_t* h_level_off, uint32_t n_levels, const PlanBuffers& B, uint32_t* fitmap, Counters* ctr,
                  void* prefill_cost, void* prefill_arg, hipStream_t stream);

@@ -132,22 +132,36 @@ struct alignas(16) ShapeRec {
 };
 static_assert(sizeof(ShapeRec) == 80, "read as five 16-byte pieces");
 
-// Plan: one wave per kPlanShapes shapes, in the order of the dependency levels.  Its first lanes take
+// Plan: one wave per up to kPlanShapes shapes, in the order of the dependency levels.  Its first lanes take
 // a shape each and write its record; then, shape by shape, the lanes are level assignments: which
 // of them fit is written as one mask per item (bit = position in rank order, one plane of nwp words
 // per value of the dtype bits) with the item's number of tasks, and the entries that fit are marked
 // in a bit map in table order (bit = cell; read by the compression pass).
-constexpr uint32_t kPlanShapes = 16;
+// Bound by instruction issue (460 vector instructions a shape), on small tables by the latency of a wave's shapes one
+// after the other: with 16 per wave always, config 3's 180 shapes took 46 us, now 11.  The map is stored whole where
+// that can be done: with an atomic per level assignment config 2 (262,144 shapes, one bit each) took 178 us, now 129.
+constexpr uint32_t kPlanShapes = 16, kPlanWaves = 4096;      // shapes per wave at most, and fewer while there are fewer waves than this
+// Whether the plan stores the map whole (a level assignment's bits, passive levels x variants, are a power of two of
+// them, and those of all level assignments whole bytes); else it adds bits to a map that is zero before.
+bool fit_map_stored(const DevParams& h) {
+  const uint32_t nb = h.npass * h.V;
+  return (nb & (nb - 1)) == 0 && (nb >= 8 || (h.ncombo <= 64 && h.ncombo * nb % 8 == 0));
+}
+static uint32_t plan_shapes(uint32_t n_shapes) {
+  uint32_t per = kPlanShapes;
+  while (per > 1 && n_shapes / per < kPlanWaves) per /= 2;
+  return per;
+}
 
-__global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, uint32_t n_shapes, const uint32_t* __restrict__ level_shapes,
+__global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, uint32_t n_shapes, uint32_t per_wave, uint32_t map_stored, const uint32_t* __restrict__ level_shapes,
                                                    ShapeRec* __restrict__ recs, unsigned long long* __restrict__ masks,
                                                    uint16_t* __restrict__ item_tasks, uint32_t* __restrict__ fitmap, Counters* __restrict__ ctr,
                                                    uint4* __restrict__ cost16, uint4* __restrict__ arg16) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   const uint32_t npass = P->npass, ncombo = P->ncombo, V = P->V, nb = npass * V, ndp = 1u << P->ndt, nwp = P->nwp, nw = ndp * nwp, NL = P->NL, nops = P->nops;
-  const uint32_t first = (blockIdx.x * 4 + wave) * kPlanShapes;
+  const uint32_t first = (blockIdx.x * 4 + wave) * per_wave;
   if (first >= n_shapes) return;
-  const uint32_t n_here = n_shapes - first < kPlanShapes ? n_shapes - first : kPlanShapes;
+  const uint32_t n_here = n_shapes - first < per_wave ? n_shapes - first : per_wave;
   // ---- a shape per lane ----
   Shape S;
   uint32_t shape = 0, var = 0, nvb = 0;
@@ -247,23 +261,33 @@ __global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__
         }
       }
     }
+    if (nb < 8 && map_stored) {
+      // less than a byte per level assignment: the lanes go from rank to table order, and as many as make a byte join up
+      uint32_t x = (uint32_t)__builtin_amdgcn_ds_permute((int)(lane < ncombo ? off0[0] / nb : lane) * 4, (int)(uint32_t)bits[0]);
+      for (uint32_t have = nb, d = 1; have < 8; have *= 2, d *= 2) x |= (uint32_t)__shfl_down((int)x, d, 64) << have;
+      if (lane * nb % 8 == 0 && lane < ncombo) ((uint8_t*)fitmap)[(group + lane * nb) >> 3] = (uint8_t)x;
+    } else {
 #pragma unroll
-    for (int it = 0; it < 4; it++) {
-      if ((uint32_t)(it * 64) >= ncombo) break;
-      if (it * 64 + lane >= ncombo) continue;
-      if (nb == 32 || nb == 64) {
-        // whole words of the map (the group size is a multiple of nb): stored, the map is not zeroed
-        uint32_t* w = fitmap + ((group + off0[it]) >> 5);
-        w[0] = (uint32_t)bits[it];
-        if (nb == 64) w[1] = (uint32_t)(bits[it] >> 32);
-      } else if (bits[it]) {
+      for (int it = 0; it < 4; it++) {
+        if ((uint32_t)(it * 64) >= ncombo) break;
+        if (it * 64 + lane >= ncombo) continue;
         const uint64_t cell0 = group + off0[it];
-        const uint32_t shift = (uint32_t)(cell0 & 31u);
-        uint32_t* w = fitmap + (cell0 >> 5);
-        atomicOr(w, (uint32_t)(bits[it] << shift));
-        if (shift + nb > 32) {
-          atomicOr(w + 1, (uint32_t)(bits[it] >> (32 - shift)));
-          if (shift + nb > 64) atomicOr(w + 2, (uint32_t)(bits[it] >> (64 - shift)));
+        if (map_stored) {
+          // whole bytes to pairs of words (the group size is a multiple of nb): stored, the map is not zeroed
+          if (nb == 8) ((uint8_t*)fitmap)[cell0 >> 3] = (uint8_t)bits[it];
+          else if (nb == 16) ((uint16_t*)fitmap)[cell0 >> 4] = (uint16_t)bits[it];
+          else {
+            fitmap[cell0 >> 5] = (uint32_t)bits[it];
+            if (nb == 64) fitmap[(cell0 >> 5) + 1] = (uint32_t)(bits[it] >> 32);
+          }
+        } else if (bits[it]) {
+          const uint32_t shift = (uint32_t)(cell0 & 31u);
+          uint32_t* w = fitmap + (cell0 >> 5);
+          atomicOr(w, (uint32_t)(bits[it] << shift));
+          if (shift + nb > 32) {
+            atomicOr(w + 1, (uint32_t)(bits[it] >> (32 - shift)));
+            if (shift + nb > 64) atomicOr(w + 2, (uint32_t)(bits[it] >> (64 - shift)));
+          }
         }
       }
     }
@@ -1659,8 +1683,9 @@ size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t np
 void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint32_t max_task, const uint32_t* level_shapes,
                  const uint32_t* level_off, const uint32_t* h_level_off, uint32_t n_levels, const PlanBuffers& B, uint32_t* fitmap, Counters* ctr,
                  void* prefill_cost, void* prefill_arg, hipStream_t stream) {
-  hipLaunchKernelGGL(plan_kernel, dim3((n_shapes + 4 * kPlanShapes - 1) / (4 * kPlanShapes)), dim3(256), 0, stream, P,
-                     n_shapes, level_shapes, (ShapeRec*)B.recs, B.masks, B.item_tasks, fitmap, ctr, (uint4*)prefill_cost, (uint4*)prefill_arg);
+  const uint32_t per_wave = plan_shapes(n_shapes);
+  hipLaunchKernelGGL(plan_kernel, dim3((n_shapes + 4 * per_wave - 1) / (4 * per_wave)), dim3(256), 0, stream, P,
+                     n_shapes, per_wave, fit_map_stored(h) ? 1u : 0u, level_shapes, (ShapeRec*)B.recs, B.masks, B.item_tasks, fitmap, ctr, (uint4*)prefill_cost, (uint4*)prefill_arg);
   const uint32_t tiles = sort_tiles(h_level_off, n_levels, h.npass), small_max = fill_small_max(max_task), min_weight = kBundle / fill_items(h);
   uint4* parts = (uint4*)B.sort_tmp;
   uint32_t* sums = tiles > n_levels ? (uint32_t*)(parts + tiles) : nullptr;
