@@ -215,10 +215,12 @@ class Table:
         """(cost, rewrite id) of the Specs at `coords`; compressed=True answers from the two box
         lists alone (mrl_query_compressed) instead of the dense table; noalloc=True asks through
         mrl_query_noalloc (at most NOALLOC_MAX_QUERIES coordinates)."""
-        coords = np.ascontiguousarray(coords, dtype=np.uint32).reshape(-1, len(self.extents))
+        if not (isinstance(coords, np.ndarray) and coords.dtype.kind in "iu"):
+            coords = np.asarray(coords, dtype=np.uint32)
+        coords = coords.reshape(-1, len(self.extents))
         n = len(coords)
         buf = np.zeros((n, MAX_DIMS), dtype=np.uint32)
-        buf[:, :coords.shape[1]] = coords
+        buf[:, :coords.shape[1]] = coords             # (integers of other widths are converted in this one pass)
         cost = np.empty(n, dtype=np.uint64)
         rw = np.empty(n, dtype=np.uint16)
         fn = lib().mrl_query_compressed if compressed else lib().mrl_query_noalloc if noalloc else lib().mrl_query

@@ -200,6 +200,31 @@ def test_query_point_counts(n_points):
         assert np.array_equal(gc, cost[lin]) and np.array_equal(ga, arg[lin])
 
 
+@pytest.mark.parametrize("compressed,n_points", [(c, n) for c in (False, True) for n in (32771, 100003, 116252, 116253, 250001)])
+def test_long_questions_in_stretches(compressed, n_points):
+    """More than 32,768 points are asked in four stretches at once, each of one launch or, beyond
+    29,063 points in the boxes and 58,190 in the table, of several: answers against the whole table
+    at sizes that four does not divide, from arrays of either integer width, and the earliest of
+    several bad points named whatever stretch it lies in."""
+    B = _binding()
+    cfg = W.config(4, max_size=8)
+    _, got = B.solve_config(cfg)
+    tab = got["M"]
+    cost, arg = tab.dense()
+    lin = np.random.default_rng(n_points).integers(0, len(cost), size=n_points)
+    specs = np.stack(np.unravel_index(lin, tab.extents), axis=1)
+    for width in (np.int64, np.uint32):
+        gc, ga = tab.query(specs.astype(width), compressed=compressed)
+        assert np.array_equal(gc, cost[lin]) and np.array_equal(ga, arg[lin])
+    for bad in (n_points // 4 + 1, n_points - 1):
+        specs[bad:, 3] = 99
+        specs[bad + 1:bad + 9, 3] = 98
+        with pytest.raises(B.MorelloError, match=f"spec {bad}:") as e:
+            tab.query(specs, compressed=compressed)
+        assert e.value.code == B.E_RANGE
+        specs[bad:] = np.stack(np.unravel_index(lin[bad:], tab.extents), axis=1)
+
+
 def test_compressed_query_one_box_and_long_axis():
     """A table that is one box (nothing solvable), and the 255-size axis (coordinates up to 254)."""
     B = _binding()
