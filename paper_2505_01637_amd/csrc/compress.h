@@ -19,6 +19,17 @@ hipError_t launch_checked(void (*kernel)(P...), dim3 grid, dim3 block, hipStream
   }, v);
 }
 
+// The place of set bit number i of a word.
+__device__ __forceinline__ uint32_t nth_bit(unsigned long long x, uint32_t i) {
+  uint32_t at = 0;
+#pragma unroll
+  for (uint32_t d = 32; d > 0; d >>= 1) {
+    const uint32_t n = (uint32_t)__popcll(x >> at & ((1ull << d) - 1ull));
+    if (i >= n) { i -= n; at += d; }
+  }
+  return at;
+}
+
 // Table geometry passed by value to the compression kernels (cells < 2^32).
 struct Geo {
   uint32_t ndim, n;

@@ -44,43 +44,55 @@ __device__ __forceinline__ bool norm_equal(uint64_t c1, uint32_t s1, uint64_t c2
 // ---------------------------------------------------------------- pass 0
 constexpr uint32_t kCellWords = 8;         // 64-cell words a wave of the lane-per-cell kernels takes (a wave per word is mostly wave launch)
 
-// A line = all cells sharing every coordinate but a0.  General form (any stride): one lane per
-// cell compares its value with the cell before it on the line; a wave covers one 64-cell word of
-// the table-order masks and writes it whole (ballots: no atomics, no zeroing).
+// A line = all cells sharing every coordinate but a0.  General form (any stride that is no multiple
+// of 64): one lane per cell compares its value with the cell before it on the line; a wave covers one
+// 64-cell word of the table-order masks and writes it whole (ballots: no atomics, no zeroing).
+// The values are read once and the pass should be bound by that, but a lane's two divisions and the
+// 128-bit products of the sizes took longer (41 M cells with memory bounds: 160 us, now 102; 410 MB take 79): the place on the line is
+// divided once per wave and carried on from word to word, the bits that say which cells fit come as
+// words the whole wave shares, shifted by the stride for the cells before, and an axis without sizes
+// compares values as they are.
 __global__ __launch_bounds__(256) void head_flags_kernel(Geo g, uint32_t a0,
                                                          const uint64_t* __restrict__ cost,
                                                          const uint16_t* __restrict__ arg,
-                                                         const uint32_t* __restrict__ fitmap,
+                                                         const unsigned long long* __restrict__ fitmap,
                                                          const uint32_t* __restrict__ axis_sizes,
                                                          unsigned long long* __restrict__ maskD,
                                                          unsigned long long* __restrict__ maskC) {
-  const uint32_t s0 = g.stride[a0], e0 = g.ext[a0];
-  const uint32_t word0 = (blockIdx.x * 4u + (threadIdx.x >> 6)) * kCellWords;     // a wave takes kCellWords words
+  const uint32_t s0 = g.stride[a0], se = s0 * g.ext[a0], n_words = (g.n + 63u) / 64u, lane = threadIdx.x & 63u;
+  const uint32_t word0 = __builtin_amdgcn_readfirstlane((blockIdx.x * 4u + (threadIdx.x >> 6)) * kCellWords);     // a wave takes kCellWords words
+  if (word0 >= n_words) return;
+  const uint32_t back = s0 >> 6, shift = s0 & 63u;               // shift > 0
+  const uint32_t step = 64u % se;
+  uint32_t r = (word0 * 64u + lane) % se;                        // from the start of the cells that share the axes before a0
 #pragma unroll
   for (uint32_t w = 0; w < kCellWords; w++) {
-    const uint32_t cell = (word0 + w) * 64u + (threadIdx.x & 63u);
+    const uint32_t word = word0 + w, cell = word * 64u + lane;
+    if (word >= n_words) break;
     const bool active = cell < g.n;
-    bool hd = false, hc = false;
-    if (active) {
-      const uint32_t j = (cell / s0) % e0;
-      const bool fits = (fitmap[cell >> 5] >> (cell & 31u)) & 1u;     // cells that cannot fit hold (INF, NONE): not read
-      const uint64_t c = fits ? cost[cell] : kInf;
-      const uint32_t a = fits ? arg[cell] : kNone;
-      hd = hc = true;
-      if (j > 0) {
-        const uint32_t p = cell - s0;
-        const bool pfits = (fitmap[p >> 5] >> (p & 31u)) & 1u;
-        const uint64_t pc = pfits ? cost[p] : kInf;
-        const uint32_t pa = pfits ? arg[p] : kNone;
-        const uint32_t sz = axis_sizes ? axis_sizes[j] : 1u, ps = axis_sizes ? axis_sizes[j - 1] : 1u;
-        hd = a != pa;
-        hc = !norm_equal(c, sz, pc, ps);
+    const unsigned long long fits = fitmap[word];                // cells that cannot fit hold (INF, NONE): not read
+    const unsigned long long pfits = (word >= back ? fitmap[word - back] << shift : 0ull) |
+                                     (word > back ? fitmap[word - back - 1u] >> (64u - shift) : 0ull);
+    bool hd = active, hc = active;
+    if (active && r >= s0) {
+      uint64_t c = kInf, pc = kInf;
+      uint32_t a = kNone, pa = kNone;
+      if ((fits >> lane) & 1ull) { c = cost[cell]; a = arg[cell]; }
+      if ((pfits >> lane) & 1ull) { pc = cost[cell - s0]; pa = arg[cell - s0]; }
+      hd = a != pa;
+      if (axis_sizes) {
+        const uint32_t j = r / s0;
+        hc = !norm_equal(c, axis_sizes[j], pc, axis_sizes[j - 1u]);
+      } else {
+        hc = c != pc;
       }
     }
+    r += step;
+    r -= r >= se ? se : 0u;
     const unsigned long long bd = __ballot(hd), bc = __ballot(hc);
-    if ((threadIdx.x & 63u) == 0 && active) {
-      maskD[cell >> 6] = bd;
-      maskC[cell >> 6] = bc;
+    if (lane == 0) {
+      maskD[word] = bd;
+      maskC[word] = bc;
     }
   }
 }
@@ -375,40 +387,65 @@ void launch_compact_boxes(uint32_t n, const uint8_t* alive, const uint32_t* pos,
 
 // ---------------------------------------------------------------- boxes of pass 0
 
-// General form (any stride): one lane per cell; a flagged cell opens the box whose index is its
-// rank in the table-order mask (prefix sums), and the box runs to the next flagged cell of the
-// line or to the line's end.
-__global__ __launch_bounds__(256) void make_boxes_kernel(Geo g, uint32_t a0,
+// A wave of the word-by-word kernels takes this many consecutive mask words: 64 (one per lane)
+// on large tables, few on small ones, which would otherwise occupy a handful of waves for long.
+static uint32_t words_per_wave(uint32_t n_words) { return n_words >= (1u << 21) ? 64u : 8u; }
+
+// General form (any stride): a flagged cell opens the box whose index is its rank in the table-order
+// mask (prefix sums), and the box runs to the next flagged cell of the line or to the line's end.
+// A wave takes wpw consecutive words (a word and its prefix sum per lane) and their boxes 64 at a
+// time, a lane each: the word by a search in the prefix sums, the cell as its n-th flag.  The lanes
+// write consecutive boxes.  (A lane per cell, most of which open no box, with the words read one
+// after the other, took 145 us for 2.4 M boxes in 41 M cells, this 26; 51 MB of boxes and 8 MB of words
+// take 11.  8 words a wave on small tables, where 64 would leave the chip idle.)
+__global__ __launch_bounds__(256) void make_boxes_kernel(Geo g, uint32_t a0, uint32_t n_words, uint32_t wpw,
                                                          const unsigned long long* __restrict__ mask,
                                                          const uint32_t* __restrict__ prefix,
                                                          uint32_t* __restrict__ bcell, uint4* __restrict__ blen,
                                                          uint8_t* __restrict__ alive) {
+  __shared__ unsigned long long s_mask[256];
+  __shared__ uint32_t s_first[256];
+  const uint32_t lane = threadIdx.x & 63u, at = threadIdx.x & ~63u;
+  const uint32_t w0 = (blockIdx.x * 4u + (threadIdx.x >> 6)) * wpw;
+  const bool mine = lane < wpw && w0 + lane < n_words;
+  const unsigned long long mv = mine ? mask[w0 + lane] : 0ull;
+  const uint32_t pv = mine ? prefix[w0 + lane] : 0xFFFFFFFFu;
+  const uint32_t id0 = (uint32_t)__shfl((int)pv, 0);
+  s_mask[threadIdx.x] = mv;
+  s_first[threadIdx.x] = pv - id0;
+  __syncthreads();
+  if (w0 >= n_words) return;
+  const uint32_t last = min(wpw, n_words - w0) - 1u;
+  const uint32_t n_boxes = s_first[at + last] + (uint32_t)__popcll(s_mask[at + last]);
   const uint32_t s0 = g.stride[a0], e0 = g.ext[a0];
-  const uint32_t word0 = (blockIdx.x * 4u + (threadIdx.x >> 6)) * kCellWords;
-  for (uint32_t wi = 0; wi < kCellWords; wi++) {
-    const uint32_t cell = (word0 + wi) * 64u + (threadIdx.x & 63u);
-    if (cell >= g.n) return;
-    const unsigned long long tm = mask[cell >> 6];
-    if (!((tm >> (cell & 63u)) & 1ull)) continue;
-    const uint32_t id = prefix[cell >> 6] + (uint32_t)__popcll(tm & ((1ull << (cell & 63u)) - 1ull));
+  // a power-of-two stride: the line's cells sit at the same bit positions (mod s0) of every word
+  const bool in_words = (s0 & (s0 - 1u)) == 0 && s0 <= 32u;
+  const unsigned long long P = s0 == 1 ? ~0ull : s0 == 2 ? 0x5555555555555555ull : s0 == 4 ? 0x1111111111111111ull
+                             : s0 == 8 ? 0x0101010101010101ull : s0 == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;
+  const uint32_t shift = (a0 & 3u) * 8u;
+  for (uint32_t i = lane; i < n_boxes; i += 64u) {
+    uint32_t t = 0;                                       // the last word whose boxes start at or before box i (words without any come before it)
+#pragma unroll
+    for (uint32_t d = 32; d > 0; d >>= 1)
+      if (t + d <= last && s_first[at + t + d] <= i) t += d;
+    const unsigned long long tm = s_mask[at + t];
+    const uint32_t bit0 = nth_bit(tm, i - s_first[at + t]);
+    const uint32_t word = w0 + t, cell = word * 64u + bit0;
     const uint32_t j = (cell / s0) % e0;
     const uint32_t R = e0 - 1u - j;                       // cells after this one on the line
     uint32_t len = R + 1u;
-    if ((s0 & (s0 - 1u)) == 0 && s0 <= 32u) {
-      // a power-of-two stride: the line's cells sit at the same bit positions (mod s0) of every
-      // word, so the next flagged one is a mask, a count of trailing zeros and a division away
-      const unsigned long long P = s0 == 1 ? ~0ull : s0 == 2 ? 0x5555555555555555ull : s0 == 4 ? 0x1111111111111111ull
-                                 : s0 == 8 ? 0x0101010101010101ull : s0 == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;
-      const uint32_t bit0 = cell & 63u;
+    if (in_words) {
+      // the next flagged one is a mask, a count of trailing zeros and a division away
       const unsigned long long same = P << (bit0 % s0);
       unsigned long long m = tm & same & ~((2ull << bit0) - 1ull);      // this word: only the cells after this one
-      for (uint32_t k = cell >> 6;; m = mask[++k] & same) {
+      for (uint32_t k = word;; m = (k - w0 <= last ? s_mask[at + k - w0] : mask[k]) & same) {
         if (m) {
-          const uint32_t t = (k * 64u + (uint32_t)__builtin_ctzll(m) - cell) / s0;
-          if (t <= R) len = t;
+          const uint32_t run = (k * 64u + (uint32_t)__builtin_ctzll(m) - cell) / s0;
+          if (run <= R) len = run;
           break;
         }
         if ((k * 64u + 63u - cell) / s0 >= R) break;      // the line ends inside this word
+        k++;
       }
     } else {
       for (len = 1; len <= R; len++) {
@@ -416,22 +453,17 @@ __global__ __launch_bounds__(256) void make_boxes_kernel(Geo g, uint32_t a0,
         if ((mask[c2 >> 6] >> (c2 & 63u)) & 1ull) break;
       }
     }
-    const uint32_t shift = (a0 & 3u) * 8u;
     uint32_t L[4] = {0x01010101u, 0x01010101u, 0x01010101u, 0x01010101u};
     const uint32_t w = (0x01010101u & ~(0xFFu << shift)) | (len << shift);
     L[0] = (a0 >> 2) == 0 ? w : L[0];
     L[1] = (a0 >> 2) == 1 ? w : L[1];
     L[2] = (a0 >> 2) == 2 ? w : L[2];
     L[3] = (a0 >> 2) == 3 ? w : L[3];
-    bcell[id] = cell;
-    blen[id] = make_uint4(L[0], L[1], L[2], L[3]);
-    alive[id] = kLive;
+    bcell[id0 + i] = cell;
+    blen[id0 + i] = make_uint4(L[0], L[1], L[2], L[3]);
+    alive[id0 + i] = kLive;
   }
 }
-
-// A wave of the word-by-word kernels takes this many consecutive mask words: 64 (one per lane)
-// on large tables, few on small ones, which would otherwise occupy a handful of waves for long.
-static uint32_t words_per_wave(uint32_t n_words) { return n_words >= (1u << 21) ? 64u : 8u; }
 
 // The same for lines whose stride is a multiple of 64 cells, word by word of the table-order
 // mask: a wave takes 64 consecutive words (lane t fetches word t and its prefix sum) and then,
@@ -712,8 +744,8 @@ void launch_head_flags(const Geo& g, uint32_t a0, const uint64_t* cost, const ui
     hipLaunchKernelGGL(head_flags_wave_kernel, dim3((blocks + 4 * kHeadSpread - 1) / (4 * kHeadSpread) * (4 * kHeadSpread)), dim3(256), 0, st, g, a0, cost, arg,
                        (const unsigned long long*)fitmap, axis_sizes, maskD, maskC, lineD, lineC);
   else
-    hipLaunchKernelGGL(head_flags_kernel, dim3((g.n + 256 * kCellWords - 1) / (256 * kCellWords)), dim3(256), 0, st, g, a0, cost, arg, fitmap, axis_sizes,
-                       maskD, maskC);
+    hipLaunchKernelGGL(head_flags_kernel, dim3((g.n + 256 * kCellWords - 1) / (256 * kCellWords)), dim3(256), 0, st, g, a0, cost, arg,
+                       (const unsigned long long*)fitmap, axis_sizes, maskD, maskC);
 }
 
 void launch_second_axis(const Geo& g, uint32_t a0, uint32_t a1, bool is_cost, const unsigned long long* runs,
@@ -733,14 +765,15 @@ void launch_second_axis(const Geo& g, uint32_t a0, uint32_t a1, bool is_cost, co
 void launch_make_boxes(const Geo& g, uint32_t a0, const unsigned long long* mask, const uint32_t* prefix,
                        const unsigned long long* line, const unsigned long long* col, uint32_t a1, uint32_t* bcell,
                        void* blen, uint8_t* alive, hipStream_t st) {
+  const uint32_t n_words = (g.n + 63) / 64;
   if (g.stride[a0] % 64 == 0) {
-    const uint32_t n_words = g.n / 64;
     const uint32_t wpw = words_per_wave(n_words);
     hipLaunchKernelGGL(make_boxes_wave_kernel, dim3((n_words + 4 * wpw - 1) / (4 * wpw)), dim3(256), 0, st, g, a0, n_words, wpw, mask, prefix,
                        line, col, a1, bcell, (uint4*)blen, alive);
   } else {
-    hipLaunchKernelGGL(make_boxes_kernel, dim3((g.n + 256 * kCellWords - 1) / (256 * kCellWords)), dim3(256), 0, st, g, a0, mask, prefix, bcell,
-                       (uint4*)blen, alive);
+    const uint32_t wpw = n_words >= (1u << 18) ? 64u : 8u;        // 4,096 waves from there on
+    hipLaunchKernelGGL(make_boxes_kernel, dim3((n_words + 4 * wpw - 1) / (4 * wpw)), dim3(256), 0, st, g, a0, n_words, wpw, mask, prefix,
+                       bcell, (uint4*)blen, alive);
   }
 }
 

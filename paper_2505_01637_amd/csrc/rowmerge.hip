@@ -1019,23 +1019,13 @@ __device__ __forceinline__ U reduce_by(U a, U b) {
   return a << shift;
 }
 
-// The lane of a wave whose word has the wave's box i (excl: boxes of the lanes before), and the place of its set bit
-// number i of a word.
+// The lane of a wave whose word has the wave's box i (excl: boxes of the lanes before).
 __device__ __forceinline__ uint32_t lane_with(uint32_t excl, uint32_t i) {
   uint32_t at = 0;
 #pragma unroll
   for (uint32_t d = 32; d > 0; d >>= 1) {
     const uint32_t there = (uint32_t)__shfl((int)excl, (int)(at + d), 64);
     at += there <= i ? d : 0u;
-  }
-  return at;
-}
-__device__ __forceinline__ uint32_t nth_bit(u64 x, uint32_t i) {
-  uint32_t at = 0;
-#pragma unroll
-  for (uint32_t d = 32; d > 0; d >>= 1) {
-    const uint32_t n = (uint32_t)__popcll(x >> at & ((1ull << d) - 1ull));
-    if (i >= n) { i -= n; at += d; }
   }
   return at;
 }

@@ -247,6 +247,17 @@ def test_compressed_query_one_box_and_long_axis():
     compare_config({"name": "100-on-k", "target": base["target"], "lattices": [("M", lat, [])]})
 
 
+@pytest.mark.parametrize("number,counts", [(1, (1, 1, 3)), (1, (5, 7, 65)), (1, (3, 3, 8)), (7, (1, 2, 3)), (7, (3, 5, 4))])
+def test_parity_boxes_of_lines_within_words(number, counts):
+    """Lines whose stride is below a word's 64 cells (8 along a size axis, 1 along a memory bound):
+    tables of less than a word, of a ragged last word and of whole words, boxes that open in each
+    word a wave holds and runs that leave the words it holds."""
+    cfg = W.config(number, max_size=2)
+    label, lat, deps = cfg["lattices"][0]
+    lat = dict(lat, sizes=[[1]] + [list(range(1, n + 1)) for n in counts])
+    compare_config({"name": "lines", "target": cfg["target"], "lattices": [(label, lat, deps)]})
+
+
 @pytest.mark.parametrize("number,max_size", [(1, 2), (5, 8), (10, 6), (12, 8)])
 def test_box_records_into_a_larger_buffer(number, max_size):
     """mrl_emit_compressed: lists from a few boxes to several chunks of 16,384 with a ragged last
