@@ -343,9 +343,15 @@ int32_t mrl_solve_graph(const mrl_target* t, const mrl_job* jobs, uint32_t n_job
 /* ---------------------------------------------------------------------------
  * Query (Section 4: a Spec that the memo table already holds is answered from
  * it).  specs, cost_out, rewrite_out: host arrays of n.  Several host threads may
- * ask one table at a time, here and through mrl_schedule: a call stages through
- * pinned host memory of its own (blocks that the library keeps for the next call)
- * and works on the table's stream. */
+ * ask one table at a time, here and through mrl_schedule, with any device current:
+ * a call stages through 4 MiB of pinned host memory of its own (blocks that the
+ * library keeps for the next call, at most four of them idle) and works on the
+ * table's stream.  A question of more than 32,768 Specs, here and to
+ * mrl_query_compressed, and a list of more than 16,384 boxes (mrl_emit_compressed)
+ * is taken in four stretches at once: three of them run on host threads and streams
+ * of the library's own, at most twelve such threads for all calls together (a call
+ * that finds them taken goes through alone), behind what the table's stream holds
+ * when the call is made.  Nothing of a call runs on when it has returned. */
 typedef struct { uint32_t x[MRL_MAX_DIMS]; } mrl_coord;
 int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n,
                   uint64_t* cost_out, uint16_t* rewrite_out);

@@ -742,7 +742,8 @@ int32_t get_stage(StageLease& lease) {
   return MRL_OK;
 }
 
-// Makes a device current for a scope.
+// Makes a device current for a scope: a question may be asked while another one is.  The null stream is the current
+// device's, and so are a helper stream and an event, which is recorded on streams of its own device only.
 struct OnDevice {
   int before = -1;
   int32_t set(int device) {
@@ -1719,6 +1720,9 @@ int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n, uint64
   if (!tab || (n && (!specs || !cost_out || !rewrite_out))) return fail(MRL_E_INVAL, "NULL argument");
   const Geo& g = tab->cp->geo;
   if (!n) return MRL_OK;
+  OnDevice on;
+  const int32_t rc = on.set(tab->device);
+  if (rc) return rc;
   // a chunk: linear indices, costs, rewrite ids
   static_assert((size_t)kQueryChunk * 18 <= kStageHalf, "a chunk fits half a staging block");
   return take_in_parts(n, kQueryChunk, 18, tab->device, tab->stream,
@@ -1910,6 +1914,9 @@ int32_t mrl_schedule(const mrl_table* tab, const mrl_coord* goal, mrl_schedule_n
   return guarded([&]() -> int32_t {
   if (!tab || !goal) return fail(MRL_E_INVAL, "NULL argument");
   struct Item { const mrl_table* t; uint32_t which; mrl_coord x; };
+  OnDevice on;
+  int32_t rc = on.set(tab->device);
+  if (rc) return rc;
   std::vector<Item> stack;
   stack.push_back({tab, 0u, *goal});
   ChainReader reader;
@@ -1921,7 +1928,7 @@ int32_t mrl_schedule(const mrl_table* tab, const mrl_coord* goal, mrl_schedule_n
     const DevParams& P = it.t->P;
     uint64_t cost;
     uint16_t rw;
-    int32_t rc = reader.entry(it.t, it.x, &cost, &rw);
+    rc = reader.entry(it.t, it.x, &cost, &rw);
     if (rc) return rc;
     if (cost == kInf) {
       if (n == 0) return fail(MRL_E_INVAL, "the goal Spec has no implementation");
@@ -2138,6 +2145,9 @@ int32_t mrl_query_compressed(const mrl_table* tab, const mrl_coord* specs, size_
   const Geo& g = c.geo;
   for (uint32_t a = 0; a < g.ndim; a++)
     if (g.ext[a] > 256) return fail(MRL_E_INVAL, "axis %u has %u coordinates: the box index holds one byte per axis", a, g.ext[a]);
+  OnDevice on;
+  const int32_t rc = on.set(tab->device);
+  if (rc) return rc;
   std::lock_guard<std::mutex> lock(tab->lookup_mu);
   LookupList lists[2];
   for (uint32_t which = 0; which < 2; which++) {

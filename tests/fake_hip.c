@@ -1,0 +1,77 @@
+/* A HIP runtime of two devices without kernels, for tests of the library's host part on the CPU.
+ * "Device" memory is host memory, launches do nothing but are counted by the device they go to, copies are
+ * made at once.  As in HIP, a stream and an event belong to the device that was current when they were made
+ * (the null stream to the current one), and an event is recorded on a stream of its own device only. */
+#include <stdint.h>
+#include <stdlib.h>
+#include <string.h>
+
+typedef struct { uint32_t x, y, z; } dim3;
+struct on { int device; };
+enum { kDevices = 2, kInvalidValue = 1, kInvalidDevice = 101, kInvalidHandle = 400 };
+
+static __thread int current;
+static __thread struct { dim3 grid, block; size_t shared; void* stream; } config;
+static int launched[kDevices];
+
+static int device_of(void* stream) { return stream ? ((struct on*)stream)->device : current; }
+static int make(void** out) {
+  struct on* s = malloc(sizeof *s);
+  s->device = current;
+  *out = s;
+  return 0;
+}
+
+int fake_launches(int device) { return __atomic_load_n(&launched[device], __ATOMIC_SEQ_CST); }
+
+int hipGetDevice(int* d) { *d = current; return 0; }
+int hipSetDevice(int d) { if (d < 0 || d >= kDevices) return kInvalidDevice; current = d; return 0; }
+int hipGetLastError(void) { return 0; }
+const char* hipGetErrorString(int e) { return e == kInvalidHandle ? "invalid resource handle" : "error"; }
+
+int hipStreamCreateWithFlags(void** s, unsigned flags) { (void)flags; return make(s); }
+int hipStreamSynchronize(void* s) { (void)s; return 0; }
+int hipStreamWaitEvent(void* s, void* e, unsigned flags) { (void)s; (void)flags; return e ? 0 : kInvalidHandle; }
+int hipEventCreate(void** e) { return make(e); }
+int hipEventCreateWithFlags(void** e, unsigned flags) { (void)flags; return make(e); }
+int hipEventDestroy(void* e) { free(e); return 0; }
+int hipEventRecord(void* e, void* s) { return ((struct on*)e)->device == device_of(s) ? 0 : kInvalidHandle; }
+int hipEventSynchronize(void* e) { (void)e; return 0; }
+int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 0; return 0; }
+
+static int zeroed(void** p, size_t n) {
+  if (posix_memalign(p, 256, n ? n : 1)) return 2;
+  memset(*p, 0, n);
+  return 0;
+}
+int hipMalloc(void** p, size_t n) { return zeroed(p, n); }
+int hipFree(void* p) { free(p); return 0; }
+int hipHostMalloc(void** p, size_t n, unsigned flags) { (void)flags; return zeroed(p, n); }
+int hipHostFree(void* p) { free(p); return 0; }
+int hipMemcpy(void* to, const void* from, size_t n, int kind) { (void)kind; memcpy(to, from, n); return 0; }
+int hipMemcpyAsync(void* to, const void* from, size_t n, int kind, void* s) { (void)s; return hipMemcpy(to, from, n, kind); }
+int hipMemsetAsync(void* p, int v, size_t n, void* s) { (void)s; memset(p, v, n); return 0; }
+int hipGetSymbolAddress(void** p, const void* symbol) { (void)symbol; *p = 0; return kInvalidValue; }
+
+int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shared, void* s) {
+  (void)f; (void)grid; (void)block; (void)args; (void)shared;
+  __atomic_add_fetch(&launched[device_of(s)], 1, __ATOMIC_SEQ_CST);
+  return 0;
+}
+int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, void* s) {
+  config.grid = grid; config.block = block; config.shared = shared; config.stream = s;
+  return 0;
+}
+int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, void** s) {
+  *grid = config.grid; *block = config.block; *shared = config.shared; *s = config.stream;
+  return 0;
+}
+void** __hipRegisterFatBinary(const void* data) { static void* handle; (void)data; return &handle; }
+void __hipUnregisterFatBinary(void** h) { (void)h; }
+void __hipRegisterFunction(void** h, const void* f, char* device_name, const char* name, unsigned threads, void* tid, void* bid, void* block,
+                           void* grid, int* warp) {
+  (void)h; (void)f; (void)device_name; (void)name; (void)threads; (void)tid; (void)bid; (void)block; (void)grid; (void)warp;
+}
+void __hipRegisterVar(void** h, void* var, char* host_name, char* device_name, int ext, size_t size, int constant, int global) {
+  (void)h; (void)var; (void)host_name; (void)device_name; (void)ext; (void)size; (void)constant; (void)global;
+}
