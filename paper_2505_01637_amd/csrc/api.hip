@@ -258,7 +258,7 @@ FixedLayout fixed_layout(const Compiled& c) {
     f.rows_info = take((size_t)g.n_planes * g.ek * kRowInfoBytes);
     f.rows_cnt = take((size_t)g.n_shapes * 8);
     f.rows_start = take((size_t)g.n_shapes * 8);
-    f.rows_sum = take(rows_sum_bytes());
+    f.rows_sum = take(rows_sum_bytes(g));
     f.rows_tot = take(kRowTotals * 4);
     f.rows_dyn = o;
   }

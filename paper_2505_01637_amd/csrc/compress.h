@@ -181,12 +181,12 @@ struct RowBufs {
   uint32_t *rows, *first, *plane_of;       // per plane: rows kept, index of its first; per kept row: its plane
   void* info;                              // per kept row: kRowInfoBytes
   uint32_t *cnt, *start;                   // per list and shape: boxes, boxes before
-  void* sum;                               // rows_sum_bytes()
+  void* sum;                               // rows_sum_bytes
   uint32_t *tot;                           // kRowTotals
   char* dyn;                               // what depends on the contents: word arrays, extents, final lists
   uint64_t room;                           // bytes there
 };
-size_t rows_sum_bytes();
+size_t rows_sum_bytes(const RowGeo& g);
 // The whole merge and the final lists; nothing is read back.  sizes: DevParams::sizes on the device.
 void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const uint16_t* arg, const uint32_t* fitmap,
                  const uint32_t* sizes, hipStream_t st);

@@ -75,13 +75,17 @@ struct RowWords {
 
 __host__ __device__ __forceinline__ uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
 
+// (16 bytes, as wide as anything is read, and not 256: a table of one word would take 3.5 KB for its arrays of 8 bytes, more
+// than the scratch that suffices for its boxes one by one leaves over, and would be merged both ways)
+__host__ __device__ __forceinline__ uint64_t up16(uint64_t x) { return (x + 15) & ~15ull; }
+
 __host__ __device__ __forceinline__ uint64_t row_word_bytes(const RowGeo& g, uint64_t n_rows) {
-  const uint64_t one = up256(n_rows * g.en * 8), both = up256(2 * n_rows * g.en * 8), sets = 2 + (g.em > 1 ? 1 : 0) + (g.eb > 1 ? 1 : 0);
+  const uint64_t one = up16(n_rows * g.en * 8), both = 2 * n_rows * g.en * 8, sets = 2 + (g.em > 1 ? 1 : 0) + (g.eb > 1 ? 1 : 0);
   return 2 * sets * one + (3 + g.n_inner) * both;
 }
 __host__ __device__ __forceinline__ uint64_t row_list_bytes(uint64_t n) { return up256(n * 4) + up256(n * 16) + 2 * up256(n * 8); }
 __host__ __device__ __forceinline__ uint64_t row_lists_at(const RowGeo& g, const uint32_t* tot) {
-  return row_word_bytes(g, tot[kRowsTotal]) + up256((uint64_t)tot[kLongTotal] * 4) + up256((uint64_t)tot[kHeadsTotal] * 2);
+  return up256(row_word_bytes(g, tot[kRowsTotal]) + up16((uint64_t)tot[kLongTotal] * 4) + up16((uint64_t)tot[kHeadsTotal] * 2));
 }
 
 bool rows_fit(const RowGeo& g, const uint32_t* tot, uint64_t room, uint64_t list_at[2], uint64_t* end) {
@@ -96,7 +100,7 @@ bool rows_fit(const RowGeo& g, const uint32_t* tot, uint64_t room, uint64_t list
 // false: the rows (or, with heads, what is kept per head) do not fit the scratch; every kernel then does nothing and the
 // host finds out by the same sums.
 __device__ __forceinline__ bool row_words(const RowGeo& g, const RowBufs& B, RowWords& W, bool heads = false) {
-  const uint64_t n_rows = B.tot[kRowsTotal], one = up256(n_rows * g.en * 8), both = up256(2 * n_rows * g.en * 8);
+  const uint64_t n_rows = B.tot[kRowsTotal], one = up16(n_rows * g.en * 8), both = 2 * n_rows * g.en * 8;
   char* p = B.dyn;
   auto take = [&](uint64_t bytes) { char* at = p; p += bytes; return at; };
   W.H[0] = (u64*)take(one); W.H[1] = (u64*)take(one);
@@ -111,7 +115,7 @@ __device__ __forceinline__ bool row_words(const RowGeo& g, const RowBufs& B, Row
   W.ext = (uint32_t*)p; W.inner = nullptr;
   if ((uint64_t)(p - B.dyn) > B.room) return false;
   if (!heads) return true;
-  W.inner = (uint16_t*)(p + up256((uint64_t)B.tot[kLongTotal] * 4));
+  W.inner = (uint16_t*)(p + up16((uint64_t)B.tot[kLongTotal] * 4));
   return row_lists_at(g, B.tot) <= B.room;
 }
 
@@ -611,7 +615,7 @@ __device__ __forceinline__ u64 not_last(uint32_t b, bool two) {
 // Where `agree` has the words of an axis: level axis q, or the field that starts at bit b.
 __device__ __forceinline__ u64* agree_level(const RowGeo& g, const RowWords& W, size_t both, uint32_t q) { return W.agree + both * q; }
 __device__ __forceinline__ u64* agree_field(const RowGeo& g, const RowWords& W, size_t both, uint32_t b) { return W.agree + both * (g.n_levels + b); }
-__device__ __forceinline__ size_t agree_stride(const RowGeo& g, uint32_t n_rows) { return (size_t)(up256(2ull * n_rows * g.en * 8) / 8); }
+__device__ __forceinline__ size_t agree_stride(const RowGeo& g, uint32_t n_rows) { return 2 * (size_t)n_rows * g.en; }
 
 // Level axis q (in merge order) is the bits [LV + 2 q, LV + 2 q + 2) of a cell's place in the shape: inside a word, or the
 // next word's row (the one step further of 32 cells runs over two words).
@@ -1235,17 +1239,20 @@ __global__ __launch_bounds__(256) void sum_kernel(S s, typename S::V* __restrict
 }
 
 // bound: the most items there can be.
+static uint32_t sum_groups(uint64_t bound) {
+  const uint64_t tiles = (bound + kSumTile - 1) / kSumTile;
+  return (uint32_t)(tiles < 1 ? 1 : tiles < kSumGroups ? tiles : kSumGroups);
+}
 template <class S>
 static void launch_sum(const S& s, uint64_t bound, void* sums, uint32_t* total, hipStream_t st) {
   typedef typename S::V V;
-  const uint64_t tiles = (bound + kSumTile - 1) / kSumTile;
-  const uint32_t groups = (uint32_t)(tiles < 1 ? 1 : tiles < kSumGroups ? tiles : kSumGroups);
+  const uint32_t groups = sum_groups(bound);
   if (groups > 1) hipLaunchKernelGGL(HIP_KERNEL_NAME(sum_kernel<S, false>), dim3(groups), dim3(256), 0, st, s, (V*)sums, (V*)total);
   hipLaunchKernelGGL(HIP_KERNEL_NAME(sum_kernel<S, true>), dim3(groups), dim3(256), 0, st, s, (V*)sums, (V*)total);
 }
 
 // ---------------------------------------------------------------- launches
-size_t rows_sum_bytes() { return kSumGroups * 8; }
+size_t rows_sum_bytes(const RowGeo& g) { return sum_groups(2 * ((uint64_t)g.n_shapes << g.lg_nw)) * 8; }      // (the words of both lists: the longest sum)
 static_assert(sizeof(RowInfo) == kRowInfoBytes, "the caller makes room for it");
 
 void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const uint16_t* arg, const uint32_t* fitmap,

@@ -443,6 +443,17 @@ def test_boxes_merged_one_by_one_where_the_rows_do_not_fit(case):
     assert took[:1] == [1.0] and (case != "long-kn" or len(took) > 1)
 
 
+@pytest.mark.parametrize("number,max_size", [(2, 1), (2, 2), (3, 1), (4, 1), (9, 1), (12, 1), (12, 2)])
+def test_scratch_for_any_contents_holds_the_words(number, max_size):
+    """Tables of one and a few mask words: with the scratch that mrl_table_bytes asks for they are merged as they are with
+    plenty (what a table of one word needs beside its boxes is a few lists of 8 bytes)."""
+    cfg = W.config(number, max_size=max_size)
+    _, got, _ = compare_config(cfg)
+    _, ample, _ = compare_config(cfg, scratch_bytes=64 << 20)
+    for label, _, _ in cfg["lattices"]:
+        assert got[label].stats.scratch_used == ample[label].stats.scratch_used, label
+
+
 def two_level_bounded(caps, sizes):
     cfg = W.config(1, seed=11, max_size=4)
     t = cfg["target"]
