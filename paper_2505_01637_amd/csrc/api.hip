@@ -1143,10 +1143,12 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
 
   const FixedLayout f = fixed_layout(c);
   tab->f = f;
+  // What the merge word by word needs beyond the fill's part depends on the contents; where that does not suffice, boxes are
+  // merged one by one.  Its words are the larger part: if those of all rows do not fit, the plan's fit map is asked how many
+  // rows there are, together with the work lists' lengths.
   RowGeo row_g;
-  const bool by_rows = row_geo(c, row_g) && scratch_bytes >= f.rows_dyn;
-  // (what the merge word by word needs beyond the fill's part depends on the contents; where it does not suffice, boxes
-  // are merged one by one)
+  bool by_rows = row_geo(c, row_g) && scratch_bytes >= f.rows_dyn && row_words_fit(row_g, row_g.n_planes, scratch_bytes - f.rows_dyn);
+  const bool ask_rows = by_rows && !row_words_fit(row_g, (uint64_t)row_g.n_planes * row_g.ek, scratch_bytes - f.rows_dyn);
   if (scratch_bytes < (by_rows ? f.fill_end : f.least())) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
   char* base = (char*)d_scratch;
   hipStream_t st = (hipStream_t)hip_stream;
@@ -1269,6 +1271,10 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
               fused_prefill ? tab->d_cost : nullptr, fused_prefill ? tab->d_arg : nullptr, st);
   if (16 + 3 * (size_t)n_lev > kPinnedCounts) return fail(MRL_E_INVAL, "too many dependency levels (%u)", n_lev);
   const uint32_t* cnt = aux->h_counts + 16;            // pinned: the copy does not go through a staging buffer
+  if (ask_rows) {
+    launch_row_total(row_g, d_fitmap, &d_ctr->rows, st);
+    HIP_TRY(hipMemcpyAsync(aux->h_counts + kRowTotals, &d_ctr->rows, 4, hipMemcpyDeviceToHost, st));
+  }
   HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, plan.list_cnt, 3 * (size_t)n_lev * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   hipEvent_t counts_ready = aux->events[ev_used++];
@@ -1279,6 +1285,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   HIP_TRY(hipEventRecord(ev[4], st));
   prefill_timed = true;
   HIP_TRY(hipEventSynchronize(counts_ready));
+  if (ask_rows) by_rows = row_words_fit(row_g, aux->h_counts[kRowTotals], scratch_bytes - f.rows_dyn);
   if (deps_late) {
     // now the tables this lattice reads: their fills are queued (or the call waits here until
     // they are); the parameters go up once more, with their addresses, and the levels wait for them

@@ -190,6 +190,10 @@ size_t rows_sum_bytes(const RowGeo& g);
 // The whole merge and the final lists; nothing is read back.  sizes: DevParams::sizes on the device.
 void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const uint16_t* arg, const uint32_t* fitmap,
                  const uint32_t* sizes, hipStream_t st);
+// Whether the words of so many kept rows fit room bytes (a plane keeps one row at least, ek at most).
+bool row_words_fit(const RowGeo& g, uint64_t n_rows, uint64_t room);
+// Adds the number of rows that will be kept to *total, from the fit map alone.
+void launch_row_total(const RowGeo& g, const uint32_t* fitmap, uint32_t* total, hipStream_t st);
 // Given the totals: whether all of it fitted (nothing valid was written if not), where in dyn the lists lie, and the end.
 bool rows_fit(const RowGeo& g, const uint32_t* tot, uint64_t room, uint64_t list_at[2], uint64_t* end);
 

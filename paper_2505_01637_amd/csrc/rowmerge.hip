@@ -64,13 +64,15 @@ __device__ __forceinline__ uint32_t spread_block() {
 
 // ---------------------------------------------------------------- where things lie
 // Word arrays of the kept rows, n_rows * en words each (T, N and their ranks: both lists' one after the other), the size
-// extents of N's heads, the extents inside the shape of the heads left at the end (at the ranks of T's).
+// extents of N's heads, the extents inside the shape of the heads left at the end (at the ranks of T's), and `agree`.  That is
+// done with when the final lists are written, which take its place: without that a caller's scratch could hold the words
+// and not the lists, and everything would be done twice, here and box by box.
 struct RowWords {
   u64 *H[2], *Fk[2], *Fm[2], *Fb[2], *T, *N;
-  u64* agree;                // per axis inside the shape (levels, then fields by their bit): T's heads that agree with the next one
   uint2* rank;               // heads of N, of T before a word's
   uint32_t* ext;
   uint16_t* inner;
+  u64* agree;                // per axis inside the shape (levels, then fields by their bit): T's heads that agree with the next one
 };
 
 __host__ __device__ __forceinline__ uint64_t up256(uint64_t x) { return (x + 255) & ~255ull; }
@@ -79,21 +81,31 @@ __host__ __device__ __forceinline__ uint64_t up256(uint64_t x) { return (x + 255
 // than the scratch that suffices for its boxes one by one leaves over, and would be merged both ways)
 __host__ __device__ __forceinline__ uint64_t up16(uint64_t x) { return (x + 15) & ~15ull; }
 
-__host__ __device__ __forceinline__ uint64_t row_word_bytes(const RowGeo& g, uint64_t n_rows) {
-  const uint64_t one = up16(n_rows * g.en * 8), both = 2 * n_rows * g.en * 8, sets = 2 + (g.em > 1 ? 1 : 0) + (g.eb > 1 ? 1 : 0);
-  return 2 * sets * one + (3 + g.n_inner) * both;
+__host__ __device__ __forceinline__ uint64_t row_base_bytes(const RowGeo& g, uint64_t n_rows) {
+  const uint64_t sets = 2 + (g.em > 1 ? 1 : 0) + (g.eb > 1 ? 1 : 0);
+  return 2 * sets * up16(n_rows * g.en * 8) + 3 * 2 * n_rows * g.en * 8;
 }
+__host__ __device__ __forceinline__ uint64_t row_agree_bytes(const RowGeo& g, uint64_t n_rows) { return g.n_inner * 2 * n_rows * g.en * 8; }
 __host__ __device__ __forceinline__ uint64_t row_list_bytes(uint64_t n) { return up256(n * 4) + up256(n * 16) + 2 * up256(n * 8); }
+// where `agree` and then the lists lie
 __host__ __device__ __forceinline__ uint64_t row_lists_at(const RowGeo& g, const uint32_t* tot) {
-  return up256(row_word_bytes(g, tot[kRowsTotal]) + up16((uint64_t)tot[kLongTotal] * 4) + up16((uint64_t)tot[kHeadsTotal] * 2));
+  return up256(row_base_bytes(g, tot[kRowsTotal]) + up16((uint64_t)tot[kLongTotal] * 4) + up16((uint64_t)tot[kHeadsTotal] * 2));
 }
+__host__ __device__ __forceinline__ bool words_fit(const RowGeo& g, uint64_t n_rows, uint64_t room) {
+  return row_base_bytes(g, n_rows) + row_agree_bytes(g, n_rows) <= room;
+}
+
+bool row_words_fit(const RowGeo& g, uint64_t n_rows, uint64_t room) { return words_fit(g, n_rows, room); }
 
 bool rows_fit(const RowGeo& g, const uint32_t* tot, uint64_t room, uint64_t list_at[2], uint64_t* end) {
   // (a kernel that found no room left the totals behind it unset: in this order)
-  if (row_word_bytes(g, tot[kRowsTotal]) > room || row_lists_at(g, tot) > room) return false;
+  if (!words_fit(g, tot[kRowsTotal], room)) return false;
   list_at[0] = row_lists_at(g, tot);
+  const uint64_t words_end = list_at[0] + row_agree_bytes(g, tot[kRowsTotal]);
+  if (words_end > room) return false;
   list_at[1] = list_at[0] + row_list_bytes(tot[kBoxesFirst]);
-  *end = list_at[1] + row_list_bytes(tot[kBoxesTotal] - tot[kBoxesFirst]);
+  const uint64_t lists_end = list_at[1] + row_list_bytes(tot[kBoxesTotal] - tot[kBoxesFirst]);
+  *end = words_end > lists_end ? words_end : lists_end;
   return *end <= room;
 }
 
@@ -110,13 +122,14 @@ __device__ __forceinline__ bool row_words(const RowGeo& g, const RowBufs& B, Row
   W.Fb[0] = (u64*)take(for_b); W.Fb[1] = (u64*)take(for_b);
   W.T = (u64*)take(both);
   W.N = (u64*)take(both);
-  W.agree = (u64*)take(g.n_inner * both);
   W.rank = (uint2*)take(both);
-  W.ext = (uint32_t*)p; W.inner = nullptr;
-  if ((uint64_t)(p - B.dyn) > B.room) return false;
+  W.ext = (uint32_t*)p; W.inner = nullptr; W.agree = nullptr;
+  if (!words_fit(g, n_rows, B.room)) return false;
   if (!heads) return true;
   W.inner = (uint16_t*)(p + up16((uint64_t)B.tot[kLongTotal] * 4));
-  return row_lists_at(g, B.tot) <= B.room;
+  const uint64_t lists = row_lists_at(g, B.tot);
+  W.agree = (u64*)(B.dyn + lists);
+  return lists + row_agree_bytes(g, n_rows) <= B.room;
 }
 
 // Words of a row that is not kept: every cell (INF, NONE), one run along n, folded into the row before it on k.
@@ -125,16 +138,28 @@ __device__ __forceinline__ u64 gone_word(uint32_t n) { return n == 0 ? ~0ull : 0
 // ---------------------------------------------------------------- rows
 // Sizes ascend, and what fits a level at some size fits it at every smaller one (a layout that only some sizes have
 // shares its word with the row-major one, which all have): a row has a fitting cell if its first step has one.
-__global__ __launch_bounds__(256) void row_count_kernel(const RowGeo g, const u64* __restrict__ fit, uint32_t* __restrict__ rows) {
-  const uint32_t p = blockIdx.x * 256u + threadIdx.x;
-  if (p >= g.n_planes) return;
+__device__ __forceinline__ uint32_t rows_kept(const RowGeo& g, const u64* __restrict__ fit, uint32_t p) {
   const uint32_t w = p & (g.nw - 1u), bm = p >> g.lg_nw;
   const u64* f = fit + (((size_t)bm * g.ek * g.en) << g.lg_nw) + w;
   const size_t step = (size_t)g.en << g.lg_nw;
   uint32_t last = 0;
 #pragma unroll 8
   for (uint32_t k = 0; k < g.ek; k++) last = f[k * step] ? k + 1u : last;
-  rows[p] = last + 1u < g.ek ? last + 1u : g.ek;
+  return last + 1u < g.ek ? last + 1u : g.ek;
+}
+
+__global__ __launch_bounds__(256) void row_count_kernel(const RowGeo g, const u64* __restrict__ fit, uint32_t* __restrict__ rows) {
+  const uint32_t p = blockIdx.x * 256u + threadIdx.x;
+  if (p < g.n_planes) rows[p] = rows_kept(g, fit, p);
+}
+
+// Only their number, added to *total: all that is known before the fill, whose lists lie where the rows' will.
+__global__ __launch_bounds__(256) void row_total_kernel(const RowGeo g, const u64* __restrict__ fit, uint32_t* __restrict__ total) {
+  const uint32_t p = blockIdx.x * 256u + threadIdx.x;
+  uint32_t n = p < g.n_planes ? rows_kept(g, fit, p) : 0u;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) n += __shfl_down(n, d, 64);
+  if ((threadIdx.x & 63u) == 0) atomicAdd(total, n);
 }
 
 // Cells whose normalised costs agree: c1 / s1 == c2 / s2, exactly.  i1, i2: the cells that are INF (finite costs stay
@@ -1254,6 +1279,10 @@ static void launch_sum(const S& s, uint64_t bound, void* sums, uint32_t* total, 
 // ---------------------------------------------------------------- launches
 size_t rows_sum_bytes(const RowGeo& g) { return sum_groups(2 * ((uint64_t)g.n_shapes << g.lg_nw)) * 8; }      // (the words of both lists: the longest sum)
 static_assert(sizeof(RowInfo) == kRowInfoBytes, "the caller makes room for it");
+
+void launch_row_total(const RowGeo& g, const uint32_t* fitmap, uint32_t* total, hipStream_t st) {
+  hipLaunchKernelGGL(row_total_kernel, dim3((g.n_planes + 255) / 256), dim3(256), 0, st, g, (const u64*)fitmap, total);
+}
 
 void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const uint16_t* arg, const uint32_t* fitmap,
                  const uint32_t* sizes, hipStream_t st) {

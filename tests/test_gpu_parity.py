@@ -409,6 +409,16 @@ def row_merge_case(case):
     elif kind == "full":                                # every cell fits: no empty words, batches of 256 everywhere
         cfg = {"fused": W.config(5, max_size=8), "chain": W.config(10, max_size=4)}[tail]
         cfg["target"]["capacity_bytes"] = [W.UNBOUNDED] * 4
+    elif kind == "regular":                             # every cell fits, costs per volume differ along n and k only: few boxes, many words
+        t = cfg["target"]
+        t["capacity_bytes"] = [W.UNBOUNDED] * 4
+        t["load_coef"] = [[[0, 0] for _ in range(4)] for _ in range(4)]
+        t["store_coef"] = [[[0, 0] for _ in range(4)] for _ in range(4)]
+        t["load_coef"][1][0][0], t["loop_overhead"] = 3, 0
+        t["microkernels"] = [(W.MK_SCALAR_FMA, 1, 2)]
+        r = list(range(1, 65))
+        lat.update(sizes={"nk": [[1], [1, 2], r, r], "bnk": [[1, 2, 3], [1, 2], r[:40], r[:50]]}[tail],
+                   layout_coord=[0, 0, 0, 0, 0] if tail == "nk" else [1, 0, 1, 0, 0])
     elif kind == "b":                                   # long along b, chains along k and m before it
         lat.update(sizes=[list(range(1, 41)), [1, 2, 4], [1, 2, 3, 6], [1, 2, 8]])
     return dict(cfg, name="rows-" + case)
@@ -441,6 +451,32 @@ def test_boxes_merged_one_by_one_where_the_rows_do_not_fit(case):
         took.append(part)
         assert [tab.boxes(which).tobytes() for which in (0, 1)] == lists
     assert took[:1] == [1.0] and (case != "long-kn" or len(took) > 1)
+
+
+@pytest.mark.parametrize("case", ["regular-nk", "regular-bnk"])
+def test_scratch_that_holds_the_boxes_and_not_the_words(case):
+    """Tables with implementations whose words take more scratch than their boxes: from the merge by words' need downwards, at
+    first by 256 bytes, the words fit but not what is kept per head, then not the words; either way the boxes are merged one by
+    one and the lists are the oracle's."""
+    B = _binding()
+    cfg = row_merge_case(case)
+    target, tabs, want = compare_config(cfg)
+    label, lat, _ = cfg["lattices"][0]
+    lists = [x.tobytes() for x in O.compress_table(cfg["target"], lat, want[label]["cost"], want[label]["argmin"])]
+    assert (want[label]["cost"] != W.UNBOUNDED).any() and tabs[label].stats.n_cost_boxes > 8
+    used = int(tabs[label].stats.scratch_used)
+    by_boxes = 0
+    for less in [256 * i for i in range(13)] + [used * i // 5120 * 256 for i in range(1, 12)]:
+        try:
+            tab = B.solve(target, lat, scratch_bytes=used - less)
+        except B.MorelloError as e:
+            assert e.code == B.E_NOMEM and less > used // 5
+            continue
+        assert tab.stats.scratch_used <= used - less
+        assert [tab.boxes(which).tobytes() for which in (0, 1)] == lists, less
+        assert (tab.stats.scratch_used == used) == (less == 0)
+        by_boxes += less > 0
+    assert by_boxes >= 14
 
 
 @pytest.mark.parametrize("number,max_size", [(2, 1), (2, 2), (3, 1), (4, 1), (9, 1), (12, 1), (12, 2)])
