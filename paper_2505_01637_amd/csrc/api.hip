@@ -138,7 +138,7 @@ struct FixedLayout {
       upload_end, fill_end, end;
   uint32_t n_words;
   // the merge word by word (row_geo): its fixed lists from `shared` on, then dyn
-  size_t shared, rows_rows, rows_first, rows_plane, rows_info, rows_cnt, rows_start, rows_sum, rows_tot, rows_dyn;
+  size_t shared, rows_rows, rows_first, rows_info, rows_cnt, rows_start, rows_sum, rows_tot, rows_dyn;
   // a solve's least: the fill's buffers share their place with the compression's and its lists
   size_t least() const { return fill_end > end ? fill_end : end; }
   size_t image_bytes() const { return upload_end - counters; }          // of what is uploaded, in pinned memory
@@ -249,12 +249,11 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.totals = take(64);
   f.end = o;
   RowGeo g;
-  f.rows_rows = f.rows_first = f.rows_plane = f.rows_info = f.rows_cnt = f.rows_start = f.rows_sum = f.rows_tot = f.rows_dyn = 0;
+  f.rows_rows = f.rows_first = f.rows_info = f.rows_cnt = f.rows_start = f.rows_sum = f.rows_tot = f.rows_dyn = 0;
   if (row_geo(c, g)) {
     o = shared;
     f.rows_rows = take((size_t)g.n_planes * 4);
     f.rows_first = take((size_t)g.n_planes * 4);
-    f.rows_plane = take((size_t)g.n_planes * g.ek * 4);
     f.rows_info = take((size_t)g.n_planes * g.ek * kRowInfoBytes);
     f.rows_cnt = take((size_t)g.n_shapes * 8);
     f.rows_start = take((size_t)g.n_shapes * 8);
@@ -1354,7 +1353,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   size_t needed = 0;
   bool merged = false;
   if (by_rows) {
-    const RowBufs rb{(uint32_t*)(base + f.rows_rows), (uint32_t*)(base + f.rows_first), (uint32_t*)(base + f.rows_plane), base + f.rows_info, (uint32_t*)(base + f.rows_cnt), (uint32_t*)(base + f.rows_start),
+    const RowBufs rb{(uint32_t*)(base + f.rows_rows), (uint32_t*)(base + f.rows_first), base + f.rows_info, (uint32_t*)(base + f.rows_cnt), (uint32_t*)(base + f.rows_start),
                      base + f.rows_sum, (uint32_t*)(base + f.rows_tot), base + f.rows_dyn, scratch_bytes - f.rows_dyn};
     launch_rows(row_g, rb, tab->d_cost, tab->d_arg, d_fitmap, (const uint32_t*)((char*)d_P + offsetof(DevParams, sizes)), st);
     HIP_TRY(hipGetLastError());

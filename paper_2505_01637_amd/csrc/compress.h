@@ -178,7 +178,7 @@ struct RowGeo {
 };
 enum : uint32_t { kLongTotal = 0, kHeadsTotal = 1, kRowsTotal = 2, kBoxesTotal = 3, kBoxesFirst = 4, kRowTotals = 5 };     // (the first two are written as one)
 struct RowBufs {
-  uint32_t *rows, *first, *plane_of;       // per plane: rows kept, index of its first; per kept row: its plane
+  uint32_t *rows, *first;                  // per plane: rows kept, index of its first
   void* info;                              // per kept row: kRowInfoBytes
   uint32_t *cnt, *start;                   // per list and shape: boxes, boxes before
   void* sum;                               // rows_sum_bytes

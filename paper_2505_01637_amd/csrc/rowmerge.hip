@@ -193,12 +193,14 @@ struct alignas(64) RowInfo {
 static_assert(sizeof(RowInfo) == 64, "kRowInfoBytes");
 
 __global__ __launch_bounds__(256) void row_info_kernel(const RowGeo g, const RowBufs B) {
-  const uint32_t row = blockIdx.x * 256u + threadIdx.x;
-  if (row >= B.tot[kRowsTotal]) return;
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
   RowInfo r;
-  r.plane = B.plane_of[row];
-  r.k = row - B.first[r.plane];
+  r.plane = i / g.ek;
+  r.k = i - r.plane * g.ek;
+  if (r.plane >= g.n_planes) return;
   r.kept = B.rows[r.plane];
+  if (r.k >= r.kept) return;
+  const uint32_t row = B.first[r.plane] + r.k;
   r.w = r.plane & (g.nw - 1u);
   const uint32_t bm = r.plane >> g.lg_nw, b = bm / g.em, m = bm - b * g.em;
   r.b_m = b << 16 | m;
@@ -1152,20 +1154,16 @@ __global__ __launch_bounds__(256) void row_emit_kernel(const RowGeo g, const Row
 // workgroups, each with a stretch of whole tiles; first the stretches' sums, then every workgroup adds up those before its own.
 constexpr uint32_t kSumGroups = 1024, kSumTile = 2048;
 
-struct SumCounts {                   // n 32-bit numbers; owner, if there is one: a number's index as often as it says
+struct SumCounts {                   // n 32-bit numbers
   typedef uint32_t V;
   const uint32_t* p;
   uint32_t* to;
   uint32_t n;
-  uint32_t* owner;
   __device__ __forceinline__ uint32_t items() const { return n; }
   __device__ __forceinline__ void open() {}
   __device__ __forceinline__ V one(uint32_t i) const { return p[i]; }
   __device__ __forceinline__ void two(uint32_t i, V& x, V& y) const { const uint2 v = *(const uint2*)(p + i); x = v.x; y = v.y; }
-  __device__ __forceinline__ void put(uint32_t i, V before, V x) const {
-    to[i] = before;
-    if (owner) for (uint32_t c = 0; c < x; c++) owner[before + c] = i;
-  }
+  __device__ __forceinline__ void put(uint32_t i, V before, V) const { to[i] = before; }
 };
 struct SumHeads {                    // the bits of N and of T (in the high half) side by side
   typedef u64 V;
@@ -1290,7 +1288,7 @@ void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const 
   const dim3 wg(256);
   const uint64_t words = (uint64_t)g.n_shapes << g.lg_nw;
   hipLaunchKernelGGL(row_count_kernel, dim3((g.n_planes + 255) / 256), wg, 0, st, g, fit, B.rows);
-  launch_sum(SumCounts{B.rows, B.first, g.n_planes, B.plane_of}, g.n_planes, B.sum, B.tot + kRowsTotal, st);
+  launch_sum(SumCounts{B.rows, B.first, g.n_planes}, g.n_planes, B.sum, B.tot + kRowsTotal, st);
   hipLaunchKernelGGL(row_info_kernel, dim3((uint32_t)(((uint64_t)g.n_planes * g.ek + 255) / 256)), wg, 0, st, g, B);
   const uint64_t most_rows = (uint64_t)g.n_planes * g.ek * 8;      // (row_parts)
   const dim3 rows((uint32_t)((most_rows + 3) / 4 < kRowGroups ? (most_rows + 3) / 4 : kRowGroups));
@@ -1309,7 +1307,7 @@ void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const 
   void (*const inner[7])(const RowGeo&, const RowBufs&, const uint64_t*, const uint16_t*, dim3, hipStream_t) = {
       launch_inner<0>, launch_inner<1>, launch_inner<2>, launch_inner<3>, launch_inner<4>, launch_inner<5>, launch_inner<6>};
   inner[g.lv](g, B, cost, arg, rows, st);
-  launch_sum(SumCounts{B.cnt, B.start, 2 * g.n_shapes, nullptr}, 2 * (uint64_t)g.n_shapes, B.sum, B.tot + kBoxesTotal, st);
+  launch_sum(SumCounts{B.cnt, B.start, 2 * g.n_shapes}, 2 * (uint64_t)g.n_shapes, B.sum, B.tot + kBoxesTotal, st);
   hipLaunchKernelGGL(row_emit_kernel, rows, wg, 0, st, g, B, cost, arg, sizes);
 }
 
