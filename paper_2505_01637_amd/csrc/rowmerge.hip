@@ -287,6 +287,12 @@ __global__ __launch_bounds__(256) void row_heads_kernel(const RowGeo g, const Ro
   }
 }
 
+// Lane i gets lane i + d's value (any value where there is none).
+__device__ __forceinline__ u64 above64(u64 x, uint32_t d) {
+  const int from = (int)((threadIdx.x & 63u) + d);
+  return (u64)(uint32_t)__shfl((int)(uint32_t)(x >> 32), from, 64) << 32 | (uint32_t)__shfl((int)(uint32_t)x, from, 64);
+}
+
 // Heads of row 0 (the wave's) and of a row before it whose runs are equally long: the next head above them, if any, is
 // the same step in both rows.  Lane n has the words of step n; seen from the far end a step settles that where it has
 // heads (both), passes it on where it has none (a prefix computation over the lanes).
@@ -296,15 +302,12 @@ __device__ __forceinline__ u64 same_runs(u64 h, u64 h1, uint32_t en) {
   en = used ? 64u - (uint32_t)__builtin_clzll(used) : 0u;           // (no heads further on)
   u64 hit = lane < en ? both : ~0ull, pass = lane < en ? ~(h | h1) : 0ull;
   for (uint32_t d = 1; d < en; d <<= 1) {
-    const uint32_t from = lane + d;
-    u64 nh = (u64)(uint32_t)__shfl((int)(uint32_t)(hit >> 32), (int)from, 64) << 32 | (uint32_t)__shfl((int)(uint32_t)hit, (int)from, 64);
-    u64 np = (u64)(uint32_t)__shfl((int)(uint32_t)(pass >> 32), (int)from, 64) << 32 | (uint32_t)__shfl((int)(uint32_t)pass, (int)from, 64);
-    if (from >= 64u) { nh = ~0ull; np = 0; }
+    u64 nh = above64(hit, d), np = above64(pass, d);
+    if (lane + d >= 64u) { nh = ~0ull; np = 0; }
     hit |= pass & nh;
     pass &= np;
   }
-  u64 above = (u64)(uint32_t)__shfl((int)(uint32_t)(hit >> 32), (int)(lane + 1u), 64) << 32 | (uint32_t)__shfl((int)(uint32_t)hit, (int)(lane + 1u), 64);
-  u64 open = (u64)(uint32_t)__shfl((int)(uint32_t)(pass >> 32), (int)(lane + 1u), 64) << 32 | (uint32_t)__shfl((int)(uint32_t)pass, (int)(lane + 1u), 64);
+  u64 above = above64(hit, 1), open = above64(pass, 1);
   if (lane == 63u) { above = ~0ull; open = 0; }
   return both & (above | open);
 }
@@ -507,6 +510,73 @@ __global__ __launch_bounds__(256) void row_fold_b_m_kernel(const RowGeo g, const
       if (own[u]) Fb[at[u]] = fold[u] & same;
       same = ~(f[u] ^ f1[u]) & (~f[u] | same);
     }
+  }
+}
+
+// The same for chains longer than a wave: the lanes on 64 steps of a chain, `same` by a prefix computation over them.  A
+// lane per chain reads a place of its own with every load there, and there are few chains.  3 sizes along b, 4 along m and n,
+// all to 255 along k: row_fold_b_k_kernel 140 us, this 6, the solve 761 -> 574; all to 255 along m, 4 along k:
+// row_fold_b_m_kernel 99 us, this 9, the solve 656 -> 560.  (box by box 708 and 697)
+// f, f1: the folds of the lane's step; same: of the step behind the 64, then of their first.  Returns that of the step behind the lane's.
+__device__ __forceinline__ u64 same_behind(u64 f, u64 f1, u64& same) {
+  const uint32_t lane = threadIdx.x & 63u;
+  u64 hit = ~(f | f1), pass = f & f1;                               // `same` of a step is hit | pass & the next one's
+#pragma unroll
+  for (uint32_t d = 1; d < 64; d <<= 1) {
+    const u64 nh = above64(hit, d), np = above64(pass, d);
+    hit |= lane + d < 64u ? pass & nh : 0ull;
+    pass &= lane + d < 64u ? np : ~0ull;
+  }
+  const u64 nh = above64(hit, 1), np = above64(pass, 1), behind = lane < 63u ? nh | (np & same) : same;
+  same = lane64(hit, 0) | (lane64(pass, 0) & same);
+  return behind;
+}
+
+// Chains along k, for m or for b's first step: a wave per (plane, n).
+__global__ __launch_bounds__(256) void row_fold_long_k_kernel(const RowGeo g, const RowBufs B, uint32_t along_b) {
+  const uint32_t lane = threadIdx.x & 63u, i = first_row(), l = blockIdx.y;
+  const uint32_t p = i / g.en, n = i - p * g.en, step = along_b ? g.em * g.nw : g.nw;
+  if (p >= g.n_planes) return;
+  RowWords W;
+  if (!row_words(g, B, W)) return;
+  if (along_b ? p < step : (p >> g.lg_nw) % g.em == 0) return;      // (the first along the axis agrees with nothing)
+  const uint32_t K = B.rows[p], K1 = B.rows[p - step];
+  const size_t at0 = (size_t)B.first[p] * g.en + n, at1 = (size_t)B.first[p - step] * g.en + n;
+  const u64* __restrict__ H = l ? W.H[1] : W.H[0];
+  const u64* __restrict__ Fk = l ? W.Fk[1] : W.Fk[0];
+  const u64* Fm = l ? W.Fm[1] : W.Fm[0];
+  u64* F = along_b ? (l ? W.Fb[1] : W.Fb[0]) : (l ? W.Fm[1] : W.Fm[0]);
+  const bool not_m = along_b && g.em > 1;
+  const u64 gone = gone_word(n);
+  u64 same = ~0ull;
+  for (int k0 = (int)(((K > K1 ? K : K1) - 1u) & ~63u); k0 >= 0; k0 -= 64) {
+    const uint32_t k = (uint32_t)k0 + lane;     // (rows that are not there: another one is read and not used)
+    const size_t j = at0 + (size_t)(k < K ? k : K - 1u) * g.en, j1 = at1 + (size_t)(k < K1 ? k : K1 - 1u) * g.en;
+    const u64 own = Fk[j], other = Fk[j1];
+    u64 left = F[j] & H[j] & H[j1];
+    if (not_m) left &= ~(Fm[j] | Fm[j1]);
+    const u64 f = k < K ? own : gone, f1 = k < K1 ? other : gone, behind = same_behind(f, f1, same);
+    if (k < K) F[j] = k < K1 ? left & ~f & ~f1 & behind : 0ull;
+  }
+}
+
+// Chains along m, for b's second step: a wave per (b, place, k, n).
+__global__ __launch_bounds__(256) void row_fold_long_m_kernel(const RowGeo g, const RowBufs B) {
+  const uint32_t lane = threadIdx.x & 63u, i = first_row(), l = blockIdx.y;
+  const uint32_t n = i % g.en, q = i / g.en, k = q % g.ek, bw = q / g.ek, w = bw & (g.nw - 1u), b = bw >> g.lg_nw;
+  if (b >= g.eb || b == 0) return;
+  RowWords W;
+  if (!row_words(g, B, W)) return;
+  const u64* __restrict__ Fm = l ? W.Fm[1] : W.Fm[0];
+  u64* __restrict__ Fb = l ? W.Fb[1] : W.Fb[0];
+  u64 same = ~0ull;
+  for (int m0 = (int)((g.em - 1u) & ~63u); m0 >= 0; m0 -= 64) {
+    const uint32_t m = (uint32_t)m0 + lane, p = ((b * g.em + (m < g.em ? m : 0u)) << g.lg_nw) + w, p1 = p - g.em * g.nw;
+    const uint32_t K = B.rows[p], K1 = B.rows[p1];
+    const bool own = m < g.em && k < K, other = m < g.em && k < K1;
+    const size_t at = ((size_t)B.first[p] + (k < K ? k : K - 1u)) * g.en + n, at1 = ((size_t)B.first[p1] + (k < K1 ? k : K1 - 1u)) * g.en + n;
+    const u64 f = Fm[at], f1 = Fm[at1], fold = Fb[at], behind = same_behind(own ? f : 0ull, other ? f1 : 0ull, same);
+    if (own) Fb[at] = fold & behind;
   }
 }
 
@@ -1296,10 +1366,19 @@ void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const 
   if (g.eb > 1) hipLaunchKernelGGL(row_agree_kernel<4>, rows, wg, 0, st, g, B, cost, arg, sizes);
   else hipLaunchKernelGGL(row_agree_kernel<3>, rows, wg, 0, st, g, B, cost, arg, sizes);
   const dim3 per_plane((uint32_t)(((uint64_t)g.n_planes * g.en + 255) / 256), 2);
-  if (g.em > 1) hipLaunchKernelGGL(row_fold_m_kernel, per_plane, wg, 0, st, g, B);
+  // (a lane holds a step of a chain in same_behind)
+  const bool long_k = g.ek > 64, long_m = g.em > 64;
+  const dim3 per_chain((uint32_t)(((uint64_t)g.n_planes * g.en + 3) / 4), 2);
+  if (g.em > 1) {
+    if (long_k) hipLaunchKernelGGL(row_fold_long_k_kernel, per_chain, wg, 0, st, g, B, 0u);
+    else hipLaunchKernelGGL(row_fold_m_kernel, per_plane, wg, 0, st, g, B);
+  }
   if (g.eb > 1) {
-    hipLaunchKernelGGL(row_fold_b_k_kernel, per_plane, wg, 0, st, g, B);
-    hipLaunchKernelGGL(row_fold_b_m_kernel, dim3((uint32_t)(((uint64_t)g.eb * g.nw * g.ek * g.en + 255) / 256), 2), wg, 0, st, g, B);
+    const uint64_t chains = (uint64_t)g.eb * g.nw * g.ek * g.en;
+    if (long_k) hipLaunchKernelGGL(row_fold_long_k_kernel, per_chain, wg, 0, st, g, B, 1u);
+    else hipLaunchKernelGGL(row_fold_b_k_kernel, per_plane, wg, 0, st, g, B);
+    if (long_m) hipLaunchKernelGGL(row_fold_long_m_kernel, dim3((uint32_t)((chains + 3) / 4), 2), wg, 0, st, g, B);
+    else hipLaunchKernelGGL(row_fold_b_m_kernel, dim3((uint32_t)((chains + 255) / 256), 2), wg, 0, st, g, B);
   }
   hipLaunchKernelGGL(row_left_kernel, dim3((uint32_t)((words + 255) / 256 < kRowGroups ? (words + 255) / 256 : kRowGroups)), wg, 0, st, g, B);
   launch_sum(SumHeads{g, B, nullptr, nullptr, nullptr, 0}, 2 * words, B.sum, B.tot + kLongTotal, st);

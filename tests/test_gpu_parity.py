@@ -417,18 +417,25 @@ def row_merge_case(case):
         t["load_coef"][1][0][0], t["loop_overhead"] = 3, 0
         t["microkernels"] = [(W.MK_SCALAR_FMA, 1, 2)]
         r = list(range(1, 65))
-        lat.update(sizes={"nk": [[1], [1, 2], r, r], "bnk": [[1, 2, 3], [1, 2], r[:40], r[:50]]}[tail],
-                   layout_coord=[0, 0, 0, 0, 0] if tail == "nk" else [1, 0, 1, 0, 0])
+        lat.update(sizes={"nk": [[1], [1, 2], r, r], "bnk": [[1, 2, 3], [1, 2], r[:40], r[:50]], "k": [[1, 2], [1, 2], list(range(1, 201)), [1, 2]],
+                          "m": [[1, 2], list(range(1, 201)), [1, 2], [1, 2]]}[tail],
+                   layout_coord=[1, 0, 1, 0, 0] if tail == "bnk" else [0, 0, 0, 0, 0])
+    elif kind == "chains":                              # chains of 64 to 255 steps along k and m, the last 64 of them whole or not
+        axis, n = tail[0], int(tail[1:])
+        lat.update(sizes=[[1, 2, 4], [1, 2, 3], [1, 2, 3], [1, 2]], layout_coord=[0, 1, 0, 0, 0])
+        lat["sizes"]["bmkn".index(axis)] = list(range(1, n + 1))
     elif kind == "b":                                   # long along b, chains along k and m before it
         lat.update(sizes=[list(range(1, 41)), [1, 2, 4], [1, 2, 3, 6], [1, 2, 8]])
     return dict(cfg, name="rows-" + case)
 
 
 @pytest.mark.parametrize("case", ["steps-1", "steps-2", "steps-63", "steps-64", "steps-65", "bits-0", "bits-1", "bits-2", "bits-2d", "bits-3d", "bits-4d",
-                                  "packed-4", "packed-5", "packed-6", "long-km", "long-bk", "long-kn", "full-fused", "full-chain", "b"])
+                                  "packed-4", "packed-5", "packed-6", "long-km", "long-bk", "long-kn", "full-fused", "full-chain", "b",
+                                  "chains-k64", "chains-k65", "chains-k129", "chains-k255", "chains-m64", "chains-m65", "chains-m128", "chains-m255", "regular-k", "regular-m"])
 def test_parity_boxes_merged_by_rows(case):
     """The merge word by word: rows of 1 to 64 steps (65: the general one), 0 to 6 bits below the level axes (a level axis
-    then lies inside a word, over two words or above), chains longer than a wave, batches without an empty word."""
+    then lies inside a word, over two words or above), chains longer than a wave along any size axis, with implementations and
+    boxes as long as the axis, batches without an empty word."""
     compare_config(row_merge_case(case))
 
 
