@@ -167,12 +167,18 @@ size_t bind_entries(const Compiled& c) {
 
 // Whether the table's boxes are merged word by word (rowmerge.hip) and its geometry there: the fit map comes from the
 // plan, the size axes are merged first, there are four memory levels, a shape is one to kRowShapeWords mask words, and a
-// row along n has at most 64 steps.
+// row has at most 64 steps.  Rows lie along n, or along the first of k, m and b that has more than one step if those before it
+// have not: a wave per row of one step is mostly waiting (b, m and k of 64, 64 and 16 sizes and one along n: 743 to 774 us
+// box by box, 899 by words in rows of one, 675 in rows of 16).  Tables of four levels with 1 to 64 steps along n, everything or
+// little fitting, 64 to 450 M cells, up to 255 sizes along k, m and b: the whole solve is 1.0 to 1.9 times as fast by words.
 bool row_geo(const Compiled& c, RowGeo& g) {
   const DevParams& P = c.P;
   memset(&g, 0, sizeof g);
   if (P.gather || P.NL != 4 || P.log2V > 6 || c.n_specs >= (1ull << 31) || P.G % 64 || P.G / 64 > kRowShapeWords || P.nsz[3] > 64) return false;
-  g.en = P.nsz[3]; g.ek = P.nsz[2]; g.em = P.nsz[1]; g.eb = P.nsz[0];
+  uint32_t turn = 0;
+  while (turn < 3 && P.nsz[3 - turn] == 1 && P.nsz[2 - turn] <= 64) turn++;
+  for (uint32_t d = 0; d < 4; d++) g.axis[d] = (d + 4 - turn) & 3;
+  g.en = P.nsz[g.axis[3]]; g.ek = P.nsz[g.axis[2]]; g.em = P.nsz[g.axis[1]]; g.eb = P.nsz[g.axis[0]];
   g.G = P.G; g.nw = P.G / 64;
   while ((1u << g.lg_nw) < g.nw) g.lg_nw++;
   g.n_shapes = c.n_shapes;

@@ -166,10 +166,12 @@ hipError_t launch_lookup(const Geo& g, const LookupList lists[2], const void* po
 constexpr uint32_t kRowLevels = 5;         // level axes at most
 constexpr uint32_t kRowInfoBytes = 64;
 constexpr uint32_t kRowShapeWords = 256;   // words of a shape at most
-// The axes n, k, m, b; inside a shape the level axes, four values each (level axis i, in merge order, is the bits
+// The size axes n, k, m, b, or k, m, b, n where there is one size along n (it then is the axis called b here, of one step; an
+// axis of one step is never merged along, so that the order is the same), and so on; inside a shape the level axes, four values each (level axis i, in merge order, is the bits
 // [lv + 2 i, lv + 2 i + 2) of a cell's place), then those of layouts and dtypes (fields of the lv bits below).
 struct RowGeo {
   uint32_t en, ek, em, eb;                 // en: at most 64
+  uint32_t axis[4];                        // the coordinate axes that b, m, k, n are here
   uint32_t G, nw, lg_nw;                   // cells and 64-cell words of a shape
   uint32_t n_shapes, n_planes;             // planes: (b, m, word of the shape)
   uint32_t lv, n_levels, n_inner, level_axis;      // n_inner = n_levels + lv; level_axis: coordinate axis of level axis 0 (the others lie before it)

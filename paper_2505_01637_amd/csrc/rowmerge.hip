@@ -132,6 +132,9 @@ __device__ __forceinline__ bool row_words(const RowGeo& g, const RowBufs& B, Row
   return lists + row_agree_bytes(g, n_rows) <= B.room;
 }
 
+// Sizes along axis d of b, m, k, n.
+__device__ __forceinline__ const uint32_t* axis_sizes(const RowGeo& g, const uint32_t* __restrict__ sizes, uint32_t d) { return sizes + g.axis[d] * kMaxSizes; }
+
 // Words of a row that is not kept: every cell (INF, NONE), one run along n, folded into the row before it on k.
 __device__ __forceinline__ u64 gone_word(uint32_t n) { return n == 0 ? ~0ull : 0ull; }
 
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(256) void row_heads_kernel(const RowGeo g, const Ro
   const uint32_t lane = threadIdx.x & 63u, n_rows = B.tot[kRowsTotal];
   RowWords W;
   if (!row_words(g, B, W)) return;
-  const uint32_t size_n = lane < g.en ? sizes[3 * kMaxSizes + lane] : 1u;
+  const uint32_t size_n = lane < g.en ? axis_sizes(g, sizes, 3)[lane] : 1u;
   for (uint32_t row = first_row(); row < n_rows; row += gridDim.x * 4u) {
     const WaveRow r(B, row);
     const u64 words = lane < g.en ? fit[((size_t)(r.shape0 + lane) << g.lg_nw) + r.w] : 0ull;
@@ -329,8 +332,9 @@ __global__ __launch_bounds__(256) void row_agree_kernel(const RowGeo g, const Ro
     const uint32_t back[4] = {0, g.en, g.ek * g.en, g.em * g.ek * g.en};
     const uint32_t before[4] = {row, row - 1u, r.m_before, r.b_before};
     const bool has[4] = {true, r.k > 0, r.m > 0, r.b > 0};
-    const uint32_t sz[4] = {1u, sizes[2 * kMaxSizes + r.k], sizes[kMaxSizes + r.m], sizes[r.b]};
-    const uint32_t sz1[4] = {1u, r.k ? sizes[2 * kMaxSizes + r.k - 1] : 1u, r.m ? sizes[kMaxSizes + r.m - 1] : 1u, r.b ? sizes[r.b - 1] : 1u};
+    const uint32_t *size_k = axis_sizes(g, sizes, 2) + r.k, *size_m = axis_sizes(g, sizes, 1) + r.m, *size_b = axis_sizes(g, sizes, 0) + r.b;
+    const uint32_t sz[4] = {1u, size_k[0], size_m[0], size_b[0]};
+    const uint32_t sz1[4] = {1u, r.k ? size_k[-1] : 1u, r.m ? size_m[-1] : 1u, r.b ? size_b[-1] : 1u};
     const size_t at = (size_t)r.row * g.en + lane;
     u64 h[2], cand[2][4];
 #pragma unroll
@@ -668,7 +672,7 @@ __global__ __launch_bounds__(256) void row_extent_kernel(const RowGeo g, const R
       todo &= todo - 1;
       const u64 tn = lane64(t, n);
       const uint32_t at_rank = (uint32_t)__builtin_amdgcn_readlane((int)rank, (int)n) + below(tn);
-      uint32_t e = 0x01010101u;                                   // b, m, k, n, a byte each
+      uint32_t e = 0x01010101u;                                   // a byte per size axis, in the coordinates' order
       const bool go_k = (has_k >> n) & 1ull, go_m = (has_m >> n) & 1ull, go_b = (has_b >> n) & 1ull;
       const u64 on_k = go_k ? word_k(2u + lane, n) : 0ull, on_m = go_m ? word_m(2u + lane, n) : 0ull, on_b = go_b ? word_b(2u + lane, n) : 0ull;
       if ((has_n >> n) & 1ull) {
@@ -677,13 +681,13 @@ __global__ __launch_bounds__(256) void row_extent_kernel(const RowGeo g, const R
           const u64 ends = __ballot(lane > n && ((h & cur) != 0 || lane >= g.en));
           const uint32_t c = ends ? (uint32_t)__builtin_ctzll(ends) : g.en;      // (64 steps: no lane is left to end the list)
           const u64 gone = c < g.en ? cur & lane64(h, c) : cur;
-          if (in_mask(gone)) e += (c - n - 1u) << 24;
+          if (in_mask(gone)) e += (c - n - 1u) << (8u * g.axis[3]);
           cur &= ~gone;
         }
       }
-      if (go_k) walk(lane64(long_k, n), n, 16, e, on_k, word_k);
-      if (go_m) walk(lane64(long_m, n), n, 8, e, on_m, word_m);
-      if (go_b) walk(lane64(long_b, n), n, 0, e, on_b, word_b);
+      if (go_k) walk(lane64(long_k, n), n, 8u * g.axis[2], e, on_k, word_k);
+      if (go_m) walk(lane64(long_m, n), n, 8u * g.axis[1], e, on_m, word_m);
+      if (go_b) walk(lane64(long_b, n), n, 8u * g.axis[0], e, on_b, word_b);
       if (in_mask(tn)) W.ext[at_rank] = e;
     }
   }
@@ -1173,8 +1177,8 @@ __global__ __launch_bounds__(256) void row_emit_kernel(const RowGeo g, const Row
     uint4* flen = (uint4*)p; p += up256(nf * 16);
     uint64_t* fv0 = (uint64_t*)p; p += up256(nf * 8);
     uint64_t* fv1 = (uint64_t*)p;
-    uint64_t vol = (uint64_t)sizes[r.b] * sizes[kMaxSizes + r.m] * sizes[2 * kMaxSizes + r.k];
-    const uint32_t size_n = lane < g.en ? sizes[3 * kMaxSizes + lane] : 1u;
+    const uint64_t vol = (uint64_t)axis_sizes(g, sizes, 0)[r.b] * axis_sizes(g, sizes, 1)[r.m] * axis_sizes(g, sizes, 2)[r.k];
+    const uint32_t size_n = lane < g.en ? axis_sizes(g, sizes, 3)[lane] : 1u;
     for (uint32_t i0 = part * 64u; i0 < total; i0 += parts * 64u) {
       const uint32_t box = i0 + lane < total ? i0 + lane : total - 1u;
       const uint32_t n = lane_with(excl, box), nth = box - (uint32_t)__shfl((int)excl, (int)n, 64);

@@ -420,6 +420,15 @@ def row_merge_case(case):
         lat.update(sizes={"nk": [[1], [1, 2], r, r], "bnk": [[1, 2, 3], [1, 2], r[:40], r[:50]], "k": [[1, 2], [1, 2], list(range(1, 201)), [1, 2]],
                           "m": [[1, 2], list(range(1, 201)), [1, 2], [1, 2]]}[tail],
                    layout_coord=[1, 0, 1, 0, 0] if tail == "bnk" else [0, 0, 0, 0, 0])
+    elif kind == "turn":                                # one size along n, or along n and k, ...: rows along the next axis of up to 64 sizes
+        r = list(range(1, 256))
+        lat.update(sizes={"k": [[1, 2, 4], [1, 2, 3], [1, 2, 4, 8, 12], [1]], "k64": [[1, 3], [1, 2], r[:64], [1]], "k70": [[1, 2], [1, 2, 3], r[:70], [1]],
+                          "m": [[1, 2, 4], [1, 2, 3, 8], [1], [1]], "m70": [[1, 2, 3], r[:70], [1], [1]], "b": [[1, 2, 4, 8], [1], [1], [1]],
+                          "b255": [r, [1], [1], [1]], "one": [[1], [1], [1], [1]], "fused": [[1], [1, 2, 4, 8], [1, 2, 4, 8], [1]]}[tail])
+        if tail == "fused":
+            cfg = W.config(5, max_size=8)
+            for _, x, _ in cfg["lattices"]:
+                x["sizes"][3] = [1]
     elif kind == "chains":                              # chains of 64 to 255 steps along k and m, the last 64 of them whole or not
         axis, n = tail[0], int(tail[1:])
         lat.update(sizes=[[1, 2, 4], [1, 2, 3], [1, 2, 3], [1, 2]], layout_coord=[0, 1, 0, 0, 0])
@@ -431,11 +440,12 @@ def row_merge_case(case):
 
 @pytest.mark.parametrize("case", ["steps-1", "steps-2", "steps-63", "steps-64", "steps-65", "bits-0", "bits-1", "bits-2", "bits-2d", "bits-3d", "bits-4d",
                                   "packed-4", "packed-5", "packed-6", "long-km", "long-bk", "long-kn", "full-fused", "full-chain", "b",
-                                  "chains-k64", "chains-k65", "chains-k129", "chains-k255", "chains-m64", "chains-m65", "chains-m128", "chains-m255", "regular-k", "regular-m"])
+                                  "chains-k64", "chains-k65", "chains-k129", "chains-k255", "chains-m64", "chains-m65", "chains-m128", "chains-m255", "regular-k", "regular-m",
+                                  "turn-k", "turn-k64", "turn-k70", "turn-m", "turn-m70", "turn-b", "turn-b255", "turn-one", "turn-fused"])
 def test_parity_boxes_merged_by_rows(case):
     """The merge word by word: rows of 1 to 64 steps (65: the general one), 0 to 6 bits below the level axes (a level axis
     then lies inside a word, over two words or above), chains longer than a wave along any size axis, with implementations and
-    boxes as long as the axis, batches without an empty word."""
+    boxes as long as the axis, rows along another axis where there is one size along n, batches without an empty word."""
     compare_config(row_merge_case(case))
 
 
