@@ -1708,9 +1708,14 @@ static void launch_items(const DevParams* P, const DevParams& h, const FillGeom&
   FillLds L;
   const uint32_t lds = carve_fill(nullptr, g, h.moves != 0, L);
   const ShapeRec* recs = (const ShapeRec*)B.recs;
-  if (h.moves) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, true>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
-  else if (h.nlay) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
-  else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, false, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+  if (h.moves) {
+    if constexpr (T < 1024)       // (more threads are slower with Move Specs, and never asked for: below)
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, true>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+  } else if (h.nlay) {
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+  } else {
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, false, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+  }
 }
 
 // The bundles of one dependency level (starts = nullptr: every item is a bundle of its own).
