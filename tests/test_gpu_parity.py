@@ -242,9 +242,55 @@ def test_compressed_query_one_box_and_long_axis():
     cfg = {"name": "255-sizes", "target": base["target"], "lattices": [("M", lat, [])]}
     _, got, want = compare_config(cfg)          # lines of four mask words; the box lists as well
     check_compressed_queries(got["M"], want["M"], 10**9, seed=1)
-    # the second merge axis longer than a mask word (its pass then runs on boxes)
+    # an axis of more sizes than a mask word has cells, merged behind another
     lat = W._lattice(W.KIND_MATMUL_ACCUM, [[1], [1, 2], list(range(1, 101)), [1, 2, 4]])
     compare_config({"name": "100-on-k", "target": base["target"], "lattices": [("M", lat, [])]})
+
+
+@pytest.mark.parametrize("number,counts", [(2, (2, 100, 65)), (2, (3, 64, 130)), (4, (3, 4, 66)), (4, (64, 64, 65))])
+def test_parity_more_than_64_sizes_along_n(number, counts):
+    """Four memory levels merged box by box: lines of whole words with the second axis on the cells (64 sizes and less) or on
+    boxes (100), 8 words a wave and, from 2^21 words on (136 M cells), 64."""
+    cfg = W.config(number)
+    cfg["lattices"][0][1]["sizes"] = [[1]] + [list(range(1, n + 1)) for n in counts]
+    compare_config(dict(cfg, name="more-than-64"), scratch_bytes=8 << 30 if counts[0] == 64 else None)
+
+
+def test_long_questions_from_six_threads_at_once():
+    """Four calls' stretches take all of the library's threads for them: the others go through alone, 32,768 Specs at a
+    time.  The calls start together, with arrays made before, and take longer than a thread needs to get there.  Every answer
+    against the dense table."""
+    import ctypes as C
+    import threading
+    B = _binding()
+    _, got = B.solve_config(W.config(4, max_size=8))
+    tab = got["M"]
+    cost, arg = tab.dense()
+    ext = tab.extents
+    n_threads, turns, bad = 6, 8, []
+    start = threading.Barrier(n_threads)
+
+    def ask(seed, points, lin):
+        gc, ga = np.empty(len(lin), dtype=np.uint64), np.empty(len(lin), dtype=np.uint16)
+        args = (tab._h, C.c_void_p(points.ctypes.data), C.c_size_t(len(lin)), C.c_void_p(gc.ctypes.data), C.c_void_p(ga.ctypes.data))
+        for turn in range(turns):
+            fn = B.lib().mrl_query_compressed if turn % 2 else B.lib().mrl_query
+            gc[:], ga[:] = 1, 1
+            start.wait(60)
+            if fn(*args) != 0 or not (np.array_equal(gc, cost[lin]) and np.array_equal(ga, arg[lin])):
+                bad.append((seed, turn))
+
+    threads = []
+    for seed in range(n_threads):
+        lin = np.random.default_rng(seed).integers(0, len(cost), size=400_003 + 7 * seed)
+        points = np.zeros((len(lin), B.MAX_DIMS), dtype=np.uint32)
+        points[:, :len(ext)] = np.stack(np.unravel_index(lin, ext), axis=1)
+        threads.append(threading.Thread(target=ask, args=(seed, points, lin), daemon=True))
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join(100)
+    assert not any(th.is_alive() for th in threads) and not bad, bad
 
 
 @pytest.mark.parametrize("number,counts", [(1, (1, 1, 3)), (1, (5, 7, 65)), (1, (3, 3, 8)), (7, (1, 2, 3)), (7, (3, 5, 4))])
@@ -451,8 +497,9 @@ def test_parity_boxes_merged_by_rows(case):
 
 @pytest.mark.parametrize("case", ["steps-64", "full-fused", "long-kn"])
 def test_boxes_merged_one_by_one_where_the_rows_do_not_fit(case):
-    """With less scratch than the merge word by word uses, the boxes are merged one by one if that is enough, and the
-    call is refused if not; both give the same lists."""
+    """With less scratch than the merge word by word uses, the boxes are merged one by one if that is enough (the last
+    case, of one box), and the call is refused if not (the first two: their many boxes take more than their words).  Tables
+    with implementations whose boxes take less: the test behind this one."""
     B = _binding()
     cfg = row_merge_case(case)
     target, tabs = B.solve_config(cfg)
