@@ -184,11 +184,12 @@ bool row_geo(const Compiled& c, RowGeo& g) {
   g.n_shapes = c.n_shapes;
   g.n_planes = g.eb * g.em * g.nw;
   g.lv = P.log2V; g.ndt = P.ndt;
-  g.n_levels = P.nlv; g.n_inner = P.nlv + P.log2V; g.level_axis = 3 + P.nlv;
+  g.n_levels = g.n_inner = P.nlv; g.level_axis = 3 + P.nlv;
   for (uint32_t a = 4 + P.nlv; a < c.geo.ndim; a++) {
     uint32_t bit = 0;
     while ((1u << bit) < c.geo.stride[a]) bit++;
     g.var_first |= 1u << bit;
+    g.n_inner++;
     if (c.geo.ext[a] == 4) g.var_two |= 1u << bit;
     g.var_axis[bit] = a;
   }

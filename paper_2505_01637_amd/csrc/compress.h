@@ -174,7 +174,7 @@ struct RowGeo {
   uint32_t axis[4];                        // the coordinate axes that b, m, k, n are here
   uint32_t G, nw, lg_nw;                   // cells and 64-cell words of a shape
   uint32_t n_shapes, n_planes;             // planes: (b, m, word of the shape)
-  uint32_t lv, n_levels, n_inner, level_axis;      // n_inner = n_levels + lv; level_axis: coordinate axis of level axis 0 (the others lie before it)
+  uint32_t lv, n_levels, n_inner, level_axis;      // n_inner: axes inside a shape, n_levels and a field each; level_axis: coordinate axis of level axis 0 (the others lie before it)
   uint32_t var_first, var_two, ndt;        // bits at which a layout or dtype field starts; which are two bits wide; dtype bits (the lowest, merged last)
   uint32_t var_axis[6];                    // coordinate axis of the field that starts at a bit
 };

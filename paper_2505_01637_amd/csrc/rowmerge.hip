@@ -715,7 +715,10 @@ __device__ __forceinline__ u64 not_last(uint32_t b, bool two) {
 
 // Where `agree` has the words of an axis: level axis q, or the field that starts at bit b.
 __device__ __forceinline__ u64* agree_level(const RowGeo& g, const RowWords& W, size_t both, uint32_t q) { return W.agree + both * q; }
-__device__ __forceinline__ u64* agree_field(const RowGeo& g, const RowWords& W, size_t both, uint32_t b) { return W.agree + both * (g.n_levels + b); }
+__device__ __forceinline__ bool field_at(const RowGeo& g, uint32_t b) { return (g.var_first >> b) & 1u; }
+__device__ __forceinline__ u64* agree_field(const RowGeo& g, const RowWords& W, size_t both, uint32_t b) {
+  return W.agree + both * (g.n_levels + (uint32_t)__popc(g.var_first & ((1u << b) - 1u)));
+}
 __device__ __forceinline__ size_t agree_stride(const RowGeo& g, uint32_t n_rows) { return 2 * (size_t)n_rows * g.en; }
 
 // Level axis q (in merge order) is the bits [LV + 2 q, LV + 2 q + 2) of a cell's place in the shape: inside a word, or the
@@ -754,7 +757,7 @@ __device__ __forceinline__ void row_inner(const RowGeo& g, const RowBufs& B, con
   }
 #pragma unroll
   for (int b = 0; b < LV; b++)
-    var[b] = (g.var_first >> b) & 1u ? T & T >> (1 << b) & ~(N ^ N >> (1 << b)) & not_last(b, (g.var_two >> b) & 1u) : 0ull;
+    var[b] = field_at(g, b) ? T & T >> (1 << b) & ~(N ^ N >> (1 << b)) & not_last(b, (g.var_two >> b) & 1u) : 0ull;
 
   // ---- values, the lanes on a word's cells ----
   u64 pairs = 0;
@@ -856,7 +859,7 @@ __device__ __forceinline__ void row_inner(const RowGeo& g, const RowBufs& B, con
 #pragma unroll
     for (int q = 0; q < kLevels; q++) if ((uint32_t)q < g.n_levels) agree_level(g, W, both, q)[at] = lev[q];
 #pragma unroll
-    for (int b = 0; b < LV; b++) agree_field(g, W, both, b)[at] = var[b];
+    for (int b = 0; b < LV; b++) if (field_at(g, b)) agree_field(g, W, both, b)[at] = var[b];
   }
 }
 
@@ -953,7 +956,7 @@ __device__ __forceinline__ void shape_merge(const RowGeo& g, const RowBufs& B, c
 #pragma unroll
     for (int q = 0; q < kLevels; q++) lev[q] = on && (uint32_t)q < g.n_levels ? agree_level(g, W, both, q)[at] : 0ull;
 #pragma unroll
-    for (int b = 0; b < LV; b++) var[b] = on ? agree_field(g, W, both, b)[at] : 0ull;
+    for (int b = 0; b < LV; b++) var[b] = on && field_at(g, b) ? agree_field(g, W, both, b)[at] : 0ull;
 #pragma unroll
     for (int q = 0; q < kLevels; q++) {
       next[q] = next2[q] = prev[q] = kNoWord;
@@ -1032,7 +1035,7 @@ __device__ __forceinline__ void shape_merge(const RowGeo& g, const RowBufs& B, c
     for (int half = 0; half < 2; half++)
 #pragma unroll
       for (int b = 0; b < LV; b++) {
-        if (!((g.var_first >> b) & 1u) || (half == 0) != ((uint32_t)b >= g.ndt)) continue;
+        if (!field_at(g, b) || (half == 0) != ((uint32_t)b >= g.ndt)) continue;
         const bool four = (g.var_two >> b) & 1u;
         const u64 link = A & var[b] & A >> (1 << b);
         const u64 two = four ? link & link >> (1 << b) : 0ull, three = four ? two & link >> (2 << b) : 0ull;
@@ -1203,7 +1206,7 @@ __global__ __launch_bounds__(256) void row_emit_kernel(const RowGeo g, const Row
         if (q < g.n_levels) put(g.level_axis - q, (code >> (g.lv + 2 * q)) & 3u);
 #pragma unroll
       for (uint32_t b = 0; b < 6; b++)
-        if ((g.var_first >> b) & 1u) put(g.var_axis[b], (code >> b) & ((g.var_two >> b) & 1u ? 3u : 1u));
+        if (field_at(g, b)) put(g.var_axis[b], (code >> b) & ((g.var_two >> b) & 1u ? 3u : 1u));
       fcell[o] = cell;
       flen[o] = make_uint4(size_ext, L1, L2, L3);
       uint64_t v0 = v, v1 = 0;
