@@ -1378,169 +1378,169 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     }
   }
   if (!merged) {
-  if (scratch_bytes < f.least()) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
-  uint32_t a0 = c.merge_order[0];
-  for (uint32_t q = 0; q < g.ndim; q++) if (g.ext[c.merge_order[q]] > 1) { a0 = c.merge_order[q]; break; }
-  unsigned long long* maskL[2] = {(unsigned long long*)(base + f.maskD), (unsigned long long*)(base + f.maskC)};
-  uint32_t* prefL[2] = {(uint32_t*)(base + f.prefD), (uint32_t*)(base + f.prefC)};
-  uint32_t* tile_tmp = (uint32_t*)(base + f.tile_tmp);
-  uint32_t* d_tot = (uint32_t*)(base + f.totals);
-  auto axis_sizes = [&](uint32_t a) -> const uint32_t* { return a < 4 ? (const uint32_t*)((char*)d_P + offsetof(DevParams, sizes) + a * sizeof(uint32_t) * kMaxSizes) : nullptr; };
-  unsigned long long* lineL[2] = {(unsigned long long*)(base + f.lineD), (unsigned long long*)(base + f.lineC)};
-  launch_head_flags(g, a0, tab->d_cost, tab->d_arg, d_fitmap, axis_sizes(a0), maskL[0], maskL[1], lineL[0], lineL[1], st);
-  uint32_t a1 = 0;
-  const bool on_cells = second_on_cells(c, nullptr, &a1);
-  const unsigned long long* colL[2] = {nullptr, nullptr};
-  if (on_cells) launch_zero_words((unsigned long long*)(base + f.colD), (uint32_t)((f.colC - f.colD) / 8 + c.n_specs / g.ext[a1]), st);
-  // the two prefix sums side by side (each is one to three short kernels): the decisions' on the helper stream
-  HIP_TRY(hipEventRecord(aux->events[ev_used], st));
-  HIP_TRY(hipStreamWaitEvent(s2, aux->events[ev_used++], 0));
-  if (on_cells) {
-    // the pass on the second merge axis, on the cells: the box heads that remain go to a second mask
-    unsigned long long* m2[2] = {(unsigned long long*)(base + f.mask2D), (unsigned long long*)(base + f.mask2C)};
-    unsigned long long* cl[2] = {(unsigned long long*)(base + f.colD), (unsigned long long*)(base + f.colC)};
-    launch_second_axis(g, a0, a1, false, maskL[0], lineL[0], d_fitmap, tab->d_cost, tab->d_arg, axis_sizes(a1), m2[0], cl[0], s2);
-    launch_second_axis(g, a0, a1, true, maskL[1], lineL[1], d_fitmap, tab->d_cost, tab->d_arg, axis_sizes(a1), m2[1], cl[1], st);
-    for (int w = 0; w < 2; w++) { maskL[w] = m2[w]; colL[w] = cl[w]; }
-  }
-  scan_mask_words(maskL[0], f.n_words, (uint32_t*)(base + f.tile_tmp2), prefL[0], d_tot + 0, s2);
-  scan_mask_words(maskL[1], f.n_words, tile_tmp, prefL[1], d_tot + 1, st);
-  HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
-  HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
-  uint32_t h_tot[4] = {0, 0, 0, 0};
-  HIP_TRY(hipMemcpyAsync(h_tot, d_tot, 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+    if (scratch_bytes < f.least()) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
+    uint32_t a0 = c.merge_order[0];
+    for (uint32_t q = 0; q < g.ndim; q++) if (g.ext[c.merge_order[q]] > 1) { a0 = c.merge_order[q]; break; }
+    unsigned long long* maskL[2] = {(unsigned long long*)(base + f.maskD), (unsigned long long*)(base + f.maskC)};
+    uint32_t* prefL[2] = {(uint32_t*)(base + f.prefD), (uint32_t*)(base + f.prefC)};
+    uint32_t* tile_tmp = (uint32_t*)(base + f.tile_tmp);
+    uint32_t* d_tot = (uint32_t*)(base + f.totals);
+    auto axis_sizes = [&](uint32_t a) -> const uint32_t* { return a < 4 ? (const uint32_t*)((char*)d_P + offsetof(DevParams, sizes) + a * sizeof(uint32_t) * kMaxSizes) : nullptr; };
+    unsigned long long* lineL[2] = {(unsigned long long*)(base + f.lineD), (unsigned long long*)(base + f.lineC)};
+    launch_head_flags(g, a0, tab->d_cost, tab->d_arg, d_fitmap, axis_sizes(a0), maskL[0], maskL[1], lineL[0], lineL[1], st);
+    uint32_t a1 = 0;
+    const bool on_cells = second_on_cells(c, nullptr, &a1);
+    const unsigned long long* colL[2] = {nullptr, nullptr};
+    if (on_cells) launch_zero_words((unsigned long long*)(base + f.colD), (uint32_t)((f.colC - f.colD) / 8 + c.n_specs / g.ext[a1]), st);
+    // the two prefix sums side by side (each is one to three short kernels): the decisions' on the helper stream
+    HIP_TRY(hipEventRecord(aux->events[ev_used], st));
+    HIP_TRY(hipStreamWaitEvent(s2, aux->events[ev_used++], 0));
+    if (on_cells) {
+      // the pass on the second merge axis, on the cells: the box heads that remain go to a second mask
+      unsigned long long* m2[2] = {(unsigned long long*)(base + f.mask2D), (unsigned long long*)(base + f.mask2C)};
+      unsigned long long* cl[2] = {(unsigned long long*)(base + f.colD), (unsigned long long*)(base + f.colC)};
+      launch_second_axis(g, a0, a1, false, maskL[0], lineL[0], d_fitmap, tab->d_cost, tab->d_arg, axis_sizes(a1), m2[0], cl[0], s2);
+      launch_second_axis(g, a0, a1, true, maskL[1], lineL[1], d_fitmap, tab->d_cost, tab->d_arg, axis_sizes(a1), m2[1], cl[1], st);
+      for (int w = 0; w < 2; w++) { maskL[w] = m2[w]; colL[w] = cl[w]; }
+    }
+    scan_mask_words(maskL[0], f.n_words, (uint32_t*)(base + f.tile_tmp2), prefL[0], d_tot + 0, s2);
+    scan_mask_words(maskL[1], f.n_words, tile_tmp, prefL[1], d_tot + 1, st);
+    HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
+    HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
+    uint32_t h_tot[4] = {0, 0, 0, 0};
+    HIP_TRY(hipMemcpyAsync(h_tot, d_tot, 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
 
-  // The two lists are merged side by side, the decisions on the helper stream: most of the
-  // kernels are bound by latency, not bandwidth.  The host waits twice per list: for the number
-  // of live boxes after the first pass (it sizes the grids of the later ones) and for the final
-  // count (it places the final list); meanwhile the other list's stream has work queued.
-  // Work areas at the end of the buffer, the final lists grow from the front.
-  const uint64_t nbL[2] = {h_tot[0], h_tot[1]};
-  const size_t wbL[2] = {work_bytes(nbL[0]), work_bytes(nbL[1])};
-  size_t front = f.end;
-  needed = f.end + wbL[0] + wbL[1] + final_bytes(nbL[0]) + final_bytes(nbL[1]);   // upper bound until the final counts are known
-  if (scratch_bytes < f.end + wbL[0] + wbL[1])
-    return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, up to %zu needed", scratch_bytes, needed);
-  char* work_lo = base + (scratch_bytes - wbL[0] - wbL[1]) / kAlign * kAlign;
-  if ((size_t)(work_lo - base) < f.end)
-    return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, up to %zu needed", scratch_bytes, needed);
-  // per list: its arrays and the pass state.  Once the first pass has merged most boxes away, the
-  // live ones move to dense arrays (cell2, len2, alive2) and get new indices 0..n-1, in order
-  struct ListWork {
-    uint32_t *bcell, *next, *pos, *cell2, *pos2, *block_linked, *d_cnt;
-    char *blen, *len2;
-    uint8_t *alive, *alive2;
-    const uint8_t* old_alive = nullptr;     // set by the compaction, with remap
-    const uint32_t* remap = nullptr;
-    uint32_t n = 0, q_next = 0;
-    uint8_t stamp = 0;
-  } LW[2];
-  hipStream_t stL[2] = {s2, st};
-  uint32_t* tileL[2] = {(uint32_t*)(base + f.tile_tmp2), tile_tmp};
-  // the passes in order; the trailing ones over bit axes inside a mask word are done in one kernel
-  uint32_t pass_axis[16], n_axes = 0;
-  for (uint32_t q = 0; q < g.ndim; q++) {
-    const uint32_t a = c.merge_order[q];
-    if (a != a0 && g.ext[a] > 1) pass_axis[n_axes++] = a;
-  }
-  uint32_t n_generic = n_axes;
-  // (a power-of-two stride: the coordinate on the axis is then one bit of the cell index, which
-  // the kernel relies on; behind an axis of another extent, e.g. a memory bound, it is not.  Not a
-  // size axis: along those the cost list compares costs per volume, which that kernel does not)
-  auto tail_axis = [&](uint32_t a) { return a >= 4 && g.ext[a] == 2 && g.stride[a] <= 32 && (g.stride[a] & (g.stride[a] - 1)) == 0; };
-  while (n_generic > 0 && n_axes - n_generic < 6 && tail_axis(pass_axis[n_generic - 1])) n_generic--;
-  TailAxes tail;
-  tail.n = n_axes - n_generic;
-  for (uint32_t k = 0; k < tail.n; k++) { tail.axis[k] = pass_axis[n_generic + k]; tail.stride[k] = g.stride[pass_axis[n_generic + k]]; }
+    // The two lists are merged side by side, the decisions on the helper stream: most of the
+    // kernels are bound by latency, not bandwidth.  The host waits twice per list: for the number
+    // of live boxes after the first pass (it sizes the grids of the later ones) and for the final
+    // count (it places the final list); meanwhile the other list's stream has work queued.
+    // Work areas at the end of the buffer, the final lists grow from the front.
+    const uint64_t nbL[2] = {h_tot[0], h_tot[1]};
+    const size_t wbL[2] = {work_bytes(nbL[0]), work_bytes(nbL[1])};
+    size_t front = f.end;
+    needed = f.end + wbL[0] + wbL[1] + final_bytes(nbL[0]) + final_bytes(nbL[1]);   // upper bound until the final counts are known
+    if (scratch_bytes < f.end + wbL[0] + wbL[1])
+      return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, up to %zu needed", scratch_bytes, needed);
+    char* work_lo = base + (scratch_bytes - wbL[0] - wbL[1]) / kAlign * kAlign;
+    if ((size_t)(work_lo - base) < f.end)
+      return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, up to %zu needed", scratch_bytes, needed);
+    // per list: its arrays and the pass state.  Once the first pass has merged most boxes away, the
+    // live ones move to dense arrays (cell2, len2, alive2) and get new indices 0..n-1, in order
+    struct ListWork {
+      uint32_t *bcell, *next, *pos, *cell2, *pos2, *block_linked, *d_cnt;
+      char *blen, *len2;
+      uint8_t *alive, *alive2;
+      const uint8_t* old_alive = nullptr;     // set by the compaction, with remap
+      const uint32_t* remap = nullptr;
+      uint32_t n = 0, q_next = 0;
+      uint8_t stamp = 0;
+    } LW[2];
+    hipStream_t stL[2] = {s2, st};
+    uint32_t* tileL[2] = {(uint32_t*)(base + f.tile_tmp2), tile_tmp};
+    // the passes in order; the trailing ones over bit axes inside a mask word are done in one kernel
+    uint32_t pass_axis[16], n_axes = 0;
+    for (uint32_t q = 0; q < g.ndim; q++) {
+      const uint32_t a = c.merge_order[q];
+      if (a != a0 && g.ext[a] > 1) pass_axis[n_axes++] = a;
+    }
+    uint32_t n_generic = n_axes;
+    // (a power-of-two stride: the coordinate on the axis is then one bit of the cell index, which
+    // the kernel relies on; behind an axis of another extent, e.g. a memory bound, it is not.  Not a
+    // size axis: along those the cost list compares costs per volume, which that kernel does not)
+    auto tail_axis = [&](uint32_t a) { return a >= 4 && g.ext[a] == 2 && g.stride[a] <= 32 && (g.stride[a] & (g.stride[a] - 1)) == 0; };
+    while (n_generic > 0 && n_axes - n_generic < 6 && tail_axis(pass_axis[n_generic - 1])) n_generic--;
+    TailAxes tail;
+    tail.n = n_axes - n_generic;
+    for (uint32_t k = 0; k < tail.n; k++) { tail.axis[k] = pass_axis[n_generic + k]; tail.stride[k] = g.stride[pass_axis[n_generic + k]]; }
 
-  auto one_pass = [&](int which) {
-    ListWork& W = LW[which];
-    const uint32_t a = pass_axis[W.q_next++];
-    launch_axis_pass(g, a, ++W.stamp, which == 1, W.n, W.old_alive, W.remap, W.bcell, W.blen, W.alive, W.next,
-                     W.block_linked, maskL[which], prefL[which], tab->d_cost, tab->d_arg, axis_sizes(a), stL[which]);
-  };
-  // first part: the boxes of pass 0 and the first generic pass, then (large lists) the compaction;
-  // the count of live boxes is fetched while the other list's first part runs
-  bool compacted[2] = {false, false};
-  for (int which = 1; which >= 0; which--) {
-    ListWork& W = LW[which];
-    const uint64_t nb = nbL[which];
-    char* w = which == 0 ? work_lo : work_lo + wbL[0];
-    W.bcell = (uint32_t*)w; w += align_up(nb * 4);
-    W.blen = w; w += align_up(nb * 16);
-    W.alive = (uint8_t*)w; w += align_up(nb);
-    W.next = (uint32_t*)w; w += align_up(nb * 4);
-    W.pos = (uint32_t*)w; w += align_up(nb * 4);
-    W.cell2 = (uint32_t*)w; w += align_up(nb * 4);
-    W.pos2 = (uint32_t*)w; w += align_up(nb * 4);
-    W.len2 = w; w += align_up(nb * 16);
-    W.alive2 = (uint8_t*)w; w += align_up(nb);
-    W.block_linked = (uint32_t*)w;
-    W.d_cnt = d_tot + 4 + which * 4;       // [0]: live boxes at the compaction; [2]: the final count
-    W.n = (uint32_t)nb;
-    launch_make_boxes(g, a0, maskL[which], prefL[which], lineL[which], colL[which], a1, W.bcell, W.blen, W.alive, stL[which]);
-    if (on_cells) W.q_next = 1;               // pass_axis[0] = a1 is done
-    if (W.q_next < n_generic) {
-      one_pass(which);
-      // (not after the pass on the cells: it leaves no dead boxes, and a compaction after the next pass costs more than it saves)
-      if (!on_cells && W.n > (1u << 20) && (W.q_next < n_generic || tail.n)) {
-        scan_flags(W.alive, W.n, tileL[which], W.pos, W.d_cnt, stL[which]);
-        launch_compact_boxes(W.n, W.alive, W.pos, W.bcell, W.blen, W.cell2, W.len2, W.alive2, stL[which]);
-        HIP_TRY(hipMemcpyAsync(aux->h_counts + 2 + which, W.d_cnt, 4, hipMemcpyDeviceToHost, stL[which]));
-        compacted[which] = true;
+    auto one_pass = [&](int which) {
+      ListWork& W = LW[which];
+      const uint32_t a = pass_axis[W.q_next++];
+      launch_axis_pass(g, a, ++W.stamp, which == 1, W.n, W.old_alive, W.remap, W.bcell, W.blen, W.alive, W.next,
+                       W.block_linked, maskL[which], prefL[which], tab->d_cost, tab->d_arg, axis_sizes(a), stL[which]);
+    };
+    // first part: the boxes of pass 0 and the first generic pass, then (large lists) the compaction;
+    // the count of live boxes is fetched while the other list's first part runs
+    bool compacted[2] = {false, false};
+    for (int which = 1; which >= 0; which--) {
+      ListWork& W = LW[which];
+      const uint64_t nb = nbL[which];
+      char* w = which == 0 ? work_lo : work_lo + wbL[0];
+      W.bcell = (uint32_t*)w; w += align_up(nb * 4);
+      W.blen = w; w += align_up(nb * 16);
+      W.alive = (uint8_t*)w; w += align_up(nb);
+      W.next = (uint32_t*)w; w += align_up(nb * 4);
+      W.pos = (uint32_t*)w; w += align_up(nb * 4);
+      W.cell2 = (uint32_t*)w; w += align_up(nb * 4);
+      W.pos2 = (uint32_t*)w; w += align_up(nb * 4);
+      W.len2 = w; w += align_up(nb * 16);
+      W.alive2 = (uint8_t*)w; w += align_up(nb);
+      W.block_linked = (uint32_t*)w;
+      W.d_cnt = d_tot + 4 + which * 4;       // [0]: live boxes at the compaction; [2]: the final count
+      W.n = (uint32_t)nb;
+      launch_make_boxes(g, a0, maskL[which], prefL[which], lineL[which], colL[which], a1, W.bcell, W.blen, W.alive, stL[which]);
+      if (on_cells) W.q_next = 1;               // pass_axis[0] = a1 is done
+      if (W.q_next < n_generic) {
+        one_pass(which);
+        // (not after the pass on the cells: it leaves no dead boxes, and a compaction after the next pass costs more than it saves)
+        if (!on_cells && W.n > (1u << 20) && (W.q_next < n_generic || tail.n)) {
+          scan_flags(W.alive, W.n, tileL[which], W.pos, W.d_cnt, stL[which]);
+          launch_compact_boxes(W.n, W.alive, W.pos, W.bcell, W.blen, W.cell2, W.len2, W.alive2, stL[which]);
+          HIP_TRY(hipMemcpyAsync(aux->h_counts + 2 + which, W.d_cnt, 4, hipMemcpyDeviceToHost, stL[which]));
+          compacted[which] = true;
+        }
       }
     }
-  }
-  // second part: the other passes on the dense arrays, the final count
-  for (int which = 1; which >= 0; which--) {
-    ListWork& W = LW[which];
-    if (compacted[which]) {
-      HIP_TRY(hipStreamSynchronize(stL[which]));
-      W.n = aux->h_counts[2 + which];
-      W.old_alive = W.alive; W.remap = W.pos;
-      W.bcell = W.cell2; W.blen = W.len2; W.alive = W.alive2; W.pos = W.pos2;
+    // second part: the other passes on the dense arrays, the final count
+    for (int which = 1; which >= 0; which--) {
+      ListWork& W = LW[which];
+      if (compacted[which]) {
+        HIP_TRY(hipStreamSynchronize(stL[which]));
+        W.n = aux->h_counts[2 + which];
+        W.old_alive = W.alive; W.remap = W.pos;
+        W.bcell = W.cell2; W.blen = W.len2; W.alive = W.alive2; W.pos = W.pos2;
+      }
+      while (W.q_next < n_generic) one_pass(which);
+      if (tail.n)
+        launch_tail_pairs(tail, which == 1, f.n_words, maskL[which], prefL[which], W.old_alive, W.remap, W.blen, W.alive,
+                          tab->d_cost, tab->d_arg, stL[which]);
+      scan_flags(W.alive, W.n, tileL[which], W.pos, W.d_cnt + 2, stL[which]);
+      HIP_TRY(hipMemcpyAsync(aux->h_counts + which, W.d_cnt + 2, 4, hipMemcpyDeviceToHost, stL[which]));
+      HIP_TRY(hipEventRecord(aux->events[ev_used + which], stL[which]));
     }
-    while (W.q_next < n_generic) one_pass(which);
-    if (tail.n)
-      launch_tail_pairs(tail, which == 1, f.n_words, maskL[which], prefL[which], W.old_alive, W.remap, W.blen, W.alive,
-                        tab->d_cost, tab->d_arg, stL[which]);
-    scan_flags(W.alive, W.n, tileL[which], W.pos, W.d_cnt + 2, stL[which]);
-    HIP_TRY(hipMemcpyAsync(aux->h_counts + which, W.d_cnt + 2, 4, hipMemcpyDeviceToHost, stL[which]));
-    HIP_TRY(hipEventRecord(aux->events[ev_used + which], stL[which]));
-  }
-  // the final lists: the decisions' first (the shorter list, as a rule through first); the host
-  // sleeps until a list's count has arrived
-  const hipEvent_t counted[2] = {aux->events[ev_used], aux->events[ev_used + 1]};
-  ev_used += 2;
-  for (int which = 0; which < 2; which++) {
-    const int left = 1 - which;
-    HIP_TRY(hipEventSynchronize(counted[which]));
-    const uint64_t nf = aux->h_counts[which];
-    const size_t fb = final_bytes(nf);
-    if (front + fb > (size_t)(work_lo - base)) {
-      return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, %zu needed", scratch_bytes,
-                  front + fb + (left ? final_bytes(nbL[1 - which]) : 0) + wbL[0] + wbL[1]);
+    // the final lists: the decisions' first (the shorter list, as a rule through first); the host
+    // sleeps until a list's count has arrived
+    const hipEvent_t counted[2] = {aux->events[ev_used], aux->events[ev_used + 1]};
+    ev_used += 2;
+    for (int which = 0; which < 2; which++) {
+      const int left = 1 - which;
+      HIP_TRY(hipEventSynchronize(counted[which]));
+      const uint64_t nf = aux->h_counts[which];
+      const size_t fb = final_bytes(nf);
+      if (front + fb > (size_t)(work_lo - base)) {
+        return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, %zu needed", scratch_bytes,
+                    front + fb + (left ? final_bytes(nbL[1 - which]) : 0) + wbL[0] + wbL[1]);
+      }
+      char* r = base + front;
+      uint32_t* fcell = (uint32_t*)r; r += align_up(nf * 4);
+      char* flen = r; r += align_up(nf * 16);
+      uint64_t* fv0 = (uint64_t*)r; r += align_up(nf * 8);
+      uint64_t* fv1 = (uint64_t*)r;
+      const ListWork& W = LW[which];
+      launch_emit(g, d_P, which == 1, W.n, W.bcell, W.blen, W.alive, W.pos, tab->d_cost, tab->d_arg, fcell, flen, fv0, fv1,
+                  stL[which]);
+      tab->list_off[which] = front;
+      tab->list_n[which] = nf;
+      front += fb;
     }
-    char* r = base + front;
-    uint32_t* fcell = (uint32_t*)r; r += align_up(nf * 4);
-    char* flen = r; r += align_up(nf * 16);
-    uint64_t* fv0 = (uint64_t*)r; r += align_up(nf * 8);
-    uint64_t* fv1 = (uint64_t*)r;
-    const ListWork& W = LW[which];
-    launch_emit(g, d_P, which == 1, W.n, W.bcell, W.blen, W.alive, W.pos, tab->d_cost, tab->d_arg, fcell, flen, fv0, fv1,
-                stL[which]);
-    tab->list_off[which] = front;
-    tab->list_n[which] = nf;
-    front += fb;
-  }
-  needed = std::max(f.fill_end, front + wbL[0] + wbL[1]);
-  HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
-  HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipEventRecord(ev[2], st));
-  HIP_TRY(hipMemcpyAsync(&h_ctr, d_ctr, sizeof h_ctr, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+    needed = std::max(f.fill_end, front + wbL[0] + wbL[1]);
+    HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
+    HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipEventRecord(ev[2], st));
+    HIP_TRY(hipMemcpyAsync(&h_ctr, d_ctr, sizeof h_ctr, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
   }
   if (h_ctr.overflow & 2u) return fail(MRL_E_HIP, "internal error: a work item exceeded its LDS slice");
   if (h_ctr.overflow) return fail(MRL_E_OVERFLOW, "a finite cost reached 2^62");
