@@ -230,8 +230,14 @@ struct WaveRow : RowInfo {
 };
 __device__ __forceinline__ uint32_t first_row() { return blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 constexpr uint32_t kRowGroups = 4096;     // workgroups that share the rows out
-// Where there are few rows, several waves share one (its steps, its boxes).
-__device__ __forceinline__ uint32_t row_parts(uint32_t n_rows) { return n_rows <= 2048u ? 8u : n_rows <= 4096u ? 4u : n_rows <= 8192u ? 2u : 1u; }
+// Where there are few rows, several waves share one (its steps, its boxes), two steps a wave at least: every wave repeats
+// what is done for the whole row.  The merge, us: with a wave a row, all sizes to 32 (at most 1,024 rows of 32 steps) 207, this 162;
+// sizes 1, 2, 4, 8 with three layouts (config 5) 95, this 100, and with eight waves to a row of four steps 141.  Half the
+// thresholds and three steps a wave: 16.8 M cells that all fit 521, this 509, small tables up to 8 % either way.
+__device__ __forceinline__ uint32_t row_parts(const RowGeo& g, uint32_t n_rows) {
+  const uint32_t most = n_rows <= 2048u ? 8u : n_rows <= 4096u ? 4u : n_rows <= 8192u ? 2u : 1u, by_steps = g.en / 2u;
+  return by_steps < 1u ? 1u : by_steps < most ? by_steps : most;
+}
 
 // Lanes on the cells of a word, walking n; what is decided is a ballot and stays in scalar registers (lane t of a
 // vector register keeps step t's word for the store).
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(256) void row_agree_kernel(const RowGeo g, const Ro
   const uint32_t lane = threadIdx.x & 63u, n_rows = B.tot[kRowsTotal];
   RowWords W;
   if (!row_words(g, B, W)) return;
-  const uint32_t parts = row_parts(n_rows), each = (g.en + parts - 1u) / parts;
+  const uint32_t parts = row_parts(g, n_rows), each = (g.en + parts - 1u) / parts;
   for (uint32_t i = first_row(); i < parts * n_rows; i += gridDim.x * 4u) {
     const uint32_t row = i / parts;
     const bool mine = lane < g.en && lane / each == i % parts;
@@ -617,7 +623,7 @@ __global__ __launch_bounds__(256) void row_extent_kernel(const RowGeo g, const R
   const uint32_t lane = threadIdx.x & 63u, n_rows = B.tot[kRowsTotal];
   RowWords W;
   if (!row_words(g, B, W, true)) return;
-  const uint32_t parts = row_parts(n_rows), each = (g.en + parts - 1u) / parts;
+  const uint32_t parts = row_parts(g, n_rows), each = (g.en + parts - 1u) / parts;
   for (uint32_t ip = first_row(); ip < 2u * parts * n_rows; ip += gridDim.x * 4u) {
     const uint32_t i = ip / parts, l = i < n_rows ? 1u : 0u;
     const WaveRow r(B, l ? i : i - n_rows);
@@ -867,7 +873,7 @@ template <int LV>
 __global__ __launch_bounds__(256) void row_inner_kernel(const RowGeo g, const RowBufs B, const uint64_t* __restrict__ cost, const uint16_t* __restrict__ arg) {
   RowWords W;
   if (!row_words(g, B, W, true)) return;
-  const uint32_t n_rows = B.tot[kRowsTotal], parts = row_parts(n_rows);
+  const uint32_t n_rows = B.tot[kRowsTotal], parts = row_parts(g, n_rows);
   for (uint32_t i = first_row(); i < 2u * parts * n_rows; i += gridDim.x * 4u) {
     const uint32_t part = i % parts, row = i / parts;
     if (row < n_rows) row_inner<true, LV>(g, B, W, n_rows, row, part, parts, cost, arg);
@@ -1147,7 +1153,7 @@ __global__ __launch_bounds__(256) void row_emit_kernel(const RowGeo g, const Row
   if (blockIdx.x == 0 && threadIdx.x == 0) B.tot[kBoxesFirst] = n0;
   const uint64_t lists = row_lists_at(g, B.tot);
   if (lists + row_list_bytes(n0) + row_list_bytes(n_all - n0) > B.room) return;
-  const uint32_t parts = row_parts(n_rows);
+  const uint32_t parts = row_parts(g, n_rows);
   for (uint32_t ip = first_row(); ip < 2u * parts * n_rows; ip += gridDim.x * 4u) {
     const uint32_t part = ip % parts, i = ip / parts, l = i < n_rows ? 1u : 0u;
     const WaveRow r(B, l ? i : i - n_rows);
