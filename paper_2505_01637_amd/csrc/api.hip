@@ -833,8 +833,8 @@ int32_t take_through(size_t n, size_t chunk, const StageHalves& stage, hipStream
 // which start behind what `stream` holds; the stretches share one staging block of per_item bytes an item.  A stretch that its
 // share of the block holds is one launch (a lookup's takes 90 us whatever its points are), a longer one goes through in halves.
 // fill, launch and drain also get the items that a chunk is laid out for, launch its stream.
-// 100,003 Specs asked of the dense table (with the caller's arrays) 727 -> 579 us, looked up in the boxes 1186 -> 969; solving a
-// pipeline of three tables (15.7 M Specs) and taking its lists, 50 MB, to the host 6.3 -> 4.4 ms, of which 1.3 are the solve's gain.
+// 100,003 Specs of the caller's arrays asked of the dense table 372 -> 147 us, looked up in the boxes 747 -> 437 (with the binding's
+// records 739 -> 600 and 1219 -> 970; runs differ by 5 to 14 %); 1,000,000 3990 -> 1200 and 6690 -> 3530.
 constexpr uint32_t kParts = 4;
 constexpr uint32_t kPartThreads = 12;       // of all calls together
 std::atomic<uint32_t> g_part_threads{0};

@@ -13,13 +13,15 @@
 // Most words of a table hold no cell that fits its levels (94 % in the largest pipeline).  Rows (the words of one k
 // for all n: same b, m and place in the shape) are kept up to one past the last with a fitting cell; in a row
 // beyond, every cell is (INF, NONE) and folded into the row before.  All arrays are indexed by the kept rows, their
-// number stays on the GPU: nothing is read back before the merge has ended.
+// number stays on the GPU: nothing is read back before the merge has ended (unless the scratch may be short: row_total_kernel).
+// (n, k, m, b here and below: RowGeo's axes, turned where there is one size along n.)
 //
 //   row_count_kernel   rows kept per plane (b, m, place), then a prefix sum
+//   row_info_kernel    what a wave needs of its row
 //   row_heads_kernel   a wave per row: H of both lists
 //   row_agree_kernel   a wave per row: heads that agree, in value and run length, with the one before on k, m, b.  Along k
 //                      that settles it: Fk
-//   row_fold_*_kernel  Fm; Fb: chains along k (and m) compared
+//   row_fold_*_kernel  Fm; Fb: chains along k (and m) compared, by a lane each, by a wave each where they are longer than 64
 //   row_left_kernel    T, and N: its heads with an extent above 1 on some size axis (few, in the cost list); prefix sums over both
 //   row_extent_kernel  the four extents of the heads in N
 //   row_inner_kernel   a wave per row: heads left that agree, in value and size extents, with the one a step further on
@@ -30,8 +32,8 @@
 //   row_emit_kernel    the two final lists
 // Bound by instruction issue (the kernels that compare values: 60 to 80 vector instructions a word and as many scalar
 // ones; emit: the reduction of the costs) and by the latency of a few dependent reads (the others).  Config 5's fused table
-// (449.5 M cells, 11.3 M that fit, 44,500 rows; two lists at once), us: heads 75, agree 160, folds 50, left 35, extent
-// 65, inner 250, merge 160, emit 110.
+// (449.5 M cells, 11.3 M that fit, in 0.42 M of 7.02 M words; 44,038 rows of 38 words kept, 1.67 M words; two lists at once), us:
+// heads 80, agree 159, fold 59, left 36, extent 78, inner 253, merge 161, emit 109.
 #include <hip/hip_runtime.h>
 #include "compress.h"
 #include "dev_params.h"
