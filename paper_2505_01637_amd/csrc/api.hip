@@ -171,12 +171,14 @@ size_t bind_entries(const Compiled& c) {
 // have not: a wave per row of one step is mostly waiting (b, m and k of 64, 64 and 16 sizes and one along n: 743 to 774 us
 // box by box, 899 by words in rows of one, 675 in rows of 16).  Tables of four levels with 1 to 64 steps along n, everything or
 // little fitting, 64 to 450 M cells, up to 255 sizes along k, m and b: the whole solve is 1.0 to 1.9 times as fast by words.
-bool row_geo(const Compiled& c, RowGeo& g) {
+// may_turn: false for rows along n all the same, which the scratch may hold where it does not hold the turned ones: these are
+// kept whole along k and dropped along m, and so can be more words (2 sizes along m, 57 along k, little fits: 3.5 instead of 2.1 MB).
+bool row_geo(const Compiled& c, bool may_turn, RowGeo& g) {
   const DevParams& P = c.P;
   memset(&g, 0, sizeof g);
   if (P.gather || P.NL != 4 || P.log2V > 6 || c.n_specs >= (1ull << 31) || P.G % 64 || P.G / 64 > kRowShapeWords || P.nsz[3] > 64) return false;
   uint32_t turn = 0;
-  while (turn < 3 && P.nsz[3 - turn] == 1 && P.nsz[2 - turn] <= 64) turn++;
+  while (may_turn && turn < 3 && P.nsz[3 - turn] == 1 && P.nsz[2 - turn] <= 64) turn++;
   for (uint32_t d = 0; d < 4; d++) g.axis[d] = (d + 4 - turn) & 3;
   g.en = P.nsz[g.axis[3]]; g.ek = P.nsz[g.axis[2]]; g.em = P.nsz[g.axis[1]]; g.eb = P.nsz[g.axis[0]];
   g.G = P.G; g.nw = P.G / 64;
@@ -196,7 +198,7 @@ bool row_geo(const Compiled& c, RowGeo& g) {
   return true;
 }
 
-FixedLayout fixed_layout(const Compiled& c) {
+FixedLayout fixed_layout(const Compiled& c, bool may_turn = true) {
   FixedLayout f;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
@@ -257,7 +259,7 @@ FixedLayout fixed_layout(const Compiled& c) {
   f.end = o;
   RowGeo g;
   f.rows_rows = f.rows_first = f.rows_info = f.rows_cnt = f.rows_start = f.rows_sum = f.rows_tot = f.rows_dyn = 0;
-  if (row_geo(c, g)) {
+  if (row_geo(c, may_turn, g)) {
     o = shared;
     f.rows_rows = take((size_t)g.n_planes * 4);
     f.rows_first = take((size_t)g.n_planes * 4);
@@ -1151,11 +1153,24 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   tab->f = f;
   // What the merge word by word needs beyond the fill's part depends on the contents; where that does not suffice, boxes are
   // merged one by one.  Its words are the larger part: if those of all rows do not fit, the plan's fit map is asked how many
-  // rows there are, together with the work lists' lengths.
-  RowGeo row_g;
-  bool by_rows = row_geo(c, row_g) && scratch_bytes >= f.rows_dyn && row_words_fit(row_g, row_g.n_planes, scratch_bytes - f.rows_dyn);
-  const bool ask_rows = by_rows && !row_words_fit(row_g, (uint64_t)row_g.n_planes * row_g.ek, scratch_bytes - f.rows_dyn);
-  if (scratch_bytes < (by_rows ? f.fill_end : f.least())) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
+  // rows there are, together with the work lists' lengths.  Turned rows are tried first, then, if there may be too little
+  // scratch for them, rows along n.
+  struct ByRows { RowGeo g; FixedLayout f; uint64_t room; bool on, ask; } by_rows[2];
+  uint32_t n_ways = 0;
+  for (const bool may_turn : {true, false}) {
+    ByRows& w = by_rows[n_ways];
+    if (!row_geo(c, may_turn, w.g)) break;
+    if (n_ways && w.g.axis[3] == by_rows[0].g.axis[3]) break;
+    w.f = fixed_layout(c, may_turn);
+    w.room = scratch_bytes > w.f.rows_dyn ? scratch_bytes - w.f.rows_dyn : 0;
+    w.on = row_words_fit(w.g, w.g.n_planes, w.room);
+    w.ask = w.on && !row_words_fit(w.g, (uint64_t)w.g.n_planes * w.g.ek, w.room);
+    n_ways++;
+    if (rows_always_fit(w.g, w.room)) break;
+  }
+  bool some_rows = false, ask_rows = false;
+  for (uint32_t i = 0; i < n_ways; i++) { some_rows |= by_rows[i].on; ask_rows |= by_rows[i].ask; }
+  if (scratch_bytes < (some_rows ? f.fill_end : f.least())) return fail(MRL_E_NOMEM, "scratch buffer too small: %zu bytes given, at least %zu needed", scratch_bytes, f.least());
   char* base = (char*)d_scratch;
   hipStream_t st = (hipStream_t)hip_stream;
   HIP_TRY(hipGetDevice(&tab->device));
@@ -1278,8 +1293,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   if (16 + 3 * (size_t)n_lev > kPinnedCounts) return fail(MRL_E_INVAL, "too many dependency levels (%u)", n_lev);
   const uint32_t* cnt = aux->h_counts + 16;            // pinned: the copy does not go through a staging buffer
   if (ask_rows) {
-    launch_row_total(row_g, d_fitmap, &d_ctr->rows, st);
-    HIP_TRY(hipMemcpyAsync(aux->h_counts + kRowTotals, &d_ctr->rows, 4, hipMemcpyDeviceToHost, st));
+    for (uint32_t i = 0; i < n_ways; i++) if (by_rows[i].ask) launch_row_total(by_rows[i].g, d_fitmap, d_ctr->rows + i, st);
+    HIP_TRY(hipMemcpyAsync(aux->h_counts + kRowTotals, d_ctr->rows, sizeof d_ctr->rows, hipMemcpyDeviceToHost, st));
   }
   HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, plan.list_cnt, 3 * (size_t)n_lev * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
@@ -1291,7 +1306,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   HIP_TRY(hipEventRecord(ev[4], st));
   prefill_timed = true;
   HIP_TRY(hipEventSynchronize(counts_ready));
-  if (ask_rows) by_rows = row_words_fit(row_g, aux->h_counts[kRowTotals], scratch_bytes - f.rows_dyn);
+  for (uint32_t i = 0; i < n_ways; i++)
+    if (by_rows[i].ask) by_rows[i].on = row_words_fit(by_rows[i].g, aux->h_counts[kRowTotals + i], by_rows[i].room);
   if (deps_late) {
     // now the tables this lattice reads: their fills are queued (or the call waits here until
     // they are); the parameters go up once more, with their addresses, and the levels wait for them
@@ -1359,22 +1375,25 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   Counters h_ctr;
   size_t needed = 0;
   bool merged = false;
-  if (by_rows) {
-    const RowBufs rb{(uint32_t*)(base + f.rows_rows), (uint32_t*)(base + f.rows_first), base + f.rows_info, (uint32_t*)(base + f.rows_cnt), (uint32_t*)(base + f.rows_start),
-                     base + f.rows_sum, (uint32_t*)(base + f.rows_tot), base + f.rows_dyn, scratch_bytes - f.rows_dyn};
-    launch_rows(row_g, rb, tab->d_cost, tab->d_arg, d_fitmap, (const uint32_t*)((char*)d_P + offsetof(DevParams, sizes)), st);
+  for (uint32_t i = 0; i < n_ways && !merged; i++) {
+    if (!by_rows[i].on) continue;
+    const RowGeo& rg = by_rows[i].g;
+    const FixedLayout& rf = by_rows[i].f;
+    const RowBufs rb{(uint32_t*)(base + rf.rows_rows), (uint32_t*)(base + rf.rows_first), base + rf.rows_info, (uint32_t*)(base + rf.rows_cnt), (uint32_t*)(base + rf.rows_start),
+                     base + rf.rows_sum, (uint32_t*)(base + rf.rows_tot), base + rf.rows_dyn, by_rows[i].room};
+    launch_rows(rg, rb, tab->d_cost, tab->d_arg, d_fitmap, (const uint32_t*)((char*)d_P + offsetof(DevParams, sizes)), st);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(ev[2], st));
     HIP_TRY(hipMemcpyAsync(aux->h_counts, rb.tot, kRowTotals * 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(&h_ctr, d_ctr, sizeof h_ctr, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     uint64_t list_at[2], end = 0;
-    merged = rows_fit(row_g, aux->h_counts, rb.room, list_at, &end);
+    merged = rows_fit(rg, aux->h_counts, rb.room, list_at, &end);
     if (merged) {
       tab->list_n[0] = aux->h_counts[kBoxesFirst];
       tab->list_n[1] = aux->h_counts[kBoxesTotal] - tab->list_n[0];
-      for (int which = 0; which < 2; which++) tab->list_off[which] = f.rows_dyn + list_at[which];
-      needed = std::max(f.fill_end, f.rows_dyn + (size_t)end);
+      for (int which = 0; which < 2; which++) tab->list_off[which] = rf.rows_dyn + list_at[which];
+      needed = std::max(rf.fill_end, rf.rows_dyn + (size_t)end);
     }
   }
   if (!merged) {

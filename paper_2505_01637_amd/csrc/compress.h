@@ -194,6 +194,8 @@ void launch_rows(const RowGeo& g, const RowBufs& B, const uint64_t* cost, const 
                  const uint32_t* sizes, hipStream_t st);
 // Whether the words of so many kept rows fit room bytes (a plane keeps one row at least, ek at most).
 bool row_words_fit(const RowGeo& g, uint64_t n_rows, uint64_t room);
+// Whether all of it fits room bytes whatever the table holds.
+bool rows_always_fit(const RowGeo& g, uint64_t room);
 // Adds the number of rows that will be kept to *total, from the fit map alone.
 void launch_row_total(const RowGeo& g, const uint32_t* fitmap, uint32_t* total, hipStream_t st);
 // Given the totals: whether all of it fitted (nothing valid was written if not), where in dyn the lists lie, and the end.

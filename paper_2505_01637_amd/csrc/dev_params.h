@@ -122,7 +122,7 @@ struct DevParams {
 constexpr uint32_t kCtrSlots = 256;
 struct Counters {
   unsigned int overflow;
-  unsigned int rows;                       // kept rows of the merge by words, where they are counted before the fill
+  unsigned int rows[2], pad;               // kept rows of the merge by words, turned and along n, where they are counted before the fill
   unsigned long long n_admissible[kCtrSlots];
   unsigned long long n_rewrites[kCtrSlots];
 };

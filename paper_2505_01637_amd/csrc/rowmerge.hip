@@ -99,6 +99,14 @@ __host__ __device__ __forceinline__ bool words_fit(const RowGeo& g, uint64_t n_r
 
 bool row_words_fit(const RowGeo& g, uint64_t n_rows, uint64_t room) { return words_fit(g, n_rows, room); }
 
+bool rows_always_fit(const RowGeo& g, uint64_t room) {
+  // every cell a head with an extent, and a box, in both lists
+  const uint64_t rows = (uint64_t)g.n_planes * g.ek, cells = rows * g.en * 64;
+  const uint64_t heads_end = up256(row_base_bytes(g, rows) + up16(2 * cells * 4) + up16(2 * cells * 2));
+  const uint64_t agree = row_agree_bytes(g, rows), lists = 2 * row_list_bytes(cells);
+  return heads_end + (agree > lists ? agree : lists) <= room;
+}
+
 bool rows_fit(const RowGeo& g, const uint32_t* tot, uint64_t room, uint64_t list_at[2], uint64_t* end) {
   // (a kernel that found no room left the totals behind it unset: in this order)
   if (!words_fit(g, tot[kRowsTotal], room)) return false;

@@ -554,6 +554,42 @@ def test_scratch_for_any_contents_holds_the_words(number, max_size):
         assert got[label].stats.scratch_used == ample[label].stats.scratch_used, label
 
 
+def test_scratch_that_sufficed_for_rows_along_n():
+    """One size along n, few along m, many along k, little fits: rows along k would need 3.5 MB here.  With the 2.1 MB that rows
+    along n use, the table is solved all the same, and uses no more."""
+    cfg = W.config(5)
+    cfg["target"]["capacity_bytes"] = [16, 64, 256, W.UNBOUNDED]
+    for _, lat, _ in cfg["lattices"]:
+        lat["sizes"] = [[1], [1, 2], [1] + list(range(40, 2000, 35)) if len(lat["sizes"][2]) > 1 else [1], [1]]
+    _, got, _ = compare_config(cfg, scratch_bytes=2099456)
+    assert got["F"].stats.scratch_used <= 2099456
+
+
+@pytest.mark.parametrize("sizes,little", [(([1, 2, 3], [1, 2, 4, 8], list(range(1, 17)), [1]), False), (([1], [1, 2], list(range(1, 58)), [1]), True),
+                                          ((list(range(1, 9)), list(range(1, 9)), [1], [1]), False), (([1], [1, 2, 4], [1, 2, 3, 6], [1, 2, 8]), True)])
+def test_scratch_that_was_used_suffices(sizes, little):
+    """A table solved again with exactly the scratch that it used: rows along n and turned ones, whichever it was that fitted."""
+    B = _binding()
+    cfg = W.config(4)
+    cfg["lattices"][0][1]["sizes"] = [list(s) for s in sizes]
+    if little:
+        cfg["target"]["capacity_bytes"] = [16, 64, 256, W.UNBOUNDED]
+    target, got, _ = compare_config(cfg)
+    lists = [got["M"].boxes(which).tobytes() for which in (0, 1)]
+    used, solved = int(got["M"].stats.scratch_used), 0
+    for part in (1.0, 0.9, 0.8, 0.7, 0.6):
+        try:
+            tab = B.solve(target, cfg["lattices"][0][1], scratch_bytes=int(used * part) // 256 * 256 + (256 if part == 1 else 0))
+        except B.MorelloError as e:
+            assert e.code == B.E_NOMEM and part < 1
+            continue
+        again = int(tab.stats.scratch_used)
+        assert [tab.boxes(which).tobytes() for which in (0, 1)] == lists
+        assert [B.solve(target, cfg["lattices"][0][1], scratch_bytes=again).boxes(which).tobytes() for which in (0, 1)] == lists
+        solved += 1
+    assert solved >= 1
+
+
 def two_level_bounded(caps, sizes):
     cfg = W.config(1, seed=11, max_size=4)
     t = cfg["target"]
