@@ -1161,7 +1161,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     ByRows& w = by_rows[n_ways];
     if (!row_geo(c, may_turn, w.g)) break;
     if (n_ways && w.g.axis[3] == by_rows[0].g.axis[3]) break;
-    w.f = fixed_layout(c, may_turn);
+    w.f = may_turn ? f : fixed_layout(c, false);
     w.room = scratch_bytes > w.f.rows_dyn ? scratch_bytes - w.f.rows_dyn : 0;
     w.on = row_words_fit(w.g, w.g.n_planes, w.room);
     w.ask = w.on && !row_words_fit(w.g, (uint64_t)w.g.n_planes * w.g.ek, w.room);

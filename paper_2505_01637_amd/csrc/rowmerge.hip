@@ -240,13 +240,13 @@ struct WaveRow : RowInfo {
 };
 __device__ __forceinline__ uint32_t first_row() { return blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 constexpr uint32_t kRowGroups = 4096;     // workgroups that share the rows out
-// Where there are few rows, several waves share one (its steps, its boxes), two steps a wave at least: every wave repeats
+// Where there are few rows, several waves share one (its steps, its boxes), two steps a wave: every wave repeats
 // what is done for the whole row.  The merge, us: with a wave a row, all sizes to 32 (at most 1,024 rows of 32 steps) 207, this 162;
 // sizes 1, 2, 4, 8 with three layouts (config 5) 95, this 100, and with eight waves to a row of four steps 141.  Half the
 // thresholds and three steps a wave: 16.8 M cells that all fit 521, this 509, small tables up to 8 % either way.
 __device__ __forceinline__ uint32_t row_parts(const RowGeo& g, uint32_t n_rows) {
-  const uint32_t most = n_rows <= 2048u ? 8u : n_rows <= 4096u ? 4u : n_rows <= 8192u ? 2u : 1u, by_steps = g.en / 2u;
-  return by_steps < 1u ? 1u : by_steps < most ? by_steps : most;
+  const uint32_t most = n_rows <= 2048u ? 8u : n_rows <= 4096u ? 4u : n_rows <= 8192u ? 2u : 1u, by_steps = (g.en + 1u) / 2u;
+  return by_steps < most ? by_steps : most;
 }
 
 // Lanes on the cells of a word, walking n; what is decided is a ballot and stays in scalar registers (lane t of a
