@@ -134,7 +134,7 @@ struct Compiled {
 
 // Offsets of the fixed part of the scratch buffer.
 struct FixedLayout {
-  size_t counters, params, tiles, level_shapes, level_off, mk_entry, qdec, recs, masks, item_tasks, sort_tmp, list_small, bundle_first, list_wide, list_cnt, bind, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
+  size_t counters, params, tiles, level_shapes, level_off, mk_entry, blk_off, qdec, recs, masks, unit_cnt, unit_seg, diag, bind, list, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
       upload_end, fill_end, end;
   uint32_t n_words;
   // the merge word by word (row_geo): its fixed lists from `shared` on, then dyn
@@ -211,24 +211,25 @@ FixedLayout fixed_layout(const Compiled& c, bool may_turn = true) {
   // and lists, which are written when the fill has ended: an 80-byte record per shape would otherwise
   // be 6 % of what a solve of a lattice with two memory levels asks for.
   const size_t shared = f.shared = o;
-  f.tiles = take(c.tiles.size() * sizeof(TileEntry) + 8);
+  f.tiles = take(c.tiles.size() * (c.P.gather ? sizeof(TileEntry) : sizeof(TileStep)) + 8);
   f.level_shapes = take(c.level_shapes.size() * 4);
   f.level_off = take(c.level_off.size() * 4);
+  f.blk_off = c.P.gather ? 0 : take(c.level_off.size() * 4);
   f.mk_entry = take(c.mk_entry.size());
   f.qdec = take(c.qdec.size() * 4);
   f.upload_end = o;
   const size_t n_items = (size_t)c.n_shapes * c.P.npass;
-  f.recs = f.sort_tmp = f.masks = f.item_tasks = f.list_small = f.bundle_first = f.list_wide = f.list_cnt = f.bind = 0;
+  f.recs = f.masks = f.unit_cnt = f.unit_seg = f.diag = f.bind = f.list = 0;
   if (!c.P.gather) {
+    const uint32_t n_lev = (uint32_t)c.level_off.size() - 1;
     f.masks = take(n_items * ((size_t)c.P.nwp << c.P.ndt) * 8);
-    f.item_tasks = take(n_items * 2);
     f.recs = take(plan_bytes_recs(c.n_shapes));
-    f.sort_tmp = take(plan_bytes_sort(c.level_off.data(), (uint32_t)c.level_off.size() - 1, c.P.npass));
-    f.list_small = take(n_items * 4);
-    f.bundle_first = take((n_items + c.level_off.size()) * 4);
-    f.list_wide = take(n_items * 4);
-    f.list_cnt = take(3 * c.level_off.size() * 4);
+    f.unit_cnt = take((size_t)unit_blocks(c.level_off.data(), n_lev, c.P.npass, nullptr) * c.P.nranks * 4);
+    f.unit_seg = take((size_t)n_lev * c.P.nranks * 4);
+    f.diag = take(((size_t)n_lev + c.P.nranks) * 4);
     if (c.P.moves) f.bind = take(bind_entries(c) * 8);
+    // the work list takes what is left of the buffer; where that is less than the whole list, it goes through in windows
+    f.list = take(std::max<size_t>(n_items / 2, 64) * 8);
   }
   f.fill_end = o;
   o = shared;
@@ -428,6 +429,11 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
   }
   if (c.n_specs >= (1ull << 32)) return fail(MRL_E_INVAL, "lattice has %llu specs; the limit is 2^32-1", (unsigned long long)c.n_specs);
 
+  for (uint32_t i = 0; i < P.nops; i++) {
+    P.mstride[i] = (P.lvpow[i] * P.npass) << P.log2V;
+    P.unit_lay += L->layout_coord[i] ? 1u : 0u;
+  }
+
   // target
   for (int l = 0; l < 4; l++) {
     P.cap[l] = T.capacity_bytes[l];
@@ -458,8 +464,21 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
           if (P.access[i] != kRead) { if (!st) continue; cf += st; }
           if (cf > UINT32_MAX) return fail(MRL_E_INVAL, "Move coefficients too large");
           P.mcoef[i][src][dst][x] = (uint32_t)cf;
+          P.mcoef[i][src][3][0] += cf ? 1u : 0u;
         }
   for (uint32_t i = 0; i < P.nops; i++) P.can_convert[i] = L->dtype_coord[i] && P.access[i] == kRead;
+  {
+    // (below 2^48 each: the volume is.  b holds p in a composition)
+    const uint64_t b = c.sizes[0].back(), m = c.sizes[1].back(), k = c.sizes[2].back(), n = c.sizes[3].back(), mk = m * k, kn = k * n, mn = m * n;
+    uint64_t most = std::max({mk, kn, mn}) * (chain ? 1 : b), coef = 0;
+    if (chain) most = std::max({most, m * b, k * b, b * n});
+    for (uint32_t i = 0; i < P.nops; i++)
+      for (uint32_t src = 0; src < P.NL; src++)
+        for (uint32_t dst = 0; dst < src; dst++)
+          for (uint32_t x = 0; x < 2; x++) coef = std::max<uint64_t>(coef, P.mcoef[i][src][dst][x]);
+    coef += P.convert;
+    P.small = most <= UINT32_MAX && coef < (1u << 30) && c.n_specs < (1u << 29);
+  }
 
   // microkernels: the level / layout / dtype part of each predicate, per (pack, variant)
   c.mk_entry.assign((size_t)256 * P.V, 0);
@@ -663,9 +682,8 @@ int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, Compil
 }
 
 // A second stream (default priority, non-blocking) for work that is independent of what runs on
-// the caller's stream: the wide items of a dependency level beside its other items, and one of the
-// two box lists beside the other; with it the events and the pinned counters a solve needs.
-constexpr size_t kPinnedCounts = 16 + 3 * 1024;   // u32: 16 for the box lists, then the level lists' lengths (3 per level, at most 1017 levels)
+// the caller's stream: one of the two box lists beside the other; with it the events and the pinned counters a solve needs.
+constexpr size_t kPinnedCounts = 16 + 128;   // u32: 16 for the box lists, then the diagonals' first places in the work list (at most 62)
 struct Aux {
   hipStream_t stream = nullptr;
   std::vector<hipEvent_t> events;
@@ -1179,12 +1197,11 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   Counters* d_ctr = (Counters*)(base + f.counters);
   DevParams* d_P = (DevParams*)(base + f.params);
   P.tiles = (const TileEntry*)(base + f.tiles);
+  P.steps = (const TileStep*)(base + f.tiles);
   const uint32_t n_lev = (uint32_t)c.level_off.size() - 1;
   uint32_t* d_level_shapes = (uint32_t*)(base + f.level_shapes);
-  uint32_t* d_level_off = (uint32_t*)(base + f.level_off);
-  const PlanBuffers plan{base + f.recs, (unsigned long long*)(base + f.masks), (uint16_t*)(base + f.item_tasks), base + f.sort_tmp,
-                         (uint32_t*)(base + f.list_small), (uint32_t*)(base + f.bundle_first), (uint32_t*)(base + f.list_wide),
-                         (uint32_t*)(base + f.list_cnt)};
+  const PlanBuffers plan{base + f.recs, (unsigned long long*)(base + f.masks), (const uint32_t*)(base + f.level_off), (const uint32_t*)(base + f.blk_off),
+                         (uint32_t*)(base + f.unit_cnt), (uint32_t*)(base + f.unit_seg), (uint32_t*)(base + f.diag), base + f.list};
   uint32_t* d_fitmap = (uint32_t*)(base + f.fitmap);
   P.mk_entry = (const uint8_t*)(base + f.mk_entry);
   P.qdec = (const uint32_t*)(base + f.qdec);
@@ -1199,7 +1216,18 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     c.solved = true;
     upload = to.mem;
     memset(upload, 0, f.params - f.counters);
-    if (!c.tiles.empty()) memcpy(image(f.tiles), c.tiles.data(), c.tiles.size() * sizeof(TileEntry));
+    if (P.gather) {
+      if (!c.tiles.empty()) memcpy(image(f.tiles), c.tiles.data(), c.tiles.size() * sizeof(TileEntry));
+    } else {
+      TileStep* steps = (TileStep*)image(f.tiles);
+      for (uint32_t d = 0; d < 4; d++)
+        for (uint32_t j = 0; j < P.nsz[d]; j++)
+          for (uint32_t q = P.tile_off[d][j]; q < P.tile_off[d][j + 1]; q++) {
+            const TileEntry te = c.tiles[q];
+            steps[q] = TileStep{(j - te.jt) * P.shape_stride[d] * P.G, te.trips, P.tile_base + d * P.maxs + te.jt, (uint32_t)(((uint64_t)te.trips + P.threads - 1) / P.threads)};
+          }
+      unit_blocks(c.level_off.data(), n_lev, P.npass, (uint32_t*)image(f.blk_off));
+    }
     memcpy(image(f.level_shapes), c.level_shapes.data(), c.level_shapes.size() * 4);
     memcpy(image(f.level_off), c.level_off.data(), c.level_off.size() * 4);
     memcpy(image(f.mk_entry), c.mk_entry.data(), c.mk_entry.size());
@@ -1207,7 +1235,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   }
   memcpy(image(f.params), &P, sizeof P);
   AuxLease lease;
-  rc = get_aux(2 * (size_t)n_lev + 8, lease);
+  rc = get_aux(16, lease);
   if (rc) return rc;
   Aux* aux = lease.a;
   // Whichever way this function is left from here on, both streams have drained before the turn
@@ -1219,7 +1247,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   } drain{st, aux->stream};
   HIP_TRY(hipMemcpyAsync(base + f.counters, upload, f.image_bytes(), hipMemcpyHostToDevice, st));
 
-  // ---- fill: plan, then one launch (or two) per dependency level ----
+  // ---- fill: plan and work list, then a launch per diagonal ----
   hipEvent_t* ev = aux->timing;
   size_t ev_used = 0;
   hipStream_t s2 = aux->stream;
@@ -1288,17 +1316,20 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   // the plan kernel also streams (INF, NONE) over the tables when a shape's entries are whole 16-byte pieces
   // (not when the pre-fill runs beside the fill of the tables this lattice reads: see launch_fill_ones)
   const bool fused_prefill = P.G % 8 == 0 && !deps_late;
-  launch_plan(d_P, P, c.n_shapes, c.max_task, d_level_shapes, d_level_off, c.level_off.data(), n_lev, plan, d_fitmap, d_ctr,
+  const uint32_t n_blk = unit_blocks(c.level_off.data(), n_lev, P.npass, nullptr), n_diag = n_lev + P.nranks - 1;
+  const uint64_t list_room = (scratch_bytes - f.list) / 8;
+  const uint32_t window = (uint32_t)std::min<uint64_t>(list_room, UINT32_MAX);
+  launch_plan(d_P, P, c.n_shapes, d_level_shapes, n_lev, n_blk, plan, d_fitmap, d_ctr,
               fused_prefill ? tab->d_cost : nullptr, fused_prefill ? tab->d_arg : nullptr, st);
-  if (16 + 3 * (size_t)n_lev > kPinnedCounts) return fail(MRL_E_INVAL, "too many dependency levels (%u)", n_lev);
-  const uint32_t* cnt = aux->h_counts + 16;            // pinned: the copy does not go through a staging buffer
+  const uint32_t* diag = aux->h_counts + 16;           // pinned: the copy does not go through a staging buffer
   if (ask_rows) {
     for (uint32_t i = 0; i < n_ways; i++) if (by_rows[i].ask) launch_row_total(by_rows[i].g, d_fitmap, d_ctr->rows + i, st);
     HIP_TRY(hipMemcpyAsync(aux->h_counts + kRowTotals, d_ctr->rows, sizeof d_ctr->rows, hipMemcpyDeviceToHost, st));
   }
-  HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, plan.list_cnt, 3 * (size_t)n_lev * 4, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, plan.diag, ((size_t)n_diag + 1) * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   hipEvent_t counts_ready = aux->events[ev_used++];
+  launch_list_units(d_P, n_lev, n_blk, plan, 0, window, st);
   if (!fused_prefill) {
     launch_fill_ones(tab->d_cost, c.n_specs * 8, st, deps_late);
     launch_fill_ones(tab->d_arg, c.n_specs * 2, st, deps_late);
@@ -1324,41 +1355,31 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   HIP_TRY(hipEventRecord(ev[5], st));
   levels_timed = true;
   if (P.moves) launch_bind(d_P, (uint64_t*)(base + f.bind), (uint32_t)bind_entries(c), st);
-  bool wide_started = false;
-  hipEvent_t wide_done = nullptr;          // recorded behind the last wide launch that the caller's stream has not waited for yet
-  for (uint32_t l = 0; l < n_lev; l++) {
-    const size_t first = (size_t)c.level_off[l] * P.npass, n_items = (size_t)(c.level_off[l + 1] - c.level_off[l]) * P.npass;
-    const uint32_t n_bundles = cnt[l], n_wide = cnt[n_lev + l], n_small = cnt[2 * n_lev + l] & ((1u << kItemsBits) - 1u), lg_tasks = cnt[2 * n_lev + l] >> kItemsBits;
-    if ((size_t)n_bundles + n_wide > n_items) return fail(MRL_E_HIP, "internal error: work lists of level %u overflow", l);
-    // The wide items (with more tasks than a bundle takes) run on the helper stream, level after
-    // level, without waiting for the other items: a tile of a wide item leads to the same item of a
-    // smaller shape, in which at least as much fits, so that one is wide as well, and wide items
-    // read nothing that the others write.  The others read entries of any kind, so a level's
-    // launch on the caller's stream waits for the wide items of all lower levels.  (With both
-    // kinds joined at every level the levels of the fused table took 1.49 ms, the wide items
-    // setting the pace of most of them.)  Packed layouts exist for some sizes only, so there a
-    // smaller shape may have fewer tasks: both kinds then share the caller's stream.
-    const hipStream_t sw = P.moves ? st : s2;
-    if (n_wide) {
-      if (!wide_started && sw != st) {
-        HIP_TRY(hipEventRecord(aux->events[ev_used], st));
-        HIP_TRY(hipStreamWaitEvent(s2, aux->events[ev_used++], 0));
-        wide_started = true;
+  const FillArgs fill = fill_args(d_P, P, plan, tab->d_cost, tab->d_arg, d_ctr);
+  uint32_t w0 = 0;                        // the list holds units [w0, w0 + window)
+  DiagRun run;
+  run.n = 0;
+  const auto flush = [&]() {
+    if (run.n) launch_fill_diagonals(fill, P, base + f.list, run, st);
+    run.n = 0;
+  };
+  for (uint32_t d = 0; d < n_diag; d++)
+    for (uint32_t u = diag[d]; u < diag[d + 1];) {
+      if (u - w0 >= window) {
+        flush();
+        w0 = u;
+        launch_list_units(d_P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), st);
       }
-      launch_fill_wide(d_P, P, c.max_task, n_wide, plan.list_wide + first, plan, tab->d_cost, tab->d_arg, d_ctr, sw);
+      const uint32_t n = std::min(diag[d + 1] - u, window - (u - w0));
+      const bool small = small_diagonal(fill, n);
+      if (!small || run.n == kRunMost) flush();
+      run.chain = small;
+      run.start[run.n] = u - w0;
+      run.start[++run.n] = u - w0 + n;
+      if (!small) flush();
+      u += n;
     }
-    if (n_bundles) {
-      if (wide_done) { HIP_TRY(hipStreamWaitEvent(st, wide_done, 0)); wide_done = nullptr; }
-      launch_fill_level(d_P, P, c.max_task, n_bundles, plan.list_small + first,
-                        n_bundles == n_small ? nullptr : plan.bundle_first + first + l, lg_tasks, plan, tab->d_cost, tab->d_arg, d_ctr, st);
-    }
-    if (n_wide && sw != st) {
-      // the next level's other items wait here
-      HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
-      wide_done = aux->events[ev_used++];
-    }
-  }
-  if (wide_done) HIP_TRY(hipStreamWaitEvent(st, wide_done, 0));
+  flush();
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(ev[1], st));
@@ -1561,7 +1582,6 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     HIP_TRY(hipMemcpyAsync(&h_ctr, d_ctr, sizeof h_ctr, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
   }
-  if (h_ctr.overflow & 2u) return fail(MRL_E_HIP, "internal error: a work item exceeded its LDS slice");
   if (h_ctr.overflow) return fail(MRL_E_OVERFLOW, "a finite cost reached 2^62");
   if (stats) {
     memset(stats, 0, sizeof *stats);

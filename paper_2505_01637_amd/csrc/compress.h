@@ -40,28 +40,47 @@ struct Geo {
 struct PlanBuffers {
   void* recs;                              // plan_bytes_recs
   unsigned long long* masks;
-  uint16_t* item_tasks;
-  void* sort_tmp;                          // plan_bytes_sort
-  uint32_t *list_small, *bundle_first, *list_wide, *list_cnt;      // counts per level: bundles, wide items, small items | log2 of the tasks per bundle << kItemsBits
+  const uint32_t *level_off, *blk_off;     // first shape and first block (unit_blocks) of every dependency level
+  uint32_t *cnt, *seg, *diag;              // [ranks][blocks], [levels][ranks], [diagonals + 1]
+  void* list;                              // 8 bytes per unit
 };
-constexpr uint32_t kItemsBits = 28;
 size_t plan_bytes_recs(uint32_t n_shapes);
-size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass);
+// Blocks of items that the work lists are made in; blk_off (may be null): first block of every level, and their number.
+uint32_t unit_blocks(const uint32_t* level_off, uint32_t n_levels, uint32_t npass, uint32_t* blk_off);
 // Whether the work lists can hold the lattice's dependency levels.  h: the host's copy of *P.
 bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels);
 bool fit_map_stored(const DevParams& h);
-// h: the host's copy of *P.  max_task: entries of the largest possible item.  fitmap: zero before, unless fit_map_stored.
-void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint32_t max_task, const uint32_t* level_shapes,
-                 const uint32_t* level_off, const uint32_t* h_level_off, uint32_t n_levels, const PlanBuffers& B, uint32_t* fitmap, Counters* ctr,
-                 void* prefill_cost, void* prefill_arg, hipStream_t stream);
+// h: the host's copy of *P.  fitmap: zero before, unless fit_map_stored.
+void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, const uint32_t* level_shapes, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B,
+                 uint32_t* fitmap, Counters* ctr, void* prefill_cost, void* prefill_arg, hipStream_t stream);
+// Units [w0, w0 + w_len) of the work list to its place.
+void launch_list_units(const DevParams* P, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream);
 // The costs of the alloc-bindings of a Matmul whose Moves are Move Specs, from its Move table.
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream);
-// One dependency level: n bundles of its small items (starts: where each begins in `items`; nullptr:
-// every item by itself) of about 2^lg_tasks tasks, and n wide items.
-void launch_fill_level(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const uint32_t* starts,
-                       uint32_t lg_tasks, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
-void launch_fill_wide(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const PlanBuffers& B,
-                      uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream);
+// What the kernels of the diagonals read of the parameters, by value: they are short, and every read of the
+// parameters in device memory would be another round trip.
+struct FillArgs {
+  const DevParams* P;
+  const void* recs;
+  const TileStep* steps;
+  uint64_t* cost;
+  uint16_t* arg;
+  Counters* ctr;
+  const uint64_t *costM, *costE;
+  const uint8_t* mk_entry;
+  uint32_t nops, NL, G, log2V, ndt, unit_lay, tile_dims;       // tile_dims: bit d = dimension d has tiles
+  uint32_t mstride[4], pack_shift[4], lay_bit[4];
+  uint32_t lay_xor[4], cv_bit[4];                              // layout bit of an operand's entry, dtype bit that a converting Move clears (0: none)
+  uint32_t convert, s, sync, move_base, buf_id, par_shift;
+  uint32_t has_buf, split, chain, GM, VM, GE, VE, nszE_n, kM_first, nkM, nsz3, layM[3], layE[3], zero[4];
+};
+FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr);
+// Diagonals that one launch takes: n of them, diagonal i at places [start[i], start[i + 1]) of the list.  Small ones
+// (small_diagonal) go into a chain, any other is a launch of its own.
+constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768;
+struct DiagRun { uint32_t n, chain, start[kRunMost + 1]; };
+bool small_diagonal(const FillArgs& A, uint32_t n_units);
+void launch_fill_diagonals(const FillArgs& A, const DevParams& h, const void* list, const DiagRun& run, hipStream_t stream);
 
 // Segments of one launch of the bounded fill: segment i is (dependency level of shapes, rank)
 // = shapes [first_shape, first_shape + n_shapes) of the level-ordered shape list at rank[i], and

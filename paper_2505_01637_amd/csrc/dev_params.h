@@ -25,6 +25,11 @@ struct TileEntry {
   uint32_t jt;
   uint32_t trips;
 };
+// The same as the fill by diagonals reads it: how many entries before the Spec's own its sub-Spec lies, the trip count,
+// the rewrite id, and the rounds of a parallel loop.
+struct alignas(16) TileStep {
+  uint32_t delta, trips, id, rounds;
+};
 
 // A level assignment of the operands is handled as a "pack": 2 bits per operand,
 // operand 0 in the highest field.  pack <-> combo (the mixed-radix index used in
@@ -41,7 +46,8 @@ struct DevParams {
   uint32_t shape_stride[4];  // in shapes
   uint32_t sizes[4][kMaxSizes];
   uint32_t tile_off[4][kMaxSizes + 1];   // CSR into tiles, per (dim, size index)
-  const TileEntry* tiles;    // device
+  const TileEntry* tiles;    // device; kinds filled by gathers
+  const TileStep* steps;     // device; the other kinds: the same list
   uint32_t tile_dim_ok[4];   // which dims this kind may tile
   uint32_t lay_bit[5];       // bit position inside the variant index, kNoBit = no coordinate
   uint32_t lay_w[5];         // bits of the layout field: 1 (row-/column-major), 2 (also packed and shuffled strips)
@@ -57,7 +63,11 @@ struct DevParams {
   uint64_t mk_cost[8];
   // Move coefficient per element, [operand][src][dst][same|transposed]; load and/or store
   // according to how the operand is accessed; 0 = the Move does not exist.
-  uint32_t mcoef[4][4][4][2];
+  // In the place of dst = 3: the number of Moves of the operand from src.
+  alignas(16) uint32_t mcoef[4][4][4][2];
+  uint32_t mstride[4];       // entries between two levels of operand i
+  uint32_t unit_lay;         // layouts of a unit of the work list: 1 << unit_lay, a lane each
+  uint32_t small;            // coefficient (+ convert) and elements fit 32 bits, their product is below 2^62; byte offsets of costs fit 32 bits
   uint32_t can_convert[4];   // operand may take a converting Move (has a dtype bit and is read-only)
   // per (pack, variant): bit j set = the level/layout/dtype part of microkernel j's predicate holds
   const uint8_t* mk_entry;   // device, [256][V]
@@ -122,7 +132,8 @@ struct DevParams {
 constexpr uint32_t kCtrSlots = 256;
 struct Counters {
   unsigned int overflow;
-  unsigned int rows[2], pad;               // kept rows of the merge by words, turned and along n, where they are counted before the fill
+  unsigned int rows[2];                    // kept rows of the merge by words, turned and along n, where they are counted before the fill
+  unsigned int ticket;                     // workgroups of the work lists' scan that have ended
   unsigned long long n_admissible[kCtrSlots];
   unsigned long long n_rewrites[kCtrSlots];
 };

@@ -1,46 +1,45 @@
-// Rewrite evaluation + argmin for one dependency level of the Spec lattice.
+// Rewrite evaluation + argmin over the Spec lattice.
 //
 // Paper, Section 4: a Spec's entry is the lowest-cost applicable rewrite, the
 // rewrite's cost being the affine function of Section 3 of its sub-Specs'
-// costs.  Here the table is filled bottom-up: all shapes of one dependency
-// level in one launch, every sub-Spec of another shape already final.
+// costs.  Here the table is filled bottom-up.
 //
 // An item is one shape (b,m,k,n) at one value of the passive level axis (the
 // intermediate's level of a fused Spec; other kinds have one value): a set of
-// entries closed under Moves.  Before the first level a plan kernel decides,
-// for every item and every value of the dtype bits, which level assignments
-// fit their levels (most do not), as one bit mask per item in rank order
-// (rank = sum of the operand levels), and sets the whole table to (INF, NONE),
-// so that the level kernels write admissible entries only; a second kernel
-// puts the items with anything to do into work lists per dependency level:
-// bundles of items (about kBundle tasks together; a task is an admissible
-// entry) and wide items of their own.
+// entries closed under Moves.  A plan kernel decides, for every item and every
+// value of the dtype bits, which level assignments fit their levels (most do
+// not), as one bit mask per item in rank order (rank = sum of the operand
+// levels), and sets the whole table to (INF, NONE).  A Move lowers the rank
+// within an item, and a tile goes to the same level assignment of a shape of a
+// lower dependency level, so the entries of one diagonal, level + rank, depend
+// on earlier diagonals only.  The admissible level assignments are listed by
+// diagonal, and one launch takes a diagonal: every candidate of an entry is a
+// read of a finished entry, no workgroup waits for another, and nothing but
+// the order of the launches has to be kept.
 //
-// A workgroup takes a bundle.  Its first lanes take an item each (shape,
-// masks, tile counts, everything that does not depend on the entry), then the
-// admissible entries of all its items are listed in LDS, once by item and once
-// by rank, and
-//   1. one lane per task evaluates the tile and bufferize rewrites, whose
-//      sub-Specs belong to other shapes or tables and are final: a tile
-//      sub-Spec sits at the same offset of a smaller shape's group, several
-//      loads in flight per lane.  The best of them is parked in LDS;
-//   2. rank by rank, a quad of lanes per task evaluates the Moves (sub-Specs
-//      of the same item at a lower rank: read from LDS), an operand per lane;
-//      the quad's first lane adds the microkernels and the parked candidate;
-//   3. the results go to the table, a task per lane.
-// The ranks of a shape are a chain (10 of three operands, 13 of four), and a
-// rank of one item holds only a few tasks; the bundle's items go through it
-// together, which fills the lanes, and share the cost of setting up.
+// Such a launch is bound by the chain of reads of one wave (unit, record, tile,
+// sub-Spec) while the chip is not full, then by instruction issue, hence three
+// forms of it: the reads of an entry shared out over several lanes; four
+// entries that differ in their layouts only on four lanes, which share what
+// does not depend on the layout; a lane per entry.
 // Ties go to the lowest id: a lane meets its candidates in the order of their
 // ids where it compares the cost alone, all else is compared by (cost, id).
 // Nothing is reduced across workgroups: the table is deterministic.
+//
+// Against the form it replaces (bundles of items in LDS, rank by rank with a
+// barrier each, a launch per dependency level; 1,900 to 3,250 vector
+// lane-instructions per entry), whole solves: two Matmuls composed 2742 ->
+// 1993 us (16.8 M entries; G's fill 1.34 -> 0.79 ms), the vector-matrix product
+// 668 -> 464, batched layouts 1061 -> 783, packed layouts 3058 -> 2424, the
+// pipeline 3728 -> 3049.
+#include <string.h>
 #include <hip/hip_runtime.h>
 #include "compress.h"
 #include "dev_params.h"
 
 namespace mrl {
 
-constexpr int kBatch = 8;              // sub-Spec costs fetched together before they are compared
+constexpr uint32_t kBatch = 8;         // tiles whose sub-Specs' costs are fetched together
 
 struct Eval {
   uint64_t best;
@@ -122,7 +121,7 @@ __device__ __forceinline__ uint32_t layout_width(const DevParams* __restrict__ P
   return cols % P->strip == 0 ? 2u : 1u;
 }
 
-// What the level kernels need of a shape, worked out once by the plan kernel.
+// What the fill needs of a shape, worked out once by the plan kernel.
 struct alignas(16) ShapeRec {
   uint64_t numel[5];             // elements of the operands ([4]: the intermediate)
   uint32_t shape, si;            // index; the four size indices, a byte each
@@ -135,8 +134,8 @@ static_assert(sizeof(ShapeRec) == 80, "read as five 16-byte pieces");
 // Plan: one wave per up to kPlanShapes shapes, in the order of the dependency levels.  Its first lanes take
 // a shape each and write its record; then, shape by shape, the lanes are level assignments: which
 // of them fit is written as one mask per item (bit = position in rank order, one plane of nwp words
-// per value of the dtype bits) with the item's number of tasks, and the entries that fit are marked
-// in a bit map in table order (bit = cell; read by the compression pass).
+// per value of the dtype bits), and the entries that fit are marked in a bit map in table order (bit = cell; read by the
+// compression pass).
 // Bound by instruction issue (460 vector instructions a shape), on small tables by the latency of a wave's shapes one
 // after the other: with 16 per wave always, config 3's 180 shapes took 46 us, now 11.  The map is stored whole where
 // that can be done: with an atomic per level assignment config 2 (262,144 shapes, one bit each) took 178 us, now 129.
@@ -155,7 +154,7 @@ static uint32_t plan_shapes(uint32_t n_shapes) {
 
 __global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, uint32_t n_shapes, uint32_t per_wave, uint32_t map_stored, const uint32_t* __restrict__ level_shapes,
                                                    ShapeRec* __restrict__ recs, unsigned long long* __restrict__ masks,
-                                                   uint16_t* __restrict__ item_tasks, uint32_t* __restrict__ fitmap, Counters* __restrict__ ctr,
+                                                   uint32_t* __restrict__ fitmap, Counters* __restrict__ ctr,
                                                    uint4* __restrict__ cost16, uint4* __restrict__ arg16) {
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   const uint32_t npass = P->npass, ncombo = P->ncombo, V = P->V, nb = npass * V, ndp = 1u << P->ndt, nwp = P->nwp, nw = ndp * nwp, NL = P->NL, nops = P->nops;
@@ -219,7 +218,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__
 #pragma unroll
     for (int i = 0; i < 5; i++) numel[i] = (uint64_t)lane_of((uint32_t)(S.numel[i] >> 32), s) << 32 | lane_of((uint32_t)S.numel[i], s);
     if (cost16) {
-      // (INF, NONE) = all-ones over the shape's whole group: the level kernels overwrite what fits
+      // (INF, NONE) = all-ones over the shape's whole group: the fill overwrites what fits
       const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
       const uint32_t nc = P->G >> 1, na = P->G >> 3;       // 16-byte pieces (G is a multiple of 8)
       uint4* c16 = cost16 + (size_t)sh * nc;
@@ -292,200 +291,211 @@ __global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__
       }
     }
     if (lane < npass * nw) masks[(size_t)(first + s) * npass * nw + lane] = my_word;
-    const uint32_t mine = lane == 0 ? ents[0] : lane == 1 ? ents[1] : lane == 2 ? ents[2] : ents[3];
-    if (lane < npass) item_tasks[(size_t)(first + s) * npass + lane] = (uint16_t)(mine << vb);
     n_adm += (unsigned long long)(ents[0] + ents[1] + ents[2] + ents[3]) << vb;
   }
   if (lane == 0 && n_adm) atomicAdd(&ctr->n_admissible[blockIdx.x % kCtrSlots], n_adm);
 }
 
-// Work lists, kSortTile items of one dependency level per workgroup: the level's items in order,
-// those of at most small_max tasks cut into bundles (bundle b = items [bundle_first[b],
-// bundle_first[b + 1]) of the level's stretch of list_small), the others in list_wide.  An item
-// weighs its tasks (at least min_weight, which bounds the items of a bundle); a bundle ends with the
-// item that fills its quota, kBundle tasks on levels with work enough to fill the chip, less on
-// others.  Levels of several tiles: sort_sums_kernel first adds up every tile.
-constexpr uint32_t kSortThreads = 1024, kSortItems = 8, kSortTile = kSortThreads * kSortItems;
-// (sweeps with the final kernels: quotas of 64, 96, 192 and 256 tasks are 0 to 3 % slower on the
-// large lattices, 2048 and 4096 bundles before they grow 3 and 8 % on config 4, 512 the same)
-constexpr uint32_t kBundle = 128;            // tasks per bundle
-constexpr uint32_t kFewBundles = 256, kManyTasks = 7;      // a bundle has a compute unit for itself, and 2^7 tasks and more
-constexpr uint32_t kMinBundles = 1024;       // a level is cut into this many bundles before they grow
+// Work lists.  A unit is an admissible (item, dtype bits, level assignment): the entries that differ in their layouts
+// only (packed layouts: a part of these, see emit_units_kernel).  Units are listed by diagonal, dependency level of the
+// shape + rank of the level assignment: a Move lowers the rank within an item and a tile goes to the same level
+// assignment of a shape of a lower level, so the units of one diagonal depend on earlier diagonals only.  Within a
+// diagonal they lie level by level, then in the order of their items: neighbours share a shape and its tiles.
+//
+// Three kernels behind the plan.  count: per block of kBlockItems items of one level, the units of every rank.  scan:
+// a workgroup per (level, rank) turns these into places within it, the last one to end adds up the diagonals.
+// emit: a wave per block walks the masks' non-empty words and writes the units.  The whole list may be longer than its
+// place in the scratch buffer: emit writes a window of it, as often as the host asks.
+constexpr uint32_t kBlockItems = 4;
+constexpr uint32_t kMaxLevels = 64;          // (b*m*k*n < 2^48: at most 49 dependency levels, 61 diagonals: a lane of a wave each)
 
-__device__ __forceinline__ unsigned long long block_scan_1024(unsigned long long v, unsigned long long* sh, unsigned long long& total) {
-  unsigned long long incl = v;
+// Level of block b: blk_off[l] = first block of level l.
+__device__ __forceinline__ uint32_t level_of_block(uint32_t my_end, uint32_t b) { return (uint32_t)__popcll(__ballot(my_end <= b)); }
+
+// Bits [lo, hi) of positions, as a mask of word `it`.
+__device__ __forceinline__ unsigned long long word_range(uint32_t lo, uint32_t hi, uint32_t it) {
+  const auto below = [&](uint32_t p) { return p <= it * 64 ? 0ull : p >= it * 64 + 64 ? ~0ull : (1ull << (p - it * 64)) - 1ull; };
+  return below(hi) & ~below(lo);
+}
+
+// Layouts beyond those of a unit, as powers of two: a packed operand may have four instead of two (unit_lay = the
+// operands with a layout coordinate).
+__device__ __forceinline__ uint32_t unit_parts(const DevParams* __restrict__ P, const ShapeRec* __restrict__ recs, uint32_t rec) {
+  return P->moves ? (recs[rec].mk_var >> 23) - P->unit_lay : 0u;
+}
+
+__global__ __launch_bounds__(256) void count_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_off, const uint32_t* __restrict__ blk_off,
+                                                          uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs,
+                                                          const unsigned long long* __restrict__ masks, uint32_t* __restrict__ cnt) {
+  const uint32_t lane = threadIdx.x & 63u, b = (blockIdx.x * 256u + threadIdx.x) / kBlockItems, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+  const uint32_t npass = P->npass, nwp = P->nwp, ndp = 1u << P->ndt, nw = ndp * nwp;
+  const uint32_t my_end = lane < n_levels ? blk_off[lane + 1] : ~0u;
+  uint32_t lev = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 64 / kBlockItems; k++) { const uint32_t l = level_of_block(my_end, b0 + k); lev = lane / kBlockItems == k ? l : lev; }
+  unsigned long long m[4] = {0, 0, 0, 0};
+  uint32_t parts = 0;
+  if (b < n_blk) {
+    const uint32_t item = level_off[lev] * npass + (b - blk_off[lev]) * kBlockItems + lane % kBlockItems;
+    if (item < level_off[lev + 1] * npass) {
+#pragma unroll
+      for (int w = 0; w < 4; w++) if ((uint32_t)w < nw) m[w] = masks[(size_t)item * nw + w];
+      parts = unit_parts(P, recs, item / npass);
+    }
+  }
+  for (uint32_t r = 0; r < P->nranks; r++) {
+    const uint32_t lo = P->rank_off[r], hi = P->rank_off[r + 1];
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < 4; w++) if (w < nw) n += (uint32_t)__popcll(m[w] & word_range(lo, hi, w % nwp));
+    n <<= parts;
+#pragma unroll
+    for (uint32_t d = 1; d < kBlockItems; d <<= 1) n += (uint32_t)__shfl_xor((int)n, d, 64);
+    if (b < n_blk && lane % kBlockItems == 0) cnt[(size_t)r * n_blk + b] = n;
+  }
+}
+
+// seg: units of every (level, rank), then their first places in the list; diag: the diagonals' first places, and the end.
+__global__ __launch_bounds__(1024) void scan_units_kernel(const uint32_t* __restrict__ blk_off, uint32_t n_levels, uint32_t n_ranks, uint32_t n_blk,
+                                                          uint32_t* __restrict__ cnt, uint32_t* __restrict__ seg, uint32_t* __restrict__ diag, unsigned int* __restrict__ ticket) {
+  __shared__ uint32_t sh[16];
+  __shared__ uint32_t tot[kMaxLevels * kMaxRanks];
+  __shared__ bool last;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, lev = blockIdx.x / n_ranks, r = blockIdx.x - lev * n_ranks;
+  uint32_t* c = cnt + (size_t)r * n_blk;
+  const uint32_t end = blk_off[lev + 1];
+  uint32_t run = 0;
+  for (uint32_t i0 = blk_off[lev]; i0 < end; i0 += 4096) {
+    const uint32_t i = i0 + threadIdx.x * 4u;
+    uint32_t v[4], mine = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) { v[k] = i + k < end ? c[i + k] : 0u; mine += v[k]; }
+    uint32_t incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t o = __shfl_up(incl, d, 64);
+      if ((int)lane >= d) incl += o;
+    }
+    __syncthreads();
+    if (lane == 63) sh[wave] = incl;
+    __syncthreads();
+    uint32_t before = run + incl - mine, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < 16; w++) { const uint32_t x = sh[w]; before += w < wave ? x : 0u; total += x; }
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) { if (i + k < end) c[i + k] = before; before += v[k]; }
+    run += total;
+  }
+  // (the totals pass between dies: written and read at the agent's scope, ordered by the ticket)
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(seg + blockIdx.x, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x;
+  }
+  __syncthreads();
+  if (!last) return;
+  const uint32_t n_seg = n_levels * n_ranks;
+  for (uint32_t i = threadIdx.x; i < n_seg; i += 1024) tot[i] = __hip_atomic_load(seg + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (wave) return;
+  const uint32_t n_diag = n_levels + n_ranks - 1;       // lane d: diagonal d
+  uint32_t n = 0;
+  for (uint32_t l = 0; l < n_levels; l++) n += lane >= l && lane - l < n_ranks ? tot[l * n_ranks + lane - l] : 0u;
+  uint32_t incl = n;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    const unsigned long long o = __shfl_up(incl, d, 64);
-    if ((int)(threadIdx.x & 63u) >= d) incl += o;
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if ((int)lane >= d) incl += o;
   }
+  uint32_t at = incl - n;
+  if (lane < n_diag) diag[lane] = at;
+  if (lane == n_diag - 1) diag[n_diag] = incl;
+  for (uint32_t l = 0; l < n_levels; l++)
+    if (lane >= l && lane - l < n_ranks) { seg[l * n_ranks + lane - l] = at; at += tot[l * n_ranks + lane - l]; }
+}
+
+// A unit of the list: x = index of its shape's record, y = pack (8 bits), dtype bits (2), level of the intermediate (2),
+// part of its layouts (6), and from bit kUnitFit on, per operand and destination level, whether the level assignment with
+// that operand there fits as well (its entries are finished, and only those are read).
+constexpr uint32_t kUnitFit = 18;
+constexpr uint32_t kEmitQueue = 256;
+
+// A wave walks its block's words one after the other (place of every unit: its rank's place + the units of that rank
+// before it) and puts them in a queue in LDS, which is then taken a lane per unit: of two to six admissible level
+// assignments per word only those lanes would have something to do.
+__global__ __launch_bounds__(256) void emit_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_off, const uint32_t* __restrict__ blk_off,
+                                                         uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs, const unsigned long long* __restrict__ masks,
+                                                         const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ seg, uint2* __restrict__ list, uint32_t w0, uint32_t w_len) {
+  __shared__ uint8_t pos_of[256];
+  __shared__ unsigned long long words[4][64];
+  __shared__ uint32_t q_unit[4][kEmitQueue], q_to[4][kEmitQueue];
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, b = blockIdx.x * 4u + wave;
+  const uint32_t npass = P->npass, nwp = P->nwp, nw = nwp << P->ndt, ncombo = P->ncombo, n_ranks = P->nranks, nops = P->nops;
+  for (uint32_t p = threadIdx.x; p < ncombo; p += 256) pos_of[P->pos_entry[p] & 0xFFu] = (uint8_t)p;
   __syncthreads();
-  if ((threadIdx.x & 63u) == 63) sh[threadIdx.x >> 6] = incl;
-  __syncthreads();
-  unsigned long long excl = incl - v;
-  total = 0;
-  for (uint32_t w = 0; w < kSortThreads / 64; w++) {
-    const unsigned long long x = sh[w];
-    if (w < (threadIdx.x >> 6)) excl += x;
-    total += x;
-  }
-  return excl;
-}
-
-// The level and the tile of it that workgroup `b` has: levels in order, each with its tiles.
-__device__ __forceinline__ void sort_place(const uint32_t* __restrict__ level_off, uint32_t npass, uint32_t b, uint32_t& lv, uint32_t& tile) {
-  lv = 0;
-  tile = b;
-  for (;;) {
-    const uint32_t t = ((level_off[lv + 1] - level_off[lv]) * npass + kSortTile - 1) / kSortTile;
-    if (tile < t) return;
-    tile -= t;
-    lv++;
-  }
-}
-
-// sums[workgroup]: tasks of the tile's small items.
-__global__ __launch_bounds__(kSortThreads) void sort_sums_kernel(const uint32_t* __restrict__ level_off, uint32_t npass, const uint16_t* __restrict__ item_tasks,
-                                                                 uint32_t small_max, uint32_t* __restrict__ sums) {
-  __shared__ unsigned long long sh[kSortThreads / 64];
-  uint32_t lv, tile;
-  sort_place(level_off, npass, blockIdx.x, lv, tile);
-  const uint32_t first = level_off[lv] * npass, n = (level_off[lv + 1] - level_off[lv]) * npass, base = tile * kSortTile;
-  unsigned long long work = 0, total = 0;
-  for (uint32_t i = base + threadIdx.x; i < n && i < base + kSortTile; i += kSortThreads) { const uint32_t t = item_tasks[first + i]; if (t <= small_max) work += t; }
-  block_scan_1024(work, sh, total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = (uint32_t)total;
-}
-
-// part 0: with the quota known, the weights and numbers of the tile (parts[workgroup]); part 1: the
-// lists.  A grid of one tile per level needs part 1 only.
-__global__ __launch_bounds__(kSortThreads) void sort_work_kernel(const uint32_t* __restrict__ level_off, uint32_t n_levels, uint32_t npass,
-                                                                 const uint16_t* __restrict__ item_tasks, uint32_t small_max, uint32_t min_weight,
-                                                                 uint32_t part, const uint32_t* __restrict__ sums, uint4* __restrict__ parts,
-                                                                 uint32_t* __restrict__ list_small, uint32_t* __restrict__ bundle_first,
-                                                                 uint32_t* __restrict__ list_wide, uint32_t* __restrict__ list_cnt) {
-  __shared__ unsigned long long sh[kSortThreads / 64];
-  uint32_t lv, tile;
-  sort_place(level_off, npass, blockIdx.x, lv, tile);
-  const uint32_t first = level_off[lv] * npass, n = (level_off[lv + 1] - level_off[lv]) * npass, base = tile * kSortTile;
-  const uint32_t tiles = (n + kSortTile - 1) / kSortTile, wg0 = blockIdx.x - tile;
-  uint32_t tasks[kSortItems];
-  unsigned long long work = 0, total = 0;
+  if (b >= n_blk) return;
+  const uint32_t lev = level_of_block(lane < n_levels ? blk_off[lane + 1] : ~0u, b);
+  const uint32_t first = level_off[lev] * npass + (b - blk_off[lev]) * kBlockItems, left = level_off[lev + 1] * npass - first;
+  const uint32_t n_here = left < kBlockItems ? left : kBlockItems;
+  const unsigned long long word = lane < n_here * nw ? masks[(size_t)first * nw + lane] : 0ull;
+  words[wave][lane] = word;
+  uint32_t run = lane < n_ranks ? seg[lev * n_ranks + lane] + cnt[(size_t)lane * n_blk + b] : 0u;       // lane r: place of rank r's next unit
+  const uint32_t rlo = lane < n_ranks ? P->rank_off[lane] : 0u, rhi = lane < n_ranks ? P->rank_off[lane + 1] : 0u;
+  const uint32_t parts = lane < n_here ? unit_parts(P, recs, (first + lane) / npass) : 0u;              // lane j: item j's
+  uint32_t rank[4];
 #pragma unroll
-  for (uint32_t k = 0; k < kSortItems; k++) {
-    const uint32_t i = base + threadIdx.x * kSortItems + k;
-    tasks[k] = i < n ? item_tasks[first + i] : 0u;
-    if (tasks[k] <= small_max) work += tasks[k];
-  }
-  if (sums) for (uint32_t t = 0; t < tiles; t++) total += sums[wg0 + t];
-  else block_scan_1024(work, sh, total);
-  const uint32_t level_tasks = (uint32_t)total;
-  uint32_t quota = (uint32_t)(total / kMinBundles);
-  quota = quota < min_weight ? min_weight : quota > kBundle ? kBundle : quota;
-  auto weight = [&](uint32_t t) { return t < min_weight ? min_weight : t > quota ? quota : t; };
-  unsigned long long mine = 0;                      // weight (32 bits) | small items (16) | wide items (16)
+  for (uint32_t it = 0; it < 4; it++) rank[it] = it * 64 + lane < ncombo ? (P->pos_entry[it * 64 + lane] >> 8) & 0xFFu : 0u;
+  uint32_t qn = 0;
+  const auto flush = [&]() {
+    for (uint32_t i0 = 0; i0 < qn; i0 += 64) {
+      const uint32_t i = i0 + lane, u = i < qn ? q_unit[wave][i] : 0u, j = u & 15u, dt = (u >> 4) & 3u;
+      const uint32_t ch = __shfl(parts, j, 64);
+      if (i >= qn) continue;
+      const uint32_t item = first + j, rec = item / npass, pass = item - rec * npass, pack = P->pos_entry[u >> 8] & 0xFFu;
+      uint32_t y = pack | dt << 8 | pass << 10;
 #pragma unroll
-  for (uint32_t k = 0; k < kSortItems; k++) {
-    if (tasks[k] > small_max) mine += 1ull << 48;
-    else if (tasks[k]) mine += 1ull << 32 | weight(tasks[k]);
-  }
-  const unsigned long long excl = block_scan_1024(mine, sh, total);
-  const uint32_t all_w = (uint32_t)total, all_s = (uint32_t)((total >> 32) & 0xFFFFu), all_x = (uint32_t)(total >> 48);
-  if (part == 0) {
-    if (threadIdx.x == 0) parts[blockIdx.x] = make_uint4(all_w, all_s, all_x, 0);
-    return;
-  }
-  uint32_t run_w = 0, run_s = 0, run_x = 0;          // weight and number of the small items, number of the wide ones, of the tiles before
-  if (sums)
-    for (uint32_t t = 0; t < tile; t++) { const uint4 p = parts[wg0 + t]; run_w += p.x; run_s += p.y; run_x += p.z; }
-  uint32_t w = run_w + (uint32_t)excl, s = run_s + (uint32_t)((excl >> 32) & 0xFFFFu), x = run_x + (uint32_t)(excl >> 48);
-  uint32_t* starts = bundle_first + first + lv;
+      for (uint32_t op = 0; op < 4; op++) {
+        if (op >= nops) break;
+        const uint32_t shift = P->pack_shift[op], src = (pack >> shift) & 3u;
 #pragma unroll
-  for (uint32_t k = 0; k < kSortItems; k++) {
-    const uint32_t item = first + base + threadIdx.x * kSortItems + k;
-    if (tasks[k] > small_max) list_wide[first + x++] = item;
-    else if (tasks[k]) {
-      const uint32_t add = weight(tasks[k]);
-      list_small[first + s++] = item;
-      if ((w + add) / quota != w / quota) starts[(w + add) / quota] = s;       // (weights are at most the quota: no bundle is skipped)
-      w += add;
+        for (uint32_t dst = 0; dst < 3; dst++)
+          if (dst < src) {
+            const uint32_t p = pos_of[pack - ((src - dst) << shift)];
+            y |= (uint32_t)(words[wave][j * nw + dt * nwp + (p >> 6)] >> (p & 63u) & 1ull) << (kUnitFit + op * 3 + dst);
+          }
+      }
+      const uint32_t to = q_to[wave][i] - w0;
+      for (uint32_t c = 0; c < (1u << ch); c++)
+        if (to + c < w_len) list[to + c] = make_uint2(rec, y | c << 12);          // (below the window: wraps around)
     }
+    qn = 0;
+  };
+  for (unsigned long long todo = __ballot(word != 0); todo; todo &= todo - 1) {
+    const uint32_t s = (uint32_t)__builtin_ctzll(todo), j = s / nw, w = s - j * nw, dt = w / nwp, it = w - dt * nwp;
+    const unsigned long long m = (unsigned long long)lane_of((uint32_t)(word >> 32), s) << 32 | lane_of((uint32_t)word, s);
+    const uint32_t ch = lane_of(parts, j), rk = it == 0 ? rank[0] : it == 1 ? rank[1] : it == 2 ? rank[2] : rank[3];
+    const uint32_t before = (uint32_t)__popcll(m & word_range(0, rlo, it));      // lane r: units of lower ranks in this word
+    const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    const uint32_t to = __shfl(run, rk, 64) + ((k - __shfl(before, rk, 64)) << ch);
+    if (qn > kEmitQueue - 64) flush();
+    if ((m >> lane) & 1ull) { q_unit[wave][qn + k] = j | dt << 4 | (it * 64 + lane) << 8; q_to[wave][qn + k] = to; }
+    qn += (uint32_t)__popcll(m);
+    run += (uint32_t)__popcll(m & word_range(rlo, rhi, it)) << ch;
   }
-  if (threadIdx.x == 0) {
-    if (tile == 0) starts[0] = 0;
-    if (tile + 1 == tiles) {
-      const uint32_t bundles = (run_w + all_w + quota - 1) / quota;
-      starts[bundles] = run_s + all_s;
-      const uint32_t each = bundles ? level_tasks / bundles : 0u, lg = each ? 31u - (uint32_t)__builtin_clz(each) : 0u;
-      list_cnt[lv] = bundles; list_cnt[n_levels + lv] = run_x + all_x;
-      list_cnt[2 * n_levels + lv] = (run_s + all_s) | (lg < 15u ? lg : 15u) << kItemsBits;       // (plan_fits: fewer than 2^28 items)
-    }
-  }
+  flush();
 }
 
-// ---------------------------------------------------------------- one dependency level
-// LDS of a workgroup: up to cap tasks of up to ni items, kt tile rewrites per item at a time.
-struct FillGeom {
-  uint32_t cap, ni, kt;
-  uint32_t bt;          // Move-cost entries per item
-  uint32_t isz;         // entries of an item's table of level assignments (dtype bits x pack)
-  uint32_t nlay;        // layout bits; without MOVES a task index is an entry index and these bits
-  uint32_t ns;          // entries at most; entry ns stands for "does not fit" (its tasks cost INF)
-};
-
-struct FillLds {
-  uint64_t *t_cost, *bterm, *it_numel, *it_z;
-  unsigned long long* it_mask;
-  uint32_t *tl_cell, *tl_trips, *tl_id, *ent, *rl_ent, *it_base, *it_si, *it_pass, *it_ntile, *it_nserial, *it_first, *it_mk, *it_rowM, *it_rowE, *it_var, *it_lo, *it_cnt, *rcnt;
-  uint16_t *t_arg, *rl_slot, *place, *idx, *tk0, *tslot;
-};
-
-// Carves the workgroup's LDS (w = nullptr: only counts the bytes).
-__host__ __device__ inline uint32_t carve_fill(unsigned char* w, const FillGeom& g, bool moves, FillLds& L) {
-  uint32_t o = 0;
-  auto take = [&](uint32_t bytes) { unsigned char* p = w + o; o += (bytes + 15u) & ~15u; return p; };
-  L.t_cost = (uint64_t*)take((g.cap + (1u << g.nlay)) * 8);
-  L.bterm = (uint64_t*)take(g.ni * g.bt * 8);
-  L.it_numel = (uint64_t*)take(g.ni * 5 * 8);
-  L.it_z = (uint64_t*)take(g.ni * 8);
-  L.it_mask = (unsigned long long*)take(g.ni * 4 * 8);
-  L.tl_cell = (uint32_t*)take(g.ni * g.kt * 4);
-  L.tl_trips = (uint32_t*)take(g.ni * g.kt * 4);
-  L.tl_id = (uint32_t*)take(g.ni * g.kt * 4);
-  L.ent = (uint32_t*)take(g.ns * 4);
-  L.rl_ent = (uint32_t*)take(g.ns * 4);
-  uint32_t* it = (uint32_t*)take((g.ni * 15 + 1) * 4);
-  L.it_base = it; L.it_si = it + g.ni; L.it_pass = it + 2 * g.ni; L.it_ntile = it + 3 * g.ni; L.it_nserial = it + 4 * g.ni;
-  L.it_mk = it + 5 * g.ni; L.it_rowM = it + 6 * g.ni; L.it_rowE = it + 7 * g.ni; L.it_var = it + 8 * g.ni; L.it_cnt = it + 9 * g.ni;
-  L.it_lo = it + 10 * g.ni; L.it_first = it + 14 * g.ni;
-  L.rcnt = (uint32_t*)take((kMaxRanks + 2) * 4);
-  L.t_arg = (uint16_t*)take(g.cap * 2);
-  L.rl_slot = (uint16_t*)take(g.ns * 2);
-  L.place = (uint16_t*)take(g.ns * 2);
-  L.idx = (uint16_t*)take(g.ni * g.isz * 2);
-  L.tk0 = (uint16_t*)take(moves ? (g.ns + 1) * 2 : 0);
-  L.tslot = (uint16_t*)take(moves ? g.cap * 2 : 0);
-  return o;
-}
-
-// An entry of the workgroup's list: level assignment, dtype bits, item, rank, mixed-radix index.
-__device__ __forceinline__ uint32_t ent_pack(uint32_t e) { return e & 0xFFu; }
-__device__ __forceinline__ uint32_t ent_dt(uint32_t e) { return (e >> 8) & 3u; }
-__device__ __forceinline__ uint32_t ent_item(uint32_t e) { return (e >> 10) & 63u; }
-__device__ __forceinline__ uint32_t ent_rank(uint32_t e) { return (e >> 16) & 15u; }
-__device__ __forceinline__ uint32_t ent_combo(uint32_t e) { return e >> 20; }
-
-// Variant of an entry's c-th task.  Without packed layouts c is the layout bits; with them an item
+// ---------------------------------------------------------------- one diagonal
+// Variant of a unit's c-th entry.  Without packed layouts c is the layout bits; with them an item
 // lists only the layouts that exist: var holds, per operand, the width of its field (2 bits at 2 * i)
-// and the field's position inside c (3 bits at 8 + 4 * i).
+// and the field's position inside c (3 bits at 6 + 3 * i).
 template <bool MOVES>
-__device__ __forceinline__ uint32_t variant_of(const DevParams* __restrict__ P, uint32_t var, uint32_t c, uint32_t dt) {
-  if (!MOVES) return c << P->ndt | dt;
+__device__ __forceinline__ uint32_t variant_of(const FillArgs& A, uint32_t var, uint32_t c, uint32_t dt) {
+  if (!MOVES) return c << A.ndt | dt;
   uint32_t v = dt;
 #pragma unroll
   for (int i = 0; i < 3; i++) {
     const uint32_t w = (var >> (2 * i)) & 3u;
-    if (w) v |= ((c >> ((var >> (8 + 4 * i)) & 7u)) & ((1u << w) - 1u)) << P->lay_bit[i];
+    if (w) v |= ((c >> ((var >> (6 + 3 * i)) & 7u)) & ((1u << w) - 1u)) << A.lay_bit[i];
   }
   return v;
 }
@@ -494,492 +504,719 @@ __device__ __forceinline__ uint32_t variant_of(const DevParams* __restrict__ P, 
 // of two Matmuls (Section 2.1): the first, (m, k, p), into the intermediate, then the second,
 // (m, p, n), out of it; both are entries of the same Matmul table.  The bias-add + ReLU with its
 // own bufferize: per level l in which the intermediate fits next to the operands that live there,
-// the bias add into it plus the ReLU out of it.  rowM, rowE: the shape's first entries in the two
-// tables; z: cost of initialising the intermediate; numel: the item's element counts.
-// Returns the number of candidates evaluated.
-__device__ __forceinline__ uint32_t task_bufferize(const DevParams* __restrict__ P, uint32_t rowM, uint32_t rowE, uint64_t z,
-                                                   const uint64_t* numel, uint32_t pack, uint32_t pass, uint32_t v, Eval& e) {
-  const uint32_t NL = P->NL;
-  const auto level = [&](int i) { return (pack >> P->pack_shift[i]) & 3u; };
-  const auto lay = [&](int i) { return P->lay_bit[i] != kNoBit ? (v >> P->lay_bit[i]) & 1u : 0u; };
+// the bias add into it plus the ReLU out of it.  si: the shape's size indices, a byte each; numel: its
+// element counts.  Returns the number of candidates evaluated.
+__device__ __forceinline__ uint32_t task_bufferize(const FillArgs& A, uint32_t si, const uint64_t* numel, uint32_t pack, uint32_t pass, uint32_t v, Eval& e) {
+  const uint32_t NL = A.NL, i0 = si & 0xFFu, i1 = (si >> 8) & 0xFFu, i2 = (si >> 16) & 0xFFu, i3 = si >> 24;
+  const auto level = [&](int i) { return (pack >> A.pack_shift[i]) & 3u; };
+  const auto lay = [&](int i) { return A.lay_bit[i] != kNoBit ? (v >> A.lay_bit[i]) & 1u : 0u; };
   const auto at = [](uint32_t y, uint32_t bit) { return bit != kNoBit ? y << bit : 0u; };
-  if (P->split) {
+  if (A.split) {
+    const uint32_t rowM = (i1 * A.nsz3 + i3) * A.GM, rowE = (i1 * A.nsz3 + i3) * A.GE;
     const uint32_t l0 = level(0), l1 = level(1), l2 = level(2);
-    const uint32_t va = at(lay(0), P->layM[0]), vr = at(lay(2), P->layE[1]);
+    const uint32_t va = at(lay(0), A.layM[0]), vr = at(lay(2), A.layE[1]);
     uint32_t cnt = 0;
     for (uint32_t l = 0; l < NL; l++) {
       const uint64_t bytes = 4u * (numel[2] + (l0 == l ? numel[0] : 0u) + (l1 == l ? numel[1] : 0u) + (l2 == l ? numel[2] : 0u));
-      if (bytes > P->cap[l]) continue;
-      const uint64_t ca = P->costM[rowM + ((l0 * NL + l1) * NL + l) * P->VM + va];
-      const uint64_t cr = P->costE[rowE + (l * NL + l2) * P->VE + vr];
+      if (bytes > A.P->cap[l]) continue;
+      const uint64_t ca = A.costM[rowM + ((l0 * NL + l1) * NL + l) * A.VM + va];
+      const uint64_t cr = A.costE[rowE + (l * NL + l2) * A.VE + vr];
       if (ca != kInf && cr != kInf) {
-        if (ca + cr >= kLimit) e.ovf = 1; else consider(e, ca + cr, P->buf_id + l);     // each below 2^62: no wrap
+        if (ca + cr >= kLimit) e.ovf = 1; else consider(e, ca + cr, A.buf_id + l);     // each below 2^62: no wrap
       }
       cnt++;
     }
     return cnt;
   }
+  // (the composition's table has this lattice's p list for its k and n lists, and this lattice's k and n lists)
+  const uint32_t rowM = (A.chain ? (i1 * A.nkM + i2) * A.nsz3 + i0 : (i1 * A.nkM + i2 + A.kM_first) * A.nsz3 + i3) * A.GM;
+  const uint32_t rowE = A.chain ? ((i1 * A.nkM + i0) * A.nsz3 + i3) * A.GM : (i1 * A.nszE_n + i3) * A.GE;
   const uint32_t l0 = level(0), l1 = level(1), l2 = level(2), l3 = level(3);
-  const uint32_t xm = ((l0 * NL + l1) * NL + pass) * P->VM + at(lay(0), P->layM[0]) + at(lay(1), P->layM[1]);
-  const uint32_t xe = P->chain ? ((pass * NL + l2) * NL + l3) * P->VM + at(lay(2), P->layM[1]) + at(lay(3), P->layM[2])
-                               : ((pass * NL + l2) * NL + l3) * P->VE + at(lay(3), P->layE[2]);
-  const uint64_t cm = P->costM[rowM + xm], ce = (P->chain ? P->costM : P->costE)[rowE + xe];
+  const uint32_t xm = ((l0 * NL + l1) * NL + pass) * A.VM + at(lay(0), A.layM[0]) + at(lay(1), A.layM[1]);
+  const uint32_t xe = A.chain ? ((pass * NL + l2) * NL + l3) * A.VM + at(lay(2), A.layM[1]) + at(lay(3), A.layM[2])
+                              : ((pass * NL + l2) * NL + l3) * A.VE + at(lay(3), A.layE[2]);
+  const uint64_t* second = A.costE;
+  if (A.chain) second = A.costM;
+  const uint64_t cm = A.costM[rowM + xm], ce = second[rowE + xe];
+  uint32_t zc = A.zero[3];             // (assignments: a conditional of members would select addresses, and copy them to scratch)
+  if (pass == 2) zc = A.zero[2];
+  if (pass == 1) zc = A.zero[1];
+  if (pass == 0) zc = A.zero[0];
+  const uint64_t z = mul_or_limit(zc, numel[4]);
   if (cm != kInf && ce != kInf) {
     const uint64_t sum = z + cm;          // each term <= 2^62: no wrap
-    if (z >= kLimit || sum >= kLimit || sum + ce >= kLimit) e.ovf = 1; else consider(e, sum + ce, P->buf_id);
+    if (z >= kLimit || sum >= kLimit || sum + ce >= kLimit) e.ovf = 1; else consider(e, sum + ce, A.buf_id);
   }
   return 1;
 }
 
-// Exchange inside a quad of lanes (lane ^ 1, lane ^ 2) without going through LDS.
+// The best so far of one run of candidates in the order of their ids.
+struct Best {
+  uint64_t cost;
+  uint32_t id;
+  __device__ __forceinline__ void take(uint64_t cand, uint32_t cand_id, bool fin) {
+    const bool better = fin && cand < cost;
+    cost = better ? cand : cost;
+    id = better ? cand_id : id;
+  }
+};
+
+// The tiles of one entry, those of the dimensions one after the other, kBatch of them at a time in registers.
+// MN: only m and n are tiled.
+template <bool MN>
+struct Tiles {
+  uint32_t n, done, q, at, b1, b2, b3, lo1, lo2, lo3;       // q: entry of the list behind tile `at`; b_d: the first tile of dimension d
+  uint4 st[kBatch];
+  __device__ __forceinline__ void begin(const uint32_t lo[4], uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
+    b1 = c0; b2 = c0 + c1; b3 = b2 + c2; n = b3 + c3;
+    lo1 = lo[1]; lo2 = lo[2]; lo3 = lo[3];
+    done = at = 0;
+    q = MN ? lo1 : lo[0];
+    jump();
+  }
+  __device__ __forceinline__ void jump() {                  // (a dimension without tiles begins where the next one does)
+    if (!MN) q = at == b1 ? lo1 : q;
+    if (!MN) q = at == b2 ? lo2 : q;
+    q = at == b3 ? lo3 : q;
+  }
+  __device__ __forceinline__ void fetch(const TileStep* steps) {
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; u++) {
+      if (at < n) st[u] = *(const uint4*)((const char*)steps + q * 16u);
+      at++; q++;
+      jump();
+    }
+  }
+};
+
+// Entry `cell` of a table; with SMALL its byte offset fits 32 bits.
+template <bool SMALL>
+__device__ __forceinline__ uint64_t at_cell(const uint64_t* table, uint32_t cell) {
+  return SMALL ? *(const uint64_t*)((const char*)table + cell * 8u) : table[cell];
+}
+
+// One entry: a unit and one of its layouts.  Its candidates are read from finished entries of the table (and of the
+// tables that it reads), several in flight.  Microkernels, Moves, the tiles of each dimension and the bufferize come in the
+// order of their ids, so a strictly lower cost is all that has to be tested, but for converting Moves, whose ids lie
+// between the others'.
+// coef: DevParams::mcoef in LDS.  over, over2: bits of finite candidates at 2^62 and above.
+// SMALL: coefficient * elements of every Move is below 2^62 and both fit 32 bits, and so do the table's byte offsets.
+template <bool MOVES, bool SMALL, bool MN>
+__device__ __forceinline__ void fill_entry(const FillArgs& A, const uint2 un, uint32_t c, const uint4* coef, uint32_t& n_rw, uint32_t& ovf) {
+  const uint4* rp = reinterpret_cast<const uint4*>(A.recs) + (size_t)un.x * 5u;
+  const uint4 r0 = rp[0], r1 = rp[1], r2 = rp[2], r3 = rp[3], r4 = rp[4];
+  const uint32_t pack = un.y & 0xFFu, dt = (un.y >> 8) & 3u, pass = (un.y >> 10) & 3u, fit = un.y >> kUnitFit;
+  const uint32_t log2V = A.log2V, nops = A.nops, NL = A.NL;
+  const uint64_t numel[5] = {(uint64_t)r0.y << 32 | r0.x, (uint64_t)r0.w << 32 | r0.z, (uint64_t)r1.y << 32 | r1.x, (uint64_t)r1.w << 32 | r1.z, (uint64_t)r2.y << 32 | r2.x};
+  const uint32_t shape = r2.z, si = r2.w, cnts = r4.z, mk_var = r4.w;
+  const uint32_t tlo[4] = {r3.z, r3.w, r4.x, r4.y};
+  uint32_t src[4], at = pass << log2V;
+#pragma unroll
+  for (uint32_t op = 0; op < 4; op++) {
+    src[op] = op < nops ? (pack >> A.pack_shift[op]) & 3u : 0u;
+    at += src[op] * A.mstride[op];
+  }
+  const uint32_t var = mk_var >> 8;
+  if (MOVES) c |= ((un.y >> 12) & 63u) << A.unit_lay;
+  const uint32_t v = variant_of<MOVES>(A, var, c, dt);
+  const uint32_t cell = shape * A.G + (at | v);
+  uint64_t* const cost = A.cost;
+
+  // tiles, kBatch at a time; the first are requested before the Moves' entries
+  const uint32_t c0 = cnts & 0xFFu, c1 = (cnts >> 8) & 0xFFu, c2 = (cnts >> 16) & 0xFFu, c3 = cnts >> 24;
+  Tiles<MN> tiles;
+  tiles.begin(tlo, MN ? 0u : c0, c1, MN ? 0u : c2, c3);
+  if (!MOVES) tiles.fetch(A.steps);
+
+  Best e{kInf, kNone};
+  uint32_t over = 0, over2 = 0;
+  // microkernels
+  if (mk_var & 0xFFu) {
+    for (uint32_t mm = A.mk_entry[(pack << log2V) + v] & mk_var & 0xFFu; mm; mm &= mm - 1) {
+      const uint32_t m = (uint32_t)__ffs((int)mm) - 1u;
+      Shape H;
+#pragma unroll
+      for (int d = 0; d < 4; d++) H.d[d] = A.P->sizes[d][(si >> (8 * d)) & 0xFFu];
+      const uint64_t ck = mul_or_limit(A.P->mk_cost[m], mk_shape_reps(A.P, H, m));
+      if (ck >= kLimit) ovf |= 1u;
+      e.take(ck, m, ck < kLimit);
+      n_rw++;
+    }
+  }
+
+  // Moves
+  if (!MOVES) {
+    uint64_t sub[4][3][2];
+#pragma unroll
+    for (uint32_t op = 0; op < 4; op++) {
+      if (op >= nops) break;
+      const uint32_t lay = A.lay_xor[op], at0 = cell - src[op] * A.mstride[op];
+#pragma unroll
+      for (uint32_t dst = 0; dst < 3; dst++)
+        if ((fit >> (op * 3 + dst)) & 1u) {
+          const uint32_t to = at0 + dst * A.mstride[op];
+          sub[op][dst][0] = at_cell<SMALL>(cost, to);
+          if (lay) sub[op][dst][1] = at_cell<SMALL>(cost, to ^ lay);
+        }
+    }
+#pragma unroll
+    for (uint32_t op = 0; op < 4; op++) {
+      if (op >= nops) break;
+      const uint32_t lay = A.lay_xor[op];
+      const uint4 ca = coef[op * 8 + src[op] * 2], cb = coef[op * 8 + src[op] * 2 + 1];
+      const uint32_t cf[6] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y};
+      const uint32_t id0 = A.move_base + op * (NL - 1u) * 4u;
+      const uint32_t cv_bit = A.cv_bit[op];                           // the dtype bit that a converting Move clears
+      const bool cv_here = (dt & cv_bit) != 0;
+      n_rw += cv_here ? 2u * cb.z : cb.z;                             // Moves that exist, whatever fits
+      const auto price = [&](uint32_t k, uint32_t extra) {
+        return SMALL ? (uint64_t)(k + extra) * (uint32_t)numel[op] : mul_or_limit((uint64_t)k + extra, numel[op]);
+      };
+#pragma unroll
+      for (uint32_t dst = 0; dst < 3; dst++)
+        if ((fit >> (op * 3 + dst)) & 1u) {
+#pragma unroll
+          for (uint32_t x = 0; x < 2; x++) {
+            if (x && !lay) break;
+            const uint64_t t = sub[op][dst][x];
+            const uint32_t k = cf[dst * 2 + x];
+            const bool fin = (uint32_t)(t >> 32) != ~0u && k != 0;    // 0: no such Move
+            const uint64_t cand = t + price(k, 0);                    // each at most 2^62 when finite: no wrap
+            over |= fin ? (uint32_t)(cand >> 32) : 0u;
+            e.take(cand, id0 + dst * 4u + x * 2u, fin);
+          }
+        }
+      if (cv_bit) {
+        // to the type without the dtype bit; what does not fit there is (INF, NONE)
+        Eval f;
+        f.best = e.cost; f.arg = e.id;
+        for (uint32_t dst = 0; dst < NL - 1u; dst++)
+          for (uint32_t x = 0; x < (lay ? 2u : 1u); x++) {
+            const uint32_t k = dst == 0 ? (x ? cf[1] : cf[0]) : dst == 1 ? (x ? cf[3] : cf[2]) : (x ? cf[5] : cf[4]);
+            if (cv_here && dst < src[op] && k) {
+              const uint64_t t = cost[((cell - (src[op] - dst) * A.mstride[op]) ^ (x ? lay : 0u)) & ~cv_bit];
+              const bool fin = (uint32_t)(t >> 32) != ~0u;
+              const uint64_t cand = t + price(k, A.convert);
+              over |= fin ? (uint32_t)(cand >> 32) : 0u;
+              consider(f, cand, id0 + dst * 4u + x * 2u + 1u, fin);
+            }
+          }
+        e.cost = f.best; e.id = f.arg;
+      }
+    }
+  } else {
+    // priced by the table of alloc-bindings (bind_kernel); xw changes of layout, those that exist for this size
+    const DevParams* __restrict__ P = A.P;
+    const uint32_t yb = P->yb, xw = P->xw, per_op = 6u << (2 * yb), per_size = P->bind_d * per_op;
+    const uint32_t i1 = (si >> 8) & 0xFFu, i2 = (si >> 16) & 0xFFu, i3 = si >> 24;
+#pragma unroll
+    for (uint32_t op = 0; op < 3; op++) {
+      const uint32_t lw = P->lay_w[op], fw = (var >> (2 * op)) & 3u;
+      const uint32_t y0 = fw ? (v >> A.lay_bit[op]) & ((1u << fw) - 1u) : 0u;
+      const uint32_t dt_bit = P->dt_bit[op], bf = dt_bit != kNoBit ? (dt >> dt_bit) & 1u : P->base_bf16[op];
+      const bool can_cv = A.cv_bit[op] != 0;
+      const uint32_t rows = op == 1 ? i2 : i1, cols = op == 0 ? i2 : i3, s = src[op];
+      const uint32_t id0 = A.move_base + op * (NL - 1u) * xw * 2u;
+      n_rw += (s << lw) << (can_cv && bf ? 1u : 0u);
+      for (uint32_t cv = 0; cv < (can_cv ? 2u : 1u); cv++) {
+        const bool plane = !cv || bf;
+        const uint32_t dc = P->bind_d == 3 && bf ? 1u + cv : 0u;
+        const uint64_t* __restrict__ row = P->bind + ((size_t)(op == 2 ? P->nszV * P->nszV : 0u) + rows * P->nszV + cols) * per_size + dc * per_op + ((s * (s - 1u) / 2u) << (2 * yb)) + (y0 << yb);
+        uint64_t b[3][4], t[3][4];
+#pragma unroll
+        for (uint32_t x = 0; x < 4; x++) {
+          if (x >= (1u << lw)) break;
+#pragma unroll
+          for (uint32_t dst = 0; dst < 3; dst++) {
+            // (a packed layout that this size cannot have: no such Spec.  Converted: what does not fit is (INF, NONE))
+            const bool ok = plane && x < (1u << fw) && (cv ? dst < s : (fit >> (op * 3 + dst)) & 1u);
+            b[dst][x] = t[dst][x] = kInf;
+            if (ok) {
+              b[dst][x] = row[(dst << (2 * yb)) + (y0 ^ x)];
+              t[dst][x] = cost[((cell - (s - dst) * A.mstride[op]) ^ (x ? x << A.lay_bit[op] : 0u)) & ~(cv ? A.cv_bit[op] : 0u)];
+            }
+          }
+        }
+#pragma unroll
+        for (uint32_t dst = 0; dst < 3; dst++)
+#pragma unroll
+          for (uint32_t x = 0; x < 4; x++) {
+            if (x >= (1u << lw)) break;
+            const bool fin = (uint32_t)(b[dst][x] >> 32) != ~0u && (uint32_t)(t[dst][x] >> 32) != ~0u;
+            const uint64_t cand = t[dst][x] + b[dst][x];              // each at most 2^62 when finite: no wrap
+            over |= fin ? (uint32_t)(cand >> 32) : 0u;
+            const uint32_t id = id0 + (dst * xw + x) * 2u + cv;
+            if (cv) { Eval f; f.best = e.cost; f.arg = e.id; consider(f, cand, id, fin); e.cost = f.best; e.id = f.arg; }
+            else e.take(cand, id, fin);
+          }
+      }
+    }
+  }
+
+  // tiles: the same entry of a smaller shape
+  if (MOVES) tiles.fetch(A.steps);
+  for (;;) {
+    uint64_t sub[kBatch];
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; u++)
+      if (tiles.done + u < tiles.n) sub[u] = at_cell<SMALL>(cost, cell - tiles.st[u].x);
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; u++)
+      if (tiles.done + u < tiles.n) {
+        const bool fin = (uint32_t)(sub[u] >> 32) != ~0u;
+        const uint32_t a = fin ? tiles.st[u].y : 0u;
+        const uint64_t lo = (uint64_t)a * (uint32_t)sub[u] + A.s;                     // (32 x 32 bits + 32 bits: no wrap)
+        const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);      // bits 32.. of the sum
+        over |= (uint32_t)hi;
+        over2 |= (uint32_t)(hi >> 32);
+        e.take((hi << 32) | (uint32_t)lo, tiles.st[u].z, fin);
+      }
+    tiles.done += kBatch;
+    if (!__any(tiles.done < tiles.n)) break;
+    tiles.fetch(A.steps);
+  }
+  n_rw += r3.y;
+  if (MN && !MOVES && A.has_buf) {
+    Eval f;
+    f.best = e.cost; f.arg = e.id; f.ovf = 0;
+    n_rw += task_bufferize(A, si, numel, pack, pass, v, f);
+    e.cost = f.best; e.id = f.arg;
+    ovf |= f.ovf;
+  }
+
+  cost[cell] = e.cost;
+  A.arg[cell] = (uint16_t)e.id;
+  ovf |= (over >> 30) | over2;
+}
+
+// The least of (cost, id) over eight consecutive lanes (all of them active), in every one of them.
 template <int CTRL>
-__device__ __forceinline__ uint32_t quad_swap(uint32_t x) {
+__device__ __forceinline__ uint32_t lane_swap(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
 }
 template <int CTRL>
-__device__ __forceinline__ void quad_min(Eval& e) {
-  const uint32_t lo = quad_swap<CTRL>((uint32_t)e.best), hi = quad_swap<CTRL>((uint32_t)(e.best >> 32));
-  const uint32_t id = quad_swap<CTRL>(e.arg);
+__device__ __forceinline__ void swap_min(Eval& e) {
+  const uint32_t lo = lane_swap<CTRL>((uint32_t)e.best), hi = lane_swap<CTRL>((uint32_t)(e.best >> 32));
+  const uint32_t id = lane_swap<CTRL>(e.arg);
   consider(e, (uint64_t)hi << 32 | lo, id);
 }
 
+// What a lane of a split entry needs of its operand, in LDS.
+struct alignas(16) OpTab {
+  uint32_t mstride, lay_xor, cv_bit, shift;        // shift: of the level inside the pack (unused operands: a place that is 0)
+};
+
+// The tiles that one of S lanes takes, B of them (S apart) at a time in registers; PAR: the parallel loops over b, m, n
+// after the serial ones.
+template <bool MN, bool PAR, uint32_t S, uint32_t B>
+struct TileShare {
+  uint32_t b1, b2, b3, n_serial, n, o0, o1, o2, o3;
+  uint4 st[B];
+  __device__ __forceinline__ TileShare(const uint4 r3, const uint4 r4, uint32_t cnts, bool active, uint32_t all) {
+    const uint32_t c0 = MN ? 0u : cnts & 0xFFu, c1 = (cnts >> 8) & 0xFFu, c2 = MN ? 0u : (cnts >> 16) & 0xFFu;
+    b1 = c0; b2 = b1 + c1; b3 = b2 + c2; n_serial = b3 + (cnts >> 24);
+    n = active ? PAR ? all : n_serial : 0u;
+    o0 = r3.z; o1 = r3.w - b1; o2 = r4.x - b2; o3 = r4.y - b3;
+  }
+  __device__ __forceinline__ void fetch(const TileStep* steps, uint32_t t0) {
+    const uint32_t p0 = o0, p1 = o1, p2 = o2, p3 = o3, e1 = b1, e2 = b2, e3 = b3;       // (choosing among members would choose among addresses, and keep them in scratch)
+#pragma unroll
+    for (uint32_t u = 0; u < B; u++) {
+      uint32_t t = t0 + u * S;
+      if (t < n) {
+        uint32_t o = p3;
+        if (!MN) { o = t < e3 ? p2 : o; o = t < e2 ? p1 : o; o = t < e1 ? p0 : o; }
+        else o = t < e3 ? p1 : o;
+        if (PAR && t >= n_serial) {
+          t -= n_serial;
+          o = p3 + e3 - e2;
+          o = t < e2 ? p1 : o;
+          o = t < e1 ? p0 : o;
+        }
+        st[u] = *(const uint4*)((const char*)steps + (o + t) * 16u);
+      }
+    }
+  }
+};
+
+// Four consecutive entries of a table.
+struct Quad { uint64_t t[4]; };
+constexpr uint64_t kNoCost = ~0ull >> 1;    // above every finite cost
+template <bool SMALL>
+__device__ __forceinline__ Quad quad_at(const uint64_t* table, uint32_t cell) {
+  const uint4* p = SMALL ? reinterpret_cast<const uint4*>((const char*)table + cell * 8u) : reinterpret_cast<const uint4*>(table + cell);
+  const uint4 a = p[0], b = p[1];
+  return Quad{{(uint64_t)a.y << 32 | a.x, (uint64_t)a.w << 32 | a.z, (uint64_t)b.y << 32 | b.x, (uint64_t)b.w << 32 | b.z}};
+}
+
+// Four entries of one unit, which differ in its two lowest layout bits (and so lie next to each other: no dtype bits),
+// shared by four lanes (all of them active): lane s takes the Moves of operand s and tiles s, s + 4, ....  What does not
+// depend on the layout is worked out once for the four entries: the tiles and their places, the Moves and their prices;
+// and an entry that a Move reads for one of the four with the layout kept serves another with it changed.
+template <bool SMALL, bool MN>
+__device__ __forceinline__ void fill_quad(const FillArgs& A, const uint2 un, uint32_t c, uint32_t s, bool active, const uint4* coef, const OpTab* tab, uint32_t& n_rw, uint32_t& ovf) {
+  constexpr uint32_t kMine = 2;                       // tiles at a time
+  const char* rec = (const char*)A.recs + (size_t)un.x * 80u;
+  const uint4 r3 = reinterpret_cast<const uint4*>(rec)[3], r4 = reinterpret_cast<const uint4*>(rec)[4];
+  const uint2 r2 = reinterpret_cast<const uint2*>(rec)[5];
+  const uint64_t numel = reinterpret_cast<const uint64_t*>(rec)[s];
+  const uint32_t pack = un.y & 0xFFu, pass = (un.y >> 10) & 3u, fit = un.y >> kUnitFit;
+  const uint32_t log2V = A.log2V, nops = A.nops, NL = A.NL;
+  const uint32_t shape = r2.x, si = r2.y, cnts = r4.z, mk_var = r4.w;
+  uint32_t at = pass << log2V;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; i++) if (i < nops) at += ((pack >> A.pack_shift[i]) & 3u) * A.mstride[i];
+  const uint32_t cell = shape * A.G + (at | c);
+  uint64_t* const cost = A.cost;
+  const OpTab my = tab[s];
+  const uint32_t src = s < nops ? (pack >> my.shift) & 3u : 0u;
+  TileShare<MN, false, 4, kMine> tiles(r3, r4, cnts, active, 0u);
+  tiles.fetch(A.steps, s);
+
+  Best e[4];
+#pragma unroll
+  for (int r = 0; r < 4; r++) e[r] = Best{kNoCost, kNone};
+  uint32_t over = 0, over2 = 0;
+  // Moves: an entry that is not finite reads as 2^63 - 1, so with any price added it has bit 63 set and is above kNoCost
+  {
+    const uint32_t my_fit = active ? (fit >> (3u * s)) & 7u : 0u, at0 = cell - src * my.mstride, lay = my.lay_xor, id0 = A.move_base + s * (NL - 1u) * 4u;
+    Quad q[3], x[3];
+#pragma unroll
+    for (uint32_t dst = 0; dst < 3; dst++)
+      if ((my_fit >> dst) & 1u) {
+        q[dst] = quad_at<SMALL>(cost, at0 + dst * my.mstride);
+        if (lay >= 4) x[dst] = quad_at<SMALL>(cost, (at0 + dst * my.mstride) ^ lay);
+      }
+    const uint4 ca = coef[s * 8 + src * 2], cb = coef[s * 8 + src * 2 + 1];
+    const uint32_t cf[6] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y};
+    if (active) n_rw += 4u * cb.z;                                  // Moves that exist, whatever fits
+    const auto add = [&](const Quad& t, uint32_t k, uint32_t id) {
+      // no such Move: a price of 2^63
+      const uint64_t price = SMALL ? (uint64_t)k * (uint32_t)numel : mul_or_limit(k, numel), b = k ? price : 1ull << 63;
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const uint64_t cand = (t.t[r] & kNoCost) + b;
+        over = (int32_t)(cand >> 32) > (int32_t)over ? (uint32_t)(cand >> 32) : over;
+        e[r].take(cand, id, true);
+      }
+    };
+#pragma unroll
+    for (uint32_t dst = 0; dst < 3; dst++)
+      if ((my_fit >> dst) & 1u) {
+        add(q[dst], cf[dst * 2], id0 + dst * 4u);
+        if (lay) {
+          if (lay < 4) {
+            const bool one = lay == 1;
+            x[dst] = Quad{{one ? q[dst].t[1] : q[dst].t[2], one ? q[dst].t[0] : q[dst].t[3], one ? q[dst].t[3] : q[dst].t[0], one ? q[dst].t[2] : q[dst].t[1]}};
+          }
+          add(x[dst], cf[dst * 2 + 1], id0 + dst * 4u + 2u);
+        }
+      }
+  }
+
+  // tiles: the same entries of a smaller shape
+  for (uint32_t t0 = s; __any(t0 < tiles.n); t0 += kMine * 4u) {
+    if (t0 != s) tiles.fetch(A.steps, t0);
+    Quad sub[kMine];
+#pragma unroll
+    for (uint32_t u = 0; u < kMine; u++)
+      if (t0 + u * 4u < tiles.n) sub[u] = quad_at<SMALL>(cost, cell - tiles.st[u].x);
+#pragma unroll
+    for (uint32_t u = 0; u < kMine; u++)
+      if (t0 + u * 4u < tiles.n) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const uint64_t t = sub[u].t[r];
+          const bool fin = (uint32_t)(t >> 32) != ~0u;
+          const uint32_t a = fin ? tiles.st[u].y : 0u;
+          const uint64_t lo = (uint64_t)a * (uint32_t)t + A.s;                          // (32 x 32 bits + 32 bits: no wrap)
+          const uint64_t hi = (uint64_t)a * (uint32_t)(t >> 32) + (lo >> 32);           // bits 32.. of the sum
+          over2 |= (uint32_t)hi >> 30 | (uint32_t)(hi >> 32);
+          e[r].take((hi << 32) | (uint32_t)lo, tiles.st[u].z, fin);
+        }
+      }
+  }
+  if (s == 0 && active) n_rw += 4u * r3.y;
+  if (active && ((mk_var & 0xFFu) | (MN ? A.has_buf : 0u))) {
+    // microkernels and the bufferize: lane s for entry s
+    Eval f;
+    f.best = kInf; f.arg = kNone; f.ovf = 0;
+    if (mk_var & 0xFFu) {
+      for (uint32_t mm = A.mk_entry[(pack << log2V) + c + s] & mk_var & 0xFFu; mm; mm &= mm - 1) {
+        const uint32_t m = (uint32_t)__ffs((int)mm) - 1u;
+        Shape H;
+#pragma unroll
+        for (int d = 0; d < 4; d++) H.d[d] = A.P->sizes[d][(si >> (8 * d)) & 0xFFu];
+        const uint64_t ck = mul_or_limit(A.P->mk_cost[m], mk_shape_reps(A.P, H, m));
+        if (ck >= kLimit) f.ovf = 1; else consider(f, ck, m);
+        n_rw++;
+      }
+    }
+    if (MN && A.has_buf) {
+      const uint64_t* np = reinterpret_cast<const uint64_t*>(rec);
+      const uint64_t all[5] = {np[0], np[1], np[2], np[3], np[4]};
+      n_rw += task_bufferize(A, si, all, pack, pass, c + s, f);
+    }
+    ovf |= f.ovf;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      Eval g;
+      g.best = e[r].cost; g.arg = e[r].id;
+      consider(g, f.best, f.arg, s == (uint32_t)r && f.best != kInf);
+      e[r].cost = g.best; e[r].id = g.arg;
+    }
+  }
+  // the least of the four lanes: lane s keeps entry s
+  Eval best;
+  best.best = kInf; best.arg = kNone;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    Eval g;
+    g.best = e[r].cost; g.arg = e[r].id;
+    swap_min<0xB1>(g);                     // lanes ^ 1
+    swap_min<0x4E>(g);                     // lanes ^ 2
+    best.best = s == (uint32_t)r ? g.best : best.best;
+    best.arg = s == (uint32_t)r ? g.arg : best.arg;
+  }
+  if (active) {
+    cost[cell + s] = best.arg == kNone ? kInf : best.best;
+    A.arg[cell + s] = (uint16_t)best.arg;
+  }
+  ovf |= ((int32_t)over >= (1 << 30) ? 1u : 0u) | over2;
+}
+
+// One entry shared by S lanes (all of them active), eight or, without layouts, four: lane s takes the Moves of operand s & 3
+// that change the layout by s >> 2 (or s >> 2 + 2), and tiles s, s + S, ...; the first also the microkernels and the
+// bufferize.
+constexpr uint32_t split_lanes(bool lay) { return lay ? 8u : 4u; }
+template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
+__device__ __forceinline__ void fill_entry_split(const FillArgs& A, const uint2 un, uint32_t c, uint32_t s, bool active, const uint4* coef, const OpTab* tab, uint32_t& n_rw, uint32_t& ovf) {
+  constexpr uint32_t kMine = 4, S = split_lanes(LAY); // tiles at a time
+  const uint32_t op = s & 3u, x0 = s >> 2;
+  const char* rec = (const char*)A.recs + (size_t)un.x * 80u;
+  const uint4 r3 = reinterpret_cast<const uint4*>(rec)[3], r4 = reinterpret_cast<const uint4*>(rec)[4];
+  const uint2 r2 = reinterpret_cast<const uint2*>(rec)[5];
+  const uint64_t numel = reinterpret_cast<const uint64_t*>(rec)[op];
+  const uint32_t pack = un.y & 0xFFu, dt = (un.y >> 8) & 3u, pass = (un.y >> 10) & 3u, fit = un.y >> kUnitFit;
+  const uint32_t log2V = A.log2V, nops = A.nops, NL = A.NL;
+  const uint32_t shape = r2.x, si = r2.y, cnts = r4.z, mk_var = r4.w;
+  uint32_t at = pass << log2V;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; i++) if (i < nops) at += ((pack >> A.pack_shift[i]) & 3u) * A.mstride[i];
+  const uint32_t var = mk_var >> 8;
+  if (MOVES) c |= ((un.y >> 12) & 63u) << A.unit_lay;
+  const uint32_t v = variant_of<MOVES>(A, var, c, dt);
+  const uint32_t cell = shape * A.G + (at | v);
+  uint64_t* const cost = A.cost;
+  const OpTab my = tab[op];
+  const uint32_t src = op < nops && active ? (pack >> my.shift) & 3u : 0u;
+
+  TileShare<MN, PAR, S, kMine> tiles(r3, r4, cnts, active, r3.y);
+  tiles.fetch(A.steps, s);
+
+  Eval e;
+  e.best = kInf; e.arg = kNone; e.ovf = 0;
+  uint32_t over = 0, over2 = 0;
+  const auto add = [&](uint64_t t, uint64_t b, uint32_t id, bool ok) {        // each at most 2^62 when finite: no wrap
+    const bool fin = ok && (uint32_t)(t >> 32) != ~0u;
+    const uint64_t cand = t + b;
+    over |= fin ? (uint32_t)(cand >> 32) : 0u;
+    consider(e, cand, id, fin);
+  };
+  // Moves
+  const uint32_t my_fit = active ? (fit >> (3u * op)) & 7u : 0u, at0 = cell - src * my.mstride;
+  if (!MOVES) {
+    const bool part = x0 == 0 || (LAY && my.lay_xor != 0);
+    uint64_t sub[3];
+#pragma unroll
+    for (uint32_t dst = 0; dst < 3; dst++)
+      if (part && ((my_fit >> dst) & 1u)) sub[dst] = at_cell<SMALL>(cost, (at0 + dst * my.mstride) ^ (x0 ? my.lay_xor : 0u));
+    const uint4 ca = coef[op * 8 + src * 2], cb = coef[op * 8 + src * 2 + 1];
+    const uint32_t k[3] = {x0 ? ca.y : ca.x, x0 ? ca.w : ca.z, x0 ? cb.y : cb.x};
+    const uint32_t id0 = A.move_base + op * (NL - 1u) * 4u + x0 * 2u;
+    const bool cv_here = (dt & my.cv_bit) != 0;
+    if (x0 == 0 && src) n_rw += cv_here ? 2u * cb.z : cb.z;             // Moves that exist, whatever fits
+    const auto price = [&](uint32_t kk, uint32_t extra) { return SMALL ? (uint64_t)(kk + extra) * (uint32_t)numel : mul_or_limit((uint64_t)kk + extra, numel); };
+#pragma unroll
+    for (uint32_t dst = 0; dst < 3; dst++)
+      if (part && ((my_fit >> dst) & 1u)) add(sub[dst], price(k[dst], 0), id0 + dst * 4u, k[dst] != 0);
+    if (__any(cv_here)) {
+      // to the type without the dtype bit; what does not fit there is (INF, NONE)
+#pragma unroll
+      for (uint32_t dst = 0; dst < 3; dst++)
+        if (part && cv_here && dst < src && k[dst])
+          add(at_cell<SMALL>(cost, ((at0 + dst * my.mstride) ^ (x0 ? my.lay_xor : 0u)) & ~my.cv_bit), price(k[dst], A.convert), id0 + dst * 4u + 1u, true);
+    }
+  } else if (op < 3) {
+    const DevParams* __restrict__ P = A.P;
+    const uint32_t yb = P->yb, xw = P->xw, per_op = 6u << (2 * yb), per_size = P->bind_d * per_op;
+    const uint32_t i1 = (si >> 8) & 0xFFu, i2 = (si >> 16) & 0xFFu, i3 = si >> 24;
+    const uint32_t lw = P->lay_w[op], lb = P->lay_bit[op], fw = (var >> (2 * op)) & 3u, y0 = fw ? (v >> lb) & ((1u << fw) - 1u) : 0u;
+    const uint32_t dt_bit = P->dt_bit[op], bf = dt_bit != kNoBit ? (dt >> dt_bit) & 1u : P->base_bf16[op];
+    const uint32_t rows = op == 1 ? i2 : i1, cols = op == 0 ? i2 : i3;
+    const uint32_t id0 = A.move_base + op * (NL - 1u) * xw * 2u;
+    if (x0 == 0) n_rw += (src << lw) << (my.cv_bit && bf ? 1u : 0u);
+    for (uint32_t cv = 0; cv < 2; cv++) {
+      if (cv && !__any(my.cv_bit && bf)) break;
+      const bool plane = !cv || (my.cv_bit && bf);
+      const uint32_t dc = P->bind_d == 3 && bf ? 1u + cv : 0u;
+      const uint64_t* __restrict__ row = P->bind + ((size_t)(op == 2 ? P->nszV * P->nszV : 0u) + rows * P->nszV + cols) * per_size + dc * per_op + ((src * (src - 1u) / 2u) << (2 * yb)) + (y0 << yb);
+      uint64_t b[3][2], t[3][2];
+#pragma unroll
+      for (uint32_t u = 0; u < 2; u++) {
+        const uint32_t x = x0 + 2u * u;
+#pragma unroll
+        for (uint32_t dst = 0; dst < 3; dst++) {
+          // (a packed layout that this size cannot have: no such Spec.  Converted: what does not fit is (INF, NONE))
+          const bool ok = plane && x < (1u << fw) && (cv ? dst < src : (my_fit >> dst) & 1u);
+          b[dst][u] = t[dst][u] = kInf;
+          if (ok) {
+            b[dst][u] = row[(dst << (2 * yb)) + (y0 ^ x)];
+            t[dst][u] = cost[((at0 + dst * my.mstride) ^ (x ? x << lb : 0u)) & ~(cv ? my.cv_bit : 0u)];
+          }
+        }
+      }
+#pragma unroll
+      for (uint32_t dst = 0; dst < 3; dst++)
+#pragma unroll
+        for (uint32_t u = 0; u < 2; u++) add(t[dst][u], b[dst][u], id0 + (dst * xw + x0 + 2u * u) * 2u + cv, (uint32_t)(b[dst][u] >> 32) != ~0u);
+    }
+  }
+
+  // tiles: the same entry of a smaller shape; a parallel loop's body is an entry of the serial table
+  for (uint32_t t0 = s; __any(t0 < tiles.n); t0 += kMine * S) {
+    if (t0 != s) tiles.fetch(A.steps, t0);
+    uint64_t sub[kMine];
+#pragma unroll
+    for (uint32_t u = 0; u < kMine; u++)
+      if (t0 + u * S < tiles.n) {
+        const uint64_t* table = cost;
+        if (PAR && t0 + u * S >= tiles.n_serial) table = A.costM;
+        sub[u] = at_cell<SMALL>(table, cell - tiles.st[u].x);
+      }
+#pragma unroll
+    for (uint32_t u = 0; u < kMine; u++)
+      if (t0 + u * S < tiles.n) {
+        const bool loop = PAR && t0 + u * S >= tiles.n_serial, fin = (uint32_t)(sub[u] >> 32) != ~0u;
+        const uint32_t a = fin ? (loop ? tiles.st[u].w : tiles.st[u].y) : 0u;
+        const uint64_t lo = (uint64_t)a * (uint32_t)sub[u] + (loop ? A.sync : A.s);
+        const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);      // bits 32.. of the sum
+        over |= (uint32_t)hi;
+        over2 |= (uint32_t)(hi >> 32);
+        consider(e, (hi << 32) | (uint32_t)lo, tiles.st[u].z + (loop ? A.par_shift : 0u), fin);
+      }
+  }
+  if (s == 0 && active) {
+    n_rw += r3.y;                          // serial and parallel loops
+    if (mk_var & 0xFFu) {
+      for (uint32_t mm = A.mk_entry[(pack << log2V) + v] & mk_var & 0xFFu; mm; mm &= mm - 1) {
+        const uint32_t m = (uint32_t)__ffs((int)mm) - 1u;
+        Shape H;
+#pragma unroll
+        for (int d = 0; d < 4; d++) H.d[d] = A.P->sizes[d][(si >> (8 * d)) & 0xFFu];
+        const uint64_t ck = mul_or_limit(A.P->mk_cost[m], mk_shape_reps(A.P, H, m));
+        if (ck >= kLimit) ovf |= 1u; else consider(e, ck, m);
+        n_rw++;
+      }
+    }
+    if (MN && !MOVES && A.has_buf) {
+      const uint64_t* np = reinterpret_cast<const uint64_t*>(rec);
+      const uint64_t all[5] = {np[0], np[1], np[2], np[3], np[4]};
+      n_rw += task_bufferize(A, si, all, pack, pass, v, e);
+    }
+  }
+  swap_min<0xB1>(e);                       // lanes ^ 1
+  swap_min<0x4E>(e);                       // lanes ^ 2
+  if (S == 8) swap_min<0x141>(e);          // the other four of eight (mirrored: the lanes of four agree by now)
+  if (s == 0 && active) {
+    cost[cell] = e.best;
+    A.arg[cell] = (uint16_t)e.arg;
+  }
+  ovf |= e.ovf | (over >> 30) | over2;
+}
+
+// (rewrites evaluated: the only sums over workgroups)
 __device__ __forceinline__ void flush_counters(Counters* __restrict__ ctr, uint32_t n_rw, uint32_t ovf) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) n_rw += __shfl_down(n_rw, d, 64);
   if ((threadIdx.x & 63u) == 0 && n_rw) atomicAdd(&ctr->n_rewrites[blockIdx.x % kCtrSlots], (unsigned long long)n_rw);
-  if (ovf) atomicOr(&ctr->overflow, ovf);
+  if (ovf) atomicOr(&ctr->overflow, 1u);
 }
 
-// One bundle (starts: the level's bundle starts; nullptr: an item each) per workgroup of T threads.
-// LAY: the lattice has layout bits.  MOVES: the Matmul whose Moves are Move Specs.
-// Bound by instruction issue on levels with many items (counters: 1,890 vector lane-instructions per
-// task in config 5's F, 3,250 in config 2; the vector units issue half of the time that the launches
-// of 128 threads take) and by the chain of memory and LDS round trips on the others (a fifth of the
-// time there; 9 us for one item of 4 tasks: records 2.4, lists 2, tiles 2.3, ranks 1.8).  Fill
-// times against one item per wave without bundles or records: config 2 1.49 -> 0.77 ms, config 3
-// 0.69 -> 0.60, config 4 0.80 -> 0.73, config 5's F 2.22 -> 2.12, config 12's Matmul, which then was
-// a lane per Spec with three gathers per Move, 5.04 -> 2.16.
-// T: 512 for a wide item (100 registers would leave 2 instead of 3 workgroups on a unit, hence the
-// bound), 256 on levels short of bundles, else 128 (64: config 4 +9 %, F +5 %).  1024 where the bundles of a level are no
-// more than the compute units and have 128 tasks and more: then the time is one bundle's, most of it the chain of ranks
-// (config 3's levels of up to 12 bundles 26 -> 19 us, the solve 773 -> 703 us, config 4's 1102 -> 1065; with fewer tasks
-// 256 threads are faster, 11 against 13 us, and so they are with Move Specs, config 12's solve 3166 against 3220).
-template <int T, bool LAY, bool MOVES>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 5 : 4))) void fill_kernel(
-    const DevParams* __restrict__ P, const FillGeom g, const uint32_t* __restrict__ items, const uint32_t* __restrict__ starts,
-    const ShapeRec* __restrict__ recs, const unsigned long long* __restrict__ masks, uint64_t* __restrict__ cost, uint16_t* __restrict__ arg,
-    Counters* __restrict__ ctr) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  FillLds L;
-  carve_fill(smem, g, MOVES, L);
-  const uint32_t tid = threadIdx.x, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-  const uint32_t i0 = starts ? starts[blockIdx.x] : blockIdx.x, n_it = starts ? starts[blockIdx.x + 1] - i0 : 1u;
-  const uint32_t npass = P->npass, nops = P->nops, ndt = P->ndt, ndp = 1u << ndt, nwp = P->nwp, nw = ndp * nwp, log2V = P->log2V;
-  const uint32_t nlay = g.nlay, psz = 1u << (2 * nops);
-  constexpr uint32_t kXw = LAY && !MOVES ? 2u : 1u;      // Move-cost entries per (operand, source, destination)
+// The operands' constants to LDS, and the Move coefficients.
+__device__ __forceinline__ void load_tabs(const FillArgs& A, uint4* coef, OpTab* tab) {
+  if (threadIdx.x < 32) coef[threadIdx.x] = reinterpret_cast<const uint4*>(A.P->mcoef)[threadIdx.x];
+  if (threadIdx.x < 4) {
+    const DevParams* P = A.P;
+    const uint32_t i = threadIdx.x;
+    tab[i] = OpTab{P->mstride[i], i < A.nops && P->lay_bit[i] != kNoBit ? 1u << P->lay_bit[i] : 0u, P->can_convert[i] && P->dt_bit[i] != kNoBit ? 1u << P->dt_bit[i] : 0u, P->pack_shift[i]};
+  }
+  __syncthreads();
+}
+
+// A diagonal: a lane per entry, the layouts of a unit in consecutive lanes (1 << unit_lay of them).
+template <bool MOVES, bool SMALL, bool MN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void fill_entry_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
+  __shared__ uint4 coef[32];
+  __shared__ OpTab tab[4];
+  const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+  const uint32_t u = (uint32_t)(t >> A.unit_lay);
+  const uint2 un = units[u < n_units ? u : 0u];
+  load_tabs(A, coef, tab);
   uint32_t n_rw = 0, ovf = 0;
-  if (n_it > g.ni) { if (tid == 0) atomicOr(&ctr->overflow, 2u); return; }       // the work lists guarantee this cannot happen
+  if (u < n_units) fill_entry<MOVES, SMALL, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 1u), coef, n_rw, ovf);
+  flush_counters(A.ctr, n_rw, ovf);
+}
 
-  // ---- the items, one per lane of the first wave ----
-  if (wave == 0) {
-    uint32_t cnt = 0;
-    if (lane < n_it) {
-      const uint32_t item = items[i0 + lane];
-      unsigned long long m[4] = {0, 0, 0, 0};
-#pragma unroll
-      for (int w = 0; w < 4; w++) if ((uint32_t)w < nw) m[w] = masks[(size_t)item * nw + w];
-      const uint32_t si_i = item / npass, pass = item - si_i * npass;
-      const ShapeRec R = recs[si_i];
-      uint32_t si[4];
-#pragma unroll
-      for (int d = 0; d < 4; d++) si[d] = (R.si >> (8 * d)) & 0xFFu;
-#pragma unroll
-      for (int w = 0; w < 4; w++) { L.it_mask[lane * 4 + w] = m[w]; cnt += (uint32_t)__popcll(m[w]); }
-      L.it_pass[lane] = pass; L.it_base[lane] = R.shape * P->G + (pass << log2V);
-      L.it_si[lane] = R.si; L.it_nserial[lane] = R.n_serial; L.it_ntile[lane] = R.n_tile; L.it_mk[lane] = R.mk_var & 0xFFu;
-      L.it_cnt[lane] = R.tile_cnt;
-#pragma unroll
-      for (int d = 0; d < 4; d++) L.it_lo[lane * 4 + d] = R.tile_lo[d];
-#pragma unroll
-      for (int i = 0; i < 5; i++) L.it_numel[lane * 5 + i] = R.numel[i];
-      uint32_t rowM = 0, rowE = 0;
-      uint64_t z = 0;
-      if (P->kind == kKindF) {
-        const uint32_t zc = pass == 0 ? P->zero[0] : pass == 1 ? P->zero[1] : pass == 2 ? P->zero[2] : P->zero[3];
-        z = mul_or_limit(zc, R.numel[4]);
-        if (P->chain) {
-          // the table's k and n lists are this lattice's p list (and k and n lists)
-          rowM = ((si[1] * P->nkM + si[2]) * P->nsz[3] + si[0]) * P->GM;
-          rowE = ((si[1] * P->nkM + si[0]) * P->nsz[3] + si[3]) * P->GM;
-        } else {
-          rowM = ((si[1] * P->nkM + si[2] + P->kM_first) * P->nsz[3] + si[3]) * P->GM;
-          rowE = (si[1] * P->nszE_n + si[3]) * P->GE;
-        }
-      } else if (P->split) {
-        const uint32_t sh = si[1] * P->nsz[3] + si[3];
-        rowM = sh * P->GM; rowE = sh * P->GE;
-      }
-      L.it_rowM[lane] = rowM; L.it_rowE[lane] = rowE; L.it_z[lane] = z;
-      // (unpacked: widths at 2 * i, positions at 8 + 4 * i, their sum at 24)
-      const uint32_t pv = R.mk_var >> 8;
-      L.it_var[lane] = (pv & 0x3Fu) | (pv >> 6 & 7u) << 8 | (pv >> 9 & 7u) << 12 | (pv >> 12 & 7u) << 16 | (pv >> 15) << 24;
-    }
-    uint32_t incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t o = __shfl_up(incl, d, 64);
-      if ((int)lane >= d) incl += o;
-    }
-    if (lane < n_it) L.it_first[lane] = incl - cnt;
-    if (lane == 63) L.it_first[n_it] = incl;
-    if (lane < kMaxRanks + 2) L.rcnt[lane] = 0;
-  }
-  for (uint32_t i = tid; i < n_it * g.isz / 2; i += T) reinterpret_cast<uint32_t*>(L.idx)[i] = g.ns | g.ns << 16;
-  if (tid < (1u << nlay)) L.t_cost[(MOVES ? g.cap : g.ns << nlay) + tid] = kInf;
-  if (MOVES && tid == 0) L.tk0[g.ns] = (uint16_t)g.cap;
-  __syncthreads();
-  const uint32_t n_ent = L.it_first[n_it];
-  if (n_ent > g.ns) { if (tid == 0) atomicOr(&ctr->overflow, 2u); return; }      // (nor this)
+// Four lanes per four entries (the lattice has two layout bits and more, and no dtype bits).
+template <bool SMALL, bool MN>
+__global__ __launch_bounds__(256) void fill_quad_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
+  __shared__ uint4 coef[32];
+  __shared__ OpTab tab[4];
+  const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+  const uint32_t u = (uint32_t)(t >> A.unit_lay);
+  const uint2 un = units[u < n_units ? u : 0u];
+  load_tabs(A, coef, tab);
+  uint32_t n_rw = 0, ovf = 0;
+  fill_quad<SMALL, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 4u), (uint32_t)t & 3u, u < n_units, coef, tab, n_rw, ovf);
+  flush_counters(A.ctr, n_rw, ovf);
+}
 
-  // (what the next three steps read of the parameters does not depend on the items: it is requested
-  // together with the first tile rewrites, so that one trip to memory serves all of them)
-  auto tile_at = [&](uint32_t i, uint32_t e0, uint32_t& td) -> uint32_t {       // entry of the tile list behind LDS place i
-    const uint32_t j = i / g.kt, e = e0 + (i - j * g.kt), cnts = L.it_cnt[j];
-    uint32_t first = 0, q = ~0u;
-    td = 0;
-    if (e >= L.it_ntile[j]) return q;
-#pragma unroll
-    for (int d = 0; d < 4; d++) {
-      const uint32_t cnt = P->tile_dim_ok[d] ? (cnts >> (8 * d)) & 0xFFu : 0u;
-      if (e >= first && e < first + cnt) { td = d; q = L.it_lo[j * 4 + d] + (e - first); }
-      first += cnt;
-    }
-    if (P->par) {        // the parallel loops over b, m, n follow
-#pragma unroll
-      for (int d = 0; d < 4; d++) {
-        if (d == 2) continue;
-        const uint32_t cnt = (cnts >> (8 * d)) & 0xFFu;
-        if (e >= first && e < first + cnt) { td = 4 + d; q = L.it_lo[j * 4 + d] + (e - first); }
-        first += cnt;
-      }
-    }
-    return q;
-  };
-  auto put_tile = [&](uint32_t i, uint32_t td, const TileEntry& te) {           // first cell of the child's item, trips, id
-    const uint32_t j = i / g.kt, si = L.it_si[j], d = td & 3u, sj = (si >> (8 * d)) & 0xFFu;
-    const uint32_t stride = d == 0 ? P->shape_stride[0] : d == 1 ? P->shape_stride[1] : d == 2 ? P->shape_stride[2] : P->shape_stride[3];
-    L.tl_cell[i] = L.it_base[j] - (sj - te.jt) * stride * P->G;                 // the serial table has the same geometry
-    L.tl_trips[i] = td >= 4 ? (te.trips + P->threads - 1) / P->threads : te.trips;
-    L.tl_id[i] = (td >= 4 ? P->par_base : P->tile_base) + d * P->maxs + te.jt;
-  };
-  uint32_t td0 = 0;
-  const uint32_t q_tile0 = tid < n_it * g.kt ? tile_at(tid, 0, td0) : ~0u;
-  const TileEntry te0 = P->tiles[q_tile0 == ~0u ? 0u : q_tile0];
-  const uint32_t pos0 = (wave % nw % nwp) * 64u + lane, pe0 = P->pos_entry[pos0 < kMaxCombo ? pos0 : 0u];
+// Eight lanes per entry, or four without layouts.
+template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
+__global__ __launch_bounds__(256) void fill_split_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
+  constexpr uint32_t lgS = LAY ? 3u : 2u;
+  __shared__ uint4 coef[32];
+  __shared__ OpTab tab[4];
+  const uint64_t t = ((uint64_t)blockIdx.x * 256u + threadIdx.x) >> lgS;
+  const uint32_t u = (uint32_t)(t >> A.unit_lay);
+  const uint2 un = units[u < n_units ? u : 0u];
+  load_tabs(A, coef, tab);
+  uint32_t n_rw = 0, ovf = 0;
+  fill_entry_split<LAY, MOVES, SMALL, PAR, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 1u), threadIdx.x & ((1u << lgS) - 1u), u < n_units, coef, tab, n_rw, ovf);
+  flush_counters(A.ctr, n_rw, ovf);
+}
 
-  // ---- the admissible entries: by item, and counted by rank ----
-  for (uint32_t jw = wave; jw < n_it * nw; jw += T / 64) {
-    const uint32_t j = jw / nw, w = jw - j * nw, dt = w / nwp, pos = (w - dt * nwp) * 64u + lane;
-    const unsigned long long m = L.it_mask[j * 4 + w];
-    uint32_t slot = L.it_first[j];
-#pragma unroll
-    for (uint32_t u = 0; u < 3; u++) if (u < w) slot += (uint32_t)__popcll(L.it_mask[j * 4 + u]);
-    if ((m >> lane) & 1ull) {
-      slot += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-      const uint32_t pe = jw == wave ? pe0 : P->pos_entry[pos], pack = pe & 0xFFu, rank = (pe >> 8) & 0xFFu;       // pack | rank << 8 | mixed-radix index << 16
-      L.ent[slot] = pack | dt << 8 | j << 10 | rank << 16 | (pe >> 16) << 20;
-      L.idx[j * g.isz + dt * psz + pack] = (uint16_t)slot;
-      L.place[slot] = (uint16_t)atomicAdd(&L.rcnt[rank], 1u);                       // its place among the rank's entries
-    }
-  }
-  // Move costs: coefficient * elements per (converted, operand, source level - 1, destination level, transposed),
-  // 0 = no such Move; of a Matmul whose Moves are Specs: what bind_kernel tabulated for the operand's size
-  if (MOVES) {
-    const uint32_t per_op = 6u << (2 * P->yb), per_size = P->bind_d * per_op;
-    for (uint32_t i = tid; i < n_it * g.bt; i += T) {
-      const uint32_t j = i / g.bt, r = i - j * g.bt, dc = r / (3u * per_op), q = r - dc * 3u * per_op, op = q / per_op;
-      const uint32_t si = L.it_si[j], sm = (si >> 8) & 0xFFu, sk = (si >> 16) & 0xFFu, sn = si >> 24;
-      const uint32_t rows = op == 1 ? sk : sm, cols = op == 0 ? sk : sn;
-      L.bterm[i] = P->bind[((size_t)(op == 2 ? P->nszV * P->nszV : 0u) + rows * P->nszV + cols) * per_size + dc * per_op + (q - op * per_op)];
-    }
-  } else {
-    for (uint32_t i = tid; i < n_it * g.bt; i += T) {
-      const uint32_t j = i / g.bt, r = i - j * g.bt, x = kXw == 2 ? r & 1u : 0u, sd = (r / kXw) % 9u, co = (r / kXw) / 9u, cv = co / nops, op = co - cv * nops;
-      const uint32_t src = sd / 3u + 1u, dst = sd - (src - 1u) * 3u;
-      const uint32_t c = dst < src ? P->mcoef[op][src][dst][x] : 0u;
-      L.bterm[i] = c ? mul_or_limit((uint64_t)c + (cv ? P->convert : 0u), L.it_numel[j * 5 + op]) : 0;
-    }
-  }
-  if (q_tile0 != ~0u) put_tile(tid, td0, te0);
-  auto stage_tiles = [&](uint32_t e0, uint32_t i0) {
-    for (uint32_t i = i0; i < n_it * g.kt; i += T) {
-      uint32_t td;
-      const uint32_t q = tile_at(i, e0, td);
-      if (q != ~0u) put_tile(i, td, P->tiles[q]);
-    }
-  };
-  stage_tiles(0, tid + T);
-  __syncthreads();
-
-  // every wave keeps the ranks' first places in its lanes (lane r: rank r)
-  uint32_t rank_first;
-  {
-    const uint32_t c = lane < P->nranks ? L.rcnt[lane] : 0u;
-    uint32_t incl = c;
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) {
-      const uint32_t o = __shfl_up(incl, d, 64);
-      if ((int)lane >= d) incl += o;
-    }
-    rank_first = lane < P->nranks ? incl - c : n_ent;
-  }
-  // the entries in rank order (used after the tile phase)
-  for (uint32_t s0 = 0; s0 < n_ent; s0 += T) {
-    const uint32_t s = s0 + tid, en = L.ent[s < n_ent ? s : 0u];
-    const uint32_t at = __shfl(rank_first, ent_rank(en), 64);
-    if (s < n_ent) { const uint32_t k = at + L.place[s]; L.rl_ent[k] = en; L.rl_slot[k] = (uint16_t)s; }
-  }
-  // tasks: the entries' layouts
-  uint32_t n_task;
-  if (MOVES) {
-    if (wave == 0) {
-      uint32_t run = 0;
-      for (uint32_t s0 = 0; s0 < n_ent; s0 += 64) {
-        const uint32_t s = s0 + lane, c = s < n_ent ? 1u << (L.it_var[ent_item(L.ent[s])] >> 24) : 0u;
-        uint32_t incl = c;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const uint32_t o = __shfl_up(incl, d, 64);
-          if ((int)lane >= d) incl += o;
-        }
-        if (s < n_ent) L.tk0[s] = (uint16_t)(run + incl - c);
-        run += __shfl(incl, 63, 64);
-      }
-      if (lane == 0) L.rcnt[kMaxRanks + 1] = run;
-    }
-    __syncthreads();
-    n_task = L.rcnt[kMaxRanks + 1];
-    if (n_task > g.cap) { if (tid == 0) atomicOr(&ctr->overflow, 2u); return; }
-    for (uint32_t s = tid; s < n_ent; s += T) {
-      const uint32_t c = 1u << (L.it_var[ent_item(L.ent[s])] >> 24), t0 = L.tk0[s];
-      for (uint32_t k = 0; k < c; k++) L.tslot[t0 + k] = (uint16_t)s;
-    }
-    __syncthreads();
-  } else {
-    n_task = n_ent << nlay;
-  }
-
-  // ---- 1. tile and bufferize candidates of every task (sub-Specs of other shapes / tables: final) ----
-  uint32_t max_tile = 0;
-  for (uint32_t j = 0; j < n_it; j++) { const uint32_t t = L.it_ntile[j]; max_tile = t > max_tile ? t : max_tile; }
-  max_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)max_tile);          // the same in every lane: kept as a scalar
-  const bool has_buf = !MOVES && (P->kind == kKindF || P->split);
-  const uint64_t s_serial = P->s, s_par = P->sync;
-  const uint64_t* __restrict__ serial = P->costM;
-  // few tasks: a quad of lanes per task, every fourth candidate each (fewer reads one after the other)
-  const uint32_t lg = n_task * 4 <= T ? 2u : 0u, sub4 = lg ? tid & 3u : 0u;
-  for (uint32_t e0 = 0; e0 == 0 || e0 < max_tile; e0 += g.kt) {
-    if (e0) { __syncthreads(); stage_tiles(e0, tid); __syncthreads(); }
-    for (uint32_t qb = 0; qb < n_task; qb += T >> lg) {
-      const uint32_t q0 = qb + (tid >> lg);
-      if (!lg && q0 >= n_task) break;
-      const uint32_t q = q0 < n_task ? q0 : 0u;
-      const uint32_t slot = MOVES ? (uint32_t)L.tslot[q] : q >> nlay, c = MOVES ? q - L.tk0[slot] : q & ((1u << nlay) - 1u);
-      const uint32_t en = L.ent[slot], j = ent_item(en);
-      const uint32_t v = variant_of<MOVES>(P, MOVES ? L.it_var[j] : 0u, c, ent_dt(en));
-      const uint32_t off = ((ent_combo(en) * npass) << log2V) + v;
-      const uint32_t all = L.it_ntile[j], n_here = all <= e0 ? 0u : all - e0 < g.kt ? all - e0 : g.kt;
-      const uint32_t n_ser = L.it_nserial[j] > e0 ? L.it_nserial[j] - e0 : 0u;     // from here on parallel loops
-      Eval e;
-      e.best = kInf; e.arg = kNone; e.ovf = 0;
-      if (e0 && sub4 == 0) { e.best = L.t_cost[q]; e.arg = L.t_arg[q]; }
-      // trips * sub + s in 96 bits; reaching 2^62 = overflow.  A parallel loop's body is the
-      // serial-only Spec (read from the serial table), its constant the synchronisation cost.
-      for (uint32_t t0 = sub4; t0 < n_here; t0 += kBatch << lg) {
-        uint64_t sub[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; u++) {
-          const uint32_t t = t0 + (u << lg);
-          sub[u] = kInf;
-          if (t < n_here) sub[u] = (t >= n_ser ? serial : cost)[L.tl_cell[j * g.kt + t] + off];     // no request for a candidate that is not there
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; u++) {
-          const uint32_t t = t0 + (u << lg);
-          if (t < n_here) {
-            const bool fin = (uint32_t)(sub[u] >> 32) != ~0u;
-            const uint32_t a = L.tl_trips[j * g.kt + t];
-            const uint64_t lo = (uint64_t)a * (uint32_t)sub[u];
-            const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);   // bits 32.. of the product
-            const uint64_t cand = ((hi << 32) | (uint32_t)lo) + (t >= n_ser ? s_par : s_serial);
-            const bool over = fin & (((hi >> 30) != 0) | (cand >= kLimit));
-            e.ovf |= over ? 1u : 0u;
-            const bool better = fin & !over & (cand < e.best);       // ids ascend, also over the stretches of kt tiles
-            e.best = better ? cand : e.best;
-            e.arg = better ? L.tl_id[j * g.kt + t] : e.arg;
-          }
-        }
-      }
-      if (has_buf && e0 + g.kt >= max_tile && sub4 == 0) {       // after the last tiles: its id is above theirs
-        const uint32_t nb = task_bufferize(P, L.it_rowM[j], L.it_rowE[j], L.it_z[j], L.it_numel + j * 5, ent_pack(en), L.it_pass[j], v, e);
-        if (q0 < n_task) n_rw += nb;
-      }
-      if (lg) { quad_min<0xB1>(e); quad_min<0x4E>(e); }
-      if (q0 < n_task) {
-        ovf |= e.ovf;
-        if (sub4 == 0) {
-          L.t_cost[q] = e.best; L.t_arg[q] = (uint16_t)e.arg;
-          if (e0 == 0) n_rw += all;
-        }
-      }
-    }
-  }
-  __syncthreads();
-
-  // ---- 2. rank by rank: Moves, microkernels, the parked tile/bufferize candidate ----
-  // Four lanes per task, one operand each (its Moves to every lower level and layout); the lanes'
-  // candidates are then reduced to the lexicographic minimum of (cost, id).  All tables are indexed
-  // directly; a level assignment that does not fit reads the tasks of entry ns (INF).  On levels
-  // short of work (T = 256) the chain of ranks is what counts, and eight lanes per task halve a
-  // lane's work in each: lane 4 * x + op takes the changes of layout x and x + 2.  Elsewhere it is
-  // the instructions, most of which a lane spends whatever its number of candidates.
-  constexpr uint32_t kTaskLanes = LAY && (T == 256 || T == 1024) ? 8u : 4u, kXLanes = kTaskLanes / 4u;
-  const uint32_t op = tid & 3u, x = kXLanes == 2 ? (tid >> 2) & 1u : 0u;
-  const uint32_t my_shift = op == 0 ? P->pack_shift[0] : op == 1 ? P->pack_shift[1] : op == 2 ? P->pack_shift[2] : P->pack_shift[3];
-  const uint32_t my_lay = op == 0 ? P->lay_bit[0] : op == 1 ? P->lay_bit[1] : op == 2 ? P->lay_bit[2] : P->lay_bit[3];
-  const uint32_t my_dt = op == 0 ? P->dt_bit[0] : op == 1 ? P->dt_bit[1] : op == 2 ? P->dt_bit[2] : P->dt_bit[3];
-  const bool my_cv = (op == 0 ? P->can_convert[0] : op == 1 ? P->can_convert[1] : op == 2 ? P->can_convert[2] : P->can_convert[3]) != 0 && my_dt != kNoBit;
-  const uint32_t base_bf = op == 0 ? P->base_bf16[0] : op == 1 ? P->base_bf16[1] : op == 2 ? P->base_bf16[2] : P->base_bf16[3];
-  const uint32_t my_lw = op == 0 ? P->lay_w[0] : op == 1 ? P->lay_w[1] : op == 2 ? P->lay_w[2] : P->lay_w[3];
-  const bool my_part = op < nops && (x == 0 || my_lay != kNoBit);
-  const uint32_t xw = MOVES ? P->xw : 2u, id0 = P->move_base + op * (P->NL - 1u) * xw * 2u + x * 2u;
-  const uint32_t yb = MOVES ? P->yb : 0u, nranks = P->nranks, bind_d = MOVES ? P->bind_d : 1u;
-  const uint32_t my_fb = my_lay != kNoBit ? my_lay - ndt : 0u, op_row = op * 9u * kXw + x;
-  // (with packed layouts the entries of a rank may have different numbers of tasks: lanes for the most of any item)
-  uint32_t lays = nlay;
-  if (MOVES) {
-    lays = 0;
-    for (uint32_t j = 0; j < n_it; j++) { const uint32_t w = L.it_var[j] >> 24; lays = w > lays ? w : lays; }
-  }
-  for (uint32_t r = 0; r < nranks; r++) {
-    const uint32_t r0 = lane_of(rank_first, r), r1 = lane_of(rank_first, r + 1);
-    if (r0 == r1) continue;
-    const uint32_t n_here = (r1 - r0) << lays;
-    for (uint32_t qb = 0; qb < n_here; qb += T / kTaskLanes) {
-      const uint32_t qq = qb + tid / kTaskLanes;
-      bool active = qq < n_here;
-      const uint32_t k = r0 + (active ? qq >> lays : 0u);
-      const uint32_t slot = L.rl_slot[k], en = L.rl_ent[k], j = ent_item(en), pack = ent_pack(en), dt = ent_dt(en);
-      uint32_t c = active ? qq & ((1u << lays) - 1u) : 0u, var = 0;
-      if (MOVES) {
-        var = L.it_var[j];
-        active = active && c < (1u << (var >> 24));
-        c = active ? c : 0u;
-      }
-      const uint32_t q = MOVES ? L.tk0[slot] + c : (slot << nlay) + c;
-      Eval parked;
-      parked.best = L.t_cost[q]; parked.arg = L.t_arg[q];
-      const uint32_t mk_shape = L.it_mk[j];
-      Eval e;
-      e.best = kInf; e.arg = kNone;
-      uint32_t hi_or = 0;           // OR of the high words of all finite Move candidates
-      const uint32_t src = (pack >> my_shift) & 3u;
-      const bool on = active && my_part && src != 0;
-      if (__any(on)) {
-        const uint32_t src1 = on ? src - 1u : 0u, at = j * g.isz + pack;
-        const uint32_t bf = my_dt != kNoBit ? (dt >> my_dt) & 1u : base_bf;
-        for (uint32_t cv = 0; cv < ndp && cv < 2u; cv++) {             // as it is, then converted
-          const bool plane = on && (cv == 0 || (my_cv && bf));
-          if (cv && !__any(plane)) break;
-          const uint32_t dt2 = cv ? dt & ~(1u << (my_dt & 31u)) : dt;
-          uint32_t to[3];
-#pragma unroll
-          for (uint32_t dst = 0; dst < 3; dst++) to[dst] = L.idx[at + dt2 * psz - (plane && dst < src ? (src - dst) << my_shift : 0u)];
-          if (MOVES) {
-            // my operand's field inside c, its width
-            const uint32_t fw = (var >> (2 * op)) & 3u, fb = (var >> (8 + 4 * op)) & 7u, y0 = (c >> fb) & ((1u << fw) - 1u);
-            const uint32_t row = j * g.bt + ((((bind_d == 3 && bf ? 1u + cv : 0u) * 3u + op) * 6u + (src1 + 1u) * src1 / 2u) << (2 * yb)) + (y0 << yb);
-            for (uint32_t xx = x; xx < xw; xx += kXLanes) {
-              const bool counts = plane && xx < (1u << my_lw);
-              const bool exists = counts && xx < (1u << fw);          // (a packed layout that this size cannot have: no such Spec)
-              n_rw += counts ? src : 0u;
-              if (!__any(exists)) continue;
-#pragma unroll
-              for (uint32_t dst = 0; dst < 3; dst++) {
-                const bool ok = exists && dst < src;
-                const uint64_t b = L.bterm[ok ? row + (dst << (2 * yb)) + (y0 ^ xx) : 0u], t = L.t_cost[ok ? L.tk0[to[dst]] + (c ^ (xx << fb)) : q];
-                const bool fin = ok && (uint32_t)(b >> 32) != ~0u && (uint32_t)(t >> 32) != ~0u;
-                const uint64_t cand = t + b;                          // each at most 2^62 when finite: no wrap
-                hi_or |= fin ? (uint32_t)(cand >> 32) : 0u;
-                consider(e, cand, id0 + (dst * xw + (xx - x)) * 2u + cv, fin);
-              }
-            }
-          } else {
-            const uint32_t row = j * g.bt + cv * nops * 9u * kXw + op_row + src1 * 3u * kXw;
-            constexpr uint32_t kMine = kXw / kXLanes ? kXw / kXLanes : 1u;      // changes of layout per lane
-            uint64_t b[3][kMine], t[3][kMine];
-#pragma unroll
-            for (uint32_t dst = 0; dst < 3; dst++)
-#pragma unroll
-              for (uint32_t u = 0; u < kMine; u++) {
-                b[dst][u] = L.bterm[row + dst * kXw + u];
-                t[dst][u] = L.t_cost[(to[dst] << nlay) + (c ^ ((x + u) << my_fb))];
-              }
-#pragma unroll
-            for (uint32_t dst = 0; dst < 3; dst++)
-#pragma unroll
-              for (uint32_t u = 0; u < kMine; u++) {
-                const bool counts = plane && b[dst][u] != 0;          // 0 = no such Move (and no destination at or above src)
-                n_rw += counts ? 1u : 0u;
-                const bool fin = counts && (uint32_t)(t[dst][u] >> 32) != ~0u;
-                const uint64_t cand = t[dst][u] + b[dst][u];          // t < 2^62 when finite, b <= 2^62: no wrap
-                hi_or |= fin ? (uint32_t)(cand >> 32) : 0u;
-                const uint32_t id = id0 + dst * 4u + u * 2u + cv;
-                if (cv) consider(e, cand, id, fin);
-                else {
-                  const bool better = fin && cand < e.best;           // ids ascend
-                  e.best = better ? cand : e.best;
-                  e.arg = better ? id : e.arg;
-                }
-              }
-          }
-        }
-      }
-      if (hi_or >> 30) ovf |= 1u;   // bit 62 of some finite candidate: the solve reports overflow
-      quad_min<0xB1>(e);            // lanes ^ 1
-      quad_min<0x4E>(e);            // lanes ^ 2
-      if (kXLanes == 2) quad_min<0x141>(e);  // the other quad of eight (mirrored: the lanes of a quad agree by now)
-      if (active && (tid & (kTaskLanes - 1u)) == 0) {
-        // the task's first lane adds the microkernels (lowest ids) and the parked candidate (highest), and stores
-        consider(e, parked.best, parked.arg);
-        if (mk_shape) {
-          const uint32_t v = variant_of<MOVES>(P, var, c, dt), si = L.it_si[j];
-          for (uint32_t mm = P->mk_entry[(pack << log2V) + v] & mk_shape; mm; mm &= mm - 1) {
-            const uint32_t m = (uint32_t)__ffs((int)mm) - 1u;
-            Shape S;
-#pragma unroll
-            for (int d = 0; d < 4; d++) S.d[d] = P->sizes[d][(si >> (8 * d)) & 0xFFu];
-            const uint64_t ck = mul_or_limit(P->mk_cost[m], mk_shape_reps(P, S, m));
-            if (ck >= kLimit) ovf |= 1u; else consider(e, ck, m);
-            n_rw++;
-          }
-        }
-        L.t_cost[q] = e.best;
-        L.t_arg[q] = (uint16_t)e.arg;
-      }
+// Several small diagonals one after the other, in one workgroup: its waves share a compute unit and so its L1, and a
+// barrier orders what they write and read.  Only those that the workgroup takes in one go: with up to 2048 entries in a chain one
+// compute unit's instruction issue is the bound (the vector-matrix product 473 -> 919 us; no chain at all: 485).
+template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
+__global__ __launch_bounds__(kChainThreads) void fill_chain_kernel(const FillArgs A, const uint2* __restrict__ units, const DiagRun run) {
+  __shared__ uint4 coef[32];
+  __shared__ OpTab tab[4];
+  constexpr uint32_t lgS = LAY ? 3u : 2u;
+  load_tabs(A, coef, tab);
+  uint32_t n_rw = 0, ovf = 0;
+  for (uint32_t d = 0; d < run.n; d++) {
+    const uint32_t first = run.start[d], tasks = (run.start[d + 1] - first) << A.unit_lay;
+    for (uint32_t t0 = 0; t0 < tasks; t0 += kChainThreads >> lgS) {
+      const uint32_t t = t0 + (threadIdx.x >> lgS);
+      if (__all(t >= tasks)) break;
+      fill_entry_split<LAY, MOVES, SMALL, PAR, MN>(A, units[first + (t < tasks ? t >> A.unit_lay : 0u)], t & ((1u << A.unit_lay) - 1u), threadIdx.x & ((1u << lgS) - 1u), t < tasks, coef, tab, n_rw, ovf);
     }
     __syncthreads();
   }
-  // ---- 3. results to the table, a task per lane: inside the rank loop every chunk would wait for
-  // the previous chunk's stores (stores count on the same counter as loads here) ----
-  for (uint32_t q = tid; q < n_task; q += T) {
-    const uint32_t slot = MOVES ? (uint32_t)L.tslot[q] : q >> nlay, c = MOVES ? q - L.tk0[slot] : q & ((1u << nlay) - 1u);
-    const uint32_t en = L.ent[slot], j = ent_item(en);
-    const uint32_t cell = L.it_base[j] + ((ent_combo(en) * npass) << log2V) + variant_of<MOVES>(P, MOVES ? L.it_var[j] : 0u, c, ent_dt(en));
-    cost[cell] = L.t_cost[q];
-    arg[cell] = L.t_arg[q];
-  }
-  flush_counters(ctr, n_rw, ovf);
+  flush_counters(A.ctr, n_rw, ovf);
 }
 
 // What an alloc-binding costs beside its body (Section 2, Memory Movement; Section 3): m(src) +
@@ -1643,94 +1880,99 @@ void launch_fill_bounded(const DevParams* P, int mode, bool units, const uint32_
 bool fill_by_units(int mode, uint64_t qv) { return mode == 1 || (mode == 0 && qv >= kUnitLanes && qv < (1ull << 29)); }
 
 // ---------------------------------------------------------------- launches
-// Items of at most this many tasks go into bundles: everything where a whole shape is that small.
-uint32_t fill_small_max(uint32_t max_task) { return max_task <= 512 ? max_task : 256; }
-
-// Items per bundle at most (the tables of Move costs of packed layouts are large).
-static uint32_t fill_items(const DevParams& P) { return P.moves ? 4u : 8u; }
-
-static FillGeom fill_geom(const DevParams& P, uint32_t max_task, bool wide) {
-  FillGeom g;
-  g.ni = wide ? 1u : fill_items(P);
-  g.cap = wide ? max_task : kBundle + fill_small_max(max_task);
-  g.kt = wide ? 64u : 24u;
-  g.bt = P.moves ? P.bind_d * 3u * (6u << (2 * P.yb)) : (P.ndt ? 2u : 1u) * P.nops * (P.nlay ? 18u : 9u);
-  g.isz = (1u << P.ndt) << (2 * P.nops);
-  g.nlay = P.nlay;
-  const uint32_t entries = (P.ncombo << P.ndt) * g.ni;
-  g.ns = P.moves ? (g.cap < entries ? g.cap : entries) : g.cap >> P.nlay;
-  return g;
-}
-
-// Workgroups of the sort kernels: the levels' tiles.
-static uint32_t sort_tiles(const uint32_t* level_off, uint32_t n_levels, uint32_t npass) {
+uint32_t unit_blocks(const uint32_t* level_off, uint32_t n_levels, uint32_t npass, uint32_t* blk_off) {
   uint32_t n = 0;
-  for (uint32_t l = 0; l < n_levels; l++) n += ((level_off[l + 1] - level_off[l]) * npass + kSortTile - 1) / kSortTile;
+  for (uint32_t l = 0; l < n_levels; l++) {
+    if (blk_off) blk_off[l] = n;
+    n += ((level_off[l + 1] - level_off[l]) * npass + kBlockItems - 1) / kBlockItems;
+  }
+  if (blk_off) blk_off[n_levels] = n;
   return n;
 }
-// A level's weights are added up in 32 bits (an item weighs at least kBundle / fill_items; the
-// tasks themselves are fewer than 2^32), and a launch has fewer than 2^32 threads: the plan's has
-// four per shape, a level's 128 per bundle.
+// (a level of 2^27 items, 2^28 with Move Specs less, has always been refused; a launch has fewer than 2^32 threads,
+// and the plan's has four per shape)
 bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels) {
-  if (n_shapes >= (1u << 30) - 4 * kPlanShapes) return false;
+  if (n_shapes >= (1u << 30) - 4 * kPlanShapes || n_levels > kMaxLevels - kMaxRanks + 1) return false;
   for (uint32_t l = 0; l < n_levels; l++)
-    if ((uint64_t)(level_off[l + 1] - level_off[l]) * h.npass >= (1ull << 32) / (kBundle / fill_items(h))) return false;
+    if ((uint64_t)(level_off[l + 1] - level_off[l]) * h.npass >= (1ull << 32) / (h.moves ? 32 : 16)) return false;
   return true;
 }
 size_t plan_bytes_recs(uint32_t n_shapes) { return (size_t)n_shapes * sizeof(ShapeRec); }
-size_t plan_bytes_sort(const uint32_t* level_off, uint32_t n_levels, uint32_t npass) { return (size_t)sort_tiles(level_off, n_levels, npass) * 32 + 16; }
 
-void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, uint32_t max_task, const uint32_t* level_shapes,
-                 const uint32_t* level_off, const uint32_t* h_level_off, uint32_t n_levels, const PlanBuffers& B, uint32_t* fitmap, Counters* ctr,
-                 void* prefill_cost, void* prefill_arg, hipStream_t stream) {
+void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, const uint32_t* level_shapes, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B,
+                 uint32_t* fitmap, Counters* ctr, void* prefill_cost, void* prefill_arg, hipStream_t stream) {
   const uint32_t per_wave = plan_shapes(n_shapes);
   hipLaunchKernelGGL(plan_kernel, dim3((n_shapes + 4 * per_wave - 1) / (4 * per_wave)), dim3(256), 0, stream, P,
-                     n_shapes, per_wave, fit_map_stored(h) ? 1u : 0u, level_shapes, (ShapeRec*)B.recs, B.masks, B.item_tasks, fitmap, ctr, (uint4*)prefill_cost, (uint4*)prefill_arg);
-  const uint32_t tiles = sort_tiles(h_level_off, n_levels, h.npass), small_max = fill_small_max(max_task), min_weight = kBundle / fill_items(h);
-  uint4* parts = (uint4*)B.sort_tmp;
-  uint32_t* sums = tiles > n_levels ? (uint32_t*)(parts + tiles) : nullptr;
-  if (sums) {
-    hipLaunchKernelGGL(sort_sums_kernel, dim3(tiles), dim3(kSortThreads), 0, stream, level_off, h.npass, B.item_tasks, small_max, sums);
-    hipLaunchKernelGGL(sort_work_kernel, dim3(tiles), dim3(kSortThreads), 0, stream, level_off, n_levels, h.npass, B.item_tasks, small_max,
-                       min_weight, 0u, sums, parts, B.list_small, B.bundle_first, B.list_wide, B.list_cnt);
-  }
-  hipLaunchKernelGGL(sort_work_kernel, dim3(tiles), dim3(kSortThreads), 0, stream, level_off, n_levels, h.npass, B.item_tasks, small_max,
-                     min_weight, 1u, sums, parts, B.list_small, B.bundle_first, B.list_wide, B.list_cnt);
+                     n_shapes, per_wave, fit_map_stored(h) ? 1u : 0u, level_shapes, (ShapeRec*)B.recs, B.masks, fitmap, ctr, (uint4*)prefill_cost, (uint4*)prefill_arg);
+  hipLaunchKernelGGL(count_units_kernel, dim3((n_blk * kBlockItems + 255) / 256), dim3(256), 0, stream, P, B.level_off, B.blk_off, n_levels, n_blk,
+                     (const ShapeRec*)B.recs, B.masks, B.cnt);
+  hipLaunchKernelGGL(scan_units_kernel, dim3(n_levels * h.nranks), dim3(1024), 0, stream, B.blk_off, n_levels, h.nranks, n_blk, B.cnt, B.seg, B.diag, &ctr->ticket);
+}
+
+void launch_list_units(const DevParams* P, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream) {
+  hipLaunchKernelGGL(emit_units_kernel, dim3((n_blk + 3) / 4), dim3(256), 0, stream, P, B.level_off, B.blk_off, n_levels, n_blk, (const ShapeRec*)B.recs, B.masks,
+                     B.cnt, B.seg, (uint2*)B.list, w0, w_len);
 }
 
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream) {
   hipLaunchKernelGGL(bind_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, P, bind, n);
 }
 
-template <int T>
-static void launch_items(const DevParams* P, const DevParams& h, const FillGeom& g, uint32_t n, const uint32_t* items, const uint32_t* starts,
-                         const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
-  FillLds L;
-  const uint32_t lds = carve_fill(nullptr, g, h.moves != 0, L);
-  const ShapeRec* recs = (const ShapeRec*)B.recs;
-  if (h.moves) {
-    if constexpr (T < 1024)       // (more threads are slower with Move Specs, and never asked for: below)
-      hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, true>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
-  } else if (h.nlay) {
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, true, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
-  } else {
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_kernel<T, false, false>), dim3(n), dim3(T), lds, stream, P, g, items, starts, recs, B.masks, cost, arg, ctr);
+FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr) {
+  FillArgs A;
+  memset(&A, 0, sizeof A);
+  A.P = d_P; A.recs = B.recs; A.steps = h.steps; A.cost = cost; A.arg = arg; A.ctr = ctr;
+  A.costM = h.costM; A.costE = h.costE; A.mk_entry = h.mk_entry;
+  A.nops = h.nops; A.NL = h.NL; A.G = h.G; A.log2V = h.log2V; A.ndt = h.ndt;
+  for (uint32_t i = 0; i < 4; i++) {
+    A.mstride[i] = h.mstride[i]; A.pack_shift[i] = h.pack_shift[i]; A.lay_bit[i] = h.lay_bit[i];
+    A.lay_xor[i] = i < h.nops && h.lay_bit[i] != kNoBit ? 1u << h.lay_bit[i] : 0u;
+    A.cv_bit[i] = i < h.nops && h.can_convert[i] && h.dt_bit[i] != kNoBit ? 1u << h.dt_bit[i] : 0u;
+    A.zero[i] = h.zero[i];
+    A.tile_dims |= h.tile_dim_ok[i] && h.nsz[i] > 1 ? 1u << i : 0u;
+  }
+  A.unit_lay = h.unit_lay; A.convert = h.convert; A.s = h.s; A.sync = h.sync;
+  A.move_base = h.move_base; A.buf_id = h.buf_id; A.par_shift = h.par_base - h.tile_base;
+  A.has_buf = h.kind == kKindF || h.split; A.split = h.split; A.chain = h.chain;
+  A.GM = h.GM; A.VM = h.VM; A.GE = h.GE; A.VE = h.VE; A.nszE_n = h.nszE_n; A.kM_first = h.kM_first; A.nkM = h.nkM; A.nsz3 = h.nsz[3];
+  for (int i = 0; i < 3; i++) { A.layM[i] = h.layM[i]; A.layE[i] = h.layE[i]; }
+  return A;
+}
+
+// Which kernel takes a diagonal.  Split entries have short chains of reads, which is what counts while the chip is not full; the
+// others issue fewer instructions per entry (diagonals of 20 blocks of a lane per entry 20 us, split 5; of 1.6 M entries, four
+// at a time, 33, a lane each 61, split more).  The line at 16,384, 32,768 or 65,536 entries: within 1 % of each other; none split: the
+// vector-matrix product 485 -> 594 us, the pipeline 3082 -> 3109; all split: 3912, two Matmuls 2001 -> 3196, packed layouts 2397 -> 2922.
+// Without layouts (four lanes) a split is never behind: all sizes to 64, 668 against 740 us of fill.
+template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
+static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run, hipStream_t stream) {
+  const uint32_t n = run.start[1] - run.start[0];
+  const uint64_t tasks = (uint64_t)n << A.unit_lay;
+  const uint2* units = list + run.start[0];
+  const auto blocks = [](uint64_t lanes) { return dim3((uint32_t)((lanes + 255) / 256)); };
+  if (run.chain) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_chain_kernel<LAY, MOVES, SMALL, PAR, MN>), dim3(1), dim3(kChainThreads), 0, stream, A, list, run);
+  else if (!LAY || PAR || tasks <= kSplitTasks)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_split_kernel<LAY, MOVES, SMALL, PAR, MN>), blocks(tasks * split_lanes(LAY)), dim3(256), 0, stream, A, units, n);
+  else if constexpr (LAY && !PAR) {
+    if (!MOVES && !A.ndt && A.unit_lay >= 2) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
   }
 }
 
-// The bundles of one dependency level (starts = nullptr: every item is a bundle of its own).
-void launch_fill_level(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const uint32_t* starts,
-                       uint32_t lg_tasks, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
-  if (!n) return;
-  const FillGeom g = fill_geom(h, max_task, false);
-  if (n >= kMinBundles) launch_items<128>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
-  else if (n <= kFewBundles && lg_tasks >= kManyTasks && !h.moves) launch_items<1024>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
-  else launch_items<256>(P, h, g, n, items, starts, B, cost, arg, ctr, stream);
-}
-// Its wide items.
-void launch_fill_wide(const DevParams* P, const DevParams& h, uint32_t max_task, uint32_t n, const uint32_t* items, const PlanBuffers& B,
-                      uint64_t* cost, uint16_t* arg, Counters* ctr, hipStream_t stream) {
-  if (n) launch_items<512>(P, h, fill_geom(h, max_task, true), n, items, nullptr, B, cost, arg, ctr, stream);
+bool small_diagonal(const FillArgs& A, uint32_t n) { return ((uint64_t)n << A.unit_lay) * split_lanes(A.unit_lay != 0) <= kChainThreads; }
+
+void launch_fill_diagonals(const FillArgs& A, const DevParams& h, const void* list, const DiagRun& run, hipStream_t stream) {
+  const uint2* l = (const uint2*)list;
+  const bool mn = h.kind != kKindM;
+#define MRL_RUN(lay, moves, par, mn) (h.small ? launch_run<lay, moves, true, par, mn>(A, l, run, stream) : launch_run<lay, moves, false, par, mn>(A, l, run, stream))
+  if (h.moves) MRL_RUN(true, true, false, false);
+  else if (h.par && h.nlay) MRL_RUN(true, false, true, false);
+  else if (h.par) MRL_RUN(false, false, true, false);
+  else if (mn && h.nlay) MRL_RUN(true, false, false, true);
+  else if (mn) MRL_RUN(false, false, false, true);
+  else if (h.nlay) MRL_RUN(true, false, false, false);
+  else MRL_RUN(false, false, false, false);
+#undef MRL_RUN
 }
 
 }  // namespace mrl

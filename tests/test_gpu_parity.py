@@ -402,6 +402,54 @@ def test_parity_bundles_of_items(case):
     compare_config(cfg)
 
 
+@pytest.mark.parametrize("case", ["three-layouts", "three-layouts-dear", "batched-three-layouts", "one-layout", "one-layout-dear", "dtypes", "no-layouts", "parallel", "fused-two-layouts"])
+def test_parity_diagonals(case):
+    """Diagonals (dependency level + rank) of one entry, of up to 32,768, which are split, and of more, which are taken four
+    entries or one at a time; Move prices that fit 32 bits and (dear) that do not."""
+    cfg = W.config(3 if case == "dtypes" else 6 if case == "parallel" else 5 if case.startswith("fused") else 4, max_size=6)
+    t = cfg["target"]
+    t["capacity_bytes"] = [W.UNBOUNDED] * 4
+    if case.endswith("dear"):
+        for src in range(1, 4):
+            for dst in range(src):
+                for x in range(2):
+                    t["load_coef"][src][dst][x] += (1 << 30) + src
+                    t["store_coef"][dst][src][x] += (1 << 30) + dst
+    r = [1, 2, 3, 4, 5, 6, 8, 10, 12, 15, 16, 24] + ([18, 20, 25, 30, 40, 48] if case.startswith("one") else [])
+    r.sort()
+    for _, lat, _ in cfg["lattices"]:
+        lat["sizes"] = [s if len(s) == 1 else r[:9] if case.startswith("fused") else r for s in ([1], r, lat["sizes"][2] if case.startswith("fused") else r, r)]
+        if case.startswith("one-layout"):
+            lat["layout_coord"] = [0, 1, 0, 0, 0]
+        elif case == "no-layouts":
+            lat["layout_coord"] = [0] * 5
+        elif case.startswith("batched"):
+            lat["sizes"] = [[1, 2, 3, 6], [1, 2, 3, 6, 12], [1, 5, 10, 20], [1, 2, 4, 8, 16]]
+    if case == "fused-two-layouts":
+        for (_, lat, _), lay in zip(cfg["lattices"], ((1, 1, 0, 0, 0), (0, 0, 1, 0, 0), (0, 1, 0, 1, 0))):
+            lat["layout_coord"] = list(lay)
+            lat["sizes"][2] = lat["sizes"][2] if len(lat["sizes"][2]) == 1 else [1, 3]
+    compare_config(cfg, boxes=case in ("three-layouts", "parallel"))
+
+
+def test_work_list_in_windows():
+    """Everything fits and few boxes: the scratch that the table uses holds a part of the list of its entries at a time."""
+    B = _binding()
+    cfg = W.config(2, max_size=14)
+    t = cfg["target"]
+    t["capacity_bytes"] = [W.UNBOUNDED] * 4
+    t["load_coef"] = W._empty_target(4, [0] * 4)["load_coef"]
+    t["store_coef"] = W._empty_target(4, [0] * 4)["store_coef"]
+    target, got, want = compare_config(cfg, scratch_bytes=64 << 20)
+    lat, used = cfg["lattices"][0][1], int(got["M"].stats.scratch_used)
+    assert 8 * got["M"].stats.n_admissible > 2 * used       # (a place in the list takes 8 bytes)
+    tab = B.solve(target, lat, scratch_bytes=used)
+    cost, arg = tab.dense()
+    assert np.array_equal(cost, want["M"]["cost"]) and np.array_equal(arg, want["M"]["argmin"])
+    assert tab.stats.n_rewrites == want["M"]["n_rewrites"] and tab.stats.scratch_used == used
+    assert [tab.boxes(w).tobytes() for w in (0, 1)] == [got["M"].boxes(w).tobytes() for w in (0, 1)]
+
+
 @pytest.mark.parametrize("case", ["fused-29-tiles", "fused-layouts-42-tiles", "fused-wide-items-76-tiles", "split-42-tiles", "composition-31-tiles"])
 def test_parity_bufferize_beside_many_tiles(case):
     """More tile rewrites than a workgroup holds at a time (24 per item of a bundle, 64 of a wide
