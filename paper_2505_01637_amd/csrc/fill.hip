@@ -1154,12 +1154,20 @@ __device__ __forceinline__ void load_tabs(const FillArgs& A, uint4* coef, OpTab*
   __syncthreads();
 }
 
+// Workgroups go to the dies in turn: this one's place where each die has a stretch of consecutive ones (neighbours share
+// units' records, children and lines of the table, and a die has an L2 of its own).
+constexpr uint32_t kDies = 8;
+__device__ __forceinline__ uint32_t die_block() {
+  const uint32_t n = gridDim.x, x = blockIdx.x % kDies, full = n / kDies, more = n % kDies;
+  return x * full + (x < more ? x : more) + blockIdx.x / kDies;
+}
+
 // A diagonal: a lane per entry, the layouts of a unit in consecutive lanes (1 << unit_lay of them).
 template <bool MOVES, bool SMALL, bool MN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void fill_entry_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
-  const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+  const uint64_t t = (uint64_t)die_block() * 256u + threadIdx.x;
   const uint32_t u = (uint32_t)(t >> A.unit_lay);
   const uint2 un = units[u < n_units ? u : 0u];
   load_tabs(A, coef, tab);
@@ -1173,7 +1181,7 @@ template <bool SMALL, bool MN>
 __global__ __launch_bounds__(256) void fill_quad_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
-  const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+  const uint64_t t = (uint64_t)die_block() * 256u + threadIdx.x;
   const uint32_t u = (uint32_t)(t >> A.unit_lay);
   const uint2 un = units[u < n_units ? u : 0u];
   load_tabs(A, coef, tab);
@@ -1188,7 +1196,7 @@ __global__ __launch_bounds__(256) void fill_split_kernel(const FillArgs A, const
   constexpr uint32_t lgS = LAY ? 3u : 2u;
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
-  const uint64_t t = ((uint64_t)blockIdx.x * 256u + threadIdx.x) >> lgS;
+  const uint64_t t = ((uint64_t)die_block() * 256u + threadIdx.x) >> lgS;
   const uint32_t u = (uint32_t)(t >> A.unit_lay);
   const uint2 un = units[u < n_units ? u : 0u];
   load_tabs(A, coef, tab);
