@@ -134,7 +134,7 @@ struct Compiled {
 
 // Offsets of the fixed part of the scratch buffer.
 struct FixedLayout {
-  size_t counters, params, tiles, level_shapes, level_off, mk_entry, blk_off, qdec, recs, masks, unit_cnt, unit_seg, diag, bind, list, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
+  size_t counters, params, tiles, level_shapes, level_off, mk_entry, blk_off, qdec, recs, masks, unit_cnt, unit_seg, bind, list, fitmap, maskD, maskC, mask2D, mask2C, colD, colC, lineD, lineC, prefD, prefC, tile_tmp, tile_tmp2, totals,
       upload_end, fill_end, end;
   uint32_t n_words;
   // the merge word by word (row_geo): its fixed lists from `shared` on, then dyn
@@ -219,14 +219,13 @@ FixedLayout fixed_layout(const Compiled& c, bool may_turn = true) {
   f.qdec = take(c.qdec.size() * 4);
   f.upload_end = o;
   const size_t n_items = (size_t)c.n_shapes * c.P.npass;
-  f.recs = f.masks = f.unit_cnt = f.unit_seg = f.diag = f.bind = f.list = 0;
+  f.recs = f.masks = f.unit_cnt = f.unit_seg = f.bind = f.list = 0;
   if (!c.P.gather) {
     const uint32_t n_lev = (uint32_t)c.level_off.size() - 1;
     f.masks = take(n_items * ((size_t)c.P.nwp << c.P.ndt) * 8);
     f.recs = take(plan_bytes_recs(c.n_shapes));
     f.unit_cnt = take((size_t)unit_blocks(c.level_off.data(), n_lev, c.P.npass, nullptr) * c.P.nranks * 4);
     f.unit_seg = take((size_t)n_lev * c.P.nranks * 4);
-    f.diag = take(((size_t)n_lev + c.P.nranks) * 4);
     if (c.P.moves) f.bind = take(bind_entries(c) * 8);
     // the work list takes what is left of the buffer; where that is less than the whole list, it goes through in windows
     f.list = take(std::max<size_t>(n_items / 2, 64) * 8);
@@ -563,7 +562,8 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
       uint32_t info = pack;
       for (uint32_t op = 0; op < P.nops; op++) info |= 1u << (8 + 4 * ((combo / P.lvpow[op]) % P.NL) + op);
       P.pos_info[i] = info;
-      P.pos_entry[i] = pack | order[i].first << 8 | combo << 16;
+      P.combo_info[combo] = info;
+      P.rank_mask[order[i].first][combo >> 6] |= 1ull << (combo & 63);
     }
   }
 
@@ -683,7 +683,7 @@ int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, Compil
 
 // A second stream (default priority, non-blocking) for work that is independent of what runs on
 // the caller's stream: one of the two box lists beside the other; with it the events and the pinned counters a solve needs.
-constexpr size_t kPinnedCounts = 16 + 128;   // u32: 16 for the box lists, then the diagonals' first places in the work list (at most 62)
+constexpr size_t kDiagFirst = 16, kPinnedCounts = kDiagFirst + 64;   // u32: 16 for the box lists, then the diagonals' first places in the work list (at most 62)
 struct Aux {
   hipStream_t stream = nullptr;
   std::vector<hipEvent_t> events;
@@ -1200,8 +1200,6 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   P.steps = (const TileStep*)(base + f.tiles);
   const uint32_t n_lev = (uint32_t)c.level_off.size() - 1;
   uint32_t* d_level_shapes = (uint32_t*)(base + f.level_shapes);
-  const PlanBuffers plan{base + f.recs, (unsigned long long*)(base + f.masks), (const uint32_t*)(base + f.level_off), (const uint32_t*)(base + f.blk_off),
-                         (uint32_t*)(base + f.unit_cnt), (uint32_t*)(base + f.unit_seg), (uint32_t*)(base + f.diag), base + f.list};
   uint32_t* d_fitmap = (uint32_t*)(base + f.fitmap);
   P.mk_entry = (const uint8_t*)(base + f.mk_entry);
   P.qdec = (const uint32_t*)(base + f.qdec);
@@ -1238,6 +1236,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   rc = get_aux(16, lease);
   if (rc) return rc;
   Aux* aux = lease.a;
+  const PlanBuffers plan{base + f.recs, (unsigned long long*)(base + f.masks), d_level_shapes, (const uint32_t*)(base + f.level_off), (const uint32_t*)(base + f.blk_off),
+                         (uint32_t*)(base + f.unit_cnt), (uint32_t*)(base + f.unit_seg), aux->h_counts + kDiagFirst, base + f.list};
   // Whichever way this function is left from here on, both streams have drained before the turn
   // for the upload image, the helper stream with its events and pinned counters, and (on
   // failure) the table object are given up: work queued on the streams may still use all of these.
@@ -1255,6 +1255,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   bool prefill_timed = false, levels_timed = false;
   const hipEvent_t uploaded = aux->events[ev_used++];
   HIP_TRY(hipEventRecord(uploaded, st));
+  hipEvent_t prefilled = nullptr;
+  uint64_t n_units = 0;
   if (P.gather) {
     // Memory bounds as coordinates (and Move Specs): every Spec is evaluated (no admissibility test, so every cell
     // counts as fitting for the compression); one launch per dependency level of shapes and rank
@@ -1308,32 +1310,32 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
       }
     }
   } else {
-  // plan (with the pre-fill; a separate streaming kernel for tables it cannot serve), then the
-  // host reads the list sizes back
-  // the map's last word (which may not be whole) and its two pad words are zeroed, all of it only where the plan adds bits to it
-  if (fit_map_stored(P)) launch_zero_words((unsigned long long*)d_fitmap + f.n_words - 1, 3, st);
-  else launch_zero_words((unsigned long long*)d_fitmap, f.n_words + 2, st);
-  // the plan kernel also streams (INF, NONE) over the tables when a shape's entries are whole 16-byte pieces
-  // (not when the pre-fill runs beside the fill of the tables this lattice reads: see launch_fill_ones)
-  const bool fused_prefill = P.G % 8 == 0 && !deps_late;
+  // plan; then the host reads the diagonals' sizes back
   const uint32_t n_blk = unit_blocks(c.level_off.data(), n_lev, P.npass, nullptr), n_diag = n_lev + P.nranks - 1;
   const uint64_t list_room = (scratch_bytes - f.list) / 8;
   const uint32_t window = (uint32_t)std::min<uint64_t>(list_room, UINT32_MAX);
-  launch_plan(d_P, P, c.n_shapes, d_level_shapes, n_lev, n_blk, plan, d_fitmap, d_ctr,
-              fused_prefill ? tab->d_cost : nullptr, fused_prefill ? tab->d_arg : nullptr, st);
-  const uint32_t* diag = aux->h_counts + 16;           // pinned: the copy does not go through a staging buffer
+  // The pre-fill, (INF, NONE) over both tables, and the fit map run beside the plan and the fill on the helper stream, where they take
+  // longer than the events do: the pre-fill is done before the first diagonal, the map before the compression.  (A lattice that
+  // reads other tables streams the pre-fill behind its plan.)  What comes before the first diagonal is host time on small tables: the
+  // map is launched when the diagonals are.
+  const bool beside = c.n_specs >= (1u << 21);
+  if (!deps_late && beside) {
+    HIP_TRY(hipStreamWaitEvent(s2, uploaded, 0));
+    launch_prefill(tab->d_cost, tab->d_arg, c.n_specs, s2);
+    HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
+    prefilled = aux->events[ev_used++];
+  }
+  memset(plan.host_diag, 0, ((size_t)n_diag + 1) * 4);
+  launch_plan(d_P, P, n_lev, n_blk, plan, d_ctr, st);
   if (ask_rows) {
+    launch_fit_map(d_P, (uint32_t)c.n_specs, plan, d_fitmap, f.n_words, st);
     for (uint32_t i = 0; i < n_ways; i++) if (by_rows[i].ask) launch_row_total(by_rows[i].g, d_fitmap, d_ctr->rows + i, st);
     HIP_TRY(hipMemcpyAsync(aux->h_counts + kRowTotals, d_ctr->rows, sizeof d_ctr->rows, hipMemcpyDeviceToHost, st));
   }
-  HIP_TRY(hipMemcpyAsync(aux->h_counts + 16, plan.diag, ((size_t)n_diag + 1) * 4, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   hipEvent_t counts_ready = aux->events[ev_used++];
-  launch_list_units(d_P, n_lev, n_blk, plan, 0, window, st);
-  if (!fused_prefill) {
-    launch_fill_ones(tab->d_cost, c.n_specs * 8, st, deps_late);
-    launch_fill_ones(tab->d_arg, c.n_specs * 2, st, deps_late);
-  }
+  launch_list_units(d_P, P, n_lev, n_blk, plan, 0, window, st);
+  if (prefilled) HIP_TRY(hipStreamWaitEvent(st, prefilled, 0)); else launch_prefill(tab->d_cost, tab->d_arg, c.n_specs, st);
   HIP_TRY(hipEventRecord(ev[4], st));
   prefill_timed = true;
   HIP_TRY(hipEventSynchronize(counts_ready));
@@ -1341,7 +1343,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     if (by_rows[i].ask) by_rows[i].on = row_words_fit(by_rows[i].g, aux->h_counts[kRowTotals + i], by_rows[i].room);
   if (deps_late) {
     // now the tables this lattice reads: their fills are queued (or the call waits here until
-    // they are); the parameters go up once more, with their addresses, and the levels wait for them
+    // they are); the parameters go up once more, with their addresses, and the diagonals wait for them
     rc = late_deps(late_tables, late_ready);
     if (rc) return rc;
     deps = late_tables;
@@ -1355,6 +1357,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   HIP_TRY(hipEventRecord(ev[5], st));
   levels_timed = true;
   if (P.moves) launch_bind(d_P, (uint64_t*)(base + f.bind), (uint32_t)bind_entries(c), st);
+  const uint32_t* diag = plan.host_diag;
   const FillArgs fill = fill_args(d_P, P, plan, tab->d_cost, tab->d_arg, d_ctr);
   uint32_t w0 = 0;                        // the list holds units [w0, w0 + window)
   DiagRun run;
@@ -1368,7 +1371,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
       if (u - w0 >= window) {
         flush();
         w0 = u;
-        launch_list_units(d_P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), st);
+        launch_list_units(d_P, P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), st);
       }
       const uint32_t n = std::min(diag[d + 1] - u, window - (u - w0));
       const bool small = small_diagonal(fill, n);
@@ -1380,6 +1383,15 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
       u += n;
     }
   flush();
+  n_units = diag[n_diag];
+  if (!ask_rows) {
+    if (beside) HIP_TRY(hipStreamWaitEvent(s2, deps_late ? uploaded : counts_ready, 0));       // behind the plan (and the second upload)
+    launch_fit_map(d_P, (uint32_t)c.n_specs, plan, d_fitmap, f.n_words, beside ? s2 : st);
+    if (beside) {
+      HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
+      HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
+    }
+  }
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(ev[1], st));
@@ -1586,7 +1598,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   if (stats) {
     memset(stats, 0, sizeof *stats);
     stats->n_specs = c.n_specs;
-    stats->n_admissible = stats->n_rewrites = 0;
+    stats->n_admissible = P.gather ? 0 : n_units << P.unit_lay;
+    stats->n_rewrites = 0;
     for (uint32_t i = 0; i < kCtrSlots; i++) { stats->n_admissible += h_ctr.n_admissible[i]; stats->n_rewrites += h_ctr.n_rewrites[i]; }
     if (P.bounded) stats->n_admissible = c.n_specs;      // no admissibility test: every Spec is evaluated
     stats->n_levels_run = n_lev;

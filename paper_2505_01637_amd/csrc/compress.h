@@ -40,8 +40,9 @@ struct Geo {
 struct PlanBuffers {
   void* recs;                              // plan_bytes_recs
   unsigned long long* masks;
-  const uint32_t *level_off, *blk_off;     // first shape and first block (unit_blocks) of every dependency level
-  uint32_t *cnt, *seg, *diag;              // [ranks][blocks], [levels][ranks], [diagonals + 1]
+  const uint32_t *level_shapes, *level_off, *blk_off;       // shapes by dependency level; first shape and first block (unit_blocks) of every level
+  uint32_t *cnt, *seg;                     // [ranks][blocks], [levels][ranks]
+  uint32_t* host_diag;                     // pinned host memory: the diagonals' first places in the list, and the end
   void* list;                              // 8 bytes per unit
 };
 size_t plan_bytes_recs(uint32_t n_shapes);
@@ -49,12 +50,12 @@ size_t plan_bytes_recs(uint32_t n_shapes);
 uint32_t unit_blocks(const uint32_t* level_off, uint32_t n_levels, uint32_t npass, uint32_t* blk_off);
 // Whether the work lists can hold the lattice's dependency levels.  h: the host's copy of *P.
 bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels);
-bool fit_map_stored(const DevParams& h);
-// h: the host's copy of *P.  fitmap: zero before, unless fit_map_stored.
-void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, const uint32_t* level_shapes, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B,
-                 uint32_t* fitmap, Counters* ctr, void* prefill_cost, void* prefill_arg, hipStream_t stream);
+// h: the host's copy of *P.
+void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, Counters* ctr, hipStream_t stream);
+// Behind the plan: which cells fit, in table order, n_words words and two of zeros.
+void launch_fit_map(const DevParams* P, uint32_t n_specs, const PlanBuffers& B, uint32_t* fitmap, uint32_t n_words, hipStream_t stream);
 // Units [w0, w0 + w_len) of the work list to its place.
-void launch_list_units(const DevParams* P, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream);
+void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream);
 // The costs of the alloc-bindings of a Matmul whose Moves are Move Specs, from its Move table.
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream);
 // What the kernels of the diagonals read of the parameters, by value: they are short, and every read of the
@@ -96,7 +97,8 @@ struct BoundSegs {
 bool fill_by_units(int mode, uint64_t qv);
 void launch_fill_bounded(const DevParams* P, int mode, bool units, const uint32_t* all_level_shapes, const BoundSegs& segs, uint64_t* cost,
                          uint16_t* arg, Counters* ctr, hipStream_t stream);
-void launch_fill_ones(void* p, size_t bytes, hipStream_t stream, bool short_lived = false);
+void launch_fill_ones(void* p, size_t bytes, hipStream_t stream);
+void launch_prefill(uint64_t* cost, uint16_t* arg, size_t n, hipStream_t stream);
 void launch_zero_words(unsigned long long* p, uint32_t n, hipStream_t st);
 void launch_head_flags(const Geo& g, uint32_t a0, const uint64_t* cost, const uint16_t* arg, const uint32_t* fitmap,
                        const uint32_t* axis_sizes,

@@ -82,7 +82,8 @@ struct DevParams {
   uint32_t rank_off[kMaxRanks + 2];
   // per rank-major position: pack | (operands resident in level l, one nibble per level) << 8
   uint32_t pos_info[kMaxCombo];
-  uint32_t pos_entry[kMaxCombo];   // pack | rank << 8 | mixed-radix index << 16
+  uint32_t combo_info[kMaxCombo];  // the same in the order of the mixed-radix index (table order)
+  unsigned long long rank_mask[kMaxRanks][4];      // level assignments of a rank, bit = mixed-radix index
   uint32_t nwp;              // 64-bit words of an item's mask per value of the dtype bits: ceil(ncombo / 64)
   // ---- memory bounds as coordinates (a Matmul lattice whose Specs carry a bound per level of
   // finite capacity; kind stays kKindM).  Bound index q stands for 0 bytes (q = 0) or 2^(q-1).

@@ -90,7 +90,7 @@ __device__ __forceinline__ void load_shape(const DevParams* __restrict__ P, uint
 // (Section 2, Microkernel Selection; Figure 1 for BroadcastVecMultAdd).  The
 // level/layout/dtype part is tabulated per entry (DevParams::mk_entry).
 __device__ __forceinline__ uint64_t mk_shape_reps(const DevParams* __restrict__ P, const Shape& S, uint32_t j) {
-  const uint64_t b = S.d[0], m = S.d[1], k = S.d[2], n = S.d[3];
+  const uint32_t b = (uint32_t)S.d[0], m = (uint32_t)S.d[1], k = (uint32_t)S.d[2], n = (uint32_t)S.d[3];      // (a size is 32 bits, and so is its division)
   const uint32_t lanes = P->mk_lanes[j];
   switch (P->mk_kind[j]) {
     case 0: return (b == 1 && m == 1 && k == 1 && n == 1) ? 1 : 0;
@@ -131,223 +131,133 @@ struct alignas(16) ShapeRec {
 };
 static_assert(sizeof(ShapeRec) == 80, "read as five 16-byte pieces");
 
-// Plan: one wave per up to kPlanShapes shapes, in the order of the dependency levels.  Its first lanes take
-// a shape each and write its record; then, shape by shape, the lanes are level assignments: which
-// of them fit is written as one mask per item (bit = position in rank order, one plane of nwp words
-// per value of the dtype bits), and the entries that fit are marked in a bit map in table order (bit = cell; read by the
-// compression pass).
-// Bound by instruction issue (460 vector instructions a shape), on small tables by the latency of a wave's shapes one
-// after the other: with 16 per wave always, config 3's 180 shapes took 46 us, now 11.  The map is stored whole where
-// that can be done: with an atomic per level assignment config 2 (262,144 shapes, one bit each) took 178 us, now 129.
-constexpr uint32_t kPlanShapes = 16, kPlanWaves = 4096;      // shapes per wave at most, and fewer while there are fewer waves than this
-// Whether the plan stores the map whole (a level assignment's bits, passive levels x variants, are a power of two of
-// them, and those of all level assignments whole bytes); else it adds bits to a map that is zero before.
-bool fit_map_stored(const DevParams& h) {
-  const uint32_t nb = h.npass * h.V;
-  return (nb & (nb - 1)) == 0 && (nb >= 8 || (h.ncombo <= 64 && h.ncombo * nb % 8 == 0));
-}
-static uint32_t plan_shapes(uint32_t n_shapes) {
-  uint32_t per = kPlanShapes;
-  while (per > 1 && n_shapes / per < kPlanWaves) per /= 2;
-  return per;
-}
-
-__global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, uint32_t n_shapes, uint32_t per_wave, uint32_t map_stored, const uint32_t* __restrict__ level_shapes,
-                                                   ShapeRec* __restrict__ recs, unsigned long long* __restrict__ masks,
-                                                   uint32_t* __restrict__ fitmap, Counters* __restrict__ ctr,
-                                                   uint4* __restrict__ cost16, uint4* __restrict__ arg16) {
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63u;
-  const uint32_t npass = P->npass, ncombo = P->ncombo, V = P->V, nb = npass * V, ndp = 1u << P->ndt, nwp = P->nwp, nw = ndp * nwp, NL = P->NL, nops = P->nops;
-  const uint32_t first = (blockIdx.x * 4 + wave) * per_wave;
-  if (first >= n_shapes) return;
-  const uint32_t n_here = n_shapes - first < per_wave ? n_shapes - first : per_wave;
-  // ---- a shape per lane ----
-  Shape S;
-  uint32_t shape = 0, var = 0, nvb = 0;
-  unsigned long long lays = 1;                  // bit v: variant v (dtype bits 0) has layouts that exist
-  if (lane < n_here) {
-    shape = level_shapes[first + lane];
-    load_shape(P, shape, S);
-    uint32_t n_serial = 0, n_par = 0, cnts = 0, mk = 0;
-    uint32_t lo[4];
-#pragma unroll
-    for (int d = 0; d < 4; d++) {
-      lo[d] = P->tile_off[d][S.si[d]];
-      const uint32_t c = P->tile_off[d][S.si[d] + 1] - lo[d];
-      cnts |= c << (8 * d);
-      if (P->tile_dim_ok[d]) n_serial += c;
-      if (P->par && d != 2) n_par += c;
-    }
-    for (uint32_t j = 0; j < P->nmk; j++) mk |= (mk_shape_reps(P, S, j) ? 1u : 0u) << j;
-    for (uint32_t i = nops; i-- > 0;) {         // from the lowest layout field up
-      const uint32_t w = layout_width(P, S, i);
-      if (i < 3) var |= w << (2 * i) | nvb << (8 + 4 * i);
-      nvb += w;
-      if (!w) continue;
-      const uint32_t step = 1u << P->lay_bit[i];
-      lays |= lays << step;
-      if (w == 2) lays |= lays << (2 * step);
-    }
-    ShapeRec r;
-#pragma unroll
-    for (int i = 0; i < 5; i++) r.numel[i] = S.numel[i];
-    r.shape = shape; r.si = S.si[0] | S.si[1] << 8 | S.si[2] << 16 | S.si[3] << 24;
-    r.n_serial = n_serial; r.n_tile = n_serial + n_par;
-#pragma unroll
-    for (int d = 0; d < 4; d++) r.tile_lo[d] = lo[d];
-    r.tile_cnt = cnts;
-    r.mk_var = mk | (P->moves ? (var & 0x3Fu) << 8 | (var >> 8 & 7u) << 14 | (var >> 12 & 7u) << 17 | (var >> 16 & 7u) << 20 | nvb << 23 : 0u);
-    const uint4* from = reinterpret_cast<const uint4*>(&r);
-    uint4* to = reinterpret_cast<uint4*>(recs + first + lane);
-#pragma unroll
-    for (int i = 0; i < 5; i++) to[i] = from[i];
-  }
-  // ---- a level assignment per lane ----
-  uint32_t info[4], off0[4];
-#pragma unroll
-  for (int it = 0; it < 4; it++) {
-    info[it] = it * 64 + lane < ncombo ? P->pos_info[it * 64 + lane] : 0u;
-    off0[it] = it * 64 + lane < ncombo ? ((P->pos_entry[it * 64 + lane] >> 16) * npass) << P->log2V : 0u;      // pass 0, variant 0 of this level assignment
-  }
-  const bool fused = P->kind == kKindF;
-  unsigned long long n_adm = 0;
-  for (uint32_t s = 0; s < n_here; s++) {
-    const uint32_t sh = lane_of(shape, s), vb = lane_of(nvb, s);
-    const unsigned long long lay_s = (unsigned long long)lane_of((uint32_t)(lays >> 32), s) << 32 | lane_of((uint32_t)lays, s);
-    uint64_t numel[5];
-#pragma unroll
-    for (int i = 0; i < 5; i++) numel[i] = (uint64_t)lane_of((uint32_t)(S.numel[i] >> 32), s) << 32 | lane_of((uint32_t)S.numel[i], s);
-    if (cost16) {
-      // (INF, NONE) = all-ones over the shape's whole group: the fill overwrites what fits
-      const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
-      const uint32_t nc = P->G >> 1, na = P->G >> 3;       // 16-byte pieces (G is a multiple of 8)
-      uint4* c16 = cost16 + (size_t)sh * nc;
-      uint4* a16 = arg16 + (size_t)sh * na;
-      for (uint32_t i = lane; i < nc; i += 64) c16[i] = ones;
-      for (uint32_t i = lane; i < na; i += 64) a16[i] = ones;
-    }
-    const uint64_t group = (uint64_t)sh * P->G;
-    uint32_t ents[4] = {0, 0, 0, 0};
-    unsigned long long my_word = 0;             // lane pass * nw + word keeps that word
-    unsigned long long bits[4] = {0, 0, 0, 0};
-    for (uint32_t dt = 0; dt < ndp; dt++) {
-      // bit b of fit[l]: the tensors of subset b (operands 0..3, bit 4 = the intermediate) together fit level l
-      uint64_t sum = 0;
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        if ((uint32_t)i >= nops) break;
-        const uint32_t bf = P->dt_bit[i] != kNoBit ? (dt >> P->dt_bit[i]) & 1u : P->base_bf16[i];
-        sum += (lane >> i) & 1u ? numel[i] << (bf ? 1u : 2u) : 0;
-      }
-      sum += (lane >> 4) & 1u ? numel[4] << 2 : 0;
-      uint32_t fit[4];
-#pragma unroll
-      for (int l = 0; l < 4; l++) fit[l] = (uint32_t)__ballot(sum <= P->cap[l]);
-#pragma unroll
-      for (int it = 0; it < 4; it++) {
-        if ((uint32_t)(it * 64) >= ncombo) break;
-#pragma unroll
-        for (int ps = 0; ps < 4; ps++) {
-          if ((uint32_t)ps >= npass) break;
-          uint32_t ok = it * 64 + lane < ncombo ? 1u : 0u;
-#pragma unroll
-          for (int l = 0; l < 4; l++)
-            if ((uint32_t)l < NL) ok &= fit[l] >> (((info[it] >> (8 + 4 * l)) & 15u) | (fused && ps == l ? 16u : 0u));
-          const unsigned long long bal = __ballot(ok & 1u);
-          if (lane == ps * nw + dt * nwp + it) my_word = bal;
-          ents[ps] += (uint32_t)__popcll(bal);
-          if (ok & 1u) bits[it] |= lay_s << (dt + ps * V);
-        }
-      }
-    }
-    if (nb < 8 && map_stored) {
-      // less than a byte per level assignment: the lanes go from rank to table order, and as many as make a byte join up
-      uint32_t x = (uint32_t)__builtin_amdgcn_ds_permute((int)(lane < ncombo ? off0[0] / nb : lane) * 4, (int)(uint32_t)bits[0]);
-      for (uint32_t have = nb, d = 1; have < 8; have *= 2, d *= 2) x |= (uint32_t)__shfl_down((int)x, d, 64) << have;
-      if (lane * nb % 8 == 0 && lane < ncombo) ((uint8_t*)fitmap)[(group + lane * nb) >> 3] = (uint8_t)x;
-    } else {
-#pragma unroll
-      for (int it = 0; it < 4; it++) {
-        if ((uint32_t)(it * 64) >= ncombo) break;
-        if (it * 64 + lane >= ncombo) continue;
-        const uint64_t cell0 = group + off0[it];
-        if (map_stored) {
-          // whole bytes to pairs of words (the group size is a multiple of nb): stored, the map is not zeroed
-          if (nb == 8) ((uint8_t*)fitmap)[cell0 >> 3] = (uint8_t)bits[it];
-          else if (nb == 16) ((uint16_t*)fitmap)[cell0 >> 4] = (uint16_t)bits[it];
-          else {
-            fitmap[cell0 >> 5] = (uint32_t)bits[it];
-            if (nb == 64) fitmap[(cell0 >> 5) + 1] = (uint32_t)(bits[it] >> 32);
-          }
-        } else if (bits[it]) {
-          const uint32_t shift = (uint32_t)(cell0 & 31u);
-          uint32_t* w = fitmap + (cell0 >> 5);
-          atomicOr(w, (uint32_t)(bits[it] << shift));
-          if (shift + nb > 32) {
-            atomicOr(w + 1, (uint32_t)(bits[it] >> (32 - shift)));
-            if (shift + nb > 64) atomicOr(w + 2, (uint32_t)(bits[it] >> (64 - shift)));
-          }
-        }
-      }
-    }
-    if (lane < npass * nw) masks[(size_t)(first + s) * npass * nw + lane] = my_word;
-    n_adm += (unsigned long long)(ents[0] + ents[1] + ents[2] + ents[3]) << vb;
-  }
-  if (lane == 0 && n_adm) atomicAdd(&ctr->n_admissible[blockIdx.x % kCtrSlots], n_adm);
-}
-
 // Work lists.  A unit is an admissible (item, dtype bits, level assignment): the entries that differ in their layouts
-// only (packed layouts: a part of these, see emit_units_kernel).  Units are listed by diagonal, dependency level of the
+// only (packed layouts: a part of these, see unit_parts).  Units are listed by diagonal, dependency level of the
 // shape + rank of the level assignment: a Move lowers the rank within an item and a tile goes to the same level
 // assignment of a shape of a lower level, so the units of one diagonal depend on earlier diagonals only.  Within a
 // diagonal they lie level by level, then in the order of their items: neighbours share a shape and its tiles.
 //
-// Three kernels behind the plan.  count: per block of kBlockItems items of one level, the units of every rank.  scan:
-// a workgroup per (level, rank) turns these into places within it, the last one to end adds up the diagonals.
-// emit: a wave per block walks the masks' non-empty words and writes the units.  The whole list may be longer than its
-// place in the scratch buffer: emit writes a window of it, as often as the host asks.
-constexpr uint32_t kBlockItems = 4;
+// plan: a lane per item, kBlockItems of one level to a block; writes the shapes' records, the items' masks (bit = level
+// assignment in table order, one plane of nwp words per value of the dtype bits) and per block the units of every rank.
+// scan: a workgroup per (level, rank) turns these into places within it, the last one to end adds up the diagonals.
+// list: a lane per unit.  The whole list may be longer than its place in the scratch buffer:
+// a window of it is written, as often as the host asks.  fit map: the bit map of the entries that fit, in table
+// order (read by the compression), beside the fill.
+// With a wave per shape, its lanes level assignments, the plan was bound by instruction issue (460 vector instructions a
+// shape; a lane per item takes 9 per level assignment for 64 items): all sizes to 64 (262,144 shapes) 124 us and the list 61, now
+// 31 and 46, the solve 1190 -> 1106.
+constexpr uint32_t kBlockItems = 8;
 constexpr uint32_t kMaxLevels = 64;          // (b*m*k*n < 2^48: at most 49 dependency levels, 61 diagonals: a lane of a wave each)
 
-// Level of block b: blk_off[l] = first block of level l.
+// Level of block b: my_end = first block behind level `lane`.
 __device__ __forceinline__ uint32_t level_of_block(uint32_t my_end, uint32_t b) { return (uint32_t)__popcll(__ballot(my_end <= b)); }
 
-// Bits [lo, hi) of positions, as a mask of word `it`.
-__device__ __forceinline__ unsigned long long word_range(uint32_t lo, uint32_t hi, uint32_t it) {
-  const auto below = [&](uint32_t p) { return p <= it * 64 ? 0ull : p >= it * 64 + 64 ? ~0ull : (1ull << (p - it * 64)) - 1ull; };
-  return below(hi) & ~below(lo);
-}
-
-// Layouts beyond those of a unit, as powers of two: a packed operand may have four instead of two (unit_lay = the
-// operands with a layout coordinate).
-__device__ __forceinline__ uint32_t unit_parts(const DevParams* __restrict__ P, const ShapeRec* __restrict__ recs, uint32_t rec) {
-  return P->moves ? (recs[rec].mk_var >> 23) - P->unit_lay : 0u;
-}
-
-__global__ __launch_bounds__(256) void count_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_off, const uint32_t* __restrict__ blk_off,
-                                                          uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs,
-                                                          const unsigned long long* __restrict__ masks, uint32_t* __restrict__ cnt) {
+__global__ __launch_bounds__(256) void plan_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_shapes, const uint32_t* __restrict__ level_off,
+                                                   const uint32_t* __restrict__ blk_off, uint32_t n_levels, uint32_t n_blk, ShapeRec* __restrict__ recs,
+                                                   unsigned long long* __restrict__ masks, uint32_t* __restrict__ cnt) {
   const uint32_t lane = threadIdx.x & 63u, b = (blockIdx.x * 256u + threadIdx.x) / kBlockItems, b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-  const uint32_t npass = P->npass, nwp = P->nwp, ndp = 1u << P->ndt, nw = ndp * nwp;
+  const uint32_t npass = P->npass, ncombo = P->ncombo, nwp = P->nwp, ndp = 1u << P->ndt, nw = ndp * nwp, NL = P->NL, nops = P->nops;
+  __shared__ unsigned long long rank_masks[kMaxRanks][4];
+  if (threadIdx.x < kMaxRanks * 4) rank_masks[threadIdx.x / 4][threadIdx.x % 4] = P->rank_mask[threadIdx.x / 4][threadIdx.x % 4];
+  __syncthreads();
   const uint32_t my_end = lane < n_levels ? blk_off[lane + 1] : ~0u;
   uint32_t lev = 0;
 #pragma unroll
   for (uint32_t k = 0; k < 64 / kBlockItems; k++) { const uint32_t l = level_of_block(my_end, b0 + k); lev = lane / kBlockItems == k ? l : lev; }
+  uint32_t item = 0;
+  bool have = b < n_blk;
+  if (have) {
+    item = level_off[lev] * npass + (b - blk_off[lev]) * kBlockItems + lane % kBlockItems;
+    have = item < level_off[lev + 1] * npass;
+  }
   unsigned long long m[4] = {0, 0, 0, 0};
   uint32_t parts = 0;
-  if (b < n_blk) {
-    const uint32_t item = level_off[lev] * npass + (b - blk_off[lev]) * kBlockItems + lane % kBlockItems;
-    if (item < level_off[lev + 1] * npass) {
+  if (have) {
+    const uint32_t at = item / npass, pass = item - at * npass, shape = level_shapes[at];
+    Shape S;
+    load_shape(P, shape, S);
+    uint32_t var = 0, nvb = 0;
+    for (uint32_t i = nops; i-- > 0;) {         // from the lowest layout field up
+      const uint32_t w = layout_width(P, S, i);
+      if (i < 3) var |= w << (2 * i) | nvb << (8 + 4 * i);
+      nvb += w;
+    }
+    if (P->moves) parts = nvb - P->unit_lay;
+    if (pass == 0) {
+      uint32_t n_serial = 0, n_par = 0, cnts = 0, mk = 0;
+      uint32_t lo[4];
 #pragma unroll
-      for (int w = 0; w < 4; w++) if ((uint32_t)w < nw) m[w] = masks[(size_t)item * nw + w];
-      parts = unit_parts(P, recs, item / npass);
+      for (int d = 0; d < 4; d++) {
+        lo[d] = P->tile_off[d][S.si[d]];
+        const uint32_t c = P->tile_off[d][S.si[d] + 1] - lo[d];
+        cnts |= c << (8 * d);
+        if (P->tile_dim_ok[d]) n_serial += c;
+        if (P->par && d != 2) n_par += c;
+      }
+      for (uint32_t j = 0; j < P->nmk; j++) mk |= (mk_shape_reps(P, S, j) ? 1u : 0u) << j;
+      ShapeRec r;
+#pragma unroll
+      for (int i = 0; i < 5; i++) r.numel[i] = S.numel[i];
+      r.shape = shape; r.si = S.si[0] | S.si[1] << 8 | S.si[2] << 16 | S.si[3] << 24;
+      r.n_serial = n_serial; r.n_tile = n_serial + n_par;
+#pragma unroll
+      for (int d = 0; d < 4; d++) r.tile_lo[d] = lo[d];
+      r.tile_cnt = cnts;
+      r.mk_var = mk | (P->moves ? (var & 0x3Fu) << 8 | (var >> 8 & 7u) << 14 | (var >> 12 & 7u) << 17 | (var >> 16 & 7u) << 20 | nvb << 23 : 0u);
+      const uint4* from = reinterpret_cast<const uint4*>(&r);
+      uint4* to = reinterpret_cast<uint4*>(recs + at);
+#pragma unroll
+      for (int i = 0; i < 5; i++) to[i] = from[i];
+    }
+    // ---- which level assignments fit ----
+    const uint64_t mid = P->kind == kKindF ? S.numel[4] << 2 : 0;
+    for (uint32_t dt = 0; dt < ndp; dt++) {
+      // bit s of fit[l]: the operands of subset s together fit level l, next to the intermediate if it lives there
+      uint64_t sum[16];
+      sum[0] = 0;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const uint32_t bf = P->dt_bit[i] != kNoBit ? (dt >> P->dt_bit[i]) & 1u : P->base_bf16[i];
+        const uint64_t bytes = (uint32_t)i < nops ? S.numel[i] << (bf ? 1u : 2u) : 0;
+#pragma unroll
+        for (int q = 0; q < 1 << i; q++) sum[q | 1 << i] = sum[q] + bytes;
+      }
+      uint32_t fit[4];
+#pragma unroll
+      for (uint32_t l = 0; l < 4; l++) {
+        const uint64_t cap = P->cap[l], extra = l == pass ? mid : 0, room = cap - extra;
+        uint32_t f = 0;
+#pragma unroll
+        for (int q = 0; q < 16; q++) f |= (sum[q] <= room ? 1u : 0u) << q;
+        fit[l] = l >= NL ? 0xFFFFu : extra > cap ? 0u : f;
+      }
+      for (uint32_t w = 0; w < nwp; w++) {
+        uint32_t half[2] = {0, 0};
+#pragma unroll
+        for (uint32_t h = 0; h < 2; h++) {
+          const uint32_t c0 = w * 64 + h * 32, n = ncombo <= c0 ? 0u : ncombo - c0 < 32u ? ncombo - c0 : 32u;
+          if (!n) break;
+          uint32_t x = 0;
+#pragma unroll
+          for (uint32_t c = 0; c < 32; c++) {
+            const uint32_t info = P->combo_info[c0 + c];      // (the same for all lanes)
+            const uint32_t ok = fit[0] >> ((info >> 8) & 15u) & fit[1] >> ((info >> 12) & 15u) & fit[2] >> ((info >> 16) & 15u) & fit[3] >> ((info >> 20) & 15u);
+            x = __builtin_amdgcn_alignbit(ok, x, 1);          // shifted in from above
+          }
+          half[h] = x & (n < 32u ? (1u << n) - 1u : ~0u);
+        }
+        const unsigned long long word = (unsigned long long)half[1] << 32 | half[0];
+        masks[((size_t)shape * npass + pass) * nw + dt * nwp + w] = word;
+        const uint32_t k = dt * nwp + w;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) m[u] = u == k ? word : m[u];
+      }
     }
   }
   for (uint32_t r = 0; r < P->nranks; r++) {
-    const uint32_t lo = P->rank_off[r], hi = P->rank_off[r + 1];
     uint32_t n = 0;
 #pragma unroll
-    for (uint32_t w = 0; w < 4; w++) if (w < nw) n += (uint32_t)__popcll(m[w] & word_range(lo, hi, w % nwp));
+    for (uint32_t w = 0; w < 4; w++) n += (uint32_t)__popcll(m[w] & rank_masks[r][nwp > 1 ? w : 0]);      // (several words: no dtype bits)
     n <<= parts;
 #pragma unroll
     for (uint32_t d = 1; d < kBlockItems; d <<= 1) n += (uint32_t)__shfl_xor((int)n, d, 64);
@@ -355,9 +265,10 @@ __global__ __launch_bounds__(256) void count_units_kernel(const DevParams* __res
   }
 }
 
-// seg: units of every (level, rank), then their first places in the list; diag: the diagonals' first places, and the end.
+// seg: units of every (level, rank), then their first places in the list; host_diag: the diagonals' first places, and the
+// end, straight to pinned host memory (behind a copy the next kernel would wait for it).
 __global__ __launch_bounds__(1024) void scan_units_kernel(const uint32_t* __restrict__ blk_off, uint32_t n_levels, uint32_t n_ranks, uint32_t n_blk,
-                                                          uint32_t* __restrict__ cnt, uint32_t* __restrict__ seg, uint32_t* __restrict__ diag, unsigned int* __restrict__ ticket) {
+                                                          uint32_t* __restrict__ cnt, uint32_t* __restrict__ seg, uint32_t* __restrict__ host_diag, unsigned int* __restrict__ ticket) {
   __shared__ uint32_t sh[16];
   __shared__ uint32_t tot[kMaxLevels * kMaxRanks];
   __shared__ bool last;
@@ -407,8 +318,8 @@ __global__ __launch_bounds__(1024) void scan_units_kernel(const uint32_t* __rest
     if ((int)lane >= d) incl += o;
   }
   uint32_t at = incl - n;
-  if (lane < n_diag) diag[lane] = at;
-  if (lane == n_diag - 1) diag[n_diag] = incl;
+  if (lane < n_diag) host_diag[lane] = at;
+  if (lane == n_diag - 1) host_diag[n_diag] = incl;
   for (uint32_t l = 0; l < n_levels; l++)
     if (lane >= l && lane - l < n_ranks) { seg[l * n_ranks + lane - l] = at; at += tot[l * n_ranks + lane - l]; }
 }
@@ -417,71 +328,164 @@ __global__ __launch_bounds__(1024) void scan_units_kernel(const uint32_t* __rest
 // part of its layouts (6), and from bit kUnitFit on, per operand and destination level, whether the level assignment with
 // that operand there fits as well (its entries are finished, and only those are read).
 constexpr uint32_t kUnitFit = 18;
-constexpr uint32_t kEmitQueue = 256;
 
-// A wave walks its block's words one after the other (place of every unit: its rank's place + the units of that rank
-// before it) and puts them in a queue in LDS, which is then taken a lane per unit: of two to six admissible level
-// assignments per word only those lanes would have something to do.
-__global__ __launch_bounds__(256) void emit_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_off, const uint32_t* __restrict__ blk_off,
-                                                         uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs, const unsigned long long* __restrict__ masks,
-                                                         const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ seg, uint2* __restrict__ list, uint32_t w0, uint32_t w_len) {
-  __shared__ uint8_t pos_of[256];
-  __shared__ unsigned long long words[4][64];
-  __shared__ uint32_t q_unit[4][kEmitQueue], q_to[4][kEmitQueue];
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, b = blockIdx.x * 4u + wave;
-  const uint32_t npass = P->npass, nwp = P->nwp, nw = nwp << P->ndt, ncombo = P->ncombo, n_ranks = P->nranks, nops = P->nops;
-  for (uint32_t p = threadIdx.x; p < ncombo; p += 256) pos_of[P->pos_entry[p] & 0xFFu] = (uint8_t)p;
+// Units [w0, w0 + w_len) of the list: a workgroup per rank and n_items (at most kListItems) items, two of which a lane counts the units of;
+// then a lane per unit looks up its item among the sums.  (A lane per rank and block of items that writes its units one after the
+// other, as many as they are: 94 us for all sizes to 64, 335 for the pipeline; a lane per unit that searches the
+// blocks' places in memory: 110 and 56.)
+constexpr uint32_t kListItems = 512;
+__global__ __launch_bounds__(256) void list_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_shapes, const uint32_t* __restrict__ level_off,
+                                                         const uint32_t* __restrict__ blk_off, uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs,
+                                                         const unsigned long long* __restrict__ masks, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ seg,
+                                                         uint2* __restrict__ list, uint32_t w0, uint32_t w_len, uint32_t n_items) {
+  __shared__ uint32_t ends[kMaxLevels], waves[4], before[kListItems + 1], item_of[kListItems], to_of[kListItems / kBlockItems];
+  __shared__ unsigned long long word_of[4][kListItems];
+  __shared__ uint8_t parts_of[kListItems], packs[kMaxCombo];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, r = blockIdx.y;
+  const uint32_t npass = P->npass, nwp = P->nwp, nw = nwp << P->ndt, n_ranks = P->nranks, nops = P->nops;
+  if (tid < kMaxLevels) ends[tid] = tid < n_levels ? blk_off[tid + 1] : ~0u;
+  packs[tid] = (uint8_t)P->combo_info[tid];
+  unsigned long long rm[4];
+#pragma unroll
+  for (uint32_t w = 0; w < 4; w++) rm[w] = P->rank_mask[r][nwp > 1 ? w : 0];       // (several words: no dtype bits)
   __syncthreads();
-  if (b >= n_blk) return;
-  const uint32_t lev = level_of_block(lane < n_levels ? blk_off[lane + 1] : ~0u, b);
-  const uint32_t first = level_off[lev] * npass + (b - blk_off[lev]) * kBlockItems, left = level_off[lev + 1] * npass - first;
-  const uint32_t n_here = left < kBlockItems ? left : kBlockItems;
-  const unsigned long long word = lane < n_here * nw ? masks[(size_t)first * nw + lane] : 0ull;
-  words[wave][lane] = word;
-  uint32_t run = lane < n_ranks ? seg[lev * n_ranks + lane] + cnt[(size_t)lane * n_blk + b] : 0u;       // lane r: place of rank r's next unit
-  const uint32_t rlo = lane < n_ranks ? P->rank_off[lane] : 0u, rhi = lane < n_ranks ? P->rank_off[lane + 1] : 0u;
-  const uint32_t parts = lane < n_here ? unit_parts(P, recs, (first + lane) / npass) : 0u;              // lane j: item j's
-  uint32_t rank[4];
+  uint32_t n2[2] = {0, 0};
+  {
+    const uint32_t b = blockIdx.x * (n_items / kBlockItems) + tid * 2u / kBlockItems;
+    if (b < n_blk && tid * 2u < n_items) {
+      uint32_t lev = 0;
 #pragma unroll
-  for (uint32_t it = 0; it < 4; it++) rank[it] = it * 64 + lane < ncombo ? (P->pos_entry[it * 64 + lane] >> 8) & 0xFFu : 0u;
-  uint32_t qn = 0;
-  const auto flush = [&]() {
-    for (uint32_t i0 = 0; i0 < qn; i0 += 64) {
-      const uint32_t i = i0 + lane, u = i < qn ? q_unit[wave][i] : 0u, j = u & 15u, dt = (u >> 4) & 3u;
-      const uint32_t ch = __shfl(parts, j, 64);
-      if (i >= qn) continue;
-      const uint32_t item = first + j, rec = item / npass, pass = item - rec * npass, pack = P->pos_entry[u >> 8] & 0xFFu;
-      uint32_t y = pack | dt << 8 | pass << 10;
+      for (uint32_t d = kMaxLevels / 2; d > 0; d >>= 1) lev += ends[lev + d - 1] <= b ? d : 0u;      // levels that end at or before block b
+      const uint32_t first = level_off[lev] * npass + (b - blk_off[lev]) * kBlockItems, end = level_off[lev + 1] * npass;
+      if (tid * 2u % kBlockItems == 0) to_of[tid * 2u / kBlockItems] = seg[lev * n_ranks + r] + cnt[(size_t)r * n_blk + b] - w0;
 #pragma unroll
-      for (uint32_t op = 0; op < 4; op++) {
-        if (op >= nops) break;
-        const uint32_t shift = P->pack_shift[op], src = (pack >> shift) & 3u;
+      for (uint32_t q = 0; q < 2; q++) {
+        const uint32_t j = tid * 2u + q, item = first + j % kBlockItems;
+        if (item < end) {
+          const uint32_t rec = item / npass, pass = item - rec * npass;
+          const unsigned long long* mp = masks + ((size_t)level_shapes[rec] * npass + pass) * nw;
+          const uint32_t parts = P->moves ? (recs[rec].mk_var >> 23) - P->unit_lay : 0u;
 #pragma unroll
-        for (uint32_t dst = 0; dst < 3; dst++)
-          if (dst < src) {
-            const uint32_t p = pos_of[pack - ((src - dst) << shift)];
-            y |= (uint32_t)(words[wave][j * nw + dt * nwp + (p >> 6)] >> (p & 63u) & 1ull) << (kUnitFit + op * 3 + dst);
-          }
+          for (uint32_t w = 0; w < 4; w++)
+            if (w < nw) { const unsigned long long m = mp[w]; word_of[w][j] = m; n2[q] += (uint32_t)__popcll(m & rm[w]); }
+          n2[q] <<= parts;
+          item_of[j] = item;
+          parts_of[j] = (uint8_t)parts;
+        }
       }
-      const uint32_t to = q_to[wave][i] - w0;
-      for (uint32_t c = 0; c < (1u << ch); c++)
-        if (to + c < w_len) list[to + c] = make_uint2(rec, y | c << 12);          // (below the window: wraps around)
     }
-    qn = 0;
-  };
-  for (unsigned long long todo = __ballot(word != 0); todo; todo &= todo - 1) {
-    const uint32_t s = (uint32_t)__builtin_ctzll(todo), j = s / nw, w = s - j * nw, dt = w / nwp, it = w - dt * nwp;
-    const unsigned long long m = (unsigned long long)lane_of((uint32_t)(word >> 32), s) << 32 | lane_of((uint32_t)word, s);
-    const uint32_t ch = lane_of(parts, j), rk = it == 0 ? rank[0] : it == 1 ? rank[1] : it == 2 ? rank[2] : rank[3];
-    const uint32_t before = (uint32_t)__popcll(m & word_range(0, rlo, it));      // lane r: units of lower ranks in this word
-    const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    const uint32_t to = __shfl(run, rk, 64) + ((k - __shfl(before, rk, 64)) << ch);
-    if (qn > kEmitQueue - 64) flush();
-    if ((m >> lane) & 1ull) { q_unit[wave][qn + k] = j | dt << 4 | (it * 64 + lane) << 8; q_to[wave][qn + k] = to; }
-    qn += (uint32_t)__popcll(m);
-    run += (uint32_t)__popcll(m & word_range(rlo, rhi, it)) << ch;
   }
-  flush();
+  uint32_t incl = n2[0] + n2[1];
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if ((int)lane >= d) incl += o;
+  }
+  if (lane == 63) waves[wave] = incl;
+  __syncthreads();
+  uint32_t at = incl - n2[0] - n2[1], total = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < 4; w++) { const uint32_t x = waves[w]; at += w < wave ? x : 0u; total += x; }
+  before[tid * 2u] = at;
+  before[tid * 2u + 1] = at + n2[0];
+  __syncthreads();
+  uint32_t shift[4], step[4];
+#pragma unroll
+  for (uint32_t op = 0; op < 4; op++) { shift[op] = op < nops ? P->pack_shift[op] : 8u; step[op] = P->lvpow[op]; }      // (an operand that is not there: level 0)
+  for (uint32_t u = tid; u < total; u += 256) {
+    uint32_t j = 0;
+#pragma unroll
+    for (uint32_t d = kListItems / 2; d > 0; d >>= 1) j += before[j + d] <= u ? d : 0u;      // the last item that begins at or before it
+    const uint32_t parts = parts_of[j], item = item_of[j], rec = item / npass, pass = item - rec * npass;
+    uint32_t k = u - before[j];
+    const uint32_t to = to_of[j / kBlockItems] + u - before[j / kBlockItems * kBlockItems], part = k & ((1u << parts) - 1u);
+    if (to >= w_len) continue;            // (before the window: wraps around)
+    k >>= parts;
+    unsigned long long m[4];
+#pragma unroll
+    for (uint32_t w = 0; w < 4; w++) m[w] = w < nw ? word_of[w][j] : 0ull;
+    uint32_t w = 0;
+    unsigned long long x = m[0] & rm[0];
+#pragma unroll
+    for (uint32_t v = 1; v < 4; v++) {
+      const uint32_t n = (uint32_t)__popcll(x);
+      if (w == v - 1 && v < nw && k >= n) { k -= n; w = v; x = m[v] & rm[v]; }
+    }
+    const uint32_t dt = nwp > 1 ? 0u : w, combo = (nwp > 1 ? w * 64u : 0u) + nth_bit(x, k), pack = packs[combo];
+    uint32_t y = pack | dt << 8 | pass << 10 | part << 12;
+    const unsigned long long plane = w == 0 ? m[0] : w == 1 ? m[1] : w == 2 ? m[2] : m[3];
+#pragma unroll
+    for (uint32_t op = 0; op < 4; op++) {
+      const uint32_t src = (pack >> shift[op]) & 3u;
+#pragma unroll
+      for (uint32_t dst = 0; dst < 3; dst++)
+        if (dst < src) {
+          const uint32_t c = combo - (src - dst) * step[op];
+          unsigned long long word = plane;
+          if (nwp > 1) {
+            word = m[3];
+            word = c < 192 ? m[2] : word;
+            word = c < 128 ? m[1] : word;
+            word = c < 64 ? m[0] : word;
+          }
+          y |= (uint32_t)(word >> (c & 63u) & 1ull) << (kUnitFit + op * 3 + dst);
+        }
+    }
+    list[to] = make_uint2(rec, y);
+  }
+}
+
+// The fit map, a word of 64 cells per lane, and two words of zeros behind it.
+__global__ __launch_bounds__(256) void fit_map_kernel(const DevParams* __restrict__ P, uint32_t n_specs, const unsigned long long* __restrict__ masks, unsigned long long* __restrict__ map, uint32_t n_words) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i >= n_words + 2) return;
+  unsigned long long out = 0;
+  if (i < n_words) {
+    const uint32_t npass = P->npass, log2V = P->log2V, V = 1u << log2V, G = P->G, nwp = P->nwp, ndp = 1u << P->ndt, nw = nwp * ndp, nops = P->nops;
+    uint32_t shape = (uint32_t)(((uint64_t)i * 64u) / G), off = i * 64u - shape * G, left = n_specs - i * 64u;
+    left = left < 64u ? left : 64u;
+    if (npass == 1 && !log2V) {                // a cell per level assignment: the masks one after the other
+      for (uint32_t at = 0; at < left;) {
+        const uint32_t room = 64u - (off & 63u), rest = G - off < left - at ? G - off : left - at, n = room < rest ? room : rest;
+        const unsigned long long bits = masks[(size_t)shape * nw + (off >> 6)] >> (off & 63u) & (n >= 64u ? ~0ull : (1ull << n) - 1ull);
+        out |= bits << at;
+        at += n;
+        off += n;
+        if (off == G) { off = 0; shape++; }
+      }
+      map[i] = out;
+      return;
+    }
+    uint32_t seen = ~0u;
+    uint32_t combo = (off >> log2V) / npass, pass = (off >> log2V) - combo * npass;
+    unsigned long long lays = 1;               // bit v: variant v (dtype bits 0) has layouts that exist
+    for (uint32_t at = 0; at < left;) {
+      if (shape != seen) {
+        seen = shape;
+        lays = 1;
+        Shape S;
+        if (P->moves) load_shape(P, shape, S);
+        for (uint32_t j = nops; j-- > 0;) {    // from the lowest layout field up
+          const uint32_t w = P->moves ? layout_width(P, S, j) : P->lay_w[j];
+          if (!w) continue;
+          const uint32_t step = 1u << P->lay_bit[j];
+          lays |= lays << step;
+          if (w == 2) lays |= lays << (2 * step);
+        }
+      }
+      const uint32_t v0 = off & (V - 1u), n = V - v0 < left - at ? V - v0 : left - at;
+      const unsigned long long* mp = masks + ((size_t)shape * npass + pass) * nw + (combo >> 6);
+      unsigned long long bits = 0;
+      for (uint32_t dt = 0; dt < ndp; dt++) bits |= (mp[dt * nwp] >> (combo & 63u) & 1ull) ? lays << dt : 0ull;
+      bits = bits >> v0 & (n >= 64u ? ~0ull : (1ull << n) - 1ull);
+      out |= bits << at;
+      at += n;
+      off += n;
+      if (v0 + n == V && ++pass == npass) { pass = 0; combo++; }
+      if (off == G) { off = 0; combo = 0; shape++; }
+    }
+  }
+  map[i] = out;
 }
 
 // ---------------------------------------------------------------- one diagonal
@@ -1283,31 +1287,36 @@ __global__ __launch_bounds__(256) void fill_ones_kernel(uint4* __restrict__ p, s
 // stream the compute units' wave slots then turn over all the time, and those kernels' workgroups
 // are placed as soon as they are launched (a grid of workgroups that live as long as the whole
 // stream of stores holds every slot until it ends).
-__global__ __launch_bounds__(256) void fill_ones_short_kernel(uint4* __restrict__ p, size_t n16) {
+// Two stretches in one launch.
+__global__ __launch_bounds__(256) void fill_ones_short_kernel(uint4* __restrict__ p, size_t n16, uint32_t blocks, uint4* __restrict__ q, size_t m16) {
   const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
-  const size_t i0 = (size_t)blockIdx.x * 1024u + threadIdx.x;
+  const bool second = blockIdx.x >= blocks;
+  uint4* to = second ? q : p;
+  const size_t n = second ? m16 : n16, i0 = (size_t)(second ? blockIdx.x - blocks : blockIdx.x) * 1024u + threadIdx.x;
 #pragma unroll
   for (int k = 0; k < 4; k++) {
     const size_t i = i0 + (size_t)k * 256u;
-    if (i < n16) p[i] = ones;
+    if (i < n) to[i] = ones;
   }
 }
 
-void launch_fill_ones(void* p, size_t bytes, hipStream_t stream, bool short_lived) {
+void launch_fill_ones(void* p, size_t bytes, hipStream_t stream) {
   const size_t n16 = bytes / 16;
-  if (n16 && short_lived) {
-    size_t done = 0;
-    while (done < n16) {          // (grids stay below 2^31 workgroups)
-      const size_t part = n16 - done < ((size_t)1 << 40) ? n16 - done : ((size_t)1 << 40);
-      hipLaunchKernelGGL(fill_ones_short_kernel, dim3((uint32_t)((part + 1023) / 1024)), dim3(256), 0, stream, (uint4*)p + done, part);
-      done += part;
-    }
-  } else if (n16) {
+  if (n16) {
     const size_t blocks = (n16 + 255) / 256;
     hipLaunchKernelGGL(fill_ones_kernel, dim3((uint32_t)(blocks < 16384 ? blocks : 16384)), dim3(256), 0, stream,
                        (uint4*)p, n16);
   }
   if (bytes % 16) (void)hipMemsetAsync((char*)p + n16 * 16, 0xFF, bytes % 16, stream);
+}
+
+// A table: (INF, NONE) everywhere.  (fewer than 2^32 Specs: the grid stays below 2^22 workgroups)
+void launch_prefill(uint64_t* cost, uint16_t* arg, size_t n, hipStream_t stream) {
+  const size_t n16 = n / 2, m16 = n / 8;
+  const uint32_t blocks = (uint32_t)((n16 + 1023) / 1024), more = (uint32_t)((m16 + 1023) / 1024);
+  if (blocks + more) hipLaunchKernelGGL(fill_ones_short_kernel, dim3(blocks + more), dim3(256), 0, stream, (uint4*)cost, n16, blocks, (uint4*)arg, m16);
+  if (n % 2) (void)hipMemsetAsync(cost + n16 * 2, 0xFF, 8, stream);
+  if (n % 8) (void)hipMemsetAsync(arg + m16 * 8, 0xFF, n % 8 * 2, stream);
 }
 
 // ---------------------------------------------------------------- memory bounds as coordinates
@@ -1900,26 +1909,29 @@ uint32_t unit_blocks(const uint32_t* level_off, uint32_t n_levels, uint32_t npas
 // (a level of 2^27 items, 2^28 with Move Specs less, has always been refused; a launch has fewer than 2^32 threads,
 // and the plan's has four per shape)
 bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels) {
-  if (n_shapes >= (1u << 30) - 4 * kPlanShapes || n_levels > kMaxLevels - kMaxRanks + 1) return false;
+  if (n_shapes >= (1u << 30) - 64u || n_levels > kMaxLevels - kMaxRanks + 1) return false;
   for (uint32_t l = 0; l < n_levels; l++)
     if ((uint64_t)(level_off[l + 1] - level_off[l]) * h.npass >= (1ull << 32) / (h.moves ? 32 : 16)) return false;
   return true;
 }
 size_t plan_bytes_recs(uint32_t n_shapes) { return (size_t)n_shapes * sizeof(ShapeRec); }
 
-void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_shapes, const uint32_t* level_shapes, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B,
-                 uint32_t* fitmap, Counters* ctr, void* prefill_cost, void* prefill_arg, hipStream_t stream) {
-  const uint32_t per_wave = plan_shapes(n_shapes);
-  hipLaunchKernelGGL(plan_kernel, dim3((n_shapes + 4 * per_wave - 1) / (4 * per_wave)), dim3(256), 0, stream, P,
-                     n_shapes, per_wave, fit_map_stored(h) ? 1u : 0u, level_shapes, (ShapeRec*)B.recs, B.masks, fitmap, ctr, (uint4*)prefill_cost, (uint4*)prefill_arg);
-  hipLaunchKernelGGL(count_units_kernel, dim3((n_blk * kBlockItems + 255) / 256), dim3(256), 0, stream, P, B.level_off, B.blk_off, n_levels, n_blk,
-                     (const ShapeRec*)B.recs, B.masks, B.cnt);
-  hipLaunchKernelGGL(scan_units_kernel, dim3(n_levels * h.nranks), dim3(1024), 0, stream, B.blk_off, n_levels, h.nranks, n_blk, B.cnt, B.seg, B.diag, &ctr->ticket);
+void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, Counters* ctr, hipStream_t stream) {
+  hipLaunchKernelGGL(plan_kernel, dim3((uint32_t)(((uint64_t)n_blk * kBlockItems + 255) / 256)), dim3(256), 0, stream, P, B.level_shapes, B.level_off, B.blk_off, n_levels, n_blk,
+                     (ShapeRec*)B.recs, B.masks, B.cnt);
+  hipLaunchKernelGGL(scan_units_kernel, dim3(n_levels * h.nranks), dim3(1024), 0, stream, B.blk_off, n_levels, h.nranks, n_blk, B.cnt, B.seg, B.host_diag, &ctr->ticket);
 }
 
-void launch_list_units(const DevParams* P, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream) {
-  hipLaunchKernelGGL(emit_units_kernel, dim3((n_blk + 3) / 4), dim3(256), 0, stream, P, B.level_off, B.blk_off, n_levels, n_blk, (const ShapeRec*)B.recs, B.masks,
-                     B.cnt, B.seg, (uint2*)B.list, w0, w_len);
+void launch_fit_map(const DevParams* P, uint32_t n_specs, const PlanBuffers& B, uint32_t* fitmap, uint32_t n_words, hipStream_t stream) {
+  hipLaunchKernelGGL(fit_map_kernel, dim3((n_words + 2 + 255) / 256), dim3(256), 0, stream, P, n_specs, B.masks, (unsigned long long*)fitmap, n_words);
+}
+
+void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream) {
+  const uint64_t items = (uint64_t)n_blk * kBlockItems;
+  uint32_t each = h.ncombo > 64 ? kListItems / 4 : kListItems;      // (enough workgroups, of a few hundred units)
+  while (each > 64 && items / each * h.nranks < 2048) each /= 2;
+  hipLaunchKernelGGL(list_units_kernel, dim3((uint32_t)((items + each - 1) / each), h.nranks), dim3(256), 0, stream, P, B.level_shapes, B.level_off, B.blk_off, n_levels, n_blk,
+                     (const ShapeRec*)B.recs, B.masks, B.cnt, B.seg, (uint2*)B.list, w0, w_len, each);
 }
 
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream) {
