@@ -683,7 +683,9 @@ int32_t get_compiled(const mrl_target_desc& T, const mrl_lattice_desc* L, Compil
 
 // A second stream (default priority, non-blocking) for work that is independent of what runs on
 // the caller's stream: one of the two box lists beside the other; with it the events and the pinned counters a solve needs.
-constexpr size_t kDiagFirst = 16, kPinnedCounts = kDiagFirst + 64;   // u32: 16 for the box lists, then the diagonals' first places in the work list (at most 62)
+// u32: 16 for the box lists, then the diagonals' first places in the work list (at most 62), then the counters (a copy to memory
+// that is not pinned goes through a staging buffer and waits for it)
+constexpr size_t kDiagFirst = 16, kCountersAt = kDiagFirst + 64, kPinnedCounts = kCountersAt + sizeof(Counters) / 4;
 struct Aux {
   hipStream_t stream = nullptr;
   std::vector<hipEvent_t> events;
@@ -1405,7 +1407,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
 
   // ---- compression ----
   const Geo& g = c.geo;
-  Counters h_ctr;
+  Counters& h_ctr = *reinterpret_cast<Counters*>(aux->h_counts + kCountersAt);
   size_t needed = 0;
   bool merged = false;
   for (uint32_t i = 0; i < n_ways && !merged; i++) {
@@ -1459,9 +1461,9 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     scan_mask_words(maskL[1], f.n_words, tile_tmp, prefL[1], d_tot + 1, st);
     HIP_TRY(hipEventRecord(aux->events[ev_used], s2));
     HIP_TRY(hipStreamWaitEvent(st, aux->events[ev_used++], 0));
-    uint32_t h_tot[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(h_tot, d_tot, 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(aux->h_counts, d_tot, 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    const uint32_t h_tot[2] = {aux->h_counts[0], aux->h_counts[1]};
 
     // The two lists are merged side by side, the decisions on the helper stream: most of the
     // kernels are bound by latency, not bandwidth.  The host waits twice per list: for the number
