@@ -216,14 +216,16 @@ def main():
     fused = big_kind in (W.KIND_FUSED_MM_ADD_RELU, W.KIND_FUSED_BOUNDED, W.KIND_MATMUL_CHAIN)    # two reads for the bufferize
     n_launch = stats[big]["n_levels_run"]
     has_deps = any(deps for label, _, deps in cfg["lattices"] if label == big)
-    kernel_text = ("fill of table %s: plan_kernel, sort_work_kernel, the (INF, NONE) pre-fill (%s), "
-                   "fill_kernel per dependency level (bundles of small items, and the wide ones beside them)"
-                   % (big, "fill_ones_short_kernel, beside the fills of the tables it reads" if has_deps else "inside plan_kernel"))
+    # one launch per diagonal: dependency level of shapes + rank (sum of the operand levels).  Runs of
+    # tiny diagonals share a launch, and those without an admissible Spec have none: an upper bound
+    if big_kind != W.KIND_MOVE:
+        n_launch += W.n_operands(big_kind) * (cfg["target"]["n_levels"] - 1)
+    kernel_text = ("fill of table %s: the (INF, NONE) pre-fill%s, plan_kernel, scan_units_kernel, list_units_kernel, "
+                   "the fill kernels, one launch per diagonal of (dependency level, rank)"
+                   % (big, " (beside the fills of the tables it reads)" if has_deps else ""))
     if big_kind == W.KIND_MOVE:
         kernel_text = "fill of table %s: fill_units_kernel, one launch per dependency level" % big
     elif big_kind in W.BOUNDED_KINDS:
-        # one launch per diagonal: dependency level of shapes + rank (sum of the operand levels)
-        n_launch += W.n_operands(big_kind) * (cfg["target"]["n_levels"] - 1)
         kernel_text = "fill of table %s: fill_units_kernel, one launch per diagonal of (dependency level, rank)" % big
     n_big, adm_big = sizes[big], stats[big]["n_admissible"]
     algo_bytes = method_bytes(n_big, adm_big, fused)
@@ -270,7 +272,7 @@ def main():
     R["measured_traffic_frac"] = None if traffic is None or stale else frac(traffic, big_fill_ms)
     R["frac_dense_formula"] = frac(18 * n_big, big_fill_ms)
     # the two kernel groups of that fill: the streaming pre-fill (with the work lists), and the
-    # level kernels, which read and write the admissible Specs only
+    # diagonals' kernels, which read and write the admissible Specs only
     big_levels_ms = big_fill_ms - big_prefill_ms
     R["groups"] = {
         "prefill": {"ms": big_prefill_ms, "bytes": 10 * n_big, "frac": frac(10 * n_big, big_prefill_ms)},

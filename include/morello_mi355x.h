@@ -272,7 +272,7 @@ int32_t mrl_geometry(const mrl_target* t, const mrl_lattice_desc* lat,
  */
 typedef struct {
   uint64_t n_specs, n_admissible, n_rewrites; /* rewrites enumerated over all admissible Specs */
-  uint32_t n_levels_run;                      /* dependency levels = fill launches             */
+  uint32_t n_levels_run;                      /* dependency levels of shapes                   */
   float fill_ms, compress_ms;                 /* device time, HIP events on the given stream   */
   uint64_t n_decision_boxes, n_cost_boxes;
   uint64_t scratch_used;                      /* bytes of d_scratch actually needed            */
