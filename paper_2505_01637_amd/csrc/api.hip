@@ -1319,7 +1319,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   // The pre-fill, (INF, NONE) over both tables, and the fit map run beside the plan and the fill on the helper stream, where they take
   // longer than the events do: the pre-fill is done before the first diagonal, the map before the compression.  (A lattice that
   // reads other tables streams the pre-fill behind its plan.)  What comes before the first diagonal is host time on small tables: the
-  // map is launched when the diagonals are.
+  // map is launched when the diagonals are.  The line: beside at any size, the vector-matrix product (180 shapes) 440 ->
+  // 463 us; never beside, the pipeline 3022 -> 3051 (F's 449.5 M Specs), all between within 1 % of each other.
   const bool beside = c.n_specs >= (1u << 21);
   if (!deps_late && beside) {
     HIP_TRY(hipStreamWaitEvent(s2, uploaded, 0));
