@@ -561,8 +561,7 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
       for (uint32_t op = 0; op < P.nops; op++) pack |= ((combo / P.lvpow[op]) % P.NL) << P.pack_shift[op];
       uint32_t info = pack;
       for (uint32_t op = 0; op < P.nops; op++) info |= 1u << (8 + 4 * ((combo / P.lvpow[op]) % P.NL) + op);
-      P.pos_info[i] = info;
-      P.combo_info[combo] = info;
+      P.combo_info[P.gather ? i : combo] = info;
       P.rank_mask[order[i].first][combo >> 6] |= 1ull << (combo & 63);
     }
   }

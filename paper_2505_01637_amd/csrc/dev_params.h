@@ -80,9 +80,10 @@ struct DevParams {
   // ---- operand-level combos ordered by rank (sum of operand levels) ----
   uint32_t nranks;
   uint32_t rank_off[kMaxRanks + 2];
-  // per rank-major position: pack | (operands resident in level l, one nibble per level) << 8
-  uint32_t pos_info[kMaxCombo];
-  uint32_t combo_info[kMaxCombo];  // the same in the order of the mixed-radix index (table order)
+  // pack | (operands resident in level l, one nibble per level) << 8 of every level assignment: rank by rank (rank_off) where the kind is
+  // filled by gathers, else in the order of the mixed-radix index (table order).  (One list: a program may keep a scratch buffer of the
+  // least size that a solve takes, and these parameters are part of it.)
+  uint32_t combo_info[kMaxCombo];
   unsigned long long rank_mask[kMaxRanks][4];      // level assignments of a rank, bit = mixed-radix index
   uint32_t nwp;              // 64-bit words of an item's mask per value of the dtype bits: ceil(ncombo / 64)
   // ---- memory bounds as coordinates (a Matmul lattice whose Specs carry a bound per level of

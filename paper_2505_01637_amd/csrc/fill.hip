@@ -1421,7 +1421,7 @@ __global__ __launch_bounds__(256) void fill_units_kernel(const DevParams* __rest
     const uint32_t shape = all_level_shapes[segs.first_shape[seg] + sl];
     Shape S;
     load_shape(P, shape, S);
-    const uint32_t pack = P->pos_info[c0 + ci] & 0xFFu;
+    const uint32_t pack = P->combo_info[c0 + ci] & 0xFFu;
     uint32_t combo = 0, lv[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < 4; i++)
@@ -1742,7 +1742,7 @@ __global__ __launch_bounds__(256) void fill_bounded_kernel(const DevParams* __re
     const uint32_t shape = level_shapes[sl];
     Shape S;
     load_shape(P, shape, S);
-    const uint32_t pack = P->pos_info[c0 + ci] & 0xFFu;
+    const uint32_t pack = P->combo_info[c0 + ci] & 0xFFu;
     uint32_t lv[4] = {0, 0, 0, 0}, combo = 0;
 #pragma unroll
     for (int i = 0; i < 4; i++)

@@ -24,13 +24,22 @@ def buffer(n):
     assert hip.hipMalloc(C.byref(p), C.c_size_t(n)) == 0
     return p
 
-def solve(target, lat, scratch_bytes=None, stream=None):
+def solve(target, lat, scratch_bytes=None, stream=None, deps=()):
     cost, arg, most = B.table_bytes(target, lat)
     scratch_bytes = most if scratch_bytes is None else scratch_bytes
     h, stats = C.c_void_p(), B.Stats()
-    B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(lat)), None, C.c_uint32(0), buffer(cost), buffer(arg), buffer(scratch_bytes),
-                               C.c_size_t(scratch_bytes), stream, C.byref(h), C.byref(stats)))
-    return B.Table(h, target, lat, B.geometry(target, lat)[0], None, stats)
+    handles = (C.c_void_p * max(1, len(deps)))(*[d._h for d in deps])
+    B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(lat)), handles if deps else None, C.c_uint32(len(deps)), buffer(cost), buffer(arg),
+                               buffer(scratch_bytes), C.c_size_t(scratch_bytes), stream, C.byref(h), C.byref(stats)))
+    return B.Table(h, target, lat, B.geometry(target, lat)[0], None, stats, deps)
+
+def least_scratch(target, lat, deps=()):
+    try:
+        solve(target, lat, 256, deps=deps)
+    except B.MorelloError as e:
+        assert e.code == B.E_NOMEM
+        return int(re.search(r"at least (\d+)", str(e)).group(1))
+    assert False
 """
 
 ASK = HEAD + r"""
@@ -78,12 +87,7 @@ def launched(scratch_bytes=None):
 
 total, rows, boxes = launched()
 assert total == 0 and rows > 5 and boxes == 0, "plenty of scratch: by words, nothing asked before"
-try:
-    solve(target, lat, 256)
-    assert False
-except B.MorelloError as e:
-    assert e.code == B.E_NOMEM
-    least = int(re.search(r"at least (\d+)", str(e)).group(1))
+least = least_scratch(target, lat)
 hip.fake_row_total(many)
 total, rows, boxes = launched(least + 4096)
 assert rows == 0 and boxes > 0 and total == (1 if many > few else 0), "the words cannot fit: no kernel of that merge"
@@ -91,6 +95,27 @@ if many > few:
     hip.fake_row_total(few)
     total, rows, boxes = launched(least + 4096)
     assert total == 1 and rows > 5 and boxes == 0, "few of the rows are kept: their words fit"
+print("done")
+"""
+
+SCRATCH = HEAD + r"""
+# (configuration, largest size, table): what mrl_table_bytes asked for, and the least that a solve took
+enough = {(1, 16, "M"): (5966080, 457216), (2, None, "M"): (3041477888, 29908736), (3, 8, "M"): (1563904, 88832),
+          (3, None, "M"): (16899584, 307712), (4, 8, "M"): (24762112, 1164544), (4, None, "M"): (4322228480, 54018304),
+          (5, 2, "M"): (823552, 85760), (5, 2, "E"): (219904, 35072), (5, 2, "F"): (12913920, 1114880), (6, 8, "P"): (6072576, 172800),
+          (7, 2, "B"): (173770240, 1400832), (9, 8, "V"): (27818240, 1271040), (9, 4, "M"): (6203648, 303872),
+          (10, 4, "G"): (254094080, 15173376), (11, 4, "A"): (459776, 44544), (11, 4, "R"): (129792, 24832), (11, 4, "S"): (459776, 44544),
+          (12, 4, "M"): (24762112, 1164544)}
+for (number, most, want), (asked, least) in enough.items():
+    cfg = W.config(number, max_size=most)
+    target, tabs = B.Target(cfg["target"]), {}
+    for label, lat, deps in cfg["lattices"]:
+        deps = [tabs[d] for d in deps]
+        if label == want:
+            assert B.table_bytes(target, lat)[2] <= asked, (number, most, label, B.table_bytes(target, lat)[2])
+            assert least_scratch(target, lat, deps) <= least, (number, most, label, least_scratch(target, lat, deps))
+            break
+        tabs[label] = solve(target, lat, deps=deps)
 print("done")
 """
 
@@ -120,3 +145,9 @@ def test_no_merge_by_words_that_cannot_fit(case, tmp_path):
     """Scratch that holds the boxes and not the words: nothing of the merge by words is launched, where the sizes tell
     (one row per plane is kept at least) and where the number of rows, which is asked for then, does."""
     run_on_fake_hip(tmp_path, ROWS, case)
+
+
+def test_scratch_that_sufficed_suffices(tmp_path):
+    """A program may keep a buffer of exactly the size that mrl_table_bytes once asked for, or of the least that a solve
+    once took, for every kind of lattice: neither has grown."""
+    run_on_fake_hip(tmp_path, SCRATCH)
