@@ -73,6 +73,7 @@ struct FillArgs {
   uint32_t mstride[4], pack_shift[4], lay_bit[4];
   uint32_t lay_xor[4], cv_bit[4];                              // layout bit of an operand's entry, dtype bit that a converting Move clears (0: none)
   uint32_t convert, s, sync, move_base, buf_id, par_shift;
+  uint32_t lg_split;                                           // lanes that share an entry where it is split: 1 << lg_split
   uint32_t has_buf, split, chain, GM, VM, GE, VE, nszE_n, kM_first, nkM, nsz3, layM[3], layE[3], zero[4];
 };
 FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr);

@@ -992,7 +992,8 @@ __device__ __forceinline__ void fill_quad(const FillArgs& A, const uint2 un, uin
 // One entry shared by S lanes (all of them active), eight or, without layouts, four: lane s takes the Moves of operand s & 3
 // that change the layout by s >> 2 (or s >> 2 + 2), and tiles s, s + S, ...; the first also the microkernels and the
 // bufferize.
-constexpr uint32_t split_lanes(bool lay) { return lay ? 8u : 4u; }
+constexpr uint32_t lg_split_lanes(bool lay) { return lay ? 3u : 2u; }
+constexpr uint32_t split_lanes(bool lay) { return 1u << lg_split_lanes(lay); }
 template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
 __device__ __forceinline__ void fill_entry_split(const FillArgs& A, const uint2 un, uint32_t c, uint32_t s, bool active, const uint4* coef, const OpTab* tab, uint32_t& n_rw, uint32_t& ovf) {
   constexpr uint32_t kMine = 4, S = split_lanes(LAY); // tiles at a time
@@ -1197,7 +1198,7 @@ __global__ __launch_bounds__(256) void fill_quad_kernel(const FillArgs A, const 
 // Eight lanes per entry, or four without layouts.
 template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
 __global__ __launch_bounds__(256) void fill_split_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
-  constexpr uint32_t lgS = LAY ? 3u : 2u;
+  constexpr uint32_t lgS = lg_split_lanes(LAY);
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
   const uint64_t t = ((uint64_t)die_block() * 256u + threadIdx.x) >> lgS;
@@ -1216,7 +1217,7 @@ template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
 __global__ __launch_bounds__(kChainThreads) void fill_chain_kernel(const FillArgs A, const uint2* __restrict__ units, const DiagRun run) {
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
-  constexpr uint32_t lgS = LAY ? 3u : 2u;
+  constexpr uint32_t lgS = lg_split_lanes(LAY);
   load_tabs(A, coef, tab);
   uint32_t n_rw = 0, ovf = 0;
   for (uint32_t d = 0; d < run.n; d++) {
@@ -1951,7 +1952,7 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
     A.zero[i] = h.zero[i];
     A.tile_dims |= h.tile_dim_ok[i] && h.nsz[i] > 1 ? 1u << i : 0u;
   }
-  A.unit_lay = h.unit_lay; A.convert = h.convert; A.s = h.s; A.sync = h.sync;
+  A.unit_lay = h.unit_lay; A.lg_split = lg_split_lanes(h.moves || h.nlay); A.convert = h.convert; A.s = h.s; A.sync = h.sync;
   A.move_base = h.move_base; A.buf_id = h.buf_id; A.par_shift = h.par_base - h.tile_base;
   A.has_buf = h.kind == kKindF || h.split; A.split = h.split; A.chain = h.chain;
   A.GM = h.GM; A.VM = h.VM; A.GE = h.GE; A.VE = h.VE; A.nszE_n = h.nszE_n; A.kM_first = h.kM_first; A.nkM = h.nkM; A.nsz3 = h.nsz[3];
@@ -1972,14 +1973,14 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
   const auto blocks = [](uint64_t lanes) { return dim3((uint32_t)((lanes + 255) / 256)); };
   if (run.chain) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_chain_kernel<LAY, MOVES, SMALL, PAR, MN>), dim3(1), dim3(kChainThreads), 0, stream, A, list, run);
   else if (!LAY || PAR || tasks <= kSplitTasks)
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_split_kernel<LAY, MOVES, SMALL, PAR, MN>), blocks(tasks * split_lanes(LAY)), dim3(256), 0, stream, A, units, n);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_split_kernel<LAY, MOVES, SMALL, PAR, MN>), blocks(tasks << A.lg_split), dim3(256), 0, stream, A, units, n);
   else if constexpr (LAY && !PAR) {
     if (!MOVES && !A.ndt && A.unit_lay >= 2) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
     else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
   }
 }
 
-bool small_diagonal(const FillArgs& A, uint32_t n) { return ((uint64_t)n << A.unit_lay) * split_lanes(A.unit_lay != 0) <= kChainThreads; }
+bool small_diagonal(const FillArgs& A, uint32_t n) { return (uint64_t)n << (A.unit_lay + A.lg_split) <= kChainThreads; }
 
 void launch_fill_diagonals(const FillArgs& A, const DevParams& h, const void* list, const DiagRun& run, hipStream_t stream) {
   const uint2* l = (const uint2*)list;

@@ -1,14 +1,15 @@
 /* A HIP runtime of two devices without kernels, for tests of the library's host part on the CPU.
  * "Device" memory is host memory, launches do nothing but are counted by the device they go to, copies are
  * made at once.  As in HIP, a stream and an event belong to the device that was current when they were made
- * (the null stream to the current one), and an event is recorded on a stream of its own device only. */
+ * (the null stream to the current one), an event is recorded on a stream of its own device only, and a launch has fewer
+ * than 2^32 threads along each axis. */
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
 
 typedef struct { uint32_t x, y, z; } dim3;
 struct on { int device; };
-enum { kDevices = 2, kInvalidValue = 1, kInvalidDevice = 101, kInvalidHandle = 400 };
+enum { kDevices = 2, kInvalidValue = 1, kInvalidConfiguration = 9, kInvalidDevice = 101, kInvalidHandle = 400 };
 
 static __thread int current;
 static __thread struct { dim3 grid, block; size_t shared; void* stream; } config;
@@ -16,6 +17,8 @@ static int launched[kDevices];
 static struct { const void* f; char name[120]; int launched; } kernels[256];
 static int n_kernels;
 static uint32_t row_total;          /* what row_total_kernel finds */
+static uint32_t units;              /* of every diagonal, as scan_units_kernel finds them */
+static __thread int last_error;
 
 static int device_of(void* stream) { return stream ? ((struct on*)stream)->device : current; }
 static int make(void** out) {
@@ -33,10 +36,11 @@ int fake_launches_of(const char* part) {
   return n;
 }
 void fake_row_total(uint32_t n) { row_total = n; }
+void fake_units(uint32_t n) { units = n; }
 
 int hipGetDevice(int* d) { *d = current; return 0; }
 int hipSetDevice(int d) { if (d < 0 || d >= kDevices) return kInvalidDevice; current = d; return 0; }
-int hipGetLastError(void) { return 0; }
+int hipGetLastError(void) { int e = last_error; last_error = 0; return e; }
 const char* hipGetErrorString(int e) { return e == kInvalidHandle ? "invalid resource handle" : "error"; }
 
 int hipStreamCreateWithFlags(void** s, unsigned flags) { (void)flags; return make(s); }
@@ -64,12 +68,17 @@ int hipMemsetAsync(void* p, int v, size_t n, void* s) { (void)s; memset(p, v, n)
 int hipGetSymbolAddress(void** p, const void* symbol) { (void)symbol; *p = 0; return kInvalidValue; }
 
 int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shared, void* s) {
-  (void)grid; (void)block; (void)shared;
+  (void)shared;
+  if ((uint64_t)grid.x * block.x >> 32 || (uint64_t)grid.y * block.y >> 32 || (uint64_t)grid.z * block.z >> 32) return last_error = kInvalidConfiguration;
   __atomic_add_fetch(&launched[device_of(s)], 1, __ATOMIC_SEQ_CST);
   for (int i = 0; i < n_kernels; i++) {
     if (kernels[i].f != f) continue;
     __atomic_add_fetch(&kernels[i].launched, 1, __ATOMIC_SEQ_CST);
     if (strstr(kernels[i].name, "row_total_kernel")) **(uint32_t**)args[2] = row_total;
+    if (strstr(kernels[i].name, "scan_units_kernel")) {
+      const uint32_t diagonals = *(uint32_t*)args[1] + *(uint32_t*)args[2] - 1;
+      for (uint32_t d = 0; d <= diagonals; d++) (*(uint32_t**)args[6])[d] = d * units;
+    }
   }
   return 0;
 }

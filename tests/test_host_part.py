@@ -119,6 +119,24 @@ for (number, most, want), (asked, least) in enough.items():
 print("done")
 """
 
+FORMS = HEAD + r"""
+# every diagonal of a Matmul whose Moves are Move Specs, without layouts, has 128 or 129 entries; a chain's workgroup of 1024 lanes takes
+# eight of them an entry
+cfg = W.config(9, max_size=2)
+(_, lat_v, _), (_, lat_m, _) = cfg["lattices"]
+lat_m["layout_coord"] = [0] * 5
+target = B.Target(cfg["target"])
+moves = solve(target, lat_v)
+for units, chained in ((128, True), (129, False)):
+    hip.fake_units(units)
+    for part in ("fill_chain", "fill_split"):
+        hip.fake_launches_of(part.encode())
+    tab = solve(target, lat_m, deps=[moves], scratch_bytes=64 << 20)
+    chains, splits = (hip.fake_launches_of(part.encode()) for part in ("fill_chain", "fill_split"))
+    assert (chains, splits) == ((1, 0) if chained else (0, 13)), (units, chains, splits)        # 4 dependency levels, 10 ranks
+print("done")
+"""
+
 
 def run_on_fake_hip(tmp_path, program, *args):
     gcc = shutil.which("gcc")
@@ -151,3 +169,8 @@ def test_scratch_that_sufficed_suffices(tmp_path):
     """A program may keep a buffer of exactly the size that mrl_table_bytes once asked for, or of the least that a solve
     once took, for every kind of lattice: neither has grown."""
     run_on_fake_hip(tmp_path, SCRATCH)
+
+
+def test_chains_hold_diagonals_of_one_round(tmp_path):
+    """A chain takes the diagonals that its workgroup does in one go, by the lanes that its kernel has per entry."""
+    run_on_fake_hip(tmp_path, FORMS)
