@@ -1361,6 +1361,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   if (P.moves) launch_bind(d_P, (uint64_t*)(base + f.bind), (uint32_t)bind_entries(c), st);
   const uint32_t* diag = plan.host_diag;
   const FillArgs fill = fill_args(d_P, P, plan, tab->d_cost, tab->d_arg, d_ctr);
+  const uint32_t most = most_units(fill);
   uint32_t w0 = 0;                        // the list holds units [w0, w0 + window)
   DiagRun run;
   run.n = 0;
@@ -1375,7 +1376,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
         w0 = u;
         launch_list_units(d_P, P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), st);
       }
-      const uint32_t n = std::min(diag[d + 1] - u, window - (u - w0));
+      const uint32_t n = std::min({diag[d + 1] - u, window - (u - w0), most});
       const bool small = small_diagonal(fill, n);
       if (!small || run.n == kRunMost) flush();
       run.chain = small;

@@ -82,6 +82,7 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
 constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768;
 struct DiagRun { uint32_t n, chain, start[kRunMost + 1]; };
 bool small_diagonal(const FillArgs& A, uint32_t n_units);
+uint32_t most_units(const FillArgs& A);            // that one launch takes
 void launch_fill_diagonals(const FillArgs& A, const DevParams& h, const void* list, const DiagRun& run, hipStream_t stream);
 
 // Segments of one launch of the bounded fill: segment i is (dependency level of shapes, rank)

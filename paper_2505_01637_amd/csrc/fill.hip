@@ -1982,6 +1982,9 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
 
 bool small_diagonal(const FillArgs& A, uint32_t n) { return (uint64_t)n << (A.unit_lay + A.lg_split) <= kChainThreads; }
 
+// (a launch has fewer than 2^32 threads, in workgroups of 256; split entries have the most)
+uint32_t most_units(const FillArgs& A) { return (uint32_t)(((1ull << 32) - 256) >> (A.unit_lay + A.lg_split)); }
+
 void launch_fill_diagonals(const FillArgs& A, const DevParams& h, const void* list, const DiagRun& run, hipStream_t stream) {
   const uint2* l = (const uint2*)list;
   const bool mn = h.kind != kKindM;

@@ -137,6 +137,31 @@ for units, chained in ((128, True), (129, False)):
 print("done")
 """
 
+LIMIT = HEAD + r"""
+# diagonals around the most that one launch's threads can take: eight lanes per entry and eight entries per unit, or four and one
+layouts, most = {"layouts": ([1, 1, 1, 0, 0], (1 << 26) - 4), "no-layouts": ([0] * 5, (1 << 30) - 64)}[sys.argv[3]]
+cfg = W.config(6, max_size=1)
+for _, lat, _ in cfg["lattices"]:
+    lat["layout_coord"] = layouts
+if layouts[0] == 0:
+    cfg["target"].update(n_levels=1, microkernels=[])                 # (one diagonal: the places in the list are 32 bits)
+target, (serial, parallel) = B.Target(cfg["target"]), [lat for _, lat, _ in cfg["lattices"]]
+table = solve(target, serial)
+diagonals = 10 if layouts[0] else 1
+room = buffer(1 << 20)                            # (nothing is launched: the list's places are never written)
+for units, pieces in ((most, 1), (most + 1, 2), (most + 100, 2)):
+    hip.fake_units(units)
+    for part in (b"fill_split", b"fill_chain"):
+        hip.fake_launches_of(part)
+    h, stats = C.c_void_p(), B.Stats()
+    B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(parallel)), (C.c_void_p * 1)(table._h), C.c_uint32(1), buffer(1 << 20), buffer(1 << 20), room,
+                               C.c_size_t(1 << 40), None, C.byref(h), C.byref(stats)))
+    launches = hip.fake_launches_of(b"fill_split") + hip.fake_launches_of(b"fill_chain")       # (a chain: a rest of few entries)
+    assert launches == diagonals * pieces, (units, pieces, launches)
+    assert stats.n_admissible == units * diagonals << (3 if layouts[0] else 0)
+print("done")
+"""
+
 
 def run_on_fake_hip(tmp_path, program, *args):
     gcc = shutil.which("gcc")
@@ -174,3 +199,9 @@ def test_scratch_that_sufficed_suffices(tmp_path):
 def test_chains_hold_diagonals_of_one_round(tmp_path):
     """A chain takes the diagonals that its workgroup does in one go, by the lanes that its kernel has per entry."""
     run_on_fake_hip(tmp_path, FORMS)
+
+
+@pytest.mark.parametrize("case", ["layouts", "no-layouts"])
+def test_diagonals_of_more_entries_than_a_launch_has_threads_for(case, tmp_path):
+    """A launch has fewer than 2^32 threads; a diagonal of the largest tables asks for more, and goes in pieces."""
+    run_on_fake_hip(tmp_path, LIMIT, case)
