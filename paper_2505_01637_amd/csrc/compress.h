@@ -79,7 +79,7 @@ struct FillArgs {
 FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr);
 // Diagonals that one launch takes: n of them, diagonal i at places [start[i], start[i + 1]) of the list.  Small ones
 // (small_diagonal) go into a chain, any other is a launch of its own.
-constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768;
+constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768, kParSplitTasks = 262144;
 struct DiagRun { uint32_t n, chain, start[kRunMost + 1]; };
 bool small_diagonal(const FillArgs& A, uint32_t n_units);
 uint32_t most_units(const FillArgs& A);            // that one launch takes

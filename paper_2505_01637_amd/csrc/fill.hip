@@ -566,22 +566,28 @@ struct Best {
 };
 
 // The tiles of one entry, those of the dimensions one after the other, kBatch of them at a time in registers.
-// MN: only m and n are tiled.
-template <bool MN>
+// MN: only m and n are tiled.  PAR: the parallel loops over b, m, n after the serial ones.
+template <bool MN, bool PAR>
 struct Tiles {
-  uint32_t n, done, q, at, b1, b2, b3, lo1, lo2, lo3;       // q: entry of the list behind tile `at`; b_d: the first tile of dimension d
+  uint32_t n, n_serial, done, q, at, b1, b2, b3, lo0, lo1, lo2, lo3;       // q: entry of the list behind tile `at`; b_d: the first tile of dimension d
   uint4 st[kBatch];
   __device__ __forceinline__ void begin(const uint32_t lo[4], uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
-    b1 = c0; b2 = c0 + c1; b3 = b2 + c2; n = b3 + c3;
-    lo1 = lo[1]; lo2 = lo[2]; lo3 = lo[3];
+    b1 = c0; b2 = c0 + c1; b3 = b2 + c2; n = n_serial = b3 + c3;
+    if (PAR) n += b2 + c3;
+    lo0 = lo[0]; lo1 = lo[1]; lo2 = lo[2]; lo3 = lo[3];
     done = at = 0;
-    q = MN ? lo1 : lo[0];
+    q = MN ? lo1 : lo0;
     jump();
   }
   __device__ __forceinline__ void jump() {                  // (a dimension without tiles begins where the next one does)
     if (!MN) q = at == b1 ? lo1 : q;
     if (!MN) q = at == b2 ? lo2 : q;
     q = at == b3 ? lo3 : q;
+    if (PAR) {
+      q = at == n_serial ? lo0 : q;
+      q = at == n_serial + b1 ? lo1 : q;
+      q = at == n_serial + b2 ? lo3 : q;
+    }
   }
   __device__ __forceinline__ void fetch(const TileStep* steps) {
 #pragma unroll
@@ -599,13 +605,43 @@ __device__ __forceinline__ uint64_t at_cell(const uint64_t* table, uint32_t cell
   return SMALL ? *(const uint64_t*)((const char*)table + cell * 8u) : table[cell];
 }
 
+// The tiles of one entry, the first kBatch of them fetched: the same entry of a smaller shape; a parallel loop's body is an
+// entry of the serial table.  over, over2: bits of finite candidates at 2^62 and above.
+template <bool SMALL, bool MN, bool PAR>
+__device__ __forceinline__ void take_tiles(const FillArgs& A, Tiles<MN, PAR>& tiles, uint32_t cell, Best& e, uint32_t& over, uint32_t& over2) {
+  for (;;) {
+    uint64_t sub[kBatch];
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; u++)
+      if (tiles.done + u < tiles.n) {
+        const uint64_t* table = A.cost;
+        if (PAR && tiles.done + u >= tiles.n_serial) table = A.costM;
+        sub[u] = at_cell<SMALL>(table, cell - tiles.st[u].x);
+      }
+#pragma unroll
+    for (uint32_t u = 0; u < kBatch; u++)
+      if (tiles.done + u < tiles.n) {
+        const bool loop = PAR && tiles.done + u >= tiles.n_serial, fin = (uint32_t)(sub[u] >> 32) != ~0u;
+        const uint32_t a = fin ? (loop ? tiles.st[u].w : tiles.st[u].y) : 0u;
+        const uint64_t lo = (uint64_t)a * (uint32_t)sub[u] + (loop ? A.sync : A.s);   // (32 x 32 bits + 32 bits: no wrap)
+        const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);      // bits 32.. of the sum
+        over |= (uint32_t)hi;
+        over2 |= (uint32_t)(hi >> 32);
+        e.take((hi << 32) | (uint32_t)lo, tiles.st[u].z + (loop ? A.par_shift : 0u), fin);
+      }
+    tiles.done += kBatch;
+    if (!__any(tiles.done < tiles.n)) break;
+    tiles.fetch(A.steps);
+  }
+}
+
 // One entry: a unit and one of its layouts.  Its candidates are read from finished entries of the table (and of the
 // tables that it reads), several in flight.  Microkernels, Moves, the tiles of each dimension and the bufferize come in the
 // order of their ids, so a strictly lower cost is all that has to be tested, but for converting Moves, whose ids lie
 // between the others'.
 // coef: DevParams::mcoef in LDS.  over, over2: bits of finite candidates at 2^62 and above.
 // SMALL: coefficient * elements of every Move is below 2^62 and both fit 32 bits, and so do the table's byte offsets.
-template <bool MOVES, bool SMALL, bool MN>
+template <bool MOVES, bool SMALL, bool PAR, bool MN>
 __device__ __forceinline__ void fill_entry(const FillArgs& A, const uint2 un, uint32_t c, const uint4* coef, uint32_t& n_rw, uint32_t& ovf) {
   const uint4* rp = reinterpret_cast<const uint4*>(A.recs) + (size_t)un.x * 5u;
   const uint4 r0 = rp[0], r1 = rp[1], r2 = rp[2], r3 = rp[3], r4 = rp[4];
@@ -628,7 +664,7 @@ __device__ __forceinline__ void fill_entry(const FillArgs& A, const uint2 un, ui
 
   // tiles, kBatch at a time; the first are requested before the Moves' entries
   const uint32_t c0 = cnts & 0xFFu, c1 = (cnts >> 8) & 0xFFu, c2 = (cnts >> 16) & 0xFFu, c3 = cnts >> 24;
-  Tiles<MN> tiles;
+  Tiles<MN, PAR> tiles;
   tiles.begin(tlo, MN ? 0u : c0, c1, MN ? 0u : c2, c3);
   if (!MOVES) tiles.fetch(A.steps);
 
@@ -757,28 +793,8 @@ __device__ __forceinline__ void fill_entry(const FillArgs& A, const uint2 un, ui
     }
   }
 
-  // tiles: the same entry of a smaller shape
   if (MOVES) tiles.fetch(A.steps);
-  for (;;) {
-    uint64_t sub[kBatch];
-#pragma unroll
-    for (uint32_t u = 0; u < kBatch; u++)
-      if (tiles.done + u < tiles.n) sub[u] = at_cell<SMALL>(cost, cell - tiles.st[u].x);
-#pragma unroll
-    for (uint32_t u = 0; u < kBatch; u++)
-      if (tiles.done + u < tiles.n) {
-        const bool fin = (uint32_t)(sub[u] >> 32) != ~0u;
-        const uint32_t a = fin ? tiles.st[u].y : 0u;
-        const uint64_t lo = (uint64_t)a * (uint32_t)sub[u] + A.s;                     // (32 x 32 bits + 32 bits: no wrap)
-        const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo >> 32);      // bits 32.. of the sum
-        over |= (uint32_t)hi;
-        over2 |= (uint32_t)(hi >> 32);
-        e.take((hi << 32) | (uint32_t)lo, tiles.st[u].z, fin);
-      }
-    tiles.done += kBatch;
-    if (!__any(tiles.done < tiles.n)) break;
-    tiles.fetch(A.steps);
-  }
+  take_tiles<SMALL>(A, tiles, cell, e, over, over2);
   n_rw += r3.y;
   if (MN && !MOVES && A.has_buf) {
     Eval f;
@@ -1168,7 +1184,7 @@ __device__ __forceinline__ uint32_t die_block() {
 }
 
 // A diagonal: a lane per entry, the layouts of a unit in consecutive lanes (1 << unit_lay of them).
-template <bool MOVES, bool SMALL, bool MN>
+template <bool MOVES, bool SMALL, bool PAR, bool MN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void fill_entry_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
@@ -1177,7 +1193,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
   const uint2 un = units[u < n_units ? u : 0u];
   load_tabs(A, coef, tab);
   uint32_t n_rw = 0, ovf = 0;
-  if (u < n_units) fill_entry<MOVES, SMALL, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 1u), coef, n_rw, ovf);
+  if (u < n_units) fill_entry<MOVES, SMALL, PAR, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 1u), coef, n_rw, ovf);
   flush_counters(A.ctr, n_rw, ovf);
 }
 
@@ -1964,7 +1980,9 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
 // others issue fewer instructions per entry (diagonals of 20 blocks of a lane per entry 20 us, split 5; of 1.6 M entries, four
 // at a time, 33, a lane each 61, split more).  The line at 16,384, 32,768 or 65,536 entries: within 1 % of each other; none split: the
 // vector-matrix product 485 -> 594 us, the pipeline 3082 -> 3109; all split: 3912, two Matmuls 2001 -> 3196, packed layouts 2397 -> 2922.
-// Without layouts (four lanes) a split is never behind: all sizes to 64, 668 against 740 us of fill.
+// Without layouts (four lanes) a split is never behind: all sizes to 64, 668 against 740 us of fill.  With parallel loops the line lies higher
+// (three layouts, sizes to 24 and to 48, everything fits: split only 1676 and 10856 us, the line at 32,768 entries 1493 and 9855, at 262,144
+// 1481 and 9847, at 524,288 1529 and 9875; as much as fits the four-level target: 1073 and 3079, 1017 and 2890, 1029 and 2862, 1080 and 2910).
 template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
 static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run, hipStream_t stream) {
   const uint32_t n = run.start[1] - run.start[0];
@@ -1972,11 +1990,11 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
   const uint2* units = list + run.start[0];
   const auto blocks = [](uint64_t lanes) { return dim3((uint32_t)((lanes + 255) / 256)); };
   if (run.chain) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_chain_kernel<LAY, MOVES, SMALL, PAR, MN>), dim3(1), dim3(kChainThreads), 0, stream, A, list, run);
-  else if (!LAY || PAR || tasks <= kSplitTasks)
+  else if (!LAY || tasks <= (PAR ? kParSplitTasks : kSplitTasks))
     hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_split_kernel<LAY, MOVES, SMALL, PAR, MN>), blocks(tasks << A.lg_split), dim3(256), 0, stream, A, units, n);
-  else if constexpr (LAY && !PAR) {
-    if (!MOVES && !A.ndt && A.unit_lay >= 2) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
+  else if constexpr (LAY) {
+    if (!PAR && !MOVES && !A.ndt && A.unit_lay >= 2) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, PAR, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
   }
 }
 

@@ -402,11 +402,12 @@ def test_parity_bundles_of_items(case):
     compare_config(cfg)
 
 
-@pytest.mark.parametrize("case", ["three-layouts", "three-layouts-dear", "batched-three-layouts", "one-layout", "one-layout-dear", "dtypes", "no-layouts", "parallel", "fused-two-layouts"])
+@pytest.mark.parametrize("case", ["three-layouts", "three-layouts-dear", "batched-three-layouts", "one-layout", "one-layout-dear", "dtypes", "no-layouts", "parallel",
+                                  "parallel-three-layouts", "parallel-three-layouts-dear", "fused-two-layouts"])
 def test_parity_diagonals(case):
-    """Diagonals (dependency level + rank) of one entry, of up to 32,768, which are split, and of more, which are taken four
-    entries or one at a time; Move prices that fit 32 bits and (dear) that do not."""
-    cfg = W.config(3 if case == "dtypes" else 6 if case == "parallel" else 5 if case.startswith("fused") else 4, max_size=6)
+    """Diagonals (dependency level + rank) of one entry, of up to 32,768, which are split (with parallel loops up to 262,144), and of more,
+    which are taken four entries or one at a time; Move prices that fit 32 bits and (dear) that do not."""
+    cfg = W.config(3 if case == "dtypes" else 6 if case.startswith("parallel") else 5 if case.startswith("fused") else 4, max_size=6)
     t = cfg["target"]
     t["capacity_bytes"] = [W.UNBOUNDED] * 4
     if case.endswith("dear"):
@@ -423,6 +424,10 @@ def test_parity_diagonals(case):
             lat["layout_coord"] = [0, 1, 0, 0, 0]
         elif case == "no-layouts":
             lat["layout_coord"] = [0] * 5
+        elif case.startswith("parallel-"):
+            lat["layout_coord"] = [1, 1, 1, 0, 0]
+            q = sorted(r + [18, 20, 30, 36])
+            lat["sizes"] = [[1], q, q, q + [48, 60, 72, 96]]
         elif case.startswith("batched"):
             lat["sizes"] = [[1, 2, 3, 6], [1, 2, 3, 6, 12], [1, 5, 10, 20], [1, 2, 4, 8, 16]]
     if case == "fused-two-layouts":
