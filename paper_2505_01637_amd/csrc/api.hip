@@ -225,7 +225,7 @@ FixedLayout fixed_layout(const Compiled& c, bool may_turn = true) {
     f.masks = take(n_items * ((size_t)c.P.nwp << c.P.ndt) * 8);
     f.recs = take(plan_bytes_recs(c.n_shapes));
     f.unit_cnt = take((size_t)unit_blocks(c.level_off.data(), n_lev, c.P.npass, nullptr) * c.P.nranks * 4);
-    f.unit_seg = take((size_t)n_lev * c.P.nranks * 4);
+    f.unit_seg = take(((size_t)n_lev * c.P.nranks + 1) * 4);
     if (c.P.moves) f.bind = take(bind_entries(c) * 8);
     // the work list takes what is left of the buffer; where that is less than the whole list, it goes through in windows
     f.list = take(std::max<size_t>(n_items / 2, 64) * 8);
@@ -1336,7 +1336,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   }
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   hipEvent_t counts_ready = aux->events[ev_used++];
-  launch_list_units(d_P, P, n_lev, n_blk, plan, 0, window, st);
+  const uint64_t shapes_from = by_shapes_from(P, c.n_shapes, n_lev);
+  launch_list_units(d_P, P, n_lev, n_blk, plan, 0, window, shapes_from, st);
   if (prefilled) HIP_TRY(hipStreamWaitEvent(st, prefilled, 0)); else launch_prefill(tab->d_cost, tab->d_arg, c.n_specs, st);
   HIP_TRY(hipEventRecord(ev[4], st));
   prefill_timed = true;
@@ -1369,12 +1370,14 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     if (run.n) launch_fill_diagonals(fill, P, base + f.list, run, st);
     run.n = 0;
   };
-  for (uint32_t d = 0; d < n_diag; d++)
+  const bool by_shapes = diag[n_diag] >= shapes_from;
+  for (uint32_t l = 0; by_shapes && l < n_lev; l++) launch_fill_shapes(fill, P, plan.masks, c.level_off[l], c.level_off[l + 1] - c.level_off[l], st);
+  for (uint32_t d = 0; !by_shapes && d < n_diag; d++)
     for (uint32_t u = diag[d]; u < diag[d + 1];) {
       if (u - w0 >= window) {
         flush();
         w0 = u;
-        launch_list_units(d_P, P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), st);
+        launch_list_units(d_P, P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), UINT64_MAX, st);
       }
       const uint32_t n = std::min({diag[d + 1] - u, window - (u - w0), most});
       const bool small = small_diagonal(fill, n);

@@ -55,7 +55,7 @@ void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_levels, uint
 // Behind the plan: which cells fit, in table order, n_words words and two of zeros.
 void launch_fit_map(const DevParams* P, uint32_t n_specs, const PlanBuffers& B, uint32_t* fitmap, uint32_t n_words, hipStream_t stream);
 // Units [w0, w0 + w_len) of the work list to its place.
-void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream);
+void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, uint64_t none_from, hipStream_t stream);
 // The costs of the alloc-bindings of a Matmul whose Moves are Move Specs, from its Move table.
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream);
 // What the kernels of the diagonals read of the parameters, by value: they are short, and every read of the
@@ -73,6 +73,7 @@ struct FillArgs {
   uint32_t mstride[4], pack_shift[4], lay_bit[4];
   uint32_t lay_xor[4], cv_bit[4];                              // layout bit of an operand's entry, dtype bit that a converting Move clears (0: none)
   uint32_t convert, s, sync, move_base, buf_id, par_shift;
+  uint32_t nranks, npass, nwp;
   uint32_t lg_split;                                           // lanes that share an entry where it is split: 1 << lg_split
   uint32_t has_buf, split, chain, GM, VM, GE, VE, nszE_n, kM_first, nkM, nsz3, layM[3], layE[3], zero[4];
 };
@@ -81,6 +82,8 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
 // (small_diagonal) go into a chain, any other is a launch of its own.
 constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768, kParSplitTasks = 262144;
 struct DiagRun { uint32_t n, chain, start[kRunMost + 1]; };
+uint64_t by_shapes_from(const DevParams& h, uint32_t n_shapes, uint32_t n_levels);      // units
+void launch_fill_shapes(const FillArgs& A, const DevParams& h, const unsigned long long* masks, uint32_t first, uint32_t n, hipStream_t stream);
 bool small_diagonal(const FillArgs& A, uint32_t n_units);
 uint32_t most_units(const FillArgs& A);            // that one launch takes
 void launch_fill_diagonals(const FillArgs& A, const DevParams& h, const void* list, const DiagRun& run, hipStream_t stream);

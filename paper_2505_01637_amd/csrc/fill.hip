@@ -33,6 +33,7 @@
 // 668 -> 464, batched layouts 1061 -> 783, packed layouts 3058 -> 2424, the
 // pipeline 3728 -> 3049.
 #include <string.h>
+#include <algorithm>
 #include <hip/hip_runtime.h>
 #include "compress.h"
 #include "dev_params.h"
@@ -319,7 +320,7 @@ __global__ __launch_bounds__(1024) void scan_units_kernel(const uint32_t* __rest
   }
   uint32_t at = incl - n;
   if (lane < n_diag) host_diag[lane] = at;
-  if (lane == n_diag - 1) host_diag[n_diag] = incl;
+  if (lane == n_diag - 1) host_diag[n_diag] = seg[n_seg] = incl;
   for (uint32_t l = 0; l < n_levels; l++)
     if (lane >= l && lane - l < n_ranks) { seg[l * n_ranks + lane - l] = at; at += tot[l * n_ranks + lane - l]; }
 }
@@ -337,7 +338,8 @@ constexpr uint32_t kListItems = 512;
 __global__ __launch_bounds__(256) void list_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_shapes, const uint32_t* __restrict__ level_off,
                                                          const uint32_t* __restrict__ blk_off, uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs,
                                                          const unsigned long long* __restrict__ masks, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ seg,
-                                                         uint2* __restrict__ list, uint32_t w0, uint32_t w_len, uint32_t n_items) {
+                                                         uint2* __restrict__ list, uint32_t w0, uint32_t w_len, uint32_t n_items, uint32_t none_from) {
+  if (seg[n_levels * P->nranks] >= none_from) return;
   __shared__ uint32_t ends[kMaxLevels], waves[4], before[kListItems + 1], item_of[kListItems], to_of[kListItems / kBlockItems];
   __shared__ unsigned long long word_of[4][kListItems];
   __shared__ uint8_t parts_of[kListItems], packs[kMaxCombo];
@@ -1248,6 +1250,232 @@ __global__ __launch_bounds__(kChainThreads) void fill_chain_kernel(const FillArg
   flush_counters(A.ctr, n_rw, ovf);
 }
 
+// ---------------------------------------------------------------- a dependency level of shapes at once
+// A diagonal takes a twelfth or so of a shape's entries, which lie all over its group: where most of them fit, every line of the group,
+// and of the groups that its tiles lead to, is read again for almost every rank.  Large tables of which much fits, and whose groups are small (no layouts, or a
+// Matmul's), are bound by that (all sizes to 64, everything fits: 49 M lines missed in the L2s, the fill 1.83 ms).  So here a workgroup takes whole groups, a launch
+// a dependency level of shapes: first a lane per cell takes the tiles, one line after the other, with the list of tiles in scalar registers; then the Moves, inside the
+// group, which stays in LDS, rank by rank: a few lanes per item, which no other wave touches, so that no barrier is needed between two
+// ranks.  8.6 M lines missed, 0.75 ms of kernels (the bundles of items that the diagonals replaced: 1.29); bound by instruction issue, the ranks' the larger part.
+// The rule is at by_shapes_from.
+constexpr uint32_t kLgShapeCells = 10, kShapeCells = 1u << kLgShapeCells;       // of a workgroup, a quarter of them a wave's
+constexpr uint32_t kShapeBatch = 8;          // tiles whose costs are fetched together
+constexpr uint64_t kShapeUnits = 1u << 20;   // a table of fewer is never taken this way
+constexpr uint32_t kNotHere = 1u << 16;      // id of a cell that does not fit
+struct RankOff { uint16_t at[kMaxRanks + 2]; };                                  // DevParams::rank_off
+
+// A group has 1 << lg_cells places (a wave's 64 cells are of one shape), an item 1 << lg_lanes lanes.
+template <bool LAY, bool SMALL, bool PAR, bool MN>
+__global__ __launch_bounds__(256) void fill_shapes_kernel(const FillArgs A, const RankOff ranks, const ShapeRec* __restrict__ all_recs, const TileStep* __restrict__ steps,
+                                                          const unsigned long long* __restrict__ masks, uint32_t first, uint32_t n_shapes, uint32_t lg_cells, uint32_t lg_lanes) {
+  constexpr uint32_t kChanges = LAY ? 2u : 1u;
+  __shared__ uint32_t coef[128];                                  // DevParams::mcoef
+  __shared__ uint64_t costs[kShapeCells];
+  // of the Moves, [shape][operand][source level][layout kept, changed][destination]: 2^63 where there is none; in the place of destination 3:
+  // how many there are (64 cells and more to a shape, with layouts 128: by_shapes_from)
+  __shared__ uint64_t prices[kShapeCells / 4][4];
+  __shared__ uint32_t ids[kShapeCells];
+  __shared__ unsigned long long rank_masks[kMaxRanks][4];
+  __shared__ uint8_t order[kMaxCombo], packs[kMaxCombo];          // level assignments rank by rank; their levels, in table order
+  const DevParams* __restrict__ P = A.P;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t nranks = A.nranks, npass = A.npass, nops = A.nops, NL = A.NL, G = A.G, log2V = A.log2V, V = 1u << log2V, ndt = A.ndt, nwp = A.nwp, nw = nwp << ndt;
+  const uint32_t lg_shapes = kLgShapeCells - lg_cells, s0 = blockIdx.x << lg_shapes;          // the workgroup's first shape of the level
+  const ShapeRec* __restrict__ recs = all_recs + first + s0;
+  const uint32_t info = P->combo_info[tid];
+  const uint32_t my_coef = reinterpret_cast<const uint32_t*>(P->mcoef)[tid & 127u];
+  // which of the wave's cells fit
+  uint32_t here = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < 4; j++) {
+    const uint32_t x = wave * 256u + j * 64u, slot = x >> lg_cells, cell = (x & ((1u << lg_cells) - 1u)) + lane;
+    if (s0 + slot < n_shapes && cell < G) {
+      const uint32_t c = cell >> log2V, combo = c / npass, pass = c - combo * npass, dt = cell & ((1u << ndt) - 1u);
+      here |= (uint32_t)(masks[((size_t)recs[slot].shape * npass + pass) * nw + dt * nwp + (combo >> 6)] >> (combo & 63u) & 1ull) << j;
+    }
+  }
+  {
+    const uint32_t pack = info & 0xFFu, rank = tid < P->ncombo ? (uint32_t)__popc(pack & 0x55u) + 2u * (uint32_t)__popc(pack & 0xAAu) : ~0u;
+    uint32_t at = 0;
+    for (uint32_t r = 0; r < nranks; r++) {
+      const unsigned long long m = __ballot(rank == r);
+      if (lane == 0) rank_masks[r][wave] = m;
+      at = rank == r ? ranks.at[r] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : at;
+    }
+    packs[tid] = (uint8_t)pack;
+    if (tid < 128) coef[tid] = my_coef;
+    __syncthreads();
+    if (rank != ~0u) {
+      for (uint32_t w = 0; w < wave; w++) at += (uint32_t)__popcll(rank_masks[rank][w]);
+      order[at] = (uint8_t)tid;
+    }
+  }
+  for (uint32_t i = tid; i < (64u * kChanges) << lg_shapes; i += 256u) {
+    const uint32_t row = i >> 2, dst = i & 3u, xx = LAY ? row & 1u : 0u, src = row / kChanges & 3u, op = row / kChanges >> 2 & 3u, slot = row / kChanges >> 4;
+    const uint32_t k = coef[((op * 4u + src) * 4u + dst) * 2u + xx];
+    uint64_t p = k;
+    if (dst < 3) {
+      const uint64_t numel = s0 + slot < n_shapes ? recs[slot].numel[op] : 0;
+      p = !k ? 1ull << 63 : SMALL ? (uint64_t)k * (uint32_t)numel : mul_or_limit(k, numel);
+    }
+    prices[row][dst] = p;
+  }
+  uint32_t n_rw = 0, ovf = 0, over = 0, over2 = 0;
+  // ---- tiles, microkernels, bufferize: a lane per cell, 64 cells of one shape at a time
+#pragma unroll 1
+  for (uint32_t j = 0; j < 4; j++) {
+    const uint32_t x = wave * 256u + j * 64u, slot = x >> lg_cells, cell = (x & ((1u << lg_cells) - 1u)) + lane;
+    Best e{kInf, kNotHere | kNone};
+    if ((here >> j) & 1u) {
+      const ShapeRec& R = recs[slot];
+      const uint32_t cnts = R.tile_cnt, mk_var = R.mk_var, at = R.shape * G + cell;
+      e.id = kNone;
+      // the lists of the dimensions one after the other, those of the parallel loops (b, m, n) behind them
+      const uint32_t c0 = MN ? 0u : cnts & 0xFFu, c1 = (cnts >> 8) & 0xFFu, c2 = MN ? 0u : (cnts >> 16) & 0xFFu, c3 = cnts >> 24;
+      const uint32_t b1 = c0, b2 = c0 + c1, b3 = b2 + c2, n_serial = b3 + c3, n_all = PAR ? n_serial + b2 + c3 : n_serial;
+      const uint32_t o0 = R.tile_lo[0], o1 = R.tile_lo[1] - b1, o2 = R.tile_lo[2] - b2, o3 = R.tile_lo[3] - b3;
+      for (uint32_t t0 = 0; t0 < n_all; t0 += kShapeBatch) {
+        TileStep st[kShapeBatch];
+        uint64_t sub[kShapeBatch];
+#pragma unroll
+        for (uint32_t u = 0; u < kShapeBatch; u++) {
+          uint32_t t = t0 + u < n_all ? t0 + u : n_all - 1u;
+          const bool loop = PAR && t >= n_serial;
+          if (loop) t -= n_serial;
+          uint32_t o = o3;
+          if (!MN) { o = t < b3 ? o2 : o; o = t < b2 ? o1 : o; o = t < b1 ? o0 : o; }
+          else o = t < b3 ? o1 : o;
+          if (loop) { o = o3 + c2; o = t < b2 ? o1 : o; o = t < b1 ? o0 : o; }
+          st[u] = steps[o + t];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kShapeBatch; u++) {
+          const uint64_t* table = A.cost;
+          if (PAR && t0 + u >= n_serial) table = A.costM;
+          sub[u] = at_cell<SMALL>(table, at - st[u].delta);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kShapeBatch; u++) {
+          const bool loop = PAR && t0 + u >= n_serial, fin = t0 + u < n_all && (uint32_t)(sub[u] >> 32) != ~0u;
+          const uint32_t a = fin ? (loop ? st[u].rounds : st[u].trips) : 0u;
+          const uint64_t lo64 = (uint64_t)a * (uint32_t)sub[u] + (loop ? A.sync : A.s);     // (32 x 32 bits + 32 bits: no wrap)
+          const uint64_t hi = (uint64_t)a * (uint32_t)(sub[u] >> 32) + (lo64 >> 32);        // bits 32.. of the sum
+          over |= (uint32_t)hi;
+          over2 |= (uint32_t)(hi >> 32);
+          e.take((hi << 32) | (uint32_t)lo64, st[u].id + (loop ? A.par_shift : 0u), fin);
+        }
+      }
+      n_rw += R.n_tile;
+      if ((mk_var & 0xFFu) | (MN ? A.has_buf : 0u)) {
+        const uint32_t v = cell & (V - 1u), c = cell >> log2V, combo = c / npass, pass = c - combo * npass, pack = packs[combo];
+        Eval f;
+        f.best = e.cost; f.arg = e.id; f.ovf = 0;
+        if (mk_var & 0xFFu) {
+          for (uint32_t mm = A.mk_entry[(pack << log2V) + v] & mk_var & 0xFFu; mm; mm &= mm - 1) {
+            const uint32_t m = (uint32_t)__ffs((int)mm) - 1u;
+            Shape H;
+#pragma unroll
+            for (int d = 0; d < 4; d++) H.d[d] = P->sizes[d][(R.si >> (8 * d)) & 0xFFu];
+            const uint64_t ck = mul_or_limit(P->mk_cost[m], mk_shape_reps(P, H, m));
+            if (ck >= kLimit) f.ovf = 1; else consider(f, ck, m);
+            n_rw++;
+          }
+        }
+        if (MN && A.has_buf) {
+          const uint64_t numel[5] = {R.numel[0], R.numel[1], R.numel[2], R.numel[3], R.numel[4]};
+          n_rw += task_bufferize(A, R.si, numel, pack, pass, v, f);
+        }
+        e.cost = f.best; e.id = f.arg;
+        ovf |= f.ovf;
+      }
+    }
+    costs[x + lane] = e.cost;
+    ids[x + lane] = e.id;
+  }
+  __syncthreads();
+  // ---- Moves, rank by rank: a few lanes of a wave per item (shape and level of the intermediate), which read and write its cells only
+  const uint32_t lg_items = 6u - lg_lanes, items = npass << lg_shapes, per_wave = (items + 3u) / 4u, end = (wave + 1u) * per_wave < items ? (wave + 1u) * per_wave : items;
+  for (uint32_t i0 = wave * per_wave; i0 < end; i0 += 1u << lg_items) {
+    const uint32_t i = i0 + (lane >> lg_lanes), slot = i / npass, pass = i - slot * npass;
+    const bool have = i < end && s0 + slot < n_shapes;
+    for (uint32_t r = 1; r < nranks; r++) {
+      const uint32_t off = ranks.at[r], n = (ranks.at[r + 1] - off) << log2V;
+      for (uint32_t e0 = lane & ((1u << lg_lanes) - 1u); __any(e0 < n); e0 += 1u << lg_lanes) {
+        if (have && e0 < n) {
+          const uint32_t combo = order[off + (e0 >> log2V)], v = e0 & (V - 1u), pack = packs[combo];
+          const uint32_t x = (slot << lg_cells) + (((combo * npass + pass) << log2V) | v);
+          const uint32_t tile_id = ids[x];
+          if (tile_id < kNotHere) {
+            Best e{kNoCost, kNone};
+            int32_t high = 0;
+#pragma unroll
+            for (uint32_t op = 0; op < 4; op++) {
+              if (op >= nops) break;
+              const uint32_t src = (pack >> A.pack_shift[op]) & 3u, to = x - __umul24(src, A.mstride[op]), lay = LAY ? A.lay_xor[op] : 0u;
+              const uint64_t* price = prices[((slot * 4u + op) * 4u + src) * kChanges];
+              // what is not finite reads as 2^63 - 1, a Move that does not exist costs 2^63: with either bit 63 is set, or the cost is kNoCost and more
+              const auto add = [&](uint64_t t, uint64_t p, uint32_t id) {
+                const uint64_t cand = (t & kNoCost) + p;
+                high = (int32_t)(cand >> 32) > high ? (int32_t)(cand >> 32) : high;
+                e.take(cand, id, true);
+              };
+#pragma unroll
+              for (uint32_t dst = 0; dst < 3; dst++) {
+                if (dst >= NL - 1u) break;
+                const uint32_t from = to + dst * A.mstride[op], id = A.move_base + op * (NL - 1u) * 4u + dst * 4u;
+                add(costs[from], price[dst], id);
+                if (lay) add(costs[from ^ lay], price[4 + dst], id + 2u);
+              }
+              n_rw += (uint32_t)price[3];
+            }
+            over |= high >= 1 << 30 ? 1u << 30 : 0u;
+            Eval f;
+            f.best = costs[x]; f.arg = tile_id; f.ovf = 0;
+            consider(f, e.cost, e.id, e.id != kNone);
+            if (ndt) {
+              // to the type without the dtype bit; what does not fit there is (INF, NONE)
+#pragma unroll
+              for (uint32_t op = 0; op < 2; op++) {
+                const uint32_t src = (pack >> A.pack_shift[op]) & 3u, cv_bit = A.cv_bit[op];
+                if (!(v & cv_bit)) continue;
+                n_rw += (uint32_t)prices[((slot * 4u + op) * 4u + src) * kChanges][3];
+                for (uint32_t dst = 0; dst < src; dst++)
+                  for (uint32_t xx = 0; xx < (LAY && A.lay_xor[op] ? 2u : 1u); xx++) {
+                    const uint64_t t = costs[((x - __umul24(src - dst, A.mstride[op])) ^ (xx ? A.lay_xor[op] : 0u)) & ~cv_bit];
+                    const uint32_t k = coef[((op * 4u + src) * 4u + dst) * 2u + xx];
+                    const uint64_t numel = recs[slot].numel[op];
+                    const bool fin = (uint32_t)(t >> 32) != ~0u && k != 0;
+                    const uint64_t cand = t + (SMALL ? (uint64_t)(k + A.convert) * (uint32_t)numel : mul_or_limit((uint64_t)k + A.convert, numel));     // each at most 2^62 when finite: no wrap
+                    over |= fin ? (uint32_t)(cand >> 32) : 0u;
+                    consider(f, cand, A.move_base + op * (NL - 1u) * 4u + dst * 4u + xx * 2u + 1u, fin);
+                  }
+              }
+            }
+            costs[x] = f.best;
+            ids[x] = f.arg;
+          }
+        }
+      }
+      // (the next rank reads what other lanes of this wave wrote: a wave's LDS operations are done in their order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  if (lg_cells > 8) __syncthreads();        // (else a wave has taken the items of its own cells)
+  // ---- whole lines to the table
+#pragma unroll
+  for (uint32_t j = 0; j < 4; j++) {
+    const uint32_t x = wave * 256u + j * 64u, slot = x >> lg_cells, cell = (x & ((1u << lg_cells) - 1u)) + lane;
+    if (s0 + slot < n_shapes && cell < G) {
+      const size_t at = (size_t)recs[slot].shape * G + cell;
+      A.cost[at] = costs[x + lane];
+      A.arg[at] = (uint16_t)ids[x + lane];
+    }
+  }
+  ovf |= (over >> 30) | over2;
+  flush_counters(A.ctr, n_rw, ovf);
+}
+
 // What an alloc-binding costs beside its body (Section 2, Memory Movement; Section 3): m(src) +
 // m(dest) in cache lines, the load Move Spec and, for the accumulated output, the store Move Spec,
 // both of fresh tensors.  It depends on the operand's size, the two levels, the two layouts and the
@@ -1943,12 +2171,12 @@ void launch_fit_map(const DevParams* P, uint32_t n_specs, const PlanBuffers& B, 
   hipLaunchKernelGGL(fit_map_kernel, dim3((n_words + 2 + 255) / 256), dim3(256), 0, stream, P, n_specs, B.masks, (unsigned long long*)fitmap, n_words);
 }
 
-void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, hipStream_t stream) {
+void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, uint64_t none_from, hipStream_t stream) {
   const uint64_t items = (uint64_t)n_blk * kBlockItems;
   uint32_t each = h.ncombo > 64 ? kListItems / 4 : kListItems;      // (enough workgroups, of a few hundred units)
   while (each > 64 && items / each * h.nranks < 2048) each /= 2;
   hipLaunchKernelGGL(list_units_kernel, dim3((uint32_t)((items + each - 1) / each), h.nranks), dim3(256), 0, stream, P, B.level_shapes, B.level_off, B.blk_off, n_levels, n_blk,
-                     (const ShapeRec*)B.recs, B.masks, B.cnt, B.seg, (uint2*)B.list, w0, w_len, each);
+                     (const ShapeRec*)B.recs, B.masks, B.cnt, B.seg, (uint2*)B.list, w0, w_len, each, (uint32_t)std::min<uint64_t>(none_from, UINT32_MAX));
 }
 
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream) {
@@ -1960,7 +2188,7 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
   memset(&A, 0, sizeof A);
   A.P = d_P; A.recs = B.recs; A.steps = h.steps; A.cost = cost; A.arg = arg; A.ctr = ctr;
   A.costM = h.costM; A.costE = h.costE; A.mk_entry = h.mk_entry;
-  A.nops = h.nops; A.NL = h.NL; A.G = h.G; A.log2V = h.log2V; A.ndt = h.ndt;
+  A.nranks = h.nranks; A.npass = h.npass; A.nwp = h.nwp; A.nops = h.nops; A.NL = h.NL; A.G = h.G; A.log2V = h.log2V; A.ndt = h.ndt;
   for (uint32_t i = 0; i < 4; i++) {
     A.mstride[i] = h.mstride[i]; A.pack_shift[i] = h.pack_shift[i]; A.lay_bit[i] = h.lay_bit[i];
     A.lay_xor[i] = i < h.nops && h.lay_bit[i] != kNoBit ? 1u << h.lay_bit[i] : 0u;
@@ -1996,6 +2224,42 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
     if (!PAR && !MOVES && !A.ndt && A.unit_lay >= 2) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
     else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, PAR, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
   }
+}
+
+// From how many units on the levels of shapes are filled at once (fill_shapes_kernel) instead of by diagonals.  A launch of a level
+// takes some 25 us, through tiles and ranks, a small diagonal 6; in return a unit is 75 ps shorter (parallel loops: 85 to 330, since a
+// lane takes their entries one by one), for the groups of a shape and of its tiles are read once, not once for each rank.  And a unit that is
+// not there is a lane that idles.  Everything fits, by diagonals and by levels: a Matmul of all sizes to 36 (3.0 M units) 733 and 747 us, to 40
+// (4.1 M) 834 and 785, to 64 2466 and 1447; with parallel loops and three layouts, sizes to 24 (0.9 M) 1512 and 1419, to 32 2982 and 2479;
+// two Matmuls composed of sizes to 7 (2.5 M) 766 and 657.  17 % of the level assignments fit: all sizes to 64 1038 and 1303; 36 %: 1316 and 1346,
+// 42 %: 1426 and 1361; two Matmuls 48 %: 3022 and 2442; fused 32 %: 2223 and 2059, 16 %: 2477 and 2729.
+// (Move Specs' prices are a table of their own, and fused Specs with layouts have more cells than a workgroup takes.)
+uint64_t by_shapes_from(const DevParams& h, uint32_t n_shapes, uint32_t n_levels) {
+  if (h.moves || (h.nlay && h.kind != kKindM) || h.G > kShapeCells || h.G <= (h.nlay ? 64u : 32u)) return UINT64_MAX;
+  const uint64_t level_assignments = ((uint64_t)n_shapes * h.npass * h.ncombo) << h.ndt;
+  const uint64_t levels_us = (h.kind == kKindM ? 26 : 22) * n_levels, diagonals_us = 6 * (n_levels + h.nranks - 1), unit_ps = !h.par ? 75 : h.nlay < 2 ? 85 : h.nlay == 2 ? 200 : 330;
+  const uint64_t worth = levels_us > diagonals_us ? (levels_us - diagonals_us) * 1000000 / unit_ps : 0;
+  return std::max({kShapeUnits, worth, level_assignments * 3 / 10});
+}
+void launch_fill_shapes(const FillArgs& A, const DevParams& h, const unsigned long long* masks, uint32_t first, uint32_t n, hipStream_t stream) {
+  uint32_t lg_cells = 0, lg_lanes = 0, most = 0;
+  while ((1u << lg_cells) < h.G) lg_cells++;
+  for (uint32_t r = 0; r < h.nranks; r++) most = std::max(most, (h.rank_off[r + 1] - h.rank_off[r]) << h.log2V);
+  while (lg_lanes < 6 && (1u << lg_lanes) < most) lg_lanes++;
+  const uint32_t each = kShapeCells >> lg_cells;
+  RankOff ranks;
+  for (uint32_t r = 0; r < kMaxRanks + 2; r++) ranks.at[r] = (uint16_t)h.rank_off[r];
+  const dim3 grid((n + each - 1) / each);
+#define MRL_SHAPES(lay, par, mn) do { \
+    if (h.small) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_shapes_kernel<lay, true, par, mn>), grid, dim3(256), 0, stream, A, ranks, (const ShapeRec*)A.recs, A.steps, masks, first, n, lg_cells, lg_lanes); \
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_shapes_kernel<lay, false, par, mn>), grid, dim3(256), 0, stream, A, ranks, (const ShapeRec*)A.recs, A.steps, masks, first, n, lg_cells, lg_lanes); \
+  } while (0)
+  if (h.par && h.nlay) MRL_SHAPES(true, true, false);
+  else if (h.par) MRL_SHAPES(false, true, false);
+  else if (h.kind != kKindM) MRL_SHAPES(false, false, true);
+  else if (h.nlay) MRL_SHAPES(true, false, false);
+  else MRL_SHAPES(false, false, false);
+#undef MRL_SHAPES
 }
 
 bool small_diagonal(const FillArgs& A, uint32_t n) { return (uint64_t)n << (A.unit_lay + A.lg_split) <= kChainThreads; }

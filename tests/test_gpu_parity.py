@@ -437,6 +437,73 @@ def test_parity_diagonals(case):
     compare_config(cfg, boxes=case in ("three-layouts", "parallel"))
 
 
+@pytest.mark.parametrize("case", ["none", "none-dear", "batched", "half", "dtypes", "dtypes-dear", "three-levels-dtypes", "layouts", "layouts-dear", "layouts-and-a-dtype",
+                                  "parallel", "parallel-dear", "parallel-layouts", "parallel-dtypes", "fused", "fused-dear", "fused-three-levels", "composition", "split"])
+def test_parity_levels_of_shapes(case):
+    """Tables of which much fits, of more level assignments than are filled by diagonals: groups of 64 to 1024 cells, whole and not a power of two,
+    numbers of shapes that are no multiple of a workgroup's, few and many tiles, cells that do not fit beside cells that do."""
+    kind, dear = case.split("-")[0], case.endswith("dear")
+    cfg = W.config({"dtypes": 3, "parallel": 6, "fused": 5, "composition": 10, "split": 11}.get(kind, 4), max_size=6)
+    t = cfg["target"]
+    t["convert_coef"] = 3
+    t["capacity_bytes"] = [2048, 4096, 1 << 14, W.UNBOUNDED] if kind == "half" else [W.UNBOUNDED] * 4
+    if "three-levels" in case:
+        t["n_levels"], t["capacity_bytes"] = 3, [8000, 100000, W.UNBOUNDED, 0]
+    if dear:
+        for src in range(1, 4):
+            for dst in range(src):
+                for x in range(2):
+                    t["load_coef"][src][dst][x] += (1 << 30) + src
+                    t["store_coef"][dst][src][x] += (1 << 30) + dst
+    r = [1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 13, 14, 15, 17, 19, 21, 22, 23, 25, 26, 29, 31, 33, 34, 35, 37, 38,
+         39, 41, 43, 46, 47, 49, 51, 53, 55, 57, 58, 59, 61, 62]          # chains of three divisors at most
+    n_sizes = {"dtypes": 18, "three": 26, "composition": 6, "fused": 17 if "three" in case else 12, "batched": 20, "half": 41}.get(kind, 27)
+    if case in ("layouts-and-a-dtype", "parallel-dtypes"):
+        n_sizes = 22
+    for label, lat, _ in cfg["lattices"]:
+        lat["layout_coord"] = [0] * 5
+        lat["sizes"] = [[1]] + [r[:n_sizes]] * 3 if lat["kind"] != W.KIND_BIAS_ADD_RELU else [[1], r[:n_sizes], [1], r[:n_sizes]]
+        if kind == "batched":
+            lat["sizes"][0] = [1, 2, 3]
+        elif kind == "composition" and label == "G":
+            lat["sizes"][0] = r[:n_sizes]
+        elif "layouts" in case:
+            lat["layout_coord"] = [0, 1, 1, 0, 0] if kind == "parallel" else [1, 1, 1, 0, 0]
+        if "dtype" in case:
+            lat["dtype_coord"] = [0, 1, 0, 0, 0] if case in ("layouts-and-a-dtype", "parallel-dtypes") else [1, 1, 0, 0, 0]
+            lat["base_dtype_bytes"] = [2, 4, 4, 4, 4]
+    if kind == "split":
+        m = list(range(1, 256))
+        cfg["lattices"] = [(label, dict(lat, sizes=[[1], m, [1], m]), deps) for label, lat, deps in cfg["lattices"] if label in "ARS"]
+    _, got, _ = compare_config(cfg, boxes=case in ("none", "half", "three-levels-dtypes", "fused", "parallel"))
+    # the table is one that is filled this way: enough level assignments, and three tenths of all there are
+    label, lat, _ = cfg["lattices"][-1]
+    stats, nops = got[label].stats, W.n_operands(lat["kind"])
+    units, levels, matmul = stats.n_admissible >> sum(lat["layout_coord"]), stats.n_levels_run, lat["kind"] in (W.KIND_MATMUL_ACCUM, W.KIND_MATMUL_PARALLEL)
+    longer = (26 if matmul else 22) * levels - 6 * (levels + nops * (t["n_levels"] - 1))
+    assert units >= max(1 << 20, longer * 1_000_000 // 75) and 10 * units >= 3 * (stats.n_specs >> sum(lat["layout_coord"]))
+    assert case != "half" or units < 0.7 * stats.n_specs
+
+
+@pytest.mark.parametrize("cost,rc", [(1 << 60, -6), (1 << 40, 0)])
+def test_cost_at_the_limit_in_levels_of_shapes(cost, rc):
+    """A loop's cost that passes 2^62 is reported, and one that does not is none."""
+    B = _binding()
+    cfg = W.config(2)
+    t, lat = cfg["target"], cfg["lattices"][0][1]
+    t["capacity_bytes"] = [W.UNBOUNDED] * 4
+    t["microkernels"] = [(W.MK_SCALAR_FMA, 1, cost)]
+    lat["sizes"] = [[1], [1, 2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31], [1] + [q for q in range(2, 200) if all(q % d for d in range(2, q))], list(range(1, 47))]
+    want = O.solve_config(cfg)["M"]
+    assert want["rc"] == rc and W.n_specs(t, lat) >= (26 * 8 - 6 * 17) * 1_000_000 // 75        # (8 levels, 17 diagonals)
+    if rc:
+        with pytest.raises(B.MorelloError) as e:
+            B.solve_config(cfg)
+        assert e.value.code == B.E_OVERFLOW
+    else:
+        compare_config(cfg, boxes=False)
+
+
 def test_work_list_in_windows():
     """Everything fits and few boxes: the scratch that the table uses holds a part of the list of its entries at a time."""
     B = _binding()

@@ -139,26 +139,53 @@ print("done")
 
 LIMIT = HEAD + r"""
 # diagonals around the most that one launch's threads can take: eight lanes per entry and eight entries per unit, or four and one
-layouts, most = {"layouts": ([1, 1, 1, 0, 0], (1 << 26) - 4), "no-layouts": ([0] * 5, (1 << 30) - 64)}[sys.argv[3]]
+# (few memory levels, so that a shape has too few cells for its levels to be filled at once; the places in the list are 32 bits)
+layouts, most, levels, diagonals = {"layouts": ([1, 1, 1, 0, 0], (1 << 26) - 4, 2, 4), "no-layouts": ([0] * 5, (1 << 30) - 64, 1, 1)}[sys.argv[3]]
 cfg = W.config(6, max_size=1)
+cfg["target"].update(n_levels=levels, microkernels=[])
 for _, lat, _ in cfg["lattices"]:
     lat["layout_coord"] = layouts
-if layouts[0] == 0:
-    cfg["target"].update(n_levels=1, microkernels=[])                 # (one diagonal: the places in the list are 32 bits)
 target, (serial, parallel) = B.Target(cfg["target"]), [lat for _, lat, _ in cfg["lattices"]]
 table = solve(target, serial)
-diagonals = 10 if layouts[0] else 1
 room = buffer(1 << 20)                            # (nothing is launched: the list's places are never written)
 for units, pieces in ((most, 1), (most + 1, 2), (most + 100, 2)):
     hip.fake_units(units)
-    for part in (b"fill_split", b"fill_chain"):
+    for part in (b"fill_split", b"fill_chain", b"fill_entry"):
         hip.fake_launches_of(part)
     h, stats = C.c_void_p(), B.Stats()
     B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(parallel)), (C.c_void_p * 1)(table._h), C.c_uint32(1), buffer(1 << 20), buffer(1 << 20), room,
                                C.c_size_t(1 << 40), None, C.byref(h), C.byref(stats)))
-    launches = hip.fake_launches_of(b"fill_split") + hip.fake_launches_of(b"fill_chain")       # (a chain: a rest of few entries)
+    launches = sum(hip.fake_launches_of(part) for part in (b"fill_split", b"fill_chain", b"fill_entry"))       # (a chain: a rest of few entries)
     assert launches == diagonals * pieces, (units, pieces, launches)
     assert stats.n_admissible == units * diagonals << (3 if layouts[0] else 0)
+print("done")
+"""
+
+LEVELS = HEAD + r"""
+# a Matmul of all sizes to 24 (13 levels, 10 ranks): its levels of shapes are filled at once from a number of level assignments on
+cfg = W.config(4, max_size=1)
+lat = cfg["lattices"][0][1]
+name = sys.argv[3]
+r = list(range(1, 25))
+lat.update(sizes=[[1], r, r, r], layout_coord={"none": [0] * 5, "layouts": [1, 1, 1, 0, 0]}.get(name, [0] * 5))
+if name == "few-levels":
+    cfg["target"]["n_levels"] = 2
+if name == "sparse":
+    lat["sizes"] = [[1], list(range(1, 97)), list(range(1, 97)), list(range(1, 97))]
+target = B.Target(cfg["target"])
+levels = 19 if name == "sparse" else 13
+diagonals = levels + (4 if name == "few-levels" else 10) - 1
+# what launches take longer, at 75 ps a level assignment; 2^20; and three tenths of all level assignments
+line = {"none": max(1 << 20, (26 * 13 - 6 * 22) * 1000000 // 75), "layouts": (26 * 13 - 6 * 22) * 1000000 // 75, "sparse": 96 ** 3 * 64 * 3 // 10, "few-levels": 1 << 40}[name]
+for units, at_once in ((line // diagonals, False), (-(-line // diagonals) if line < 1 << 32 else 1 << 22, line < 1 << 32)):
+    hip.fake_units(units)
+    for part in (b"fill_shapes", b"fill_split", b"fill_quad", b"fill_entry"):
+        hip.fake_launches_of(part)
+    h, stats = C.c_void_p(), B.Stats()
+    units < 1 << 26 and B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(lat)), None, C.c_uint32(0), buffer(1 << 20), buffer(1 << 20), buffer(1 << 28),
+                               C.c_size_t(1 << 40), None, C.byref(h), C.byref(stats)))
+    others = sum(hip.fake_launches_of(part) for part in (b"fill_split", b"fill_quad", b"fill_entry"))
+    assert (hip.fake_launches_of(b"fill_shapes"), others) == ((levels, 0) if at_once else (0, diagonals if units < 1 << 26 else 0)), (units, at_once, others)
 print("done")
 """
 
@@ -205,3 +232,9 @@ def test_chains_hold_diagonals_of_one_round(tmp_path):
 def test_diagonals_of_more_entries_than_a_launch_has_threads_for(case, tmp_path):
     """A launch has fewer than 2^32 threads; a diagonal of the largest tables asks for more, and goes in pieces."""
     run_on_fake_hip(tmp_path, LIMIT, case)
+
+
+@pytest.mark.parametrize("case", ["none", "layouts", "sparse", "few-levels"])
+def test_tables_of_which_much_fits_are_filled_by_levels_of_shapes(case, tmp_path):
+    """From as many level assignments as pay for a launch a level, if three tenths of all are there, and if a shape has cells enough."""
+    run_on_fake_hip(tmp_path, LEVELS, case)
