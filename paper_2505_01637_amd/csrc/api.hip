@@ -228,7 +228,7 @@ FixedLayout fixed_layout(const Compiled& c, bool may_turn = true) {
     f.unit_seg = take(((size_t)n_lev * c.P.nranks + 1) * 4);
     if (c.P.moves) f.bind = take(bind_entries(c) * 8);
     // the work list takes what is left of the buffer; where that is less than the whole list, it goes through in windows
-    f.list = take(std::max<size_t>(n_items / 2, 64) * 8);
+    f.list = take(std::max<size_t>(n_items, 64) * 8);
   }
   f.fill_end = o;
   o = shared;
@@ -1312,7 +1312,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     }
   } else {
   // plan; then the host reads the diagonals' sizes back
-  const uint32_t n_blk = unit_blocks(c.level_off.data(), n_lev, P.npass, nullptr), n_diag = n_lev + P.nranks - 1;
+  uint32_t blk_off[kMaxLevels + 1];
+  const uint32_t n_blk = unit_blocks(c.level_off.data(), n_lev, P.npass, blk_off), n_diag = n_lev + P.nranks - 1;
   const uint64_t list_room = (scratch_bytes - f.list) / 8;
   const uint32_t window = (uint32_t)std::min<uint64_t>(list_room, UINT32_MAX);
   // The pre-fill, (INF, NONE) over both tables, and the fit map run beside the plan and the fill on the helper stream, where they take
@@ -1337,7 +1338,7 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
   HIP_TRY(hipEventRecord(aux->events[ev_used], st));
   hipEvent_t counts_ready = aux->events[ev_used++];
   const uint64_t shapes_from = by_shapes_from(P, c.n_shapes, n_lev);
-  launch_list_units(d_P, P, n_lev, n_blk, plan, 0, window, shapes_from, st);
+  launch_list_units(d_P, P, n_lev, blk_off, plan, 0, window, 0, n_diag - 1, shapes_from, st);
   if (prefilled) HIP_TRY(hipStreamWaitEvent(st, prefilled, 0)); else launch_prefill(tab->d_cost, tab->d_arg, c.n_specs, st);
   HIP_TRY(hipEventRecord(ev[4], st));
   prefill_timed = true;
@@ -1377,7 +1378,10 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
       if (u - w0 >= window) {
         flush();
         w0 = u;
-        launch_list_units(d_P, P, n_lev, n_blk, plan, w0, std::min(window, diag[n_diag] - w0), UINT64_MAX, st);
+        const uint32_t w_len = std::min(window, diag[n_diag] - w0);
+        uint32_t last = d;
+        while (diag[last + 1] - w0 < w_len) last++;
+        launch_list_units(d_P, P, n_lev, blk_off, plan, w0, w_len, d, last, UINT64_MAX, st);
       }
       const uint32_t n = std::min({diag[d + 1] - u, window - (u - w0), most});
       const bool small = small_diagonal(fill, n);

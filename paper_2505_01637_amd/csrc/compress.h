@@ -54,8 +54,10 @@ bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off,
 void launch_plan(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, Counters* ctr, hipStream_t stream);
 // Behind the plan: which cells fit, in table order, n_words words and two of zeros.
 void launch_fit_map(const DevParams* P, uint32_t n_specs, const PlanBuffers& B, uint32_t* fitmap, uint32_t n_words, hipStream_t stream);
-// Units [w0, w0 + w_len) of the work list to its place.
-void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, uint64_t none_from, hipStream_t stream);
+// Units [w0, w0 + w_len) of the work list, which lie on diagonals d0 to d1, to its place; none if there are none_from units and more.
+// h_blk_off: the host's copy of the first block of every level.
+void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, const uint32_t* h_blk_off, const PlanBuffers& B, uint32_t w0, uint32_t w_len, uint32_t d0, uint32_t d1,
+                       uint64_t none_from, hipStream_t stream);
 // The costs of the alloc-bindings of a Matmul whose Moves are Move Specs, from its Move table.
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream);
 // What the kernels of the diagonals read of the parameters, by value: they are short, and every read of the

@@ -14,6 +14,7 @@ constexpr uint64_t kLimit = 1ull << 62;      // finite costs stay below this
 constexpr int kMaxSizes = 256;
 constexpr int kMaxCombo = 256;               // n_levels ^ n_operands
 constexpr int kMaxRanks = 16;
+constexpr uint32_t kMaxLevels = 64;          // (b*m*k*n < 2^48: at most 49 dependency levels, 61 diagonals: a lane of a wave each)
 constexpr uint32_t kNoBit = 0xFF;            // "this operand has no such coordinate"
 
 enum : uint32_t { kKindM = 0, kKindE = 1, kKindF = 2, kKindV = 3,     // V: Move Specs (two tensors: source, destination)

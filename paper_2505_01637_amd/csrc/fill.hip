@@ -148,7 +148,6 @@ static_assert(sizeof(ShapeRec) == 80, "read as five 16-byte pieces");
 // shape; a lane per item takes 9 per level assignment for 64 items): all sizes to 64 (262,144 shapes) 124 us and the list 61, now
 // 31 and 46, the solve 1190 -> 1106.
 constexpr uint32_t kBlockItems = 8;
-constexpr uint32_t kMaxLevels = 64;          // (b*m*k*n < 2^48: at most 49 dependency levels, 61 diagonals: a lane of a wave each)
 
 // Level of block b: my_end = first block behind level `lane`.
 __device__ __forceinline__ uint32_t level_of_block(uint32_t my_end, uint32_t b) { return (uint32_t)__popcll(__ballot(my_end <= b)); }
@@ -335,11 +334,26 @@ constexpr uint32_t kUnitFit = 18;
 // other, as many as they are: 94 us for all sizes to 64, 335 for the pipeline; a lane per unit that searches the
 // blocks' places in memory: 110 and 56.)
 constexpr uint32_t kListItems = 512;
+struct ListFirst { uint32_t block[kMaxRanks]; };       // first block that has units of the rank in the window
 __global__ __launch_bounds__(256) void list_units_kernel(const DevParams* __restrict__ P, const uint32_t* __restrict__ level_shapes, const uint32_t* __restrict__ level_off,
                                                          const uint32_t* __restrict__ blk_off, uint32_t n_levels, uint32_t n_blk, const ShapeRec* __restrict__ recs,
                                                          const unsigned long long* __restrict__ masks, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ seg,
-                                                         uint2* __restrict__ list, uint32_t w0, uint32_t w_len, uint32_t n_items, uint32_t none_from) {
-  if (seg[n_levels * P->nranks] >= none_from) return;
+                                                         uint2* __restrict__ list, uint32_t w0, uint32_t w_len, uint32_t n_items, uint32_t none_from, const ListFirst firsts) {
+  const uint32_t n_units = seg[n_levels * P->nranks], b0 = firsts.block[blockIdx.y] + blockIdx.x * (n_items / kBlockItems);
+  if (n_units >= none_from || b0 >= n_blk) return;
+  if (n_units > w_len) {
+    // a part of the list: nothing of these blocks may lie in it
+    const uint32_t b1 = b0 + n_items / kBlockItems < n_blk ? b0 + n_items / kBlockItems : n_blk, r = blockIdx.y, n_ranks = P->nranks;
+    uint32_t lev = 0;
+    while (blk_off[lev + 1] <= b0) lev++;
+    if (b1 <= blk_off[lev + 1]) {         // (of one level)
+      const uint32_t start = seg[lev * n_ranks + r], from = start + cnt[(size_t)r * n_blk + b0];
+      uint32_t to = ~0u;                  // behind a level's last block: the next level's units of the rank below, if it is not the diagonal's end
+      if (b1 < blk_off[lev + 1]) to = start + cnt[(size_t)r * n_blk + b1];
+      else if (lev + 1 < n_levels && r) to = seg[(lev + 1) * n_ranks + r - 1];
+      if (to <= w0 || (from >= w0 && from - w0 >= w_len)) return;
+    }
+  }
   __shared__ uint32_t ends[kMaxLevels], waves[4], before[kListItems + 1], item_of[kListItems], to_of[kListItems / kBlockItems];
   __shared__ unsigned long long word_of[4][kListItems];
   __shared__ uint8_t parts_of[kListItems], packs[kMaxCombo];
@@ -353,7 +367,7 @@ __global__ __launch_bounds__(256) void list_units_kernel(const DevParams* __rest
   __syncthreads();
   uint32_t n2[2] = {0, 0};
   {
-    const uint32_t b = blockIdx.x * (n_items / kBlockItems) + tid * 2u / kBlockItems;
+    const uint32_t b = b0 + tid * 2u / kBlockItems;
     if (b < n_blk && tid * 2u < n_items) {
       uint32_t lev = 0;
 #pragma unroll
@@ -2171,12 +2185,24 @@ void launch_fit_map(const DevParams* P, uint32_t n_specs, const PlanBuffers& B, 
   hipLaunchKernelGGL(fit_map_kernel, dim3((n_words + 2 + 255) / 256), dim3(256), 0, stream, P, n_specs, B.masks, (unsigned long long*)fitmap, n_words);
 }
 
-void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, uint32_t n_blk, const PlanBuffers& B, uint32_t w0, uint32_t w_len, uint64_t none_from, hipStream_t stream) {
+void launch_list_units(const DevParams* P, const DevParams& h, uint32_t n_levels, const uint32_t* h_blk_off, const PlanBuffers& B, uint32_t w0, uint32_t w_len, uint32_t d0, uint32_t d1,
+                       uint64_t none_from, hipStream_t stream) {
+  const uint32_t n_blk = h_blk_off[n_levels];
   const uint64_t items = (uint64_t)n_blk * kBlockItems;
   uint32_t each = h.ncombo > 64 ? kListItems / 4 : kListItems;      // (enough workgroups, of a few hundred units)
   while (each > 64 && items / each * h.nranks < 2048) each /= 2;
-  hipLaunchKernelGGL(list_units_kernel, dim3((uint32_t)((items + each - 1) / each), h.nranks), dim3(256), 0, stream, P, B.level_shapes, B.level_off, B.blk_off, n_levels, n_blk,
-                     (const ShapeRec*)B.recs, B.masks, B.cnt, B.seg, (uint2*)B.list, w0, w_len, each, (uint32_t)std::min<uint64_t>(none_from, UINT32_MAX));
+  // the levels that have units of a rank on diagonals d0 to d1
+  ListFirst firsts;
+  uint32_t most = 0;
+  for (uint32_t r = 0; r < kMaxRanks; r++) {
+    const uint32_t l0 = d0 > r ? d0 - r : 0, l1 = d1 < r ? 0 : std::min(d1 - r + 1, n_levels);
+    firsts.block[r] = n_blk;
+    if (r >= h.nranks || l0 >= l1) continue;
+    firsts.block[r] = h_blk_off[l0];
+    most = std::max(most, h_blk_off[l1] - h_blk_off[l0]);
+  }
+  hipLaunchKernelGGL(list_units_kernel, dim3((uint32_t)(((uint64_t)most * kBlockItems + each - 1) / each), h.nranks), dim3(256), 0, stream, P, B.level_shapes, B.level_off, B.blk_off, n_levels, n_blk,
+                     (const ShapeRec*)B.recs, B.masks, B.cnt, B.seg, (uint2*)B.list, w0, w_len, each, (uint32_t)std::min<uint64_t>(none_from, UINT32_MAX), firsts);
 }
 
 void launch_bind(const DevParams* P, uint64_t* bind, uint32_t n, hipStream_t stream) {

@@ -14,7 +14,7 @@ enum { kDevices = 2, kInvalidValue = 1, kInvalidConfiguration = 9, kInvalidDevic
 static __thread int current;
 static __thread struct { dim3 grid, block; size_t shared; void* stream; } config;
 static int launched[kDevices];
-static struct { const void* f; char name[120]; int launched; } kernels[256];
+static struct { const void* f; char name[120]; int launched; uint64_t blocks; } kernels[256];
 static int n_kernels;
 static uint32_t row_total;          /* what row_total_kernel finds */
 static uint32_t units;              /* of every diagonal, as scan_units_kernel finds them */
@@ -33,6 +33,12 @@ int fake_launches(int device) { return __atomic_load_n(&launched[device], __ATOM
 int fake_launches_of(const char* part) {
   int n = 0;
   for (int i = 0; i < n_kernels; i++) if (strstr(kernels[i].name, part)) n += __atomic_exchange_n(&kernels[i].launched, 0, __ATOMIC_SEQ_CST);
+  return n;
+}
+/* and their workgroups */
+uint64_t fake_blocks_of(const char* part) {
+  uint64_t n = 0;
+  for (int i = 0; i < n_kernels; i++) if (strstr(kernels[i].name, part)) n += __atomic_exchange_n(&kernels[i].blocks, 0, __ATOMIC_SEQ_CST);
   return n;
 }
 void fake_row_total(uint32_t n) { row_total = n; }
@@ -74,6 +80,7 @@ int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t sh
   for (int i = 0; i < n_kernels; i++) {
     if (kernels[i].f != f) continue;
     __atomic_add_fetch(&kernels[i].launched, 1, __ATOMIC_SEQ_CST);
+    __atomic_add_fetch(&kernels[i].blocks, (uint64_t)grid.x * grid.y * grid.z, __ATOMIC_SEQ_CST);
     if (strstr(kernels[i].name, "row_total_kernel")) **(uint32_t**)args[2] = row_total;
     if (strstr(kernels[i].name, "scan_units_kernel")) {
       const uint32_t diagonals = *(uint32_t*)args[1] + *(uint32_t*)args[2] - 1;

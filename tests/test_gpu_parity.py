@@ -522,6 +522,39 @@ def test_work_list_in_windows():
     assert [tab.boxes(w).tobytes() for w in (0, 1)] == [got["M"].boxes(w).tobytes() for w in (0, 1)]
 
 
+@pytest.mark.parametrize("case", ["dtypes", "fused", "composition", "parallel"])
+def test_work_list_in_windows_of_other_kinds(case):
+    """The list in windows that end between the planes of the dtype bits, inside masks of four words and between levels of the
+    intermediate, and of loops that read another table.  (With layouts, or the boxes of Move Specs, the scratch that is used holds the whole list.)"""
+    B = _binding()
+    cfg = W.config({"dtypes": 3, "fused": 5, "composition": 10, "parallel": 6}[case], max_size=14)
+    t = cfg["target"]
+    t["capacity_bytes"], t["loop_overhead"], t["sync_cost"], t["threads"], t["zero_coef"] = [W.UNBOUNDED] * 4, 0, 0, 1, [0] * 4
+    t["load_coef"] = W._empty_target(4, [0] * 4)["load_coef"]
+    t["store_coef"] = W._empty_target(4, [0] * 4)["store_coef"]
+    t["load_coef"][1][0], t["load_coef"][2][1], t["store_coef"][0][1] = [3, 3], [1, 1], [3, 3]
+    t["microkernels"] = [(kind, lanes, 1) for kind, lanes, _ in t["microkernels"]]
+    r = [1, 2, 3, 4, 5, 6, 8, 10, 12, 14]
+    for _, lat, _ in cfg["lattices"]:
+        lat["layout_coord"] = [0] * 5
+        if case == "dtypes":
+            lat["sizes"] = [[1], r, r, r]
+        elif case == "composition":
+            lat["sizes"] = [q if len(q) == 1 else [1, 2, 3, 4, 6] for q in lat["sizes"]]
+        elif case == "fused":
+            lat["sizes"] = [q if len(q) == 1 else r[:6] for q in lat["sizes"]]
+    target, got, want = compare_config(cfg, scratch_bytes=256 << 20)
+    label, lat, deps = cfg["lattices"][-1]
+    used, deps = int(got[label].stats.scratch_used), [got[d] for d in deps]
+    print("list", 8 * got[label].stats.n_admissible, "scratch", used, flush=True)
+    assert 8 * got[label].stats.n_admissible > used         # (a place in the list takes 8 bytes)
+    tab = B.solve(target, lat, deps=deps, scratch_bytes=used)
+    cost, arg = tab.dense()
+    assert np.array_equal(cost, want[label]["cost"]) and np.array_equal(arg, want[label]["argmin"])
+    assert tab.stats.n_rewrites == want[label]["n_rewrites"] and tab.stats.scratch_used == used
+    assert [tab.boxes(w).tobytes() for w in (0, 1)] == [got[label].boxes(w).tobytes() for w in (0, 1)]
+
+
 @pytest.mark.parametrize("case", ["fused-29-tiles", "fused-layouts-42-tiles", "fused-wide-items-76-tiles", "split-42-tiles", "composition-31-tiles"])
 def test_parity_bufferize_beside_many_tiles(case):
     """More tile rewrites than a workgroup holds at a time (24 per item of a bundle, 64 of a wide

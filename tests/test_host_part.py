@@ -189,6 +189,29 @@ for units, at_once in ((line // diagonals, False), (-(-line // diagonals) if lin
 print("done")
 """
 
+WINDOWS = HEAD + r"""
+# all sizes to 40, 64 level assignments a shape: 4 million units in 27 diagonals, of which the least scratch holds a part at a time
+hip.fake_blocks_of.restype = C.c_uint64
+cfg = W.config(2, max_size=40)
+target, lat = B.Target(cfg["target"]), cfg["lattices"][0][1]
+least = least_scratch(target, lat)
+hip.fake_units(100000)
+
+def listed(scratch_bytes):
+    for part in (b"list_units", b"fill_split"):
+        hip.fake_launches_of(part)
+    hip.fake_blocks_of(b"list_units")
+    solve(target, lat, scratch_bytes)
+    return hip.fake_launches_of(b"list_units"), hip.fake_blocks_of(b"list_units"), hip.fake_launches_of(b"fill_split")
+
+once, blocks, pieces = listed(64 << 20)
+assert (once, pieces) == (1, 25) and blocks > 1000
+windows, more, parts = listed(least)
+assert windows > 3 and parts >= 25
+assert more < windows * blocks / 4, (windows, blocks, more)          # a window's levels and ranks, not all of them again
+print("done")
+"""
+
 
 def run_on_fake_hip(tmp_path, program, *args):
     gcc = shutil.which("gcc")
@@ -238,3 +261,8 @@ def test_diagonals_of_more_entries_than_a_launch_has_threads_for(case, tmp_path)
 def test_tables_of_which_much_fits_are_filled_by_levels_of_shapes(case, tmp_path):
     """From as many level assignments as pay for a launch a level, if three tenths of all are there, and if a shape has cells enough."""
     run_on_fake_hip(tmp_path, LEVELS, case)
+
+
+def test_a_window_of_the_work_list_is_made_from_its_own_levels(tmp_path):
+    """Where the scratch holds a part of the list at a time, a part is made from the shapes that have units in it."""
+    run_on_fake_hip(tmp_path, WINDOWS)
