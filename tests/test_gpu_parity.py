@@ -402,12 +402,11 @@ def test_parity_bundles_of_items(case):
     compare_config(cfg)
 
 
-@pytest.mark.parametrize("case", ["three-layouts", "three-layouts-dear", "batched-three-layouts", "one-layout", "one-layout-dear", "dtypes", "no-layouts", "parallel",
-                                  "parallel-three-layouts", "parallel-three-layouts-dear", "fused-two-layouts"])
+@pytest.mark.parametrize("case", ["three-layouts", "three-layouts-dear", "batched-three-layouts", "one-layout", "one-layout-dear", "dtypes", "no-layouts", "parallel", "fused-two-layouts"])
 def test_parity_diagonals(case):
-    """Diagonals (dependency level + rank) of one entry, of up to 32,768, which are split (with parallel loops up to 262,144), and of more,
-    which are taken four entries or one at a time; Move prices that fit 32 bits and (dear) that do not."""
-    cfg = W.config(3 if case == "dtypes" else 6 if case.startswith("parallel") else 5 if case.startswith("fused") else 4, max_size=6)
+    """Diagonals (dependency level + rank) of one entry, of up to 32,768, which are split, and of more, which are taken four
+    entries or one at a time; Move prices that fit 32 bits and (dear) that do not."""
+    cfg = W.config(3 if case == "dtypes" else 6 if case == "parallel" else 5 if case.startswith("fused") else 4, max_size=6)
     t = cfg["target"]
     t["capacity_bytes"] = [W.UNBOUNDED] * 4
     if case.endswith("dear"):
@@ -424,10 +423,6 @@ def test_parity_diagonals(case):
             lat["layout_coord"] = [0, 1, 0, 0, 0]
         elif case == "no-layouts":
             lat["layout_coord"] = [0] * 5
-        elif case.startswith("parallel-"):
-            lat["layout_coord"] = [1, 1, 1, 0, 0]
-            q = sorted(r + [18, 20, 30, 36])
-            lat["sizes"] = [[1], q, q, q + [48, 60, 72, 96]]
         elif case.startswith("batched"):
             lat["sizes"] = [[1, 2, 3, 6], [1, 2, 3, 6, 12], [1, 5, 10, 20], [1, 2, 4, 8, 16]]
     if case == "fused-two-layouts":
@@ -435,6 +430,75 @@ def test_parity_diagonals(case):
             lat["layout_coord"] = list(lay)
             lat["sizes"][2] = lat["sizes"][2] if len(lat["sizes"][2]) == 1 else [1, 3]
     compare_config(cfg, boxes=case in ("three-layouts", "parallel"))
+
+
+@pytest.mark.parametrize("case", ["no-layouts", "parallel", "parallel-two-layouts", "parallel-three-layouts", "fused", "fused-one-layout", "fused-no-layouts", "fused-no-layouts-primes",
+                                  "composition", "split", "moves", "packed"])
+@pytest.mark.parametrize("dear", [False, True])
+def test_parity_diagonals_of_other_kinds(case, dear):
+    """Diagonals of few and of many entries in the forms of the other kinds, with prices that fit 32 bits and (dear) that do not: of Moves, or,
+    where these are Specs of their own, of the conversion.  Split, four layouts at a time and one lane each, with parallel loops (split up to
+    262,144 entries), a bufferize, Moves priced by a table."""
+    kind = case.split("-")[0]
+    cfg = W.config({"no": 2, "parallel": 6, "fused": 5, "composition": 10, "split": 11, "moves": 9, "packed": 12}[kind], max_size=6)
+    t = cfg["target"]
+    t["capacity_bytes"] = [W.UNBOUNDED] * 4
+    if dear:
+        t["convert_coef"] = (1 << 30) + 1
+        for src in range(1, 4):
+            for dst in range(src):
+                for x in range(2):
+                    t["load_coef"][src][dst][x] += (1 << 30) + src
+                    t["store_coef"][dst][src][x] += (1 << 30) + dst
+    r = [1, 2, 3, 4, 5, 6, 8, 10, 12, 15, 16, 18, 20, 24, 30, 36]
+    sizes = {"no": [[1], r[:12], r[:12], r], "parallel": [[1], r, r, r + [48, 60, 72, 96]], "fused": [[1], r[:11], [1, 3], r[:11]], "composition": [[1, 2, 4, 8]] * 4,
+             "split": [[1], list(range(1, 41)), [1], list(range(1, 41))], "moves": [[1], r[:9], r[:9], r[:9]], "packed": [[1], r[:9], r[:9], r[:9]]}[kind]
+    for label, lat, _ in cfg["lattices"]:
+        lat["sizes"] = [[1] if len(old) == 1 and d != 2 else new for d, (old, new) in enumerate(zip(lat["sizes"], sizes))]
+        if lat["kind"] in (W.KIND_BIAS_ADD, W.KIND_RELU, W.KIND_BIAS_ADD_RELU, W.KIND_BIAS_ADD_RELU_SPLIT, W.KIND_MOVE):
+            lat["sizes"][2] = [1]
+        if kind == "parallel":
+            lat["layout_coord"] = {"parallel": [0] * 5, "parallel-two-layouts": [1, 0, 1, 0, 0], "parallel-three-layouts": [1, 1, 1, 0, 0]}[case]
+        elif case.startswith("fused-no-layouts"):
+            lat["layout_coord"] = [0] * 5
+            if case.endswith("primes"):           # diagonals of 131,072 entries and more, and too few of all for levels of shapes
+                q = [1] + [q for q in range(2, 200) if all(q % d for d in range(2, q))]
+                lat["sizes"] = [[1], q, [1], q]
+                t["capacity_bytes"] = [4096, 1 << 14, 1 << 16, W.UNBOUNDED]
+        elif case == "fused-one-layout":
+            lat["layout_coord"] = [0, 1, 0, 0, 0] if label != "E" else [0] * 5
+        elif kind in ("moves", "packed") and label == "V":
+            lat["dtype_coord"] = [1, 1, 0, 0, 0]
+        elif kind in ("moves", "packed"):
+            lat["layout_coord"], lat["dtype_coord"] = ([1, 1, 1, 0, 0], [1, 0, 0, 0, 0]) if kind == "moves" else ([0, 2, 1, 0, 0], [0, 1, 0, 0, 0])
+    if kind == "split":
+        cfg["lattices"] = [x for x in cfg["lattices"] if x[0] in "ARS"]
+    compare_config(cfg, boxes=False)
+
+
+@pytest.mark.parametrize("case,tiles", [(case, n + d) for case, n in (("split", 32), ("split-no-layouts", 16), ("four-layouts", 8), ("lane-each", 8), ("fused-split", 32),
+                                                                   ("fused-split-no-layouts", 16), ("fused-four-layouts", 8), ("fused-lane-each", 8)) for d in (-1, 0, 1)])
+def test_parity_tiles_around_what_is_fetched_together(case, tiles):
+    """Shapes of one tile less, as many and one more than are fetched together: four by each of eight or four lanes, two by each of four, eight by
+    a lane.  Loops are free, so that candidates of either batch and the bufferize, whose id is higher, cost the same: the lowest id is the answer."""
+    fused, split = case.startswith("fused"), "split" in case
+    lay = 0 if case.endswith("no-layouts") else 1
+    primes = [q for q in range(2, 200) if all(q % d for d in range(2, q))]
+    b, m, k = ([1], [1], [1]) if split else ([1], [1] + primes[:45], [1] if fused else [1] + primes[:12])
+    if case == "fused-lane-each":
+        k = [1, 2, 3, 5]
+    elif case == "lane-each":
+        b = [1, 2, 3, 5]
+    tiled = sum(len(q) > 1 for q in ((m,) if fused else (b, m, k)))          # (a tile each of a prime)
+    n = [d for d in range(1, 5041) if 5040 % d == 0][:tiles - tiled] + [5040]
+    cfg = W.config(5, seed=1, max_size=1)
+    cfg["target"].update(loop_overhead=0, capacity_bytes=[W.UNBOUNDED] * 4)
+    rest = 0 if case.endswith("lane-each") else lay          # (one layout bit: no four layouts to take at a time)
+    lats = [("M", W._lattice(W.KIND_MATMUL_ACCUM, [b, m, k, n], layout=(rest, lay, rest, 0, 0)), []),
+            ("E", W._lattice(W.KIND_BIAS_ADD_RELU, [[1], m, [1], n], layout=(rest, 0, rest, 0, 0)), []),
+            ("F", W._lattice(W.KIND_FUSED_MM_ADD_RELU, [[1], m, k, n], layout=(rest, lay, 0, rest, 0)), ["M", "E"])]
+    cfg["lattices"] = lats if fused else lats[:1]
+    compare_config(cfg, boxes=False)
 
 
 @pytest.mark.parametrize("case", ["none", "none-dear", "batched", "half", "dtypes", "dtypes-dear", "three-levels-dtypes", "layouts", "layouts-dear", "layouts-and-a-dtype",

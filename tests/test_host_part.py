@@ -24,22 +24,13 @@ def buffer(n):
     assert hip.hipMalloc(C.byref(p), C.c_size_t(n)) == 0
     return p
 
-def solve(target, lat, scratch_bytes=None, stream=None, deps=()):
+def solve(target, lat, scratch_bytes=None, stream=None):
     cost, arg, most = B.table_bytes(target, lat)
     scratch_bytes = most if scratch_bytes is None else scratch_bytes
     h, stats = C.c_void_p(), B.Stats()
-    handles = (C.c_void_p * max(1, len(deps)))(*[d._h for d in deps])
-    B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(lat)), handles if deps else None, C.c_uint32(len(deps)), buffer(cost), buffer(arg),
-                               buffer(scratch_bytes), C.c_size_t(scratch_bytes), stream, C.byref(h), C.byref(stats)))
-    return B.Table(h, target, lat, B.geometry(target, lat)[0], None, stats, deps)
-
-def least_scratch(target, lat, deps=()):
-    try:
-        solve(target, lat, 256, deps=deps)
-    except B.MorelloError as e:
-        assert e.code == B.E_NOMEM
-        return int(re.search(r"at least (\d+)", str(e)).group(1))
-    assert False
+    B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(lat)), None, C.c_uint32(0), buffer(cost), buffer(arg), buffer(scratch_bytes),
+                               C.c_size_t(scratch_bytes), stream, C.byref(h), C.byref(stats)))
+    return B.Table(h, target, lat, B.geometry(target, lat)[0], None, stats)
 """
 
 ASK = HEAD + r"""
@@ -87,7 +78,12 @@ def launched(scratch_bytes=None):
 
 total, rows, boxes = launched()
 assert total == 0 and rows > 5 and boxes == 0, "plenty of scratch: by words, nothing asked before"
-least = least_scratch(target, lat)
+try:
+    solve(target, lat, 256)
+    assert False
+except B.MorelloError as e:
+    assert e.code == B.E_NOMEM
+    least = int(re.search(r"at least (\d+)", str(e)).group(1))
 hip.fake_row_total(many)
 total, rows, boxes = launched(least + 4096)
 assert rows == 0 and boxes > 0 and total == (1 if many > few else 0), "the words cannot fit: no kernel of that merge"
@@ -98,7 +94,28 @@ if many > few:
 print("done")
 """
 
-SCRATCH = HEAD + r"""
+
+# (tables that read others, and the least scratch of a lattice)
+MORE = HEAD + r"""
+def solve(target, lat, scratch_bytes=None, deps=()):
+    cost, arg, most = B.table_bytes(target, lat)
+    scratch_bytes = most if scratch_bytes is None else scratch_bytes
+    h, stats = C.c_void_p(), B.Stats()
+    handles = (C.c_void_p * max(1, len(deps)))(*[d._h for d in deps])
+    B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(lat)), handles if deps else None, C.c_uint32(len(deps)), buffer(cost), buffer(arg),
+                               buffer(scratch_bytes), C.c_size_t(scratch_bytes), None, C.byref(h), C.byref(stats)))
+    return B.Table(h, target, lat, B.geometry(target, lat)[0], None, stats, deps)
+
+def least_scratch(target, lat, deps=()):
+    try:
+        solve(target, lat, 256, deps=deps)
+    except B.MorelloError as e:
+        assert e.code == B.E_NOMEM
+        return int(re.search(r"at least (\d+)", str(e)).group(1))
+    assert False
+"""
+
+SCRATCH = MORE + r"""
 # (configuration, largest size, table): what mrl_table_bytes asked for, and the least that a solve took
 enough = {(1, 16, "M"): (5966080, 457216), (2, None, "M"): (3041477888, 29908736), (3, 8, "M"): (1563904, 88832),
           (3, None, "M"): (16899584, 307712), (4, 8, "M"): (24762112, 1164544), (4, None, "M"): (4322228480, 54018304),
@@ -119,7 +136,7 @@ for (number, most, want), (asked, least) in enough.items():
 print("done")
 """
 
-FORMS = HEAD + r"""
+FORMS = MORE + r"""
 # every diagonal of a Matmul whose Moves are Move Specs, without layouts, has 128 or 129 entries; a chain's workgroup of 1024 lanes takes
 # eight of them an entry
 cfg = W.config(9, max_size=2)
@@ -137,7 +154,7 @@ for units, chained in ((128, True), (129, False)):
 print("done")
 """
 
-LIMIT = HEAD + r"""
+LIMIT = MORE + r"""
 # diagonals around the most that one launch's threads can take: eight lanes per entry and eight entries per unit, or four and one
 # (few memory levels, so that a shape has too few cells for its levels to be filled at once; the places in the list are 32 bits)
 layouts, most, levels, diagonals = {"layouts": ([1, 1, 1, 0, 0], (1 << 26) - 4, 2, 4), "no-layouts": ([0] * 5, (1 << 30) - 64, 1, 1)}[sys.argv[3]]
@@ -161,7 +178,7 @@ for units, pieces in ((most, 1), (most + 1, 2), (most + 100, 2)):
 print("done")
 """
 
-LEVELS = HEAD + r"""
+LEVELS = MORE + r"""
 # a Matmul of all sizes to 24 (13 levels, 10 ranks): its levels of shapes are filled at once from a number of level assignments on
 cfg = W.config(4, max_size=1)
 lat = cfg["lattices"][0][1]
@@ -189,7 +206,7 @@ for units, at_once in ((line // diagonals, False), (-(-line // diagonals) if lin
 print("done")
 """
 
-WINDOWS = HEAD + r"""
+WINDOWS = MORE + r"""
 # all sizes to 40, 64 level assignments a shape: 4 million units in 27 diagonals, of which the least scratch holds a part at a time
 hip.fake_blocks_of.restype = C.c_uint64
 cfg = W.config(2, max_size=40)
