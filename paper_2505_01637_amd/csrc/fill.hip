@@ -889,7 +889,7 @@ __device__ __forceinline__ Quad quad_at(const uint64_t* table, uint32_t cell) {
 // shared by four lanes (all of them active): lane s takes the Moves of operand s and tiles s, s + 4, ....  What does not
 // depend on the layout is worked out once for the four entries: the tiles and their places, the Moves and their prices;
 // and an entry that a Move reads for one of the four with the layout kept serves another with it changed.
-template <bool SMALL, bool MN>
+template <bool SMALL, bool PAR, bool MN>
 __device__ __forceinline__ void fill_quad(const FillArgs& A, const uint2 un, uint32_t c, uint32_t s, bool active, const uint4* coef, const OpTab* tab, uint32_t& n_rw, uint32_t& ovf) {
   constexpr uint32_t kMine = 2;                       // tiles at a time
   const char* rec = (const char*)A.recs + (size_t)un.x * 80u;
@@ -906,7 +906,7 @@ __device__ __forceinline__ void fill_quad(const FillArgs& A, const uint2 un, uin
   uint64_t* const cost = A.cost;
   const OpTab my = tab[s];
   const uint32_t src = s < nops ? (pack >> my.shift) & 3u : 0u;
-  TileShare<MN, false, 4, kMine> tiles(r3, r4, cnts, active, 0u);
+  TileShare<MN, PAR, 4, kMine> tiles(r3, r4, cnts, active, r3.y);
   tiles.fetch(A.steps, s);
 
   Best e[4];
@@ -950,25 +950,31 @@ __device__ __forceinline__ void fill_quad(const FillArgs& A, const uint2 un, uin
       }
   }
 
-  // tiles: the same entries of a smaller shape
+  // tiles: the same entries of a smaller shape; a parallel loop's body: entries of the serial table
   for (uint32_t t0 = s; __any(t0 < tiles.n); t0 += kMine * 4u) {
     if (t0 != s) tiles.fetch(A.steps, t0);
     Quad sub[kMine];
 #pragma unroll
     for (uint32_t u = 0; u < kMine; u++)
-      if (t0 + u * 4u < tiles.n) sub[u] = quad_at<SMALL>(cost, cell - tiles.st[u].x);
+      if (t0 + u * 4u < tiles.n) {
+        const uint64_t* table = cost;
+        if (PAR && t0 + u * 4u >= tiles.n_serial) table = A.costM;
+        sub[u] = quad_at<SMALL>(table, cell - tiles.st[u].x);
+      }
 #pragma unroll
     for (uint32_t u = 0; u < kMine; u++)
       if (t0 + u * 4u < tiles.n) {
+        const bool loop = PAR && t0 + u * 4u >= tiles.n_serial;
+        const uint32_t trips = loop ? tiles.st[u].w : tiles.st[u].y, more = loop ? A.sync : A.s, id = tiles.st[u].z + (loop ? A.par_shift : 0u);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           const uint64_t t = sub[u].t[r];
           const bool fin = (uint32_t)(t >> 32) != ~0u;
-          const uint32_t a = fin ? tiles.st[u].y : 0u;
-          const uint64_t lo = (uint64_t)a * (uint32_t)t + A.s;                          // (32 x 32 bits + 32 bits: no wrap)
+          const uint32_t a = fin ? trips : 0u;
+          const uint64_t lo = (uint64_t)a * (uint32_t)t + more;                         // (32 x 32 bits + 32 bits: no wrap)
           const uint64_t hi = (uint64_t)a * (uint32_t)(t >> 32) + (lo >> 32);           // bits 32.. of the sum
           over2 |= (uint32_t)hi >> 30 | (uint32_t)(hi >> 32);
-          e[r].take((hi << 32) | (uint32_t)lo, tiles.st[u].z, fin);
+          e[r].take((hi << 32) | (uint32_t)lo, id, fin);
         }
       }
   }
@@ -1214,7 +1220,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
 }
 
 // Four lanes per four entries (the lattice has two layout bits and more, and no dtype bits).
-template <bool SMALL, bool MN>
+template <bool SMALL, bool PAR, bool MN>
 __global__ __launch_bounds__(256) void fill_quad_kernel(const FillArgs A, const uint2* __restrict__ units, uint32_t n_units) {
   __shared__ uint4 coef[32];
   __shared__ OpTab tab[4];
@@ -1223,7 +1229,7 @@ __global__ __launch_bounds__(256) void fill_quad_kernel(const FillArgs A, const 
   const uint2 un = units[u < n_units ? u : 0u];
   load_tabs(A, coef, tab);
   uint32_t n_rw = 0, ovf = 0;
-  fill_quad<SMALL, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 4u), (uint32_t)t & 3u, u < n_units, coef, tab, n_rw, ovf);
+  fill_quad<SMALL, PAR, MN>(A, un, (uint32_t)t & ((1u << A.unit_lay) - 4u), (uint32_t)t & 3u, u < n_units, coef, tab, n_rw, ovf);
   flush_counters(A.ctr, n_rw, ovf);
 }
 
@@ -2234,9 +2240,8 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
 // others issue fewer instructions per entry (diagonals of 20 blocks of a lane per entry 20 us, split 5; of 1.6 M entries, four
 // at a time, 33, a lane each 61, split more).  The line at 16,384, 32,768 or 65,536 entries: within 1 % of each other; none split: the
 // vector-matrix product 485 -> 594 us, the pipeline 3082 -> 3109; all split: 3912, two Matmuls 2001 -> 3196, packed layouts 2397 -> 2922.
-// Without layouts (four lanes) a split is never behind: all sizes to 64, 668 against 740 us of fill.  With parallel loops the line lies higher
-// (three layouts, sizes to 24 and to 48, everything fits: split only 1676 and 10856 us, the line at 32,768 entries 1493 and 9855, at 262,144
-// 1481 and 9847, at 524,288 1529 and 9875; as much as fits the four-level target: 1073 and 3079, 1017 and 2890, 1029 and 2862, 1080 and 2910).
+// Without layouts (four lanes) a split is never behind: all sizes to 64, 668 against 740 us of fill.  With parallel loops, three layouts,
+// sizes to 24 and 40 of which much fits: four at a time from 32,768 entries 802 and 1560 us, from 262,144 819 and 1583 (a lane each instead of four at a time, from 262,144: 998 and 1966).
 template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
 static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run, hipStream_t stream) {
   const uint32_t n = run.start[1] - run.start[0];
@@ -2244,11 +2249,15 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
   const uint2* units = list + run.start[0];
   const auto blocks = [](uint64_t lanes) { return dim3((uint32_t)((lanes + 255) / 256)); };
   if (run.chain) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_chain_kernel<LAY, MOVES, SMALL, PAR, MN>), dim3(1), dim3(kChainThreads), 0, stream, A, list, run);
-  else if (!LAY || tasks <= (PAR ? kParSplitTasks : kSplitTasks))
+  else if (!LAY || tasks <= kSplitTasks)
     hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_split_kernel<LAY, MOVES, SMALL, PAR, MN>), blocks(tasks << A.lg_split), dim3(256), 0, stream, A, units, n);
   else if constexpr (LAY) {
-    if (!PAR && !MOVES && !A.ndt && A.unit_lay >= 2) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, PAR, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
+    if constexpr (!MOVES)
+      if (!A.ndt && A.unit_lay >= 2) {
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, PAR, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
+        return;
+      }
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_entry_kernel<MOVES, SMALL, PAR, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
   }
 }
 

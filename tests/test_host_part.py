@@ -167,12 +167,12 @@ table = solve(target, serial)
 room = buffer(1 << 20)                            # (nothing is launched: the list's places are never written)
 for units, pieces in ((most, 1), (most + 1, 2), (most + 100, 2)):
     hip.fake_units(units)
-    for part in (b"fill_split", b"fill_chain", b"fill_entry"):
+    for part in (b"fill_split", b"fill_chain", b"fill_quad"):
         hip.fake_launches_of(part)
     h, stats = C.c_void_p(), B.Stats()
     B._check(B.lib().mrl_solve(target._h, C.byref(B._lattice_desc(parallel)), (C.c_void_p * 1)(table._h), C.c_uint32(1), buffer(1 << 20), buffer(1 << 20), room,
                                C.c_size_t(1 << 40), None, C.byref(h), C.byref(stats)))
-    launches = sum(hip.fake_launches_of(part) for part in (b"fill_split", b"fill_chain", b"fill_entry"))       # (a chain: a rest of few entries)
+    launches = sum(hip.fake_launches_of(part) for part in (b"fill_split", b"fill_chain", b"fill_quad"))       # (a chain: a rest of few entries)
     assert launches == diagonals * pieces, (units, pieces, launches)
     assert stats.n_admissible == units * diagonals << (3 if layouts[0] else 0)
 print("done")
