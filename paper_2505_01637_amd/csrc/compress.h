@@ -82,7 +82,7 @@ struct FillArgs {
 FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& B, uint64_t* cost, uint16_t* arg, Counters* ctr);
 // Diagonals that one launch takes: n of them, diagonal i at places [start[i], start[i + 1]) of the list.  Small ones
 // (small_diagonal) go into a chain, any other is a launch of its own.
-constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768;
+constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768, kBareSplitTasks = 131072;
 struct DiagRun { uint32_t n, chain, start[kRunMost + 1]; };
 uint64_t by_shapes_from(const DevParams& h, uint32_t n_shapes, uint32_t n_levels);      // units
 void launch_fill_shapes(const FillArgs& A, const DevParams& h, const unsigned long long* masks, uint32_t first, uint32_t n, hipStream_t stream);

@@ -472,6 +472,20 @@ __global__ __launch_bounds__(256) void fit_map_kernel(const DevParams* __restric
       map[i] = out;
       return;
     }
+    if (npass == 4 && !log2V) {                // four levels of the intermediate: 16 level assignments of one shape (256 to a shape), whose bits lie four apart
+      const unsigned long long* mp = masks + (size_t)shape * 4u * nw + (off >> 8);
+#pragma unroll
+      for (uint32_t p = 0; p < 4; p++) {
+        unsigned long long x = mp[p * nw] >> ((off >> 2) & 63u) & 0xFFFFull;
+        x = (x | x << 24) & 0x000000FF000000FFull;
+        x = (x | x << 12) & 0x000F000F000F000Full;
+        x = (x | x << 6) & 0x0303030303030303ull;
+        x = (x | x << 3) & 0x1111111111111111ull;
+        out |= x << p;
+      }
+      map[i] = out;
+      return;
+    }
     uint32_t seen = ~0u;
     uint32_t combo = (off >> log2V) / npass, pass = (off >> log2V) - combo * npass;
     unsigned long long lays = 1;               // bit v: variant v (dtype bits 0) has layouts that exist
@@ -2240,8 +2254,10 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
 // others issue fewer instructions per entry (diagonals of 20 blocks of a lane per entry 20 us, split 5; of 1.6 M entries, four
 // at a time, 33, a lane each 61, split more).  The line at 16,384, 32,768 or 65,536 entries: within 1 % of each other; none split: the
 // vector-matrix product 485 -> 594 us, the pipeline 3082 -> 3109; all split: 3912, two Matmuls 2001 -> 3196, packed layouts 2397 -> 2922.
-// Without layouts (four lanes) a split is never behind: all sizes to 64, 668 against 740 us of fill.  With parallel loops, three layouts,
-// sizes to 24 and 40 of which much fits: four at a time from 32,768 entries 802 and 1560 us, from 262,144 819 and 1583 (a lane each instead of four at a time, from 262,144: 998 and 1966).
+// Without layouts (four lanes) a Matmul's split is never behind: all sizes to 64, 668 against 740 us of fill; where m and n alone are tiled and the
+// bufferize is one lane's, it is: fused, sizes to 40 and 48, alone, all split 2098 and 3131 us, the line at 131,072 entries 1953 and 2923; at 32,768 the
+// same, but the pipeline's sizes to 256 1236 -> 1269.  With parallel loops, three layouts, sizes to 24 and 40 of which much fits: four at a time from 32,768
+// entries 802 and 1560 us, from 262,144 819 and 1583 (a lane each instead of four at a time, from 262,144: 998 and 1966).
 template <bool LAY, bool MOVES, bool SMALL, bool PAR, bool MN>
 static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run, hipStream_t stream) {
   const uint32_t n = run.start[1] - run.start[0];
@@ -2249,10 +2265,10 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
   const uint2* units = list + run.start[0];
   const auto blocks = [](uint64_t lanes) { return dim3((uint32_t)((lanes + 255) / 256)); };
   if (run.chain) hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_chain_kernel<LAY, MOVES, SMALL, PAR, MN>), dim3(1), dim3(kChainThreads), 0, stream, A, list, run);
-  else if (!LAY || tasks <= kSplitTasks)
+  else if ((!LAY && !MN) || tasks <= (LAY ? kSplitTasks : kBareSplitTasks))
     hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_split_kernel<LAY, MOVES, SMALL, PAR, MN>), blocks(tasks << A.lg_split), dim3(256), 0, stream, A, units, n);
-  else if constexpr (LAY) {
-    if constexpr (!MOVES)
+  else if constexpr (LAY || MN) {
+    if constexpr (LAY && !MOVES)
       if (!A.ndt && A.unit_lay >= 2) {
         hipLaunchKernelGGL(HIP_KERNEL_NAME(fill_quad_kernel<SMALL, PAR, MN>), blocks(tasks), dim3(256), 0, stream, A, units, n);
         return;
