@@ -1371,7 +1371,8 @@ int32_t solve_impl(const mrl_target* t, const mrl_lattice_desc* lat, const mrl_t
     if (run.n) launch_fill_diagonals(fill, P, base + f.list, run, st);
     run.n = 0;
   };
-  const bool by_shapes = diag[n_diag] >= shapes_from;
+  const uint64_t more_windows = diag[n_diag] ? (diag[n_diag] - 1) / window : 0;
+  const bool by_shapes = shapes_from != UINT64_MAX && diag[n_diag] + more_windows * units_for_a_launch(P) >= shapes_from;
   for (uint32_t l = 0; by_shapes && l < n_lev; l++) launch_fill_shapes(fill, P, plan.masks, c.level_off[l], c.level_off[l + 1] - c.level_off[l], st);
   for (uint32_t d = 0; !by_shapes && d < n_diag; d++)
     for (uint32_t u = diag[d]; u < diag[d + 1];) {

@@ -85,6 +85,7 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
 constexpr uint32_t kRunMost = 63, kChainThreads = 1024, kSplitTasks = 32768, kBareSplitTasks = 131072;
 struct DiagRun { uint32_t n, chain, start[kRunMost + 1]; };
 uint64_t by_shapes_from(const DevParams& h, uint32_t n_shapes, uint32_t n_levels);      // units
+uint32_t units_for_a_launch(const DevParams& h);
 void launch_fill_shapes(const FillArgs& A, const DevParams& h, const unsigned long long* masks, uint32_t first, uint32_t n, hipStream_t stream);
 bool small_diagonal(const FillArgs& A, uint32_t n_units);
 uint32_t most_units(const FillArgs& A);            // that one launch takes

@@ -2277,20 +2277,27 @@ static void launch_run(const FillArgs& A, const uint2* list, const DiagRun& run,
   }
 }
 
-// From how many units on the levels of shapes are filled at once (fill_shapes_kernel) instead of by diagonals.  A launch of a level
-// takes some 25 us, through tiles and ranks, a small diagonal 6; in return a unit is 75 ps shorter (parallel loops: 85 to 330, since a
-// lane takes their entries one by one), for the groups of a shape and of its tiles are read once, not once for each rank.  And a unit that is
-// not there is a lane that idles.  Everything fits, by diagonals and by levels: a Matmul of all sizes to 36 (3.0 M units) 733 and 747 us, to 40
-// (4.1 M) 834 and 785, to 64 2466 and 1447; with parallel loops and three layouts, sizes to 24 (0.9 M) 1512 and 1419, to 32 2982 and 2479;
-// two Matmuls composed of sizes to 7 (2.5 M) 766 and 657.  17 % of the level assignments fit: all sizes to 64 1038 and 1303; 36 %: 1316 and 1346,
-// 42 %: 1426 and 1361; two Matmuls 48 %: 3022 and 2442; fused 32 %: 2223 and 2059, 16 %: 2477 and 2729.
+// From how many units on the levels of shapes are filled at once (fill_shapes_kernel) instead of by diagonals.  A launch of a level takes some 25 us, through
+// tiles and ranks, a small diagonal 6; a place of a shape that does not fit is a lane that idles; in return a unit is shorter, for the groups of a shape
+// and of its tiles are read once, not once for each rank.  So: as many as units_for_a_launch for each level, and a part of all places: a larger one the more layouts, which
+// the diagonals take four at a time (fill_quad_kernel) and the levels one by one.  Both fitted to ten tables and more of each form, of three sizes, of
+// which 10 to 100 % fits; solve alone, by diagonals and by levels, in us, on either side of the line.  A Matmul of all sizes to 56: 48 % 1096 and 1042, 30 % 922 and 1012; to
+// 80: 30 % 2674 and 2528, 17 % 1944 and 2164; to 36, everything: 685 and 735.  One layout, to 56: 1509 and 1424, 1168 and 1288; two: 70 % 2585 and
+// 2320, 48 % 2031 and 2144; three: everything 5328 and 4505, 70 % 4137 and 4244, to 80, 30 % 12267 and 14227.  A dtype bit, to 60: 35 % 1418 and
+// 1240, 18 % 989 and 1115.  Parallel loops, to 60: 44 % 1573 and 1447, 27 % 1229 and 1393; three layouts, to 44: 85 % 3048 and 2915, 63 % 2412 and 2642.
+// Fused, to 40: 38 % 3316 and 2995, 15 % 1866 and 2269; two Matmuls composed, to 6, everything 414 and 389, to 4 332 and 347; bias add, ReLU and the two, to 255,
+// everything 2087 and 1870, to 160 1345 and 1559.
 // (Move Specs' prices are a table of their own, and fused Specs with layouts have more cells than a workgroup takes.)
+// Where the scratch holds a part of the work list at a time, every further part is a launch between two others, 14 to 24 us (alone, bias add and
+// ReLU, to 255, 5 dependency levels: ample scratch 914 us, 64 parts 2451, by levels 761): it counts as a level does.
+uint32_t units_for_a_launch(const DevParams& h) {
+  return h.chain ? 200000 : h.npass > 1 ? 340000 : h.kind != kKindM ? 150000 : h.ndt ? 220000 : h.par ? (h.nlay ? 110000 : 160000) : h.nlay ? 150000 : 190000;
+}
 uint64_t by_shapes_from(const DevParams& h, uint32_t n_shapes, uint32_t n_levels) {
   if (h.moves || (h.nlay && h.kind != kKindM) || h.G > kShapeCells || h.G <= (h.nlay ? 64u : 32u)) return UINT64_MAX;
-  const uint64_t level_assignments = ((uint64_t)n_shapes * h.npass * h.ncombo) << h.ndt;
-  const uint64_t levels_us = (h.kind == kKindM ? 26 : 22) * n_levels, diagonals_us = 6 * (n_levels + h.nranks - 1), unit_ps = !h.par ? 75 : h.nlay < 2 ? 85 : h.nlay == 2 ? 200 : 330;
-  const uint64_t worth = levels_us > diagonals_us ? (levels_us - diagonals_us) * 1000000 / unit_ps : 0;
-  return std::max({kShapeUnits, worth, level_assignments * 3 / 10});
+  const uint64_t places = ((uint64_t)n_shapes * h.npass * h.ncombo) << h.ndt;
+  const uint64_t percent = h.kind != kKindM ? 22 : h.nlay == 0 ? 16 : h.nlay == 1 ? 19 : h.nlay == 2 ? 33 : 50;
+  return std::max(kShapeUnits, (uint64_t)units_for_a_launch(h) * n_levels + places * percent / 100);
 }
 void launch_fill_shapes(const FillArgs& A, const DevParams& h, const unsigned long long* masks, uint32_t first, uint32_t n, hipStream_t stream) {
   uint32_t lg_cells = 0, lg_lanes = 0, most = 0;

@@ -192,9 +192,9 @@ if name == "sparse":
 target = B.Target(cfg["target"])
 levels = 19 if name == "sparse" else 13
 diagonals = levels + (4 if name == "few-levels" else 10) - 1
-# what launches take longer, at 75 ps a level assignment; 2^20; and three tenths of all level assignments
-line = {"none": max(1 << 20, (26 * 13 - 6 * 22) * 1000000 // 75), "layouts": (26 * 13 - 6 * 22) * 1000000 // 75, "sparse": 96 ** 3 * 64 * 3 // 10, "few-levels": 1 << 40}[name]
-for units, at_once in ((line // diagonals, False), (-(-line // diagonals) if line < 1 << 32 else 1 << 22, line < 1 << 32)):
+# so many for each level, and a part of all places, the larger the more layouts there are
+line = {"none": 190000 * 13 + 24 ** 3 * 64 * 16 // 100, "layouts": 150000 * 13 + 24 ** 3 * 64 * 50 // 100, "sparse": 190000 * 19 + 96 ** 3 * 64 * 16 // 100, "few-levels": 1 << 40}[name]
+for units, at_once in (((line - 1) // diagonals, False), (-(-line // diagonals) if line < 1 << 32 else 1 << 22, line < 1 << 32)):
     hip.fake_units(units)
     for part in (b"fill_shapes", b"fill_split", b"fill_quad", b"fill_entry"):
         hip.fake_launches_of(part)
@@ -207,12 +207,13 @@ print("done")
 """
 
 WINDOWS = MORE + r"""
-# all sizes to 40, 64 level assignments a shape: 4 million units in 27 diagonals, of which the least scratch holds a part at a time
+# all sizes to 40, two memory levels, 8 level assignments a shape: half a million units in 19 diagonals, of which the least scratch holds a part at a time
 hip.fake_blocks_of.restype = C.c_uint64
-cfg = W.config(2, max_size=40)
+cfg = W.config(1)
+cfg["lattices"][0][1]["sizes"][1:] = [list(range(1, 41))] * 3
 target, lat = B.Target(cfg["target"]), cfg["lattices"][0][1]
 least = least_scratch(target, lat)
-hip.fake_units(100000)
+hip.fake_units(28000)
 
 def listed(scratch_bytes):
     for part in (b"list_units", b"fill_split"):
@@ -222,10 +223,22 @@ def listed(scratch_bytes):
     return hip.fake_launches_of(b"list_units"), hip.fake_blocks_of(b"list_units"), hip.fake_launches_of(b"fill_split")
 
 once, blocks, pieces = listed(64 << 20)
-assert (once, pieces) == (1, 25) and blocks > 1000
+assert (once, pieces) == (1, 19) and blocks > 500, (once, pieces, blocks)
 windows, more, parts = listed(least)
-assert windows > 3 and parts >= 25
-assert more < windows * blocks / 4, (windows, blocks, more)          # a window's levels and ranks, not all of them again
+assert windows > 3 and parts >= 19
+assert more < windows * blocks / 2, (windows, blocks, more)          # a window's levels and ranks, not all of them again
+
+# four memory levels, of which a shape has cells enough: in two parts, and by levels of shapes where there would be more parts than those are launches
+cfg = W.config(2, max_size=40)
+target, lat = B.Target(cfg["target"]), cfg["lattices"][0][1]
+least = least_scratch(target, lat)
+for scratch_bytes, want in ((64 << 20, (1, 0)), (least + 8 * 60000 * 25, (2, 0)), (least, (1, 16))):
+    hip.fake_units(100000)
+    for part in (b"list_units", b"fill_shapes"):
+        hip.fake_launches_of(part)
+    solve(target, lat, scratch_bytes)
+    lists, levels = (hip.fake_launches_of(part) for part in (b"list_units", b"fill_shapes"))
+    assert (lists, levels) == want, (scratch_bytes, lists, levels)
 print("done")
 """
 
@@ -276,7 +289,7 @@ def test_diagonals_of_more_entries_than_a_launch_has_threads_for(case, tmp_path)
 
 @pytest.mark.parametrize("case", ["none", "layouts", "sparse", "few-levels"])
 def test_tables_of_which_much_fits_are_filled_by_levels_of_shapes(case, tmp_path):
-    """From as many level assignments as pay for a launch a level, if three tenths of all are there, and if a shape has cells enough."""
+    """From as many level assignments as pay for a launch a level and for the places of those that are not there, and if a shape has cells enough."""
     run_on_fake_hip(tmp_path, LEVELS, case)
 
 
