@@ -120,7 +120,6 @@ struct Compiled {
   uint64_t n_specs;
   std::vector<uint8_t> mk_entry;          // [256][V]
   std::vector<uint32_t> qdec;             // [Q] the axes of every bound vector, a byte each
-  uint32_t max_task;                      // entries of one unit = ncombo * V
   int lay_axis[5], dt_axis[5];            // coordinate axis of the operand's bit, -1 if none
   mrl_target_desc target;
   mrl_lattice_desc lat;                   // sizes pointers re-pointed to this->sizes
@@ -622,8 +621,6 @@ int32_t compile(const mrl_target_desc& T, const mrl_lattice_desc* L, Compiled& c
     for (int a = (int)nd - 1; a >= lay0 + n_lay_axes; a--) c.merge_order[q++] = (uint32_t)a;
   }
 
-  c.max_task = P.ncombo * P.V;
-  if (c.max_task > 4096) return fail(MRL_E_INVAL, "too many entries per shape and intermediate level (%u > 4096)", c.max_task);
   return MRL_OK;
 }
 

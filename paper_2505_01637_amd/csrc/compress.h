@@ -71,7 +71,7 @@ struct FillArgs {
   Counters* ctr;
   const uint64_t *costM, *costE;
   const uint8_t* mk_entry;
-  uint32_t nops, NL, G, log2V, ndt, unit_lay, tile_dims;       // tile_dims: bit d = dimension d has tiles
+  uint32_t nops, NL, G, log2V, ndt, unit_lay;
   uint32_t mstride[4], pack_shift[4], lay_bit[4];
   uint32_t lay_xor[4], cv_bit[4];                              // layout bit of an operand's entry, dtype bit that a converting Move clears (0: none)
   uint32_t convert, s, sync, move_base, buf_id, par_shift;

@@ -8,8 +8,9 @@
 // intermediate's level of a fused Spec; other kinds have one value): a set of
 // entries closed under Moves.  A plan kernel decides, for every item and every
 // value of the dtype bits, which level assignments fit their levels (most do
-// not), as one bit mask per item in rank order (rank = sum of the operand
-// levels), and sets the whole table to (INF, NONE).  A Move lowers the rank
+// not), as one bit mask per item (bit = level assignment in table order).  The
+// whole table is set to (INF, NONE) by a launch of its own, beside the plan in
+// large tables.  The rank is the sum of the operand levels.  A Move lowers the rank
 // within an item, and a tile goes to the same level assignment of a shape of a
 // lower dependency level, so the entries of one diagonal, level + rank, depend
 // on earlier diagonals only.  The admissible level assignments are listed by
@@ -2185,8 +2186,8 @@ uint32_t unit_blocks(const uint32_t* level_off, uint32_t n_levels, uint32_t npas
   if (blk_off) blk_off[n_levels] = n;
   return n;
 }
-// (a level of 2^27 items, 2^28 with Move Specs less, has always been refused; a launch has fewer than 2^32 threads,
-// and the plan's has four per shape)
+// (Refused: a level of 2^28 items and more, with Move Specs 2^27, and 2^30 shapes.  The plan takes a lane per item, in blocks of eight; the scan a workgroup
+// per level and rank, in whose last one a lane of a wave is a diagonal.)
 bool plan_fits(const DevParams& h, uint32_t n_shapes, const uint32_t* level_off, uint32_t n_levels) {
   if (n_shapes >= (1u << 30) - 64u || n_levels > kMaxLevels - kMaxRanks + 1) return false;
   for (uint32_t l = 0; l < n_levels; l++)
@@ -2240,7 +2241,6 @@ FillArgs fill_args(const DevParams* d_P, const DevParams& h, const PlanBuffers& 
     A.lay_xor[i] = i < h.nops && h.lay_bit[i] != kNoBit ? 1u << h.lay_bit[i] : 0u;
     A.cv_bit[i] = i < h.nops && h.can_convert[i] && h.dt_bit[i] != kNoBit ? 1u << h.dt_bit[i] : 0u;
     A.zero[i] = h.zero[i];
-    A.tile_dims |= h.tile_dim_ok[i] && h.nsz[i] > 1 ? 1u << i : 0u;
   }
   A.unit_lay = h.unit_lay; A.lg_split = lg_split_lanes(h.moves || h.nlay); A.convert = h.convert; A.s = h.s; A.sync = h.sync;
   A.move_base = h.move_base; A.buf_id = h.buf_id; A.par_shift = h.par_base - h.tile_base;
