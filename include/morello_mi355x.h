@@ -275,7 +275,10 @@ typedef struct {
   uint32_t n_levels_run;                      /* dependency levels of shapes                   */
   float fill_ms, compress_ms;                 /* device time, HIP events on the given stream   */
   uint64_t n_decision_boxes, n_cost_boxes;
-  uint64_t scratch_used;                      /* bytes of d_scratch actually needed            */
+  uint64_t scratch_used;                      /* bytes of d_scratch actually needed.  The fill's list
+                                                 of 8 bytes per admissible level assignment takes
+                                                 what is left of the buffer; where that is not
+                                                 enough, it is made in parts, some 20 us each  */
   float prefill_ms;                           /* the part of fill_ms before the first dependency
                                                  level: work lists and the (MRL_INF, MRL_NONE)
                                                  written over the whole table; 0 for BOUNDED kinds */

@@ -27,12 +27,14 @@
 // ids where it compares the cost alone, all else is compared by (cost, id).
 // Nothing is reduced across workgroups: the table is deterministic.
 //
+// Large tables of which much fits are not filled by diagonals but a dependency
+// level of shapes at a time (fill_shapes_kernel).
 // Against the form it replaces (bundles of items in LDS, rank by rank with a
 // barrier each, a launch per dependency level; 1,900 to 3,250 vector
 // lane-instructions per entry), whole solves: two Matmuls composed 2742 ->
-// 1993 us (16.8 M entries; G's fill 1.34 -> 0.79 ms), the vector-matrix product
-// 668 -> 464, batched layouts 1061 -> 783, packed layouts 3058 -> 2424, the
-// pipeline 3728 -> 3049.
+// 1960 us (16.8 M entries; G's fill 1.34 -> 0.79 ms), the vector-matrix product
+// 668 -> 437, batched layouts 1061 -> 751, packed layouts 3058 -> 2404, the
+// pipeline 3728 -> 3040.
 #include <string.h>
 #include <algorithm>
 #include <hip/hip_runtime.h>
@@ -473,7 +475,9 @@ __global__ __launch_bounds__(256) void fit_map_kernel(const DevParams* __restric
       map[i] = out;
       return;
     }
-    if (npass == 4 && !log2V) {                // four levels of the intermediate: 16 level assignments of one shape (256 to a shape), whose bits lie four apart
+    // Four levels of the intermediate: 16 level assignments of one shape (256 to a shape), whose bits lie four apart.  (Cell by cell, as below: 93 us at
+    // 113 M Specs, beside the fill, which it held up; now 11.)
+    if (npass == 4 && !log2V) {
       const unsigned long long* mp = masks + (size_t)shape * 4u * nw + (off >> 8);
 #pragma unroll
       for (uint32_t p = 0; p < 4; p++) {

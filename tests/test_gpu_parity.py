@@ -369,6 +369,8 @@ def test_parity_parallel_loops_with_layout_and_dtype_bits():
     assert e.value.code == B.E_INVAL
 
 
+# (Written for items that were filled in bundles.  What the sizes reach now: planes of dtype bits, masks of two words, levels of many blocks of
+# items and of one.)
 @pytest.mark.parametrize("case", ["two-levels-40-sizes", "three-levels-dtypes", "fused-three-levels", "one-item-per-level"])
 def test_parity_bundles_of_items(case):
     """Level assignments of 8, 27 x 4 dtypes and 81, several items per workgroup, dependency levels
@@ -622,6 +624,7 @@ def test_work_list_in_windows_of_other_kinds(case):
         assert [tab.boxes(w).tobytes() for w in (0, 1)] == [got[label].boxes(w).tobytes() for w in (0, 1)]
 
 
+# (Written for stretches of 24 and 64 tiles.  What is fetched together now is 8, 16 or 32 tiles: test_parity_tiles_around_what_is_fetched_together.)
 @pytest.mark.parametrize("case", ["fused-29-tiles", "fused-layouts-42-tiles", "fused-wide-items-76-tiles", "split-42-tiles", "composition-31-tiles"])
 def test_parity_bufferize_beside_many_tiles(case):
     """More tile rewrites than a workgroup holds at a time (24 per item of a bundle, 64 of a wide
