@@ -503,7 +503,7 @@ def test_parity_tiles_around_what_is_fetched_together(case, tiles):
     compare_config(cfg, boxes=False)
 
 
-@pytest.mark.parametrize("case", ["none", "none-dear", "batched", "half", "dtypes", "dtypes-dear", "three-levels-dtypes", "layouts", "layouts-dear", "layouts-and-a-dtype",
+@pytest.mark.parametrize("case", ["none", "none-dear", "batched", "half", "dtypes", "dtypes-dear", "three-levels-dtypes", "two-levels-layouts-dtypes", "layouts", "layouts-dear", "layouts-and-a-dtype",
                                   "parallel", "parallel-dear", "parallel-layouts", "parallel-dtypes", "fused", "fused-dear", "fused-three-levels", "composition", "split"])
 def test_parity_levels_of_shapes(case):
     """Tables of which much fits, of more level assignments than are filled by diagonals: groups of 64 to 1024 cells, whole and not a power of two,
@@ -515,6 +515,8 @@ def test_parity_levels_of_shapes(case):
     t["capacity_bytes"] = [2048, 4096, 1 << 14, W.UNBOUNDED] if kind == "half" else [W.UNBOUNDED] * 4
     if "three-levels" in case:
         t["n_levels"], t["capacity_bytes"] = 3, [8000, 100000, W.UNBOUNDED, 0]
+    elif kind == "two":
+        t["n_levels"], t["capacity_bytes"] = 2, [60000, W.UNBOUNDED, 0, 0]
     if dear:
         for src in range(1, 4):
             for dst in range(src):
@@ -523,7 +525,7 @@ def test_parity_levels_of_shapes(case):
                     t["store_coef"][dst][src][x] += (1 << 30) + dst
     prime = [q for q in range(2, 1000) if all(q % d for d in range(2, q))]
     r = sorted([1] + prime + [p * q for p in prime for q in prime if p <= q and p * q < 1000])         # (three levels along a dimension at most)
-    n_sizes = {"dtypes": 21, "three": 27, "composition": 8, "fused": 25 if "three" in case else 16, "batched": 23, "half": 42, "parallel": 29, "layouts": 27 if "dtype" in case else 30}.get(kind, 31)
+    n_sizes = {"dtypes": 21, "three": 27, "two": 37, "composition": 8, "fused": 25 if "three" in case else 16, "batched": 23, "half": 42, "parallel": 29, "layouts": 27 if "dtype" in case else 30}.get(kind, 31)
     for label, lat, _ in cfg["lattices"]:
         lat["layout_coord"] = [0] * 5
         lat["sizes"] = [[1]] + [r[:n_sizes]] * 3 if lat["kind"] != W.KIND_BIAS_ADD_RELU else [[1], r[:n_sizes], [1], r[:n_sizes]]
@@ -536,6 +538,8 @@ def test_parity_levels_of_shapes(case):
             lat["sizes"][1] = lat["sizes"][2] = ([1] + prime)[:n_sizes]
         elif "layouts" in case:
             lat["layout_coord"] = [0, 1, 1, 0, 0]
+            if kind == "two":
+                lat["sizes"] = [[1]] + [([1] + prime)[:n_sizes]] * 3
         if "dtype" in case:
             lat["dtype_coord"] = [0, 1, 0, 0, 0] if case in ("layouts-and-a-dtype", "parallel-dtypes") else [1, 1, 0, 0, 0]
             lat["base_dtype_bytes"] = [2, 4, 4, 4, 4]
